@@ -62,6 +62,14 @@ struct GemmArgs {
   const void* ln_gamma; const void* ln_beta; void* ln_out; float ln_eps; int* ln_applied;
 };
 int launch_gemm(const GemmArgs& a, hipStream_t s);
+// Bytes from the first to one past the last element of a bf16 operand; rows x inner elements, row stride ld.
+static inline size_t operand_extent_bytes(int rows, int inner, int ld) { return 2 * ((size_t)(rows - 1) * ld + inner); }
+// Several weight gradients dW = dy^T x (a_mc, b_mc, out_f32; colsum_out and accumulate as in launch_gemm) in one launch, all with the
+// same fixed-order split-K scratch (that of the first problem).  force_tile: 0 = chosen from the shapes, 1.. = forced.
+constexpr int DW_GROUP_MAX = 16;
+int launch_gemm_dw_group(const GemmArgs* a, int n, int force_tile, hipStream_t s);
+size_t gemm_dw_group_ws_bytes(const GemmArgs* a, int n);
+bool gemm_dw_group_supported(const GemmArgs& a);
 // Index (as force_cfg - 1) of the tile configuration launch_gemm would choose for y = x W^T with M rows, contraction-contiguous bf16 operands.
 int gemm_choose_cfg(int M, int N, int K);
 bool gemm_geglu_fwd_supported(const GemmArgs& a);

@@ -13,6 +13,8 @@
 #include "dp_errors.h"
 #include "dp_ktime.h"
 #include "dp_gemm_epilogue.h"
+#include "dp_gemm_pp.h"
+#include "dp_host.h"
 
 #include <algorithm>
 #include <atomic>
@@ -36,8 +38,6 @@ struct GemmBf16Params {
   EpiParams<bf16> epi;
 };
 
-// Bytes from the first to one past the last element of an operand; rows x inner elements, row stride ld.
-static inline size_t operand_extent_bytes(int rows, int inner, int ld) { return 2 * ((size_t)(rows - 1) * ld + inner); }
 // The direct-to-LDS kernels need both operands below 4 GiB.
 static inline bool dtl_addressable(const GemmArgs& a) {
   const size_t ab = a.a_mc ? operand_extent_bytes(a.K, a.M, a.lda) : operand_extent_bytes(a.M, a.K, a.lda);
@@ -264,8 +264,6 @@ template <int BK> __device__ __forceinline__ int kc_key(int r) { return BK == 32
 // k-step (64 bytes instead of 32: two 16-byte chunks per lane) and the instruction, v_mfma_f32_32x32x64_f8f6f4 with both
 // block scales at 2^0.  Any assignment of the 64 bytes of a k-step to lanes and byte slots gives the right product as
 // long as it is the same for both operands, which it is by symmetry.
-typedef __attribute__((ext_vector_type(8))) int i32x8;
-
 template <int BM, int BN, int BK, int STAGES, int WGM, int WGN, bool A_MC, bool B_MC, bool FP8 = false>
 __global__ void __launch_bounds__(WGM * WGN * 64)
 gemm_bf16_dtl_kernel(const GemmBf16Params p) {
@@ -637,6 +635,64 @@ gemm_bf16_dtl16_kernel(const GemmBf16Params p) {
   }
 }
 
+// ------------------------------------------------------------------ bf16 / fp8 MFMA kernel, alternating wave groups
+// y = x W^T on contraction-contiguous operands with the main loop of dp_gemm_pp.h.  KTAIL: K is not a multiple of the k-tile;
+// chunks of the last k-tile past K are fetched from outside the buffers (zeros) in both operands.
+template <class T, int KIND, bool FP8, bool KTAIL>
+__global__ void __launch_bounds__(512, 2) gemm_pp_kernel(const GemmBf16Params p) {
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave / T::WGN, wn = wave % T::WGN;
+  int tile_m, tile_n;
+  tile_of_block(blockIdx.x, p.tiles_m, p.tiles_n, p.group_m, tile_m, tile_n);
+  const int m0 = tile_m * T::BM, n0 = tile_n * T::BN;
+  const int nk = (p.K + T::BK - 1) / T::BK;
+  constexpr uint32_t OUTSIDE = 0xFFFFFFF0u;
+  // rows past the edge are fetched from the last valid one: they only feed outputs that are never stored
+  uint32_t va[2][T::LA], vb0[T::LB0], vb1[T::LB1];
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int j = 0; j < T::LA; ++j) {
+      const int r = pp_piece_row(wave * T::LA + j, lane), c = pp_piece_chunk(r, lane);
+      va[h][j] = 2u * ((uint32_t)min(m0 + h * (T::BM / 2) + r, p.M - 1) * p.lda + c * 8);
+    }
+  auto piece_b = [&](int h, int j) { return min(wave * (h ? T::LB1 : T::LB0) + j, (h ? T::B1_BYTES : T::B0_BYTES) / 1024 - 1); };
+  auto offset_b = [&](int h, int j) {
+    const int r = pp_piece_row(piece_b(h, j), lane), c = pp_piece_chunk(r, lane);
+    const int row = KIND == PE_GEGLU1 ? h * p.epi.geglu_inner + min(n0 / 2 + r, p.epi.geglu_inner - 1) : min(n0 + h * T::BN0 + r, p.N - 1);
+    return 2u * ((uint32_t)row * p.ldb + c * 8);
+  };
+#pragma unroll
+  for (int j = 0; j < T::LB0; ++j) vb0[j] = offset_b(0, j);
+#pragma unroll
+  for (int j = 0; j < T::LB1; ++j) vb1[j] = offset_b(1, j);
+  const int k_last = p.K - (nk - 1) * T::BK;         // columns of the last k-tile
+  auto tail = [&](uint32_t v, int piece, int t) {
+    if (!KTAIL || t != nk - 1) return v;
+    const int r = pp_piece_row(piece, lane);
+    return pp_piece_chunk(r, lane) * 8 < k_last ? v : OUTSIDE;
+  };
+  typename T::acc_t acc[2][T::TM][T::TN];
+  float csum[2][T::TM];
+  pp_main_loop<T, FP8, false>(acc, smem_raw, nk, wm, wn, wave >= 4, lane,
+      [&](int h, int t, unsigned char* dst) {
+        const rsrc_t r = make_rsrc(p.A, t < nk ? p.a_bytes : 0u);
+        const uint32_t off = t < nk ? (uint32_t)t * (2u * T::BK) : 0u;
+#pragma unroll
+        for (int j = 0; j < T::LA; ++j) async_copy_16B_buf(r, tail(va[h][j], wave * T::LA + j, t), off, dst + (wave * T::LA + j) * 1024);
+      },
+      [&](auto hc, int t, unsigned char* dst) {
+        constexpr int h = decltype(hc)::value;
+        const rsrc_t r = make_rsrc(p.B, t < nk ? p.b_bytes : 0u);
+        const uint32_t off = t < nk ? (uint32_t)t * (2u * T::BK) : 0u;
+#pragma unroll
+        for (int j = 0; j < (h ? T::LB1 : T::LB0); ++j)
+          async_copy_16B_buf(r, tail(h ? vb1[h ? j : 0] : vb0[h ? 0 : j], piece_b(h, j), t), off, dst + piece_b(h, j) * 1024);
+      }, false, csum);
+  pp_epilogue<T, KIND>(acc, smem_raw, p.epi, m0, n0, wave, wm, wn, lane);
+}
+
 // ------------------------------------------------------------------ fp32 FMA kernel
 struct GemmF32Params {
   const float* A; const float* B;
@@ -755,6 +811,8 @@ static int choose_group_m(const GemmArgs& a, int tiles_m, int tiles_n) {
   return (int)std::max<long>(1, std::min<long>(g, tiles_m));
 }
 
+static int pp_kind(const GemmArgs& a);
+
 // Tile configurations of the bf16 kernel.
 struct TileCfg { int bm, bn, bk, waves; };
 static const TileCfg kCfgs[] = {
@@ -828,36 +886,34 @@ size_t gemm_epi_splitk_ws_bytes(int M, int N, int K) {
 //    direct-to-LDS tiles when they fill the CUs, else the register-staged kernel;
 //  - dW = dy^T x (both operands read through the transposing LDS load): register-staged 128x128 tiles,
 //    two workgroups per CU; 256x256 direct-to-LDS tiles for large M and N.
-static int choose_cfg(int M, int N, int K, bool a_mc, bool b_mc, bool dtl_ok, bool allow16 = true) {
+static int choose_cfg(int M, int N, int K, bool a_mc, bool b_mc, bool dtl_ok, bool pp_ok, bool allow16 = true) {
   const long t256x256 = (long)((M + 255) / 256) * ((N + 255) / 256);
   const long t256x128 = (long)((M + 255) / 256) * ((N + 127) / 128);
   const bool dtl32 = dtl_ok && K % 32 == 0, dtl64 = dtl_ok && K % 64 == 0;
+  pp_ok = pp_ok && dtl_ok;
   if (a_mc) return (dtl32 && b_mc && t256x256 >= 80) ? 6 : 0;
   if (!b_mc) {
-    // y = x W^T on contraction-contiguous operands: pick the direct-to-LDS tile with the least
-    // (rounds over the 256 CUs) x (tile area / measured relative efficiency).  The efficiencies were
-    // fitted on MI355X over the GEMM shapes of the five workloads: 256x256 tiles move the fewest LDS
-    // and L1 bytes per FLOP; 256x160 (16x16x32 MFMA tiles) exists for widths that leave the others
-    // with padded columns or a badly filled last round (N = 320, 1152, 2560).  A 192x128 tile for
-    // N = 640 (215 instead of 160 workgroups) won 5 % on bare GEMMs and lost 2 % inside the stage.
+    // y = x W^T on contraction-contiguous operands.
     // A few hundred rows and a short contraction (the frozen encoder's projections on a partial batch): 64x64 tiles give
     // 4x the workgroups of 128x128 ones, each with a quarter of the work per k-tile, and no split-K pass is needed.
     // Measured on the text encoder (samples/s at slices of 1 / 4 / 16): 1538 / 5617 / 19148 -> 1733 / 6490 / 20040; with more
     // 128x128 tiles than the limits below the larger tiles win again (16 samples, K = 3072: -6 % with 64x64 tiles).
     if (dtl64 && (long)((M + 127) / 128) * ((N + 127) / 128) <= (K <= 1024 ? 100 : 24)) return 15;
-    struct Cand { int idx, bm, bn; float eff; bool need64; };
-    // Two 256x128 workgroups per CU (configuration 12, three 32-deep buffers) hide each other's prologue,
-    // epilogue and barrier stalls: the shorter the contraction and the more tiles per CU, the more it pays.
-    const float eff12 = t256x128 <= kCUs ? 0.95f : (K <= 384 ? 1.6f : (K <= 768 ? 1.25f : (K <= 1536 ? 1.15f : 0.9f)));
-    const Cand cands[] = {{6, 256, 256, 1.27f, false}, {11, 256, 160, 1.01f, true}, {12, 256, 128, eff12, false},
-                          {9, 256, 128, 1.00f, true}, {13, 128, 128, 0.98f, true}, {8, 128, 128, 0.85f, false}};
+    // Otherwise the tile with the least estimated time: rounds over the 256 CUs x (fixed part of a tile + k-tiles x time of
+    // one), both in us, fitted on MI355X over projections of 1024..32768 rows, 320..5120 columns, contractions of
+    // 320..5120.  The alternating-group tiles hold one workgroup per CU; which of their widths wins is mostly a matter of how
+    // full the last round is (8192 x 4608: 576 tiles of 256x256 are 2.25 rounds, 768 of 256x192 exactly 3 shorter ones).
+    struct Cand { int idx, bm, bn; float fixed, per_kt; bool pp, need64; };
+    static const Cand cands[] = {{17, 256, 256, 5.0f, 1.30f, true, false}, {19, 256, 192, 5.0f, 1.05f, true, false}, {20, 256, 160, 5.5f, 0.99f, true, false},
+                                 {18, 256, 128, 5.0f, 0.72f, true, false}, {13, 128, 128, 4.0f, 0.45f, false, true}, {8, 128, 128, 4.0f, 0.55f, false, false},
+                                 {6, 256, 256, 5.0f, 1.70f, false, false}, {9, 256, 128, 5.0f, 0.85f, false, true}};
     int best = -1;
     float best_cost = 0.f;
     for (const Cand& c : cands) {
-      if (c.need64 ? !dtl64 : !dtl32) continue;
-      if (c.idx == 11 && !allow16) continue;       // the 16x16x32 instruction sums a k-step of 32 at once: other bits than the 32x32x16 tiles
+      if (c.pp ? !pp_ok : (c.need64 ? !dtl64 : !dtl32)) continue;
+      if (c.idx == 20 && !allow16) continue;       // the 16x16x32 instruction sums a k-step of 32 at once: other bits than the 32x32x16 tiles
       const long tiles = (long)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
-      const float cost = (float)((tiles + kCUs - 1) / kCUs) * (float)(c.bm * c.bn) / c.eff;
+      const float cost = (float)((tiles + kCUs - 1) / kCUs) * (c.fixed + (float)((K + 63) / 64) * c.per_kt);
       if (best < 0 || cost < best_cost) { best = c.idx; best_cost = cost; }
     }
     if (best >= 0) return best;
@@ -1068,6 +1124,66 @@ static int launch_dtl16(const GemmArgs& a, hipStream_t s) {
   return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "gemm launch failed");
 }
 
+// Epilogue kind of a problem for the kernels with one epilogue per kind, or -1 if it combines what no kind combines.
+static int pp_kind(const GemmArgs& a) {
+  if (a.geglu) return a.geglu == 1 ? PE_GEGLU1 : PE_GEGLU2;
+  if (a.residual) {
+    if (!a.residual_f32 || a.act || a.dact_pre || (a.pre_out && !a.gate)) return -1;
+    return a.gate ? PE_GATE : PE_RES;
+  }
+  if (a.gate || a.out_fused_f32) return -1;
+  if (a.act) return a.dact_pre || a.act > 3 ? -1 : PE_ACT1 + a.act - 1;
+  if (a.pre_out) return -1;
+  if (a.dact_pre) return a.dact_kind == ACT_GELU_ERF ? PE_DACT1 : (a.dact_kind == ACT_GELU_TANH ? PE_DACT2 : -1);
+  return PE_PLAIN;
+}
+
+static int set_lds_limit(const void* kern, size_t bytes, std::atomic<bool>& done) {
+  if (done.load(std::memory_order_acquire)) return DP_OK;     // setting it twice is harmless; the flag only saves the call
+  if (hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) != hipSuccess) return set_error(DP_EHIP, "hipFuncSetAttribute(gemm) failed");
+  done.store(true, std::memory_order_release);
+  return DP_OK;
+}
+
+template <class T, int KIND, bool FP8, bool KTAIL>
+static int launch_pp_kernel(const GemmBf16Params& p, hipStream_t s) {
+  auto kern = gemm_pp_kernel<T, KIND, FP8, KTAIL>;
+  static std::atomic<bool> attr_set{false};
+  DP_TRY(set_lds_limit((const void*)kern, T::BYTES, attr_set));
+  hipLaunchKernelGGL(kern, dim3(p.tiles_m * p.tiles_n), dim3(512), T::BYTES, s, p);
+  return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "gemm launch failed");
+}
+template <class T, int KIND>
+static int launch_pp_kind(const GemmBf16Params& p, hipStream_t s) {
+  return p.K % T::BK ? launch_pp_kernel<T, KIND, false, true>(p, s) : launch_pp_kernel<T, KIND, false, false>(p, s);
+}
+
+template <class T>
+static int launch_pp(const GemmArgs& a, hipStream_t s) {
+  if (a.a_mc || a.b_mc || a.out_f32) return set_error(DP_EUNSUPPORTED, "gemm: the forced configuration needs contraction-contiguous operands and a storage-dtype output");
+  if (!dtl_addressable(a)) return set_error(DP_EUNSUPPORTED, "gemm: operand too large for the forced direct-to-LDS configuration");
+  const int kind = pp_kind(a);
+  if (kind < 0) return set_error(DP_EUNSUPPORTED, "gemm: the forced configuration does not have this epilogue");
+  GemmBf16Params p;
+  p.A = (const bf16*)a.A; p.B = (const bf16*)a.B;
+  p.M = a.M; p.N = a.N; p.K = a.K; p.lda = a.lda; p.ldb = a.ldb; p.split_major = 0;
+  p.epi = make_epi<bf16>(a);
+  p.tiles_m = (a.M + T::BM - 1) / T::BM; p.tiles_n = (a.N + T::BN - 1) / T::BN;
+  p.group_m = choose_group_m(a, p.tiles_m, p.tiles_n);
+  p.a_bytes = (uint32_t)operand_extent_bytes(a.M, a.K, a.lda);
+  p.b_bytes = (uint32_t)operand_extent_bytes(a.N, a.K, a.ldb);
+  KScope ks(KK_GEMM_NT, 2.0 * a.M * a.N * a.K, gemm_tensor_bytes(a), s, a.M, a.N, a.K);
+  switch (kind) {
+#define DP_PP_CASE(k_) case k_: return launch_pp_kind<T, k_>(p, s)
+    DP_PP_CASE(PE_PLAIN); DP_PP_CASE(PE_RES); DP_PP_CASE(PE_GATE); DP_PP_CASE(PE_ACT1); DP_PP_CASE(PE_ACT2);
+    DP_PP_CASE(PE_ACT3); DP_PP_CASE(PE_DACT1); DP_PP_CASE(PE_DACT2); DP_PP_CASE(PE_GEGLU2);
+#undef DP_PP_CASE
+    case PE_GEGLU1:
+      if constexpr (T::SN0 == T::SN1) return launch_pp_kind<T, PE_GEGLU1>(p, s);
+    default: return set_error(DP_EUNSUPPORTED, "gemm: epilogue kind");
+  }
+}
+
 template <int BM, int BN, int BK, int STAGES, int WGM, int WGN>
 static int launch_dtl_layout(const GemmArgs& a, hipStream_t s) {
   if (a.K % BK) return set_error(DP_EUNSUPPORTED, "gemm: K is not a multiple of the k-tile of the forced configuration");
@@ -1088,7 +1204,7 @@ static int launch_bf16_layout(const GemmArgs& a, hipStream_t s) {
 // The bias gradient can ride in a weight-gradient GEMM when that GEMM runs on the register-staged kernel.
 bool gemm_colsum_supported(const GemmArgs& a) {
   if (a.dtype != BF16 || !a.a_mc || !a.b_mc || !a.out_f32 || a.M % 8) return false;
-  const int cfg = (a.force_cfg > 0) ? a.force_cfg - 1 : choose_cfg(a.M, a.N, a.K, true, true, dtl_addressable(a));
+  const int cfg = (a.force_cfg > 0) ? a.force_cfg - 1 : choose_cfg(a.M, a.N, a.K, true, true, dtl_addressable(a), false);
   return cfg >= 0 && cfg <= 5;
 }
 
@@ -1097,7 +1213,7 @@ bool gemm_geglu_fwd_supported(const GemmArgs& a) {
          a.N == 2 * a.geglu_inner && a.ldo >= a.geglu_inner && (!a.pre_out || a.ld_pre >= a.N) && dtl_addressable(a);
 }
 
-int gemm_choose_cfg(int M, int N, int K) { return choose_cfg(M, N, K, false, false, true); }
+int gemm_choose_cfg(int M, int N, int K) { return choose_cfg(M, N, K, false, false, true, true); }
 
 int launch_gemm(const GemmArgs& a, hipStream_t s) {
   if (a.ln_applied) *a.ln_applied = 0;
@@ -1130,11 +1246,11 @@ int launch_gemm(const GemmArgs& a, hipStream_t s) {
           return set_error(DP_EINVAL, "gemm: bad fused GeGLU backward arguments");
       }
     }
-    int cfg = (a.force_cfg > 0 && a.force_cfg <= kNumCfgs + 11) ? a.force_cfg - 1 : choose_cfg(a.choice_rows > 0 ? a.choice_rows : a.M, a.N, a.K, a.a_mc != 0, a.b_mc != 0, dtl_addressable(a), a.choice_rows >= 0);
-    if (a.geglu == 1 && (cfg < 6 || cfg > 14 || cfg == 11)) {   // cfg 11 has no column permutation in its loader either
-      // the column permutation lives in the direct-to-LDS loader
+    int cfg = (a.force_cfg > 0 && a.force_cfg <= kNumCfgs + 18) ? a.force_cfg - 1 : choose_cfg(a.choice_rows > 0 ? a.choice_rows : a.M, a.N, a.K, a.a_mc != 0, a.b_mc != 0, dtl_addressable(a), !a.out_f32 && pp_kind(a) >= 0, a.choice_rows >= 0);
+    // the column permutation of the fused GeGLU lives in the direct-to-LDS loaders, and in tiles with equal column halves
+    if (a.geglu == 1 && (cfg < 6 || cfg == 11 || cfg == 15 || cfg == 16 || cfg > 18)) {
       const long t256x256 = (long)((a.M + 255) / 256) * ((a.N + 255) / 256);
-      cfg = t256x256 >= 128 ? 6 : 8;
+      cfg = t256x256 >= 128 ? 17 : 8;
     }
     switch (cfg) {
       case 1: return launch_bf16_layout<256, 128, 64, 4, 2>(a, s);
@@ -1157,6 +1273,11 @@ int launch_gemm(const GemmArgs& a, hipStream_t s) {
       case 16:
         if (a.a_mc || a.b_mc || a.K % 64) return set_error(DP_EUNSUPPORTED, "gemm: the forced 64-row configurations need contraction-contiguous operands and K % 64 == 0");
         return cfg == 15 ? launch_dtl_cfg<64, 64, 64, 3, 2, 2, false, false>(a, s) : launch_dtl_cfg<64, 128, 64, 3, 2, 2, false, false>(a, s);
+      case 17: return launch_pp<PpTile<256, 128, 128, 4, 2>>(a, s);
+      case 18: return launch_pp<PpTile<256, 64, 64, 4, 2>>(a, s);
+      case 19: return launch_pp<PpTile<256, 128, 64, 4, 2>>(a, s);
+      case 21: case 22: case 23: return launch_gemm_dw_group(&a, 1, cfg - 20, s);
+      case 20: return launch_pp<PpTile<256, 96, 64, 4, 2, 16>>(a, s);
       default: break;
     }
     return launch_bf16_layout<128, 128, 64, 2, 2>(a, s);
