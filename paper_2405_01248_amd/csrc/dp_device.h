@@ -4,6 +4,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 
 namespace dp {
 
@@ -73,6 +74,18 @@ __device__ __forceinline__ bf16x8 frag_from_mc_accorder(const bf16* tile, int ld
   bf16x4 lo = lds_read_tr(p);
   bf16x4 hi = lds_read_tr(p + 8 * ld);
   return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
+// The transposing LDS load as an instruction the compiler knows nothing about: for the builtin it cannot tell which
+// copies to LDS it depends on and waits for all of those in flight (vmcnt(0)) before every load, which undoes the pipeline.
+// The caller waits (lgkmcnt) and then passes the value through lds_arrived() before using it.
+template <int OFF> __device__ __forceinline__ void lds_read_tr_raw(u32x2& d, uint32_t addr) {
+  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(d) : "v"(addr), "n"(OFF) : "memory");
+}
+__device__ __forceinline__ void lds_arrived(u32x2& d) { asm volatile("" : "+v"(d)); }
+__device__ __forceinline__ uint32_t lds_address(const void* p) { return (uint32_t)(uintptr_t)(const DP_LDS unsigned char*)p; }
+template <int N, class F> __device__ __forceinline__ void static_for(F f) {
+  if constexpr (N > 0) { static_for<N - 1>(f); f(std::integral_constant<int, N - 1>{}); }
 }
 
 // Asynchronous global -> LDS copy: every lane fetches 16 bytes from its own global address and the

@@ -62,18 +62,6 @@ __device__ __forceinline__ uint32_t pp_mc_offset(int col0, int lane) {
   const int b = lane >> 4, j = lane & 15, k = 8 * (b >> 1) + (j >> 2), c = col0 / 8 + 2 * (b & 1) + ((j & 3) >> 1);
   return (uint32_t)(k * COLS + pp_mc_swz<COLS>(c, k) * 8 + 4 * (j & 1)) * 2u;
 }
-// The transposing LDS load as an instruction the compiler knows nothing about: for the builtin it cannot tell which
-// copies to LDS it depends on and waits for all of those in flight (vmcnt(0)) before every load, which undoes the pipeline.
-// The caller waits (lgkmcnt) and then passes the value through lds_arrived() before using it.
-template <int OFF> __device__ __forceinline__ void lds_read_tr_raw(u32x2& d, uint32_t addr) {
-  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(d) : "v"(addr), "n"(OFF) : "memory");
-}
-__device__ __forceinline__ void lds_arrived(u32x2& d) { asm volatile("" : "+v"(d)); }
-__device__ __forceinline__ uint32_t lds_address(const void* p) { return (uint32_t)(uintptr_t)(const DP_LDS unsigned char*)p; }
-template <int N, class F> __device__ __forceinline__ void static_for(F f) {
-  if constexpr (N > 0) { static_for<N - 1>(f); f(std::integral_constant<int, N - 1>{}); }
-}
-
 // copy_a(half, t, dst) / copy_b(half, t, dst): issue this wave's LA / LB0, LB1 copies of a half of k-tile t to dst (the
 // half's first byte in LDS).  t may be >= nk: then the copies have to be issued all the same (the waits count them), from
 // outside the buffers, so that they move nothing.
@@ -266,7 +254,7 @@ __device__ __forceinline__ void pp_main_loop(typename T::acc_t (&acc)[2][T::TM][
 // One kernel per kind: what a kind does not use is not compiled into it, so the loops can be unrolled and all
 // global operands of a 32-row slab (residual, saved pre-activation, gate) are requested before the first of them is
 // needed; in the rolled, all-purpose epilogue each 8-column group waits for its own operands in turn.
-enum PpEpi { PE_PLAIN = 0, PE_F32, PE_RES, PE_GATE, PE_ACT1, PE_ACT2, PE_ACT3, PE_DACT1, PE_DACT2, PE_GEGLU1, PE_GEGLU2, PE_COUNT };
+enum PpEpi { PE_PLAIN = 0, PE_F32, PE_RES, PE_RESH, PE_GATE, PE_ACT1, PE_ACT2, PE_ACT3, PE_DACT1, PE_DACT2, PE_GEGLU1, PE_GEGLU2, PE_COUNT };
 
 template <int KIND> struct PpIn { f32x4 r0, r1; bf16x8 a, b; };
 
@@ -283,6 +271,7 @@ __device__ __forceinline__ void pp_load(const EpiParams<bf16>& e, int m, int n, 
     const float* rp = (const float*)e.residual + (size_t)m * e.ld_res + n;
     in.r0 = *reinterpret_cast<const f32x4*>(rp); in.r1 = *reinterpret_cast<const f32x4*>(rp + 4);
   }
+  if constexpr (KIND == PE_RESH) in.a = *reinterpret_cast<const bf16x8*>((const bf16*)e.residual + (size_t)m * e.ld_res + n);
   if constexpr (KIND == PE_GATE) in.a = *reinterpret_cast<const bf16x8*>(e.gate + (size_t)(m / e.rows_per_batch) * e.gate_ld + n);
   if constexpr (KIND == PE_DACT1 || KIND == PE_DACT2) in.a = *reinterpret_cast<const bf16x8*>(e.dact_pre + (size_t)m * e.ld_dact + n);
   if constexpr (KIND == PE_GEGLU2) {
@@ -337,6 +326,7 @@ __device__ __forceinline__ void pp_finish(const EpiParams<bf16>& e, int m, int n
     if constexpr (KIND == PE_DACT1) v[t] *= gelu_erf_grad_f((float)in.a[t]);
     if constexpr (KIND == PE_DACT2) v[t] *= gelu_tanh_grad_f((float)in.a[t]);
     if constexpr (KIND == PE_GATE) v[t] *= (float)in.a[t];
+    if constexpr (KIND == PE_RESH) v[t] += (float)in.a[t];
     if constexpr (KIND == PE_RES || KIND == PE_GATE) v[t] += t < 4 ? in.r0[t & 3] : in.r1[t & 3];
   }
   if constexpr (KIND == PE_RES || KIND == PE_GATE) {

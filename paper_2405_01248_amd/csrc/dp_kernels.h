@@ -64,14 +64,14 @@ struct GemmArgs {
 int launch_gemm(const GemmArgs& a, hipStream_t s);
 // Bytes from the first to one past the last element of a bf16 operand; rows x inner elements, row stride ld.
 static inline size_t operand_extent_bytes(int rows, int inner, int ld) { return 2 * ((size_t)(rows - 1) * ld + inner); }
-// Several weight gradients dW = dy^T x (a_mc, b_mc, out_f32; colsum_out and accumulate as in launch_gemm) in one launch, all with the
-// same fixed-order split-K scratch (that of the first problem).  force_tile: 0 = chosen from the shapes, 1.. = forced.
-constexpr int DW_GROUP_MAX = 16;
-int launch_gemm_dw_group(const GemmArgs* a, int n, int force_tile, hipStream_t s);
-size_t gemm_dw_group_ws_bytes(const GemmArgs* a, int n);
+// Several weight gradients dW = dy^T x (a_mc, b_mc, out_f32; colsum_out and accumulate as in launch_gemm) in one launch, with
+// the fixed-order split-K scratch of the first problem.  The plan depends on the shapes (M, N, K) only; force_tile: 0 = chosen
+// from them, 1.. = forced; ws_limit: scratch it may use.
+constexpr int DW_GROUP_MAX = 16;      // one more than the problems of a launch
+struct DwGroupPlan { int tile, whole, splits; size_t ws_bytes; };
+DwGroupPlan gemm_dw_group_plan(const GemmArgs* a, int n, int force_tile, size_t ws_limit);
+int launch_gemm_dw_group(const GemmArgs* a, int n, const DwGroupPlan& plan, hipStream_t s);
 bool gemm_dw_group_supported(const GemmArgs& a);
-// Index (as force_cfg - 1) of the tile configuration launch_gemm would choose for y = x W^T with M rows, contraction-contiguous bf16 operands.
-int gemm_choose_cfg(int M, int N, int K);
 bool gemm_geglu_fwd_supported(const GemmArgs& a);
 bool gemm_colsum_supported(const GemmArgs& a);
 size_t gemm_splitk_ws_bytes(int M, int N, int K);   // upper bound for out_f32 GEMMs
@@ -188,7 +188,8 @@ struct LnBwdArgs {
   int defer_reduce;        // 1: only write the column partials; the caller runs launch_ln_bwd_reduce (maybe on another stream)
 };
 int launch_ln_bwd(const LnBwdArgs& a, hipStream_t s);
-int launch_ln_bwd_reduce(const LnBwdArgs& a, hipStream_t s);
+constexpr int LN_REDUCE_MAX = 4;
+int launch_ln_bwd_reduce(const LnBwdArgs* a, int n, hipStream_t s);
 size_t ln_bwd_partial_bytes(int rows, int d, int rows_per_batch);
 
 // g[m, j] = u[m, j] * gelu_erf(u[m, inner + j])
@@ -228,7 +229,7 @@ int launch_embed(int dtype, const int32_t* ids, const void* tok, const void* pos
 
 // dst[c, r] = src[r, c] for up to kTransposeMax dense row-major 16-bit matrices in one launch.
 // tile_start[i] is the number of 64 x 64 tiles of the matrices before matrix i (tile_start[n] = total).
-constexpr int kTransposeMax = 16;
+constexpr int kTransposeMax = 48;
 struct TransposeBatch {
   int n;
   const void* src[kTransposeMax]; void* dst[kTransposeMax];

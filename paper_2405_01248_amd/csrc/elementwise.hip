@@ -397,9 +397,13 @@ __global__ void __launch_bounds__(256) ln_bwd_kernel(int d, int rows_per_batch, 
 // its chunks in ascending order and the group sums are added in ascending order (fixed order).  Fewer columns
 // per workgroup mean more workgroups: the unbatched reduction of a narrow model (2d = 640 columns, 1024 chunks)
 // ran on 20 workgroups with 32 columns each and took 21 us; with 8 it runs on 80.
+// blockIdx.z: one of several LayerNorms of the same shape.
+struct LnReduceSet { const float* partial[LN_REDUCE_MAX]; float* out0[LN_REDUCE_MAX]; float* out1[LN_REDUCE_MAX]; };
 template <int COLS>
-__global__ void __launch_bounds__(1024) ln_bwd_reduce_kernel(const float* __restrict__ partial, int nchunk, int d, float* out0,
-                                                             float* out1, int ld, int accumulate) {
+__global__ void __launch_bounds__(1024) ln_bwd_reduce_kernel(const LnReduceSet set, int nchunk, int d, int ld, int accumulate) {
+  const float* __restrict__ partial = set.partial[blockIdx.z];
+  float* out0 = set.out0[blockIdx.z];
+  float* out1 = set.out1[blockIdx.z];
   constexpr int GROUPS = 1024 / COLS;
   __shared__ float red[GROUPS][COLS + 1];
   const int lc = threadIdx.x % COLS, grp = threadIdx.x / COLS;
@@ -464,23 +468,33 @@ int launch_ln_bwd(const LnBwdArgs& a, hipStream_t s) {
     e = a.dtype == BF16 ? ln_bwd_t<bf16>(a, rpb, nb, nchunk, partial, s) : ln_bwd_t<float>(a, rpb, nb, nchunk, partial, s);
   }
   if (e || !want_cols || a.defer_reduce) return e;
-  return launch_ln_bwd_reduce(a, s);
+  return launch_ln_bwd_reduce(&a, 1, s);
 }
 
-// Second half of launch_ln_bwd: fixed-order sum of the per-workgroup column partials into the parameter
-// (or modulation) gradients.  Separate so that a caller can put it on another stream (defer_reduce).
-int launch_ln_bwd_reduce(const LnBwdArgs& a, hipStream_t s) {
-  const bool modulated = a.scale != nullptr;
-  const int rpb = modulated ? a.rows_per_batch : a.rows;
-  if (rpb <= 0 || a.rows % rpb || !a.partial) return set_error(DP_EINVAL, "ln_bwd_reduce: bad arguments");
-  const int nb = a.rows / rpb, nchunk = (rpb + LNB_ROWS - 1) / LNB_ROWS;
-  KScope ks(KK_REDUCE, 0.0, (double)nb * nchunk * 2 * a.d * 4, s, nchunk, 2 * a.d);
+// Second half of launch_ln_bwd for n LayerNorms of the same shape: fixed-order sum of the per-workgroup column partials
+// into the parameter (or modulation) gradients.  Separate so that a caller can do it for a whole block at once (defer_reduce).
+int launch_ln_bwd_reduce(const LnBwdArgs* a, int n, hipStream_t s) {
+  if (n < 1 || n > LN_REDUCE_MAX) return set_error(DP_EINVAL, "ln_bwd_reduce: bad count");
+  const bool modulated = a[0].scale != nullptr;
+  const int d = a[0].d, rpb = modulated ? a[0].rows_per_batch : a[0].rows;
+  LnReduceSet set;
+  for (int i = 0; i < n; ++i) {
+    if (rpb <= 0 || a[i].rows % rpb || !a[i].partial) return set_error(DP_EINVAL, "ln_bwd_reduce: bad arguments");
+    if (a[i].rows != a[0].rows || a[i].d != d || (a[i].scale != nullptr) != modulated || (modulated && a[i].rows_per_batch != rpb) ||
+        a[i].dmod_ld != a[0].dmod_ld || a[i].accumulate != a[0].accumulate)
+      return set_error(DP_EINVAL, "ln_bwd_reduce: the LayerNorms differ in shape");
+    set.partial[i] = a[i].partial;
+    set.out0[i] = modulated ? a[i].dscale : a[i].dgamma;
+    set.out1[i] = modulated ? a[i].dshift : a[i].dbeta;
+  }
+  const int nb = a[0].rows / rpb, nchunk = (rpb + LNB_ROWS - 1) / LNB_ROWS;
+  KScope ks(KK_REDUCE, 0.0, (double)n * nb * nchunk * 2 * d * 4, s, nchunk, 2 * d);
   if (modulated)
-    hipLaunchKernelGGL(ln_bwd_reduce_kernel<32>, dim3((2 * a.d + 31) / 32, nb), dim3(1024), 0, s, a.partial, nchunk, a.d, a.dscale, a.dshift, a.dmod_ld, 0);
-  else if (2 * a.d <= 1024)
-    hipLaunchKernelGGL(ln_bwd_reduce_kernel<8>, dim3((2 * a.d + 7) / 8, 1), dim3(1024), 0, s, a.partial, nchunk, a.d, a.dgamma, a.dbeta, a.d, a.accumulate);
+    hipLaunchKernelGGL(ln_bwd_reduce_kernel<32>, dim3((2 * d + 31) / 32, nb, n), dim3(1024), 0, s, set, nchunk, d, a[0].dmod_ld, 0);
+  else if (2 * d <= 1024)
+    hipLaunchKernelGGL(ln_bwd_reduce_kernel<8>, dim3((2 * d + 7) / 8, 1, n), dim3(1024), 0, s, set, nchunk, d, d, a[0].accumulate);
   else
-    hipLaunchKernelGGL(ln_bwd_reduce_kernel<16>, dim3((2 * a.d + 15) / 16, 1), dim3(1024), 0, s, a.partial, nchunk, a.d, a.dgamma, a.dbeta, a.d, a.accumulate);
+    hipLaunchKernelGGL(ln_bwd_reduce_kernel<16>, dim3((2 * d + 15) / 16, 1, n), dim3(1024), 0, s, set, nchunk, d, d, a[0].accumulate);
   return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "ln_bwd_reduce launch failed");
 }
 

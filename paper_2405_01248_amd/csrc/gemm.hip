@@ -1128,7 +1128,8 @@ static int launch_dtl16(const GemmArgs& a, hipStream_t s) {
 static int pp_kind(const GemmArgs& a) {
   if (a.geglu) return a.geglu == 1 ? PE_GEGLU1 : PE_GEGLU2;
   if (a.residual) {
-    if (!a.residual_f32 || a.act || a.dact_pre || (a.pre_out && !a.gate)) return -1;
+    if (a.act || a.dact_pre || (a.pre_out && !a.gate)) return -1;
+    if (!a.residual_f32) return a.gate || a.out_fused_f32 ? -1 : PE_RESH;
     return a.gate ? PE_GATE : PE_RES;
   }
   if (a.gate || a.out_fused_f32) return -1;
@@ -1175,7 +1176,7 @@ static int launch_pp(const GemmArgs& a, hipStream_t s) {
   KScope ks(KK_GEMM_NT, 2.0 * a.M * a.N * a.K, gemm_tensor_bytes(a), s, a.M, a.N, a.K);
   switch (kind) {
 #define DP_PP_CASE(k_) case k_: return launch_pp_kind<T, k_>(p, s)
-    DP_PP_CASE(PE_PLAIN); DP_PP_CASE(PE_RES); DP_PP_CASE(PE_GATE); DP_PP_CASE(PE_ACT1); DP_PP_CASE(PE_ACT2);
+    DP_PP_CASE(PE_PLAIN); DP_PP_CASE(PE_RES); DP_PP_CASE(PE_RESH); DP_PP_CASE(PE_GATE); DP_PP_CASE(PE_ACT1); DP_PP_CASE(PE_ACT2);
     DP_PP_CASE(PE_ACT3); DP_PP_CASE(PE_DACT1); DP_PP_CASE(PE_DACT2); DP_PP_CASE(PE_GEGLU2);
 #undef DP_PP_CASE
     case PE_GEGLU1:
@@ -1213,8 +1214,6 @@ bool gemm_geglu_fwd_supported(const GemmArgs& a) {
          a.N == 2 * a.geglu_inner && a.ldo >= a.geglu_inner && (!a.pre_out || a.ld_pre >= a.N) && dtl_addressable(a);
 }
 
-int gemm_choose_cfg(int M, int N, int K) { return choose_cfg(M, N, K, false, false, true, true); }
-
 int launch_gemm(const GemmArgs& a, hipStream_t s) {
   if (a.ln_applied) *a.ln_applied = 0;
   if (a.M <= 0 || a.N <= 0 || a.K <= 0) return set_error(DP_EINVAL, "gemm: non-positive size");
@@ -1246,7 +1245,7 @@ int launch_gemm(const GemmArgs& a, hipStream_t s) {
           return set_error(DP_EINVAL, "gemm: bad fused GeGLU backward arguments");
       }
     }
-    int cfg = (a.force_cfg > 0 && a.force_cfg <= kNumCfgs + 18) ? a.force_cfg - 1 : choose_cfg(a.choice_rows > 0 ? a.choice_rows : a.M, a.N, a.K, a.a_mc != 0, a.b_mc != 0, dtl_addressable(a), !a.out_f32 && pp_kind(a) >= 0, a.choice_rows >= 0);
+    int cfg = (a.force_cfg > 0 && a.force_cfg <= kNumCfgs + 19) ? a.force_cfg - 1 : choose_cfg(a.choice_rows > 0 ? a.choice_rows : a.M, a.N, a.K, a.a_mc != 0, a.b_mc != 0, dtl_addressable(a), !a.out_f32 && pp_kind(a) >= 0, a.choice_rows >= 0);
     // the column permutation of the fused GeGLU lives in the direct-to-LDS loaders, and in tiles with equal column halves
     if (a.geglu == 1 && (cfg < 6 || cfg == 11 || cfg == 15 || cfg == 16 || cfg > 18)) {
       const long t256x256 = (long)((a.M + 255) / 256) * ((a.N + 255) / 256);
@@ -1276,7 +1275,8 @@ int launch_gemm(const GemmArgs& a, hipStream_t s) {
       case 17: return launch_pp<PpTile<256, 128, 128, 4, 2>>(a, s);
       case 18: return launch_pp<PpTile<256, 64, 64, 4, 2>>(a, s);
       case 19: return launch_pp<PpTile<256, 128, 64, 4, 2>>(a, s);
-      case 21: case 22: case 23: return launch_gemm_dw_group(&a, 1, cfg - 20, s);
+      case 21: case 22: case 23: case 24:
+        return launch_gemm_dw_group(&a, 1, gemm_dw_group_plan(&a, 1, cfg - 20, a.splitk_ws ? a.splitk_ws_bytes : 0), s);
       case 20: return launch_pp<PpTile<256, 96, 64, 4, 2, 16>>(a, s);
       default: break;
     }

@@ -38,14 +38,15 @@ __global__ void __launch_bounds__(512, 2) gemm_dw_group_kernel(const DwGroup grp
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave / T::WGN, wn = wave % T::WGN;
-  // every XCD takes a contiguous range of (problem, split, tile): neighbours share operand panels in its L2
-  const int id0 = xcd_contiguous_id(blockIdx.x, grp.total);
+  // The hardware deals workgroups round-robin to the 8 XCDs.  Inside each problem every XCD takes a contiguous range of
+  // (split, tile) -- neighbours share operand panels in its L2 -- and every XCD gets its share of each problem, so that the
+  // XCDs' queues are equally long whatever the problems' contractions are.
   int q = 0;
-  while (q + 1 < grp.n && id0 >= grp.p[q + 1].first) ++q;
+  while (q + 1 < grp.n && (int)blockIdx.x >= grp.p[q + 1].first) ++q;
   const DwProblem& p = grp.p[q];
-  const int tiles = p.tiles_m * p.tiles_n, split = (id0 - p.first) / tiles;
+  const int tiles = p.tiles_m * p.tiles_n, id = xcd_contiguous_id(blockIdx.x - p.first, tiles * p.splits), split = id / tiles;
   int tile_m, tile_n;
-  tile_of_id((id0 - p.first) % tiles, p.tiles_m, p.tiles_n, p.group_m, tile_m, tile_n);
+  tile_of_id(id % tiles, p.tiles_m, p.tiles_n, p.group_m, tile_m, tile_n);
   const int m0 = tile_m * T::BM, n0 = tile_n * T::BN, M = p.M, N = p.N, K = p.K, lda = p.lda, ldb = p.ldb;
   const int kt0 = split * p.kt_per_split, kt_all = (K + 63) / 64, nk = min(kt_all, kt0 + p.kt_per_split) - kt0;
   const int k_end = K - kt0 * 64;                       // contraction rows from this split's first one on
@@ -134,48 +135,90 @@ __global__ void __launch_bounds__(256) gemm_dw_reduce_kernel(const DwReduce r) {
 
 // ------------------------------------------------------------------ host side
 struct DwTile { int bm, bn; float us; };        // us: time of a k-tile with the chip full
-static const DwTile kDwTiles[] = {{256, 256, 1.5f}, {256, 128, 0.85f}, {128, 256, 0.85f}};
-constexpr int kDwTileCount = 3;
+static const DwTile kDwTiles[] = {{256, 256, 1.63f}, {256, 128, 1.06f}, {128, 256, 1.06f}, {256, 192, 1.33f}};
+constexpr int kDwTileCount = 4;
 
-struct DwPlan { int tile, kt_per_wg; size_t ws_bytes; };
+// A problem, or a range of output rows of one, as it is launched.
+struct DwPart { int problem, row0, rows, splits, kt_per_split; };
 
-static size_t dw_plan_eval(const GemmArgs* a, int n, int tile, int L, double& us) {
-  const DwTile& t = kDwTiles[tile];
-  long wgs = 0;
-  double bytes = 0;
-  size_t ws = 0;
-  int longest = 0;
+static int dw_tiles(const GemmArgs& a, const DwTile& t) { return ((a.M + t.bm - 1) / t.bm) * ((a.N + t.bn - 1) / t.bn); }
+
+// The parts of a plan in launch order: the problems with long contractions, their first `whole` tiles unsplit (to whole tile-rows)
+// and the rest split along the contraction; then the ones with short contractions, unsplit.  At most n + 1 of them.
+static int dw_parts(const GemmArgs* a, int n, const DwGroupPlan& plan, DwPart* out) {
+  const DwTile& t = kDwTiles[plan.tile];
+  int kt_max = 0, cnt = 0, left = plan.whole;
+  for (int i = 0; i < n; ++i) kt_max = std::max(kt_max, (a[i].K + 63) / 64);
+  auto add = [&](int i, int row0, int rows, int splits) {
+    const int kt = (a[i].K + 63) / 64, per = (kt + splits - 1) / splits;
+    if (rows > 0) out[cnt++] = {i, row0, rows, (kt + per - 1) / per, per};
+  };
   for (int i = 0; i < n; ++i) {
-    const long tiles = (long)((a[i].M + t.bm - 1) / t.bm) * ((a[i].N + t.bn - 1) / t.bn);
-    const int kt = (a[i].K + 63) / 64, splits = (kt + L - 1) / L;
-    wgs += tiles * splits;
-    longest = std::max(longest, (kt + splits - 1) / splits);
-    if (splits > 1) {
-      ws += ((size_t)splits * ((size_t)a[i].M * a[i].N + a[i].M) * sizeof(float) + 255) / 256 * 256;
-      bytes += 2.0 * splits * 4.0 * a[i].M * a[i].N;
-    }
+    if ((a[i].K + 63) / 64 * 2 < kt_max) continue;
+    const int tn = (a[i].N + t.bn - 1) / t.bn, tm = (a[i].M + t.bm - 1) / t.bm, rows = std::min(a[i].M, std::min(tm, left / tn) * t.bm);
+    if (rows < a[i].M && left > 0) left = 0; else left -= std::min(left, tm * tn);
+    add(i, 0, rows, 1);
+    add(i, rows, a[i].M - rows, plan.splits);
   }
-  const double per_wg = longest * t.us + 4.0;
-  us = (double)((wgs + 255) / 256) * per_wg + bytes / 4.0e6 + (ws ? 4.0 : 0.0);
-  return ws;
+  for (int i = 0; i < n; ++i)
+    if ((a[i].K + 63) / 64 * 2 < kt_max) add(i, 0, a[i].M, 1);
+  return cnt;
+}
+static size_t dw_part_ws_bytes(const GemmArgs& a, const DwPart& d) {
+  return d.splits > 1 ? ((size_t)d.splits * ((size_t)d.rows * a.N + d.rows) * sizeof(float) + 255) / 256 * 256 : 0;
 }
 
-// Tile and split: the pair with the least estimated time, (rounds of 256 workgroups) x (k-tiles per workgroup x time of a
-// k-tile + prologue and epilogue) + the partial sums' traffic.
-static DwPlan dw_plan(const GemmArgs* a, int n, int force_tile, size_t ws_limit) {
+// Estimated time: on each XCD its eighth of the workgroups, in launch order, on 32 CUs, each taking the one that is free first
+// (kept as groups of CUs that are free at the same time); then the traffic of the partial sums.
+static double dw_plan_us(const GemmArgs* a, const DwGroupPlan& plan, const DwPart* d, int n) {
+  const DwTile& t = kDwTiles[plan.tile];
+  struct Slots { double at; int count; } q[33];
+  int nq = 1;
+  q[0] = {0.0, 32};
+  double bytes = 0, us = 0;
+  for (int i = 0; i < n; ++i) {
+    const GemmArgs& g = a[d[i].problem];
+    int jobs = (((d[i].rows + t.bm - 1) / t.bm) * ((g.N + t.bn - 1) / t.bn) * d[i].splits + 7) / 8;
+    const double dur = d[i].kt_per_split * t.us + 5.0;
+    while (jobs > 0) {
+      int e = 0;
+      for (int k = 1; k < nq; ++k) if (q[k].at < q[e].at) e = k;
+      if (jobs >= q[e].count) { jobs -= q[e].count; q[e].at += dur; }
+      else { q[nq++] = {q[e].at + dur, jobs}; q[e].count -= jobs; jobs = 0; }
+      for (int k = 0; k < nq; ++k)           // groups that became free at the same time are one
+        for (int m = nq - 1; m > k; --m)
+          if (q[m].at == q[k].at) { q[k].count += q[m].count; q[m] = q[--nq]; }
+    }
+    if (d[i].splits > 1) bytes += 2.0 * d[i].splits * 4.0 * d[i].rows * g.N;
+  }
+  for (int k = 0; k < nq; ++k) us = std::max(us, q[k].at);
+  return us + bytes / 5.0e6 + (bytes > 0 ? 6.0 : 0.0);
+}
+
+// Tile, number of unsplit tiles and split of the rest with the least estimated time.  Whole rounds of 256 workgroups run
+// unsplit; what is left over, which would leave most CUs idle for the length of a whole contraction, is cut to fill the chip.
+DwGroupPlan gemm_dw_group_plan(const GemmArgs* a, int n, int force_tile, size_t ws_limit) {
+  DwGroupPlan best{-1, 0, 1, 0};
+  double best_us = 0;
   int kt_max = 0;
   for (int i = 0; i < n; ++i) kt_max = std::max(kt_max, (a[i].K + 63) / 64);
-  DwPlan best{-1, 0, 0};
-  double best_us = 0;
   for (int tile = 0; tile < kDwTileCount; ++tile) {
     if (force_tile && tile != force_tile - 1) continue;
-    for (int s = 1; s <= 64 && s <= kt_max; ++s) {
-      const int L = (kt_max + s - 1) / s;
-      if (s > 1 && L < 4) break;
-      double us;
-      const size_t ws = dw_plan_eval(a, n, tile, L, us);
-      if (ws > ws_limit) continue;
-      if (best.tile < 0 || us < best_us) { best = {tile, L, ws}; best_us = us; }
+    int total = 0;
+    for (int i = 0; i < n; ++i) if ((a[i].K + 63) / 64 * 2 >= kt_max) total += dw_tiles(a[i], kDwTiles[tile]);
+    for (int rounds = 0; rounds <= total / 256; ++rounds) {
+      if (rounds > 2 && rounds < total / 256 - 1) continue;
+      for (int s = 1; s <= 64 && (s == 1 || (kt_max + s - 1) / s >= 4); s += 1 + s / 8) {
+        const DwGroupPlan plan{tile, 256 * rounds, s, 0};
+        DwPart parts[2 * DW_GROUP_MAX];
+        const int np = dw_parts(a, n, plan, parts);
+        size_t ws = 0;
+        for (int i = 0; i < np; ++i) ws += dw_part_ws_bytes(a[parts[i].problem], parts[i]);
+        if (ws > ws_limit) continue;
+        const double us = dw_plan_us(a, plan, parts, np);
+        if (best.tile < 0 || us < best_us) { best = plan; best.ws_bytes = ws; best_us = us; }
+        if (rounds == 0 && s == 1 && total >= 256 * 8) break;       // many rounds: nothing to gain from a split
+      }
     }
   }
   return best;
@@ -188,8 +231,6 @@ bool gemm_dw_group_supported(const GemmArgs& a) {
   // 32-bit offsets, also of the k-tile past the last one
   return operand_extent_bytes(a.K + 128, a.M, a.lda) < 0xFFFFFFF0ull && operand_extent_bytes(a.K + 128, a.N, a.ldb) < 0xFFFFFFF0ull;
 }
-
-size_t gemm_dw_group_ws_bytes(const GemmArgs* a, int n) { return dw_plan(a, n, 0, (size_t)-1).ws_bytes; }
 
 template <class T>
 static int launch_dw_tile(DwGroup& g, hipStream_t s) {
@@ -204,36 +245,39 @@ static int launch_dw_tile(DwGroup& g, hipStream_t s) {
   return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "gemm dW launch failed");
 }
 
-int launch_gemm_dw_group(const GemmArgs* a, int n, int force_tile, hipStream_t s) {
-  if (n < 1 || n > DW_GROUP_MAX) return set_error(DP_EINVAL, "gemm dW: bad number of problems");
+int launch_gemm_dw_group(const GemmArgs* a, int n, const DwGroupPlan& plan, hipStream_t s) {
+  if (n < 1 || n >= DW_GROUP_MAX) return set_error(DP_EINVAL, "gemm dW: bad number of problems");
   for (int i = 0; i < n; ++i)
     if (!gemm_dw_group_supported(a[i])) return set_error(DP_EUNSUPPORTED, "gemm dW: problem not supported");
-  const DwPlan plan = dw_plan(a, n, force_tile, a[0].splitk_ws ? a[0].splitk_ws_bytes : 0);
-  if (plan.tile < 0) return set_error(DP_EUNSUPPORTED, "gemm dW: bad tile");
+  if (plan.tile < 0 || plan.tile >= kDwTileCount) return set_error(DP_EUNSUPPORTED, "gemm dW: bad tile");
+  if (plan.ws_bytes && (!a[0].splitk_ws || a[0].splitk_ws_bytes < plan.ws_bytes)) return set_error(DP_EWORKSPACE, "gemm dW: split-K workspace too small");
   const DwTile& t = kDwTiles[plan.tile];
+  static_assert(sizeof(DwGroup) <= 4096 && sizeof(DwReduce) <= 4096, "kernel arguments");
+  DwPart parts[2 * DW_GROUP_MAX];
+  const int np = dw_parts(a, n, plan, parts);
   DwGroup g;
   DwReduce r;
-  g.n = n; g.total = 0; r.n = 0; r.first[0] = 0;
+  g.n = np; g.total = 0; r.n = 0; r.first[0] = 0;
   char* ws = (char*)a[0].splitk_ws;
   double flops = 0, bytes = 0, red = 0;
-  for (int i = 0; i < n; ++i) {
+  for (int i = 0; i < np; ++i) {
+    const GemmArgs& b = a[parts[i].problem];
+    const int row0 = parts[i].row0;
     DwProblem& p = g.p[i];
-    p.A = (const bf16*)a[i].A; p.B = (const bf16*)a[i].B; p.out = a[i].out_f32; p.colsum = a[i].colsum_out; p.partial = nullptr;
-    p.M = a[i].M; p.N = a[i].N; p.K = a[i].K; p.lda = a[i].lda; p.ldb = a[i].ldb; p.accumulate = a[i].accumulate;
-    p.a_bytes = (uint32_t)operand_extent_bytes(a[i].K, a[i].M, a[i].lda);
-    p.b_bytes = (uint32_t)operand_extent_bytes(a[i].K, a[i].N, a[i].ldb);
+    p.A = (const bf16*)b.A + row0; p.B = (const bf16*)b.B; p.out = b.out_f32 + (size_t)row0 * b.N;
+    p.colsum = b.colsum_out ? b.colsum_out + row0 : nullptr; p.partial = nullptr;
+    p.M = parts[i].rows; p.N = b.N; p.K = b.K; p.lda = b.lda; p.ldb = b.ldb; p.accumulate = b.accumulate;
+    p.a_bytes = (uint32_t)operand_extent_bytes(b.K, p.M, b.lda);
+    p.b_bytes = (uint32_t)operand_extent_bytes(b.K, b.N, b.ldb);
     p.tiles_m = (p.M + t.bm - 1) / t.bm; p.tiles_n = (p.N + t.bn - 1) / t.bn;
     p.group_m = std::min(p.tiles_m, 8);
-    const int kt = (p.K + 63) / 64;
-    p.splits = (kt + plan.kt_per_wg - 1) / plan.kt_per_wg;
-    p.kt_per_split = (kt + p.splits - 1) / p.splits;
-    p.splits = (kt + p.kt_per_split - 1) / p.kt_per_split;
+    p.splits = parts[i].splits; p.kt_per_split = parts[i].kt_per_split;
     p.first = g.total;
     g.total += p.tiles_m * p.tiles_n * p.splits;
     const size_t mn = (size_t)p.M * p.N;
     if (p.splits > 1) {
       p.partial = (float*)ws;
-      ws += ((size_t)p.splits * (mn + p.M) * sizeof(float) + 255) / 256 * 256;
+      ws += dw_part_ws_bytes(b, parts[i]);
       auto add = [&](float* out, const float* part, size_t count) {
         r.p[r.n] = {out, part, (long)(count / 4), p.splits, p.accumulate};
         r.first[r.n + 1] = r.first[r.n] + (long)(count / 4);
@@ -251,6 +295,7 @@ int launch_gemm_dw_group(const GemmArgs* a, int n, int force_tile, hipStream_t s
     switch (plan.tile) {
       case 0: rc = launch_dw_tile<PpTile<256, 128, 128, 4, 2>>(g, s); break;
       case 1: rc = launch_dw_tile<PpTile<256, 64, 64, 4, 2>>(g, s); break;
+      case 3: rc = launch_dw_tile<PpTile<256, 128, 64, 4, 2>>(g, s); break;
       default: rc = launch_dw_tile<PpTile<128, 128, 128, 2, 4>>(g, s); break;
     }
     DP_TRY(rc);

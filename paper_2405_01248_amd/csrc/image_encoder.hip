@@ -243,12 +243,12 @@ static void plan_image(const dp_image_encoder& e, void* base, int lb, int le, in
   b.bytes = p.off;
 }
 
-// y = x W^T + bias on M rows.  rows_per_sample > 0: the tile configuration is chosen for one sample's rows, so that the
-// arithmetic behind a sample's outputs is the same whatever the number of samples in the call.
-static GemmArgs linear(const void* x, long M, int K, const void* W, int N, const void* bias, void* y, int rows_per_sample = 0) {
+// y = x W^T + bias on M rows.  Only tiles that add an output's products in the same order are taken, so that the arithmetic
+// behind a sample's outputs is the same whatever the number of samples in the call.
+static GemmArgs linear(const void* x, long M, int K, const void* W, int N, const void* bias, void* y) {
   GemmArgs g; memset(&g, 0, sizeof(g));
   g.dtype = BF16; g.A = x; g.B = W; g.M = (int)M; g.N = N; g.K = K; g.lda = K; g.ldb = K; g.out = y; g.ldo = N; g.bias = bias;
-  if (rows_per_sample > 0) g.force_cfg = 1 + gemm_choose_cfg(rows_per_sample, N, K);
+  g.choice_rows = -1;
   return g;
 }
 
@@ -287,7 +287,7 @@ static int image_layer(const dp_image_encoder& e, int l, const void* const* P, c
       DP_TRY(gn(w.t2, co, P[4], P[5], 1, w.t1));
       const void* skip = src;
       if (ci != co) {
-        DP_TRY(launch_gemm(linear(src, (long)n * HW, ci, P[8], co, P[9], w.t3, HW), st));
+        DP_TRY(launch_gemm(linear(src, (long)n * HW, ci, P[8], co, P[9], w.t3), st));
         skip = w.t3;
       }
       return conv(w.t1, co, co, 1, P[6], P[7], skip, dst);
@@ -295,8 +295,8 @@ static int image_layer(const dp_image_encoder& e, int l, const void* const* P, c
     case DP_IMG_ATTN: {
       const long R = (long)n * HW;
       DP_TRY(gn(src, ci, P[0], P[1], 0, w.t1));
-      DP_TRY(launch_gemm(linear(w.t1, R, ci, P[2], ci, P[3], w.q, HW), st));
-      DP_TRY(launch_gemm(linear(w.t1, R, ci, P[4], ci, P[5], w.k, HW), st));
+      DP_TRY(launch_gemm(linear(w.t1, R, ci, P[2], ci, P[3], w.q), st));
+      DP_TRY(launch_gemm(linear(w.t1, R, ci, P[4], ci, P[5], w.k), st));
       const float scale = 1.0f / sqrtf((float)ci);
       for (int s = 0; s < n; ++s) {
         const size_t off = (size_t)s * HW * ci * 2;
@@ -312,7 +312,7 @@ static int image_layer(const dp_image_encoder& e, int l, const void* const* P, c
         g = linear(w.probs, HW, HW, w.v, ci, P[7], (char*)w.a + off);      // a_s = probs v_s + b_v
         DP_TRY(launch_gemm(g, st));
       }
-      GemmArgs g = linear(w.a, R, ci, P[8], ci, P[9], dst, HW);
+      GemmArgs g = linear(w.a, R, ci, P[8], ci, P[9], dst);
       g.residual = src; g.ld_res = ci;
       w.stat_of = nullptr;          // dst is written by a GEMM: no statistics come with it
       return launch_gemm(g, st);

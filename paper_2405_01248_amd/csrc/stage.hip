@@ -51,6 +51,7 @@ struct dp_stage {
   hipStream_t side = nullptr;
   std::vector<hipEvent_t> events;
   bool overlap = true;
+  DwGroupPlan dw_plan{-1, 0, 1, 0};     // how a block's weight gradients are cut into workgroups (bf16)
   int fuse = 3;   // bit 0: GeGLU forward in the projection GEMM's epilogue; bit 1: its backward in the dx GEMM's
 };
 
@@ -75,16 +76,25 @@ struct DitBuf {
   void *xin, *m, *h1, *qkv, *a, *o, *x1, *h2, *f1, *f, *f2;
   float *mean1, *rstd1, *lse, *mean2, *rstd2;
 };
-// A residual-stream gradient lives twice: fp32 (f) for the running sum and in the storage
-// dtype (h) as a GEMM operand.  For fp32 storage both point at the same buffer.
+// A residual-stream gradient lives twice: fp32 (f) for the running sum and in the storage dtype (h) as a GEMM
+// operand (U-Net only).  For fp32 storage both point at the same buffer.
 struct GradPair { float* f; void* h; };
+// What the weight-gradient work of a block reads.  It is done for the whole block at once, after (bf16 stages: possibly
+// beside) the activation-gradient chain, so these buffers alternate between consecutive blocks.
+struct BwdSet {
+  void *dqkv, *dq2, *dkv2, *du, *dg, *dg2, *h[2];      // dg, dg2: DiT gated-branch gradients; h: storage copies of dx2, dx1
+  float* ln_partial[3];                                  // column partials of the LayerNorm backward kernels
+  float *dmv, *dcond_pre; void* dm_t;                    // DiT: modulation gradients (fp32, then storage dtype)
+};
 struct BwdScratch {
-  GradPair r[2];
-  void *dh, *da, *dqkv, *dq2, *dkv2, *dg, *dg2, *du, *dm_t;
-  float *delta, *dmv[2], *dcond_pre, *partial, *partial_side; size_t partial_bytes;   // dmv: modulation gradients, alternating by block
+  float* f[2];
+  void* out_h[3];                         // storage copies of the blocks' dx, taken in turn (read by the weight gradients of the next block)
+  BwdSet set[2];
+  void *dh, *da, *dg_raw;                 // dg_raw: unfused GeGLU backward
+  float *delta, *partial; size_t partial_bytes;
   float* dkv_ws; size_t dkv_ws_bytes;     // query-split partials of the cross-attention dK/dV kernel
   void* wt;                               // transposed copies of every block's weight matrices (bf16 stages only)
-  float* ln_partial[4]; size_t ln_partial_bytes;   // column partials of the LayerNorm backward kernels, reduced on the side stream (U-Net: one per LayerNorm; DiT: [2 * block parity + LayerNorm])
+  size_t ln_partial_bytes;
 };
 
 static void plan_unet_block(Plan& p, const dp_stage& s, UnetBuf& u, bool with_xin) {
@@ -111,20 +121,42 @@ static void plan_dit_block(Plan& p, const dp_stage& s, DitBuf& u, bool with_xin)
   u.mean2 = (float*)p.take(T * 4); u.rstd2 = (float*)p.take(T * 4);
 }
 
+static GemmArgs gemm_dw(int dtype, const void* dy, int M, int N, const void* x, int K, float* dW, int accumulate, float* partial, size_t partial_bytes);
+
+// Shapes of a block's weight gradients in the order in which they are collected: out features, in features, rows.
+struct DwShape { int out, in, rows; };
+static int dw_shapes(const dp_stage& s, DwShape* e) {
+  const int T = s.T, d = s.d.d_model, ff = s.d.ff_inner;
+  if (s.d.kind == DP_BLOCK_UNET_XATTN_GEGLU) {
+    const DwShape t[] = {{d, ff, T}, {2 * ff, d, T}, {d, d, T}, {d, d, T}, {d, d, T}, {3 * d, d, T}, {2 * d, s.d.ctx_dim, s.Tc}};
+    memcpy(e, t, sizeof(t));
+    return 7;
+  }
+  const DwShape t[] = {{d, ff, T}, {ff, d, T}, {d, d, T}, {3 * d, d, T}, {6 * d, d, s.d.batch}};
+  memcpy(e, t, sizeof(t));
+  return 5;
+}
+
+static DwGroupPlan plan_dw(const dp_stage& s) {
+  DwShape e[8];
+  GemmArgs g[8];
+  const int n = dw_shapes(s, e);
+  for (int i = 0; i < n; ++i) g[i] = gemm_dw(s.d.dtype, nullptr, e[i].rows, e[i].out, nullptr, e[i].in, nullptr, 0, nullptr, 0);
+  return gemm_dw_group_plan(g, n, 0, (size_t)-1);
+}
+
 static size_t partial_need(const dp_stage& s) {
   const int T = s.T, d = s.d.d_model, ff = s.d.ff_inner;
   size_t n = 0;
   auto mx = [&](size_t v) { n = std::max(n, v); };
   const bool unet = s.d.kind == DP_BLOCK_UNET_XATTN_GEGLU;
-  const int wide = unet ? 2 * ff : ff;
-  // dW GEMMs (M = out features, N = in features, K = rows)
-  mx(gemm_splitk_ws_bytes(3 * d, d, T)); mx(gemm_splitk_ws_bytes(d, d, T));
-  mx(gemm_splitk_ws_bytes(wide, d, T)); mx(gemm_splitk_ws_bytes(d, ff, T));
-  if (unet) mx(gemm_splitk_ws_bytes(2 * d, s.d.ctx_dim, s.Tc));
-  else { mx(gemm_splitk_ws_bytes(6 * d, d, s.d.batch)); mx(gemm_splitk_ws_bytes(s.d.batch, d, 6 * d)); }
-  mx(colsum_partial_bytes(T, std::max(3 * d, wide)));
+  DwShape e[8];
+  const int ne = dw_shapes(s, e);
+  for (int i = 0; i < ne; ++i) mx(gemm_splitk_ws_bytes(e[i].out, e[i].in, e[i].rows));        // where the group is not available
+  if (s.es == 2) mx(s.dw_plan.ws_bytes);
+  if (!unet) mx(gemm_splitk_ws_bytes(s.d.batch, d, 6 * d));
+  mx(colsum_partial_bytes(T, std::max(3 * d, unet ? 2 * ff : ff)));
   mx(colsum_partial_bytes(s.d.batch, 6 * d));
-  mx(ln_bwd_partial_bytes(T, d, unet ? T : s.d.tokens));
   return n;
 }
 
@@ -153,36 +185,34 @@ static size_t wt_block_elems(const dp_stage& s) {
 static void plan_bwd_scratch(Plan& p, const dp_stage& s, BwdScratch& b) {
   const size_t T = s.T, Tc = s.Tc, d = s.d.d_model, ff = s.d.ff_inner, es = s.es, B = s.d.batch;
   const bool unet = s.d.kind == DP_BLOCK_UNET_XATTN_GEGLU;
-  for (int i = 0; i < 2; ++i) {
-    b.r[i].f = (float*)p.take(T * d * 4);
-    b.r[i].h = es == 4 ? (void*)b.r[i].f : p.take(T * d * es);
-  }
+  b = BwdScratch();
+  for (int i = 0; i < 2; ++i) b.f[i] = (float*)p.take(T * d * 4);
+  const bool copies = unet && es == 2;
+  if (copies) for (int i = 0; i < 3 && i + 1 < s.d.n_blocks; ++i) b.out_h[i] = p.take(T * d * es);
   b.dh = p.take(T * d * es); b.da = p.take(T * d * es);
-  b.dqkv = p.take(T * 3 * d * es);
   b.delta = (float*)p.take((size_t)s.d.batch * s.d.n_heads * s.d.tokens * sizeof(float));
+  b.ln_partial_bytes = ln_bwd_partial_bytes((int)T, (int)d, unet ? (int)T : s.d.tokens);
+  for (int i = 0; i < 2; ++i) {
+    BwdSet& t = b.set[i];
+    if (i && (s.d.n_blocks == 1 || es == 4)) { t = b.set[0]; continue; }
+    t.dqkv = p.take(T * 3 * d * es);
+    if (copies) for (int k = 0; k < 2; ++k) t.h[k] = p.take(T * d * es);
+    for (int k = 0; k < (unet ? 3 : 2); ++k) t.ln_partial[k] = (float*)p.take(b.ln_partial_bytes);
+    if (unet) {
+      t.dq2 = p.take(T * d * es); t.dkv2 = p.take(Tc * 2 * d * es); t.du = p.take(T * 2 * ff * es);
+    } else {
+      t.dg = p.take(T * d * es); t.dg2 = p.take(T * d * es); t.du = p.take(T * ff * es);
+      t.dmv = (float*)p.take(B * 6 * d * 4); t.dm_t = p.take(B * 6 * d * es); t.dcond_pre = (float*)p.take(B * d * 4);
+    }
+  }
   if (unet) {
-    b.dq2 = p.take(T * d * es); b.dkv2 = p.take(Tc * 2 * d * es);
     b.dkv_ws_bytes = attn_dkv_ws_bytes(s.d.batch, s.d.n_heads, s.d.ctx_tokens, s.d.d_head);
     b.dkv_ws = (float*)p.take(b.dkv_ws_bytes);
-    b.dg = p.take(T * ff * es); b.du = p.take(T * 2 * ff * es); b.dg2 = nullptr;
-    b.dm_t = nullptr; b.dmv[0] = b.dmv[1] = nullptr; b.dcond_pre = nullptr;
-    b.ln_partial_bytes = ln_bwd_partial_bytes((int)T, (int)d, (int)T);
-    for (int i = 0; i < 3; ++i) b.ln_partial[i] = (float*)p.take(b.ln_partial_bytes);
-    b.ln_partial[3] = nullptr;
-  } else {
-    b.dq2 = nullptr; b.dkv2 = nullptr; b.dkv_ws = nullptr; b.dkv_ws_bytes = 0;
-    b.ln_partial_bytes = ln_bwd_partial_bytes((int)T, (int)d, s.d.tokens);
-    for (int i = 0; i < 4; ++i) b.ln_partial[i] = (float*)p.take(b.ln_partial_bytes);
-    b.dg = p.take(T * d * es);          // gated-branch gradients: df2 ...
-    b.dg2 = p.take(T * d * es);         // ... and do (separate, so the side stream can still read df2)
-    b.du = p.take(T * ff * es);         // df1
-    for (int i = 0; i < 2; ++i) b.dmv[i] = (float*)p.take(B * 6 * d * 4);
-    b.dm_t = p.take(B * 6 * d * es); b.dcond_pre = (float*)p.take(B * d * 4);
+    b.dg_raw = p.take(T * ff * es);
   }
   b.wt = s.es == 2 ? p.take((size_t)s.d.n_blocks * wt_block_elems(s) * s.es) : nullptr;
   b.partial_bytes = partial_need(s);
   b.partial = (float*)p.take(b.partial_bytes);
-  b.partial_side = (float*)p.take(b.partial_bytes);   // split-K / column-sum partials of the side stream
 }
 
 struct StagePlan {
@@ -277,8 +307,49 @@ struct Side {
   }
 };
 
-// Last side batch that reads each reusable backward buffer.
-struct SideReads { int pair[2] = {0, 0}; int du = 0, dq2 = 0, dqkv = 0, dg = 0, dg2 = 0; int dmv[2] = {0, 0}; int lnp[3] = {0, 0, 0}; };
+// Weight- and bias-gradient work of one block.  bf16 stages collect it and launch it for the whole block (flush); otherwise, and
+// where a problem does not fit the grouped kernel, every piece is launched as it comes.
+struct BlockGrads {
+  const dp_stage& s; BwdScratch& b; hipStream_t st; int acc;
+  GemmArgs dw[DW_GROUP_MAX]; int n_dw = 0;
+  LnBwdArgs ln[LN_REDUCE_MAX]; int n_ln = 0;
+  bool defer;
+  BlockGrads(const dp_stage& s_, BwdScratch& b_, hipStream_t st_, int acc_) : s(s_), b(b_), st(st_), acc(acc_), defer(s_.es == 2) {}
+
+  // dW[N, K] = gy[M, N]^T x[M, K], and db[N] = column sums of gy
+  int weight(const void* gy, int M, int N, const void* x, int K, float* dW, float* db) {
+    GemmArgs g = gemm_dw(s.d.dtype, gy, M, N, x, K, dW, acc, b.partial, b.partial_bytes);
+    g.colsum_out = db;
+    if (defer) { dw[n_dw++] = g; return DP_OK; }
+    return one(g, st);
+  }
+  int one(GemmArgs g, hipStream_t q) {
+    float* db = g.colsum_out;
+    if (db && !gemm_colsum_supported(g)) g.colsum_out = nullptr;
+    DP_TRY(launch_gemm(g, q));
+    return db && !g.colsum_out ? launch_colsum(s.d.dtype, g.A, g.lda, g.K, g.M, db, acc, b.partial, b.partial_bytes, q) : DP_OK;
+  }
+  // LayerNorm backward on the main stream; the sums of its column partials are left for later
+  int layer_norm(LnBwdArgs& lb, float* partial) {
+    lb.partial = partial; lb.partial_bytes = b.ln_partial_bytes; lb.defer_reduce = 1;
+    DP_TRY(launch_ln_bwd(lb, st));
+    ln[n_ln++] = lb;
+    return DP_OK;
+  }
+  int flush_ln(hipStream_t q) {
+    if (n_ln) DP_TRY(launch_ln_bwd_reduce(ln, n_ln, q));
+    n_ln = 0;
+    return DP_OK;
+  }
+  int flush_dw(hipStream_t q) {
+    bool group = n_dw > 0;
+    for (int i = 0; i < n_dw; ++i) group = group && gemm_dw_group_supported(dw[i]);
+    if (group) DP_TRY(launch_gemm_dw_group(dw, n_dw, s.dw_plan, q));
+    else for (int i = 0; i < n_dw; ++i) DP_TRY(one(dw[i], q));
+    n_dw = 0;
+    return DP_OK;
+  }
+};
 
 static AttnArgs attn_base(const dp_stage& s) {
   AttnArgs a;
@@ -356,121 +427,72 @@ static int unet_block_fwd(const dp_stage& s, const void* const* P, const float* 
   return DP_OK;
 }
 
-// dy: gradient of the block output (fp32 running sum in pair `c`'s fp32 buffer + a storage-dtype
-// copy).  dx2 goes to pair c ^ 1, dx1 to pair c, the block's dx to pair c ^ 1 again or, for the
-// first block of the stage, to dx_final (storage dtype only).  Weight- and bias-gradient work runs
-// in side-stream batches.
+// dy: gradient of the block output (fp32 running sum in f[c] + a storage-dtype copy).  The fp32 sums go from f[c] to
+// f[c ^ 1] (dx2), f[c] (dx1) and f[c ^ 1] (the block's dx; not for the first block of the stage, whose dx goes to
+// dx_final in the storage dtype only).  `t`: the block's buffers; out_h: storage copy of the block's dx.
 // dy.f == nullptr: the upstream gradient exists in the storage dtype only (dy.h, the caller's tensor)
 static int unet_block_bwd(const dp_stage& s, const void* const* P, const void* const* WT, void* const* G, int acc, const void* ctx, GradPair dy, int c,
-                          void* dx_final, UnetBuf& u, BwdScratch& b, Side& sd, SideReads& rd) {
+                          void* dx_final, void* out_h, UnetBuf& u, BwdScratch& b, BwdSet& t, Side& sd, int* batch) {
   const int dt = s.d.dtype, T = s.T, Tc = s.Tc, d = s.d.d_model, inner = s.d.ff_inner, dc = s.d.ctx_dim;
   const size_t es = s.es;
   hipStream_t st = sd.main;
-  const GradPair dx2 = b.r[c ^ 1], dx1 = b.r[c], out = b.r[c ^ 1];
+  const bool f32 = es == 4;
+  const GradPair dx2{b.f[c ^ 1], f32 ? (void*)b.f[c ^ 1] : t.h[0]}, dx1{b.f[c], f32 ? (void*)b.f[c] : t.h[1]}, out{b.f[c ^ 1], out_h};
   auto gf = [&](int i) { return (float*)G[i]; };
-  auto set_dx = [&](LnBwdArgs& lb, GradPair t) { lb.dx32 = t.f; lb.dx = (es == 4) ? nullptr : t.h; };
-  auto dw = [&](const void* gy, int M, int N, const void* x, int K, int pidx, hipStream_t q) {
-    return launch_gemm(gemm_dw(dt, gy, M, N, x, K, gf(pidx), acc, b.partial_side, b.partial_bytes), q);
-  };
-  auto db = [&](const void* gy, int cols, int rows, int pidx, hipStream_t q) {
-    return launch_colsum(dt, gy, cols, rows, cols, gf(pidx), acc, b.partial_side, b.partial_bytes, q);
-  };
-  // weight gradient and bias gradient of one projection: the column sums of dy ride in the dW GEMM where it can take them
-  auto dwb = [&](const void* gy, int M, int N, const void* x, int K, int pw, int pb, hipStream_t q) -> int {
-    GemmArgs g = gemm_dw(dt, gy, M, N, x, K, gf(pw), acc, b.partial_side, b.partial_bytes);
-    if (gemm_colsum_supported(g)) { g.colsum_out = gf(pb); return launch_gemm(g, q); }
-    DP_TRY(launch_gemm(g, q));
-    return db(gy, N, M, pb, q);
-  };
-  // LayerNorm backward: dx on the main stream; the sum of the column partials into d gamma / d beta
-  // (parameter gradients, nothing downstream waits for them) on the side stream, from a buffer of its own
-  auto ln_bwd = [&](LnBwdArgs& lb, int k) -> int {
-    sd.wait(rd.lnp[k]);
-    lb.partial = b.ln_partial[k]; lb.partial_bytes = b.ln_partial_bytes; lb.defer_reduce = 1;
-    DP_TRY(launch_ln_bwd(lb, st));
-    hipStream_t q = sd.begin();
-    DP_TRY(launch_ln_bwd_reduce(lb, q));
-    rd.lnp[k] = sd.end();
-    return DP_OK;
-  };
+  auto set_dx = [&](LnBwdArgs& lb, GradPair p) { lb.dx32 = p.f; lb.dx = f32 ? nullptr : p.h; };
+  BlockGrads bg(s, b, st, acc);
   // ---- feed-forward
-  {
-    hipStream_t q = sd.begin();
-    DP_TRY(dwb(dy.h, T, d, u.g, inner, U_W2, U_B2, q));
-    rd.pair[c] = sd.end();
-  }
-  sd.wait(rd.du);
+  DP_TRY(bg.weight(dy.h, T, d, u.g, inner, gf(U_W2), gf(U_B2)));
   if (dt == BF16 && (s.fuse & 2)) {
     // dg = dy W2 never reaches memory: the GEMM epilogue turns it into du = [dg gelu(gate) | dg value gelu'(gate)]
-    GemmArgs f = gemm_dx(dt, dy.h, T, d, P[U_W2], WT[U_W2], inner, b.du);
+    GemmArgs f = gemm_dx(dt, dy.h, T, d, P[U_W2], WT[U_W2], inner, t.du);
     f.ldo = 2 * inner; f.geglu = 2; f.geglu_inner = inner; f.geglu_u = u.u; f.ld_geglu = 2 * inner;
     DP_TRY(launch_gemm(f, st));
   } else {
-    DP_TRY(launch_gemm(gemm_dx(dt, dy.h, T, d, P[U_W2], WT[U_W2], inner, b.dg), st));
-    DP_TRY(launch_geglu_bwd(dt, b.dg, u.u, b.du, T, inner, st));
+    DP_TRY(launch_gemm(gemm_dx(dt, dy.h, T, d, P[U_W2], WT[U_W2], inner, b.dg_raw), st));
+    DP_TRY(launch_geglu_bwd(dt, b.dg_raw, u.u, t.du, T, inner, st));
   }
-  {
-    hipStream_t q = sd.begin();
-    DP_TRY(dwb(b.du, T, 2 * inner, u.h3, d, U_W1, U_B1, q));
-    rd.du = sd.end();
-  }
-  DP_TRY(launch_gemm(gemm_dx(dt, b.du, T, 2 * inner, P[U_W1], WT[U_W1], d, b.dh), st));
+  DP_TRY(bg.weight(t.du, T, 2 * inner, u.h3, d, gf(U_W1), gf(U_B1)));
+  DP_TRY(launch_gemm(gemm_dx(dt, t.du, T, 2 * inner, P[U_W1], WT[U_W1], d, b.dh), st));
   LnBwdArgs lb; memset(&lb, 0, sizeof(lb));
-  lb.dtype = dt; lb.rows = T; lb.d = d; lb.accumulate = acc; lb.partial = b.partial; lb.partial_bytes = b.partial_bytes;
+  lb.dtype = dt; lb.rows = T; lb.d = d; lb.accumulate = acc;
   lb.dy = b.dh; lb.x = u.x2; lb.mean = u.mean3; lb.rstd = u.rstd3; lb.gamma = P[U_LN3_G]; set_dx(lb, dx2);
   if (dy.f) lb.dres = dy.f; else { lb.dres = dy.h; lb.dres_storage = 1; }
   lb.dgamma = gf(U_LN3_G); lb.dbeta = gf(U_LN3_B);
-  sd.wait(rd.pair[c ^ 1]);
-  DP_TRY(ln_bwd(lb, 2));
+  DP_TRY(bg.layer_norm(lb, t.ln_partial[2]));
   // ---- cross-attention
-  {
-    hipStream_t q = sd.begin();
-    DP_TRY(dwb(dx2.h, T, d, u.a2, d, U_WO2, U_BO2, q));
-    rd.pair[c ^ 1] = sd.end();
-  }
+  DP_TRY(bg.weight(dx2.h, T, d, u.a2, d, gf(U_WO2), gf(U_BO2)));
   DP_TRY(launch_gemm(gemm_dx(dt, dx2.h, T, d, P[U_WO2], WT[U_WO2], d, b.da), st));
   AttnArgs a = attn_base(s);
   a.Nk = s.d.ctx_tokens; a.q = u.q2; a.ldq = d; a.k = u.kv2; a.v = at(u.kv2, d, es); a.ldk = a.ldv = 2 * d;
   a.o = u.a2; a.ldo = d; a.lse = u.lse2; a.dout = b.da; a.lddo = d; a.delta = b.delta;
-  a.dq = b.dq2; a.lddq = d; a.dk = b.dkv2; a.dv = at(b.dkv2, d, es); a.lddk = a.lddv = 2 * d;
+  a.dq = t.dq2; a.lddq = d; a.dk = t.dkv2; a.dv = at(t.dkv2, d, es); a.lddk = a.lddv = 2 * d;
   a.dkv_ws = b.dkv_ws; a.dkv_ws_bytes = b.dkv_ws_bytes;
-  sd.wait(rd.dq2);
   DP_TRY(launch_attn_bwd(a, st));
-  {
-    hipStream_t q = sd.begin();
-    DP_TRY(dw(b.dq2, T, d, u.h2, d, U_WQ2, q));
-    DP_TRY(dw(b.dkv2, Tc, 2 * d, ctx, dc, U_WKV2, q));
-    rd.dq2 = sd.end();
-  }
-  DP_TRY(launch_gemm(gemm_dx(dt, b.dq2, T, d, P[U_WQ2], WT[U_WQ2], d, b.dh), st));
+  DP_TRY(bg.weight(t.dq2, T, d, u.h2, d, gf(U_WQ2), nullptr));
+  DP_TRY(launch_gemm(gemm_dx(dt, t.dq2, T, d, P[U_WQ2], WT[U_WQ2], d, b.dh), st));
   lb.dy = b.dh; lb.x = u.x1; lb.mean = u.mean2; lb.rstd = u.rstd2; lb.gamma = P[U_LN2_G]; lb.dres = dx2.f; lb.dres_storage = 0; set_dx(lb, dx1);
   lb.dgamma = gf(U_LN2_G); lb.dbeta = gf(U_LN2_B);
-  sd.wait(rd.pair[c]);
-  DP_TRY(ln_bwd(lb, 1));
+  DP_TRY(bg.layer_norm(lb, t.ln_partial[1]));
   // ---- self-attention
-  {
-    hipStream_t q = sd.begin();
-    DP_TRY(dwb(dx1.h, T, d, u.a1, d, U_WO1, U_BO1, q));
-    rd.pair[c] = sd.end();
-  }
+  DP_TRY(bg.weight(dx1.h, T, d, u.a1, d, gf(U_WO1), gf(U_BO1)));
   DP_TRY(launch_gemm(gemm_dx(dt, dx1.h, T, d, P[U_WO1], WT[U_WO1], d, b.da), st));
   a = attn_base(s);
   a.Nk = s.d.tokens; a.q = u.qkv; a.k = at(u.qkv, d, es); a.v = at(u.qkv, 2 * d, es); a.ldq = a.ldk = a.ldv = 3 * d;
   a.o = u.a1; a.ldo = d; a.lse = u.lse1; a.dout = b.da; a.lddo = d; a.delta = b.delta;
-  a.dq = b.dqkv; a.dk = at(b.dqkv, d, es); a.dv = at(b.dqkv, 2 * d, es); a.lddq = a.lddk = a.lddv = 3 * d;
-  sd.wait(rd.dqkv);
+  a.dq = t.dqkv; a.dk = at(t.dqkv, d, es); a.dv = at(t.dqkv, 2 * d, es); a.lddq = a.lddk = a.lddv = 3 * d;
   DP_TRY(launch_attn_bwd(a, st));
-  {
-    hipStream_t q = sd.begin();
-    DP_TRY(dw(b.dqkv, T, 3 * d, u.h1, d, U_WQKV, q));
-    rd.dqkv = sd.end();
-  }
-  DP_TRY(launch_gemm(gemm_dx(dt, b.dqkv, T, 3 * d, P[U_WQKV], WT[U_WQKV], d, b.dh), st));
+  DP_TRY(bg.weight(t.dqkv, T, 3 * d, u.h1, d, gf(U_WQKV), nullptr));
+  DP_TRY(bg.weight(t.dkv2, Tc, 2 * d, ctx, dc, gf(U_WKV2), nullptr));      // last: its contraction is the short one
+  DP_TRY(launch_gemm(gemm_dx(dt, t.dqkv, T, 3 * d, P[U_WQKV], WT[U_WQKV], d, b.dh), st));
   lb.dy = b.dh; lb.x = u.xin; lb.mean = u.mean1; lb.rstd = u.rstd1; lb.gamma = P[U_LN1_G]; lb.dres = dx1.f;
   if (dx_final) { lb.dx = dx_final; lb.dx32 = nullptr; } else set_dx(lb, out);
   lb.dgamma = gf(U_LN1_G); lb.dbeta = gf(U_LN1_B);
-  sd.wait(rd.pair[c ^ 1]);
-  DP_TRY(ln_bwd(lb, 0));
+  DP_TRY(bg.layer_norm(lb, t.ln_partial[0]));
+  hipStream_t q = sd.begin();
+  DP_TRY(bg.flush_dw(q));
+  DP_TRY(bg.flush_ln(q));
+  *batch = sd.end();
   return sd.err;
 }
 
@@ -511,98 +533,58 @@ static int dit_block_fwd(const dp_stage& s, const void* const* P, const float* x
   return DP_OK;
 }
 
-// dy lives in pair c; dx1 goes to pair c ^ 1 and the block's dx back to pair c (or dx_final).
+// dy lives in f[c]; dx1 goes to f[c ^ 1] and the block's dx back to f[c] (or, in the storage dtype, to dx_final).
 static int dit_block_bwd(const dp_stage& s, const void* const* P, const void* const* WT, void* const* G, int acc, const void* cond, const void* sc_in,
-                         GradPair dy, int c, void* dx_final, float* d_cond, int dcond_acc, int par, DitBuf& u, BwdScratch& b, Side& sd,
-                         SideReads& rd) {
+                         int c, void* dx_final, float* d_cond, int dcond_acc, DitBuf& u, BwdScratch& b, BwdSet& t, Side& sd, int* batch) {
   const int dt = s.d.dtype, T = s.T, d = s.d.d_model, ff = s.d.ff_inner, B = s.d.batch, N = s.d.tokens;
   const size_t es = s.es;
   hipStream_t st = sd.main;
-  const GradPair dx1 = b.r[c ^ 1], out = b.r[c];
+  float *dy = b.f[c], *dx1 = b.f[c ^ 1], *dm = t.dmv;
   auto gf = [&](int i) { return (float*)G[i]; };
-  auto set_dx = [&](LnBwdArgs& lb, GradPair t) { lb.dx32 = t.f; lb.dx = (es == 4) ? nullptr : t.h; };
-  auto db = [&](const void* gy, int cols, int rows, int pidx, hipStream_t q) {
-    return launch_colsum(dt, gy, cols, rows, cols, gf(pidx), acc, b.partial_side, b.partial_bytes, q);
-  };
-  // weight gradient and bias gradient of one projection: the column sums of dy ride in the dW GEMM where it can take them
-  auto dwb = [&](const void* gy, int M, int N, const void* x, int K, int pw, int pb, hipStream_t q) -> int {
-    GemmArgs g = gemm_dw(dt, gy, M, N, x, K, gf(pw), acc, b.partial_side, b.partial_bytes);
-    if (gemm_colsum_supported(g)) { g.colsum_out = gf(pb); return launch_gemm(g, q); }
-    DP_TRY(launch_gemm(g, q));
-    return db(gy, N, M, pb, q);
-  };
-  // modulation gradients of this block: the buffer alternates with the block parity `par`, because the
-  // conditioning path that reads it runs on the side stream while the next block already writes its own
-  float* const dm = b.dmv[par];
-  sd.wait(rd.dmv[par]);
+  BlockGrads bg(s, b, st, acc);
   // ---- MLP branch
-  sd.wait(rd.dg);
-  DP_TRY(launch_gate_bwd(dt, dy.f, u.f2, at(u.m, 5 * d, es), 6 * d, b.dg, dm + 5 * d, 6 * d, B, N, d, st));
-  {
-    hipStream_t q = sd.begin();
-    DP_TRY(dwb(b.dg, T, d, u.f, ff, D_FC2_W, D_FC2_B, q));
-    rd.dg = sd.end();
-  }
-  GemmArgs g = gemm_dx(dt, b.dg, T, d, P[D_FC2_W], WT[D_FC2_W], ff, b.du);
+  DP_TRY(launch_gate_bwd(dt, dy, u.f2, at(u.m, 5 * d, es), 6 * d, t.dg, dm + 5 * d, 6 * d, B, N, d, st));
+  DP_TRY(bg.weight(t.dg, T, d, u.f, ff, gf(D_FC2_W), gf(D_FC2_B)));
+  GemmArgs g = gemm_dx(dt, t.dg, T, d, P[D_FC2_W], WT[D_FC2_W], ff, t.du);
   g.dact_pre = u.f1; g.ld_dact = ff; g.dact_kind = s.d.gelu_tanh ? 2 : 1;
-  sd.wait(rd.du);
   DP_TRY(launch_gemm(g, st));
-  {
-    hipStream_t q = sd.begin();
-    DP_TRY(dwb(b.du, T, ff, u.h2, d, D_FC1_W, D_FC1_B, q));
-    rd.du = sd.end();
-  }
-  DP_TRY(launch_gemm(gemm_dx(dt, b.du, T, ff, P[D_FC1_W], WT[D_FC1_W], d, b.dh), st));
+  DP_TRY(bg.weight(t.du, T, ff, u.h2, d, gf(D_FC1_W), gf(D_FC1_B)));
+  DP_TRY(launch_gemm(gemm_dx(dt, t.du, T, ff, P[D_FC1_W], WT[D_FC1_W], d, b.dh), st));
   LnBwdArgs lb; memset(&lb, 0, sizeof(lb));
-  lb.dtype = dt; lb.rows = T; lb.d = d; lb.partial = b.partial; lb.partial_bytes = b.partial_bytes;
+  lb.dtype = dt; lb.rows = T; lb.d = d;
   lb.mod_ld = 6 * d; lb.rows_per_batch = N; lb.dmod_ld = 6 * d;
-  lb.dy = b.dh; lb.x = u.x1; lb.mean = u.mean2; lb.rstd = u.rstd2; lb.scale = at(u.m, 4 * d, es); lb.dres = dy.f; set_dx(lb, dx1);
+  lb.dy = b.dh; lb.x = u.x1; lb.mean = u.mean2; lb.rstd = u.rstd2; lb.scale = at(u.m, 4 * d, es); lb.dres = dy; lb.dx32 = dx1;
   lb.dscale = dm + 4 * d; lb.dshift = dm + 3 * d;
-  // the sums of the column partials into d scale / d shift feed the conditioning path only: they run with it on the side stream
-  lb.partial = b.ln_partial[2 * par + 1]; lb.partial_bytes = b.ln_partial_bytes; lb.defer_reduce = 1;
-  DP_TRY(launch_ln_bwd(lb, st));
-  const LnBwdArgs lb2 = lb;
+  DP_TRY(bg.layer_norm(lb, t.ln_partial[1]));
   // ---- attention branch
-  sd.wait(rd.dg2);
-  DP_TRY(launch_gate_bwd(dt, dx1.f, u.o, at(u.m, 2 * d, es), 6 * d, b.dg2, dm + 2 * d, 6 * d, B, N, d, st));
-  {
-    hipStream_t q = sd.begin();
-    DP_TRY(dwb(b.dg2, T, d, u.a, d, D_WO, D_BO, q));
-    rd.dg2 = sd.end();
-  }
-  DP_TRY(launch_gemm(gemm_dx(dt, b.dg2, T, d, P[D_WO], WT[D_WO], d, b.da), st));
+  DP_TRY(launch_gate_bwd(dt, dx1, u.o, at(u.m, 2 * d, es), 6 * d, t.dg2, dm + 2 * d, 6 * d, B, N, d, st));
+  DP_TRY(bg.weight(t.dg2, T, d, u.a, d, gf(D_WO), gf(D_BO)));
+  DP_TRY(launch_gemm(gemm_dx(dt, t.dg2, T, d, P[D_WO], WT[D_WO], d, b.da), st));
   AttnArgs a = attn_base(s);
   a.Nk = N; a.q = u.qkv; a.k = at(u.qkv, d, es); a.v = at(u.qkv, 2 * d, es); a.ldq = a.ldk = a.ldv = 3 * d;
   a.o = u.a; a.ldo = d; a.lse = u.lse; a.dout = b.da; a.lddo = d; a.delta = b.delta;
-  a.dq = b.dqkv; a.dk = at(b.dqkv, d, es); a.dv = at(b.dqkv, 2 * d, es); a.lddq = a.lddk = a.lddv = 3 * d;
-  sd.wait(rd.dqkv);
+  a.dq = t.dqkv; a.dk = at(t.dqkv, d, es); a.dv = at(t.dqkv, 2 * d, es); a.lddq = a.lddk = a.lddv = 3 * d;
   DP_TRY(launch_attn_bwd(a, st));
-  {
-    hipStream_t q = sd.begin();
-    DP_TRY(dwb(b.dqkv, T, 3 * d, u.h1, d, D_WQKV, D_BQKV, q));
-    rd.dqkv = sd.end();
-  }
-  DP_TRY(launch_gemm(gemm_dx(dt, b.dqkv, T, 3 * d, P[D_WQKV], WT[D_WQKV], d, b.dh), st));
-  lb.dy = b.dh; lb.x = u.xin; lb.mean = u.mean1; lb.rstd = u.rstd1; lb.scale = at(u.m, d, es); lb.dres = dx1.f;
-  if (dx_final) { lb.dx = dx_final; lb.dx32 = nullptr; } else set_dx(lb, out);
+  DP_TRY(bg.weight(t.dqkv, T, 3 * d, u.h1, d, gf(D_WQKV), gf(D_BQKV)));
+  DP_TRY(launch_gemm(gemm_dx(dt, t.dqkv, T, 3 * d, P[D_WQKV], WT[D_WQKV], d, b.dh), st));
+  lb.dy = b.dh; lb.x = u.xin; lb.mean = u.mean1; lb.rstd = u.rstd1; lb.scale = at(u.m, d, es); lb.dres = dx1;
+  if (dx_final) { lb.dx = dx_final; lb.dx32 = nullptr; } else lb.dx32 = b.f[c];
   lb.dscale = dm + d; lb.dshift = dm;
-  lb.partial = b.ln_partial[2 * par];
-  DP_TRY(launch_ln_bwd(lb, st));
-  // ---- conditioning path: m = SiLU(cond) W_ada^T + b_ada.  Nothing on the main stream reads its results (d W_ada, d b_ada and
-  // d cond, accumulated over the blocks in issue order), so all of it runs on the side stream.
-  {
-    hipStream_t q = sd.begin();
-    DP_TRY(launch_ln_bwd_reduce(lb2, q));
-    DP_TRY(launch_ln_bwd_reduce(lb, q));
-    DP_TRY(launch_cast_from_f32(dt, dm, b.dm_t, (size_t)B * 6 * d, q));
-    DP_TRY(dwb(b.dm_t, B, 6 * d, sc_in, d, D_ADA_W, D_ADA_B, q));
-    g = gemm_base(dt);
-    g.A = b.dm_t; g.B = P[D_ADA_W]; g.M = B; g.N = d; g.K = 6 * d; g.lda = 6 * d; g.ldb = d; g.b_mc = 1;
-    g.out_f32 = b.dcond_pre; g.ldo32 = d; g.accumulate = 0; g.splitk_ws = b.partial_side; g.splitk_ws_bytes = b.partial_bytes;
-    DP_TRY(launch_gemm(g, q));
-    DP_TRY(launch_silu_bwd(dt, b.dcond_pre, cond, d_cond, dcond_acc, (size_t)B * d, q));
-    rd.dmv[par] = sd.end();
-  }
+  DP_TRY(bg.layer_norm(lb, t.ln_partial[0]));
+  // ---- weight gradients and the conditioning path (m = SiLU(cond) W_ada^T + b_ada: d W_ada, d b_ada and d cond, accumulated over
+  // the blocks in issue order); nothing on the main stream reads their results
+  hipStream_t q = sd.begin();
+  DP_TRY(bg.flush_ln(q));
+  DP_TRY(launch_cast_from_f32(dt, dm, t.dm_t, (size_t)B * 6 * d, q));
+  bg.st = q;
+  DP_TRY(bg.weight(t.dm_t, B, 6 * d, sc_in, d, gf(D_ADA_W), gf(D_ADA_B)));
+  DP_TRY(bg.flush_dw(q));
+  g = gemm_base(dt);
+  g.A = t.dm_t; g.B = P[D_ADA_W]; g.M = B; g.N = d; g.K = 6 * d; g.lda = 6 * d; g.ldb = d; g.b_mc = 1;
+  g.out_f32 = t.dcond_pre; g.ldo32 = d; g.accumulate = 0; g.splitk_ws = b.partial; g.splitk_ws_bytes = b.partial_bytes;
+  DP_TRY(launch_gemm(g, q));
+  DP_TRY(launch_silu_bwd(dt, t.dcond_pre, cond, d_cond, dcond_acc, (size_t)B * d, q));
+  *batch = sd.end();
   return sd.err;
 }
 
@@ -644,7 +626,7 @@ static int run_stage_fwd(dp_stage* s, const void* const* params, const void* x, 
   // DiT: likewise the modulation vectors m = SiLU(cond) W_ada^T + b_ada of all blocks (32 rows each: latency, not work);
   // not while profiling, where each block's row has to hold its own projection
   Side sd;
-  sd.main = st; sd.on = s->overlap && (unet ? save != 0 : ph == nullptr);
+  sd.main = st; sd.on = s->overlap && s->es == 2 && (unet ? save != 0 : ph == nullptr);
   int kv_batch = 0;
   std::vector<int> mod_batch((size_t)nb, 0);
   if (sd.on) {
@@ -696,55 +678,50 @@ static int run_stage_bwd(dp_stage* s, const void* const* params, const void* dy,
   const int nb = s->d.n_blocks;
   BwdScratch& bs = sp.bs;
   Side sd;
-  sd.main = st; sd.on = s->overlap;
+  sd.main = st; sd.on = s->overlap && s->es == 2;
   if (sd.on) {
     DP_TRY(ensure_side_stream(s));
     sd.side = s->side; sd.ev = &s->events;
   }
-  SideReads rd;
-  // dy as a gradient pair: the caller's tensor as GEMM operand; an fp32 copy only where a kernel of the
-  // last block wants one (the U-Net block reads dy in the storage dtype everywhere)
-  if (!unet || s->es == 4) DP_TRY(launch_cast_to_f32(s->d.dtype, dy, bs.r[1].f, (size_t)s->T * s->d.d_model, st));
-  GradPair cur{(!unet || s->es == 4) ? bs.r[1].f : nullptr, const_cast<void*>(dy)};
-  int ci = 1;   // index of the pair whose fp32 buffer holds cur
-  // Transposed weight copies: one launch per block on the side stream, issued one block ahead of
-  // the block that uses them; the main stream waits for a block's copies right before that block.
+  // Transposed weight copies of all blocks, in one launch (a few for a long stage).
   std::vector<const void*> wt_ptrs((size_t)nb * s->per_block, nullptr);
-  std::vector<int> wt_batch(nb, 0);
-  auto transpose_block = [&](int b) -> int {
+  if (bs.wt) {
     WtEntry we[8];
     const int nw = wt_entries(*s, we);
     TransposeBatch tb; tb.n = 0;
-    size_t off = (size_t)b * wt_block_elems(*s);
-    for (int i = 0; i < nw; ++i) {
-      void* dst = at(bs.wt, off, s->es);
-      transpose_batch_add(tb, params[(size_t)b * s->per_block + we[i].param], dst, we[i].rows, we[i].cols);
-      wt_ptrs[(size_t)b * s->per_block + we[i].param] = dst;
-      off += ((size_t)we[i].rows * we[i].cols + 127) / 128 * 128;
+    size_t off = 0;
+    for (int b = 0; b < nb; ++b) {
+      for (int i = 0; i < nw; ++i) {
+        void* dst = at(bs.wt, off, s->es);
+        transpose_batch_add(tb, params[(size_t)b * s->per_block + we[i].param], dst, we[i].rows, we[i].cols);
+        wt_ptrs[(size_t)b * s->per_block + we[i].param] = dst;
+        off += ((size_t)we[i].rows * we[i].cols + 127) / 128 * 128;
+      }
+      if (tb.n + nw > kTransposeMax || b == nb - 1) { DP_TRY(launch_transpose16_batch(tb, st)); tb.n = 0; }
     }
-    hipStream_t q = sd.begin();
-    DP_TRY(launch_transpose16_batch(tb, q));
-    wt_batch[b] = sd.end();
-    return DP_OK;
-  };
-  if (bs.wt) DP_TRY(transpose_block(nb - 1));
-  for (int b = nb - 1; b >= 0; --b) {
-    DP_TRY(record(ph, nb - 1 - b, st));
-    if (bs.wt) {
-      if (b > 0) DP_TRY(transpose_block(b - 1));
-      sd.wait(wt_batch[b]);
-    }
+  }
+  // dy as a gradient pair: the caller's tensor as GEMM operand; an fp32 copy only where a kernel of the
+  // last block wants one (the U-Net block reads dy in the storage dtype everywhere)
+  const bool widen = !unet || s->es == 4;
+  if (widen) DP_TRY(launch_cast_to_f32(s->d.dtype, dy, bs.f[1], (size_t)s->T * s->d.d_model, st));
+  GradPair cur{widen ? bs.f[1] : nullptr, const_cast<void*>(dy)};
+  int ci = 1;   // index of the fp32 buffer that holds cur
+  int batch[2] = {0, 0};      // last side batch that reads each of the two buffer sets
+  for (int i = 0; i < nb; ++i) {
+    const int b = nb - 1 - i;
+    DP_TRY(record(ph, i, st));
+    // the set's previous user, two blocks ago; its weight gradients also were the last to read out_h[i % 3]
+    sd.wait(batch[i & 1]);
     const void* const* P = params + (size_t)b * s->per_block;
     const void* const* WT = wt_ptrs.data() + (size_t)b * s->per_block;
     void* const* G = dparams + (size_t)b * s->per_block;
     void* dx_final = b == 0 ? dx : nullptr;
     if (unet) {
-      DP_TRY(unet_block_bwd(*s, P, WT, G, acc, cc, cur, ci, dx_final, sp.ub[b], bs, sd, rd));
+      DP_TRY(unet_block_bwd(*s, P, WT, G, acc, cc, cur, ci, dx_final, bs.out_h[i % 3], sp.ub[b], bs, bs.set[i & 1], sd, &batch[i & 1]));
       ci ^= 1;
-      cur = bs.r[ci];
+      cur = GradPair{bs.f[ci], s->es == 4 ? (void*)bs.f[ci] : bs.out_h[i % 3]};
     } else {
-      DP_TRY(dit_block_bwd(*s, P, WT, G, acc, cc, sp.sc_in, cur, ci, dx_final, (float*)d_cond, b != nb - 1, b & 1, sp.db[b], bs, sd, rd));
-      cur = bs.r[ci];
+      DP_TRY(dit_block_bwd(*s, P, WT, G, acc, cc, sp.sc_in, ci, dx_final, (float*)d_cond, i != 0, sp.db[b], bs, bs.set[i & 1], sd, &batch[i & 1]));
     }
     if (ph && ph->ev) sd.wait(sd.issued);      // per-block timing: charge a block's side work to that block
   }
@@ -933,6 +910,7 @@ int dp_stage_create(const dp_stage_desc* desc, dp_stage** out) {
            {"attn_bo", dm, 0}, {"fc1_w", inner, dm}, {"fc1_b", inner, 0}, {"fc2_w", dm, inner}, {"fc2_b", dm, 0}};
   }
   s->per_block = (int)per.size();
+  if (s->es == 2) s->dw_plan = plan_dw(*s);
   for (int b = 0; b < d.n_blocks; ++b)
     for (auto& sp : per) s->params.push_back({"block" + std::to_string(b) + "." + sp.n, sp.r, sp.c});
   *out = s;

@@ -18,7 +18,7 @@ def test_forward_tiles(tile_cfg):
         assert e <= TOL_BF16
 
 
-@pytest.mark.parametrize("tile_cfg", [22, 23, 24])
+@pytest.mark.parametrize("tile_cfg", [22, 23, 24, 25])
 @pytest.mark.parametrize("accumulate", [False, True])
 def test_weight_gradient_tiles(tile_cfg, accumulate):
     for M, N, K in [(8, 8, 8), (256, 256, 64), (328, 392, 1000), (264, 136, 72), (64, 520, 2053)]:
