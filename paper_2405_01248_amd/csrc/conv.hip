@@ -12,9 +12,10 @@
 #include "dp_kernels.h"
 #include "dp_errors.h"
 #include "dp_ktime.h"
-#include "dp_gemm_epilogue.h"
+#include "dp_gemm_pp.h"
 
 #include <algorithm>
+#include <atomic>
 
 namespace dp {
 
@@ -144,272 +145,177 @@ __global__ void __launch_bounds__(WGM * WGN * 64) conv3x3_bf16_kernel(const Conv
 }
 
 
-// ------------------------------------------------------------------ direct-to-LDS pipeline
-// The same product with the GEMM kernels' copy pipeline: tiles travel global -> LDS without passing through
-// registers (buffer_load ... lds, 16 bytes per lane, every lane with an address of its own, so the gather of
-// the input pixels costs nothing extra), three 64-deep k-tiles in flight, fragments fetched one k-step ahead,
-// one fence-free barrier per k-tile.  A k-tile lies inside one filter tap (C_in a multiple of 64): its source
-// address is the output pixel's base address plus an offset that is the same for the whole wave, and a lane
-// whose tap falls into the padding aims its copy past the end of the buffer, which the hardware answers with
-// zeros.  256 x 128 output tile, eight waves of 64 x 64 (or 256 x 256, eight waves of 128 x 64).  LDS tiles are unpadded with permuted 16-byte
-// chunks, as in the GEMM kernels: chunk c of tile row r sits at position c ^ ((r >> 1) & 7).
-template <int BK_, int BN_ = 128>
-struct ConvDtlSmem {
-  static constexpr int BM = 256, BN = BN_, BK = BK_, STAGES = 3, WGM = BN_ == 256 ? 2 : 4, WGN = BN_ == 256 ? 4 : 2;
-  static constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2, STAGE = A_BYTES + B_BYTES;
-  static constexpr int WN = BN / WGN, C_LD = WN + 4;
-  static constexpr size_t TILE_BYTES = (size_t)STAGES * STAGE;
-  static constexpr size_t EPI_BYTES = (size_t)WGM * WGN * 32 * C_LD * 4;
-  static constexpr size_t BYTES = TILE_BYTES > EPI_BYTES ? TILE_BYTES : EPI_BYTES;
-};
-
-// Chunk permutation of a tile row (BK / 8 chunks of 16 bytes): BK = 64: key (r >> 1) & 7; BK = 32: (r >> 2) & 3.
-template <int BK> __device__ __forceinline__ int conv_key(int r) { return BK == 32 ? ((r >> 2) & 3) : ((r >> 1) & 7); }
-
-// BK = 64: 144 KB of LDS, one workgroup per CU.  BK = 32: 72 KB, two workgroups per CU (MINW = 4 waves per SIMD), which hide
-// each other's prologue and epilogue where the contraction is short (C_in = 128 .. 256).
-// BN = 256 (BK = 32, 96 KB, eight waves of 128 x 64): half the weight-tile copies and A-fragment reads per FLOP, for layers
-// with at least 256 output channels.
-template <int BK_, int MINW, int BN_ = 128>
-__global__ void __launch_bounds__(512, MINW) conv3x3_dtl_kernel(const ConvParams p, uint32_t x_bytes, uint32_t w_bytes) {
-  using S = ConvDtlSmem<BK_, BN_>;
-  constexpr int BM = S::BM, BN = S::BN, BK = S::BK, STAGES = S::STAGES, WGN = S::WGN, NW = S::WGM * S::WGN, KS = BK / 16, CPR = BK / 8;
-  constexpr int WM = BM / S::WGM, WN = BN / WGN, TM = WM / 32, TN = WN / 32;
-  constexpr int A_LOADS = S::A_BYTES / 1024 / NW, B_LOADS = S::B_BYTES / 1024 / NW, LOADS = A_LOADS + B_LOADS, PART_LAST = LOADS / KS;
-  static_assert(S::A_BYTES % (1024 * NW) == 0 && S::B_BYTES % (1024 * NW) == 0 && STAGES == 3 && KS % 2 == 0, "pipeline shape");
-  constexpr bool INTERLEAVE = BK == 64;
+// ------------------------------------------------------------------ alternating wave groups
+// The same product with the main loop of dp_gemm_pp.h.  Tiles travel global -> LDS without passing through registers
+// (buffer_load ... lds, 16 bytes per lane, every lane with an address of its own, so the gather of the input pixels costs
+// nothing extra).  A 64-deep k-tile lies inside one filter tap (C_in a multiple of 64): its source address is the
+// output pixel's base address plus an offset that is the same for the whole wave, and a lane whose tap falls into the
+// padding aims its copy past the end of the buffer, which the hardware answers with zeros.
+// Measured on the 256 -> 256 channel layers at 256 x 256 pixels, 8 samples: see launch_conv3x3.
+//
+// Epilogue: bias, optional residual, bf16 store and, if asked, the first pass of a GroupNorm over the output: per channel the
+// sum and the sum of squares of the stored (rounded) values over 256 pixels.  They are formed in an order that no tile shape
+// changes: in a band of 32 rows, the rows with equal r % 8 in ascending order, these eight sums pairwise by the bits of
+// r from the lowest up, then the eight bands in ascending order.
+template <class T>
+__global__ void __launch_bounds__(512, 2) conv3x3_pp_kernel(const ConvParams p, uint32_t x_bytes, uint32_t w_bytes) {
   constexpr uint32_t OUTSIDE = 0xFFFFFFF0u;          // an offset past any buffer this kernel accepts: the copy delivers zeros
-
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 5, l32 = lane & 31;
-  const int wm0 = (wave / WGN) * WM, wn0 = (wave % WGN) * WN;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / T::WGN, wn = wave % T::WGN;
   int tile_m, tile_n;
   tile_of_block(blockIdx.x, p.tiles_m, p.tiles_n, p.group_m, tile_m, tile_n);
-  const int m0 = tile_m * BM, n0 = tile_n * BN;
-  const int nk = p.K / BK;
+  const int m0 = tile_m * T::BM, n0 = tile_n * T::BN, nk = p.K / T::BK;
 
-  const rsrc_t rx = make_rsrc(p.x, x_bytes), rw = make_rsrc(p.w, w_bytes);
   // per A piece of this wave: byte offset of the output pixel's own input pixel (tap centre) plus this lane's
   // chunk, and the 9-bit set of taps that fall inside the image for that pixel (empty for rows past M)
-  int a_base[A_LOADS];
-  unsigned a_taps[A_LOADS];
+  int a_base[2][T::LA];
+  unsigned a_taps[2][(T::LA + 1) / 2];
 #pragma unroll
-  for (int j = 0; j < A_LOADS; ++j) {
-    const int r = (wave * A_LOADS + j) * (512 / BK) + lane / CPR, pc = lane % CPR, c = pc ^ conv_key<BK>(r);
-    const int gm = m0 + r, q = min(gm, p.M - 1);
-    const int b = q / (p.Ho * p.Wo), rem = q - b * (p.Ho * p.Wo), ho = rem / p.Wo, wo = rem - ho * p.Wo;
-    const int hc = ho * p.stride, wc = wo * p.stride;
-    a_base[j] = (int)(2u * ((uint32_t)((b * p.H + hc) * p.W + wc) * (uint32_t)p.Cin + (uint32_t)c * 8u));
-    unsigned m = 0;
+  for (int h = 0; h < 2; ++h)
 #pragma unroll
-    for (int tap = 0; tap < 9; ++tap) {
-      const int hi = hc + tap / 3 - 1, wi = wc + tap % 3 - 1;
-      m |= (unsigned)((unsigned)hi < (unsigned)p.H && (unsigned)wi < (unsigned)p.W) << tap;
+    for (int j = 0; j < T::LA; ++j) {
+      const int r = pp_piece_row(wave * T::LA + j, lane), c = pp_piece_chunk(r, lane);
+      const int gm = m0 + h * (T::BM / 2) + r, q = min(gm, p.M - 1);
+      const int b = q / (p.Ho * p.Wo), rem = q - b * (p.Ho * p.Wo), ho = rem / p.Wo, wo = rem - ho * p.Wo;
+      const int hc = ho * p.stride, wc = wo * p.stride;
+      a_base[h][j] = (int)(2u * ((uint32_t)((b * p.H + hc) * p.W + wc) * (uint32_t)p.Cin + (uint32_t)c * 8u));
+      unsigned m = 0;
+#pragma unroll
+      for (int tap = 0; tap < 9; ++tap) {
+        const int hi = hc + tap / 3 - 1, wi = wc + tap % 3 - 1;
+        m |= (unsigned)((unsigned)hi < (unsigned)p.H && (unsigned)wi < (unsigned)p.W) << tap;
+      }
+      m = gm < p.M ? m : 0u;
+      a_taps[h][j / 2] = j % 2 ? a_taps[h][j / 2] | m << 16 : m;
     }
-    a_taps[j] = gm < p.M ? m : 0u;
-  }
-  uint32_t vb[B_LOADS];
-#pragma unroll
-  for (int j = 0; j < B_LOADS; ++j) {
-    const int r = (wave * B_LOADS + j) * (512 / BK) + lane / CPR, pc = lane % CPR, c = pc ^ conv_key<BK>(r);
-    vb[j] = 2u * ((uint32_t)min(n0 + r, p.N - 1) * (uint32_t)p.K + (uint32_t)c * 8u);
-  }
-  // the k-tile whose copies are being issued: its tap and its wave-uniform source offset relative to the tap centre
-  int it_tap = 0, it_c0 = 0, cur_tap = 0, cur_off = 0;
-  auto next_tile = [&]() {
-    const int u = (it_tap * 11) >> 5, v = it_tap - 3 * u;          // tap / 3, tap % 3 for tap < 9
-    cur_tap = it_tap;
-    cur_off = 2 * (((u - 1) * p.W + (v - 1)) * p.Cin + it_c0);
-    it_c0 += BK;
-    if (it_c0 == p.Cin) { it_c0 = 0; ++it_tap; }
+  auto piece_b = [&](int h, int j) { return min(wave * (h ? T::LB1 : T::LB0) + j, (h ? T::B1_BYTES : T::B0_BYTES) / 1024 - 1); };
+  auto offset_b = [&](int h, int j) {
+    const int r = pp_piece_row(piece_b(h, j), lane), c = pp_piece_chunk(r, lane);
+    return 2u * ((uint32_t)min(n0 + h * T::BN0 + r, p.N - 1) * (uint32_t)p.K + (uint32_t)c * 8u);
   };
-#define DPC_ISSUE_PART(t_, part_, parts_)                                                                             \
-  {                                                                                                                   \
-    unsigned char* st_ = smem_raw + ((t_) % STAGES) * S::STAGE;                                                       \
-    _Pragma("unroll") for (int j = 0; j < A_LOADS; ++j)                                                               \
-      if (j % (parts_) == (part_)) {                                                                                  \
-        const uint32_t off_ = ((a_taps[j] >> cur_tap) & 1u) ? (uint32_t)(a_base[j] + cur_off) : OUTSIDE;              \
-        async_copy_16B_buf(rx, off_, 0u, st_ + (wave * A_LOADS + j) * 1024);                                          \
-      }                                                                                                               \
-    _Pragma("unroll") for (int j = 0; j < B_LOADS; ++j)                                                               \
-      if ((A_LOADS + j) % (parts_) == (part_))                                                                        \
-        async_copy_16B_buf(rw, vb[j], (uint32_t)(t_) * (2u * BK), st_ + S::A_BYTES + (wave * B_LOADS + j) * 1024);    \
-  }
-
-  f32x16 acc[TM][TN];
+  uint32_t vb0[T::LB0], vb1[T::LB1];
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+  for (int j = 0; j < T::LB0; ++j) vb0[j] = offset_b(0, j);
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+  for (int j = 0; j < T::LB1; ++j) vb1[j] = offset_b(1, j);
+  // per row half, the k-tile whose copies come next (each half is copied tile by tile in order): its tap and first channel, and
+  // the lanes' source offsets for that tap, which are formed once per tap
+  int it_tap[2] = {0, 0}, it_c0[2] = {0, 0};
+  uint32_t va[2][T::LA];
+  typename T::acc_t acc[2][T::TM][T::TN];
+  float csum[2][T::TM];
+  pp_main_loop<T, false, false>(acc, smem_raw, nk, wm, wn, wave >= 4, lane,
+      [&](int h, int t, unsigned char* dst) {
+        const rsrc_t r = make_rsrc(p.x, t < nk ? x_bytes : 0u);
+        if (it_c0[h] == 0) {
+          const int tap = it_tap[h], u = (tap * 11) >> 5, v = tap - 3 * u;          // tap / 3, tap % 3
+          const int off = 2 * ((u - 1) * p.W + (v - 1)) * p.Cin;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  bf16x8 fa[2][TM], fb[2][TN];
-#define DPC_FRAGS(st_, ks_, set_)                                                                                     \
-  {                                                                                                                   \
-    const bf16* as = reinterpret_cast<const bf16*>(smem_raw + (st_) * S::STAGE);                                      \
-    const bf16* bs = reinterpret_cast<const bf16*>(smem_raw + (st_) * S::STAGE + S::A_BYTES);                         \
-    _Pragma("unroll") for (int i = 0; i < TM; ++i) {                                                                  \
-      const int r = wm0 + i * 32 + l32;                                                                               \
-      fa[set_][i] = *reinterpret_cast<const bf16x8*>(as + r * BK + (((2 * (ks_) + g) ^ conv_key<BK>(r)) * 8));         \
-    }                                                                                                                 \
-    _Pragma("unroll") for (int j2 = 0; j2 < TN; ++j2) {                                                               \
-      const int r = wn0 + j2 * 32 + l32;                                                                              \
-      fb[set_][j2] = *reinterpret_cast<const bf16x8*>(bs + r * BK + (((2 * (ks_) + g) ^ conv_key<BK>(r)) * 8));        \
-    }                                                                                                                 \
-  }
-#define DPC_MFMAS(set_)                                                                                               \
-  _Pragma("unroll") for (int i = 0; i < TM; ++i)                                                                      \
-    _Pragma("unroll") for (int j2 = 0; j2 < TN; ++j2) acc[i][j2] = mfma32(fa[set_][i], fb[set_][j2], acc[i][j2]);
-
-  // pipeline: as in the GEMM kernels (all three buffers filled up front; k-tile t + 2 is copied, a few pieces per
-  // k-step, while k-tile t is multiplied; every wait names exactly the copies it needs)
-  for (int t = 0; t < STAGES && t < nk; ++t) { next_tile(); DPC_ISSUE_PART(t, 0, 1); }
-  {
-    const int y = min(nk, STAGES) - 1;
-    if (y == 2) wait_vmcnt<2 * LOADS>();
-    else if (y == 1) wait_vmcnt<LOADS>();
-    else wait_vmcnt<0>();
-  }
-  barrier_nofence();
-  DPC_FRAGS(0, 0, 0);
-  for (int t = 0; t + 1 < nk; ++t) {
-    const int st = t % STAGES;
-    const bool refill = t >= 1 && t - 1 + STAGES < nk;
-    if (refill) next_tile();
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      if (ks + 1 < KS) {
-        DPC_FRAGS(st, ks + 1, (ks + 1) & 1);
-      } else {
-        wait_lgkmcnt0();
-        if (nk - 2 - t >= 1) wait_vmcnt<LOADS - PART_LAST>();
-        else wait_vmcnt<0>();
-        barrier_nofence();
-        DPC_FRAGS((t + 1) % STAGES, 0, 0);
-      }
-      if (INTERLEAVE && ks + 1 < KS) {
-        _Pragma("unroll") for (int q_ = 0; q_ < TM * TN; ++q_) {     // one fragment read behind each MFMA, as in the GEMM kernel
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+          for (int j = 0; j < T::LA; ++j) va[h][j] = (a_taps[h][j / 2] >> (tap + 16 * (j % 2))) & 1u ? (uint32_t)(a_base[h][j] + off) : OUTSIDE;
         }
-      } else {
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      DPC_MFMAS(ks & 1);
-      __builtin_amdgcn_sched_barrier(0);
-      if (refill) DPC_ISSUE_PART(t - 1 + STAGES, ks, KS);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  }
-  {
-    const int st = (nk - 1) % STAGES;
+        const uint32_t off = 2u * (uint32_t)it_c0[h];
+        it_c0[h] += T::BK;
+        if (it_c0[h] == p.Cin) { it_c0[h] = 0; ++it_tap[h]; }
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      if (ks + 1 < KS) DPC_FRAGS(st, ks + 1, (ks + 1) & 1);
-      __builtin_amdgcn_sched_barrier(0);
-      DPC_MFMAS(ks & 1);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  }
-#undef DPC_FRAGS
-#undef DPC_MFMAS
-#undef DPC_ISSUE_PART
-  __syncthreads();   // every wave is done with the operand tiles before they are reused below
-  float* Cw = reinterpret_cast<float*>(smem_raw) + wave * 32 * S::C_LD;
-  if (!p.gn_partial) {
-    wave_epilogue<TM, TN, WN, S::C_LD>(acc, Cw, p.epi, m0 + wm0, n0 + wn0, lane);
-    return;
-  }
-  // Epilogue with the next GroupNorm's first pass folded in: bias, optional residual, bf16 store, and per channel the sum
-  // and the sum of squares of the stored (rounded) values over this tile's 256 pixels.  A lane owns the same 8 columns in
-  // every pass over the rows.  The sums are formed per 64-row band (one band per wave in the 256 x 128 tile, two in the
-  // 256 x 256 one): the lane's rows in order, the 8 lanes with equal lane % 8 by a butterfly, the four bands of a column in
-  // ascending order.  Nothing depends on timing, and both tile shapes associate the additions the same way, so they
-  // produce the same bits.
-  constexpr int NH = WM / 64;       // 64-row bands per wave
-  static_assert(WN == 64 && WM % 64 == 0 && S::BYTES >= S::EPI_BYTES + (size_t)S::WGM * NH * WGN * 2 * 64 * 4, "statistics slab");
+        for (int j = 0; j < T::LA; ++j) async_copy_16B_buf(r, va[h][j], off, dst + (wave * T::LA + j) * 1024);
+      },
+      [&](auto hc, int t, unsigned char* dst) {
+        constexpr int h = decltype(hc)::value;
+        const rsrc_t r = make_rsrc(p.w, t < nk ? w_bytes : 0u);
+        const uint32_t off = t < nk ? (uint32_t)t * (2u * T::BK) : 0u;
+#pragma unroll
+        for (int j = 0; j < (h ? T::LB1 : T::LB0); ++j) async_copy_16B_buf(r, h ? vb1[h ? j : 0] : vb0[h ? 0 : j], off, dst + piece_b(h, j) * 1024);
+      }, false, csum);
+
+  constexpr int CH = T::W / 8, RPI = 64 / CH, NIT = 32 / RPI, SETS = 8 / RPI;      // SETS: sums per column a lane keeps
+  static_assert(64 % CH == 0 && RPI <= 8 && T::SM == 32 && T::WGM * 2 * 32 == T::BM, "epilogue shape");
   const EpiParams<bf16>& e = p.epi;
-  float* stat = reinterpret_cast<float*>(smem_raw + S::EPI_BYTES);      // [band][wave column][sum | sum of squares][64 columns], past the slabs
-  float cs[8], cq[8];
-  const int lc = (lane & 7) * 8, n = n0 + wn0 + lc;
-  bf16x8 bv;
+  float* Cw = reinterpret_cast<float*>(smem_raw) + wave * 32 * T::C_LD;
+  float* stat = reinterpret_cast<float*>(smem_raw + T::EPI_BYTES);      // [band][sum | sum of squares][BN], past the slabs
+  const int lc = (lane % CH) * 8, lr = lane / CH;
+  const int nt = lc < T::SN0 ? wn * T::SN0 + lc : T::BN0 + wn * T::SN1 + lc - T::SN0, n = n0 + nt;
+  float bias[8];
+  pp_bias(e.bias, min(n, e.N - 8), bias);
 #pragma unroll
-  for (int t = 0; t < 8; ++t) bv[t] = (bf16)0.f;
-  if (e.bias && n < e.N) bv = *reinterpret_cast<const bf16x8*>(e.bias + n);
+  for (int ha = 0; ha < 2; ++ha) {
+    const int row0 = m0 + ha * (T::BM / 2) + wm * 32;
+    bf16x8 res[NIT];
 #pragma unroll
-  for (int i = 0; i < TM; ++i) {
-    if (i % 2 == 0) {
+    for (int it = 0; it < NIT; ++it)
+      if (e.residual) res[it] = *reinterpret_cast<const bf16x8*>((const bf16*)e.residual + (size_t)min(row0 + it * RPI + lr, e.M - 1) * e.ld_res + min(n, e.N - 8));
+      else res[it] = zero8();
 #pragma unroll
-      for (int t = 0; t < 8; ++t) { cs[t] = 0.f; cq[t] = 0.f; }
-    }
+    for (int j = 0; j < T::TN; ++j)
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) Cw[(8 * (r >> 2) + 4 * g + (r & 3)) * S::C_LD + j * 32 + l32] = acc[i][j][r];
+      for (int r = 0; r < 16; ++r) Cw[acc_row(r, lane >> 5) * T::C_LD + j * 32 + (lane & 31)] = acc[ha][0][j][r];
     asm volatile("" ::: "memory");
-#pragma unroll 1
-    for (int it = 0; it < 4; ++it) {
-      const int lr = it * 8 + (lane >> 3), m = m0 + wm0 + i * 32 + lr;
-      if (m < e.M && n < e.N) {
-        float v[8];
-        *reinterpret_cast<f32x4*>(&v[0]) = *reinterpret_cast<const f32x4*>(&Cw[lr * S::C_LD + lc]);
-        *reinterpret_cast<f32x4*>(&v[4]) = *reinterpret_cast<const f32x4*>(&Cw[lr * S::C_LD + lc + 4]);
+    float cs[SETS][8], cq[SETS][8];
 #pragma unroll
-        for (int t = 0; t < 8; ++t) v[t] += (float)bv[t];
-        if (e.residual) {
-          const bf16x8 rv = *reinterpret_cast<const bf16x8*>((const bf16*)e.residual + (size_t)m * e.ld_res + n);
+    for (int a = 0; a < SETS; ++a)
 #pragma unroll
-          for (int t = 0; t < 8; ++t) v[t] += (float)rv[t];
-        }
-        bf16x8 o;
+      for (int t = 0; t < 8; ++t) { cs[a][t] = 0.f; cq[a][t] = 0.f; }
 #pragma unroll
-        for (int t = 0; t < 8; ++t) {
-          o[t] = (bf16)v[t];
-          const float f = (float)o[t];
-          cs[t] += f; cq[t] = fmaf(f, f, cq[t]);
-        }
-        *reinterpret_cast<bf16x8*>(e.out + (size_t)m * e.ldo + n) = o;
-      }
-    }
-    asm volatile("" ::: "memory");
-    if (i % 2 == 1) {
-      // the band is complete: lanes with equal lane % 8 hold the same columns
+    for (int it = 0; it < NIT; ++it) {
+      const int m = row0 + it * RPI + lr;
+      float v[8];
+      pp_slab_row(&Cw[(it * RPI + lr) * T::C_LD + lc], v);
+      bf16x8 o;
+#pragma unroll
+      for (int t = 0; t < 8; ++t) o[t] = (bf16)((v[t] + bias[t]) + (float)res[it][t]);
+      if (m < e.M && n < e.N) *reinterpret_cast<bf16x8*>(e.out + (size_t)m * e.ldo + n) = o;
 #pragma unroll
       for (int t = 0; t < 8; ++t) {
-#pragma unroll
-        for (int o = 8; o < 64; o <<= 1) { cs[t] += __shfl_xor(cs[t], o, 64); cq[t] += __shfl_xor(cq[t], o, 64); }
+        const float f = (float)o[t];
+        cs[it % SETS][t] += f; cq[it % SETS][t] = fmaf(f, f, cq[it % SETS][t]);
       }
-      const int band = (wave / WGN) * NH + i / 2, wcol = wave % WGN;
-      if (lane < 8) {
+    }
+    asm volatile("" ::: "memory");
+    if (p.gn_partial) {      // then every row exists
+#pragma unroll
+      for (int t = 0; t < 8; ++t)
+#pragma unroll
+        for (int a = 0; a < SETS; ++a)
+#pragma unroll
+          for (int o = CH; o < 64; o <<= 1) { cs[a][t] += __shfl_xor(cs[a][t], o, 64); cq[a][t] += __shfl_xor(cq[a][t], o, 64); }
+      if (lane < CH) {
+        float* st = stat + (size_t)(ha * T::WGM + wm) * 2 * T::BN + nt;
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
-          stat[((band * WGN + wcol) * 2) * 64 + lane * 8 + t] = cs[t];
-          stat[((band * WGN + wcol) * 2 + 1) * 64 + lane * 8 + t] = cq[t];
+          st[t] = SETS == 2 ? cs[0][t] + cs[SETS - 1][t] : cs[0][t];
+          st[T::BN + t] = SETS == 2 ? cq[0][t] + cq[SETS - 1][t] : cq[0][t];
         }
       }
     }
   }
+  if (!p.gn_partial) return;
   __syncthreads();
-  if (tid < 2 * BN) {
-    const int which = tid / BN, c = tid % BN, wcol = c / 64, cc = c % 64;
+  constexpr int BLOCKS = T::BM / 256;
+  for (int i = tid; i < BLOCKS * 2 * T::BN; i += 512) {
+    const int blk = i / (2 * T::BN), which = i / T::BN % 2, c = i % T::BN;
     float sum = 0.f;
 #pragma unroll
-    for (int band = 0; band < S::WGM * NH; ++band) sum += stat[((band * WGN + wcol) * 2 + which) * 64 + cc];
-    if (n0 + c < e.N) p.gn_partial[((size_t)tile_m * e.N + n0 + c) * 2 + which] = sum;
+    for (int band = 0; band < 8; ++band) sum += stat[((size_t)(blk * 8 + band) * 2 + which) * T::BN + c];
+    if (n0 + c < e.N && m0 + blk * 256 < e.M) p.gn_partial[((size_t)(tile_m * BLOCKS + blk) * e.N + n0 + c) * 2 + which] = sum;
   }
 }
 
-template <int BK, int MINW, int BN = 128>
-static int launch_conv_dtl(ConvParams& p, size_t x_bytes, size_t w_bytes, hipStream_t s) {
-  using S = ConvDtlSmem<BK, BN>;
-  p.tiles_m = (p.M + S::BM - 1) / S::BM; p.tiles_n = (p.N + S::BN - 1) / S::BN;
+template <class T>
+static int launch_conv_pp(ConvParams& p, size_t x_bytes, size_t w_bytes, hipStream_t s) {
+  constexpr size_t LDS = T::EPI_BYTES + (size_t)T::BM / 32 * 2 * T::BN * 4 > T::BYTES ? T::EPI_BYTES + (size_t)T::BM / 32 * 2 * T::BN * 4 : T::BYTES;
+  static_assert(LDS <= 160 * 1024, "tile shape");
+  p.tiles_m = (p.M + T::BM - 1) / T::BM; p.tiles_n = (p.N + T::BN - 1) / T::BN;
+  // whole tile-rows per XCD: the tiles that share a band of input pixels run on one L2
   const long n = (long)p.tiles_m * p.tiles_n, ppx = (n + 7) / 8;
   p.group_m = (int)std::max<long>(1, std::min<long>((ppx + p.tiles_n / 2) / p.tiles_n, p.tiles_m));
-  auto kern = conv3x3_dtl_kernel<BK, MINW, BN>;
-  if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::BYTES) != hipSuccess)
-    return set_error(DP_EHIP, "hipFuncSetAttribute(conv) failed");
-  hipLaunchKernelGGL(kern, dim3((unsigned)n), dim3(512), S::BYTES, s, p, (uint32_t)x_bytes, (uint32_t)w_bytes);
+  auto kern = conv3x3_pp_kernel<T>;
+  static std::atomic<bool> attr_set{false};   // setting it twice is harmless; the flag only saves the call
+  if (!attr_set.load(std::memory_order_acquire)) {
+    if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS) != hipSuccess)
+      return set_error(DP_EHIP, "hipFuncSetAttribute(conv) failed");
+    attr_set.store(true, std::memory_order_release);
+  }
+  hipLaunchKernelGGL(kern, dim3((unsigned)n), dim3(512), LDS, s, p, (uint32_t)x_bytes, (uint32_t)w_bytes);
   return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "conv launch failed");
 }
 
@@ -460,16 +366,20 @@ int launch_conv3x3(const ConvArgs& a, hipStream_t s) {
   // (whether this kernel is taken depends on one sample's pixel count, not on the number of samples)
   if (a.Cin % 64 == 0 && a.Cout >= 64 && (long)Ho * Wo >= 1024 && x_bytes < (1ull << 31) && w_bytes < (1ull << 31) && !a.force_staged) {
     if (a.gn_partial && (Ho * Wo) % 256 == 0 && ((uintptr_t)a.gn_partial % 16) == 0) { p.gn_partial = a.gn_partial; *a.gn_applied = 1; }
-    // measured on the layers of the 512 x 512 encoder: C_in = 128 at stride 1 runs 18 % faster (C_out = 256: 7 %) on the
-    // two-workgroups-per-CU variant; from C_in = 256 on, and at stride 2, the deeper k-tile wins
-    // 256 x 256 tiles for at least 256 output channels when they load the CUs no worse than the 256 x 128 ones: a CU's time
-    // is its number of tiles times the tile's cost, and a 256 x 128 tile costs about 0.6 of a 256 x 256 one.  This choice may
-    // depend on the number of samples: the two tile shapes produce the same bits, statistics included.
-    if (a.Cout % 256 == 0 && a.Cin >= 128) {
-      const long tw = ((M + 255) / 256) * (a.Cout / 256), cus = 256;
-      if ((double)((tw + cus - 1) / cus) <= 0.6 * (double)((2 * tw + cus - 1) / cus)) return launch_conv_dtl<32, 2, 256>(p, x_bytes, w_bytes, s);
+    // The tile with the least estimated time, rounds over the 256 CUs x (fixed part + k-tiles x time of one).  This choice may
+    // depend on the number of samples: the shapes produce the same bits, statistics included.
+    const struct { int bm, bn; float fixed, per_kt; } tiles[] = {{256, 256, 6.0f, 1.75f}, {256, 128, 5.0f, 1.14f}, {512, 64, 6.0f, 1.90f}, {512, 128, 6.0f, 2.10f}};
+    int best = 0;
+    float best_us = 0.f;
+    for (int i = 0; i < 4; ++i) {
+      const long n = ((M + tiles[i].bm - 1) / tiles[i].bm) * ((a.Cout + tiles[i].bn - 1) / tiles[i].bn);
+      const float us = (float)((n + 255) / 256) * (tiles[i].fixed + (float)(p.K / 64) * tiles[i].per_kt);
+      if (i == 0 || us < best_us) { best = i; best_us = us; }
     }
-    return (a.Cin <= 128 && a.stride == 1) ? launch_conv_dtl<32, 4>(p, x_bytes, w_bytes, s) : launch_conv_dtl<64, 2>(p, x_bytes, w_bytes, s);
+    if (best == 0) return launch_conv_pp<PpTile<256, 128, 128, 4, 2>>(p, x_bytes, w_bytes, s);
+    if (best == 1) return launch_conv_pp<PpTile<256, 64, 64, 4, 2>>(p, x_bytes, w_bytes, s);
+    if (best == 2) return launch_conv_pp<PpTile<512, 32, 32, 8, 1>>(p, x_bytes, w_bytes, s);
+    return launch_conv_pp<PpTile<512, 64, 64, 8, 1>>(p, x_bytes, w_bytes, s);
   }
   if (a.Cout <= 64) return launch_conv_cfg<128, 64, 4, 1>(p, s);
   if ((long)Ho * Wo >= 16384) return launch_conv_cfg<256, 128, 4, 2>(p, s);
