@@ -1056,30 +1056,54 @@ static int launch_dtl_cfg(const GemmArgs& a, hipStream_t s) {
   return DP_OK;
 }
 
+static int set_lds_limit(const void* kern, size_t bytes, std::atomic<bool>& done) {
+  if (done.load(std::memory_order_acquire)) return DP_OK;     // setting it twice is harmless; the flag only saves the call
+  if (hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) != hipSuccess) return set_error(DP_EHIP, "hipFuncSetAttribute(gemm) failed");
+  done.store(true, std::memory_order_release);
+  return DP_OK;
+}
+
+template <class T, int KIND, bool FP8, bool KTAIL>
+static int launch_pp_kernel(const GemmBf16Params& p, hipStream_t s) {
+  auto kern = gemm_pp_kernel<T, KIND, FP8, KTAIL>;
+  static std::atomic<bool> attr_set{false};
+  DP_TRY(set_lds_limit((const void*)kern, T::BYTES, attr_set));
+  hipLaunchKernelGGL(kern, dim3(p.tiles_m * p.tiles_n), dim3(512), T::BYTES, s, p);
+  return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "gemm launch failed");
+}
 // C = out_scale * (A_q B_q^T) (+ bias) for OCP E4M3 operands A_q [M, K], B_q [N, K] (bytes, contraction contiguous), storage-dtype
 // (bf16) output.  The kernel sees the operands as two-byte elements: K / 2 of them per row.
-template <int BM, int BN, int WGM, int WGN>
-static int launch_fp8_cfg(const Fp8GemmArgs& a, hipStream_t s) {
-  constexpr int BK = 64, STAGES = 3;
-  using S = DtlSmem<BM, BN, BK, STAGES, WGM, WGN>;
+static GemmBf16Params fp8_params(const Fp8GemmArgs& a, int bm, int bn) {
   GemmBf16Params p;
   memset(&p, 0, sizeof(p));
   p.A = (const bf16*)a.A; p.B = (const bf16*)a.B;
   p.M = a.M; p.N = a.N; p.K = a.K / 2; p.lda = a.lda / 2; p.ldb = a.ldb / 2;
   EpiParams<bf16>& e = p.epi;
   e.M = a.M; e.N = a.N; e.out = (bf16*)a.out; e.ldo = a.ldo; e.bias = (const bf16*)a.bias; e.rows_per_batch = 1; e.out_scale = a.out_scale;
-  p.tiles_m = (a.M + BM - 1) / BM; p.tiles_n = (a.N + BN - 1) / BN;
+  p.tiles_m = (a.M + bm - 1) / bm; p.tiles_n = (a.N + bn - 1) / bn;
   GemmArgs shape; memset(&shape, 0, sizeof(shape)); shape.M = a.M; shape.N = a.N;
   p.group_m = choose_group_m(shape, p.tiles_m, p.tiles_n);
   p.a_bytes = (uint32_t)((size_t)(a.M - 1) * a.lda + a.K);
   p.b_bytes = (uint32_t)((size_t)(a.N - 1) * a.ldb + a.K);
+  return p;
+}
+template <int BM, int BN, int WGM, int WGN>
+static int launch_fp8_cfg(const Fp8GemmArgs& a, hipStream_t s) {
+  constexpr int BK = 64, STAGES = 3;
+  using S = DtlSmem<BM, BN, BK, STAGES, WGM, WGN>;
+  GemmBf16Params p = fp8_params(a, BM, BN);
   p.k_tiles_per_split = p.K / BK;
   auto kern = gemm_bf16_dtl_kernel<BM, BN, BK, STAGES, WGM, WGN, false, false, true>;
-  if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::BYTES) != hipSuccess)
-    return set_error(DP_EHIP, "hipFuncSetAttribute(gemm fp8) failed");
+  static std::atomic<bool> attr_set{false};
+  DP_TRY(set_lds_limit((const void*)kern, S::BYTES, attr_set));
   KScope ks(KK_GEMM_FP8, 2.0 * a.M * a.N * a.K, (double)a.M * a.K + (double)a.N * a.K + 2.0 * a.M * a.N, s, a.M, a.N, a.K);
   hipLaunchKernelGGL(kern, dim3(p.tiles_m * p.tiles_n, 1, 1), dim3(WGM * WGN * 64), S::BYTES, s, p);
   return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "gemm fp8 launch failed");
+}
+template <class T>
+static int launch_fp8_pp(const Fp8GemmArgs& a, hipStream_t s) {
+  KScope ks(KK_GEMM_FP8, 2.0 * a.M * a.N * a.K, (double)a.M * a.K + (double)a.N * a.K + 2.0 * a.M * a.N, s, a.M, a.N, a.K);
+  return launch_pp_kernel<T, PE_PLAIN, true, false>(fp8_params(a, T::BM, T::BN), s);
 }
 
 int launch_gemm_fp8(const Fp8GemmArgs& a, hipStream_t s) {
@@ -1093,9 +1117,22 @@ int launch_gemm_fp8(const Fp8GemmArgs& a, hipStream_t s) {
   for (const void* q : ps) if ((uintptr_t)q % 16) return set_error(DP_EALIGN, "gemm fp8: operands must be 16-byte aligned");
   if ((size_t)(a.M - 1) * a.lda + a.K >= (1ull << 32) || (size_t)(a.N - 1) * a.ldb + a.K >= (1ull << 32))
     return set_error(DP_EUNSUPPORTED, "gemm fp8: operand larger than 4 GiB");
-  const long t256 = (long)((a.M + 255) / 256) * ((a.N + 127) / 128);
-  if (t256 >= kCUs / 2) return launch_fp8_cfg<256, 128, 4, 2>(a, s);
-  return launch_fp8_cfg<128, 128, 4, 2>(a, s);
+  // the tile with the least estimated time, as in choose_cfg: a k-tile of 128 8-bit values costs what one of 64 bf16 values costs
+  // (same bytes, twice the products at twice the rate)
+  const struct { int bm, bn; float fixed, per_kt; } tiles[] = {{256, 256, 6.0f, 1.40f}, {256, 192, 6.0f, 1.10f}, {256, 128, 5.0f, 0.75f}, {128, 128, 4.0f, 0.45f}};
+  int best = 0;
+  float best_us = 0.f;
+  for (int i = 0; i < 4; ++i) {
+    const long n = (long)((a.M + tiles[i].bm - 1) / tiles[i].bm) * ((a.N + tiles[i].bn - 1) / tiles[i].bn);
+    const float us = (float)((n + kCUs - 1) / kCUs) * (tiles[i].fixed + (float)(a.K / 128) * tiles[i].per_kt);
+    if (i == 0 || us < best_us) { best = i; best_us = us; }
+  }
+  switch (best) {
+    case 0: return launch_fp8_pp<PpTile<256, 128, 128, 4, 2>>(a, s);
+    case 1: return launch_fp8_pp<PpTile<256, 128, 64, 4, 2>>(a, s);
+    case 2: return launch_fp8_pp<PpTile<256, 64, 64, 4, 2>>(a, s);
+    default: return launch_fp8_cfg<128, 128, 4, 2>(a, s);
+  }
 }
 
 template <int BM, int BN, int WGM, int WGN>
@@ -1139,21 +1176,6 @@ static int pp_kind(const GemmArgs& a) {
   return PE_PLAIN;
 }
 
-static int set_lds_limit(const void* kern, size_t bytes, std::atomic<bool>& done) {
-  if (done.load(std::memory_order_acquire)) return DP_OK;     // setting it twice is harmless; the flag only saves the call
-  if (hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) != hipSuccess) return set_error(DP_EHIP, "hipFuncSetAttribute(gemm) failed");
-  done.store(true, std::memory_order_release);
-  return DP_OK;
-}
-
-template <class T, int KIND, bool FP8, bool KTAIL>
-static int launch_pp_kernel(const GemmBf16Params& p, hipStream_t s) {
-  auto kern = gemm_pp_kernel<T, KIND, FP8, KTAIL>;
-  static std::atomic<bool> attr_set{false};
-  DP_TRY(set_lds_limit((const void*)kern, T::BYTES, attr_set));
-  hipLaunchKernelGGL(kern, dim3(p.tiles_m * p.tiles_n), dim3(512), T::BYTES, s, p);
-  return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "gemm launch failed");
-}
 template <class T, int KIND>
 static int launch_pp_kind(const GemmBf16Params& p, hipStream_t s) {
   return p.K % T::BK ? launch_pp_kernel<T, KIND, false, true>(p, s) : launch_pp_kernel<T, KIND, false, false>(p, s);

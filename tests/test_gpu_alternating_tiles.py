@@ -25,3 +25,10 @@ def test_weight_gradient_tiles(tile_cfg, accumulate):
         e = _gemm_case("tn", M, N, K, tile_cfg, seed=M + K, bias=False, accumulate=accumulate)
         print(f"\n[gemm tn cfg {tile_cfg} {M}x{N}x{K}] rel err {e:.2e}", flush=True)
         assert e <= TOL_F32OUT
+
+
+@pytest.mark.parametrize("M,N,K", [(4090, 4088, 256), (4100, 4616, 128), (2060, 1544, 384)])
+def test_fp8_tiles(M, N, K):
+    # 256, 192 and 128 columns wide, ragged on both sides
+    import test_gpu_ops
+    test_gpu_ops.test_fp8_gemm_matches_oracle(M, N, K)
