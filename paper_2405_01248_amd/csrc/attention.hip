@@ -284,29 +284,6 @@ __global__ void __launch_bounds__(256, DHP == 64 ? 4 : 3) attn_fwd_bf16_kernel(c
   }
 }
 
-// ------------------------------------------------------------------ delta = rowsum(dO * O)
-// 8 lanes per (token, head) pair.
-template <typename T>
-__global__ void attn_delta_kernel(const T* __restrict__ o, int ldo, const T* __restrict__ dout, int lddo, float* __restrict__ delta,
-                                  int B, int H, int Nq, int dh) {
-  const size_t gid = (blockIdx.x * (size_t)blockDim.x + threadIdx.x) / 8;
-  const int sub = threadIdx.x & 7;
-  const size_t total = (size_t)B * Nq * H;
-  float s = 0.f;
-  if (gid < total) {
-    const int h = gid % H; const size_t row = gid / H;   // row = b * Nq + n
-    const T* po = o + row * ldo + h * dh;
-    const T* pd = dout + row * lddo + h * dh;
-    for (int t = sub; t < dh; t += 8) s += to_f<T>(po[t]) * to_f<T>(pd[t]);
-  }
-  s += __shfl_xor(s, 1, 64); s += __shfl_xor(s, 2, 64); s += __shfl_xor(s, 4, 64);
-  if (gid < total && sub == 0) {
-    const int h = gid % H; const size_t row = gid / H;
-    const size_t b = row / Nq, n = row % Nq;
-    delta[(b * H + h) * Nq + n] = s;
-  }
-}
-
 // ------------------------------------------------------------------ dQ (bf16)
 template <int DHP>
 __global__ void __launch_bounds__(256, DHP == 64 ? 4 : 2) attn_bwd_dq_bf16_kernel(const AttnK p) {
@@ -639,10 +616,15 @@ __global__ void __launch_bounds__(64) attn_bwd_dq_f32_kernel(const AttnK p) {
   const float* dor = (const float*)p.dout + ((size_t)b * p.Nq + i) * p.lddo + h * p.dh;
   const float* kb = (const float*)p.k + (size_t)b * p.Nk * p.ldk + h * p.dh;
   const float* vb = (const float*)p.v + (size_t)b * p.Nk * p.ldv + h * p.dh;
-  for (int t = lane; t < p.dh; t += 64) { qs[t] = q[t]; dos[t] = dor[t]; }
-  __syncthreads();
+  // delta = rowsum(dO * O), also stored for the dK/dV kernel that follows on the stream
+  const float* orow = (const float*)p.o + ((size_t)b * p.Nq + i) * p.ldo + h * p.dh;
   const size_t sidx = ((size_t)b * p.H + h) * p.Nq + i;
-  const float lse = p.lse[sidx], dlt = p.delta[sidx];
+  const float lse = p.lse[sidx];
+  float dlt = 0.f;
+  for (int t = lane; t < p.dh; t += 64) { qs[t] = q[t]; dos[t] = dor[t]; dlt = fmaf(dor[t], orow[t], dlt); }
+  dlt = wave_sum(dlt);
+  if (lane == 0) p.delta[sidx] = dlt;
+  __syncthreads();
   for (int j = lane; j < p.Nk; j += 64) {
     float s = 0.f, dp = 0.f;
     for (int t = 0; t < p.dh; ++t) {
@@ -763,8 +745,6 @@ int launch_attn_fwd(const AttnArgs& a, hipStream_t s) {
 int launch_attn_bwd(const AttnArgs& a, hipStream_t s) {
   if (int e = check_attn(a, true)) return e;
   const AttnK k = make_k(a);
-  const size_t pairs = (size_t)a.B * a.Nq * a.H;
-  const dim3 dgrid((pairs * 8 + 255) / 256);
   if (a.dtype == BF16) {
     dim3 gq(((a.Nq + 127) / 128) * a.B * a.H), gk(((a.Nk + 127) / 128) * a.B * a.H);
     // algorithmic backward work = 2x forward, split evenly between the two kernels for accounting
@@ -803,7 +783,6 @@ int launch_attn_bwd(const AttnArgs& a, hipStream_t s) {
       }
     }
   } else {
-    hipLaunchKernelGGL(attn_delta_kernel<float>, dgrid, dim3(256), 0, s, (const float*)a.o, a.ldo, (const float*)a.dout, a.lddo, a.delta, a.B, a.H, a.Nq, a.d_head);
     hipLaunchKernelGGL(attn_bwd_dq_f32_kernel, dim3(a.Nq, a.B * a.H), dim3(64), (size_t)a.Nk * sizeof(float), s, k);
     hipLaunchKernelGGL(attn_bwd_dkv_f32_kernel, dim3(a.Nk, a.B * a.H), dim3(64), (size_t)2 * a.Nq * sizeof(float), s, k);
   }

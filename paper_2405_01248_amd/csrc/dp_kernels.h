@@ -62,6 +62,7 @@ struct GemmArgs {
   const void* ln_gamma; const void* ln_beta; void* ln_out; float ln_eps; int* ln_applied;
 };
 int launch_gemm(const GemmArgs& a, hipStream_t s);
+int launch_gemm_f32(const GemmArgs& a, hipStream_t s);      // the fp32 part of launch_gemm
 // Bytes from the first to one past the last element of a bf16 operand; rows x inner elements, row stride ld.
 static inline size_t operand_extent_bytes(int rows, int inner, int ld) { return 2 * ((size_t)(rows - 1) * ld + inner); }
 // Several weight gradients dW = dy^T x (a_mc, b_mc, out_f32; colsum_out and accumulate as in launch_gemm) in one launch, with
@@ -72,6 +73,12 @@ struct DwGroupPlan { int tile, whole, splits; size_t ws_bytes; };
 DwGroupPlan gemm_dw_group_plan(const GemmArgs* a, int n, int force_tile, size_t ws_limit);
 int launch_gemm_dw_group(const GemmArgs* a, int n, const DwGroupPlan& plan, hipStream_t s);
 bool gemm_dw_group_supported(const GemmArgs& a);
+// y = x W^T + bias for few rows (at most 48; bf16) with several weights, biases and outputs of the same shape in one launch;
+// a.B, a.bias and a.out are not used.
+constexpr int GEMM_BATCH_MAX = 16;
+struct GemmBatch { int n; const void* B[GEMM_BATCH_MAX]; const void* bias[GEMM_BATCH_MAX]; void* out[GEMM_BATCH_MAX]; };
+bool gemm_few_rows_supported(const GemmArgs& a);
+int launch_gemm_few_rows(const GemmArgs& a, const GemmBatch& batch, hipStream_t s);
 bool gemm_geglu_fwd_supported(const GemmArgs& a);
 bool gemm_colsum_supported(const GemmArgs& a);
 size_t gemm_splitk_ws_bytes(int M, int N, int K);   // upper bound for out_f32 GEMMs

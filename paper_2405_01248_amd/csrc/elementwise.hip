@@ -57,7 +57,7 @@ __global__ void __launch_bounds__(256) ln_fwd_kernel(int rows, int d, float eps,
     if (col < d) {
       if (sizeof(TX) == 4) load_f32<V>(reinterpret_cast<const float*>(xr + col), v[c]);
       else load_vec<T>(reinterpret_cast<const T*>(xr + col), v[c]);
-      if (sizeof(TX) != 4 && x32_out) store_f32<V>(x32_out + (size_t)row * d + col, v[c]);
+      if (x32_out) store_f32<V>(x32_out + (size_t)row * d + col, v[c]);
 #pragma unroll
       for (int i = 0; i < V; ++i) s += v[c][i];
     }
@@ -251,7 +251,7 @@ int launch_ln_fwd(const LnArgs& a, hipStream_t s) {
   if (int e = check_ln_dim(a.dtype, a.d)) return e;
   if ((a.gamma == nullptr) != (a.beta == nullptr) || (a.scale == nullptr) != (a.shift == nullptr))
     return set_error(DP_EINVAL, "ln_fwd: gamma/beta and scale/shift come in pairs");
-  if (a.x32_out && (a.x_f32 || a.dtype != BF16 || ((uintptr_t)a.x32_out % 16))) return set_error(DP_EINVAL, "ln_fwd: the widened copy goes with a bf16 input and a 16-byte aligned destination");
+  if (a.x32_out && ((a.x_f32 && a.dtype == BF16) || ((uintptr_t)a.x32_out % 16))) return set_error(DP_EINVAL, "ln_fwd: the fp32 copy goes with an input in the storage dtype and a 16-byte aligned destination");
   KScope ks(KK_LN_FWD, 0.0, a.rows * (double)a.d * (dtype_size(a.dtype) + (a.x_f32 ? 4 : dtype_size(a.dtype)) + (a.x32_out ? 4 : 0)) + 8.0 * a.rows, s, a.rows, a.d);
   if (a.dtype == BF16) return a.x_f32 ? ln_fwd_t<float, bf16>(a, s) : ln_fwd_t<bf16, bf16>(a, s);
   return ln_fwd_t<float, float>(a, s);

@@ -693,52 +693,6 @@ __global__ void __launch_bounds__(512, 2) gemm_pp_kernel(const GemmBf16Params p)
   pp_epilogue<T, KIND>(acc, smem_raw, p.epi, m0, n0, wave, wm, wn, lane);
 }
 
-// ------------------------------------------------------------------ fp32 FMA kernel
-struct GemmF32Params {
-  const float* A; const float* B;
-  int M, N, K, lda, ldb, a_mc, b_mc;
-  EpiParams<float> epi;
-};
-
-// 64x64 output tile, 16-deep k slices, 256 threads each owning a 4x4 micro-tile.
-__global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmF32Params p) {
-  __shared__ float As[16][65];
-  __shared__ float Bs[16][65];
-  const int tid = threadIdx.x;
-  const int tm = (tid / 16) * 4, tn = (tid % 16) * 4;
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < p.K; k0 += 16) {
-    for (int i = tid; i < 64 * 16; i += 256) {
-      const int kk = i % 16, r = i / 16;
-      const int gm = m0 + r, gn = n0 + r, gk = k0 + kk;
-      float a = 0.f, b = 0.f;
-      if (gk < p.K) {
-        if (gm < p.M) a = p.a_mc ? p.A[(size_t)gk * p.lda + gm] : p.A[(size_t)gm * p.lda + gk];
-        if (gn < p.N) b = p.b_mc ? p.B[(size_t)gk * p.ldb + gn] : p.B[(size_t)gn * p.ldb + gk];
-      }
-      As[kk][r] = a;
-      Bs[kk][r] = b;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      float a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) { a[i] = As[kk][tm + i]; b[i] = Bs[kk][tn + i]; }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) epi_store<float>(p.epi, m0 + tm + i, n0 + tn + j, acc[i][j]);
-}
-
 // Second pass of a split-K GEMM with a storage-dtype output: sums the fp32 partial tiles in ascending
 // split order (fixed order, run-to-run identical) and applies the GEMM's epilogue to the sums.  One thread
 // per 8 consecutive columns of a row.
@@ -855,28 +809,35 @@ static int choose_splits_epi(long tiles, int kt) {
   return s;
 }
 
+// Split-K factor of a storage-dtype GEMM on 128x128 tiles (configuration 13) and its estimated time in us: rounds of 256
+// workgroups plus, where it is split, a second launch and the partial sums' traffic.  A stage on a small local batch (1024 rows,
+// 72 tiles, contractions of 3456 or 4608) spends 28-36 us in one of these projections unsplit, 22-27 us split by 3.  ln: the
+// second launch also does the LayerNorm that would otherwise be one of its own.
+static int splits_128(int rows, int N, int K, bool ln, float* us) {
+  const long tiles = (long)((rows + 127) / 128) * ((N + 127) / 128);
+  const int kt = K / 64;
+  int best = 1;
+  for (int s = 1; s <= 8 && (s == 1 || kt / s >= 6); ++s) {
+    const float t = (float)((tiles * s + kCUs - 1) / kCUs) * (4.0f + (float)((kt + s - 1) / s) * 0.45f) +
+                    (s > 1 ? (ln ? 0.5f : 5.0f) + (float)(s + 2) * (float)rows * (float)N * 1.5e-6f : 0.0f);
+    if (s == 1 || t < *us) { best = s; *us = t; }
+  }
+  return best;
+}
+
 // The same when the choice is made for `choice_rows` rows (GemmArgs::choice_rows) but M rows are computed.
 size_t gemm_epi_splitk_ws_bytes_for(int M, int N, int K, int choice_rows) {
-  size_t worst = 0;
+  float us;
+  int sp = std::max(1, std::max(splits_128(choice_rows, N, K, false, &us), splits_128(choice_rows, N, K, true, &us)));
   const int shapes[][2] = {{64, 64}, {128, 128}, {256, 128}, {256, 256}};
   for (const auto& t : shapes) {
     const long tiles = (long)((choice_rows + t[0] - 1) / t[0]) * ((N + t[1] - 1) / t[1]);
-    const int sp = choose_splits_epi(tiles, K / 64);
-    if (sp > 1) worst = std::max(worst, (size_t)sp * M * N * sizeof(float));
+    sp = std::max(sp, choose_splits_epi(tiles, K / 64));
   }
-  return worst;
+  return sp > 1 ? (size_t)sp * M * N * sizeof(float) : 0;
 }
 
-size_t gemm_epi_splitk_ws_bytes(int M, int N, int K) {
-  size_t worst = 0;
-  const int shapes[][2] = {{64, 64}, {128, 128}, {256, 128}, {256, 256}};
-  for (const auto& t : shapes) {
-    const long tiles = (long)((M + t[0] - 1) / t[0]) * ((N + t[1] - 1) / t[1]);
-    const int sp = choose_splits_epi(tiles, K / 64);
-    if (sp > 1) worst = std::max(worst, (size_t)sp * M * N * sizeof(float));
-  }
-  return worst;
-}
+size_t gemm_epi_splitk_ws_bytes(int M, int N, int K) { return gemm_epi_splitk_ws_bytes_for(M, N, K, M); }
 
 // Picks the tile configuration (indices as in launch_gemm's switch), from sweeps of all GEMM shapes of
 // the five workloads on MI355X:
@@ -886,7 +847,7 @@ size_t gemm_epi_splitk_ws_bytes(int M, int N, int K) {
 //    direct-to-LDS tiles when they fill the CUs, else the register-staged kernel;
 //  - dW = dy^T x (both operands read through the transposing LDS load): register-staged 128x128 tiles,
 //    two workgroups per CU; 256x256 direct-to-LDS tiles for large M and N.
-static int choose_cfg(int M, int N, int K, bool a_mc, bool b_mc, bool dtl_ok, bool pp_ok, bool allow16 = true) {
+static int choose_cfg(int M, int N, int K, bool a_mc, bool b_mc, bool dtl_ok, bool pp_ok, bool allow16 = true, bool may_split = false, bool ln = false) {
   const long t256x256 = (long)((M + 255) / 256) * ((N + 255) / 256);
   const long t256x128 = (long)((M + 255) / 256) * ((N + 127) / 128);
   const bool dtl32 = dtl_ok && K % 32 == 0, dtl64 = dtl_ok && K % 64 == 0;
@@ -913,8 +874,15 @@ static int choose_cfg(int M, int N, int K, bool a_mc, bool b_mc, bool dtl_ok, bo
       if (c.pp ? !pp_ok : (c.need64 ? !dtl64 : !dtl32)) continue;
       if (c.idx == 20 && !allow16) continue;       // the 16x16x32 instruction sums a k-step of 32 at once: other bits than the 32x32x16 tiles
       const long tiles = (long)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
-      const float cost = (float)((tiles + kCUs - 1) / kCUs) * (c.fixed + (float)((K + 63) / 64) * c.per_kt);
+      float cost = (float)((tiles + kCUs - 1) / kCUs) * (c.fixed + (float)((K + 63) / 64) * c.per_kt);
+      if (c.idx == 13 && may_split) splits_128(M, N, K, ln, &cost);
       if (best < 0 || cost < best_cost) { best = c.idx; best_cost = cost; }
+    }
+    if (dtl64) {
+      // 64x64 tiles: up to three workgroups per CU; a k-tile costs 0.23 us while they have CUs to themselves, 0.39 us beside others
+      const long tiles = (long)((M + 63) / 64) * ((N + 63) / 64);
+      const float cost = 4.0f + (float)(K / 64) * (tiles <= 128 ? 0.23f : 0.39f * std::max(1.0f, (float)tiles / 512.0f));
+      if (cost < best_cost) best = 15;
     }
     if (best >= 0) return best;
     return t256x128 >= 128 ? 1 : 0;
@@ -1007,7 +975,9 @@ static int launch_dtl_cfg(const GemmArgs& a, hipStream_t s) {
     splits = choose_splits((long)p.tiles_m * p.tiles_n, kt * BK / 64, S::BYTES <= 80 * 1024 ? 2 * kCUs : kCUs);
   } else if (a.splitk_ws && a.geglu != 1) {
     const long rows_for_choice = a.choice_rows > 0 ? a.choice_rows : a.M;
+    float us;
     splits = a.choice_rows < 0 ? 1 : choose_splits_epi(((rows_for_choice + BM - 1) / BM) * p.tiles_n, kt * BK / 64);
+    if (a.choice_rows >= 0 && BM == 128 && BN == 128 && BK == 64) splits = splits_128((int)rows_for_choice, a.N, a.K, a.ln_out != nullptr, &us);
   }
   if (splits > 1) {
     const size_t need = (size_t)splits * a.M * a.N * sizeof(float);
@@ -1224,8 +1194,9 @@ static int launch_bf16_layout(const GemmArgs& a, hipStream_t s) {
   return launch_bf16_cfg<BM, BN, BK, WGM, WGN, true, false>(a, s);
 }
 
-// The bias gradient can ride in a weight-gradient GEMM when that GEMM runs on the register-staged kernel.
+// The bias gradient can ride in a weight-gradient GEMM when that GEMM runs on the register-staged kernel, or in fp32.
 bool gemm_colsum_supported(const GemmArgs& a) {
+  if (a.dtype == F32) return a.a_mc && a.out_f32;
   if (a.dtype != BF16 || !a.a_mc || !a.b_mc || !a.out_f32 || a.M % 8) return false;
   const int cfg = (a.force_cfg > 0) ? a.force_cfg - 1 : choose_cfg(a.M, a.N, a.K, true, true, dtl_addressable(a), false);
   return cfg >= 0 && cfg <= 5;
@@ -1267,7 +1238,8 @@ int launch_gemm(const GemmArgs& a, hipStream_t s) {
           return set_error(DP_EINVAL, "gemm: bad fused GeGLU backward arguments");
       }
     }
-    int cfg = (a.force_cfg > 0 && a.force_cfg <= kNumCfgs + 19) ? a.force_cfg - 1 : choose_cfg(a.choice_rows > 0 ? a.choice_rows : a.M, a.N, a.K, a.a_mc != 0, a.b_mc != 0, dtl_addressable(a), !a.out_f32 && pp_kind(a) >= 0, a.choice_rows >= 0);
+    const bool may_split = !a.out_f32 && a.splitk_ws && a.geglu != 1 && a.choice_rows >= 0;
+    int cfg = (a.force_cfg > 0 && a.force_cfg <= kNumCfgs + 19) ? a.force_cfg - 1 : choose_cfg(a.choice_rows > 0 ? a.choice_rows : a.M, a.N, a.K, a.a_mc != 0, a.b_mc != 0, dtl_addressable(a), !a.out_f32 && pp_kind(a) >= 0, a.choice_rows >= 0, may_split, a.ln_out != nullptr);
     // the column permutation of the fused GeGLU lives in the direct-to-LDS loaders, and in tiles with equal column halves
     if (a.geglu == 1 && (cfg < 6 || cfg == 11 || cfg == 15 || cfg == 16 || cfg > 18)) {
       const long t256x256 = (long)((a.M + 255) / 256) * ((a.N + 255) / 256);
@@ -1304,15 +1276,7 @@ int launch_gemm(const GemmArgs& a, hipStream_t s) {
     }
     return launch_bf16_layout<128, 128, 64, 2, 2>(a, s);
   }
-  GemmF32Params p;
-  p.A = (const float*)a.A; p.B = (const float*)a.B;
-  p.M = a.M; p.N = a.N; p.K = a.K; p.lda = a.lda; p.ldb = a.ldb; p.a_mc = a.a_mc; p.b_mc = a.b_mc;
-  p.epi = make_epi<float>(a);
-  dim3 grid((a.N + 63) / 64, (a.M + 63) / 64, 1);
-  KScope ks(KK_GEMM_F32, 2.0 * a.M * a.N * a.K, 4.0 * ((double)a.M * a.K + (double)a.N * a.K + (double)a.M * a.N), s, a.M, a.N, a.K);
-  hipLaunchKernelGGL(gemm_f32_kernel, grid, dim3(256), 0, s, p);
-  if (hipGetLastError() != hipSuccess) return set_error(DP_EHIP, "gemm(f32) launch failed");
-  return DP_OK;
+  return launch_gemm_f32(a, s);
 }
 
 }  // namespace dp

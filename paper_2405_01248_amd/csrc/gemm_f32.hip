@@ -1,0 +1,143 @@
+// fp32 GEMM (every operand layout) for the fp32 stages: small problems, so what counts is the time of one dependent launch.
+//
+// A workgroup owns a 32 x 32 tile of the output; its waves share the contraction in chunks of 16 and fetch their fragments straight
+// from global memory, several chunks in flight, for v_mfma_f32_16x16x4_f32 (full fp32 products and sums); the waves' partial tiles
+// are added through LDS in ascending order.  Against a tile walked 16 contraction steps at a time through LDS by all waves, each step two
+// barriers and a memory round trip deep: 128 x 64 x 64 13 -> 5 us, 64 x 256 x 128 (a weight gradient) 24 -> 5 us.
+#include "dp_kernels.h"
+#include "dp_errors.h"
+#include "dp_host.h"
+#include "dp_ktime.h"
+#include "dp_gemm_epilogue.h"
+
+namespace dp {
+
+struct GemmF32Params {
+  const float* A; const float* B;
+  int M, N, K, lda, ldb;
+  float* colsum; int colsum_acc;      // A contraction-strided: sum of A over the contraction, per row of the output
+  EpiParams<float> epi;
+};
+
+template <int NW, bool A_MC, bool B_MC>
+__global__ void __launch_bounds__(NW * 64) gemm_f32_kernel(const GemmF32Params p) {
+  constexpr int U = 4;                // chunks in flight per wave
+  __shared__ float red[NW][32][33];
+  __shared__ float csred[NW][32];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l16 = lane & 15, q = lane >> 4;
+  const int m0 = blockIdx.y * 32, n0 = blockIdx.x * 32, chunks = (p.K + 15) / 16;
+  f32x4 acc[2][2];
+  float cs[2] = {0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int am[2] = {min(m0 + l16, p.M - 1), min(m0 + 16 + l16, p.M - 1)};
+  const int bn[2] = {min(n0 + l16, p.N - 1), min(n0 + 16 + l16, p.N - 1)};
+  const bool do_cs = A_MC && p.colsum != nullptr && blockIdx.x == 0;
+  // a lane's four contraction values of chunk c: k = 16 c + 4 q + 0..3, the same for both operands
+  auto fetch = [&](const float* base, int ld, bool mc, int row, int c) {
+    const int k = c * 16 + 4 * q;
+    if (!mc) return *reinterpret_cast<const f32x4*>(base + (size_t)row * ld + min(k, p.K - 4));
+    f32x4 v;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) v[t] = base[(size_t)min(k + t, p.K - 1) * ld + row];
+    return v;
+  };
+  for (int c0 = wave; c0 < chunks; c0 += NW * U) {
+    f32x4 a[U][2], b[U][2];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int c = min(c0 + NW * u, chunks - 1);      // a chunk past the wave's last one is fetched, but not multiplied
+        a[u][i] = fetch(p.A, p.lda, A_MC, am[i], c);
+        b[u][i] = fetch(p.B, p.ldb, B_MC, bn[i], c);
+      }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int c = c0 + NW * u;
+      if (c >= chunks) continue;
+      if (c * 16 + 16 > p.K) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int t = 0; t < 4; ++t)
+            if (c * 16 + 4 * q + t >= p.K) { a[u][i][t] = 0.f; b[u][i][t] = 0.f; }
+      }
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][i][t], b[u][j][t], acc[i][j], 0, 0, 0);
+      if (do_cs) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) cs[i] += (a[u][i][0] + a[u][i][1]) + (a[u][i][2] + a[u][i][3]);
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) red[wave][16 * i + 4 * q + r][16 * j + l16] = acc[i][j][r];
+  if (do_cs) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      cs[i] += __shfl_xor(cs[i], 16, 64);
+      cs[i] += __shfl_xor(cs[i], 32, 64);
+      if (q == 0) csred[wave][16 * i + l16] = cs[i];
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < 1024 / (NW * 64); ++e) {
+    const int id = tid + e * NW * 64, r = id / 32, c = id % 32;
+    float v = red[0][r][c];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) v += red[w][r][c];
+    epi_store<float>(p.epi, m0 + r, n0 + c, v);
+  }
+  if (do_cs && tid < 32 && m0 + tid < p.M) {
+    float s = csred[0][tid];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) s += csred[w][tid];
+    float* o = p.colsum + m0 + tid;
+    *o = p.colsum_acc ? *o + s : s;
+  }
+}
+
+template <int NW>
+static void launch_f32(const GemmF32Params& p, int a_mc, int b_mc, hipStream_t s) {
+  const dim3 grid((p.N + 31) / 32, (p.M + 31) / 32), block(NW * 64);
+  if (a_mc && b_mc) hipLaunchKernelGGL((gemm_f32_kernel<NW, true, true>), grid, block, 0, s, p);
+  else if (a_mc) hipLaunchKernelGGL((gemm_f32_kernel<NW, true, false>), grid, block, 0, s, p);
+  else if (b_mc) hipLaunchKernelGGL((gemm_f32_kernel<NW, false, true>), grid, block, 0, s, p);
+  else hipLaunchKernelGGL((gemm_f32_kernel<NW, false, false>), grid, block, 0, s, p);
+}
+
+int launch_gemm_f32(const GemmArgs& a, hipStream_t s) {
+  // 16-byte loads along the contraction of an operand that has it contiguous
+  if ((!a.a_mc && (a.K % 4 || a.lda % 4 || (uintptr_t)a.A % 16)) || (!a.b_mc && (a.K % 4 || a.ldb % 4 || (uintptr_t)a.B % 16)))
+    return set_error(DP_EUNSUPPORTED, "gemm(f32): contraction-contiguous operands need K and leading dims that are multiples of 4 and 16-byte alignment");
+  if ((a.M + 31) / 32 > 65535) return set_error(DP_EUNSUPPORTED, "gemm(f32): too many rows");
+  GemmF32Params p;
+  p.A = (const float*)a.A; p.B = (const float*)a.B;
+  p.M = a.M; p.N = a.N; p.K = a.K; p.lda = a.lda; p.ldb = a.ldb; p.colsum = a.colsum_out; p.colsum_acc = a.accumulate;
+  EpiParams<float>& e = p.epi;
+  e = EpiParams<float>();
+  e.M = a.M; e.N = a.N; e.out = (float*)a.out; e.ldo = a.ldo; e.out32 = a.out_f32; e.ldo32 = a.ldo32; e.accumulate = a.accumulate;
+  e.bias = (const float*)a.bias; e.pre_out = (float*)a.pre_out; e.ld_pre = a.ld_pre; e.act = a.act;
+  e.dact_pre = (const float*)a.dact_pre; e.ld_dact = a.ld_dact; e.dact_kind = a.dact_kind;
+  e.gate = (const float*)a.gate; e.gate_ld = a.gate_ld; e.rows_per_batch = a.rows_per_batch > 0 ? a.rows_per_batch : 1;
+  e.residual = a.residual; e.ld_res = a.ld_res; e.out_scale = 1.0f;
+  KScope ks(KK_GEMM_F32, 2.0 * a.M * a.N * a.K, 4.0 * ((double)a.M * a.K + (double)a.N * a.K + (double)a.M * a.N), s, a.M, a.N, a.K);
+  // eight waves share a contraction that gives four of them more than two chunks each
+  if (a.K > 128) launch_f32<8>(p, a.a_mc, a.b_mc, s);
+  else launch_f32<4>(p, a.a_mc, a.b_mc, s);
+  return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "gemm(f32) launch failed");
+}
+
+}  // namespace dp

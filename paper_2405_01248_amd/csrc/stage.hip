@@ -220,8 +220,20 @@ struct StagePlan {
   void *pp0 = nullptr, *pp1 = nullptr, *pp2 = nullptr, *sc_in = nullptr;   // pp*: fp32 block inputs of a no-save forward
   std::vector<void*> mods;   // DiT, no-save forward: one modulation buffer per block (they are all computed up front)
   BwdScratch bs{};
+  float* splitk = nullptr; size_t splitk_bytes = 0;   // partial sums of the projections that are split along the contraction (small batches)
   size_t bytes = 0;
 };
+
+// Scratch of the forward's and, with save, the backward's activation projections.
+static size_t splitk_need(const dp_stage& s, bool save) {
+  if (s.es != 2) return 0;
+  const int T = s.T, d = s.d.d_model, ff = s.d.ff_inner;
+  const bool unet = s.d.kind == DP_BLOCK_UNET_XATTN_GEGLU;
+  size_t n = std::max(gemm_epi_splitk_ws_bytes(T, d, d), std::max(gemm_epi_splitk_ws_bytes(T, 3 * d, d), gemm_epi_splitk_ws_bytes(T, d, ff)));
+  if (!unet) n = std::max(n, gemm_epi_splitk_ws_bytes(T, ff, d));
+  if (save) n = std::max(n, std::max(gemm_epi_splitk_ws_bytes(T, d, 3 * d), std::max(gemm_epi_splitk_ws_bytes(T, d, unet ? 2 * ff : ff), gemm_epi_splitk_ws_bytes(T, ff, d))));
+  return n;
+}
 
 static void make_plan(const dp_stage& s, void* base, bool save, StagePlan& sp) {
   Plan p(base);
@@ -230,6 +242,8 @@ static void make_plan(const dp_stage& s, void* base, bool save, StagePlan& sp) {
   if (!unet) sp.sc_in = p.take((size_t)s.d.batch * s.d.d_model * s.es);
   if (unet) { sp.ub.resize(nb); for (int i = 0; i < nb; ++i) plan_unet_block(p, s, sp.ub[i], save); }
   else { sp.db.resize(nb); for (int i = 0; i < nb; ++i) plan_dit_block(p, s, sp.db[i], save); }
+  sp.splitk_bytes = splitk_need(s, save);
+  sp.splitk = sp.splitk_bytes ? (float*)p.take(sp.splitk_bytes) : nullptr;
   if (save) plan_bwd_scratch(p, s, sp.bs);
   else {
     const size_t rb = (size_t)s.T * s.d.d_model * 4;
@@ -369,44 +383,51 @@ static int record(ProfileHooks* ph, int idx, hipStream_t st) {
   return DP_OK;
 }
 
+// Scratch of the projections on the caller's stream that are split along the contraction (few rows, long contractions).
+struct SplitK {
+  float* ws; size_t bytes;
+  int launch(GemmArgs g, hipStream_t st) const { g.splitk_ws = ws; g.splitk_ws_bytes = bytes; return launch_gemm(g, st); }
+};
+
 // ============================================================ U-Net stage
 // x: fp32 block input.  y: fp32 (next block's input) unless y_is_out (storage dtype, the stage output).
 // kv_side: the context K/V projection of this block was issued on the side stream as batch kv_batch
 // of *kv_side (it depends on the context and the weights only); otherwise it is computed here.
-// x_storage (first block of a bf16 stage): the stage input in the storage dtype; the first LayerNorm reads it and
-// writes its rows widened to fp32 into x on the way, which saves a conversion pass over the input.
+// x_storage (first block): the stage input in the storage dtype; the first LayerNorm reads it and writes its rows in fp32
+// into x on the way, which saves a pass over the input.
 static int unet_block_fwd(const dp_stage& s, const void* const* P, const float* x, const void* ctx, void* y, bool y_is_out,
-                          UnetBuf& u, hipStream_t st, Side* kv_side = nullptr, int kv_batch = 0, const void* x_storage = nullptr) {
+                          UnetBuf& u, const SplitK& sk, hipStream_t st, Side* kv_side = nullptr, int kv_batch = 0, const void* x_storage = nullptr) {
   const int dt = s.d.dtype, T = s.T, Tc = s.Tc, d = s.d.d_model, inner = s.d.ff_inner, dc = s.d.ctx_dim;
   const size_t es = s.es;
+  auto proj = [&](const GemmArgs& g) { return sk.launch(g, st); };
   LnArgs ln; memset(&ln, 0, sizeof(ln));
   ln.dtype = dt; ln.rows = T; ln.d = d; ln.eps = s.d.ln_eps; ln.x_f32 = 1;
   // self-attention
   ln.x = x; ln.y = u.h1; ln.gamma = P[U_LN1_G]; ln.beta = P[U_LN1_B]; ln.mean = u.mean1; ln.rstd = u.rstd1;
-  if (x_storage) { ln.x = x_storage; ln.x_f32 = 0; ln.x32_out = const_cast<float*>(x); }
+  if (x_storage) { ln.x = x_storage; ln.x_f32 = dt == F32; ln.x32_out = const_cast<float*>(x); }
   DP_TRY(launch_ln_fwd(ln, st));
   ln.x_f32 = 1; ln.x32_out = nullptr;
-  DP_TRY(launch_gemm(gemm_fwd(dt, u.h1, T, d, P[U_WQKV], 3 * d, nullptr, u.qkv), st));
+  DP_TRY(proj(gemm_fwd(dt, u.h1, T, d, P[U_WQKV], 3 * d, nullptr, u.qkv)));
   AttnArgs a = attn_base(s);
   a.Nk = s.d.tokens; a.q = u.qkv; a.k = at(u.qkv, d, es); a.v = at(u.qkv, 2 * d, es); a.ldq = a.ldk = a.ldv = 3 * d;
   a.o = u.a1; a.ldo = d; a.lse = u.lse1;
   DP_TRY(launch_attn_fwd(a, st));
   GemmArgs g = gemm_fwd(dt, u.a1, T, d, P[U_WO1], d, P[U_BO1], u.x1);
   g.residual = x; g.ld_res = d; g.residual_f32 = 1; g.out_fused_f32 = 1;
-  DP_TRY(launch_gemm(g, st));
+  DP_TRY(proj(g));
   // cross-attention
   ln.x = u.x1; ln.y = u.h2; ln.gamma = P[U_LN2_G]; ln.beta = P[U_LN2_B]; ln.mean = u.mean2; ln.rstd = u.rstd2;
   DP_TRY(launch_ln_fwd(ln, st));
-  DP_TRY(launch_gemm(gemm_fwd(dt, u.h2, T, d, P[U_WQ2], d, nullptr, u.q2), st));
+  DP_TRY(proj(gemm_fwd(dt, u.h2, T, d, P[U_WQ2], d, nullptr, u.q2)));
   if (kv_side) kv_side->wait(kv_batch);
-  else DP_TRY(launch_gemm(gemm_fwd(dt, ctx, Tc, dc, P[U_WKV2], 2 * d, nullptr, u.kv2), st));
+  else DP_TRY(proj(gemm_fwd(dt, ctx, Tc, dc, P[U_WKV2], 2 * d, nullptr, u.kv2)));
   a = attn_base(s);
   a.Nk = s.d.ctx_tokens; a.q = u.q2; a.ldq = d; a.k = u.kv2; a.v = at(u.kv2, d, es); a.ldk = a.ldv = 2 * d;
   a.o = u.a2; a.ldo = d; a.lse = u.lse2;
   DP_TRY(launch_attn_fwd(a, st));
   g = gemm_fwd(dt, u.a2, T, d, P[U_WO2], d, P[U_BO2], u.x2);
   g.residual = u.x1; g.ld_res = d; g.residual_f32 = 1; g.out_fused_f32 = 1;
-  DP_TRY(launch_gemm(g, st));
+  DP_TRY(proj(g));
   // GeGLU feed-forward
   ln.x = u.x2; ln.y = u.h3; ln.gamma = P[U_LN3_G]; ln.beta = P[U_LN3_B]; ln.mean = u.mean3; ln.rstd = u.rstd3;
   DP_TRY(launch_ln_fwd(ln, st));
@@ -415,15 +436,15 @@ static int unet_block_fwd(const dp_stage& s, const void* const* P, const float* 
     GemmArgs f = gemm_fwd(dt, u.h3, T, d, P[U_W1], 2 * inner, P[U_B1], u.g);
     f.ldo = inner; f.pre_out = u.u; f.ld_pre = 2 * inner; f.geglu = 1; f.geglu_inner = inner;
     if ((s.fuse & 1) && gemm_geglu_fwd_supported(f)) {
-      DP_TRY(launch_gemm(f, st));
+      DP_TRY(proj(f));
     } else {
-      DP_TRY(launch_gemm(gemm_fwd(dt, u.h3, T, d, P[U_W1], 2 * inner, P[U_B1], u.u), st));
+      DP_TRY(proj(gemm_fwd(dt, u.h3, T, d, P[U_W1], 2 * inner, P[U_B1], u.u)));
       DP_TRY(launch_geglu_fwd(dt, u.u, u.g, T, inner, st));
     }
   }
   g = gemm_fwd(dt, u.g, T, inner, P[U_W2], d, P[U_B2], y);
   g.residual = u.x2; g.ld_res = d; g.residual_f32 = 1; g.out_fused_f32 = y_is_out ? 0 : 1;
-  DP_TRY(launch_gemm(g, st));
+  DP_TRY(proj(g));
   return DP_OK;
 }
 
@@ -432,10 +453,11 @@ static int unet_block_fwd(const dp_stage& s, const void* const* P, const float* 
 // dx_final in the storage dtype only).  `t`: the block's buffers; out_h: storage copy of the block's dx.
 // dy.f == nullptr: the upstream gradient exists in the storage dtype only (dy.h, the caller's tensor)
 static int unet_block_bwd(const dp_stage& s, const void* const* P, const void* const* WT, void* const* G, int acc, const void* ctx, GradPair dy, int c,
-                          void* dx_final, void* out_h, UnetBuf& u, BwdScratch& b, BwdSet& t, Side& sd, int* batch) {
+                          void* dx_final, void* out_h, UnetBuf& u, BwdScratch& b, BwdSet& t, const SplitK& sk, Side& sd, int* batch) {
   const int dt = s.d.dtype, T = s.T, Tc = s.Tc, d = s.d.d_model, inner = s.d.ff_inner, dc = s.d.ctx_dim;
   const size_t es = s.es;
   hipStream_t st = sd.main;
+  auto proj = [&](const GemmArgs& g) { return sk.launch(g, st); };
   const bool f32 = es == 4;
   const GradPair dx2{b.f[c ^ 1], f32 ? (void*)b.f[c ^ 1] : t.h[0]}, dx1{b.f[c], f32 ? (void*)b.f[c] : t.h[1]}, out{b.f[c ^ 1], out_h};
   auto gf = [&](int i) { return (float*)G[i]; };
@@ -447,13 +469,13 @@ static int unet_block_bwd(const dp_stage& s, const void* const* P, const void* c
     // dg = dy W2 never reaches memory: the GEMM epilogue turns it into du = [dg gelu(gate) | dg value gelu'(gate)]
     GemmArgs f = gemm_dx(dt, dy.h, T, d, P[U_W2], WT[U_W2], inner, t.du);
     f.ldo = 2 * inner; f.geglu = 2; f.geglu_inner = inner; f.geglu_u = u.u; f.ld_geglu = 2 * inner;
-    DP_TRY(launch_gemm(f, st));
+    DP_TRY(proj(f));
   } else {
-    DP_TRY(launch_gemm(gemm_dx(dt, dy.h, T, d, P[U_W2], WT[U_W2], inner, b.dg_raw), st));
+    DP_TRY(proj(gemm_dx(dt, dy.h, T, d, P[U_W2], WT[U_W2], inner, b.dg_raw)));
     DP_TRY(launch_geglu_bwd(dt, b.dg_raw, u.u, t.du, T, inner, st));
   }
   DP_TRY(bg.weight(t.du, T, 2 * inner, u.h3, d, gf(U_W1), gf(U_B1)));
-  DP_TRY(launch_gemm(gemm_dx(dt, t.du, T, 2 * inner, P[U_W1], WT[U_W1], d, b.dh), st));
+  DP_TRY(proj(gemm_dx(dt, t.du, T, 2 * inner, P[U_W1], WT[U_W1], d, b.dh)));
   LnBwdArgs lb; memset(&lb, 0, sizeof(lb));
   lb.dtype = dt; lb.rows = T; lb.d = d; lb.accumulate = acc;
   lb.dy = b.dh; lb.x = u.x2; lb.mean = u.mean3; lb.rstd = u.rstd3; lb.gamma = P[U_LN3_G]; set_dx(lb, dx2);
@@ -462,7 +484,7 @@ static int unet_block_bwd(const dp_stage& s, const void* const* P, const void* c
   DP_TRY(bg.layer_norm(lb, t.ln_partial[2]));
   // ---- cross-attention
   DP_TRY(bg.weight(dx2.h, T, d, u.a2, d, gf(U_WO2), gf(U_BO2)));
-  DP_TRY(launch_gemm(gemm_dx(dt, dx2.h, T, d, P[U_WO2], WT[U_WO2], d, b.da), st));
+  DP_TRY(proj(gemm_dx(dt, dx2.h, T, d, P[U_WO2], WT[U_WO2], d, b.da)));
   AttnArgs a = attn_base(s);
   a.Nk = s.d.ctx_tokens; a.q = u.q2; a.ldq = d; a.k = u.kv2; a.v = at(u.kv2, d, es); a.ldk = a.ldv = 2 * d;
   a.o = u.a2; a.ldo = d; a.lse = u.lse2; a.dout = b.da; a.lddo = d; a.delta = b.delta;
@@ -470,13 +492,13 @@ static int unet_block_bwd(const dp_stage& s, const void* const* P, const void* c
   a.dkv_ws = b.dkv_ws; a.dkv_ws_bytes = b.dkv_ws_bytes;
   DP_TRY(launch_attn_bwd(a, st));
   DP_TRY(bg.weight(t.dq2, T, d, u.h2, d, gf(U_WQ2), nullptr));
-  DP_TRY(launch_gemm(gemm_dx(dt, t.dq2, T, d, P[U_WQ2], WT[U_WQ2], d, b.dh), st));
+  DP_TRY(proj(gemm_dx(dt, t.dq2, T, d, P[U_WQ2], WT[U_WQ2], d, b.dh)));
   lb.dy = b.dh; lb.x = u.x1; lb.mean = u.mean2; lb.rstd = u.rstd2; lb.gamma = P[U_LN2_G]; lb.dres = dx2.f; lb.dres_storage = 0; set_dx(lb, dx1);
   lb.dgamma = gf(U_LN2_G); lb.dbeta = gf(U_LN2_B);
   DP_TRY(bg.layer_norm(lb, t.ln_partial[1]));
   // ---- self-attention
   DP_TRY(bg.weight(dx1.h, T, d, u.a1, d, gf(U_WO1), gf(U_BO1)));
-  DP_TRY(launch_gemm(gemm_dx(dt, dx1.h, T, d, P[U_WO1], WT[U_WO1], d, b.da), st));
+  DP_TRY(proj(gemm_dx(dt, dx1.h, T, d, P[U_WO1], WT[U_WO1], d, b.da)));
   a = attn_base(s);
   a.Nk = s.d.tokens; a.q = u.qkv; a.k = at(u.qkv, d, es); a.v = at(u.qkv, 2 * d, es); a.ldq = a.ldk = a.ldv = 3 * d;
   a.o = u.a1; a.ldo = d; a.lse = u.lse1; a.dout = b.da; a.lddo = d; a.delta = b.delta;
@@ -484,7 +506,7 @@ static int unet_block_bwd(const dp_stage& s, const void* const* P, const void* c
   DP_TRY(launch_attn_bwd(a, st));
   DP_TRY(bg.weight(t.dqkv, T, 3 * d, u.h1, d, gf(U_WQKV), nullptr));
   DP_TRY(bg.weight(t.dkv2, Tc, 2 * d, ctx, dc, gf(U_WKV2), nullptr));      // last: its contraction is the short one
-  DP_TRY(launch_gemm(gemm_dx(dt, t.dqkv, T, 3 * d, P[U_WQKV], WT[U_WQKV], d, b.dh), st));
+  DP_TRY(proj(gemm_dx(dt, t.dqkv, T, 3 * d, P[U_WQKV], WT[U_WQKV], d, b.dh)));
   lb.dy = b.dh; lb.x = u.xin; lb.mean = u.mean1; lb.rstd = u.rstd1; lb.gamma = P[U_LN1_G]; lb.dres = dx1.f;
   if (dx_final) { lb.dx = dx_final; lb.dx32 = nullptr; } else set_dx(lb, out);
   lb.dgamma = gf(U_LN1_G); lb.dbeta = gf(U_LN1_B);
@@ -498,21 +520,20 @@ static int unet_block_bwd(const dp_stage& s, const void* const* P, const void* c
 
 // ============================================================ DiT stage
 // save = false (the self-conditioning pass) skips the tensors only the backward reads.
-// mod_side: the modulation vectors of this block (they depend on the conditioning and the weights only) were
-// issued on the side stream as batch mod_batch of *mod_side; otherwise they are computed here.
+// have_mods: the modulation vectors of this block are there already.
 static int dit_block_fwd(const dp_stage& s, const void* const* P, const float* x, const void* sc_in, void* y, bool y_is_out,
-                         bool save, DitBuf& u, hipStream_t st, Side* mod_side = nullptr, int mod_batch = 0, const void* x_storage = nullptr) {
+                         bool save, DitBuf& u, const SplitK& sk, hipStream_t st, bool have_mods, const void* x_storage) {
   const int dt = s.d.dtype, T = s.T, d = s.d.d_model, ff = s.d.ff_inner, B = s.d.batch, N = s.d.tokens;
   const size_t es = s.es;
-  if (mod_side) mod_side->wait(mod_batch);
-  else DP_TRY(launch_gemm(gemm_fwd(dt, sc_in, B, d, P[D_ADA_W], 6 * d, P[D_ADA_B], u.m), st));
+  auto proj = [&](const GemmArgs& g) { return sk.launch(g, st); };
+  if (!have_mods) DP_TRY(proj(gemm_fwd(dt, sc_in, B, d, P[D_ADA_W], 6 * d, P[D_ADA_B], u.m)));
   LnArgs ln; memset(&ln, 0, sizeof(ln));
   ln.dtype = dt; ln.rows = T; ln.d = d; ln.eps = s.d.ln_eps; ln.mod_ld = 6 * d; ln.rows_per_batch = N; ln.x_f32 = 1;
   ln.x = x; ln.y = u.h1; ln.shift = u.m; ln.scale = at(u.m, d, es); ln.mean = u.mean1; ln.rstd = u.rstd1;
-  if (x_storage) { ln.x = x_storage; ln.x_f32 = 0; ln.x32_out = const_cast<float*>(x); }     // see unet_block_fwd
+  if (x_storage) { ln.x = x_storage; ln.x_f32 = dt == F32; ln.x32_out = const_cast<float*>(x); }     // see unet_block_fwd
   DP_TRY(launch_ln_fwd(ln, st));
   ln.x_f32 = 1; ln.x32_out = nullptr;
-  DP_TRY(launch_gemm(gemm_fwd(dt, u.h1, T, d, P[D_WQKV], 3 * d, P[D_BQKV], u.qkv), st));
+  DP_TRY(proj(gemm_fwd(dt, u.h1, T, d, P[D_WQKV], 3 * d, P[D_BQKV], u.qkv)));
   AttnArgs a = attn_base(s);
   a.Nk = N; a.q = u.qkv; a.k = at(u.qkv, d, es); a.v = at(u.qkv, 2 * d, es); a.ldq = a.ldk = a.ldv = 3 * d;
   a.o = u.a; a.ldo = d; a.lse = u.lse;
@@ -520,26 +541,27 @@ static int dit_block_fwd(const dp_stage& s, const void* const* P, const float* x
   GemmArgs g = gemm_fwd(dt, u.a, T, d, P[D_WO], d, P[D_BO], u.x1);
   g.pre_out = save ? u.o : nullptr; g.ld_pre = d; g.gate = at(u.m, 2 * d, es); g.gate_ld = 6 * d; g.rows_per_batch = N;
   g.residual = x; g.ld_res = d; g.residual_f32 = 1; g.out_fused_f32 = 1;
-  DP_TRY(launch_gemm(g, st));
+  DP_TRY(proj(g));
   ln.x = u.x1; ln.y = u.h2; ln.shift = at(u.m, 3 * d, es); ln.scale = at(u.m, 4 * d, es); ln.mean = u.mean2; ln.rstd = u.rstd2;
   DP_TRY(launch_ln_fwd(ln, st));
   g = gemm_fwd(dt, u.h2, T, d, P[D_FC1_W], ff, P[D_FC1_B], u.f);
   g.pre_out = save ? u.f1 : nullptr; g.ld_pre = ff; g.act = s.d.gelu_tanh ? 2 : 1;
-  DP_TRY(launch_gemm(g, st));
+  DP_TRY(proj(g));
   g = gemm_fwd(dt, u.f, T, ff, P[D_FC2_W], d, P[D_FC2_B], y);
   g.pre_out = save ? u.f2 : nullptr; g.ld_pre = d; g.gate = at(u.m, 5 * d, es); g.gate_ld = 6 * d; g.rows_per_batch = N;
   g.residual = u.x1; g.ld_res = d; g.residual_f32 = 1; g.out_fused_f32 = y_is_out ? 0 : 1;
-  DP_TRY(launch_gemm(g, st));
+  DP_TRY(proj(g));
   return DP_OK;
 }
 
-// dy lives in f[c]; dx1 goes to f[c ^ 1] and the block's dx back to f[c] (or, in the storage dtype, to dx_final).
+// dy: fp32, f[c] or the caller's tensor; dx1 goes to f[c ^ 1] and the block's dx back to f[c] (or, in the storage dtype, to dx_final).
 static int dit_block_bwd(const dp_stage& s, const void* const* P, const void* const* WT, void* const* G, int acc, const void* cond, const void* sc_in,
-                         int c, void* dx_final, float* d_cond, int dcond_acc, DitBuf& u, BwdScratch& b, BwdSet& t, Side& sd, int* batch) {
+                         const float* dy, int c, void* dx_final, float* d_cond, int dcond_acc, DitBuf& u, BwdScratch& b, BwdSet& t, const SplitK& sk, Side& sd, int* batch) {
   const int dt = s.d.dtype, T = s.T, d = s.d.d_model, ff = s.d.ff_inner, B = s.d.batch, N = s.d.tokens;
   const size_t es = s.es;
   hipStream_t st = sd.main;
-  float *dy = b.f[c], *dx1 = b.f[c ^ 1], *dm = t.dmv;
+  auto proj = [&](const GemmArgs& g) { return sk.launch(g, st); };
+  float *dx1 = b.f[c ^ 1], *dm = t.dmv;
   auto gf = [&](int i) { return (float*)G[i]; };
   BlockGrads bg(s, b, st, acc);
   // ---- MLP branch
@@ -547,9 +569,9 @@ static int dit_block_bwd(const dp_stage& s, const void* const* P, const void* co
   DP_TRY(bg.weight(t.dg, T, d, u.f, ff, gf(D_FC2_W), gf(D_FC2_B)));
   GemmArgs g = gemm_dx(dt, t.dg, T, d, P[D_FC2_W], WT[D_FC2_W], ff, t.du);
   g.dact_pre = u.f1; g.ld_dact = ff; g.dact_kind = s.d.gelu_tanh ? 2 : 1;
-  DP_TRY(launch_gemm(g, st));
+  DP_TRY(proj(g));
   DP_TRY(bg.weight(t.du, T, ff, u.h2, d, gf(D_FC1_W), gf(D_FC1_B)));
-  DP_TRY(launch_gemm(gemm_dx(dt, t.du, T, ff, P[D_FC1_W], WT[D_FC1_W], d, b.dh), st));
+  DP_TRY(proj(gemm_dx(dt, t.du, T, ff, P[D_FC1_W], WT[D_FC1_W], d, b.dh)));
   LnBwdArgs lb; memset(&lb, 0, sizeof(lb));
   lb.dtype = dt; lb.rows = T; lb.d = d;
   lb.mod_ld = 6 * d; lb.rows_per_batch = N; lb.dmod_ld = 6 * d;
@@ -559,14 +581,14 @@ static int dit_block_bwd(const dp_stage& s, const void* const* P, const void* co
   // ---- attention branch
   DP_TRY(launch_gate_bwd(dt, dx1, u.o, at(u.m, 2 * d, es), 6 * d, t.dg2, dm + 2 * d, 6 * d, B, N, d, st));
   DP_TRY(bg.weight(t.dg2, T, d, u.a, d, gf(D_WO), gf(D_BO)));
-  DP_TRY(launch_gemm(gemm_dx(dt, t.dg2, T, d, P[D_WO], WT[D_WO], d, b.da), st));
+  DP_TRY(proj(gemm_dx(dt, t.dg2, T, d, P[D_WO], WT[D_WO], d, b.da)));
   AttnArgs a = attn_base(s);
   a.Nk = N; a.q = u.qkv; a.k = at(u.qkv, d, es); a.v = at(u.qkv, 2 * d, es); a.ldq = a.ldk = a.ldv = 3 * d;
   a.o = u.a; a.ldo = d; a.lse = u.lse; a.dout = b.da; a.lddo = d; a.delta = b.delta;
   a.dq = t.dqkv; a.dk = at(t.dqkv, d, es); a.dv = at(t.dqkv, 2 * d, es); a.lddq = a.lddk = a.lddv = 3 * d;
   DP_TRY(launch_attn_bwd(a, st));
   DP_TRY(bg.weight(t.dqkv, T, 3 * d, u.h1, d, gf(D_WQKV), gf(D_BQKV)));
-  DP_TRY(launch_gemm(gemm_dx(dt, t.dqkv, T, 3 * d, P[D_WQKV], WT[D_WQKV], d, b.dh), st));
+  DP_TRY(proj(gemm_dx(dt, t.dqkv, T, 3 * d, P[D_WQKV], WT[D_WQKV], d, b.dh)));
   lb.dy = b.dh; lb.x = u.xin; lb.mean = u.mean1; lb.rstd = u.rstd1; lb.scale = at(u.m, d, es); lb.dres = dx1;
   if (dx_final) { lb.dx = dx_final; lb.dx32 = nullptr; } else lb.dx32 = b.f[c];
   lb.dscale = dm + d; lb.dshift = dm;
@@ -615,6 +637,7 @@ static int run_stage_fwd(dp_stage* s, const void* const* params, const void* x, 
                          hipStream_t st, ProfileHooks* ph) {
   StagePlan sp;
   make_plan(*s, ws, save != 0, sp);
+  const SplitK sk{sp.splitk, sp.splitk_bytes};
   const bool unet = s->d.kind == DP_BLOCK_UNET_XATTN_GEGLU;
   const int nb = s->d.n_blocks;
   const size_t act = (size_t)s->T * s->d.d_model;
@@ -623,30 +646,35 @@ static int run_stage_fwd(dp_stage* s, const void* const* params, const void* x, 
   float* cur = (float*)(save ? (unet ? sp.ub[0].xin : sp.db[0].xin) : sp.pp2);
   // U-Net, saving pass (one K/V buffer per block): the context projections of all blocks run on the
   // side stream while the main stream works through block 0's self-attention
-  // DiT: likewise the modulation vectors m = SiLU(cond) W_ada^T + b_ada of all blocks (32 rows each: latency, not work);
-  // not while profiling, where each block's row has to hold its own projection
   Side sd;
-  sd.main = st; sd.on = s->overlap && s->es == 2 && (unet ? save != 0 : ph == nullptr);
+  sd.main = st; sd.on = s->overlap && s->es == 2 && unet && save != 0;
   int kv_batch = 0;
-  std::vector<int> mod_batch((size_t)nb, 0);
   if (sd.on) {
     DP_TRY(ensure_side_stream(s));
     sd.side = s->side; sd.ev = &s->events;
     hipStream_t q = sd.begin();
     for (int b = 0; b < nb; ++b) {
       const void* const* P = params + (size_t)b * s->per_block;
-      if (unet) DP_TRY(launch_gemm(gemm_fwd(s->d.dtype, cc, s->Tc, s->d.ctx_dim, P[U_WKV2], 2 * s->d.d_model, nullptr, sp.ub[b].kv2), q));
-      else {
-        DP_TRY(launch_gemm(gemm_fwd(s->d.dtype, sp.sc_in, s->d.batch, s->d.d_model, P[D_ADA_W], 6 * s->d.d_model, P[D_ADA_B],
-                                    save ? sp.db[b].m : sp.mods[b]), q));
-        mod_batch[b] = sd.end();      // a block waits for its own vectors only
-      }
+      DP_TRY(launch_gemm(gemm_fwd(s->d.dtype, cc, s->Tc, s->d.ctx_dim, P[U_WKV2], 2 * s->d.d_model, nullptr, sp.ub[b].kv2), q));
     }
-    if (unet) kv_batch = sd.end();
+    kv_batch = sd.end();
   }
-  // bf16 stages: the first block's first LayerNorm widens the input on its way (one pass less over it)
-  const bool widen_in_ln = s->d.dtype == DP_BF16;
-  if (!widen_in_ln) DP_TRY(launch_cast_to_f32(s->d.dtype, x, cur, act, st));
+  // DiT: the modulation vectors m = SiLU(cond) W_ada^T + b_ada of all blocks are as many rows as the batch has samples: one launch
+  // reads the blocks' weights together (not while profiling, where each block's row has to hold its own projection)
+  bool mods = false;
+  if (!unet && !ph) {
+    GemmArgs g = gemm_fwd(s->d.dtype, sp.sc_in, s->d.batch, s->d.d_model, nullptr, 6 * s->d.d_model, nullptr, nullptr);
+    mods = gemm_few_rows_supported(g);
+    for (int b0 = 0; mods && b0 < nb; b0 += GEMM_BATCH_MAX) {
+      GemmBatch bt;
+      bt.n = std::min(nb - b0, GEMM_BATCH_MAX);
+      for (int i = 0; i < bt.n; ++i) {
+        const void* const* P = params + (size_t)(b0 + i) * s->per_block;
+        bt.B[i] = P[D_ADA_W]; bt.bias[i] = P[D_ADA_B]; bt.out[i] = save ? sp.db[b0 + i].m : sp.mods[b0 + i];
+      }
+      DP_TRY(launch_gemm_few_rows(g, bt, st));
+    }
+  }
   for (int b = 0; b < nb; ++b) {
     DP_TRY(record(ph, b, st));
     const void* const* P = params + (size_t)b * s->per_block;
@@ -656,12 +684,12 @@ static int run_stage_fwd(dp_stage* s, const void* const* params, const void* x, 
     else if (save) out = unet ? sp.ub[b + 1].xin : sp.db[b + 1].xin;
     else out = (b & 1) ? sp.pp1 : sp.pp0;
     const int slot = save ? b : 0;
-    const void* xs = (b == 0 && widen_in_ln) ? x : nullptr;
-    if (unet) DP_TRY(unet_block_fwd(*s, P, cur, cc, out, last, sp.ub[slot], st, sd.on ? &sd : nullptr, kv_batch, xs));
+    const void* xs = b == 0 ? x : nullptr;
+    if (unet) DP_TRY(unet_block_fwd(*s, P, cur, cc, out, last, sp.ub[slot], sk, st, sd.on ? &sd : nullptr, kv_batch, xs));
     else {
       DitBuf ub = sp.db[slot];
       if (!save) ub.m = sp.mods[b];
-      DP_TRY(dit_block_fwd(*s, P, cur, sp.sc_in, out, last, save != 0, ub, st, sd.on ? &sd : nullptr, mod_batch[b], xs));
+      DP_TRY(dit_block_fwd(*s, P, cur, sp.sc_in, out, last, save != 0, ub, sk, st, mods, xs));
     }
     cur = (float*)out;
   }
@@ -674,6 +702,7 @@ static int run_stage_bwd(dp_stage* s, const void* const* params, const void* dy,
                          void* const* dparams, int acc, void* ws, hipStream_t st, ProfileHooks* ph) {
   StagePlan sp;
   make_plan(*s, ws, true, sp);
+  const SplitK sk{sp.splitk, sp.splitk_bytes};
   const bool unet = s->d.kind == DP_BLOCK_UNET_XATTN_GEGLU;
   const int nb = s->d.n_blocks;
   BwdScratch& bs = sp.bs;
@@ -700,11 +729,10 @@ static int run_stage_bwd(dp_stage* s, const void* const* params, const void* dy,
       if (tb.n + nw > kTransposeMax || b == nb - 1) { DP_TRY(launch_transpose16_batch(tb, st)); tb.n = 0; }
     }
   }
-  // dy as a gradient pair: the caller's tensor as GEMM operand; an fp32 copy only where a kernel of the
-  // last block wants one (the U-Net block reads dy in the storage dtype everywhere)
-  const bool widen = !unet || s->es == 4;
-  if (widen) DP_TRY(launch_cast_to_f32(s->d.dtype, dy, bs.f[1], (size_t)s->T * s->d.d_model, st));
-  GradPair cur{widen ? bs.f[1] : nullptr, const_cast<void*>(dy)};
+  // dy as a gradient pair: the caller's tensor as GEMM operand and, in fp32 stages, as the running sum; a widened copy only
+  // where a kernel of the last block wants one (the U-Net block reads dy in the storage dtype everywhere)
+  if (!unet && s->es == 2) DP_TRY(launch_cast_to_f32(s->d.dtype, dy, bs.f[1], (size_t)s->T * s->d.d_model, st));
+  GradPair cur{s->es == 4 ? (float*)const_cast<void*>(dy) : (unet ? nullptr : bs.f[1]), const_cast<void*>(dy)};
   int ci = 1;   // index of the fp32 buffer that holds cur
   int batch[2] = {0, 0};      // last side batch that reads each of the two buffer sets
   for (int i = 0; i < nb; ++i) {
@@ -717,11 +745,11 @@ static int run_stage_bwd(dp_stage* s, const void* const* params, const void* dy,
     void* const* G = dparams + (size_t)b * s->per_block;
     void* dx_final = b == 0 ? dx : nullptr;
     if (unet) {
-      DP_TRY(unet_block_bwd(*s, P, WT, G, acc, cc, cur, ci, dx_final, bs.out_h[i % 3], sp.ub[b], bs, bs.set[i & 1], sd, &batch[i & 1]));
+      DP_TRY(unet_block_bwd(*s, P, WT, G, acc, cc, cur, ci, dx_final, bs.out_h[i % 3], sp.ub[b], bs, bs.set[i & 1], sk, sd, &batch[i & 1]));
       ci ^= 1;
       cur = GradPair{bs.f[ci], s->es == 4 ? (void*)bs.f[ci] : bs.out_h[i % 3]};
     } else {
-      DP_TRY(dit_block_bwd(*s, P, WT, G, acc, cc, sp.sc_in, ci, dx_final, (float*)d_cond, i != 0, sp.db[b], bs, bs.set[i & 1], sd, &batch[i & 1]));
+      DP_TRY(dit_block_bwd(*s, P, WT, G, acc, cc, sp.sc_in, i == 0 ? cur.f : bs.f[ci], ci, dx_final, (float*)d_cond, i != 0, sp.db[b], bs, bs.set[i & 1], sk, sd, &batch[i & 1]));
     }
     if (ph && ph->ev) sd.wait(sd.issued);      // per-block timing: charge a block's side work to that block
   }

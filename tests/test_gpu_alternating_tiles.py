@@ -32,3 +32,40 @@ def test_fp8_tiles(M, N, K):
     # 256, 192 and 128 columns wide, ragged on both sides
     import test_gpu_ops
     test_gpu_ops.test_fp8_gemm_matches_oracle(M, N, K)
+
+
+@pytest.mark.parametrize("batch", [1, 16, 17, 40, 49])
+def test_dit_stage_by_batch_size(batch):
+    # the modulation projections: 1, 2, 3 row tiles of the few-rows kernel, one launch for all blocks, and the tile kernels beyond
+    import numpy as np
+    import torch
+    import synth_inputs as si
+    from oracle import blocks
+    from paper_2405_01248_amd.harness import DeviceStage, rel_err
+    cfg = si.StageConfig("dit_batch", si.DIT, "bf16", 2, batch, 8, 160, 2, 80, 0, 0, 320, 1e-6, 1)
+    inp = si.make_stage_inputs(cfg, seed=batch)
+    ds = DeviceStage(cfg, inp)
+    ds.step()
+    torch.cuda.synchronize()
+    got = ds.results()
+    y, caches = blocks.stage_fwd(cfg.kind, inp["params"], inp["x"], inp["cond"], cfg.n_blocks, cfg.n_heads, cfg.ln_eps, gelu_tanh=True)
+    e = rel_err(got["y"], y)
+    assert np.isfinite(got["y"]).all() and e <= TOL_BF16, e
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 4, 4), (32, 32, 16), (33, 36, 20), (65, 68, 132), (40, 96, 260)])
+@pytest.mark.parametrize("layout", ["nt", "nn", "tn"])
+def test_f32_gemm(layout, M, N, K):
+    import numpy as np
+    import torch
+    from paper_2405_01248_amd import binding as B
+    a_k, b_k = {"nt": (0, 0), "nn": (0, 1), "tn": (1, 1)}[layout]
+    rng = np.random.default_rng(M + K)
+    A, Bm = rng.standard_normal((M, K)).astype(np.float32), rng.standard_normal((K, N)).astype(np.float32)
+    dA = torch.from_numpy(np.ascontiguousarray(A.T if a_k else A)).cuda()
+    dB = torch.from_numpy(np.ascontiguousarray(Bm if b_k else Bm.T)).cuda()
+    out = torch.zeros((M, N), device="cuda")
+    B.op_gemm(B.DP_F32, dA, dA.shape[1], a_k, dB, dB.shape[1], b_k, M, N, K, None, out, N, layout == "tn")
+    torch.cuda.synchronize()
+    ref = A.astype(np.float64) @ Bm.astype(np.float64)
+    assert float(np.abs(out.cpu().numpy() - ref).max() / np.abs(ref).max()) <= 1e-5
