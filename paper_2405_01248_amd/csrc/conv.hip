@@ -25,7 +25,7 @@ struct ConvParams {
   int M, N, K;                   // output pixels, output channels, 9 * C_in
   int tiles_m, tiles_n, group_m;
   int taps_uniform;              // C_in % 64 == 0: a 64-deep k-tile lies inside one filter tap
-  float* gn_partial;             // direct-to-LDS kernel: per-(256-pixel block, channel) sum and sum of squares of the output, or nullptr
+  float* gn_partial; int gn_block;   // per (block of gn_block pixels, channel): sum and sum of squares of the output, or nullptr
   EpiParams<bf16> epi;
 };
 
@@ -154,9 +154,88 @@ __global__ void __launch_bounds__(WGM * WGN * 64) conv3x3_bf16_kernel(const Conv
 // Measured on the 256 -> 256 channel layers at 256 x 256 pixels, 8 samples: see launch_conv3x3.
 //
 // Epilogue: bias, optional residual, bf16 store and, if asked, the first pass of a GroupNorm over the output: per channel the
-// sum and the sum of squares of the stored (rounded) values over 256 pixels.  They are formed in an order that no tile shape
+// sum and the sum of squares of the stored (rounded) values over a block of pixels (ConvParams::gn_block).  They are formed in an order that no tile shape
 // changes: in a band of 32 rows, the rows with equal r % 8 in ascending order, these eight sums pairwise by the bits of
-// r from the lowest up, then the eight bands in ascending order.
+// r from the lowest up, then the block's bands in ascending order.
+// Byte offset of the input pixel at the tap centre of output pixel m0 + row, plus this lane's 16-byte chunk of the tile row `row`, and
+// the 9-bit set of taps that fall inside the image for that pixel (empty for rows past M).
+__device__ __forceinline__ void conv_pixel(const ConvParams& p, int m0, int row, int lane, int& base, unsigned& taps) {
+  const int gm = m0 + row, q = min(gm, p.M - 1), c = pp_piece_chunk(row, lane);
+  const int b = q / (p.Ho * p.Wo), rem = q - b * (p.Ho * p.Wo), ho = rem / p.Wo, wo = rem - ho * p.Wo;
+  const int hc = ho * p.stride, wc = wo * p.stride;
+  base = (int)(2u * ((uint32_t)((b * p.H + hc) * p.W + wc) * (uint32_t)p.Cin + (uint32_t)c * 8u));
+  unsigned m = 0;
+#pragma unroll
+  for (int tap = 0; tap < 9; ++tap) {
+    const int hi = hc + tap / 3 - 1, wi = wc + tap % 3 - 1;
+    m |= (unsigned)((unsigned)hi < (unsigned)p.H && (unsigned)wi < (unsigned)p.W) << tap;
+  }
+  taps = gm < p.M ? m : 0u;
+}
+
+// Epilogue of one band: the 32 rows x W columns of fp32 values at Cw.  row0, col0: output row and column of the band; column(lc): the
+// output column of slab column lc, relative to col0 (and to stat).  stat: where the band's sums go, the sums of squares ld later.
+template <int W, class Column>
+__device__ __forceinline__ void conv_band_epilogue(const ConvParams& p, const float* Cw, int c_ld, int row0, int col0, int lane, float* stat, int ld,
+                                                   Column column) {
+  constexpr int CH = W / 8, RPI = 64 / CH, NIT = 32 / RPI;      // rows per pass over the band and passes
+  static_assert(RPI == 4 || RPI == 8 || RPI == 16, "band shape");
+  const EpiParams<bf16>& e = p.epi;
+  const int lc = (lane % CH) * 8, lr = lane / CH, nt = column(lc), n = col0 + nt;
+  float bias[8];
+  pp_bias(e.bias, min(n, e.N - 8), bias);
+  bf16x8 o[NIT];
+#pragma unroll
+  for (int it = 0; it < NIT; ++it)
+    o[it] = e.residual ? *reinterpret_cast<const bf16x8*>((const bf16*)e.residual + (size_t)min(row0 + it * RPI + lr, e.M - 1) * e.ld_res + min(n, e.N - 8)) : zero8();
+#pragma unroll
+  for (int it = 0; it < NIT; ++it) {
+    const int m = row0 + it * RPI + lr;
+    float v[8];
+    pp_slab_row(&Cw[(it * RPI + lr) * c_ld + lc], v);
+#pragma unroll
+    for (int t = 0; t < 8; ++t) o[it][t] = (bf16)((v[t] + bias[t]) + (float)o[it][t]);
+    if (m < e.M && n < e.N) *reinterpret_cast<bf16x8*>(e.out + (size_t)m * e.ldo + n) = o[it];
+  }
+  if (!p.gn_partial) return;      // otherwise every row exists
+  // sums over the rows with equal r % 8, ascending; then pairwise over the bits of r % 8
+  constexpr int SETS = RPI == 4 ? 2 : 1;
+#pragma unroll
+  for (int t = 0; t < 8; ++t) {
+    float cs[SETS], cq[SETS];
+#pragma unroll
+    for (int a = 0; a < SETS; ++a) { cs[a] = 0.f; cq[a] = 0.f; }
+#pragma unroll
+    for (int it = 0; it < NIT; ++it) {
+      const float f = (float)o[it][t];
+      cs[it % SETS] += f; cq[it % SETS] = fmaf(f, f, cq[it % SETS]);
+      if constexpr (RPI == 16) {      // rows lr and lr + 8 of this pass lie in different lanes (the upper one's sums are not used)
+        const float h = __shfl_xor(f, 8 * CH, 64);
+        cs[0] += h; cq[0] = fmaf(h, h, cq[0]);
+      }
+    }
+#pragma unroll
+    for (int a = 0; a < SETS; ++a)
+#pragma unroll
+      for (int s = CH; s < (RPI == 16 ? 32 : 64); s <<= 1) { cs[a] += __shfl_xor(cs[a], s, 64); cq[a] += __shfl_xor(cq[a], s, 64); }
+    if (lane < CH) {
+      stat[nt + t] = SETS == 2 ? cs[0] + cs[SETS - 1] : cs[0];
+      stat[ld + nt + t] = SETS == 2 ? cq[0] + cq[SETS - 1] : cq[0];
+    }
+  }
+}
+// The tile's statistics: bands of a statistics block added in ascending order.
+template <int BM, int BN>
+__device__ __forceinline__ void conv_store_stats(const ConvParams& p, const float* stat, int tile_m, int n0, int m0, int tid, int threads) {
+  const int bands = p.gn_block / 32, blocks = BM / p.gn_block;
+  for (int i = tid; i < blocks * 2 * BN; i += threads) {
+    const int blk = i / (2 * BN), which = i / BN % 2, c = i % BN;
+    float sum = 0.f;
+    for (int band = 0; band < bands; ++band) sum += stat[((size_t)(blk * bands + band) * 2 + which) * BN + c];
+    if (n0 + c < p.epi.N && m0 + blk * p.gn_block < p.epi.M) p.gn_partial[((size_t)(tile_m * blocks + blk) * p.epi.N + n0 + c) * 2 + which] = sum;
+  }
+}
+
 template <class T>
 __global__ void __launch_bounds__(512, 2) conv3x3_pp_kernel(const ConvParams p, uint32_t x_bytes, uint32_t w_bytes) {
   constexpr uint32_t OUTSIDE = 0xFFFFFFF0u;          // an offset past any buffer this kernel accepts: the copy delivers zeros
@@ -175,18 +254,8 @@ __global__ void __launch_bounds__(512, 2) conv3x3_pp_kernel(const ConvParams p, 
   for (int h = 0; h < 2; ++h)
 #pragma unroll
     for (int j = 0; j < T::LA; ++j) {
-      const int r = pp_piece_row(wave * T::LA + j, lane), c = pp_piece_chunk(r, lane);
-      const int gm = m0 + h * (T::BM / 2) + r, q = min(gm, p.M - 1);
-      const int b = q / (p.Ho * p.Wo), rem = q - b * (p.Ho * p.Wo), ho = rem / p.Wo, wo = rem - ho * p.Wo;
-      const int hc = ho * p.stride, wc = wo * p.stride;
-      a_base[h][j] = (int)(2u * ((uint32_t)((b * p.H + hc) * p.W + wc) * (uint32_t)p.Cin + (uint32_t)c * 8u));
-      unsigned m = 0;
-#pragma unroll
-      for (int tap = 0; tap < 9; ++tap) {
-        const int hi = hc + tap / 3 - 1, wi = wc + tap % 3 - 1;
-        m |= (unsigned)((unsigned)hi < (unsigned)p.H && (unsigned)wi < (unsigned)p.W) << tap;
-      }
-      m = gm < p.M ? m : 0u;
+      unsigned m;
+      conv_pixel(p, m0 + h * (T::BM / 2), pp_piece_row(wave * T::LA + j, lane), lane, a_base[h][j], m);
       a_taps[h][j / 2] = j % 2 ? a_taps[h][j / 2] | m << 16 : m;
     }
   auto piece_b = [&](int h, int j) { return min(wave * (h ? T::LB1 : T::LB0) + j, (h ? T::B1_BYTES : T::B0_BYTES) / 1024 - 1); };
@@ -228,76 +297,120 @@ __global__ void __launch_bounds__(512, 2) conv3x3_pp_kernel(const ConvParams p, 
         for (int j = 0; j < (h ? T::LB1 : T::LB0); ++j) async_copy_16B_buf(r, h ? vb1[h ? j : 0] : vb0[h ? 0 : j], off, dst + piece_b(h, j) * 1024);
       }, false, csum);
 
-  constexpr int CH = T::W / 8, RPI = 64 / CH, NIT = 32 / RPI, SETS = 8 / RPI;      // SETS: sums per column a lane keeps
-  static_assert(64 % CH == 0 && RPI <= 8 && T::SM == 32 && T::WGM * 2 * 32 == T::BM, "epilogue shape");
-  const EpiParams<bf16>& e = p.epi;
+  static_assert(T::SM == 32 && T::WGM * 2 * 32 == T::BM, "epilogue shape");
   float* Cw = reinterpret_cast<float*>(smem_raw) + wave * 32 * T::C_LD;
   float* stat = reinterpret_cast<float*>(smem_raw + T::EPI_BYTES);      // [band][sum | sum of squares][BN], past the slabs
-  const int lc = (lane % CH) * 8, lr = lane / CH;
-  const int nt = lc < T::SN0 ? wn * T::SN0 + lc : T::BN0 + wn * T::SN1 + lc - T::SN0, n = n0 + nt;
-  float bias[8];
-  pp_bias(e.bias, min(n, e.N - 8), bias);
 #pragma unroll
   for (int ha = 0; ha < 2; ++ha) {
-    const int row0 = m0 + ha * (T::BM / 2) + wm * 32;
-    bf16x8 res[NIT];
-#pragma unroll
-    for (int it = 0; it < NIT; ++it)
-      if (e.residual) res[it] = *reinterpret_cast<const bf16x8*>((const bf16*)e.residual + (size_t)min(row0 + it * RPI + lr, e.M - 1) * e.ld_res + min(n, e.N - 8));
-      else res[it] = zero8();
 #pragma unroll
     for (int j = 0; j < T::TN; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) Cw[acc_row(r, lane >> 5) * T::C_LD + j * 32 + (lane & 31)] = acc[ha][0][j][r];
     asm volatile("" ::: "memory");
-    float cs[SETS][8], cq[SETS][8];
-#pragma unroll
-    for (int a = 0; a < SETS; ++a)
-#pragma unroll
-      for (int t = 0; t < 8; ++t) { cs[a][t] = 0.f; cq[a][t] = 0.f; }
-#pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-      const int m = row0 + it * RPI + lr;
-      float v[8];
-      pp_slab_row(&Cw[(it * RPI + lr) * T::C_LD + lc], v);
-      bf16x8 o;
-#pragma unroll
-      for (int t = 0; t < 8; ++t) o[t] = (bf16)((v[t] + bias[t]) + (float)res[it][t]);
-      if (m < e.M && n < e.N) *reinterpret_cast<bf16x8*>(e.out + (size_t)m * e.ldo + n) = o;
-#pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        const float f = (float)o[t];
-        cs[it % SETS][t] += f; cq[it % SETS][t] = fmaf(f, f, cq[it % SETS][t]);
-      }
-    }
+    conv_band_epilogue<T::W>(p, Cw, T::C_LD, m0 + ha * (T::BM / 2) + wm * 32, n0, lane, stat + (size_t)(ha * T::WGM + wm) * 2 * T::BN, T::BN,
+                             [&](int lc) { return lc < T::SN0 ? wn * T::SN0 + lc : T::BN0 + wn * T::SN1 + lc - T::SN0; });
     asm volatile("" ::: "memory");
-    if (p.gn_partial) {      // then every row exists
-#pragma unroll
-      for (int t = 0; t < 8; ++t)
-#pragma unroll
-        for (int a = 0; a < SETS; ++a)
-#pragma unroll
-          for (int o = CH; o < 64; o <<= 1) { cs[a][t] += __shfl_xor(cs[a][t], o, 64); cq[a][t] += __shfl_xor(cq[a][t], o, 64); }
-      if (lane < CH) {
-        float* st = stat + (size_t)(ha * T::WGM + wm) * 2 * T::BN + nt;
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-          st[t] = SETS == 2 ? cs[0][t] + cs[SETS - 1][t] : cs[0][t];
-          st[T::BN + t] = SETS == 2 ? cq[0][t] + cq[SETS - 1][t] : cq[0][t];
-        }
-      }
-    }
   }
   if (!p.gn_partial) return;
   __syncthreads();
-  constexpr int BLOCKS = T::BM / 256;
-  for (int i = tid; i < BLOCKS * 2 * T::BN; i += 512) {
-    const int blk = i / (2 * T::BN), which = i / T::BN % 2, c = i % T::BN;
-    float sum = 0.f;
+  conv_store_stats<T::BM, T::BN>(p, stat, tile_m, n0, m0, tid, 512);
+}
+
+// ------------------------------------------------------------------ small tiles
+// 64x64 and 128x128 tiles for layers with few output pixels (a partial batch of one sample in the deep layers: 32 tiles of 256x128 for 256
+// CUs, each walking all 72 k-tiles of a 4608-deep contraction, 61 us).  A plain ring of direct-to-LDS stages, one barrier
+// per k-tile; several workgroups per CU hide each other's latencies.  The order of the additions is that of the large tiles, so
+// the tile shape, which depends on the number of samples, changes no bit: same k order, same 32-row statistics bands.
+// Measured (512 -> 512 channels): 48 x 41 pixels 61 -> 24 us (64x64), 96 x 82 65 -> 47 us (128x128); 512 -> 8 head at 48 x 41 71 -> 24 us.
+template <int BM_, int BN_, int WGM_, int WGN_, int STAGES_>
+struct ConvSmallTile {
+  static constexpr int BM = BM_, BN = BN_, WGM = WGM_, WGN = WGN_, STAGES = STAGES_, NW = WGM * WGN, WM = BM / WGM, WN = BN / WGN, TN = WN / 32;
+  static constexpr int A_BYTES = BM * 128, B_BYTES = BN * 128, STAGE = A_BYTES + B_BYTES, LA = A_BYTES / 1024 / NW, LB = B_BYTES / 1024 / NW;
+  static constexpr int C_LD = WN + 8;
+  static constexpr size_t EPI_BYTES = (size_t)NW * 32 * C_LD * 4, STAT_BYTES = (size_t)BM / 32 * 2 * BN * 4;
+  static constexpr size_t BYTES = (size_t)STAGES * STAGE > EPI_BYTES + STAT_BYTES ? (size_t)STAGES * STAGE : EPI_BYTES + STAT_BYTES;
+  static_assert(WM == 32 && WN % 32 == 0 && A_BYTES % (1024 * NW) == 0 && B_BYTES % (1024 * NW) == 0, "tile shape");
+};
+
+template <class T>
+__global__ void __launch_bounds__(T::NW * 64) conv3x3_small_kernel(const ConvParams p, uint32_t x_bytes, uint32_t w_bytes) {
+  constexpr uint32_t OUTSIDE = 0xFFFFFFF0u;
+  constexpr int LA = T::LA, LB = T::LB;
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 5, l32 = lane & 31;
+  const int wm = wave / T::WGN, wn = wave % T::WGN;
+  int tile_m, tile_n;
+  tile_of_block(blockIdx.x, p.tiles_m, p.tiles_n, p.group_m, tile_m, tile_n);
+  const int m0 = tile_m * T::BM, n0 = tile_n * T::BN, nk = p.K / 64;
+  int a_base[LA];
+  unsigned a_taps[LA];
 #pragma unroll
-    for (int band = 0; band < 8; ++band) sum += stat[((size_t)(blk * 8 + band) * 2 + which) * T::BN + c];
-    if (n0 + c < e.N && m0 + blk * 256 < e.M) p.gn_partial[((size_t)(tile_m * BLOCKS + blk) * e.N + n0 + c) * 2 + which] = sum;
+  for (int j = 0; j < LA; ++j) conv_pixel(p, m0, pp_piece_row(wave * LA + j, lane), lane, a_base[j], a_taps[j]);
+  uint32_t va[LA], vb[LB];
+#pragma unroll
+  for (int j = 0; j < LB; ++j) {
+    const int r = pp_piece_row(wave * LB + j, lane), c = pp_piece_chunk(r, lane);
+    vb[j] = 2u * ((uint32_t)min(n0 + r, p.N - 1) * (uint32_t)p.K + (uint32_t)c * 8u);
   }
+  int it_tap = 0, it_c0 = 0;
+  auto issue = [&](int t) {
+    unsigned char* st = smem_raw + t % T::STAGES * T::STAGE;
+    const rsrc_t rx = make_rsrc(p.x, t < nk ? x_bytes : 0u), rw = make_rsrc(p.w, t < nk ? w_bytes : 0u);
+    if (it_c0 == 0) {
+      const int u = (it_tap * 11) >> 5, v = it_tap - 3 * u, off = 2 * ((u - 1) * p.W + (v - 1)) * p.Cin;
+#pragma unroll
+      for (int j = 0; j < LA; ++j) va[j] = (a_taps[j] >> it_tap) & 1u ? (uint32_t)(a_base[j] + off) : OUTSIDE;
+    }
+    const uint32_t oa = 2u * (uint32_t)it_c0, ob = t < nk ? (uint32_t)t * 128u : 0u;
+    it_c0 += 64;
+    if (it_c0 == p.Cin) { it_c0 = 0; ++it_tap; }
+#pragma unroll
+    for (int j = 0; j < LA; ++j) async_copy_16B_buf(rx, va[j], oa, st + (wave * LA + j) * 1024);
+#pragma unroll
+    for (int j = 0; j < LB; ++j) async_copy_16B_buf(rw, vb[j], ob, st + T::A_BYTES + (wave * LB + j) * 1024);
+  };
+  f32x16 acc[T::TN];
+#pragma unroll
+  for (int j = 0; j < T::TN; ++j)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
+#pragma unroll
+  for (int t = 0; t < T::STAGES - 1; ++t) issue(t);
+  const int ra = wm * 32 + l32;
+  for (int t = 0; t < nk; ++t) {
+    wait_vmcnt<(T::STAGES - 2) * (LA + LB)>();
+    barrier_nofence();             // k-tile t is there for everybody, and nobody reads k-tile t - 1 any more
+    issue(t + T::STAGES - 1);
+    const unsigned char* st = smem_raw + t % T::STAGES * T::STAGE;
+    bf16x8 fa[4], fb[4][T::TN];
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      fa[ks] = *reinterpret_cast<const bf16x8*>(st + ra * 128 + ((2 * ks + g) ^ pp_key(ra)) * 16);
+#pragma unroll
+      for (int j = 0; j < T::TN; ++j) {
+        const int r = wn * T::WN + j * 32 + l32;
+        fb[ks][j] = *reinterpret_cast<const bf16x8*>(st + T::A_BYTES + r * 128 + ((2 * ks + g) ^ pp_key(r)) * 16);
+      }
+    }
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+      for (int j = 0; j < T::TN; ++j) acc[j] = mfma32(fa[ks], fb[ks][j], acc[j]);
+  }
+  wait_vmcnt<0>();
+  __syncthreads();
+  float* Cw = reinterpret_cast<float*>(smem_raw) + wave * 32 * T::C_LD;
+  float* stat = reinterpret_cast<float*>(smem_raw + T::EPI_BYTES);      // [band][sum | sum of squares][BN], past the slabs
+#pragma unroll
+  for (int j = 0; j < T::TN; ++j)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) Cw[acc_row(r, g) * T::C_LD + j * 32 + l32] = acc[j][r];
+  asm volatile("" ::: "memory");
+  conv_band_epilogue<T::WN>(p, Cw, T::C_LD, m0 + wm * 32, n0 + wn * T::WN, lane, stat + (size_t)wm * 2 * T::BN + wn * T::WN, T::BN,
+                            [](int lc) { return lc; });
+  if (!p.gn_partial) return;
+  __syncthreads();
+  conv_store_stats<T::BM, T::BN>(p, stat, tile_m, n0, m0, tid, T::NW * 64);
 }
 
 template <class T>
@@ -333,6 +446,25 @@ static int launch_conv_cfg(ConvParams& p, hipStream_t s) {
   return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "conv launch failed");
 }
 
+template <class T>
+static int launch_conv_small(ConvParams& p, size_t x_bytes, size_t w_bytes, hipStream_t s) {
+  p.tiles_m = (p.M + T::BM - 1) / T::BM; p.tiles_n = (p.N + T::BN - 1) / T::BN;
+  const long n = (long)p.tiles_m * p.tiles_n, ppx = (n + 7) / 8;
+  p.group_m = (int)std::max<long>(1, std::min<long>((ppx + p.tiles_n / 2) / p.tiles_n, p.tiles_m));
+  auto kern = conv3x3_small_kernel<T>;
+  static std::atomic<bool> attr_set{false};   // setting it twice is harmless; the flag only saves the call
+  if (!attr_set.load(std::memory_order_acquire)) {
+    if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)T::BYTES) != hipSuccess)
+      return set_error(DP_EHIP, "hipFuncSetAttribute(conv) failed");
+    attr_set.store(true, std::memory_order_release);
+  }
+  hipLaunchKernelGGL(kern, dim3((unsigned)n), dim3(T::NW * 64), T::BYTES, s, p, (uint32_t)x_bytes, (uint32_t)w_bytes);
+  return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "conv launch failed");
+}
+
+// Pixels per statistics block for an output of `px` pixels per sample: blocks of 256, of 64 where the small tiles may run (their 64 rows).
+int conv_stat_block(int px) { return px < 16384 ? 64 : 256; }
+
 int launch_conv3x3(const ConvArgs& a, hipStream_t s) {
   if (a.dtype != BF16) return set_error(DP_EUNSUPPORTED, "conv3x3: bf16 storage only");
   if (a.B <= 0 || a.H <= 0 || a.W <= 0 || a.Cin <= 0 || a.Cout <= 0) return set_error(DP_EINVAL, "conv3x3: non-positive size");
@@ -349,7 +481,7 @@ int launch_conv3x3(const ConvArgs& a, hipStream_t s) {
   p.H = a.H; p.W = a.W; p.Cin = a.Cin; p.Ho = Ho; p.Wo = Wo; p.stride = a.stride;
   p.M = (int)M; p.N = a.Cout; p.K = 9 * a.Cin;
   p.taps_uniform = a.Cin % 64 == 0;
-  p.gn_partial = nullptr;
+  p.gn_partial = nullptr; p.gn_block = 256;
   if (a.gn_applied) *a.gn_applied = 0;
   if (a.gn_partial && !a.gn_applied) return set_error(DP_EINVAL, "conv3x3: gn_partial comes with gn_applied");
   EpiParams<bf16>& e = p.epi;
@@ -364,22 +496,31 @@ int launch_conv3x3(const ConvArgs& a, hipStream_t s) {
   // the direct-to-LDS kernel: k-tiles inside one tap, 32-bit byte offsets with room for the "outside" marker
   const size_t x_bytes = 2 * (size_t)a.B * a.H * a.W * a.Cin, w_bytes = 2 * (size_t)p.N * p.K;
   // (whether this kernel is taken depends on one sample's pixel count, not on the number of samples)
-  if (a.Cin % 64 == 0 && a.Cout >= 64 && (long)Ho * Wo >= 1024 && x_bytes < (1ull << 31) && w_bytes < (1ull << 31) && !a.force_staged) {
-    if (a.gn_partial && (Ho * Wo) % 256 == 0 && ((uintptr_t)a.gn_partial % 16) == 0) { p.gn_partial = a.gn_partial; *a.gn_applied = 1; }
+  if (a.Cin % 64 == 0 && x_bytes < (1ull << 31) && w_bytes < (1ull << 31) && !a.force_staged) {
+    p.gn_block = conv_stat_block(Ho * Wo);
+    if (a.gn_partial && (Ho * Wo) % p.gn_block == 0 && ((uintptr_t)a.gn_partial % 16) == 0) { p.gn_partial = a.gn_partial; *a.gn_applied = 1; }
     // The tile with the least estimated time, rounds over the 256 CUs x (fixed part + k-tiles x time of one).  This choice may
-    // depend on the number of samples: the shapes produce the same bits, statistics included.
-    const struct { int bm, bn; float fixed, per_kt; } tiles[] = {{256, 256, 6.0f, 1.75f}, {256, 128, 5.0f, 1.14f}, {512, 64, 6.0f, 1.90f}, {512, 128, 6.0f, 2.10f}};
+    // depend on the number of samples: the shapes produce the same bits, statistics included.  The times of a k-tile are measured ones
+    // (us at 72 k-tiles: 256x256 130, 256x128 87, 128x128 48 with one workgroup per CU each; 64x64 24 with one, 33 with two).
+    const bool small = p.gn_block == 64 || !p.gn_partial;
+    const struct { int bm, bn, at_once; float fixed, per_kt; } tiles[] = {{256, 256, 256, 6.0f, 1.75f}, {256, 128, 256, 5.0f, 1.14f}, {512, 64, 256, 6.0f, 1.90f},
+                                                                          {512, 128, 256, 6.0f, 2.10f}, {64, 64, 512, 5.0f, 0.38f}, {128, 128, 256, 5.0f, 0.58f}};
     int best = 0;
     float best_us = 0.f;
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < (small ? 6 : 4); ++i) {
       const long n = ((M + tiles[i].bm - 1) / tiles[i].bm) * ((a.Cout + tiles[i].bn - 1) / tiles[i].bn);
-      const float us = (float)((n + 255) / 256) * (tiles[i].fixed + (float)(p.K / 64) * tiles[i].per_kt);
+      const float per_kt = i == 4 && n <= 256 ? 0.26f : tiles[i].per_kt;        // two of the smallest tiles on a CU slow each other down
+      const float us = (float)((n + tiles[i].at_once - 1) / tiles[i].at_once) * (tiles[i].fixed + (float)(p.K / 64) * per_kt);
       if (i == 0 || us < best_us) { best = i; best_us = us; }
     }
-    if (best == 0) return launch_conv_pp<PpTile<256, 128, 128, 4, 2>>(p, x_bytes, w_bytes, s);
-    if (best == 1) return launch_conv_pp<PpTile<256, 64, 64, 4, 2>>(p, x_bytes, w_bytes, s);
-    if (best == 2) return launch_conv_pp<PpTile<512, 32, 32, 8, 1>>(p, x_bytes, w_bytes, s);
-    return launch_conv_pp<PpTile<512, 64, 64, 8, 1>>(p, x_bytes, w_bytes, s);
+    switch (best) {
+      case 0: return launch_conv_pp<PpTile<256, 128, 128, 4, 2>>(p, x_bytes, w_bytes, s);
+      case 1: return launch_conv_pp<PpTile<256, 64, 64, 4, 2>>(p, x_bytes, w_bytes, s);
+      case 2: return launch_conv_pp<PpTile<512, 32, 32, 8, 1>>(p, x_bytes, w_bytes, s);
+      case 3: return launch_conv_pp<PpTile<512, 64, 64, 8, 1>>(p, x_bytes, w_bytes, s);
+      case 4: return launch_conv_small<ConvSmallTile<64, 64, 2, 2, 4>>(p, x_bytes, w_bytes, s);
+      default: return launch_conv_small<ConvSmallTile<128, 128, 4, 2, 3>>(p, x_bytes, w_bytes, s);
+    }
   }
   if (a.Cout <= 64) return launch_conv_cfg<128, 64, 4, 1>(p, s);
   if ((long)Ho * Wo >= 16384) return launch_conv_cfg<256, 128, 4, 2>(p, s);

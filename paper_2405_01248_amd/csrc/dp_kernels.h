@@ -105,13 +105,14 @@ struct ConvArgs {
   int B, H, W, Cin, Cout, stride;
   const void* x; const void* w; const void* bias; const void* residual; void* y;
   int force_staged;   // 1: always the register-staged kernel (measurement and tests of that path)
-  // Optional: per-channel sums and sums of squares of the output (as rounded to bf16) per block of 256 output pixels, in
-  // the layout of GroupNorm's first pass, gn_partial[((b * (HoWo / 256) + block) * Cout + c) * 2 + {0, 1}], so that a
-  // GroupNorm of y can skip that pass.  Only when Ho * Wo is a multiple of 256 and the direct-to-LDS kernel runs:
+  // Optional: per-channel sums and sums of squares of the output (as rounded to bf16) per block of conv_stat_block(Ho * Wo) output
+  // pixels, in the layout of GroupNorm's first pass, gn_partial[((b * blocks + block) * Cout + c) * 2 + {0, 1}], so that a
+  // GroupNorm of y can skip that pass.  Only when Ho * Wo is a multiple of the block and a direct-to-LDS kernel runs:
   // *gn_applied (required with gn_partial) tells whether they were written.
   float* gn_partial; int* gn_applied;
 };
 int launch_conv3x3(const ConvArgs& a, hipStream_t s);
+int conv_stat_block(int px);      // pixels per block of gn_partial for px output pixels per sample
 
 // GroupNorm over channels-last x [B, HW, C]: per (sample, group of C / groups consecutive channels) mean and
 // biased variance over the group's channels at all pixels; y = (x - mean) * rstd * gamma + beta, then SiLU

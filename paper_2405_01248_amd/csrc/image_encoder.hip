@@ -227,7 +227,8 @@ static void plan_image(const dp_image_encoder& e, void* base, int lb, int le, in
   size_t maxact = 0, gn = 0, gnc = 0, attn_rows = 0, attn_px = 0; int attn_c = 0;
   for (int l = lb; l < le; ++l) {
     maxact = std::max(maxact, layer_act_elems(e, l, n));
-    gnc = std::max(gnc, (size_t)n * ((size_t)e.h[l + 1] * e.w[l + 1] / 256 + 1) * e.c[l + 1] * 2 * sizeof(float));
+    const int px = e.h[l + 1] * e.w[l + 1];
+    gnc = std::max(gnc, (size_t)n * (px / conv_stat_block(px) + 1) * e.c[l + 1] * 2 * sizeof(float));
     const int HW = e.h[l] * e.w[l];
     if (e.layers[l].kind != DP_IMG_CONV) gn = std::max(gn, std::max(gn_scratch_bytes(n, HW, e.c[l]), gn_scratch_bytes(n, HW, e.c[l + 1])));
     if (e.layers[l].kind == DP_IMG_ATTN) { attn_rows = std::max(attn_rows, (size_t)n * HW); attn_px = std::max(attn_px, (size_t)HW); attn_c = std::max(attn_c, e.c[l]); }
@@ -262,10 +263,10 @@ static int image_layer(const dp_image_encoder& e, int l, const void* const* P, c
     // the convolution's epilogue can produce the first pass of a GroupNorm over its output
     const int out_px = ((H - 1) / stride + 1) * ((W - 1) / stride + 1);
     int applied = 0;
-    if (w.gnc && (size_t)n * (out_px / 256 + 1) * cout * 2 * sizeof(float) <= w.gnc_bytes) { a.gn_partial = w.gnc; a.gn_applied = &applied; }
+    if (w.gnc && (size_t)n * (out_px / conv_stat_block(out_px) + 1) * cout * 2 * sizeof(float) <= w.gnc_bytes) { a.gn_partial = w.gnc; a.gn_applied = &applied; }
     w.stat_of = nullptr;
     const int rc = launch_conv3x3(a, st);
-    if (rc == DP_OK && applied) { w.stat_of = y; w.stat_blocks = out_px / 256; }
+    if (rc == DP_OK && applied) { w.stat_of = y; w.stat_blocks = out_px / conv_stat_block(out_px); }
     return rc;
   };
   auto gn = [&](const void* x, int ch, const void* gamma, const void* beta, int silu, void* y) {
