@@ -413,6 +413,146 @@ __global__ void __launch_bounds__(T::NW * 64) conv3x3_small_kernel(const ConvPar
   conv_store_stats<T::BM, T::BN>(p, stat, tile_m, n0, m0, tid, T::NW * 64);
 }
 
+// ------------------------------------------------------------------ eight input channels
+// The encoder's first layer (an image padded to eight channels): 9 taps x 8 channels, bound by writing the output.  A tap's 8 channels are the
+// 16 bytes a lane contributes to an MFMA step of 16, so a pixel's neighbourhood goes from memory straight into the operand: five
+// steps of two taps; the tenth slot holds a one against the bias.  The weights are the row operand, dealt to its
+// rows so that a lane's 16 accumulators are 16 consecutive channels of one pixel: two 16-byte LDS writes turn them into whole
+// lines of the output.  A workgroup walks over tiles of 256 pixels, 64 per wave; GroupNorm sums are kept in lanes over a wave's
+// 64 rows and reduced with lane swaps, each step halving the values a lane holds.
+// 8 samples of 512 x 512 -> 128 channels (537 MB out): 288 us + 73 us for the sums in a pass of their own through the staged kernel; now 138 us (4.1 TB/s), sums included.
+template <int TN>
+struct ConvIn8 {
+  static constexpr int BN = 32 * TN, KP = 80;
+  static constexpr int W_BYTES = BN * KP * 2, SLAB_BYTES = 4 * 32 * 64 * 2, STAT_BYTES = 4 * 2 * BN * 4, BYTES = W_BYTES + SLAB_BYTES + STAT_BYTES;
+};
+// a's upper half of the wave (of every row pair) against b's lower half: afterwards a + b holds the pairwise sums of a in the lower, of b in the upper one
+__device__ __forceinline__ float fold_halves32(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), false, false);
+  const uint32_t lo = r[0], hi = r[1];
+  return __builtin_bit_cast(float, lo) + __builtin_bit_cast(float, hi);
+}
+__device__ __forceinline__ float fold_halves16(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), false, false);
+  const uint32_t lo = r[0], hi = r[1];
+  return __builtin_bit_cast(float, lo) + __builtin_bit_cast(float, hi);
+}
+template <int TN>
+__global__ void __launch_bounds__(256, 4) conv3x3_in8_kernel(const ConvParams p, uint32_t x_bytes) {
+  using T = ConvIn8<TN>;
+  constexpr uint32_t OUTSIDE = 0xFFFFFFF0u;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 5, l32 = lane & 31;
+  bf16* Ws = reinterpret_cast<bf16*>(smem_raw);
+  bf16* slab = reinterpret_cast<bf16*>(smem_raw + T::W_BYTES) + wave * 32 * 64;
+  float* stat = reinterpret_cast<float*>(smem_raw + T::W_BYTES + T::SLAB_BYTES);
+  for (int i = tid; i < T::BN * 10; i += 256) {
+    const int r = i / 10, tap = i - 10 * r, n = (r & ~31) + 16 * (r >> 2 & 1) + 4 * (r >> 3 & 3) + (r & 3);      // row r of the operand: channel n
+    bf16x8 v = zero8();
+    if (n < p.N) {
+      if (tap < 9) v = *reinterpret_cast<const bf16x8*>(p.w + (size_t)n * 72 + tap * 8);
+      else if (p.epi.bias) v[0] = p.epi.bias[n];
+    }
+    *reinterpret_cast<bf16x8*>(Ws + r * T::KP + tap * 8) = v;
+  }
+  __syncthreads();
+  const rsrc_t rx = make_rsrc(p.x, x_bytes);
+  bf16x8 px[5];
+  auto fetch = [&](int row0) {
+    const int gm = row0 + l32, q = min(gm, p.M - 1), hw = p.Ho * p.Wo;
+    const int b = q / hw, rem = q - b * hw, ho = rem / p.Wo, wo = rem - ho * p.Wo;
+    const int hc = ho * p.stride, wc = wo * p.stride, base = (b * p.H + hc) * p.W + wc;
+#pragma unroll
+    for (int s = 0; s < 5; ++s) {
+      const int u = (g ? (2 * s + 1) / 3 : 2 * s / 3) - 1, v = (g ? (2 * s + 1) % 3 : 2 * s % 3) - 1;
+      const bool in = gm < p.M && (unsigned)(hc + u) < (unsigned)p.H && (unsigned)(wc + v) < (unsigned)p.W;
+      px[s] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rx, in ? (uint32_t)(base + u * p.W + v) * 16u : OUTSIDE, 0, 0));
+    }
+    bf16x8 one = zero8();
+    one[0] = (bf16)1.0f;
+    px[4] = g ? one : px[4];
+  };
+  const int lc = lane & 7, lr = lane >> 3;
+  int tile = blockIdx.x;
+  fetch(tile * 256 + wave * 64);
+  for (; tile < p.tiles_m; tile += gridDim.x) {
+    float sums[TN / 2][2];
+#pragma unroll
+    for (int h = 0; h < TN / 2; ++h) sums[h][0] = sums[h][1] = 0.f;
+#pragma unroll
+    for (int band = 0; band < 2; ++band) {
+      const int row0 = tile * 256 + wave * 64 + band * 32;
+#pragma unroll
+      for (int half = 0; half < TN / 2; ++half) {
+        f32x16 acc[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
+#pragma unroll
+          for (int s = 0; s < 5; ++s)
+            acc[j] = mfma32(*reinterpret_cast<const bf16x8*>(Ws + ((2 * half + j) * 32 + l32) * T::KP + s * 16 + 8 * g), px[s], acc[j]);
+        }
+        if (half == TN / 2 - 1) {
+          const int next = band == 0 ? row0 + 32 : row0 - 32 + (int)gridDim.x * 256;
+          if (next < p.M) fetch(next);
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          bf16x8 o;
+#pragma unroll
+          for (int t = 0; t < 8; ++t) o[t] = (bf16)acc[c >> 1][8 * (c & 1) + t];
+          const int chunk = 4 * (c >> 1) + 2 * g + (c & 1);
+          *reinterpret_cast<bf16x8*>(slab + l32 * 64 + (chunk ^ (l32 & 7)) * 8) = o;
+        }
+        asm volatile("" ::: "memory");      // lanes of one wave exchange through the slab: LDS serves a wave in order
+        const int n = 64 * half + lc * 8;
+        float v[16];
+#pragma unroll
+        for (int t = 0; t < 16; ++t) v[t] = 0.f;
+#pragma unroll
+        for (int it = 0; it < 4; ++it) {
+          const int row = it * 8 + lr;
+          const bf16x8 o = *reinterpret_cast<const bf16x8*>(slab + row * 64 + (lc ^ (row & 7)) * 8);
+          if (row0 + row < p.M && n < p.N) *reinterpret_cast<bf16x8*>(p.epi.out + (size_t)(row0 + row) * p.epi.ldo + n) = o;
+#pragma unroll
+          for (int t = 0; t < 8; ++t) {
+            const float f = (float)o[t];
+            v[t] += f; v[8 + t] = fmaf(f, f, v[8 + t]);
+          }
+        }
+        asm volatile("" ::: "memory");
+        if (p.gn_partial) {
+#pragma unroll
+          for (int t = 0; t < 8; ++t) v[t] = fold_halves32(v[t], v[t + 8]);
+#pragma unroll
+          for (int t = 0; t < 4; ++t) v[t] = fold_halves16(v[t], v[t + 4]);
+#pragma unroll
+          for (int t = 0; t < 4; ++t) v[t] += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v[t]), 0x128, 0xF, 0xF, true));   // row_ror:8
+          sums[half][0] += lane & 8 ? v[2] : v[0];
+          sums[half][1] += lane & 8 ? v[3] : v[1];
+        }
+      }
+    }
+    if (p.gn_partial) {      // lanes below 32 hold sums, the others sums of squares
+#pragma unroll
+      for (int half = 0; half < TN / 2; ++half) {
+        float* d = stat + (wave * 2 + g) * T::BN + 64 * half + lc * 8 + 4 * (lane >> 4 & 1) + 2 * (lane >> 3 & 1);
+        d[0] = sums[half][0]; d[1] = sums[half][1];
+      }
+      __syncthreads();
+      const int parts = p.gn_block / 64, blocks = 4 / parts;
+      for (int i = tid; i < blocks * 2 * T::BN; i += 256) {
+        const int blk = i / (2 * T::BN), which = i / T::BN % 2, c = i % T::BN;
+        float sum = 0.f;
+        for (int q = 0; q < parts; ++q) sum += stat[((blk * parts + q) * 2 + which) * T::BN + c];
+        if (c < p.N && tile * 256 + blk * p.gn_block < p.M) p.gn_partial[((size_t)(tile * blocks + blk) * p.N + c) * 2 + which] = sum;
+      }
+      __syncthreads();
+    }
+  }
+}
+
 template <class T>
 static int launch_conv_pp(ConvParams& p, size_t x_bytes, size_t w_bytes, hipStream_t s) {
   constexpr size_t LDS = T::EPI_BYTES + (size_t)T::BM / 32 * 2 * T::BN * 4 > T::BYTES ? T::EPI_BYTES + (size_t)T::BM / 32 * 2 * T::BN * 4 : T::BYTES;
@@ -462,6 +602,14 @@ static int launch_conv_small(ConvParams& p, size_t x_bytes, size_t w_bytes, hipS
   return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "conv launch failed");
 }
 
+template <int TN>
+static int launch_conv_in8(ConvParams& p, size_t x_bytes, hipStream_t s) {
+  p.tiles_m = (p.M + 255) / 256; p.tiles_n = 1; p.group_m = 1;
+  const int rounds = (p.tiles_m + 1023) / 1024;      // four workgroups per CU, each with an equal share of the tiles
+  hipLaunchKernelGGL(conv3x3_in8_kernel<TN>, dim3((p.tiles_m + rounds - 1) / rounds), dim3(256), ConvIn8<TN>::BYTES, s, p, (uint32_t)x_bytes);
+  return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "conv launch failed");
+}
+
 // Pixels per statistics block for an output of `px` pixels per sample: blocks of 256, of 64 where the small tiles may run (their 64 rows).
 int conv_stat_block(int px) { return px < 16384 ? 64 : 256; }
 
@@ -496,6 +644,11 @@ int launch_conv3x3(const ConvArgs& a, hipStream_t s) {
   // the direct-to-LDS kernel: k-tiles inside one tap, 32-bit byte offsets with room for the "outside" marker
   const size_t x_bytes = 2 * (size_t)a.B * a.H * a.W * a.Cin, w_bytes = 2 * (size_t)p.N * p.K;
   // (whether this kernel is taken depends on one sample's pixel count, not on the number of samples)
+  if (a.Cin == 8 && a.Cout <= 128 && !a.residual && x_bytes < (1ull << 31) && !a.force_staged) {
+    p.gn_block = conv_stat_block(Ho * Wo);
+    if (a.gn_partial && (Ho * Wo) % p.gn_block == 0 && ((uintptr_t)a.gn_partial % 16) == 0) { p.gn_partial = a.gn_partial; *a.gn_applied = 1; }
+    return a.Cout <= 64 ? launch_conv_in8<2>(p, x_bytes, s) : launch_conv_in8<4>(p, x_bytes, s);
+  }
   if (a.Cin % 64 == 0 && x_bytes < (1ull << 31) && w_bytes < (1ull << 31) && !a.force_staged) {
     p.gn_block = conv_stat_block(Ho * Wo);
     if (a.gn_partial && (Ho * Wo) % p.gn_block == 0 && ((uintptr_t)a.gn_partial % 16) == 0) { p.gn_partial = a.gn_partial; *a.gn_applied = 1; }

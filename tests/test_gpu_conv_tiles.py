@@ -1,4 +1,4 @@
-"""The convolution's tiles for few pixels (64 x 64 and 128 x 128) at the edges of their range, against the fp64 oracle
+"""The convolution's kernel for eight input channels and its tiles for few pixels (64 x 64 and 128 x 128) at the edges of their range, against the fp64 oracle
 through the image encoder's C ABI: pixel counts around a tile, a single pixel, the 8-channel head, stride 2, GroupNorm sums over
 blocks of 64 pixels.  Metric: max|gpu - oracle| / max|oracle| <= 2e-2 (bf16 storage)."""
 import numpy as np
@@ -22,6 +22,10 @@ def _layer(kind, ci, co, stride, hw, batch, groups=8):
     _layer("conv", 64, 128, 2, (31, 34), 2),
     _layer("resnet", 64, 64, 1, (8, 8), 3),          # one statistics block a sample
     _layer("resnet", 128, 136, 1, (24, 24), 2),      # nine blocks of 64, three channel tiles
+    _layer("conv", 8, 8, 1, (3, 5), 2),              # eight input channels: less than a band of pixels
+    _layer("conv", 8, 72, 2, (33, 31), 3),           # ... ragged bands and channels, stride 2
+    _layer("resnet", 8, 64, 1, (24, 24), 3),         # ... statistics blocks of 64, nine a sample
+    _layer("resnet", 8, 128, 1, (128, 132), 1),      # ... statistics blocks of 256
     _layer("resnet", 256, 256, 1, (64, 80), 1, 32),  # enough tiles for the 128-row shape
 ], ids=lambda c: c.name)
 def test_few_pixel_tiles_match_oracle(cfg):
