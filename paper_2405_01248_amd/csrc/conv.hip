@@ -156,7 +156,7 @@ __global__ void __launch_bounds__(WGM * WGN * 64) conv3x3_bf16_kernel(const Conv
 // Epilogue: bias, optional residual, bf16 store and, if asked, the first pass of a GroupNorm over the output: per channel the
 // sum and the sum of squares of the stored (rounded) values over a block of pixels (ConvParams::gn_block).  They are formed in an order that no tile shape
 // changes: in a band of 32 rows, the rows with equal r % 8 in ascending order, these eight sums pairwise by the bits of
-// r from the lowest up, then the block's bands in ascending order.
+// r from the highest down, then the block's bands in ascending order.
 // Byte offset of the input pixel at the tap centre of output pixel m0 + row, plus this lane's 16-byte chunk of the tile row `row`, and
 // the 9-bit set of taps that fall inside the image for that pixel (empty for rows past M).
 __device__ __forceinline__ void conv_pixel(const ConvParams& p, int m0, int row, int lane, int& base, unsigned& taps) {
@@ -171,6 +171,48 @@ __device__ __forceinline__ void conv_pixel(const ConvParams& p, int m0, int row,
     m |= (unsigned)((unsigned)hi < (unsigned)p.H && (unsigned)wi < (unsigned)p.W) << tap;
   }
   taps = gm < p.M ? m : 0u;
+}
+
+// Reduction over lanes of two values at once, by v_permlane*_swap: the lower half of the wave (16-lane row of each pair) gets a's sum of both
+// halves, the upper one b's.  One swap and one add for two values, no LDS: through ds_bpermute the sums below took 64 LDS operations per band.
+__device__ __forceinline__ float fold_halves32(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), false, false);
+  const uint32_t lo = r[0], hi = r[1];
+  return __builtin_bit_cast(float, lo) + __builtin_bit_cast(float, hi);
+}
+__device__ __forceinline__ float fold_halves16(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), false, false);
+  const uint32_t lo = r[0], hi = r[1];
+  return __builtin_bit_cast(float, lo) + __builtin_bit_cast(float, hi);
+}
+template <int N> __device__ __forceinline__ float row_rotate(float v) {      // lane i of a row of 16 gets lane (i - N) mod 16
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x120 + N, 0xF, 0xF, true));
+}
+// Sums over the 64 / CH rows of a pass (lane = row * CH + chunk) of v[0..7] and v[8..15], by the bits of the row from the highest down; stores the
+// sums of v[0..7] at dst[0..7], those of v[8..15] at dst[ld + 0..7].  CH 4: bit 5 of the lane is summed already.
+template <int CH>
+__device__ __forceinline__ void conv_reduce_rows(float (&v)[16], int lane, float* dst, int ld) {
+  const int b5 = lane >> 5, b4 = lane >> 4 & 1, b3 = lane >> 3 & 1, b2 = lane >> 2 & 1;
+#pragma unroll
+  for (int t = 0; t < 8; ++t) v[t] = CH == 4 ? (b5 ? v[t + 8] : v[t]) : fold_halves32(v[t], v[t + 8]);
+#pragma unroll
+  for (int t = 0; t < 4; ++t) v[t] = fold_halves16(v[t], v[t + 4]);
+  float* d = dst + b5 * ld + 4 * b4;
+  if constexpr (CH == 16) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) d[t] = v[t];
+  } else {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) v[t] += row_rotate<8>(v[t]);
+    if constexpr (CH == 4) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) v[t] += row_rotate<4>(v[t]);
+    }
+    const float v0 = b3 ? v[2] : v[0], v1 = b3 ? v[3] : v[1];
+    d += 2 * b3;
+    if constexpr (CH == 8) { d[0] = v0; d[1] = v1; }
+    else d[b2] = b2 ? v1 : v0;
+  }
 }
 
 // Epilogue of one band: the 32 rows x W columns of fp32 values at Cw.  row0, col0: output row and column of the band; column(lc): the
@@ -199,30 +241,32 @@ __device__ __forceinline__ void conv_band_epilogue(const ConvParams& p, const fl
   }
   if (!p.gn_partial) return;      // otherwise every row exists
   // sums over the rows with equal r % 8, ascending; then pairwise over the bits of r % 8
-  constexpr int SETS = RPI == 4 ? 2 : 1;
+  float v[RPI == 4 ? 2 : 1][16];
 #pragma unroll
-  for (int t = 0; t < 8; ++t) {
-    float cs[SETS], cq[SETS];
+  for (int t = 0; t < 16; ++t)
 #pragma unroll
-    for (int a = 0; a < SETS; ++a) { cs[a] = 0.f; cq[a] = 0.f; }
+    for (int a = 0; a < (RPI == 4 ? 2 : 1); ++a) v[a][t] = 0.f;
 #pragma unroll
-    for (int it = 0; it < NIT; ++it) {
+  for (int it = 0; it < NIT; ++it)
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
       const float f = (float)o[it][t];
-      cs[it % SETS] += f; cq[it % SETS] = fmaf(f, f, cq[it % SETS]);
-      if constexpr (RPI == 16) {      // rows lr and lr + 8 of this pass lie in different lanes (the upper one's sums are not used)
-        const float h = __shfl_xor(f, 8 * CH, 64);
-        cs[0] += h; cq[0] = fmaf(h, h, cq[0]);
+      float& cs = v[RPI == 4 ? it % 2 : 0][t];
+      float& cq = v[RPI == 4 ? it % 2 : 0][t + 8];
+      if constexpr (RPI == 16) {      // rows lr and lr + 8 of this pass lie in the two halves of the wave
+        const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, f), __builtin_bit_cast(uint32_t, f), false, false);
+        const uint32_t lo = r[0], hi = r[1];
+        const float f0 = __builtin_bit_cast(float, lo), f1 = __builtin_bit_cast(float, hi);
+        cs = (cs + f0) + f1; cq = fmaf(f1, f1, fmaf(f0, f0, cq));
+      } else {
+        cs += f; cq = fmaf(f, f, cq);
       }
     }
+  if constexpr (RPI == 4) {
 #pragma unroll
-    for (int a = 0; a < SETS; ++a)
-#pragma unroll
-      for (int s = CH; s < (RPI == 16 ? 32 : 64); s <<= 1) { cs[a] += __shfl_xor(cs[a], s, 64); cq[a] += __shfl_xor(cq[a], s, 64); }
-    if (lane < CH) {
-      stat[nt + t] = SETS == 2 ? cs[0] + cs[SETS - 1] : cs[0];
-      stat[ld + nt + t] = SETS == 2 ? cq[0] + cq[SETS - 1] : cq[0];
-    }
+    for (int t = 0; t < 16; ++t) v[0][t] += v[1][t];
   }
+  conv_reduce_rows<CH>(v[0], lane, stat + nt, ld);
 }
 // The tile's statistics: bands of a statistics block added in ascending order.
 template <int BM, int BN>
@@ -426,17 +470,6 @@ struct ConvIn8 {
   static constexpr int BN = 32 * TN, KP = 80;
   static constexpr int W_BYTES = BN * KP * 2, SLAB_BYTES = 4 * 32 * 64 * 2, STAT_BYTES = 4 * 2 * BN * 4, BYTES = W_BYTES + SLAB_BYTES + STAT_BYTES;
 };
-// a's upper half of the wave (of every row pair) against b's lower half: afterwards a + b holds the pairwise sums of a in the lower, of b in the upper one
-__device__ __forceinline__ float fold_halves32(float a, float b) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), false, false);
-  const uint32_t lo = r[0], hi = r[1];
-  return __builtin_bit_cast(float, lo) + __builtin_bit_cast(float, hi);
-}
-__device__ __forceinline__ float fold_halves16(float a, float b) {
-  const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), false, false);
-  const uint32_t lo = r[0], hi = r[1];
-  return __builtin_bit_cast(float, lo) + __builtin_bit_cast(float, hi);
-}
 template <int TN>
 __global__ void __launch_bounds__(256, 4) conv3x3_in8_kernel(const ConvParams p, uint32_t x_bytes) {
   using T = ConvIn8<TN>;
@@ -526,9 +559,7 @@ __global__ void __launch_bounds__(256, 4) conv3x3_in8_kernel(const ConvParams p,
 #pragma unroll
           for (int t = 0; t < 8; ++t) v[t] = fold_halves32(v[t], v[t + 8]);
 #pragma unroll
-          for (int t = 0; t < 4; ++t) v[t] = fold_halves16(v[t], v[t + 4]);
-#pragma unroll
-          for (int t = 0; t < 4; ++t) v[t] += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v[t]), 0x128, 0xF, 0xF, true));   // row_ror:8
+          for (int t = 0; t < 4; ++t) { v[t] = fold_halves16(v[t], v[t + 4]); v[t] += row_rotate<8>(v[t]); }
           sums[half][0] += lane & 8 ? v[2] : v[0];
           sums[half][1] += lane & 8 ? v[3] : v[1];
         }
