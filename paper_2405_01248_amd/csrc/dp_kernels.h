@@ -62,6 +62,8 @@ struct GemmArgs {
   const void* ln_gamma; const void* ln_beta; void* ln_out; float ln_eps; int* ln_applied;
 };
 int launch_gemm(const GemmArgs& a, hipStream_t s);
+// `count` products y = x W^T (+ bias; storage-dtype or fp32 output, choice_rows < 0), operands and outputs at these distances in elements
+int launch_gemm_strided(const GemmArgs& a, int count, long stride_a, long stride_b, long stride_out, hipStream_t s);
 int launch_gemm_f32(const GemmArgs& a, hipStream_t s);      // the fp32 part of launch_gemm
 // Bytes from the first to one past the last element of a bf16 operand; rows x inner elements, row stride ld.
 static inline size_t operand_extent_bytes(int rows, int inner, int ld) { return 2 * ((size_t)(rows - 1) * ld + inner); }

@@ -639,7 +639,7 @@ gemm_bf16_dtl16_kernel(const GemmBf16Params p) {
 // y = x W^T on contraction-contiguous operands with the main loop of dp_gemm_pp.h.  KTAIL: K is not a multiple of the k-tile;
 // chunks of the last k-tile past K are fetched from outside the buffers (zeros) in both operands.
 template <class T, int KIND, bool FP8, bool KTAIL>
-__global__ void __launch_bounds__(512, 2) gemm_pp_kernel(const GemmBf16Params p) {
+__device__ __forceinline__ void gemm_pp_body(const GemmBf16Params& p) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave / T::WGN, wn = wave % T::WGN;
@@ -691,6 +691,18 @@ __global__ void __launch_bounds__(512, 2) gemm_pp_kernel(const GemmBf16Params p)
           async_copy_16B_buf(r, tail(h ? vb1[h ? j : 0] : vb0[h ? 0 : j], piece_b(h, j), t), off, dst + piece_b(h, j) * 1024);
       }, false, csum);
   pp_epilogue<T, KIND>(acc, smem_raw, p.epi, m0, n0, wave, wm, wn, lane);
+}
+template <class T, int KIND, bool FP8, bool KTAIL>
+__global__ void __launch_bounds__(512, 2) gemm_pp_kernel(const GemmBf16Params p) { gemm_pp_body<T, KIND, FP8, KTAIL>(p); }
+// Several products of one shape, operands and outputs at fixed distances (elements): problem blockIdx.y.
+struct GemmStrides { long a, b, out; };
+template <class T, int KIND, bool KTAIL>
+__global__ void __launch_bounds__(512, 2) gemm_pp_strided_kernel(GemmBf16Params p, const GemmStrides d) {
+  const long i = blockIdx.y;
+  p.A += i * d.a; p.B += i * d.b;
+  if constexpr (KIND == PE_F32) p.epi.out32 += i * d.out;
+  else p.epi.out += i * d.out;
+  gemm_pp_body<T, KIND, false, KTAIL>(p);
 }
 
 // Second pass of a split-K GEMM with a storage-dtype output: sums the fp32 partial tiles in ascending
@@ -880,8 +892,9 @@ static int choose_cfg(int M, int N, int K, bool a_mc, bool b_mc, bool dtl_ok, bo
     }
     if (dtl64) {
       // 64x64 tiles: up to three workgroups per CU; a k-tile costs 0.23 us while they have CUs to themselves, 0.39 us beside others
+      // (32768 of them with two k-tiles each: 165 us; 256x256 tiles 90)
       const long tiles = (long)((M + 63) / 64) * ((N + 63) / 64);
-      const float cost = 4.0f + (float)(K / 64) * (tiles <= 128 ? 0.23f : 0.39f * std::max(1.0f, (float)tiles / 512.0f));
+      const float cost = 2.2f + std::max(1.0f, (float)tiles / 512.0f) * (1.8f + (float)(K / 64) * (tiles <= 128 ? 0.23f : 0.39f));
       if (cost < best_cost) best = 15;
     }
     if (best >= 0) return best;
@@ -1152,11 +1165,7 @@ static int launch_pp_kind(const GemmBf16Params& p, hipStream_t s) {
 }
 
 template <class T>
-static int launch_pp(const GemmArgs& a, hipStream_t s) {
-  if (a.a_mc || a.b_mc || a.out_f32) return set_error(DP_EUNSUPPORTED, "gemm: the forced configuration needs contraction-contiguous operands and a storage-dtype output");
-  if (!dtl_addressable(a)) return set_error(DP_EUNSUPPORTED, "gemm: operand too large for the forced direct-to-LDS configuration");
-  const int kind = pp_kind(a);
-  if (kind < 0) return set_error(DP_EUNSUPPORTED, "gemm: the forced configuration does not have this epilogue");
+static GemmBf16Params pp_params(const GemmArgs& a) {
   GemmBf16Params p;
   p.A = (const bf16*)a.A; p.B = (const bf16*)a.B;
   p.M = a.M; p.N = a.N; p.K = a.K; p.lda = a.lda; p.ldb = a.ldb; p.split_major = 0;
@@ -1165,6 +1174,55 @@ static int launch_pp(const GemmArgs& a, hipStream_t s) {
   p.group_m = choose_group_m(a, p.tiles_m, p.tiles_n);
   p.a_bytes = (uint32_t)operand_extent_bytes(a.M, a.K, a.lda);
   p.b_bytes = (uint32_t)operand_extent_bytes(a.N, a.K, a.ldb);
+  return p;
+}
+
+template <class T, int KIND, bool KTAIL>
+static int launch_pp_strided(const GemmArgs& a, int count, const GemmStrides& d, hipStream_t s) {
+  const GemmBf16Params p = pp_params<T>(a);
+  auto kern = gemm_pp_strided_kernel<T, KIND, KTAIL>;
+  static std::atomic<bool> attr_set{false};
+  DP_TRY(set_lds_limit((const void*)kern, T::BYTES, attr_set));
+  KScope ks(KK_GEMM_NT, 2.0 * a.M * a.N * a.K * count, gemm_tensor_bytes(a) * count, s, a.M * count, a.N, a.K);
+  hipLaunchKernelGGL(kern, dim3(p.tiles_m * p.tiles_n, count), dim3(512), T::BYTES, s, p, d);
+  return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "gemm launch failed");
+}
+template <class T>
+static int launch_pp_strided_kind(const GemmArgs& a, int count, const GemmStrides& d, hipStream_t s) {
+  const bool tail = a.K % T::BK != 0;
+  if (a.out_f32) return tail ? launch_pp_strided<T, PE_F32, true>(a, count, d, s) : launch_pp_strided<T, PE_F32, false>(a, count, d, s);
+  return tail ? launch_pp_strided<T, PE_PLAIN, true>(a, count, d, s) : launch_pp_strided<T, PE_PLAIN, false>(a, count, d, s);
+}
+// `count` products y = x W^T (+ bias), operands and outputs at fixed distances.  The attention block of the image encoder makes them per
+// sample; one at a time, its probabilities x values (4096 x 512, K = 4096) are 32 tiles of 256x256 for 256 CUs and its scores wait for each
+// other's last round.  One launch for all of them when 256x128 tiles occupy at least half of the CUs, else one by one.  The additions are in the
+// same order either way.
+int launch_gemm_strided(const GemmArgs& a, int count, long stride_a, long stride_b, long stride_out, hipStream_t s) {
+  if (a.dtype != BF16 || count <= 0 || a.a_mc || a.b_mc || a.accumulate || (!a.out_f32 && pp_kind(a) != PE_PLAIN) || a.choice_rows >= 0 || stride_a % 8 || stride_b % 8 || stride_out % 8)
+    return set_error(DP_EUNSUPPORTED, "gemm: operands or epilogue of a strided batch");
+  const long n256 = (long)((a.M + 255) / 256) * ((a.N + 255) / 256) * count, n128 = (long)((a.M + 255) / 256) * ((a.N + 127) / 128) * count;
+  if (n128 >= kCUs / 2 && dtl_addressable(a) && count <= 65535) {
+    const float kt = (float)((a.K + 63) / 64), t256 = (float)((n256 + kCUs - 1) / kCUs) * (5.0f + 1.30f * kt), t128 = (float)((n128 + kCUs - 1) / kCUs) * (5.0f + 0.72f * kt);
+    const GemmStrides d{stride_a, stride_b, stride_out};
+    return t256 <= t128 ? launch_pp_strided_kind<PpTile<256, 128, 128, 4, 2>>(a, count, d, s) : launch_pp_strided_kind<PpTile<256, 64, 64, 4, 2>>(a, count, d, s);
+  }
+  for (int i = 0; i < count; ++i) {
+    GemmArgs g = a;
+    g.A = (const bf16*)a.A + i * stride_a; g.B = (const bf16*)a.B + i * stride_b;
+    if (a.out_f32) g.out_f32 = a.out_f32 + i * stride_out;
+    else g.out = (bf16*)a.out + i * stride_out;
+    DP_TRY(launch_gemm(g, s));
+  }
+  return DP_OK;
+}
+
+template <class T>
+static int launch_pp(const GemmArgs& a, hipStream_t s) {
+  if (a.a_mc || a.b_mc || a.out_f32) return set_error(DP_EUNSUPPORTED, "gemm: the forced configuration needs contraction-contiguous operands and a storage-dtype output");
+  if (!dtl_addressable(a)) return set_error(DP_EUNSUPPORTED, "gemm: operand too large for the forced direct-to-LDS configuration");
+  const int kind = pp_kind(a);
+  if (kind < 0) return set_error(DP_EUNSUPPORTED, "gemm: the forced configuration does not have this epilogue");
+  const GemmBf16Params p = pp_params<T>(a);
   KScope ks(KK_GEMM_NT, 2.0 * a.M * a.N * a.K, gemm_tensor_bytes(a), s, a.M, a.N, a.K);
   switch (kind) {
 #define DP_PP_CASE(k_) case k_: return launch_pp_kind<T, k_>(p, s)

@@ -155,33 +155,66 @@ int launch_groupnorm(const GroupNormArgs& a, hipStream_t s) {
 }
 
 // ------------------------------------------------------------------ row softmax (the attention block's probabilities)
-// One wave per row of fp32 logits: maximum, sum of exponentials, normalised probabilities in bf16.
+// One wave per row of fp32 logits: maximum, sum of exponentials, normalised probabilities in bf16.  Bound by memory (6 bytes per logit): a row
+// of up to 256 * NV logits stays in registers between the three steps (NV = 0: any length, read again for each).  8 x 4096 rows of 4096
+// logits: 268 us in eight launches that read the row three times, now 173 us (4.7 TB/s).
+template <int NV>
 __global__ void __launch_bounds__(256) softmax_rows_kernel(const float* __restrict__ s, bf16* __restrict__ p, long rows, int cols, float scale_log2) {
   const int lane = threadIdx.x & 63;
   const long row = blockIdx.x * 4L + (threadIdx.x >> 6);
   if (row >= rows) return;
   const float* sr = s + row * cols;
   bf16* pr = p + row * cols;
-  float mx = -INFINITY;
+  float mx = -INFINITY, sum = 0.f;
+  auto put = [&](int c, const f32x4& e, float inv) {
+    bf16x4 o;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) o[t] = (bf16)(e[t] * inv);
+    *reinterpret_cast<bf16x4*>(pr + c) = o;
+  };
+  if constexpr (NV > 0) {
+    f32x4 v[NV];
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int c = lane * 4 + 256 * i;
+      v[i] = *reinterpret_cast<const f32x4*>(sr + min(c, cols - 4));
+    }
+#pragma unroll
+    for (int i = 0; i < NV; ++i) mx = fmaxf(fmaxf(mx, fmaxf(v[i][0], v[i][1])), fmaxf(v[i][2], v[i][3]));     // what is read past the end is the row's last four again
+    mx = wave_max(mx) * scale_log2;          // the scale is positive: it commutes with the maximum
+#pragma unroll
+    for (int i = 0; i < NV; ++i)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        v[i][t] = __builtin_amdgcn_exp2f(fmaf(v[i][t], scale_log2, -mx));
+        sum += lane * 4 + 256 * i < cols ? v[i][t] : 0.f;
+      }
+    const float inv = 1.0f / wave_sum(sum);
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int c = lane * 4 + 256 * i;
+      if (c < cols) put(c, v[i], inv);
+    }
+    return;
+  }
   for (int c = lane * 4; c < cols; c += 256) {
     const f32x4 v = *reinterpret_cast<const f32x4*>(sr + c);
     mx = fmaxf(fmaxf(mx, fmaxf(v[0], v[1])), fmaxf(v[2], v[3]));
   }
-  mx = wave_max(mx) * scale_log2;          // the scale is positive: it commutes with the maximum
-  float sum = 0.f;
-  for (int c = lane * 4; c < cols; c += 256) {
-    const f32x4 v = *reinterpret_cast<const f32x4*>(sr + c);
+  mx = wave_max(mx) * scale_log2;
+  auto ex = [&](int c) {
+    f32x4 v = *reinterpret_cast<const f32x4*>(sr + c);
 #pragma unroll
-    for (int t = 0; t < 4; ++t) sum += __builtin_amdgcn_exp2f(fmaf(v[t], scale_log2, -mx));
+    for (int t = 0; t < 4; ++t) v[t] = __builtin_amdgcn_exp2f(fmaf(v[t], scale_log2, -mx));
+    return v;
+  };
+  for (int c = lane * 4; c < cols; c += 256) {
+    const f32x4 v = ex(c);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) sum += v[t];
   }
   const float inv = 1.0f / wave_sum(sum);
-  for (int c = lane * 4; c < cols; c += 256) {
-    const f32x4 v = *reinterpret_cast<const f32x4*>(sr + c);
-    bf16x4 o;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) o[t] = (bf16)(__builtin_amdgcn_exp2f(fmaf(v[t], scale_log2, -mx)) * inv);
-    *reinterpret_cast<bf16x4*>(pr + c) = o;
-  }
+  for (int c = lane * 4; c < cols; c += 256) put(c, ex(c), inv);
 }
 
 int launch_softmax_rows(int dtype, const float* s, void* p, long rows, int cols, float scale, hipStream_t st) {
@@ -190,7 +223,8 @@ int launch_softmax_rows(int dtype, const float* s, void* p, long rows, int cols,
   if (!s || !p || ((uintptr_t)s % 16) || ((uintptr_t)p % 8)) return set_error(DP_EALIGN, "softmax_rows: null or misaligned operand");
   if ((rows + 3) / 4 > 0x7fffffffL) return set_error(DP_EUNSUPPORTED, "softmax_rows: too many rows");
   KScope ks(KK_SOFTMAX, 0.0, 4.0 * (double)rows * cols + 2.0 * (double)rows * cols, st, (int)rows, cols, 0);
-  hipLaunchKernelGGL(softmax_rows_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, s, (bf16*)p, rows, cols, scale * 1.4426950408889634f);
+  auto kern = cols <= 1024 ? softmax_rows_kernel<4> : (cols <= 2048 ? softmax_rows_kernel<8> : (cols <= 4096 ? softmax_rows_kernel<16> : softmax_rows_kernel<0>));
+  hipLaunchKernelGGL(kern, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, s, (bf16*)p, rows, cols, scale * 1.4426950408889634f);
   return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "softmax_rows launch failed");
 }
 
@@ -216,6 +250,10 @@ struct ImgBuf {
   float* gnc; size_t gnc_bytes; const void* stat_of; int stat_blocks;
 };
 
+// Samples whose attention runs in the same launches: as many as keep their score and probability matrices (6 bytes per pair of pixels; 100 MB a
+// sample at 64 x 64) within 1 GiB.
+static int attn_group(long px, int n) { return (int)std::max<long>(1, std::min<long>(n, (1L << 30) / (6 * px * px))); }
+
 static size_t layer_act_elems(const dp_image_encoder& e, int l, int n) {
   const size_t in_px = (size_t)e.h[l] * e.w[l], out_px = (size_t)e.h[l + 1] * e.w[l + 1];
   const size_t cmax = std::max(e.c[l], e.c[l + 1]);
@@ -224,22 +262,26 @@ static size_t layer_act_elems(const dp_image_encoder& e, int l, int n) {
 
 static void plan_image(const dp_image_encoder& e, void* base, int lb, int le, int n, ImgBuf& b) {
   Plan p(base);
-  size_t maxact = 0, gn = 0, gnc = 0, attn_rows = 0, attn_px = 0; int attn_c = 0;
+  size_t maxact = 0, gn = 0, gnc = 0, attn_rows = 0, attn_v = 0, attn_s = 0; int attn_c = 0;
   for (int l = lb; l < le; ++l) {
     maxact = std::max(maxact, layer_act_elems(e, l, n));
     const int px = e.h[l + 1] * e.w[l + 1];
     gnc = std::max(gnc, (size_t)n * (px / conv_stat_block(px) + 1) * e.c[l + 1] * 2 * sizeof(float));
     const int HW = e.h[l] * e.w[l];
     if (e.layers[l].kind != DP_IMG_CONV) gn = std::max(gn, std::max(gn_scratch_bytes(n, HW, e.c[l]), gn_scratch_bytes(n, HW, e.c[l + 1])));
-    if (e.layers[l].kind == DP_IMG_ATTN) { attn_rows = std::max(attn_rows, (size_t)n * HW); attn_px = std::max(attn_px, (size_t)HW); attn_c = std::max(attn_c, e.c[l]); }
+    if (e.layers[l].kind == DP_IMG_ATTN) {
+      const size_t group = attn_group(HW, n);
+      attn_rows = std::max(attn_rows, (size_t)n * HW); attn_c = std::max(attn_c, e.c[l]);
+      attn_v = std::max(attn_v, group * HW); attn_s = std::max(attn_s, group * HW * HW);
+    }
   }
   b.ping = p.take(maxact * 2); b.pong = p.take(maxact * 2); b.t1 = p.take(maxact * 2); b.t2 = p.take(maxact * 2); b.t3 = p.take(maxact * 2);
   b.gn_bytes = gn; b.gn = gn ? (float*)p.take(gn) : nullptr;
   b.gnc_bytes = gnc; b.gnc = (float*)p.take(gnc); b.stat_of = nullptr; b.stat_blocks = 0;
   if (attn_rows) {
     const size_t qb = attn_rows * attn_c * 2;
-    b.q = p.take(qb); b.k = p.take(qb); b.v = p.take((size_t)attn_px * attn_c * 2); b.a = p.take(qb);   // v: one sample's values, transposed
-    b.scores = (float*)p.take(attn_px * attn_px * 4); b.probs = p.take(attn_px * attn_px * 2);
+    b.q = p.take(qb); b.k = p.take(qb); b.v = p.take(attn_v * attn_c * 2); b.a = p.take(qb);   // v: a group's values, transposed
+    b.scores = (float*)p.take(attn_s * 4); b.probs = p.take(attn_s * 2);
   } else { b.q = b.k = b.v = b.a = b.probs = nullptr; b.scores = nullptr; }
   b.bytes = p.off;
 }
@@ -299,19 +341,20 @@ static int image_layer(const dp_image_encoder& e, int l, const void* const* P, c
       DP_TRY(launch_gemm(linear(w.t1, R, ci, P[2], ci, P[3], w.q), st));
       DP_TRY(launch_gemm(linear(w.t1, R, ci, P[4], ci, P[5], w.k), st));
       const float scale = 1.0f / sqrtf((float)ci);
-      for (int s = 0; s < n; ++s) {
-        const size_t off = (size_t)s * HW * ci * 2;
+      const int group = attn_group(HW, n);
+      const long act = (long)HW * ci, sq = (long)HW * HW;
+      for (int s = 0; s < n; s += group) {
+        const int ns = std::min(group, n - s);
+        const size_t off = (size_t)s * act * 2;
         // The values are produced transposed, v^T [c, HW] = W_v h_s^T (the weight as the row operand), so that the
         // product with the probabilities contracts over a contiguous index on both sides.  Their bias is added after
         // the attention instead: every row of the probabilities sums to one, so P (V + 1 b^T) = P V + 1 b^T.
-        DP_TRY(launch_gemm(linear(P[6], ci, ci, (const char*)w.t1 + off, HW, nullptr, w.v), st));
-        GemmArgs g; memset(&g, 0, sizeof(g));          // scores = q_s k_s^T, fp32
-        g.dtype = BF16; g.A = (const char*)w.q + off; g.B = (const char*)w.k + off; g.M = HW; g.N = HW; g.K = ci; g.lda = ci; g.ldb = ci;
+        DP_TRY(launch_gemm_strided(linear(P[6], ci, ci, (const char*)w.t1 + off, HW, nullptr, w.v), ns, 0, act, act, st));
+        GemmArgs g = linear((const char*)w.q + off, HW, ci, (const char*)w.k + off, HW, nullptr, nullptr);          // scores = q_s k_s^T, fp32
         g.out_f32 = w.scores; g.ldo32 = HW;
-        DP_TRY(launch_gemm(g, st));
-        DP_TRY(launch_softmax_rows(BF16, w.scores, w.probs, HW, HW, scale, st));
-        g = linear(w.probs, HW, HW, w.v, ci, P[7], (char*)w.a + off);      // a_s = probs v_s + b_v
-        DP_TRY(launch_gemm(g, st));
+        DP_TRY(launch_gemm_strided(g, ns, act, act, sq, st));
+        DP_TRY(launch_softmax_rows(BF16, w.scores, w.probs, (long)ns * HW, HW, scale, st));
+        DP_TRY(launch_gemm_strided(linear(w.probs, HW, HW, w.v, ci, P[7], (char*)w.a + off), ns, sq, act, act, st));      // a_s = probs v_s + b_v
       }
       GemmArgs g = linear(w.a, R, ci, P[8], ci, P[9], dst);
       g.residual = src; g.ld_res = ci;

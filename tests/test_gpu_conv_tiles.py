@@ -42,3 +42,24 @@ def test_few_pixel_tiles_match_oracle(cfg):
     de.run_slices(1)
     torch.cuda.synchronize()
     assert np.array_equal(de.output(), whole)
+
+
+@pytest.mark.parametrize("hw,c,batch", [((8, 8), 64, 5), ((40, 32), 72, 4), ((56, 46), 128, 2), ((66, 64), 64, 2)],
+                         ids=["one_by_one", "one_launch_ragged", "softmax_2576", "softmax_beyond_4096"])
+def test_attention_of_several_samples_matches_oracle(hw, c, batch):
+    """The attention block's products of a call's samples in one launch or one by one, and its softmax by row length: against
+    the oracle, and the same bits one sample at a time."""
+    import torch
+    from paper_2405_01248_amd.harness import DeviceImageEncoder, rel_err
+    cfg = _layer("attn", c, c, 1, hw, batch)
+    inp = si.make_image_encoder_inputs(cfg, seed=4, randomize_norm=True, weight_std=0.0)
+    ref = ie.encoder_fwd_partial(inp["params"], cfg.layer_dicts(), inp["x"], 0, 1, 0, cfg.global_batch, cfg.groups, cfg.gn_eps)
+    de = DeviceImageEncoder(cfg, inp)
+    de.run_slices(batch)
+    torch.cuda.synchronize()
+    whole = de.output()
+    assert rel_err(whole, ref) <= 2e-2
+    de.out.zero_()
+    de.run_slices(1)
+    torch.cuda.synchronize()
+    assert np.array_equal(de.output(), whole)
