@@ -70,10 +70,11 @@ __global__ void __launch_bounds__(256) gn_finalize_kernel(const float* __restric
   const int b = wg / groups, g = wg % groups, cpg = C / groups;
   double s = 0.0, q = 0.0;
   const int n = nblocks * cpg;
+#pragma unroll 8
   for (int i = tid; i < n; i += 256) {
     const int blk = i / cpg, c = g * cpg + i % cpg;
-    const float* pp = partial + (((size_t)b * nblocks + blk) * C + c) * 2;
-    s += (double)pp[0]; q += (double)pp[1];
+    const float2 v = *reinterpret_cast<const float2*>(partial + (((size_t)b * nblocks + blk) * C + c) * 2);
+    s += (double)v.x; q += (double)v.y;
   }
   s = wave_sum_f64(s); q = wave_sum_f64(q);
   if (lane == 0) { red[0][wave] = s; red[1][wave] = q; }
@@ -116,6 +117,78 @@ __global__ void __launch_bounds__(256) gn_apply_kernel(const bf16* __restrict__ 
   *reinterpret_cast<bf16x8*>(y + pix * C + c) = o;
 }
 
+// GroupNorm of samples with few pixels in one launch: a workgroup per (sample, group) keeps the group's values in registers, takes mean
+// and variance from them and writes the result.  Bound by latency: of the three passes above each takes 5 us at 48 x 41 pixels,
+// 512 channels; together 16 us and two gaps, now 9 us.  Thread tid holds 16-byte chunks tid + 512 j of the group's HW x cpg / 8.
+constexpr int GN_SMALL_MAX = 8;      // chunks a thread holds at most: with 16 (64 x 64 pixels) it is no faster than the passes
+template <int NV>
+__global__ void __launch_bounds__(512) gn_small_kernel(const bf16* __restrict__ x, bf16* __restrict__ y, int HW, int C, int groups, float eps,
+                                                       const bf16* __restrict__ gamma, const bf16* __restrict__ beta, int silu) {
+  __shared__ double red[2][8];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, b = blockIdx.y;
+  // adjacent groups share cache lines: give them to one XCD
+  const int g = groups % 8 ? blockIdx.x : (blockIdx.x % 8) * (groups / 8) + blockIdx.x / 8;
+  const int cpg = C / groups, cp8 = cpg / 8, n = HW * cp8;
+  const int ch = g * cpg + tid % cp8 * 8;                 // 512 is a multiple of cp8: the same channels in every chunk of a thread
+  const bf16* xs = x + (size_t)b * HW * C + ch;
+  bf16* ys = y + (size_t)b * HW * C + ch;
+  bf16x8 v[NV];
+#pragma unroll
+  for (int j = 0; j < NV; ++j) {
+    const int i = tid + 512 * j;
+    v[j] = i < n ? *reinterpret_cast<const bf16x8*>(xs + (size_t)(i / cp8) * C) : zero8();
+  }
+  float s = 0.f;
+#pragma unroll
+  for (int j = 0; j < NV; ++j)
+#pragma unroll
+    for (int t = 0; t < 8; ++t) s += (float)v[j][t];
+  auto total = [&](float part, double* slot) {
+    const double w = wave_sum_f64((double)part);
+    if (lane == 0) slot[wave] = w;
+    __syncthreads();
+    double sum = slot[0];
+#pragma unroll
+    for (int i = 1; i < 8; ++i) sum += slot[i];
+    return sum;
+  };
+  const double cnt = (double)HW * cpg, mean = total(s, red[0]) / cnt;
+  const float m = (float)mean;
+  float q = 0.f;
+#pragma unroll
+  for (int j = 0; j < NV; ++j)
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      const float d = (float)v[j][t] - m;
+      q = tid + 512 * j < n ? fmaf(d, d, q) : q;
+    }
+  const double rstd = 1.0 / sqrt(total(q, red[1]) / cnt + (double)eps);
+  const bf16x8 gm = *reinterpret_cast<const bf16x8*>(gamma + ch), bt = *reinterpret_cast<const bf16x8*>(beta + ch);
+  float sc[8], sh[8];
+#pragma unroll
+  for (int t = 0; t < 8; ++t) {
+    const double a = rstd * (double)(float)gm[t];
+    sc[t] = (float)a; sh[t] = (float)((double)(float)bt[t] - mean * a);
+  }
+#pragma unroll
+  for (int j = 0; j < NV; ++j) {
+    const int i = tid + 512 * j;
+    bf16x8 o;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      float f = fmaf((float)v[j][t], sc[t], sh[t]);
+      if (silu) f = silu_f(f);
+      o[t] = (bf16)f;
+    }
+    if (i < n) *reinterpret_cast<bf16x8*>(ys + (size_t)(i / cp8) * C) = o;
+  }
+}
+// Decided per sample, never by the number of samples: the two ways do not round alike.  (16-byte segments, 8 channels a group, are too short.)
+bool gn_in_one_launch(int HW, int C, int groups) {
+  const int cpg = C / groups, cp8 = cpg / 8;
+  return C % groups == 0 && cpg >= 16 && cpg % 8 == 0 && 512 % cp8 == 0 && (long)HW * cp8 <= 512 * GN_SMALL_MAX;
+}
+
 static int gn_blocks(int B, int HW, int C, int* pix_per_block) {
   const int C8 = C / 8, PPB = GN_THREADS / C8;
   // (the block count per sample does not depend on the number of samples: a sample's sums are grouped the same way in every slice)
@@ -143,6 +216,13 @@ int launch_groupnorm(const GroupNormArgs& a, hipStream_t s) {
   float* partial = a.scratch;
   float* ab = (float*)((char*)a.scratch + align_up((size_t)a.B * nb * a.C * 2 * sizeof(float), 256));
   const double bytes = 2.0 * 2.0 * (double)a.B * a.HW * a.C + 2.0 * (double)a.B * a.HW * a.C;   // x read twice, y written once
+  if (gn_in_one_launch(a.HW, a.C, a.groups)) {
+    KScope ks(KK_GROUPNORM, 0.0, 4.0 * (double)a.B * a.HW * a.C, s, a.B * a.HW, a.C, a.groups);
+    const int nv = (a.HW * (a.C / a.groups / 8) + 511) / 512;
+    auto kern = nv <= 4 ? gn_small_kernel<4> : gn_small_kernel<GN_SMALL_MAX>;
+    hipLaunchKernelGGL(kern, dim3(a.groups, a.B), dim3(512), 0, s, (const bf16*)a.x, (bf16*)a.y, a.HW, a.C, a.groups, a.eps, (const bf16*)a.gamma, (const bf16*)a.beta, a.silu);
+    return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "groupnorm launch failed");
+  }
   const bool ready = a.ready_partial != nullptr && a.ready_blocks > 0;
   KScope ks(KK_GROUPNORM, 0.0, ready ? bytes - 2.0 * (double)a.B * a.HW * a.C : bytes, s, a.B * a.HW, a.C, a.groups);
   if (!ready) hipLaunchKernelGGL(gn_partial_kernel, dim3(nb, a.B), dim3(GN_THREADS), 0, s, (const bf16*)a.x, a.HW, a.C, ppb, partial);
@@ -305,7 +385,7 @@ static int image_layer(const dp_image_encoder& e, int l, const void* const* P, c
     // the convolution's epilogue can produce the first pass of a GroupNorm over its output
     const int out_px = ((H - 1) / stride + 1) * ((W - 1) / stride + 1);
     int applied = 0;
-    if (w.gnc && (size_t)n * (out_px / conv_stat_block(out_px) + 1) * cout * 2 * sizeof(float) <= w.gnc_bytes) { a.gn_partial = w.gnc; a.gn_applied = &applied; }
+    if (w.gnc && !gn_in_one_launch(out_px, cout, e.d.groups) && (size_t)n * (out_px / conv_stat_block(out_px) + 1) * cout * 2 * sizeof(float) <= w.gnc_bytes) { a.gn_partial = w.gnc; a.gn_applied = &applied; }
     w.stat_of = nullptr;
     const int rc = launch_conv3x3(a, st);
     if (rc == DP_OK && applied) { w.stat_of = y; w.stat_blocks = out_px / conv_stat_block(out_px); }

@@ -26,6 +26,8 @@ def _layer(kind, ci, co, stride, hw, batch, groups=8):
     _layer("conv", 8, 72, 2, (33, 31), 3),           # ... ragged bands and channels, stride 2
     _layer("resnet", 8, 64, 1, (24, 24), 3),         # ... statistics blocks of 64, nine a sample
     _layer("resnet", 8, 128, 1, (128, 132), 1),      # ... statistics blocks of 256
+    _layer("resnet", 64, 64, 1, (45, 45), 2, 4),     # 16 channels a group, 4050 of 4096 values in the one-launch GroupNorm
+    _layer("resnet", 64, 128, 1, (7, 5), 2, 2),      # ... 32 and 64 channels a group
     _layer("resnet", 256, 256, 1, (64, 80), 1, 32),  # enough tiles for the 128-row shape
 ], ids=lambda c: c.name)
 def test_few_pixel_tiles_match_oracle(cfg):
