@@ -264,7 +264,9 @@ template <int BK> __device__ __forceinline__ int kc_key(int r) { return BK == 32
 // k-step (64 bytes instead of 32: two 16-byte chunks per lane) and the instruction, v_mfma_f32_32x32x64_f8f6f4 with both
 // block scales at 2^0.  Any assignment of the 64 bytes of a k-step to lanes and byte slots gives the right product as
 // long as it is the same for both operands, which it is by symmetry.
-template <int BM, int BN, int BK, int STAGES, int WGM, int WGN, bool A_MC, bool B_MC, bool FP8 = false>
+// SEG: the sums of the contraction's segments of k_tiles_per_split k-tiles are formed apart and added in order, the additions of a split-K
+// launch and its reduction without the partial tiles' way through memory.
+template <int BM, int BN, int BK, int STAGES, int WGM, int WGN, bool A_MC, bool B_MC, bool FP8 = false, bool SEG = false>
 __global__ void __launch_bounds__(WGM * WGN * 64)
 gemm_bf16_dtl_kernel(const GemmBf16Params p) {
   using S = DtlSmem<BM, BN, BK, STAGES, WGM, WGN>;
@@ -285,7 +287,7 @@ gemm_bf16_dtl_kernel(const GemmBf16Params p) {
   tile_of_block(blockIdx.x, p.tiles_m, p.tiles_n, p.group_m, tile_m, tile_n);
   const int m0 = tile_m * BM, n0 = tile_n * BN;
   const int kt_begin = blockIdx.z * p.k_tiles_per_split;
-  const int kt_end = min(p.K / BK, kt_begin + p.k_tiles_per_split);
+  const int kt_end = SEG ? p.K / BK : min(p.K / BK, kt_begin + p.k_tiles_per_split);
   const int nk = kt_end - kt_begin;
 
   // per-lane byte offset (inside the operand) of each of this wave's 1 KB pieces at k-tile 0;
@@ -410,6 +412,20 @@ gemm_bf16_dtl_kernel(const GemmBf16Params p) {
   // all k-tiles but the last: no branch between the fragment reads and the MFMAs, so the waits for
   // LDS data stay exact (a merge of paths with different numbers of reads in flight would make the
   // compiler wait for all of them)
+  f32x16 total[SEG ? TM : 1][SEG ? TN : 1];
+  int seg_left = p.k_tiles_per_split, segments = 0;
+  auto close_segment = [&]() {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          total[SEG ? i : 0][SEG ? j : 0][r] = segments ? total[SEG ? i : 0][SEG ? j : 0][r] + acc[i][j][r] : acc[i][j][r];
+          acc[i][j][r] = 0.f;
+        }
+    ++segments; seg_left = p.k_tiles_per_split;
+  };
   for (int t = 0; t + 1 < nk; ++t) {
     const int st = t % STAGES;
     const bool refill = t >= 1 && t - 1 + STAGES < nk;   // k-tile t - 1 + STAGES goes into the buffer k-tile t - 1 left
@@ -444,6 +460,7 @@ gemm_bf16_dtl_kernel(const GemmBf16Params p) {
       if (refill) DP_DTL_ISSUE_PART(t - 1 + STAGES, ks, KS);
       __builtin_amdgcn_sched_barrier(0);
     }
+    if (SEG && --seg_left == 0) close_segment();
   }
   {
     const int st = (nk - 1) % STAGES;
@@ -459,6 +476,13 @@ gemm_bf16_dtl_kernel(const GemmBf16Params p) {
 #undef DP_DTL_MFMAS
 #undef DP_DTL_ISSUE
 #undef DP_DTL_ISSUE_PART
+  if (SEG) {
+    close_segment();
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[i][j] = total[SEG ? i : 0][SEG ? j : 0];
+  }
   __syncthreads();   // every wave is done with the operand tiles before they are reused below
 
   float* Cw = reinterpret_cast<float*>(smem_raw) + wave * 32 * S::C_LD;
@@ -705,6 +729,114 @@ __global__ void __launch_bounds__(512, 2) gemm_pp_strided_kernel(GemmBf16Params 
   gemm_pp_body<T, KIND, false, KTAIL>(p);
 }
 
+// y = x W^T on 64x64 tiles whose NW waves share the contraction instead of the tile: wave w computes the whole tile over the k-tiles
+// w, w + NW, ... of the workgroup's range, from a stage of LDS of its own, and the NW partial tiles are added at the end, in wave order.
+// Why: a 64x64 tile split 2x2 among four waves is bound by LDS (each wave reads 2 fragments per MFMA: 32 KB read and 16 KB written per k-tile,
+// 0.23 us) and by its barriers; here a k-tile is read once (16 KB, 4 fragments for 4 MFMAs) and no wave ever waits for another before the
+// end.  A wave holds one k-tile in registers and one on its way to LDS; the other waves of the CU hide the latency.
+// What bounds it is fetching operands, about 20 TB/s over all CUs, so the widest tile that still gives one workgroup per CU is taken (kWave).
+// Measured (M x N, K; us, 64x64 tiles split 2x2 or 128x128 ones with split-K before): 1026 x 1280, 3840: 27 -> 19, 10240: 66 -> 40;
+// 1024 x 1152, 4608: 32 -> 20; 2048 x 1152, 4608: 37 -> 30; 924 x 768, 3072: 21 -> 12.5.
+template <int NW_, int TM_, int TN_>
+struct WaveTile {
+  static constexpr int NW = NW_, TM = TM_, TN = TN_, BM = 32 * TM, BN = 32 * TN, LD = BN + 4, A_BYTES = BM * 128, REGION = (BM + BN) * 128;
+  static constexpr size_t SLAB = (size_t)32 * LD * 4, BYTES = NW * (REGION > SLAB ? REGION : SLAB);
+};
+template <class T>
+__global__ void __launch_bounds__(T::NW * 64, T::TM * T::TN <= 6 ? 2 : 1) gemm_wave_kernel(const GemmBf16Params p) {
+  constexpr int NW = T::NW, TM = T::TM, TN = T::TN, LD = T::LD;
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 5, l32 = lane & 31;
+  int tile_m, tile_n;
+  tile_of_block(blockIdx.x, p.tiles_m, p.tiles_n, p.group_m, tile_m, tile_n);
+  const int m0 = tile_m * T::BM, n0 = tile_n * T::BN;
+  const int kt_begin = blockIdx.z * p.k_tiles_per_split, kt_end = min(p.K / 64, kt_begin + p.k_tiles_per_split);
+  const rsrc_t ra = make_rsrc(p.A, p.a_bytes), rb = make_rsrc(p.B, p.b_bytes);
+  uint32_t va[4 * TM], vb[4 * TN];
+#pragma unroll
+  for (int j = 0; j < 4 * TM; ++j) {
+    const int r = 8 * j + (lane >> 3), c = (lane & 7) ^ kc_key<64>(r);
+    va[j] = 2u * ((uint32_t)min(m0 + r, p.M - 1) * p.lda + c * 8);
+  }
+#pragma unroll
+  for (int j = 0; j < 4 * TN; ++j) {
+    const int r = 8 * j + (lane >> 3), c = (lane & 7) ^ kc_key<64>(r);
+    vb[j] = 2u * ((uint32_t)min(n0 + r, p.N - 1) * p.ldb + c * 8);
+  }
+  unsigned char* own = smem_raw + wave * T::REGION;
+  auto issue = [&](int t) {
+#pragma unroll
+    for (int j = 0; j < 4 * TM; ++j) async_copy_16B_buf(ra, va[j], (uint32_t)t * 128u, own + j * 1024);
+#pragma unroll
+    for (int j = 0; j < 4 * TN; ++j) async_copy_16B_buf(rb, vb[j], (uint32_t)t * 128u, own + T::A_BYTES + j * 1024);
+  };
+  f32x16 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+  int t = kt_begin + wave;
+  if (t < kt_end) issue(t);
+#pragma unroll 1
+  for (; t < kt_end; t += NW) {
+    bf16x8 fa[4][TM], fb[4][TN];
+    wait_vmcnt<0>();
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        const int r = 32 * i + l32;
+        fa[ks][i] = *reinterpret_cast<const bf16x8*>(own + r * 128 + ((2 * ks + g) ^ kc_key<64>(r)) * 16);
+      }
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const int r = 32 * j + l32;
+        fb[ks][j] = *reinterpret_cast<const bf16x8*>(own + T::A_BYTES + r * 128 + ((2 * ks + g) ^ kc_key<64>(r)) * 16);
+      }
+    }
+    wait_lgkmcnt0();
+    if (t + NW < kt_end) issue(t + NW);
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = mfma32(fb[ks][j], fa[ks][i], acc[i][j]);      // transposed: a lane gets four neighbouring columns of a row
+  }
+  float* slab = reinterpret_cast<float*>(smem_raw);
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        f32x4 v;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = acc[i][j][4 * q + u];
+        *reinterpret_cast<f32x4*>(slab + (wave * 32 + l32) * LD + 32 * j + 8 * q + 4 * g) = v;
+      }
+    __syncthreads();
+    for (int x = tid; x < 4 * T::BN; x += NW * 64) {
+      const int row = x / (T::BN / 8), c = x % (T::BN / 8) * 8, m = m0 + 32 * i + row, n = n0 + c;
+      if (m >= p.epi.M || n >= p.epi.N) continue;
+      float v[8];
+      const float* src = slab + row * LD + c;
+      *reinterpret_cast<f32x4*>(&v[0]) = *reinterpret_cast<const f32x4*>(src);
+      *reinterpret_cast<f32x4*>(&v[4]) = *reinterpret_cast<const f32x4*>(src + 4);
+#pragma unroll
+      for (int w = 1; w < NW; ++w) {
+        const f32x4 y0 = *reinterpret_cast<const f32x4*>(src + w * 32 * LD), y1 = *reinterpret_cast<const f32x4*>(src + w * 32 * LD + 4);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) { v[u] += y0[u]; v[4 + u] += y1[u]; }
+      }
+      epi_vec8(p.epi, m, n, v);
+    }
+  }
+}
+
 // Second pass of a split-K GEMM with a storage-dtype output: sums the fp32 partial tiles in ascending
 // split order (fixed order, run-to-run identical) and applies the GEMM's epilogue to the sums.  One thread
 // per 8 consecutive columns of a row.
@@ -821,26 +953,72 @@ static int choose_splits_epi(long tiles, int kt) {
   return s;
 }
 
+// 64x64 tiles: a k-tile costs 0.31 us while they have CUs to themselves, 0.39 us beside another, 0.5 us per 512 tiles where there are more
+// (32768 of them with two k-tiles each: 165 us; 256x256 tiles 90).
+static float tile64_us(long tiles, int kt, int z) {
+  tiles *= z; kt = (kt + z - 1) / z;
+  const float some = 4.0f + (float)kt * (tiles <= 128 ? 0.31f : 0.39f);
+  return tiles <= 512 ? some : std::max(some, 0.2f + (float)tiles / 512.0f * (1.57f + 0.5f * (float)kt));
+}
+// 128x128 tiles, eight waves.  heavy: an epilogue with an activation, which nothing overlaps.
+static float tile128_us(long tiles, int kt, bool heavy) {
+  return (float)((tiles + kCUs - 1) / kCUs) * ((heavy ? 5.5f : 4.0f) + (float)kt * (0.40f + 0.0004f * (float)std::min<long>(tiles, kCUs)));
+}
+// The pass that adds z partial results; ln: and does the LayerNorm that would otherwise be a launch of its own.
+static float reduce_us(int rows, int N, int z, bool ln) { return (ln ? 0.5f : 5.0f) + (float)(z + 2) * (float)rows * (float)N * 1.5e-6f; }
+
 // Split-K factor of a storage-dtype GEMM on 128x128 tiles (configuration 13) and its estimated time in us: rounds of 256
 // workgroups plus, where it is split, a second launch and the partial sums' traffic.  A stage on a small local batch (1024 rows,
 // 72 tiles, contractions of 3456 or 4608) spends 28-36 us in one of these projections unsplit, 22-27 us split by 3.  ln: the
 // second launch also does the LayerNorm that would otherwise be one of its own.
-static int splits_128(int rows, int N, int K, bool ln, float* us) {
+static int splits_128(int rows, int N, int K, bool ln, float* us, bool heavy = false) {
   const long tiles = (long)((rows + 127) / 128) * ((N + 127) / 128);
   const int kt = K / 64;
   int best = 1;
   for (int s = 1; s <= 8 && (s == 1 || kt / s >= 6); ++s) {
-    const float t = (float)((tiles * s + kCUs - 1) / kCUs) * (4.0f + (float)((kt + s - 1) / s) * 0.45f) +
-                    (s > 1 ? (ln ? 0.5f : 5.0f) + (float)(s + 2) * (float)rows * (float)N * 1.5e-6f : 0.0f);
+    const float t = tile128_us(tiles * s, (kt + s - 1) / s, heavy && s == 1) + (s > 1 ? reduce_us(rows, N, s, ln) : 0.0f);
     if (s == 1 || t < *us) { best = s; *us = t; }
   }
   return best;
 }
 
+
+// Tiles whose waves share the contraction (gemm_wave_kernel): fixed part of a tile, and the time of a k-tile of the workgroup, which grows
+// with the number of tiles in flight since what bounds it is the rate at which all CUs together fetch operands (about 20 TB/s).  us,
+// fitted on MI355X over 77..4928 rows, 640..10240 columns, contractions of 640..10240.
+struct WaveCost { int bm, bn; bool two_on_cu; float fixed, per_kt, per_kt_tile; };
+static const WaveCost kWave[] = {{64, 64, true, 5.8f, 0.070f, 0.00040f}, {64, 96, false, 7.0f, 0.115f, 0.00040f}, {128, 96, false, 9.0f, 0.115f, 0.00091f}, {128, 128, false, 9.6f, 0.20f, 0.0010f}};
+// Estimated time; splits: parts the contraction is cut into beyond the waves of a workgroup, where few tiles would each walk a long one.
+static float wave_us(const WaveCost& c, int rows, int N, int K, bool may_split, bool ln, int* splits) {
+  const int kt = K / 64;
+  const int tiles_n = (N + c.bn - 1) / c.bn;
+  const int tiles = (int)std::min<long>((long)((rows + c.bm - 1) / c.bm) * tiles_n, 1 << 24);
+  auto time = [&](int z) {
+    const int n = tiles * z;
+    // more than 256 of the smallest tiles: two on a CU
+    const bool two = n > kCUs && c.two_on_cu;
+    const float per_kt = two ? 0.32f : std::max(0.13f, c.per_kt + c.per_kt_tile * (float)std::min(n, kCUs));
+    const float rounds = two ? std::max(1.0f, (float)n / 512.0f) : (float)((n + kCUs - 1) / kCUs);
+    return rounds * (c.fixed + (float)((kt + z - 1) / z) * per_kt) + (two && n > 2 * kCUs ? 2.2f : 0.f) + (z > 1 ? reduce_us(rows, N, z, ln) : 0.f);
+  };
+  float best = 0.f;
+  *splits = 1;
+  for (int z = 1; z <= 8 && (z == 1 || (may_split && kt / z >= 4 && tiles * z <= kCUs)); ++z) {
+    const float t = time(z);
+    if (z == 1 || t < best) { best = t; *splits = z; }
+  }
+  return best;
+}
 // The same when the choice is made for `choice_rows` rows (GemmArgs::choice_rows) but M rows are computed.
 size_t gemm_epi_splitk_ws_bytes_for(int M, int N, int K, int choice_rows) {
   float us;
   int sp = std::max(1, std::max(splits_128(choice_rows, N, K, false, &us), splits_128(choice_rows, N, K, true, &us)));
+  for (const WaveCost& c : kWave)
+    for (const bool ln : {false, true}) {
+      int w;
+      wave_us(c, choice_rows, N, K, true, ln, &w);
+      sp = std::max(sp, w);
+    }
   const int shapes[][2] = {{64, 64}, {128, 128}, {256, 128}, {256, 256}};
   for (const auto& t : shapes) {
     const long tiles = (long)((choice_rows + t[0] - 1) / t[0]) * ((N + t[1] - 1) / t[1]);
@@ -859,7 +1037,7 @@ size_t gemm_epi_splitk_ws_bytes(int M, int N, int K) { return gemm_epi_splitk_ws
 //    direct-to-LDS tiles when they fill the CUs, else the register-staged kernel;
 //  - dW = dy^T x (both operands read through the transposing LDS load): register-staged 128x128 tiles,
 //    two workgroups per CU; 256x256 direct-to-LDS tiles for large M and N.
-static int choose_cfg(int M, int N, int K, bool a_mc, bool b_mc, bool dtl_ok, bool pp_ok, bool allow16 = true, bool may_split = false, bool ln = false) {
+static int choose_cfg(int M, int N, int K, bool a_mc, bool b_mc, bool dtl_ok, bool pp_ok, bool allow16 = true, bool may_split = false, bool ln = false, bool wave_ok = false, bool heavy = false) {
   const long t256x256 = (long)((M + 255) / 256) * ((N + 255) / 256);
   const long t256x128 = (long)((M + 255) / 256) * ((N + 127) / 128);
   const bool dtl32 = dtl_ok && K % 32 == 0, dtl64 = dtl_ok && K % 64 == 0;
@@ -871,32 +1049,39 @@ static int choose_cfg(int M, int N, int K, bool a_mc, bool b_mc, bool dtl_ok, bo
     // 4x the workgroups of 128x128 ones, each with a quarter of the work per k-tile, and no split-K pass is needed.
     // Measured on the text encoder (samples/s at slices of 1 / 4 / 16): 1538 / 5617 / 19148 -> 1733 / 6490 / 20040; with more
     // 128x128 tiles than the limits below the larger tiles win again (16 samples, K = 3072: -6 % with 64x64 tiles).
-    if (dtl64 && (long)((M + 127) / 128) * ((N + 127) / 128) <= (K <= 1024 ? 100 : 24)) return 15;
+    if (dtl64 && !allow16 && (long)((M + 127) / 128) * ((N + 127) / 128) <= (K <= 1024 ? 100 : 24)) return 15;
     // Otherwise the tile with the least estimated time: rounds over the 256 CUs x (fixed part of a tile + k-tiles x time of
     // one), both in us, fitted on MI355X over projections of 1024..32768 rows, 320..5120 columns, contractions of
     // 320..5120.  The alternating-group tiles hold one workgroup per CU; which of their widths wins is mostly a matter of how
     // full the last round is (8192 x 4608: 576 tiles of 256x256 are 2.25 rounds, 768 of 256x192 exactly 3 shorter ones).
     struct Cand { int idx, bm, bn; float fixed, per_kt; bool pp, need64; };
     static const Cand cands[] = {{17, 256, 256, 5.0f, 1.30f, true, false}, {19, 256, 192, 5.0f, 1.05f, true, false}, {20, 256, 160, 5.5f, 0.99f, true, false},
-                                 {18, 256, 128, 5.0f, 0.72f, true, false}, {13, 128, 128, 4.0f, 0.45f, false, true}, {8, 128, 128, 4.0f, 0.55f, false, false},
+                                 {18, 256, 128, 5.0f, 0.72f, true, false}, {13, 128, 128, 0.f, 0.f, false, true}, {8, 128, 128, 5.0f, 0.75f, false, false},
                                  {6, 256, 256, 5.0f, 1.70f, false, false}, {9, 256, 128, 5.0f, 0.85f, false, true}};
     int best = -1;
     float best_cost = 0.f;
+    auto consider = [&](int idx, float cost) { if (best < 0 || cost < best_cost) { best = idx; best_cost = cost; } };
     for (const Cand& c : cands) {
       if (c.pp ? !pp_ok : (c.need64 ? !dtl64 : !dtl32)) continue;
       if (c.idx == 20 && !allow16) continue;       // the 16x16x32 instruction sums a k-step of 32 at once: other bits than the 32x32x16 tiles
       const long tiles = (long)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
       float cost = (float)((tiles + kCUs - 1) / kCUs) * (c.fixed + (float)((K + 63) / 64) * c.per_kt);
-      if (c.idx == 13 && may_split) splits_128(M, N, K, ln, &cost);
-      if (best < 0 || cost < best_cost) { best = c.idx; best_cost = cost; }
+      if (c.idx == 13) {
+        cost = tile128_us(tiles, K / 64, heavy);
+        if (may_split) splits_128(M, N, K, ln, &cost, heavy);
+      }
+      consider(c.idx, cost);
     }
     if (dtl64) {
-      // 64x64 tiles: up to three workgroups per CU; a k-tile costs 0.23 us while they have CUs to themselves, 0.39 us beside others
-      // (32768 of them with two k-tiles each: 165 us; 256x256 tiles 90)
       const long tiles = (long)((M + 63) / 64) * ((N + 63) / 64);
-      const float cost = 2.2f + std::max(1.0f, (float)tiles / 512.0f) * (1.8f + (float)(K / 64) * (tiles <= 128 ? 0.23f : 0.39f));
-      if (cost < best_cost) best = 15;
+      const int z = may_split ? choose_splits_epi(tiles, K / 64) : 1;
+      consider(15, tile64_us(tiles, K / 64, z) + (z > 1 ? reduce_us(M, N, z, ln) : 0.f));
     }
+    if (dtl64 && wave_ok)
+      for (int i = 0; i < (int)(sizeof(kWave) / sizeof(kWave[0])); ++i) {
+        int splits;
+        consider(25 + i, wave_us(kWave[i], M, N, K, may_split, ln, &splits));
+      }
     if (best >= 0) return best;
     return t256x128 >= 128 ? 1 : 0;
   }
@@ -970,28 +1155,21 @@ static int launch_bf16_cfg(const GemmArgs& a, hipStream_t s) {
   return DP_OK;
 }
 
-template <int BM, int BN, int BK, int STAGES, int WGM, int WGN, bool A_MC, bool B_MC>
-static int launch_dtl_cfg(const GemmArgs& a, hipStream_t s) {
-  using S = DtlSmem<BM, BN, BK, STAGES, WGM, WGN>;
-  GemmBf16Params p;
-  p.A = (const bf16*)a.A; p.B = (const bf16*)a.B;
-  p.M = a.M; p.N = a.N; p.K = a.K; p.lda = a.lda; p.ldb = a.ldb; p.split_major = 0;
-  p.epi = make_epi<bf16>(a);
-  p.tiles_m = (a.M + BM - 1) / BM; p.tiles_n = (a.N + BN - 1) / BN;
-  p.group_m = choose_group_m(a, p.tiles_m, p.tiles_n);
-  if (!dtl_addressable(a)) return set_error(DP_EUNSUPPORTED, "gemm: operand too large for the forced direct-to-LDS configuration");
-  p.a_bytes = (uint32_t)(A_MC ? operand_extent_bytes(a.K, a.M, a.lda) : operand_extent_bytes(a.M, a.K, a.lda));
-  p.b_bytes = (uint32_t)(B_MC ? operand_extent_bytes(a.K, a.N, a.ldb) : operand_extent_bytes(a.N, a.K, a.ldb));
-  const int kt = a.K / BK;
-  int splits = 1;
-  if (a.out_f32) {
-    splits = choose_splits((long)p.tiles_m * p.tiles_n, kt * BK / 64, S::BYTES <= 80 * 1024 ? 2 * kCUs : kCUs);
-  } else if (a.splitk_ws && a.geglu != 1) {
-    const long rows_for_choice = a.choice_rows > 0 ? a.choice_rows : a.M;
-    float us;
-    splits = a.choice_rows < 0 ? 1 : choose_splits_epi(((rows_for_choice + BM - 1) / BM) * p.tiles_n, kt * BK / 64);
-    if (a.choice_rows >= 0 && BM == 128 && BN == 128 && BK == 64) splits = splits_128((int)rows_for_choice, a.N, a.K, a.ln_out != nullptr, &us);
-  }
+static int set_lds_limit(const void* kern, size_t bytes, std::atomic<bool>& done) {
+  if (done.load(std::memory_order_acquire)) return DP_OK;     // setting it twice is harmless; the flag only saves the call
+  if (hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) != hipSuccess) return set_error(DP_EHIP, "hipFuncSetAttribute(gemm) failed");
+  done.store(true, std::memory_order_release);
+  return DP_OK;
+}
+
+static bool reduction_does_ln(const GemmArgs& a) {
+  return !a.out_f32 && a.ln_out && a.ln_applied && a.ln_gamma && a.ln_beta && a.residual && a.residual_f32 && a.out_fused_f32 &&
+         a.out == a.residual && a.ldo == a.N && a.ld_res == a.N && !a.act && !a.dact_pre && !a.gate && !a.pre_out && !a.geglu && a.N <= 2048;
+}
+
+// A kernel of `kt` k-tiles per output tile with its contraction cut into `splits` parts (1: none), and the pass that adds them.
+template <class Kern>
+static int launch_split(const GemmArgs& a, GemmBf16Params& p, Kern kern, int threads, size_t smem, std::atomic<bool>& attr_set, int kt, int splits, hipStream_t s) {
   if (splits > 1) {
     const size_t need = (size_t)splits * a.M * a.N * sizeof(float);
     if (!a.splitk_ws || a.splitk_ws_bytes < need) {
@@ -1003,25 +1181,16 @@ static int launch_dtl_cfg(const GemmArgs& a, hipStream_t s) {
   p.k_tiles_per_split = (kt + splits - 1) / splits;
   splits = (kt + p.k_tiles_per_split - 1) / p.k_tiles_per_split;
   if (splits > 1) p.epi.partial = a.splitk_ws;
-  dim3 grid(p.tiles_m * p.tiles_n, 1, splits);
-  const size_t smem = S::BYTES;
-  auto kern = gemm_bf16_dtl_kernel<BM, BN, BK, STAGES, WGM, WGN, A_MC, B_MC>;
-  static std::atomic<bool> attr_set{false};   // setting it twice is harmless; the flag only saves the call
-  if (!attr_set.load(std::memory_order_acquire)) {
-    if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) != hipSuccess)
-      return set_error(DP_EHIP, "hipFuncSetAttribute(gemm) failed");
-    attr_set.store(true, std::memory_order_release);
-  }
+  DP_TRY(set_lds_limit((const void*)kern, smem, attr_set));
   {
     // the timing scope brackets the GEMM kernel alone (the split-K reduction is its own class)
     KScope ks(a.a_mc ? KK_GEMM_TN : (a.b_mc ? KK_GEMM_NN : KK_GEMM_NT), 2.0 * a.M * a.N * a.K,
               gemm_tensor_bytes(a), s, a.M, a.N, a.K);
-    hipLaunchKernelGGL(kern, grid, dim3(WGM * WGN * 64), smem, s, p);
+    hipLaunchKernelGGL(kern, dim3(p.tiles_m * p.tiles_n, 1, splits), dim3(threads), smem, s, p);
   }
   if (hipGetLastError() != hipSuccess) return set_error(DP_EHIP, "gemm launch failed");
   if (a.ln_applied) *a.ln_applied = 0;
-  if (splits > 1 && !a.out_f32 && a.ln_out && a.ln_applied && a.ln_gamma && a.ln_beta && a.residual && a.residual_f32 && a.out_fused_f32 &&
-      a.out == a.residual && a.ldo == a.N && a.ld_res == a.N && !a.act && !a.dact_pre && !a.gate && !a.pre_out && !a.geglu && a.N <= 2048) {
+  if (splits > 1 && reduction_does_ln(a)) {
     // the reduction pass also normalises the rows it completes (one launch less per projection onto the residual stream)
     *a.ln_applied = 1;
     return launch_reduce_residual_ln(a.splitk_ws, splits, a.M, a.N, a.bias, (float*)a.out, a.ln_out, a.ln_gamma, a.ln_beta, a.ln_eps, s);
@@ -1039,11 +1208,58 @@ static int launch_dtl_cfg(const GemmArgs& a, hipStream_t s) {
   return DP_OK;
 }
 
-static int set_lds_limit(const void* kern, size_t bytes, std::atomic<bool>& done) {
-  if (done.load(std::memory_order_acquire)) return DP_OK;     // setting it twice is harmless; the flag only saves the call
-  if (hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) != hipSuccess) return set_error(DP_EHIP, "hipFuncSetAttribute(gemm) failed");
-  done.store(true, std::memory_order_release);
+template <int BM, int BN, bool A_MC, bool B_MC>
+static int dtl_params(const GemmArgs& a, GemmBf16Params& p) {
+  p.A = (const bf16*)a.A; p.B = (const bf16*)a.B;
+  p.M = a.M; p.N = a.N; p.K = a.K; p.lda = a.lda; p.ldb = a.ldb; p.split_major = 0;
+  p.epi = make_epi<bf16>(a);
+  p.tiles_m = (a.M + BM - 1) / BM; p.tiles_n = (a.N + BN - 1) / BN;
+  p.group_m = choose_group_m(a, p.tiles_m, p.tiles_n);
+  if (!dtl_addressable(a)) return set_error(DP_EUNSUPPORTED, "gemm: operand too large for the forced direct-to-LDS configuration");
+  p.a_bytes = (uint32_t)(A_MC ? operand_extent_bytes(a.K, a.M, a.lda) : operand_extent_bytes(a.M, a.K, a.lda));
+  p.b_bytes = (uint32_t)(B_MC ? operand_extent_bytes(a.K, a.N, a.ldb) : operand_extent_bytes(a.N, a.K, a.ldb));
   return DP_OK;
+}
+
+template <int BM, int BN, int BK, int STAGES, int WGM, int WGN, bool A_MC, bool B_MC>
+static int launch_dtl_cfg(const GemmArgs& a, hipStream_t s) {
+  using S = DtlSmem<BM, BN, BK, STAGES, WGM, WGN>;
+  GemmBf16Params p;
+  DP_TRY((dtl_params<BM, BN, A_MC, B_MC>(a, p)));
+  const int kt = a.K / BK;
+  int splits = 1;
+  if (a.out_f32) {
+    splits = choose_splits((long)p.tiles_m * p.tiles_n, kt * BK / 64, S::BYTES <= 80 * 1024 ? 2 * kCUs : kCUs);
+  } else if (a.splitk_ws && a.geglu != 1) {
+    const long rows_for_choice = a.choice_rows > 0 ? a.choice_rows : a.M;
+    float us;
+    splits = a.choice_rows < 0 ? 1 : choose_splits_epi(((rows_for_choice + BM - 1) / BM) * p.tiles_n, kt * BK / 64);
+    if (a.choice_rows >= 0 && BM == 128 && BN == 128 && BK == 64) splits = splits_128((int)rows_for_choice, a.N, a.K, a.ln_out != nullptr, &us);
+  }
+  static std::atomic<bool> attr_set{false};
+  return launch_split(a, p, gemm_bf16_dtl_kernel<BM, BN, BK, STAGES, WGM, WGN, A_MC, B_MC>, WGM * WGN * 64, S::BYTES, attr_set, kt, splits, s);
+}
+
+// The additions of a launch with its contraction cut into `splits` parts, in one workgroup per output tile.
+template <int BM, int BN, int BK, int STAGES, int WGM, int WGN>
+static int launch_segments(const GemmArgs& a, int splits, hipStream_t s) {
+  using S = DtlSmem<BM, BN, BK, STAGES, WGM, WGN>;
+  GemmBf16Params p;
+  DP_TRY((dtl_params<BM, BN, false, false>(a, p)));
+  p.k_tiles_per_split = (a.K / BK + splits - 1) / splits;
+  const bool ln = reduction_does_ln(a);
+  if (ln && (!a.splitk_ws || a.splitk_ws_bytes < (size_t)a.M * a.N * sizeof(float))) return set_error(DP_EWORKSPACE, "gemm: split-K workspace too small for the split chosen from choice_rows");
+  if (ln) p.epi.partial = a.splitk_ws;      // the sums, for the pass that adds bias and residual and normalises (the same one as after a split launch)
+  auto kern = gemm_bf16_dtl_kernel<BM, BN, BK, STAGES, WGM, WGN, false, false, false, true>;
+  static std::atomic<bool> attr_set{false};
+  DP_TRY(set_lds_limit((const void*)kern, S::BYTES, attr_set));
+  {
+    KScope ks(KK_GEMM_NT, 2.0 * a.M * a.N * a.K, gemm_tensor_bytes(a), s, a.M, a.N, a.K);
+    hipLaunchKernelGGL(kern, dim3(p.tiles_m * p.tiles_n), dim3(WGM * WGN * 64), S::BYTES, s, p);
+  }
+  if (hipGetLastError() != hipSuccess) return set_error(DP_EHIP, "gemm launch failed");
+  if (a.ln_applied) *a.ln_applied = ln;
+  return ln ? launch_reduce_residual_ln(a.splitk_ws, 1, a.M, a.N, a.bias, (float*)a.out, a.ln_out, a.ln_gamma, a.ln_beta, a.ln_eps, s) : DP_OK;
 }
 
 template <class T, int KIND, bool FP8, bool KTAIL>
@@ -1235,6 +1451,16 @@ static int launch_pp(const GemmArgs& a, hipStream_t s) {
   }
 }
 
+template <class T>
+static int launch_wave(const GemmArgs& a, const WaveCost& c, hipStream_t s) {
+  if (a.a_mc || a.b_mc || a.out_f32 || a.geglu == 1 || a.K % 64 || !dtl_addressable(a)) return set_error(DP_EUNSUPPORTED, "gemm: the forced configuration needs contraction-contiguous operands, K % 64 == 0 and a storage-dtype output");
+  GemmBf16Params p = pp_params<T>(a);
+  int splits = 1;
+  if (a.splitk_ws && a.choice_rows == 0) wave_us(c, a.M, a.N, a.K, true, a.ln_out != nullptr, &splits);
+  static std::atomic<bool> attr_set{false};
+  return launch_split(a, p, gemm_wave_kernel<T>, T::NW * 64, T::BYTES, attr_set, a.K / 64, splits, s);
+}
+
 template <int BM, int BN, int BK, int STAGES, int WGM, int WGN>
 static int launch_dtl_layout(const GemmArgs& a, hipStream_t s) {
   if (a.K % BK) return set_error(DP_EUNSUPPORTED, "gemm: K is not a multiple of the k-tile of the forced configuration");
@@ -1263,6 +1489,52 @@ bool gemm_colsum_supported(const GemmArgs& a) {
 bool gemm_geglu_fwd_supported(const GemmArgs& a) {
   return a.dtype == BF16 && !a.a_mc && !a.b_mc && a.K % 32 == 0 && a.geglu_inner > 0 && a.geglu_inner % 32 == 0 &&
          a.N == 2 * a.geglu_inner && a.ldo >= a.geglu_inner && (!a.pre_out || a.ld_pre >= a.N) && dtl_addressable(a);
+}
+
+// The tile choice for a problem of `rows` rows.  Its estimates cost the host about a microsecond, so each thread remembers the last choices, by
+// everything they depend on.
+static int chosen_cfg(const GemmArgs& a, int rows, bool may_split) {
+  struct Entry { int rows, n, k, flags, cfg; };
+  constexpr int ENTRIES = 64;
+  static thread_local Entry table[ENTRIES] = {};        // n = 0: empty
+  const bool pp = !a.out_f32 && pp_kind(a) >= 0, any_order = a.choice_rows == 0, wave = any_order && !a.out_f32 && a.geglu != 1, dtl = dtl_addressable(a), heavy = a.act || a.dact_pre || a.geglu;
+  const int flags = heavy << 8 | (a.a_mc != 0) | (a.b_mc != 0) << 1 | dtl << 2 | pp << 3 | any_order << 4 | may_split << 5 | (a.ln_out != nullptr) << 6 | wave << 7;
+  Entry& e = table[((unsigned)rows * 0x9E3779B1u ^ (unsigned)a.N * 0x85EBCA77u ^ (unsigned)a.K * 0xC2B2AE3Du ^ (unsigned)flags * 0x27D4EB2Fu) >> 26];
+  if (e.n == a.N && e.rows == rows && e.k == a.K && e.flags == flags) return e.cfg;
+  e = Entry{rows, a.N, a.K, flags, choose_cfg(rows, a.N, a.K, a.a_mc != 0, a.b_mc != 0, dtl, pp, any_order, may_split, a.ln_out != nullptr, wave, heavy)};
+  return e.cfg;
+}
+
+// choice_rows > 0: the parts the contraction is cut into depend on the shape of the problem with choice_rows rows alone, and so do the sums; the
+// tile and whether the parts run as workgroups of their own (few tiles) or one after the other in a workgroup (many: no partial tiles through
+// memory) may depend on the rows there are, since they change no bit.  Encoder of 12 layers of width 768, calls of 24 / 48 / 96 samples of 77 rows: 1.27 / 2.26 / 4.10 ms with the
+// tiles of one sample's shape as well, 1.05 / 1.51 / 2.73 ms.
+static int launch_invariant(const GemmArgs& a, bool may_split, hipStream_t s) {
+  const int cfg = chosen_cfg(a, a.choice_rows, may_split), kt = a.K / 64;
+  GemmArgs g = a;
+  int z = 1;
+  if (may_split && (cfg == 13 || cfg == 15)) {
+    float us;
+    z = cfg == 13 ? splits_128(a.choice_rows, a.N, a.K, a.ln_out != nullptr, &us) : choose_splits_epi((long)((a.choice_rows + 63) / 64) * ((a.N + 63) / 64), kt);
+  } else if (may_split && cfg >= 6 && cfg <= 16) {
+    g.force_cfg = cfg + 1;       // another kind of tile with a split of its own
+    return launch_gemm(g, s);
+  }
+  if (z == 1) {
+    g.choice_rows = -1;
+    return launch_gemm(g, s);
+  }
+  const long t64 = (long)((a.M + 63) / 64) * ((a.N + 63) / 64), t128 = (long)((a.M + 127) / 128) * ((a.N + 127) / 128);
+  const bool ln = reduction_does_ln(a);
+  // (the partial tiles of a launch this size stay in the caches: 0.6 us per million of them)
+  auto pass = [&](int planes) { return (ln ? 1.0f : 5.0f) + (float)(planes + 2) * (float)a.M * (float)a.N * 0.6e-6f; };
+  const float parts = (cfg == 15 ? tile64_us(t64, kt, z) : tile128_us(t128 * z, (kt + z - 1) / z, false)) + pass(z);
+  const float seg64 = tile64_us(t64, kt, 1) + (ln ? pass(1) : 0.f), seg128 = tile128_us(t128, kt, !ln && a.act) + (ln ? pass(1) : 0.f);
+  if (parts <= seg64 && parts <= seg128) {
+    g.force_cfg = cfg + 1;
+    return launch_gemm(g, s);
+  }
+  return seg64 <= seg128 ? launch_segments<64, 64, 64, 3, 2, 2>(a, z, s) : launch_segments<128, 128, 64, 3, 4, 2>(a, z, s);
 }
 
 int launch_gemm(const GemmArgs& a, hipStream_t s) {
@@ -1297,7 +1569,9 @@ int launch_gemm(const GemmArgs& a, hipStream_t s) {
       }
     }
     const bool may_split = !a.out_f32 && a.splitk_ws && a.geglu != 1 && a.choice_rows >= 0;
-    int cfg = (a.force_cfg > 0 && a.force_cfg <= kNumCfgs + 19) ? a.force_cfg - 1 : choose_cfg(a.choice_rows > 0 ? a.choice_rows : a.M, a.N, a.K, a.a_mc != 0, a.b_mc != 0, dtl_addressable(a), !a.out_f32 && pp_kind(a) >= 0, a.choice_rows >= 0, may_split, a.ln_out != nullptr);
+    const bool forced = a.force_cfg > 0 && a.force_cfg <= kNumCfgs + 23;
+    if (a.choice_rows > 0 && !forced && !a.a_mc && !a.b_mc) return launch_invariant(a, may_split, s);
+    int cfg = forced ? a.force_cfg - 1 : chosen_cfg(a, a.M, may_split);
     // the column permutation of the fused GeGLU lives in the direct-to-LDS loaders, and in tiles with equal column halves
     if (a.geglu == 1 && (cfg < 6 || cfg == 11 || cfg == 15 || cfg == 16 || cfg > 18)) {
       const long t256x256 = (long)((a.M + 255) / 256) * ((a.N + 255) / 256);
@@ -1330,6 +1604,10 @@ int launch_gemm(const GemmArgs& a, hipStream_t s) {
       case 21: case 22: case 23: case 24:
         return launch_gemm_dw_group(&a, 1, gemm_dw_group_plan(&a, 1, cfg - 20, a.splitk_ws ? a.splitk_ws_bytes : 0), s);
       case 20: return launch_pp<PpTile<256, 96, 64, 4, 2, 16>>(a, s);
+      case 25: return launch_wave<WaveTile<4, 2, 2>>(a, kWave[0], s);
+      case 26: return launch_wave<WaveTile<4, 2, 3>>(a, kWave[1], s);
+      case 27: return launch_wave<WaveTile<4, 4, 3>>(a, kWave[2], s);
+      case 28: return launch_wave<WaveTile<4, 4, 4>>(a, kWave[3], s);
       default: break;
     }
     return launch_bf16_layout<128, 128, 64, 2, 2>(a, s);

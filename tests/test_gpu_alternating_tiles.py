@@ -18,6 +18,15 @@ def test_forward_tiles(tile_cfg):
         assert e <= TOL_BF16
 
 
+@pytest.mark.parametrize("tile_cfg", [26, 27, 28, 29])
+def test_tiles_whose_waves_share_the_contraction(tile_cfg):
+    # fewer k-tiles than waves, as many, one more; a part of a tile and ragged edges
+    for M, N, K in [(8, 8, 64), (64, 96, 256), (77, 264, 320), (129, 136, 192), (300, 520, 1088)]:
+        e = _gemm_case("nt", M, N, K, tile_cfg, seed=M + K)
+        print(f"\n[gemm nt cfg {tile_cfg} {M}x{N}x{K}] rel err {e:.2e}", flush=True)
+        assert e <= TOL_BF16
+
+
 @pytest.mark.parametrize("tile_cfg", [22, 23, 24, 25])
 @pytest.mark.parametrize("accumulate", [False, True])
 def test_weight_gradient_tiles(tile_cfg, accumulate):
