@@ -258,15 +258,17 @@ int launch_ln_fwd(const LnArgs& a, hipStream_t s) {
 }
 
 // ------------------------------------------------------------------ LayerNorm backward
-constexpr int LNB_ROWS = 16;   // rows per workgroup (4 per wave)
+// Rows per workgroup (a multiple of its four waves): 16, fewer where that leaves CUs without a workgroup.  1024 rows of 1152 on 64
+// workgroups took 16.3 us, on 256 8.8 us; the partial sums to be added afterwards grow to the same number, a few MB.
+static int ln_bwd_rows(int rows) { return rows >= 8192 ? 16 : (rows >= 2048 ? 8 : 4); }
 
 // grid = (chunks_per_batch, n_batches).  partial: [batch][chunk][2][d]
 // NCH = number of 64-lane vector chunks a row spans (d <= 64 * V * NCH).  A wave owns every fourth row of the
-// workgroup's 16.  All loads of a row (dy, x, the residual gradient) are issued before the first is used; rows
+// workgroup's.  All loads of a row (dy, x, the residual gradient) are issued before the first is used; rows
 // of a single chunk (d <= 512 in bf16) are taken two at a time, which doubles the bytes in flight per wave --
 // the kernel moves ~16 bytes per element and is bound by how much of that is outstanding, not by arithmetic.
 template <typename T, int NCH>
-__global__ void __launch_bounds__(256) ln_bwd_kernel(int d, int rows_per_batch, const T* __restrict__ dy, const float* __restrict__ x,
+__global__ void __launch_bounds__(256) ln_bwd_kernel(int d, int rows_per_batch, int wg_rows, const T* __restrict__ dy, const float* __restrict__ x,
                                                      const float* __restrict__ mean, const float* __restrict__ rstd,
                                                      const T* __restrict__ gamma, const T* __restrict__ scale, int mod_ld,
                                                      const float* __restrict__ dres, const T* __restrict__ dres_t,
@@ -276,7 +278,7 @@ __global__ void __launch_bounds__(256) ln_bwd_kernel(int d, int rows_per_batch, 
   extern __shared__ float cols[];   // [4 waves][2][d]
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int b = blockIdx.y;
-  const int r_begin = blockIdx.x * LNB_ROWS, r_end = min(rows_per_batch, r_begin + LNB_ROWS);
+  const int r_begin = blockIdx.x * wg_rows, r_end = min(rows_per_batch, r_begin + wg_rows);
   float gsum[NCH][V], bsum[NCH][V], gain[NCH][V];
 #pragma unroll
   for (int c = 0; c < NCH; ++c) {
@@ -427,13 +429,13 @@ __global__ void __launch_bounds__(1024) ln_bwd_reduce_kernel(const LnReduceSet s
 size_t ln_bwd_partial_bytes(int rows, int d, int rows_per_batch) {
   if (rows_per_batch <= 0) rows_per_batch = rows;
   const int nb = rows / rows_per_batch;
-  const int nchunk = (rows_per_batch + LNB_ROWS - 1) / LNB_ROWS;
+  const int wg_rows = ln_bwd_rows(rows), nchunk = (rows_per_batch + wg_rows - 1) / wg_rows;
   return (size_t)nb * nchunk * 2 * d * sizeof(float);
 }
 
 template <typename T, int NCH>
 static void ln_bwd_launch(const LnBwdArgs& a, int rpb, int nb, int nchunk, float* partial, hipStream_t s) {
-  hipLaunchKernelGGL((ln_bwd_kernel<T, NCH>), dim3(nchunk, nb), dim3(256), (size_t)8 * a.d * sizeof(float), s, a.d, rpb, (const T*)a.dy,
+  hipLaunchKernelGGL((ln_bwd_kernel<T, NCH>), dim3(nchunk, nb), dim3(256), (size_t)8 * a.d * sizeof(float), s, a.d, rpb, ln_bwd_rows(a.rows), (const T*)a.dy,
                      (const float*)a.x, a.mean, a.rstd, (const T*)a.gamma, (const T*)a.scale, a.mod_ld,
                      a.dres_storage ? nullptr : (const float*)a.dres, a.dres_storage ? (const T*)a.dres : nullptr, (T*)a.dx, a.dx32, partial);
 }
@@ -455,7 +457,7 @@ int launch_ln_bwd(const LnBwdArgs& a, hipStream_t s) {
   const bool modulated = a.scale != nullptr;
   const int rpb = modulated ? a.rows_per_batch : a.rows;
   if (rpb <= 0 || a.rows % rpb) return set_error(DP_EINVAL, "ln_bwd: rows must be a multiple of rows_per_batch");
-  const int nb = a.rows / rpb, nchunk = (rpb + LNB_ROWS - 1) / LNB_ROWS;
+  const int nb = a.rows / rpb, wg_rows = ln_bwd_rows(a.rows), nchunk = (rpb + wg_rows - 1) / wg_rows;
   const bool want_cols = modulated ? (a.dscale && a.dshift) : (a.dgamma && a.dbeta);
   float* partial = nullptr;
   if (want_cols) {
@@ -487,7 +489,7 @@ int launch_ln_bwd_reduce(const LnBwdArgs* a, int n, hipStream_t s) {
     set.out0[i] = modulated ? a[i].dscale : a[i].dgamma;
     set.out1[i] = modulated ? a[i].dshift : a[i].dbeta;
   }
-  const int nb = a[0].rows / rpb, nchunk = (rpb + LNB_ROWS - 1) / LNB_ROWS;
+  const int nb = a[0].rows / rpb, wg_rows = ln_bwd_rows(a[0].rows), nchunk = (rpb + wg_rows - 1) / wg_rows;
   KScope ks(KK_REDUCE, 0.0, (double)n * nb * nchunk * 2 * d * 4, s, nchunk, 2 * d);
   if (modulated)
     hipLaunchKernelGGL(ln_bwd_reduce_kernel<32>, dim3((2 * d + 31) / 32, nb, n), dim3(1024), 0, s, set, nchunk, d, a[0].dmod_ld, 0);
