@@ -79,6 +79,12 @@ bool gemm_dw_group_supported(const GemmArgs& a);
 // a.B, a.bias and a.out are not used.
 constexpr int GEMM_BATCH_MAX = 16;
 struct GemmBatch { int n; const void* B[GEMM_BATCH_MAX]; const void* bias[GEMM_BATCH_MAX]; void* out[GEMM_BATCH_MAX]; };
+// Gradient of a stage's conditioning vectors: parts of sum_b dm_b [batch, 6 d] W_b [6 d, d] for the given blocks, appended to ws after the *parts
+// there already; then d_cond = SiLU'(cond) * their sum.
+bool cond_grad_supported(int dtype, int batch, int d);
+size_t cond_grad_ws_bytes(int blocks, int batch, int d);      // for all blocks at once or one by one
+int launch_cond_grad(const void* const* dm, const void* const* w, int blocks, int batch, int d, float* ws, int* parts, hipStream_t s);
+int launch_cond_grad_finish(const float* ws, int parts, const void* cond, float* d_cond, int batch, int d, hipStream_t s);
 bool gemm_few_rows_supported(const GemmArgs& a);
 int launch_gemm_few_rows(const GemmArgs& a, const GemmBatch& batch, hipStream_t s);
 bool gemm_geglu_fwd_supported(const GemmArgs& a);
@@ -182,7 +188,7 @@ int launch_reduce_residual_ln(const float* partial, int splits, int rows, int d,
 
 // dx = [dres +] LN backward of dy.  x (the LayerNorm input) and dres are fp32 residual-stream
 // tensors; the result is written to dx32 (fp32) and/or dx (storage dtype).  Affine: dgamma/dbeta (fp32 [d], accumulate flag).
-// Modulated: dscale/dshift rows written to fp32 [B, dmod_ld] (overwrite) and the
+// Modulated: dscale/dshift rows written in the storage dtype to [B, dmod_ld] (overwrite) and the
 // effective gain is (1 + scale).  partial is scratch of ln_bwd_partial_bytes().
 struct LnBwdArgs {
   int dtype; int rows, d;
@@ -193,7 +199,7 @@ struct LnBwdArgs {
   int dres_storage;
   void* dx; float* dx32;
   float* dgamma; float* dbeta; int accumulate;
-  float* dscale; float* dshift; int dmod_ld;
+  void* dscale; void* dshift; int dmod_ld;
   float* partial; size_t partial_bytes;
   int defer_reduce;        // 1: only write the column partials; the caller runs launch_ln_bwd_reduce (maybe on another stream)
 };
@@ -224,9 +230,9 @@ int launch_silu(int dtype, const void* x, void* y, size_t n, hipStream_t s);
 int launch_silu_bwd(int dtype, const float* dz, const void* c, float* dc, int accumulate, size_t n, hipStream_t s);
 
 // Gated-branch backward helper (dres is the fp32 residual-stream gradient): dbranch[m,n] = dres[m,n] * gate[b,n];
-// dgate[b,n] = sum_{rows of batch b} dres[m,n] * branch[m,n]   (fp32, overwrite)
+// dgate[b,n] = sum_{rows of batch b} dres[m,n] * branch[m,n]   (fp32 sums, storage dtype, overwrite)
 int launch_gate_bwd(int dtype, const void* dres, const void* branch, const void* gate, int gate_ld,
-                    void* dbranch, float* dgate, int dgate_ld, int B, int rows_per_batch, int d, hipStream_t s);
+                    void* dbranch, void* dgate, int dgate_ld, int B, int rows_per_batch, int d, hipStream_t s);
 
 // storage dtype -> fp32
 int launch_cast_to_f32(int dtype, const void* in, float* out, size_t n, hipStream_t s);

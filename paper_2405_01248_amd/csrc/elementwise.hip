@@ -400,12 +400,13 @@ __global__ void __launch_bounds__(256) ln_bwd_kernel(int d, int rows_per_batch, 
 // per workgroup mean more workgroups: the unbatched reduction of a narrow model (2d = 640 columns, 1024 chunks)
 // ran on 20 workgroups with 32 columns each and took 21 us; with 8 it runs on 80.
 // blockIdx.z: one of several LayerNorms of the same shape.
-struct LnReduceSet { const float* partial[LN_REDUCE_MAX]; float* out0[LN_REDUCE_MAX]; float* out1[LN_REDUCE_MAX]; };
-template <int COLS>
+// Out: float, or the storage dtype for modulation gradients.
+struct LnReduceSet { const float* partial[LN_REDUCE_MAX]; void* out0[LN_REDUCE_MAX]; void* out1[LN_REDUCE_MAX]; };
+template <int COLS, typename Out>
 __global__ void __launch_bounds__(1024) ln_bwd_reduce_kernel(const LnReduceSet set, int nchunk, int d, int ld, int accumulate) {
   const float* __restrict__ partial = set.partial[blockIdx.z];
-  float* out0 = set.out0[blockIdx.z];
-  float* out1 = set.out1[blockIdx.z];
+  Out* out0 = (Out*)set.out0[blockIdx.z];
+  Out* out1 = (Out*)set.out1[blockIdx.z];
   constexpr int GROUPS = 1024 / COLS;
   __shared__ float red[GROUPS][COLS + 1];
   const int lc = threadIdx.x % COLS, grp = threadIdx.x / COLS;
@@ -421,8 +422,8 @@ __global__ void __launch_bounds__(1024) ln_bwd_reduce_kernel(const LnReduceSet s
     float t = 0.f;
 #pragma unroll 8
     for (int g = 0; g < GROUPS; ++g) t += red[g][lc];
-    float* o = (col < d ? out0 + col : out1 + (col - d)) + (size_t)b * ld;
-    *o = accumulate ? *o + t : t;
+    Out* o = (col < d ? out0 + col : out1 + (col - d)) + (size_t)b * ld;
+    *o = from_f<Out>(accumulate ? to_f<Out>(*o) + t : t);
   }
 }
 
@@ -486,17 +487,17 @@ int launch_ln_bwd_reduce(const LnBwdArgs* a, int n, hipStream_t s) {
         a[i].dmod_ld != a[0].dmod_ld || a[i].accumulate != a[0].accumulate)
       return set_error(DP_EINVAL, "ln_bwd_reduce: the LayerNorms differ in shape");
     set.partial[i] = a[i].partial;
-    set.out0[i] = modulated ? a[i].dscale : a[i].dgamma;
-    set.out1[i] = modulated ? a[i].dshift : a[i].dbeta;
+    set.out0[i] = modulated ? a[i].dscale : (void*)a[i].dgamma;
+    set.out1[i] = modulated ? a[i].dshift : (void*)a[i].dbeta;
   }
   const int nb = a[0].rows / rpb, wg_rows = ln_bwd_rows(a[0].rows), nchunk = (rpb + wg_rows - 1) / wg_rows;
   KScope ks(KK_REDUCE, 0.0, (double)n * nb * nchunk * 2 * d * 4, s, nchunk, 2 * d);
   if (modulated)
-    hipLaunchKernelGGL(ln_bwd_reduce_kernel<32>, dim3((2 * d + 31) / 32, nb, n), dim3(1024), 0, s, set, nchunk, d, a[0].dmod_ld, 0);
+    hipLaunchKernelGGL((a[0].dtype == BF16 ? ln_bwd_reduce_kernel<32, bf16> : ln_bwd_reduce_kernel<32, float>), dim3((2 * d + 31) / 32, nb, n), dim3(1024), 0, s, set, nchunk, d, a[0].dmod_ld, 0);
   else if (2 * d <= 1024)
-    hipLaunchKernelGGL(ln_bwd_reduce_kernel<8>, dim3((2 * d + 7) / 8, 1, n), dim3(1024), 0, s, set, nchunk, d, d, a[0].accumulate);
+    hipLaunchKernelGGL((ln_bwd_reduce_kernel<8, float>), dim3((2 * d + 7) / 8, 1, n), dim3(1024), 0, s, set, nchunk, d, d, a[0].accumulate);
   else
-    hipLaunchKernelGGL(ln_bwd_reduce_kernel<16>, dim3((2 * d + 15) / 16, 1, n), dim3(1024), 0, s, set, nchunk, d, d, a[0].accumulate);
+    hipLaunchKernelGGL((ln_bwd_reduce_kernel<16, float>), dim3((2 * d + 15) / 16, 1, n), dim3(1024), 0, s, set, nchunk, d, d, a[0].accumulate);
   return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "ln_bwd_reduce launch failed");
 }
 
@@ -698,7 +699,7 @@ constexpr int GB_WAVES = 16;
 template <typename T>
 __global__ void __launch_bounds__(64 * GB_WAVES) gate_bwd_kernel(const float* __restrict__ dres, const T* __restrict__ branch,
                                                                  const T* __restrict__ gate, int gate_ld, T* __restrict__ dbranch,
-                                                                 float* __restrict__ dgate, int dgate_ld, int rows_per_batch, int d) {
+                                                                 T* __restrict__ dgate, int dgate_ld, int rows_per_batch, int d) {
   constexpr int V = Vec<T>::N;
   __shared__ float red[GB_WAVES][16 * V];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -736,11 +737,11 @@ __global__ void __launch_bounds__(64 * GB_WAVES) gate_bwd_kernel(const float* __
       float t = 0.f;
 #pragma unroll
       for (int w = 0; w < GB_WAVES; ++w) t += red[w][threadIdx.x];
-      dgate[(size_t)b * dgate_ld + gc] = t;
+      dgate[(size_t)b * dgate_ld + gc] = from_f<T>(t);
     }
   }
 }
-int launch_gate_bwd(int dtype, const void* dres, const void* branch, const void* gate, int gate_ld, void* dbranch, float* dgate,
+int launch_gate_bwd(int dtype, const void* dres, const void* branch, const void* gate, int gate_ld, void* dbranch, void* dgate,
                     int dgate_ld, int B, int rows_per_batch, int d, hipStream_t s) {
   const int V = dtype == BF16 ? 8 : 4;
   if (B <= 0 || rows_per_batch <= 0 || d <= 0 || d % V || gate_ld % V) return set_error(DP_EINVAL, "gate_bwd: bad sizes");
@@ -748,8 +749,8 @@ int launch_gate_bwd(int dtype, const void* dres, const void* branch, const void*
   for (const void* q : ptrs) if (!q || ((uintptr_t)q % 16)) return set_error(DP_EALIGN, "gate_bwd: operands must be non-null and 16-byte aligned");
   if (!dgate) return set_error(DP_EINVAL, "gate_bwd: dgate is NULL");
   dim3 grid((d + 16 * V - 1) / (16 * V), B);
-  if (dtype == BF16) hipLaunchKernelGGL(gate_bwd_kernel<bf16>, grid, dim3(64 * GB_WAVES), 0, s, (const float*)dres, (const bf16*)branch, (const bf16*)gate, gate_ld, (bf16*)dbranch, dgate, dgate_ld, rows_per_batch, d);
-  else hipLaunchKernelGGL(gate_bwd_kernel<float>, grid, dim3(64 * GB_WAVES), 0, s, (const float*)dres, (const float*)branch, (const float*)gate, gate_ld, (float*)dbranch, dgate, dgate_ld, rows_per_batch, d);
+  if (dtype == BF16) hipLaunchKernelGGL(gate_bwd_kernel<bf16>, grid, dim3(64 * GB_WAVES), 0, s, (const float*)dres, (const bf16*)branch, (const bf16*)gate, gate_ld, (bf16*)dbranch, (bf16*)dgate, dgate_ld, rows_per_batch, d);
+  else hipLaunchKernelGGL(gate_bwd_kernel<float>, grid, dim3(64 * GB_WAVES), 0, s, (const float*)dres, (const float*)branch, (const float*)gate, gate_ld, (float*)dbranch, (float*)dgate, dgate_ld, rows_per_batch, d);
   return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "gate_bwd launch failed");
 }
 

@@ -84,7 +84,7 @@ struct GradPair { float* f; void* h; };
 struct BwdSet {
   void *dqkv, *dq2, *dkv2, *du, *dg, *dg2, *h[2];      // dg, dg2: DiT gated-branch gradients; h: storage copies of dx2, dx1
   float* ln_partial[3];                                  // column partials of the LayerNorm backward kernels
-  float *dmv, *dcond_pre; void* dm_t;                    // DiT: modulation gradients (fp32, then storage dtype)
+  float* dcond_pre;                                      // DiT: gradient of SiLU(cond) (where not all blocks' are formed together)
 };
 struct BwdScratch {
   float* f[2];
@@ -95,6 +95,8 @@ struct BwdScratch {
   float* dkv_ws; size_t dkv_ws_bytes;     // query-split partials of the cross-attention dK/dV kernel
   void* wt;                               // transposed copies of every block's weight matrices (bf16 stages only)
   size_t ln_partial_bytes;
+  void* dm;                               // DiT: every block's modulation gradients [batch, 6 d]
+  float* cond_ws;                         // ... and the parts of the conditioning gradient; nullptr: block by block
 };
 
 static void plan_unet_block(Plan& p, const dp_stage& s, UnetBuf& u, bool with_xin) {
@@ -202,13 +204,17 @@ static void plan_bwd_scratch(Plan& p, const dp_stage& s, BwdScratch& b) {
       t.dq2 = p.take(T * d * es); t.dkv2 = p.take(Tc * 2 * d * es); t.du = p.take(T * 2 * ff * es);
     } else {
       t.dg = p.take(T * d * es); t.dg2 = p.take(T * d * es); t.du = p.take(T * ff * es);
-      t.dmv = (float*)p.take(B * 6 * d * 4); t.dm_t = p.take(B * 6 * d * es); t.dcond_pre = (float*)p.take(B * d * 4);
+      t.dcond_pre = (float*)p.take(B * d * 4);
     }
   }
   if (unet) {
     b.dkv_ws_bytes = attn_dkv_ws_bytes(s.d.batch, s.d.n_heads, s.d.ctx_tokens, s.d.d_head);
     b.dkv_ws = (float*)p.take(b.dkv_ws_bytes);
     b.dg_raw = p.take(T * ff * es);
+  }
+  if (!unet) {
+    b.dm = p.take((size_t)s.d.n_blocks * B * 6 * d * es);
+    if (cond_grad_supported(s.d.dtype, s.d.batch, s.d.d_model)) b.cond_ws = (float*)p.take(cond_grad_ws_bytes(s.d.n_blocks, s.d.batch, s.d.d_model));
   }
   b.wt = s.es == 2 ? p.take((size_t)s.d.n_blocks * wt_block_elems(s) * s.es) : nullptr;
   b.partial_bytes = partial_need(s);
@@ -556,16 +562,16 @@ static int dit_block_fwd(const dp_stage& s, const void* const* P, const float* x
 
 // dy: fp32, f[c] or the caller's tensor; dx1 goes to f[c ^ 1] and the block's dx back to f[c] (or, in the storage dtype, to dx_final).
 static int dit_block_bwd(const dp_stage& s, const void* const* P, const void* const* WT, void* const* G, int acc, const void* cond, const void* sc_in,
-                         const float* dy, int c, void* dx_final, float* d_cond, int dcond_acc, DitBuf& u, BwdScratch& b, BwdSet& t, const SplitK& sk, Side& sd, int* batch) {
+                         const float* dy, int c, void* dx_final, float* d_cond, int dcond_acc, void* dm, DitBuf& u, BwdScratch& b, BwdSet& t, const SplitK& sk, Side& sd, int* batch) {
   const int dt = s.d.dtype, T = s.T, d = s.d.d_model, ff = s.d.ff_inner, B = s.d.batch, N = s.d.tokens;
   const size_t es = s.es;
   hipStream_t st = sd.main;
   auto proj = [&](const GemmArgs& g) { return sk.launch(g, st); };
-  float *dx1 = b.f[c ^ 1], *dm = t.dmv;
+  float* dx1 = b.f[c ^ 1];
   auto gf = [&](int i) { return (float*)G[i]; };
   BlockGrads bg(s, b, st, acc);
   // ---- MLP branch
-  DP_TRY(launch_gate_bwd(dt, dy, u.f2, at(u.m, 5 * d, es), 6 * d, t.dg, dm + 5 * d, 6 * d, B, N, d, st));
+  DP_TRY(launch_gate_bwd(dt, dy, u.f2, at(u.m, 5 * d, es), 6 * d, t.dg, at(dm, 5 * d, es), 6 * d, B, N, d, st));
   DP_TRY(bg.weight(t.dg, T, d, u.f, ff, gf(D_FC2_W), gf(D_FC2_B)));
   GemmArgs g = gemm_dx(dt, t.dg, T, d, P[D_FC2_W], WT[D_FC2_W], ff, t.du);
   g.dact_pre = u.f1; g.ld_dact = ff; g.dact_kind = s.d.gelu_tanh ? 2 : 1;
@@ -576,10 +582,10 @@ static int dit_block_bwd(const dp_stage& s, const void* const* P, const void* co
   lb.dtype = dt; lb.rows = T; lb.d = d;
   lb.mod_ld = 6 * d; lb.rows_per_batch = N; lb.dmod_ld = 6 * d;
   lb.dy = b.dh; lb.x = u.x1; lb.mean = u.mean2; lb.rstd = u.rstd2; lb.scale = at(u.m, 4 * d, es); lb.dres = dy; lb.dx32 = dx1;
-  lb.dscale = dm + 4 * d; lb.dshift = dm + 3 * d;
+  lb.dscale = at(dm, 4 * d, es); lb.dshift = at(dm, 3 * d, es);
   DP_TRY(bg.layer_norm(lb, t.ln_partial[1]));
   // ---- attention branch
-  DP_TRY(launch_gate_bwd(dt, dx1, u.o, at(u.m, 2 * d, es), 6 * d, t.dg2, dm + 2 * d, 6 * d, B, N, d, st));
+  DP_TRY(launch_gate_bwd(dt, dx1, u.o, at(u.m, 2 * d, es), 6 * d, t.dg2, at(dm, 2 * d, es), 6 * d, B, N, d, st));
   DP_TRY(bg.weight(t.dg2, T, d, u.a, d, gf(D_WO), gf(D_BO)));
   DP_TRY(proj(gemm_dx(dt, t.dg2, T, d, P[D_WO], WT[D_WO], d, b.da)));
   AttnArgs a = attn_base(s);
@@ -591,21 +597,22 @@ static int dit_block_bwd(const dp_stage& s, const void* const* P, const void* co
   DP_TRY(proj(gemm_dx(dt, t.dqkv, T, 3 * d, P[D_WQKV], WT[D_WQKV], d, b.dh)));
   lb.dy = b.dh; lb.x = u.xin; lb.mean = u.mean1; lb.rstd = u.rstd1; lb.scale = at(u.m, d, es); lb.dres = dx1;
   if (dx_final) { lb.dx = dx_final; lb.dx32 = nullptr; } else lb.dx32 = b.f[c];
-  lb.dscale = dm + d; lb.dshift = dm;
+  lb.dscale = at(dm, d, es); lb.dshift = dm;
   DP_TRY(bg.layer_norm(lb, t.ln_partial[0]));
   // ---- weight gradients and the conditioning path (m = SiLU(cond) W_ada^T + b_ada: d W_ada, d b_ada and d cond, accumulated over
-  // the blocks in issue order); nothing on the main stream reads their results
+  // the blocks in issue order, or formed for all blocks after the last); nothing on the main stream reads their results
   hipStream_t q = sd.begin();
   DP_TRY(bg.flush_ln(q));
-  DP_TRY(launch_cast_from_f32(dt, dm, t.dm_t, (size_t)B * 6 * d, q));
   bg.st = q;
-  DP_TRY(bg.weight(t.dm_t, B, 6 * d, sc_in, d, gf(D_ADA_W), gf(D_ADA_B)));
+  DP_TRY(bg.weight(dm, B, 6 * d, sc_in, d, gf(D_ADA_W), gf(D_ADA_B)));
   DP_TRY(bg.flush_dw(q));
-  g = gemm_base(dt);
-  g.A = t.dm_t; g.B = P[D_ADA_W]; g.M = B; g.N = d; g.K = 6 * d; g.lda = 6 * d; g.ldb = d; g.b_mc = 1;
-  g.out_f32 = t.dcond_pre; g.ldo32 = d; g.accumulate = 0; g.splitk_ws = b.partial; g.splitk_ws_bytes = b.partial_bytes;
-  DP_TRY(launch_gemm(g, q));
-  DP_TRY(launch_silu_bwd(dt, t.dcond_pre, cond, d_cond, dcond_acc, (size_t)B * d, q));
+  if (!b.cond_ws) {
+    g = gemm_base(dt);
+    g.A = dm; g.B = P[D_ADA_W]; g.M = B; g.N = d; g.K = 6 * d; g.lda = 6 * d; g.ldb = d; g.b_mc = 1;
+    g.out_f32 = t.dcond_pre; g.ldo32 = d; g.accumulate = 0; g.splitk_ws = b.partial; g.splitk_ws_bytes = b.partial_bytes;
+    DP_TRY(launch_gemm(g, q));
+    DP_TRY(launch_silu_bwd(dt, t.dcond_pre, cond, d_cond, dcond_acc, (size_t)B * d, q));
+  }
   *batch = sd.end();
   return sd.err;
 }
@@ -739,6 +746,8 @@ static int run_stage_bwd(dp_stage* s, const void* const* params, const void* dy,
   if (!unet && s->es == 2) DP_TRY(launch_cast_to_f32(s->d.dtype, dy, bs.f[1], (size_t)s->T * s->d.d_model, st));
   GradPair cur{s->es == 4 ? (float*)const_cast<void*>(dy) : (unet ? nullptr : bs.f[1]), const_cast<void*>(dy)};
   int ci = 1;   // index of the fp32 buffer that holds cur
+  std::vector<const void*> dm(nb), w_ada(nb);
+  int cond_parts = 0;
   int batch[2] = {0, 0};      // last side batch that reads each of the two buffer sets
   for (int i = 0; i < nb; ++i) {
     const int b = nb - 1 - i;
@@ -754,7 +763,16 @@ static int run_stage_bwd(dp_stage* s, const void* const* params, const void* dy,
       ci ^= 1;
       cur = GradPair{bs.f[ci], s->es == 4 ? (void*)bs.f[ci] : bs.out_h[i % 3]};
     } else {
-      DP_TRY(dit_block_bwd(*s, P, WT, G, acc, cc, sp.sc_in, i == 0 ? cur.f : bs.f[ci], ci, dx_final, (float*)d_cond, i != 0, sp.db[b], bs, bs.set[i & 1], sk, sd, &batch[i & 1]));
+      dm[b] = at(bs.dm, (size_t)b * s->d.batch * 6 * s->d.d_model, s->es);
+      w_ada[b] = P[D_ADA_W];
+      DP_TRY(dit_block_bwd(*s, P, WT, G, acc, cc, sp.sc_in, i == 0 ? cur.f : bs.f[ci], ci, dx_final, (float*)d_cond, i != 0, const_cast<void*>(dm[b]), sp.db[b], bs, bs.set[i & 1], sk, sd, &batch[i & 1]));
+    }
+    // d cond of this block where blocks are timed one by one, else of all blocks after the last
+    if (bs.cond_ws && (ph ? true : b == 0)) {
+      hipStream_t q = sd.begin();
+      DP_TRY(launch_cond_grad(&dm[b], &w_ada[b], ph ? 1 : nb, s->d.batch, s->d.d_model, bs.cond_ws, &cond_parts, q));
+      if (b == 0) DP_TRY(launch_cond_grad_finish(bs.cond_ws, cond_parts, cc, (float*)d_cond, s->d.batch, s->d.d_model, q));
+      sd.end();
     }
     if (ph && ph->ev) sd.wait(sd.issued);      // per-block timing: charge a block's side work to that block
   }
