@@ -200,6 +200,9 @@ struct LnBwdArgs {
   void* dx; float* dx32;
   float* dgamma; float* dbeta; int accumulate;
   void* dscale; void* dshift; int dmod_ld;
+  // the result rows (fp32 values) are the gradient of x + gate_b * branch: also dbranch = result * gate_b (storage dtype), and column sums of
+  // result * branch per workgroup into gate_partial [batch][chunk][2][d] (the caller picks which of the two), summed like the others
+  const void* gate; int gate_ld; const void* branch; void* dbranch; float* gate_partial;
   float* partial; size_t partial_bytes;
   int defer_reduce;        // 1: only write the column partials; the caller runs launch_ln_bwd_reduce (maybe on another stream)
 };
@@ -229,10 +232,8 @@ int launch_silu(int dtype, const void* x, void* y, size_t n, hipStream_t s);
 // dc[i] (+)= dsilu_in[i] * silu'(c[i])   (fp32 in, storage-dtype c, fp32 out)
 int launch_silu_bwd(int dtype, const float* dz, const void* c, float* dc, int accumulate, size_t n, hipStream_t s);
 
-// Gated-branch backward helper (dres is the fp32 residual-stream gradient): dbranch[m,n] = dres[m,n] * gate[b,n];
-// dgate[b,n] = sum_{rows of batch b} dres[m,n] * branch[m,n]   (fp32 sums, storage dtype, overwrite)
-int launch_gate_bwd(int dtype, const void* dres, const void* branch, const void* gate, int gate_ld,
-                    void* dbranch, void* dgate, int dgate_ld, int B, int rows_per_batch, int d, hipStream_t s);
+// The gated branch of LnBwdArgs alone, for result rows `dres` (fp32)
+int launch_gate_bwd(const LnBwdArgs& a, hipStream_t s);
 
 // storage dtype -> fp32
 int launch_cast_to_f32(int dtype, const void* in, float* out, size_t n, hipStream_t s);

@@ -258,140 +258,150 @@ int launch_ln_fwd(const LnArgs& a, hipStream_t s) {
 }
 
 // ------------------------------------------------------------------ LayerNorm backward
-// Rows per workgroup (a multiple of its four waves): 16, fewer where that leaves CUs without a workgroup.  1024 rows of 1152 on 64
-// workgroups took 16.3 us, on 256 8.8 us; the partial sums to be added afterwards grow to the same number, a few MB.
-static int ln_bwd_rows(int rows) { return rows >= 8192 ? 16 : (rows >= 2048 ? 8 : 4); }
+// Rows per workgroup (a multiple of LNB_AT_ONCE): 16, fewer where that leaves fewer than 1536 waves for the CUs.  1024 rows of 1152 on 64
+// workgroups took 16.3 us, on 256 8.8; 8192 rows of 640 on 512 workgroups of two waves 26.8 us, on 1024 20.2.  A few dozen rows: two, one pass.
+// (The partial sums to be added afterwards grow to the same number, a few MB.)
+static int ln_bwd_rows(int rows, int d) {
+  const long waves = (d + 511) / 512;
+  return rows * waves >= 1536 * 16 ? 16 : (rows * waves >= 1536 * 8 ? 8 : (rows * waves >= 512 ? 4 : 2));
+}
 
-// grid = (chunks_per_batch, n_batches).  partial: [batch][chunk][2][d]
-// NCH = number of 64-lane vector chunks a row spans (d <= 64 * V * NCH).  A wave owns every fourth row of the
-// workgroup's.  All loads of a row (dy, x, the residual gradient) are issued before the first is used; rows
-// of a single chunk (d <= 512 in bf16) are taken two at a time, which doubles the bytes in flight per wave --
-// the kernel moves ~16 bytes per element and is bound by how much of that is outstanding, not by arithmetic.
-template <typename T, int NCH>
-__global__ void __launch_bounds__(256) ln_bwd_kernel(int d, int rows_per_batch, int wg_rows, const T* __restrict__ dy, const float* __restrict__ x,
-                                                     const float* __restrict__ mean, const float* __restrict__ rstd,
-                                                     const T* __restrict__ gamma, const T* __restrict__ scale, int mod_ld,
-                                                     const float* __restrict__ dres, const T* __restrict__ dres_t,
-                                                     T* __restrict__ dx, float* __restrict__ dx32, float* __restrict__ partial) {
+// Gated branch behind a result row: see ln_bwd_kernel.
+struct GateBwd { const void* gate; int gate_ld; const void* branch; void* dbranch; float* partial; };
+// A gated branch on its own (the last block's, whose result gradient comes from outside).  Rows and workgroups as in ln_bwd_kernel.
+template <typename T>
+__global__ void __launch_bounds__(256) gate_bwd_kernel(int d, int rows_per_batch, int wg_rows, const float* __restrict__ dres, const GateBwd gt) {
   constexpr int V = Vec<T>::N;
-  using VT = typename Vec<T>::type;
-  extern __shared__ float cols[];   // [4 waves][2][d]
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int b = blockIdx.y;
-  const int r_begin = blockIdx.x * wg_rows, r_end = min(rows_per_batch, r_begin + wg_rows);
-  float gsum[NCH][V], bsum[NCH][V], gain[NCH][V];
+  const int b = blockIdx.y, col = threadIdx.x * V, r_begin = blockIdx.x * wg_rows, r_end = min(rows_per_batch, r_begin + wg_rows);
+  if (col >= d) return;
+  float hsum[V], gate[V];
 #pragma unroll
-  for (int c = 0; c < NCH; ++c) {
-    const int col = (c * 64 + lane) * V;
+  for (int i = 0; i < V; ++i) hsum[i] = 0.f;
+  load_vec<T>((const T*)gt.gate + (size_t)b * gt.gate_ld + col, gate);
+#pragma unroll 4
+  for (int r = r_begin; r < r_end; ++r) {
+    const size_t o = ((size_t)b * rows_per_batch + r) * d + col;
+    float dr[V], br[V], ob[V];
+    load_f32<V>(dres + o, dr);
+    load_vec<T>((const T*)gt.branch + o, br);
 #pragma unroll
-    for (int i = 0; i < V; ++i) { gsum[c][i] = 0.f; bsum[c][i] = 0.f; gain[c][i] = 1.f; }
-    if (col < d) {
-      if (scale) {
-        load_vec<T>(scale + (size_t)b * mod_ld + col, gain[c]);
-#pragma unroll
-        for (int i = 0; i < V; ++i) gain[c][i] += 1.0f;
-      } else if (gamma) {
-        load_vec<T>(gamma + col, gain[c]);
-      }
-    }
+    for (int i = 0; i < V; ++i) { hsum[i] = fmaf(dr[i], br[i], hsum[i]); ob[i] = dr[i] * gate[i]; }
+    store_vec<T>((T*)gt.dbranch + o, ob);
   }
-  struct Row {
-    size_t row; float mu, rs, s1, s2;
-    VT dyr[NCH], drt[NCH];            // raw loads
-    float xr[NCH][V], drf[NCH][V];
-    float g[NCH][V], xh[NCH][V];
-  };
-  auto issue = [&](Row& R, int r) {
-    R.row = (size_t)b * rows_per_batch + r;
-    R.mu = mean[R.row]; R.rs = rstd[R.row];
+  store_f32<V>(gt.partial + ((size_t)b * gridDim.x + blockIdx.x) * 2 * d + col, hsum);
+}
+
+// grid = (chunks_per_batch, n_batches); a thread owns V columns of all rows of its workgroup (as many waves as a row has 64-lane
+// chunks), so the column sums need no exchange; the rows' sums meet in LDS.  partial: [batch][chunk][2][d].
+// The kernel moves ~16 bytes per element and is bound by how much of that is outstanding: LNB_AT_ONCE rows are loaded before the first is used.
+// (With whole rows per wave a row of 1152 needed 242 registers; 1024 x 1152 8.8 us, 8192 x 1152 28.8 us; now 9.0 and 26 to 30 us, 32768 x 320 40.6 -> 31.6.)
+//
+// GATE: the result is also the gradient of a gated branch's sum, x_next = x + gate_b * branch: dbranch = result * gate_b, and per
+// workgroup the column sums of result * branch (gate_partial, [batch][chunk][2][d], one of the two).  A kernel of its own for it reads the
+// result again: 7.9 us at 1024 x 1152, 18.9 us at 8192 x 1152, against 2.5 and 14 to 18 here.
+constexpr int LNB_AT_ONCE = 2;
+template <typename T, bool GATE>
+__global__ void __launch_bounds__(256, 2) ln_bwd_kernel(int d, int rows_per_batch, int wg_rows, const T* __restrict__ dy, const float* __restrict__ x,
+                                                        const float* __restrict__ mean, const float* __restrict__ rstd,
+                                                        const T* __restrict__ gamma, const T* __restrict__ scale, int mod_ld,
+                                                        const float* __restrict__ dres, const T* __restrict__ dres_t,
+                                                        T* __restrict__ dx, float* __restrict__ dx32, float* __restrict__ partial, const GateBwd gt) {
+  constexpr int V = Vec<T>::N, R = LNB_AT_ONCE;
+  using VT = typename Vec<T>::type;
+  __shared__ float red[2][4][2 * R];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, waves = blockDim.x >> 6, b = blockIdx.y, col = tid * V;
+  const bool on = col < d;
+  const int r_begin = blockIdx.x * wg_rows, r_end = min(rows_per_batch, r_begin + wg_rows);
+  float gsum[V], bsum[V], gain[V], hsum[V], gate[V];
 #pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-      const int col = (c * 64 + lane) * V;
-      if (col < d) {
-        R.dyr[c] = *reinterpret_cast<const VT*>(dy + R.row * d + col);
-        load_f32<V>(x + R.row * d + col, R.xr[c]);
-        if (dres) load_f32<V>(dres + R.row * d + col, R.drf[c]);
-        else if (dres_t) R.drt[c] = *reinterpret_cast<const VT*>(dres_t + R.row * d + col);
+  for (int i = 0; i < V; ++i) { gsum[i] = 0.f; bsum[i] = 0.f; gain[i] = 1.f; hsum[i] = 0.f; gate[i] = 0.f; }
+  if (on) {
+    if (scale) {
+      load_vec<T>(scale + (size_t)b * mod_ld + col, gain);
+#pragma unroll
+      for (int i = 0; i < V; ++i) gain[i] += 1.0f;
+    } else if (gamma) {
+      load_vec<T>(gamma + col, gain);
+    }
+    if constexpr (GATE) load_vec<T>((const T*)gt.gate + (size_t)b * gt.gate_ld + col, gate);
+  }
+  const float inv_d = 1.0f / d;
+  int turn = 0;
+  for (int r0 = r_begin; r0 < r_end; r0 += R, turn ^= 1) {
+    VT dyr[R], drt[R], br[R];
+    float xh[R][V], drf[R][V], g[R][V], mu[R], rs[R], s1[R], s2[R];
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      const size_t row = (size_t)b * rows_per_batch + min(r0 + k, r_end - 1);
+      mu[k] = mean[row]; rs[k] = rstd[row];
+      if (on) {
+        const size_t o = row * d + col;
+        dyr[k] = *reinterpret_cast<const VT*>(dy + o);
+        load_f32<V>(x + o, xh[k]);
+        if (dres) load_f32<V>(dres + o, drf[k]);
+        else if (dres_t) drt[k] = *reinterpret_cast<const VT*>(dres_t + o);
+        if constexpr (GATE) br[k] = *reinterpret_cast<const VT*>((const T*)gt.branch + o);
       }
     }
-  };
-  auto reduce_in = [&](Row& R) {
-    R.s1 = 0.f; R.s2 = 0.f;
 #pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-      const int col = (c * 64 + lane) * V;
-      if (col < d) {
+    for (int k = 0; k < R; ++k) {
+      s1[k] = 0.f; s2[k] = 0.f;
+      const float live = r0 + k < r_end ? 1.f : 0.f;
+      if (on) {
 #pragma unroll
         for (int i = 0; i < V; ++i) {
-          const float dyv = to_f<T>(R.dyr[c][i]);
-          R.xh[c][i] = (R.xr[c][i] - R.mu) * R.rs;
-          gsum[c][i] += dyv * R.xh[c][i];
-          bsum[c][i] += dyv;
-          R.g[c][i] = dyv * gain[c][i];
-          R.s1 += R.g[c][i];
-          R.s2 += R.g[c][i] * R.xh[c][i];
+          const float dyv = to_f<T>(dyr[k][i]) * live;
+          xh[k][i] = (xh[k][i] - mu[k]) * rs[k];
+          gsum[i] += dyv * xh[k][i];
+          bsum[i] += dyv;
+          g[k][i] = dyv * gain[i];
+          s1[k] += g[k][i];
+          s2[k] += g[k][i] * xh[k][i];
         }
       }
+      s1[k] = wave_sum(s1[k]); s2[k] = wave_sum(s2[k]);
     }
-  };
-  auto finish = [&](Row& R) {
-    const float m1 = wave_sum(R.s1) / d, m2 = wave_sum(R.s2) / d;
+    if (waves > 1) {      // (two copies in turn: one barrier per pass)
+      if (lane == 0) {
 #pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-      const int col = (c * 64 + lane) * V;
-      if (col < d) {
-        float o[V];
+        for (int k = 0; k < R; ++k) { red[turn][wave][2 * k] = s1[k]; red[turn][wave][2 * k + 1] = s2[k]; }
+      }
+      __syncthreads();
 #pragma unroll
-        for (int i = 0; i < V; ++i) o[i] = R.rs * (R.g[c][i] - m1 - R.xh[c][i] * m2);
-        if (dres) {
-#pragma unroll
-          for (int i = 0; i < V; ++i) o[i] += R.drf[c][i];
-        } else if (dres_t) {
-#pragma unroll
-          for (int i = 0; i < V; ++i) o[i] += to_f<T>(R.drt[c][i]);
-        }
-        if (dx32) store_f32<V>(dx32 + R.row * d + col, o);
-        if (dx) store_vec<T>(dx + R.row * d + col, o);
+      for (int k = 0; k < R; ++k) {
+        s1[k] = red[turn][0][2 * k]; s2[k] = red[turn][0][2 * k + 1];
+        for (int w = 1; w < waves; ++w) { s1[k] += red[turn][w][2 * k]; s2[k] += red[turn][w][2 * k + 1]; }
       }
     }
-  };
-  if (NCH == 1) {
-    for (int r = r_begin + wave; r < r_end; r += 8) {
-      const bool two = r + 4 < r_end;                        // wave-uniform
-      Row A, B;
-      issue(A, r);
-      if (two) issue(B, r + 4);
-      reduce_in(A);
-      if (two) reduce_in(B);
-      finish(A);
-      if (two) finish(B);
-    }
-  } else {
-    // wider rows: a second row's registers would cost occupancy (measured slower at d = 640 and 1152)
-    for (int r = r_begin + wave; r < r_end; r += 4) {
-      Row A;
-      issue(A, r);
-      reduce_in(A);
-      finish(A);
-    }
-  }
-  if (!partial) return;
-  // fixed-order reduction of the four waves' column sums
 #pragma unroll
-  for (int c = 0; c < NCH; ++c) {
-    const int col = (c * 64 + lane) * V;
-    if (col < d) {
+    for (int k = 0; k < R; ++k) {
+      if (!on || r0 + k >= r_end) continue;
+      const size_t o = ((size_t)b * rows_per_batch + r0 + k) * d + col;
+      const float m1 = s1[k] * inv_d, m2 = s2[k] * inv_d;
+      float v[V];
 #pragma unroll
-      for (int i = 0; i < V; ++i) {
-        cols[(wave * 2 + 0) * d + col + i] = gsum[c][i];
-        cols[(wave * 2 + 1) * d + col + i] = bsum[c][i];
+      for (int i = 0; i < V; ++i) v[i] = rs[k] * (g[k][i] - m1 - xh[k][i] * m2);
+      if (dres) {
+#pragma unroll
+        for (int i = 0; i < V; ++i) v[i] += drf[k][i];
+      } else if (dres_t) {
+#pragma unroll
+        for (int i = 0; i < V; ++i) v[i] += to_f<T>(drt[k][i]);
       }
+      if constexpr (GATE) {
+        float ob[V];
+#pragma unroll
+        for (int i = 0; i < V; ++i) { hsum[i] = fmaf(v[i], to_f<T>(br[k][i]), hsum[i]); ob[i] = v[i] * gate[i]; }
+        store_vec<T>((T*)gt.dbranch + o, ob);
+      }
+      if (dx32) store_f32<V>(dx32 + o, v);
+      if (dx) store_vec<T>(dx + o, v);
     }
   }
-  __syncthreads();
-  float* out = partial + ((size_t)b * gridDim.x + blockIdx.x) * 2 * d;
-  for (int i = threadIdx.x; i < 2 * d; i += 256)
-    out[i] = ((cols[i] + cols[2 * d + i]) + cols[4 * d + i]) + cols[6 * d + i];
+  if (!on) return;
+  const size_t chunk = ((size_t)b * gridDim.x + blockIdx.x) * 2 * d;
+  if (partial) { store_f32<V>(partial + chunk + col, gsum); store_f32<V>(partial + chunk + d + col, bsum); }
+  if constexpr (GATE) store_f32<V>(gt.partial + chunk + col, hsum);
 }
 
 // out_k[b * ld + col] = (acc ? old : 0) + sum_chunks partial[b][chunk][k][col], k = 0 (gain grad), 1 (shift grad).
@@ -414,6 +424,7 @@ __global__ void __launch_bounds__(1024) ln_bwd_reduce_kernel(const LnReduceSet s
   float s = 0.f;
   if (col < 2 * d) {
     const float* p = partial + (size_t)b * nchunk * 2 * d + col;
+#pragma unroll 8
     for (int c = grp; c < nchunk; c += GROUPS) s += p[(size_t)c * 2 * d];
   }
   red[grp][lc] = s;
@@ -430,25 +441,18 @@ __global__ void __launch_bounds__(1024) ln_bwd_reduce_kernel(const LnReduceSet s
 size_t ln_bwd_partial_bytes(int rows, int d, int rows_per_batch) {
   if (rows_per_batch <= 0) rows_per_batch = rows;
   const int nb = rows / rows_per_batch;
-  const int wg_rows = ln_bwd_rows(rows), nchunk = (rows_per_batch + wg_rows - 1) / wg_rows;
+  const int wg_rows = ln_bwd_rows(rows, d), nchunk = (rows_per_batch + wg_rows - 1) / wg_rows;
   return (size_t)nb * nchunk * 2 * d * sizeof(float);
 }
 
-template <typename T, int NCH>
-static void ln_bwd_launch(const LnBwdArgs& a, int rpb, int nb, int nchunk, float* partial, hipStream_t s) {
-  hipLaunchKernelGGL((ln_bwd_kernel<T, NCH>), dim3(nchunk, nb), dim3(256), (size_t)8 * a.d * sizeof(float), s, a.d, rpb, ln_bwd_rows(a.rows), (const T*)a.dy,
-                     (const float*)a.x, a.mean, a.rstd, (const T*)a.gamma, (const T*)a.scale, a.mod_ld,
-                     a.dres_storage ? nullptr : (const float*)a.dres, a.dres_storage ? (const T*)a.dres : nullptr, (T*)a.dx, a.dx32, partial);
-}
+static GateBwd gate_of(const LnBwdArgs& a) { return GateBwd{a.gate, a.gate_ld, a.branch, a.dbranch, a.gate_partial}; }
+static int ln_bwd_threads(const LnBwdArgs& a) { return (a.d / (a.dtype == BF16 ? 8 : 4) + 63) / 64 * 64; }      // at most 256: check_ln_dim
 template <typename T>
 static int ln_bwd_t(const LnBwdArgs& a, int rpb, int nb, int nchunk, float* partial, hipStream_t s) {
-  const int nch = (a.d + 64 * Vec<T>::N - 1) / (64 * Vec<T>::N);
-  switch (nch) {
-    case 1: ln_bwd_launch<T, 1>(a, rpb, nb, nchunk, partial, s); break;
-    case 2: ln_bwd_launch<T, 2>(a, rpb, nb, nchunk, partial, s); break;
-    case 3: ln_bwd_launch<T, 3>(a, rpb, nb, nchunk, partial, s); break;
-    default: ln_bwd_launch<T, LN_MAXCH>(a, rpb, nb, nchunk, partial, s); break;
-  }
+  auto kern = a.gate ? ln_bwd_kernel<T, true> : ln_bwd_kernel<T, false>;
+  hipLaunchKernelGGL(kern, dim3(nchunk, nb), dim3(ln_bwd_threads(a)), 0, s, a.d, rpb, ln_bwd_rows(a.rows, a.d), (const T*)a.dy,
+                     (const float*)a.x, a.mean, a.rstd, (const T*)a.gamma, (const T*)a.scale, a.mod_ld,
+                     a.dres_storage ? nullptr : (const float*)a.dres, a.dres_storage ? (const T*)a.dres : nullptr, (T*)a.dx, a.dx32, partial, gate_of(a));
   return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "ln_bwd launch failed");
 }
 
@@ -458,7 +462,8 @@ int launch_ln_bwd(const LnBwdArgs& a, hipStream_t s) {
   const bool modulated = a.scale != nullptr;
   const int rpb = modulated ? a.rows_per_batch : a.rows;
   if (rpb <= 0 || a.rows % rpb) return set_error(DP_EINVAL, "ln_bwd: rows must be a multiple of rows_per_batch");
-  const int nb = a.rows / rpb, wg_rows = ln_bwd_rows(a.rows), nchunk = (rpb + wg_rows - 1) / wg_rows;
+  const int nb = a.rows / rpb, wg_rows = ln_bwd_rows(a.rows, a.d), nchunk = (rpb + wg_rows - 1) / wg_rows;
+  if (a.gate && (!modulated || !a.branch || !a.dbranch || !a.gate_partial || !a.partial || a.gate_ld % 8)) return set_error(DP_EINVAL, "ln_bwd: a gated branch needs modulated rows, its operands and partial buffers");
   const bool want_cols = modulated ? (a.dscale && a.dshift) : (a.dgamma && a.dbeta);
   float* partial = nullptr;
   if (want_cols) {
@@ -472,6 +477,17 @@ int launch_ln_bwd(const LnBwdArgs& a, hipStream_t s) {
   }
   if (e || !want_cols || a.defer_reduce) return e;
   return launch_ln_bwd_reduce(&a, 1, s);
+}
+
+int launch_gate_bwd(const LnBwdArgs& a, hipStream_t s) {
+  if (a.rows <= 0 || a.rows_per_batch <= 0 || a.rows % a.rows_per_batch || a.gate_ld % 8) return set_error(DP_EINVAL, "gate_bwd: bad sizes");
+  if (int e = check_ln_dim(a.dtype, a.d)) return e;
+  const void* ptrs[] = {a.dres, a.branch, a.gate, a.dbranch, a.gate_partial};
+  for (const void* q : ptrs) if (!q || ((uintptr_t)q % 16)) return set_error(DP_EALIGN, "gate_bwd: operands must be non-null and 16-byte aligned");
+  const int wg_rows = ln_bwd_rows(a.rows, a.d), nchunk = (a.rows_per_batch + wg_rows - 1) / wg_rows;
+  auto kern = a.dtype == BF16 ? gate_bwd_kernel<bf16> : gate_bwd_kernel<float>;
+  hipLaunchKernelGGL(kern, dim3(nchunk, a.rows / a.rows_per_batch), dim3(ln_bwd_threads(a)), 0, s, a.d, a.rows_per_batch, wg_rows, (const float*)a.dres, gate_of(a));
+  return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "gate_bwd launch failed");
 }
 
 // Second half of launch_ln_bwd for n LayerNorms of the same shape: fixed-order sum of the per-workgroup column partials
@@ -490,7 +506,7 @@ int launch_ln_bwd_reduce(const LnBwdArgs* a, int n, hipStream_t s) {
     set.out0[i] = modulated ? a[i].dscale : (void*)a[i].dgamma;
     set.out1[i] = modulated ? a[i].dshift : (void*)a[i].dbeta;
   }
-  const int nb = a[0].rows / rpb, wg_rows = ln_bwd_rows(a[0].rows), nchunk = (rpb + wg_rows - 1) / wg_rows;
+  const int nb = a[0].rows / rpb, wg_rows = ln_bwd_rows(a[0].rows, d), nchunk = (rpb + wg_rows - 1) / wg_rows;
   KScope ks(KK_REDUCE, 0.0, (double)n * nb * nchunk * 2 * d * 4, s, nchunk, 2 * d);
   if (modulated)
     hipLaunchKernelGGL((a[0].dtype == BF16 ? ln_bwd_reduce_kernel<32, bf16> : ln_bwd_reduce_kernel<32, float>), dim3((2 * d + 31) / 32, nb, n), dim3(1024), 0, s, set, nchunk, d, a[0].dmod_ld, 0);
@@ -688,70 +704,6 @@ int launch_silu_bwd(int dtype, const float* dz, const void* c, float* dc, int ac
   if (dtype == BF16) hipLaunchKernelGGL(silu_bwd_kernel<bf16>, dim3((n + 255) / 256), dim3(256), 0, s, dz, (const bf16*)c, dc, accumulate, n);
   else hipLaunchKernelGGL(silu_bwd_kernel<float>, dim3((n + 255) / 256), dim3(256), 0, s, dz, (const float*)c, dc, accumulate, n);
   return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "silu_bwd launch failed");
-}
-
-// ------------------------------------------------------------------ gated branch backward
-// grid = (ceil(d / (16 V)), B), 16 waves per workgroup.  A workgroup owns 16 V columns (V = 8 bf16 / 4 fp32
-// per lane, 16-byte accesses) of one batch; a wave covers 4 rows at a time (lane = row-in-group * 16 +
-// column chunk), the 16 waves 64 rows.  Column sums: over a wave's 4 row lanes by shuffles, over the
-// waves through LDS in wave order (fixed order).
-constexpr int GB_WAVES = 16;
-template <typename T>
-__global__ void __launch_bounds__(64 * GB_WAVES) gate_bwd_kernel(const float* __restrict__ dres, const T* __restrict__ branch,
-                                                                 const T* __restrict__ gate, int gate_ld, T* __restrict__ dbranch,
-                                                                 T* __restrict__ dgate, int dgate_ld, int rows_per_batch, int d) {
-  constexpr int V = Vec<T>::N;
-  __shared__ float red[GB_WAVES][16 * V];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int cl = lane & 15, rl = lane >> 4;
-  const int b = blockIdx.y, col = (blockIdx.x * 16 + cl) * V;
-  float s[V], g[V];
-#pragma unroll
-  for (int i = 0; i < V; ++i) s[i] = 0.f;
-  if (col < d) {
-    load_vec<T>(gate + (size_t)b * gate_ld + col, g);
-#pragma unroll 2
-    for (int r = wave * 4 + rl; r < rows_per_batch; r += 4 * GB_WAVES) {
-      const size_t o = ((size_t)b * rows_per_batch + r) * d + col;
-      float dr[V], br[V], ob[V];
-      load_f32<V>(dres + o, dr);
-      load_vec<T>(branch + o, br);
-#pragma unroll
-      for (int i = 0; i < V; ++i) { s[i] = fmaf(dr[i], br[i], s[i]); ob[i] = dr[i] * g[i]; }
-      store_vec<T>(dbranch + o, ob);
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < V; ++i) {
-    s[i] += __shfl_xor(s[i], 16, 64);
-    s[i] += __shfl_xor(s[i], 32, 64);
-  }
-  if (rl == 0) {
-#pragma unroll
-    for (int i = 0; i < V; ++i) red[wave][cl * V + i] = s[i];
-  }
-  __syncthreads();
-  if (threadIdx.x < 16 * V) {
-    const int gc = blockIdx.x * 16 * V + threadIdx.x;
-    if (gc < d) {
-      float t = 0.f;
-#pragma unroll
-      for (int w = 0; w < GB_WAVES; ++w) t += red[w][threadIdx.x];
-      dgate[(size_t)b * dgate_ld + gc] = from_f<T>(t);
-    }
-  }
-}
-int launch_gate_bwd(int dtype, const void* dres, const void* branch, const void* gate, int gate_ld, void* dbranch, void* dgate,
-                    int dgate_ld, int B, int rows_per_batch, int d, hipStream_t s) {
-  const int V = dtype == BF16 ? 8 : 4;
-  if (B <= 0 || rows_per_batch <= 0 || d <= 0 || d % V || gate_ld % V) return set_error(DP_EINVAL, "gate_bwd: bad sizes");
-  const void* ptrs[] = {dres, branch, gate, dbranch};
-  for (const void* q : ptrs) if (!q || ((uintptr_t)q % 16)) return set_error(DP_EALIGN, "gate_bwd: operands must be non-null and 16-byte aligned");
-  if (!dgate) return set_error(DP_EINVAL, "gate_bwd: dgate is NULL");
-  dim3 grid((d + 16 * V - 1) / (16 * V), B);
-  if (dtype == BF16) hipLaunchKernelGGL(gate_bwd_kernel<bf16>, grid, dim3(64 * GB_WAVES), 0, s, (const float*)dres, (const bf16*)branch, (const bf16*)gate, gate_ld, (bf16*)dbranch, (bf16*)dgate, dgate_ld, rows_per_batch, d);
-  else hipLaunchKernelGGL(gate_bwd_kernel<float>, grid, dim3(64 * GB_WAVES), 0, s, (const float*)dres, (const float*)branch, (const float*)gate, gate_ld, (float*)dbranch, (float*)dgate, dgate_ld, rows_per_batch, d);
-  return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "gate_bwd launch failed");
 }
 
 // ------------------------------------------------------------------ cast, embedding

@@ -83,7 +83,7 @@ struct GradPair { float* f; void* h; };
 // beside) the activation-gradient chain, so these buffers alternate between consecutive blocks.
 struct BwdSet {
   void *dqkv, *dq2, *dkv2, *du, *dg, *dg2, *h[2];      // dg, dg2: DiT gated-branch gradients; h: storage copies of dx2, dx1
-  float* ln_partial[3];                                  // column partials of the LayerNorm backward kernels
+  float* ln_partial[3];                                  // column partials of the LayerNorm backward kernels; DiT: [2] of the gated branches
   float* dcond_pre;                                      // DiT: gradient of SiLU(cond) (where not all blocks' are formed together)
 };
 struct BwdScratch {
@@ -196,10 +196,14 @@ static void plan_bwd_scratch(Plan& p, const dp_stage& s, BwdScratch& b) {
   b.ln_partial_bytes = ln_bwd_partial_bytes((int)T, (int)d, unet ? (int)T : s.d.tokens);
   for (int i = 0; i < 2; ++i) {
     BwdSet& t = b.set[i];
-    if (i && (s.d.n_blocks == 1 || es == 4)) { t = b.set[0]; continue; }
+    if (i && (s.d.n_blocks == 1 || es == 4)) {
+      t = b.set[0];
+      if (!unet && s.d.n_blocks > 1) t.ln_partial[2] = (float*)p.take(b.ln_partial_bytes);      // written for the next block before this one's are summed
+      continue;
+    }
     t.dqkv = p.take(T * 3 * d * es);
     if (copies) for (int k = 0; k < 2; ++k) t.h[k] = p.take(T * d * es);
-    for (int k = 0; k < (unet ? 3 : 2); ++k) t.ln_partial[k] = (float*)p.take(b.ln_partial_bytes);
+    for (int k = 0; k < 3; ++k) t.ln_partial[k] = (float*)p.take(b.ln_partial_bytes);
     if (unet) {
       t.dq2 = p.take(T * d * es); t.dkv2 = p.take(Tc * 2 * d * es); t.du = p.take(T * 2 * ff * es);
     } else {
@@ -561,8 +565,9 @@ static int dit_block_fwd(const dp_stage& s, const void* const* P, const float* x
 }
 
 // dy: fp32, f[c] or the caller's tensor; dx1 goes to f[c ^ 1] and the block's dx back to f[c] (or, in the storage dtype, to dx_final).
-static int dit_block_bwd(const dp_stage& s, const void* const* P, const void* const* WT, void* const* G, int acc, const void* cond, const void* sc_in,
-                         const float* dy, int c, void* dx_final, float* d_cond, int dcond_acc, void* dm, DitBuf& u, BwdScratch& b, BwdSet& t, const SplitK& sk, Side& sd, int* batch) {
+static int dit_block_bwd(const dp_stage& s, bool last, const void* const* P, const void* const* WT, void* const* G, int acc, const void* cond, const void* sc_in,
+                         const float* dy, int c, void* dx_final, float* d_cond, int dcond_acc, void* dm, DitBuf& u, const DitBuf* prev, BwdScratch& b, BwdSet& t, BwdSet& t_prev,
+                         const SplitK& sk, Side& sd, int* batch, int prev_batch) {
   const int dt = s.d.dtype, T = s.T, d = s.d.d_model, ff = s.d.ff_inner, B = s.d.batch, N = s.d.tokens;
   const size_t es = s.es;
   hipStream_t st = sd.main;
@@ -571,21 +576,30 @@ static int dit_block_bwd(const dp_stage& s, const void* const* P, const void* co
   auto gf = [&](int i) { return (float*)G[i]; };
   BlockGrads bg(s, b, st, acc);
   // ---- MLP branch
-  DP_TRY(launch_gate_bwd(dt, dy, u.f2, at(u.m, 5 * d, es), 6 * d, t.dg, at(dm, 5 * d, es), 6 * d, B, N, d, st));
+  LnBwdArgs lb; memset(&lb, 0, sizeof(lb));
+  lb.dtype = dt; lb.rows = T; lb.d = d;
+  lb.mod_ld = 6 * d; lb.rows_per_batch = N; lb.dmod_ld = 6 * d;
+  // a gated branch's backward rides in the kernel that forms the gradient of its sum: the attention branch's in this block's second
+  // LayerNorm, the MLP branch's in the first LayerNorm of the block after it (the last block's gradient comes from outside)
+  auto gated = [&](LnBwdArgs& l, const void* m, int k, const void* branch, void* dbranch, float* partial) {
+    l.gate = at(m, (size_t)k * d, es); l.gate_ld = 6 * d; l.branch = branch; l.dbranch = dbranch; l.gate_partial = partial + (k == 2 ? 0 : d);
+  };
+  if (last) {
+    lb.dres = dy;
+    gated(lb, u.m, 5, u.f2, t.dg, t.ln_partial[2]);
+    DP_TRY(launch_gate_bwd(lb, st));
+  }
   DP_TRY(bg.weight(t.dg, T, d, u.f, ff, gf(D_FC2_W), gf(D_FC2_B)));
   GemmArgs g = gemm_dx(dt, t.dg, T, d, P[D_FC2_W], WT[D_FC2_W], ff, t.du);
   g.dact_pre = u.f1; g.ld_dact = ff; g.dact_kind = s.d.gelu_tanh ? 2 : 1;
   DP_TRY(proj(g));
   DP_TRY(bg.weight(t.du, T, ff, u.h2, d, gf(D_FC1_W), gf(D_FC1_B)));
   DP_TRY(proj(gemm_dx(dt, t.du, T, ff, P[D_FC1_W], WT[D_FC1_W], d, b.dh)));
-  LnBwdArgs lb; memset(&lb, 0, sizeof(lb));
-  lb.dtype = dt; lb.rows = T; lb.d = d;
-  lb.mod_ld = 6 * d; lb.rows_per_batch = N; lb.dmod_ld = 6 * d;
   lb.dy = b.dh; lb.x = u.x1; lb.mean = u.mean2; lb.rstd = u.rstd2; lb.scale = at(u.m, 4 * d, es); lb.dres = dy; lb.dx32 = dx1;
   lb.dscale = at(dm, 4 * d, es); lb.dshift = at(dm, 3 * d, es);
+  gated(lb, u.m, 2, u.o, t.dg2, t.ln_partial[2]);
   DP_TRY(bg.layer_norm(lb, t.ln_partial[1]));
   // ---- attention branch
-  DP_TRY(launch_gate_bwd(dt, dx1, u.o, at(u.m, 2 * d, es), 6 * d, t.dg2, at(dm, 2 * d, es), 6 * d, B, N, d, st));
   DP_TRY(bg.weight(t.dg2, T, d, u.a, d, gf(D_WO), gf(D_BO)));
   DP_TRY(proj(gemm_dx(dt, t.dg2, T, d, P[D_WO], WT[D_WO], d, b.da)));
   AttnArgs a = attn_base(s);
@@ -598,7 +612,14 @@ static int dit_block_bwd(const dp_stage& s, const void* const* P, const void* co
   lb.dy = b.dh; lb.x = u.xin; lb.mean = u.mean1; lb.rstd = u.rstd1; lb.scale = at(u.m, d, es); lb.dres = dx1;
   if (dx_final) { lb.dx = dx_final; lb.dx32 = nullptr; } else lb.dx32 = b.f[c];
   lb.dscale = at(dm, d, es); lb.dshift = dm;
+  lb.gate = nullptr;
+  if (prev) {
+    sd.wait(prev_batch);      // the last to read these buffers
+    gated(lb, prev->m, 5, prev->f2, t_prev.dg, t_prev.ln_partial[2]);
+  }
   DP_TRY(bg.layer_norm(lb, t.ln_partial[0]));
+  lb.gate = nullptr; lb.partial = t.ln_partial[2]; lb.dscale = at(dm, 2 * d, es); lb.dshift = at(dm, 5 * d, es);
+  bg.ln[bg.n_ln++] = lb;      // the gates' gradients are summed with the others
   // ---- weight gradients and the conditioning path (m = SiLU(cond) W_ada^T + b_ada: d W_ada, d b_ada and d cond, accumulated over
   // the blocks in issue order, or formed for all blocks after the last); nothing on the main stream reads their results
   hipStream_t q = sd.begin();
@@ -765,7 +786,8 @@ static int run_stage_bwd(dp_stage* s, const void* const* params, const void* dy,
     } else {
       dm[b] = at(bs.dm, (size_t)b * s->d.batch * 6 * s->d.d_model, s->es);
       w_ada[b] = P[D_ADA_W];
-      DP_TRY(dit_block_bwd(*s, P, WT, G, acc, cc, sp.sc_in, i == 0 ? cur.f : bs.f[ci], ci, dx_final, (float*)d_cond, i != 0, const_cast<void*>(dm[b]), sp.db[b], bs, bs.set[i & 1], sk, sd, &batch[i & 1]));
+      DP_TRY(dit_block_bwd(*s, i == 0, P, WT, G, acc, cc, sp.sc_in, i == 0 ? cur.f : bs.f[ci], ci, dx_final, (float*)d_cond, i != 0, const_cast<void*>(dm[b]), sp.db[b],
+                           b ? &sp.db[b - 1] : nullptr, bs, bs.set[i & 1], bs.set[(i + 1) & 1], sk, sd, &batch[i & 1], batch[(i + 1) & 1]));
     }
     // d cond of this block where blocks are timed one by one, else of all blocks after the last
     if (bs.cond_ws && (ph ? true : b == 0)) {

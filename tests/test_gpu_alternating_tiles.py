@@ -78,3 +78,28 @@ def test_f32_gemm(layout, M, N, K):
     torch.cuda.synchronize()
     ref = A.astype(np.float64) @ Bm.astype(np.float64)
     assert float(np.abs(out.cpu().numpy() - ref).max() / np.abs(ref).max()) <= 1e-5
+
+
+@pytest.mark.parametrize("heads,d_head,batch,tokens,blocks", [(1, 64, 3, 9, 17), (9, 72, 33, 7, 2), (25, 80, 2, 5, 1)])
+def test_dit_backward_by_width(heads, d_head, batch, tokens, blocks):
+    # LayerNorm backward with the gated branch in it: one wave and four per row, ragged rows; the conditioning gradient: less than a column
+    # tile, 33 rows, more blocks than one launch takes
+    import numpy as np
+    import torch
+    import synth_inputs as si
+    from oracle import blocks as ob
+    from paper_2405_01248_amd.harness import DeviceStage, rel_err
+    cfg = si.StageConfig("dit_width", si.DIT, "bf16", blocks, batch, tokens, heads * d_head, heads, d_head, 0, 0, 64, 1e-6, 1)
+    inp = si.make_stage_inputs(cfg, seed=heads)
+    ds = DeviceStage(cfg, inp)
+    ds.step()
+    torch.cuda.synchronize()
+    got = ds.results()
+    y, caches = ob.stage_fwd(cfg.kind, inp["params"], inp["x"], inp["cond"], cfg.n_blocks, cfg.n_heads, cfg.ln_eps, gelu_tanh=True)
+    dx, dcond, grads = ob.stage_bwd(cfg.kind, inp["params"], caches, inp["dy"], cfg.n_heads)
+    assert rel_err(got["y"], y) <= TOL_BF16
+    assert rel_err(got["dx"], dx) <= TOL_BF16 and rel_err(got["dcond"], dcond) <= TOL_BF16
+    for k in ("ada_w", "ada_b"):
+        for b in range(blocks):
+            name = [n for n in grads if n.startswith(f"block{b}.") and n.endswith(k)][0]
+            assert rel_err(got["grads"][name], grads[name]) <= TOL_BF16, name
