@@ -223,7 +223,7 @@ __global__ void __launch_bounds__(256, DHP == 64 ? 4 : 3) attn_fwd_bf16_kernel(c
     for (int t = 0; t < 2; ++t)
 #pragma unroll
       for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[t][r]);
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    mx = reduce_halves(mx, MaxOp());
     mx = fmaxf(m, mx * p.scale_log2);                    // m is kept in the scaled (log2) domain
     // The reference point only has to bound the exponents, not equal the maximum: it is moved (and the
     // accumulators rescaled) when some query of the wave has outgrown it by 2^8; until then the
@@ -241,7 +241,6 @@ __global__ void __launch_bounds__(256, DHP == 64 ? 4 : 3) attn_fwd_bf16_kernel(c
         s[t][r] = e;
         rs += e;
       }
-    rs += __shfl_xor(rs, 32, 64);
     if (bump) {
       const float alpha = __builtin_amdgcn_exp2f(m - mref);
       lsum *= alpha;
@@ -265,6 +264,7 @@ __global__ void __launch_bounds__(256, DHP == 64 ? 4 : 3) attn_fwd_bf16_kernel(c
     __syncthreads();      // ... and everybody's; all reads of stage buf are done
   }
 
+  lsum = reduce_halves(lsum, AddOp());      // (each lane summed its own keys)
   if (qi < p.Nq) {
     const float inv = lsum > 0.f ? 1.0f / lsum : 0.f;
     bf16* ob = (bf16*)p.o + ((size_t)b * p.Nq + qi) * p.ldo + h * p.dh;
@@ -332,7 +332,7 @@ __global__ void __launch_bounds__(256, DHP == 64 ? 4 : 2) attn_bwd_dq_bf16_kerne
 #pragma unroll
       for (int u = 0; u < 8; ++u) dlt = fmaf((float)of[u], (float)dof[c][u], dlt);
     }
-    dlt += __shfl_xor(dlt, 32, 64);
+    dlt = reduce_halves(dlt, AddOp());
     if (qok && g == 0) p.delta[sidx] = dlt;
   }
 

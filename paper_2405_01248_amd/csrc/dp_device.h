@@ -139,16 +139,31 @@ __device__ __forceinline__ bf16x8 ld8_sel(const bf16* p, bool ok) {
   return __builtin_bit_cast(bf16x8, v);
 }
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+// Reductions over the wave by lane swaps and DPP, six dependent VALU steps: through ds_bpermute (what __shfl_xor compiles to) each step is an LDS
+// round trip of some 50 ns, which a LayerNorm of few rows waits for twelve times.  Pairs as in a butterfly over lane bits 5, 4, ..., 0 (a row
+// rotated by 8 and by 4 holds the partner's value, since the lanes that differ in the higher bits are equal by then).  All lanes must be active.
+template <int CTRL> __device__ __forceinline__ float lane_dpp(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
 }
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
+template <class Op> __device__ __forceinline__ float reduce_halves(float v, Op op) {      // over lanes i and i ^ 32
+  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, v), __builtin_bit_cast(uint32_t, v), false, false);
+  const uint32_t lo = r[0], hi = r[1];
+  return op(__builtin_bit_cast(float, lo), __builtin_bit_cast(float, hi));
 }
+template <class Op> __device__ __forceinline__ float wave_reduce(float v, Op op) {
+  v = reduce_halves(v, op);
+  const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, v), __builtin_bit_cast(uint32_t, v), false, false);
+  const uint32_t lo = r[0], hi = r[1];
+  v = op(__builtin_bit_cast(float, lo), __builtin_bit_cast(float, hi));
+  v = op(v, lane_dpp<0x128>(v));      // row_ror:8
+  v = op(v, lane_dpp<0x124>(v));      // row_ror:4
+  v = op(v, lane_dpp<0x4E>(v));       // quad_perm:[2,3,0,1]
+  return op(v, lane_dpp<0xB1>(v));    // quad_perm:[1,0,3,2]
+}
+struct AddOp { __device__ __forceinline__ float operator()(float a, float b) const { return a + b; } };
+struct MaxOp { __device__ __forceinline__ float operator()(float a, float b) const { return fmaxf(a, b); } };
+__device__ __forceinline__ float wave_sum(float v) { return wave_reduce(v, AddOp()); }
+__device__ __forceinline__ float wave_max(float v) { return wave_reduce(v, MaxOp()); }
 
 // ---- storage conversion -------------------------------------------------
 template <typename T> __device__ __forceinline__ float to_f(T v);

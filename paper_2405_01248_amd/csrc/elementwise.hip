@@ -120,122 +120,70 @@ static int ln_fwd_t(const LnArgs& a, hipStream_t s) {
   return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "ln_fwd launch failed");
 }
 
-// Split-K reduction onto the fp32 residual stream fused with the LayerNorm that follows (bf16 storage).
-// NCH: number of 512-column chunks a row spans.
-template <int NCH>
-__global__ void __launch_bounds__(256) reduce_residual_ln_kernel(int rows, int d, float eps, const float* __restrict__ partial, int splits,
+// Split-K reduction onto the fp32 residual stream fused with the LayerNorm that follows (bf16 storage).  One workgroup per row, four columns
+// per thread.  On a slice of a few samples the time is the chain of memory round trips, so the planes of partial sums are loaded eight at a time
+// (and added in ascending order), bias, gain and shift with the first.  Encoder of one sample (24 launches
+// of 77 rows of 768): 583 us with a wave per row and LDS-permute reductions, 528; twelve samples 882, 846.
+constexpr int RRLN_PLANES = 8;
+__global__ void __launch_bounds__(512) reduce_residual_ln_kernel(int rows, int d, float eps, const float* __restrict__ partial, int splits,
                                                                  const bf16* __restrict__ bias, float* __restrict__ x, bf16* __restrict__ y,
                                                                  const bf16* __restrict__ gamma, const bf16* __restrict__ beta) {
-  constexpr int V = 8;
-  const int lane = threadIdx.x & 63, row = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= rows) return;
-  const size_t plane = (size_t)rows * d;
-  // The partial sums are added in ascending split order (fixed summation order), but their loads are issued four
-  // planes at a time for all of the row's chunks: on a slice of a few samples the kernel runs on a few dozen
-  // workgroups and its time is the chain of memory round trips, one per plane when load and add alternate.
-  float v[NCH][V], acc[NCH][V];
-  bf16x8 bi[NCH], ga[NCH], be[NCH];     // fetched with the row, used after the reductions
-  const float* prow = partial + (size_t)row * d;
+  constexpr int V = 4;
+  __shared__ float red[2][8];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, waves = blockDim.x >> 6, col = tid * V;
+  const bool on = col < d;
+  const size_t plane = (size_t)rows * d, o = (size_t)blockIdx.x * d + col;
+  float v[V] = {}, acc[V] = {};
+  bf16x4 bi = {}, ga = {}, be = {};
+  if (on) {
+    load_f32<V>(x + o, v);
+    if (bias) bi = *reinterpret_cast<const bf16x4*>(bias + col);
+    ga = *reinterpret_cast<const bf16x4*>(gamma + col);
+    be = *reinterpret_cast<const bf16x4*>(beta + col);
+    for (int z = 0; z < splits; z += RRLN_PLANES) {
+      float t[RRLN_PLANES][V];
 #pragma unroll
-  for (int c = 0; c < NCH; ++c) {
-    const int col = (c * 64 + lane) * V;
-    if (col < d) {
-      load_f32<V>(x + (size_t)row * d + col, v[c]);
-      load_f32<V>(prow + col, acc[c]);
-      if (bias) bi[c] = *reinterpret_cast<const bf16x8*>(bias + col);
-      ga[c] = *reinterpret_cast<const bf16x8*>(gamma + col);
-      be[c] = *reinterpret_cast<const bf16x8*>(beta + col);
-    }
-  }
-  int z = 1;
-  for (; z + 3 < splits; z += 4) {
-    float t[4][NCH][V];
+      for (int u = 0; u < RRLN_PLANES; ++u)
+        if (z + u < splits) load_f32<V>(partial + (z + u) * plane + o, t[u]);
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
+      for (int u = 0; u < RRLN_PLANES; ++u)
+        if (z + u < splits) {
 #pragma unroll
-      for (int c = 0; c < NCH; ++c) {
-        const int col = (c * 64 + lane) * V;
-        if (col < d) load_f32<V>(prow + (size_t)(z + u) * plane + col, t[u][c]);
-      }
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-      for (int c = 0; c < NCH; ++c) {
-        const int col = (c * 64 + lane) * V;
-        if (col < d) {
-#pragma unroll
-          for (int i = 0; i < V; ++i) acc[c][i] += t[u][c][i];
+          for (int i = 0; i < V; ++i) acc[i] = z + u ? acc[i] + t[u][i] : t[u][i];
         }
-      }
-  }
-  for (; z < splits; ++z) {
-    float t[NCH][V];
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-      const int col = (c * 64 + lane) * V;
-      if (col < d) load_f32<V>(prow + (size_t)z * plane + col, t[c]);
     }
 #pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-      const int col = (c * 64 + lane) * V;
-      if (col < d) {
-#pragma unroll
-        for (int i = 0; i < V; ++i) acc[c][i] += t[c][i];
-      }
-    }
+    for (int i = 0; i < V; ++i) v[i] += acc[i] + (float)bi[i];
+    store_f32<V>(x + o, v);
   }
-  float s = 0.f;
-#pragma unroll
-  for (int c = 0; c < NCH; ++c) {
-    const int col = (c * 64 + lane) * V;
-    if (col < d) {
-      if (bias) {
-#pragma unroll
-        for (int i = 0; i < V; ++i) acc[c][i] += (float)bi[c][i];
-      }
-#pragma unroll
-      for (int i = 0; i < V; ++i) { v[c][i] += acc[c][i]; s += v[c][i]; }
-      store_f32<V>(x + (size_t)row * d + col, v[c]);
-    }
-  }
-  const float mu = wave_sum(s) / d;
+  auto row_sum = [&](float s, float* r) {
+    s = wave_sum(s);
+    if (waves == 1) return s;
+    if (lane == 0) r[wave] = s;
+    __syncthreads();
+    s = r[0];
+    for (int w = 1; w < waves; ++w) s += r[w];
+    return s;
+  };
+  const float mu = row_sum((v[0] + v[1]) + (v[2] + v[3]), red[0]) / d;
   float q = 0.f;
 #pragma unroll
-  for (int c = 0; c < NCH; ++c) {
-    const int col = (c * 64 + lane) * V;
-    if (col < d) {
+  for (int i = 0; i < V; ++i) { v[i] = on ? v[i] - mu : 0.f; q += v[i] * v[i]; }
+  const float rs = rsqrtf(row_sum(q, red[1]) / d + eps);
+  if (!on) return;
+  bf16x4 out;
 #pragma unroll
-      for (int i = 0; i < V; ++i) { v[c][i] -= mu; q += v[c][i] * v[c][i]; }
-    }
-  }
-  const float rs = rsqrtf(wave_sum(q) / d + eps);
-#pragma unroll
-  for (int c = 0; c < NCH; ++c) {
-    const int col = (c * 64 + lane) * V;
-    if (col < d) {
-      float o[V];
-#pragma unroll
-      for (int i = 0; i < V; ++i) o[i] = v[c][i] * rs * (float)ga[c][i] + (float)be[c][i];
-      store_vec<bf16>(y + (size_t)row * d + col, o);
-    }
-  }
+  for (int i = 0; i < V; ++i) out[i] = (bf16)(v[i] * rs * (float)ga[i] + (float)be[i]);
+  *reinterpret_cast<bf16x4*>(y + o) = out;
 }
 
 int launch_reduce_residual_ln(const float* partial, int splits, int rows, int d, const void* bias, float* x, void* y,
                               const void* gamma, const void* beta, float eps, hipStream_t s) {
   if (!partial || splits < 1 || rows <= 0 || !x || !y || !gamma || !beta) return set_error(DP_EINVAL, "reduce_residual_ln: bad arguments");
-  if (d <= 0 || d % 8 || d > 64 * LN_MAXCH * 8) return set_error(DP_EUNSUPPORTED, "reduce_residual_ln: d must be a multiple of 8, at most 2048");
+  if (d <= 0 || d % 8 || d > 512 * 4) return set_error(DP_EUNSUPPORTED, "reduce_residual_ln: d must be a multiple of 8, at most 2048");
   KScope ks(KK_REDUCE, 0.0, (double)rows * d * (4.0 * splits + 8.0 + 2.0), s, rows, d, splits);
-  const dim3 grid((rows + 3) / 4);
-#define DP_RRLN(n_) hipLaunchKernelGGL(reduce_residual_ln_kernel<n_>, grid, dim3(256), 0, s, rows, d, eps, partial, splits, (const bf16*)bias, x, \
-                                       (bf16*)y, (const bf16*)gamma, (const bf16*)beta)
-  switch ((d + 511) / 512) {
-    case 1: DP_RRLN(1); break;
-    case 2: DP_RRLN(2); break;
-    case 3: DP_RRLN(3); break;
-    default: DP_RRLN(4); break;
-  }
-#undef DP_RRLN
+  hipLaunchKernelGGL(reduce_residual_ln_kernel, dim3(rows), dim3((d / 4 + 63) / 64 * 64), 0, s, rows, d, eps, partial, splits, (const bf16*)bias, x,
+                     (bf16*)y, (const bf16*)gamma, (const bf16*)beta);
   return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "reduce_residual_ln launch failed");
 }
 
