@@ -225,23 +225,30 @@ static void plan_bwd_scratch(Plan& p, const dp_stage& s, BwdScratch& b) {
   b.partial = (float*)p.take(b.partial_bytes);
 }
 
+constexpr int SIDE_MIN_BLOCKS = 3;      // stages that use the side stream: see use_side_stream
+
 struct StagePlan {
   std::vector<UnetBuf> ub; std::vector<DitBuf> db;
   void *pp0 = nullptr, *pp1 = nullptr, *pp2 = nullptr, *sc_in = nullptr;   // pp*: fp32 block inputs of a no-save forward
   std::vector<void*> mods;   // DiT, no-save forward: one modulation buffer per block (they are all computed up front)
   BwdScratch bs{};
   float* splitk = nullptr; size_t splitk_bytes = 0;   // partial sums of the projections that are split along the contraction (small batches)
+  float* splitk_kv = nullptr; size_t splitk_kv_bytes = 0;   // ... of the context projections on the side stream, beside the others
   size_t bytes = 0;
 };
 
-// Scratch of the forward's and, with save, the backward's activation projections.
+// Scratch of the forward's and, with save, the backward's activation projections: enough for the split of every one of them, so that a
+// projection is cut alike (and gives the same bits) whichever pass or stream it runs on.
+static size_t kv_splitk_need(const dp_stage& s) { return s.es == 2 && s.Tc ? gemm_epi_splitk_ws_bytes(s.Tc, 2 * s.d.d_model, s.d.ctx_dim) : 0; }
 static size_t splitk_need(const dp_stage& s, bool save) {
   if (s.es != 2) return 0;
   const int T = s.T, d = s.d.d_model, ff = s.d.ff_inner;
   const bool unet = s.d.kind == DP_BLOCK_UNET_XATTN_GEGLU;
-  size_t n = std::max(gemm_epi_splitk_ws_bytes(T, d, d), std::max(gemm_epi_splitk_ws_bytes(T, 3 * d, d), gemm_epi_splitk_ws_bytes(T, d, ff)));
-  if (!unet) n = std::max(n, gemm_epi_splitk_ws_bytes(T, ff, d));
-  if (save) n = std::max(n, std::max(gemm_epi_splitk_ws_bytes(T, d, 3 * d), std::max(gemm_epi_splitk_ws_bytes(T, d, unet ? 2 * ff : ff), gemm_epi_splitk_ws_bytes(T, ff, d))));
+  size_t n = kv_splitk_need(s);
+  auto mx = [&](int rows, int out, int in) { n = std::max(n, gemm_epi_splitk_ws_bytes(rows, out, in)); };
+  mx(T, 3 * d, d); mx(T, d, d); mx(T, unet ? 2 * ff : ff, d); mx(T, d, ff);
+  if (!unet) mx(s.d.batch, 6 * d, d);
+  if (save) { mx(T, d, 3 * d); mx(T, d, unet ? 2 * ff : ff); mx(T, ff, d); }
   return n;
 }
 
@@ -254,6 +261,8 @@ static void make_plan(const dp_stage& s, void* base, bool save, StagePlan& sp) {
   else { sp.db.resize(nb); for (int i = 0; i < nb; ++i) plan_dit_block(p, s, sp.db[i], save); }
   sp.splitk_bytes = splitk_need(s, save);
   sp.splitk = sp.splitk_bytes ? (float*)p.take(sp.splitk_bytes) : nullptr;
+  if (save && s.d.n_blocks >= SIDE_MIN_BLOCKS) sp.splitk_kv_bytes = kv_splitk_need(s);
+  sp.splitk_kv = sp.splitk_kv_bytes ? (float*)p.take(sp.splitk_kv_bytes) : nullptr;
   if (save) plan_bwd_scratch(p, s, sp.bs);
   else {
     const size_t rb = (size_t)s.T * s.d.d_model * 4;
@@ -655,7 +664,7 @@ static int check_stage_call(const dp_stage* s, const void* const* params, const 
 // The side stream carries a block's weight gradients beside the next block's backward.  The first block's have nothing beside them, and what
 // does run together slows each other down: over 40 drawn stages of both kinds, 1 and 2 blocks took 0 to 29 % longer with it (median 3 %;
 // events and waits are most of a small stage's loss), 3 and more blocks 0 to 3 % less.
-static bool use_side_stream(const dp_stage& s) { return s.overlap && s.es == 2 && s.d.n_blocks >= 3; }
+static bool use_side_stream(const dp_stage& s) { return s.overlap && s.es == 2 && s.d.n_blocks >= SIDE_MIN_BLOCKS; }
 
 static int ensure_side_stream(dp_stage* s) {
   if (s->side) return DP_OK;
@@ -688,7 +697,7 @@ static int run_stage_fwd(dp_stage* s, const void* const* params, const void* x, 
     hipStream_t q = sd.begin();
     for (int b = 0; b < nb; ++b) {
       const void* const* P = params + (size_t)b * s->per_block;
-      DP_TRY(launch_gemm(gemm_fwd(s->d.dtype, cc, s->Tc, s->d.ctx_dim, P[U_WKV2], 2 * s->d.d_model, nullptr, sp.ub[b].kv2), q));
+      DP_TRY(SplitK({sp.splitk_kv, sp.splitk_kv_bytes}).launch(gemm_fwd(s->d.dtype, cc, s->Tc, s->d.ctx_dim, P[U_WKV2], 2 * s->d.d_model, nullptr, sp.ub[b].kv2), q));
     }
     kv_batch = sd.end();
   }

@@ -1,0 +1,31 @@
+"""The side stream of a stage (three and more blocks): results do not depend on whether it is used, nor on whether the forward
+keeps its activations."""
+import numpy as np
+import pytest
+
+import synth_inputs as si
+from test_gpu_parity import _run
+
+pytestmark = pytest.mark.gpu
+
+FIVE_UNET = si.StageConfig("five_unet_bf16", si.UNET, "bf16", 5, 2, 200, 192, 3, 64, 77, 64, 288)
+FIVE_DIT = si.StageConfig("five_dit_bf16", si.DIT, "bf16", 5, 3, 72, 144, 2, 72, 0, 0, 296, 1e-6, 1)
+# few context rows and a long contraction: the K/V projection is cut along the contraction where it has scratch for it
+WIDE_CTX = si.StageConfig("unet_wide_context", si.UNET, "bf16", 3, 1, 1024, 256, 4, 64, 77, 4096, 1024)
+
+
+@pytest.mark.parametrize("cfg", [FIVE_UNET, FIVE_DIT, WIDE_CTX], ids=lambda c: c.name)
+def test_overlap_and_saving_change_no_bit(cfg):
+    import torch
+    ds, _ = _run(cfg, randomize_ln=True)
+    on = ds.results()
+    ds.stage.set_overlap(False)
+    ds.step()
+    ds.stage.fwd(ds.params, ds.x, ds.cc, ds.y_sc, ds.ws_nograd, False)
+    torch.cuda.synchronize()
+    off = ds.results()
+    assert np.array_equal(on["y"], off["y_sc"])
+    for k in ("y", "dx"):
+        assert np.array_equal(on[k], off[k]), k
+    for k in on["grads"]:
+        assert np.array_equal(on["grads"][k], off["grads"][k]), k
