@@ -1,10 +1,10 @@
 """The side stream of a stage (three and more blocks): results do not depend on whether it is used, nor on whether the forward
-keeps its activations."""
+keeps its activations; buffers that consecutive blocks take in turn come round from the fourth block on."""
 import numpy as np
 import pytest
 
 import synth_inputs as si
-from test_gpu_parity import _run
+from test_gpu_parity import _compare, _oracle_stage, _run, test_step_can_be_captured_in_a_hip_graph_and_replayed as capture_and_replay
 
 pytestmark = pytest.mark.gpu
 
@@ -12,6 +12,12 @@ FIVE_UNET = si.StageConfig("five_unet_bf16", si.UNET, "bf16", 5, 2, 200, 192, 3,
 FIVE_DIT = si.StageConfig("five_dit_bf16", si.DIT, "bf16", 5, 3, 72, 144, 2, 72, 0, 0, 296, 1e-6, 1)
 # few context rows and a long contraction: the K/V projection is cut along the contraction where it has scratch for it
 WIDE_CTX = si.StageConfig("unet_wide_context", si.UNET, "bf16", 3, 1, 1024, 256, 4, 64, 77, 4096, 1024)
+
+
+@pytest.mark.parametrize("cfg", [FIVE_UNET, FIVE_DIT], ids=lambda c: c.name)
+def test_five_blocks_match_oracle(cfg):
+    ds, inp = _run(cfg, randomize_ln=True)
+    _compare(cfg, ds.results(), _oracle_stage(cfg, inp))
 
 
 @pytest.mark.parametrize("cfg", [FIVE_UNET, FIVE_DIT, WIDE_CTX], ids=lambda c: c.name)
@@ -29,3 +35,7 @@ def test_overlap_and_saving_change_no_bit(cfg):
         assert np.array_equal(on[k], off[k]), k
     for k in on["grads"]:
         assert np.array_equal(on["grads"][k], off["grads"][k]), k
+
+
+def test_five_blocks_in_a_graph():
+    capture_and_replay(FIVE_UNET)
