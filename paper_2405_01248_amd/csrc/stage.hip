@@ -454,10 +454,13 @@ static int unet_block_fwd(const dp_stage& s, const void* const* P, const float* 
     // u = h3 W1^T + b1 and g = value * gelu(gate) in one kernel where the GEMM supports it
     GemmArgs f = gemm_fwd(dt, u.h3, T, d, P[U_W1], 2 * inner, P[U_B1], u.g);
     f.ldo = inner; f.pre_out = u.u; f.ld_pre = 2 * inner; f.geglu = 1; f.geglu_inner = inner;
-    if ((s.fuse & 1) && gemm_geglu_fwd_supported(f)) {
+    const bool can_fuse = gemm_geglu_fwd_supported(f);
+    if ((s.fuse & 1) && can_fuse) {
       DP_TRY(proj(f));
     } else {
-      DP_TRY(proj(gemm_fwd(dt, u.h3, T, d, P[U_W1], 2 * inner, P[U_B1], u.u)));
+      GemmArgs v = gemm_fwd(dt, u.h3, T, d, P[U_W1], 2 * inner, P[U_B1], u.u);
+      if (can_fuse) v.choice_rows = -1;      // the fused kernel's order of additions: switching the fusion off changes no bit
+      DP_TRY(proj(v));
       DP_TRY(launch_geglu_fwd(dt, u.u, u.g, T, inner, st));
     }
   }

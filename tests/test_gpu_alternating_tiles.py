@@ -103,3 +103,22 @@ def test_dit_backward_by_width(heads, d_head, batch, tokens, blocks):
         for b in range(blocks):
             name = [n for n in grads if n.startswith(f"block{b}.") and n.endswith(k)][0]
             assert rel_err(got["grads"][name], grads[name]) <= TOL_BF16, name
+
+
+@pytest.mark.parametrize("batch,tokens,heads", [(2, 77, 8), (1, 77, 20), (2, 1024, 10)])
+def test_geglu_fusion_changes_no_bit_of_the_forward(batch, tokens, heads):
+    # sizes at which a plain projection takes tiles whose waves share the contraction, or 16x16 instructions: another order of additions
+    import numpy as np
+    import torch
+    import synth_inputs as si
+    from paper_2405_01248_amd.harness import DeviceStage
+    d = 64 * heads
+    cfg = si.StageConfig("fusion_bits", si.UNET, "bf16", 1, batch, tokens, d, heads, 64, 7, 64, 4 * d)
+    ds = DeviceStage(cfg, si.make_stage_inputs(cfg, seed=heads))
+    y = []
+    for mask in (3, 0):
+        ds.stage.set_fusion(mask)
+        ds.step()
+        torch.cuda.synchronize()
+        y.append(ds.results()["y"])
+    assert np.array_equal(y[0], y[1])
