@@ -92,6 +92,7 @@ bool gemm_colsum_supported(const GemmArgs& a);
 size_t gemm_splitk_ws_bytes(int M, int N, int K);   // upper bound for out_f32 GEMMs
 size_t gemm_epi_splitk_ws_bytes(int M, int N, int K);   // same for storage-dtype outputs (0: such a GEMM is never split)
 size_t gemm_epi_splitk_ws_bytes_for(int M, int N, int K, int choice_rows);   // with GemmArgs::choice_rows
+int gemm_epi_split_rows(int N, int K);   // no such GEMM of more rows is split
 
 // ---------------------------------------------------------------- FP8 (OCP E4M3) projection GEMM
 // q[i, j] = e4m3(clamp(x[i, j] * inv_scale, -448, 448)), round to nearest even; x [rows, cols] in bf16 (row stride ldx

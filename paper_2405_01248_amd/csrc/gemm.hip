@@ -1028,6 +1028,19 @@ size_t gemm_epi_splitk_ws_bytes_for(int M, int N, int K, int choice_rows) {
 }
 
 size_t gemm_epi_splitk_ws_bytes(int M, int N, int K) { return gemm_epi_splitk_ws_bytes_for(M, N, K, M); }
+// Waves and choose_splits_epi split up to a number of tiles; splits_128 while the reduction of two parts costs less than the most a split can
+// save, one round of tiles.
+int gemm_epi_split_rows(int N, int K) {
+  const int kt = K / 64;
+  long rows = 0;
+  auto tiles = [&](int most, int bm, int bn) { rows = std::max(rows, (long)(most / ((N + bn - 1) / bn)) * bm); };
+  if (kt >= 8) for (const WaveCost& c : kWave) tiles(kCUs / 2, c.bm, c.bn);
+  if (kt >= 12) {
+    tiles(96, 64, 64); tiles(96, 128, 128); tiles(96, 256, 128); tiles(96, 256, 256);
+    rows = std::max(rows, (long)(tile128_us(kCUs, kt, true) / (reduce_us(1000, N, 2, true) - 0.5f) * 1000.f) + 1);
+  }
+  return (int)std::min<long>(rows, 1L << 30);
+}
 
 // Picks the tile configuration (indices as in launch_gemm's switch), from sweeps of all GEMM shapes of
 // the five workloads on MI355X:

@@ -59,6 +59,8 @@ struct dp_encoder {
   dp_encoder_desc d;
   std::vector<ParamInfo> params;
   size_t es;
+  // scratch of the split projections for up to (i + 1) * SPLITK_STEP rows, in every call of fewer rows too (mode 0; constant beyond the last entry)
+  std::vector<size_t> splitk_bytes;
   int batch_invariant = 0;   // 1: tile shapes and split-K factors chosen for one sample's rows; 2: no split-K, 32x32x16 tiles only
 };
 
@@ -819,15 +821,32 @@ static int run_stage_bwd(dp_stage* s, const void* const* params, const void* dy,
 enum { E_LN1_G, E_LN1_B, E_WQKV, E_BQKV, E_WO, E_BO, E_LN2_G, E_LN2_B, E_FC1_W, E_FC1_B, E_FC2_W, E_FC2_B, E_PER_LAYER };
 
 struct EncBuf { void *h, *qkv, *a, *f; float* res; float* splitk; size_t splitk_bytes; size_t bytes; };
+// Scratch of the four projections on `rows` rows whose splits are chosen for `choice_rows` rows.
+static size_t encoder_splitk(const dp_encoder& e, int rows, int choice_rows) {
+  const int d = e.d.d_model, ff = e.d.ff_inner;
+  auto need = [&](int N, int K) { return gemm_epi_splitk_ws_bytes_for(rows, N, K, choice_rows); };
+  return std::max(std::max(need(3 * d, d), need(d, d)), std::max(need(ff, d), need(d, ff)));
+}
+// More rows are split into fewer parts, down to none, and a workspace has to serve every smaller call: the running maximum over the rows.  Between two
+// multiples of 64 all tile counts are the same and the reduction of the partial sums costs least on the fewest rows, so the parts chosen there
+// are the most.
+constexpr size_t SPLITK_STEP = 64;
+static void plan_encoder_splitk(dp_encoder& e) {
+  if (e.es != 2) return;
+  const int d = e.d.d_model, ff = e.d.ff_inner, last = std::max(std::max(gemm_epi_split_rows(3 * d, d), gemm_epi_split_rows(d, d)), std::max(gemm_epi_split_rows(ff, d), gemm_epi_split_rows(d, ff)));
+  size_t most = 0;
+  for (int hi = (int)SPLITK_STEP; hi - (int)SPLITK_STEP < last; hi += (int)SPLITK_STEP) {
+    most = std::max(most, encoder_splitk(e, hi, hi - (int)SPLITK_STEP + 1));
+    e.splitk_bytes.push_back(most);
+  }
+}
 static void plan_encoder(const dp_encoder& e, void* base, int samples, EncBuf& b) {
   Plan p(base);
   const size_t R = (size_t)samples * e.d.seq, d = e.d.d_model, es = e.es;
   b.h = p.take(R * d * es); b.qkv = p.take(R * 3 * d * es); b.a = p.take(R * d * es); b.f = p.take(R * e.d.ff_inner * es);
   b.res = (float*)p.take(R * d * 4);
   // partial sums of the projections that are split along the contraction on small batches
-  const int Ri = (int)R, di = e.d.d_model, ff = e.d.ff_inner;
-  auto sk = [&](int N, int K) { return e.batch_invariant == 1 ? gemm_epi_splitk_ws_bytes_for(Ri, N, K, e.d.seq) : gemm_epi_splitk_ws_bytes(Ri, N, K); };
-  b.splitk_bytes = std::max(std::max(sk(3 * di, di), sk(di, di)), std::max(sk(ff, di), sk(di, ff)));
+  b.splitk_bytes = e.batch_invariant == 1 ? encoder_splitk(e, (int)R, e.d.seq) : (e.splitk_bytes.empty() ? 0 : e.splitk_bytes[std::min((R + SPLITK_STEP - 1) / SPLITK_STEP, e.splitk_bytes.size()) - 1]);
   b.splitk = b.splitk_bytes ? (float*)p.take(b.splitk_bytes) : nullptr;
   b.bytes = p.off;
 }
@@ -1091,6 +1110,8 @@ int dp_encoder_create(const dp_encoder_desc* desc, dp_encoder** out) {
     for (auto& sp : per) e->params.push_back({"layer" + std::to_string(l) + "." + sp.n, sp.r, sp.c});
   e->params.push_back({"lnf_g", dm, 0});
   e->params.push_back({"lnf_b", dm, 0});
+  try { plan_encoder_splitk(*e); }
+  catch (...) { delete e; return set_error(DP_EINVAL, "out of host memory"); }
   *out = e;
   return DP_OK;
 }

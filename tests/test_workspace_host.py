@@ -1,0 +1,23 @@
+"""Workspace sizes, on the host: a workspace sized for a number of samples serves every call of fewer."""
+import pytest
+
+from paper_2405_01248_amd import binding as B
+
+
+@pytest.mark.parametrize("width", [128, 256, 640, 768, 1024, 2048])
+@pytest.mark.parametrize("mode", [0, 1, 2])
+def test_text_encoder_workspace_grows_with_the_samples(width, mode):
+    enc = B.Encoder(B.DP_BF16, 2, width, width // 64, 64, 77, 1000, 4 * width)
+    enc.set_batch_invariant(mode)
+    sizes = [enc.workspace_bytes(n) for n in list(range(1, 129)) + [200, 500, 1000]]
+    assert all(a <= b for a, b in zip(sizes, sizes[1:]))
+
+
+def test_image_encoder_workspace_grows_with_the_samples():
+    from synth_inputs import vae_encoder_layers
+    layers = vae_encoder_layers(32, (1, 2, 4, 4), 8, 8)
+    for h, w in ((64, 64), (384, 328), (512, 512)):
+        enc = B.ImageEncoder(B.DP_BF16, h, w, 8, 32, layers)
+        for lo, hi in ((0, len(layers)), (len(layers) - 3, len(layers))):
+            sizes = [enc.workspace_bytes(lo, hi, n) for n in range(1, 40)]
+            assert all(a <= b for a, b in zip(sizes, sizes[1:]))
