@@ -122,3 +122,25 @@ def test_geglu_fusion_changes_no_bit_of_the_forward(batch, tokens, heads):
         torch.cuda.synchronize()
         y.append(ds.results()["y"])
     assert np.array_equal(y[0], y[1])
+
+
+@pytest.mark.parametrize("M,N,K,lda,ldb", [(5, 7, 1, 3, 5), (33, 34, 3, 0, 0), (65, 31, 130, 131, 133), (40, 41, 257, 0, 1), (64, 64, 64, 66, 0), (2097153, 4, 4, 0, 0)])
+@pytest.mark.parametrize("layout", ["nt", "nn", "tn"])
+def test_f32_gemm_of_any_size_and_stride(layout, M, N, K, lda, ldb):
+    # contractions and strides that are not multiples of 4; more row tiles than a grid's second dimension holds
+    import torch
+    from paper_2405_01248_amd import binding as B
+    a_k, b_k = {"nt": (0, 0), "nn": (0, 1), "tn": (1, 1)}[layout]
+    g = torch.Generator().manual_seed(M + K)
+    A, Bm = torch.randn(M, K, generator=g), torch.randn(K, N, generator=g)
+    stored = [A.T if a_k else A, Bm if b_k else Bm.T]
+    dev = []
+    for t, extra in zip(stored, (lda, ldb)):
+        buf = torch.full((t.shape[0], t.shape[1] + extra), float("nan"))      # what lies between the rows is not read
+        buf[:, :t.shape[1]] = t
+        dev.append(buf.cuda())
+    out = torch.zeros((M, N), device="cuda")
+    B.op_gemm(B.DP_F32, dev[0], dev[0].shape[1], a_k, dev[1], dev[1].shape[1], b_k, M, N, K, None, out, N, layout == "tn")
+    torch.cuda.synchronize()
+    ref = A.double() @ Bm.double()
+    assert float((out.cpu().double() - ref).abs().max() / ref.abs().max()) <= 1e-5
