@@ -294,12 +294,12 @@ __global__ void __launch_bounds__(256, 2) ln_bwd_kernel(int d, int rows_per_batc
 #pragma unroll
     for (int k = 0; k < R; ++k) {
       s1[k] = 0.f; s2[k] = 0.f;
-      const float live = r0 + k < r_end ? 1.f : 0.f;
+      const bool live = r0 + k < r_end;      // a row past the last one is the last one again: taken out by choice, since 0 times an infinity is NaN
       if (on) {
 #pragma unroll
         for (int i = 0; i < V; ++i) {
-          const float dyv = to_f<T>(dyr[k][i]) * live;
-          xh[k][i] = (xh[k][i] - mu[k]) * rs[k];
+          const float dyv = live ? to_f<T>(dyr[k][i]) : 0.f;
+          xh[k][i] = live ? (xh[k][i] - mu[k]) * rs[k] : 0.f;
           gsum[i] += dyv * xh[k][i];
           bsum[i] += dyv;
           g[k][i] = dyv * gain[i];

@@ -144,3 +144,28 @@ def test_f32_gemm_of_any_size_and_stride(layout, M, N, K, lda, ldb):
     torch.cuda.synchronize()
     ref = A.double() @ Bm.double()
     assert float((out.cpu().double() - ref).abs().max() / ref.abs().max()) <= 1e-5
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("tokens", [4, 5])
+def test_layer_norm_backward_with_an_infinite_gradient(dtype, tokens):
+    """Weights that are zero but for one path carry the last row's gradient to the feed-forward's LayerNorm, where its first column overflows:
+    that column's shift gradient is infinite, not NaN, and no other column's is touched, with an odd number of rows as with an even one."""
+    import numpy as np
+    import torch
+    import synth_inputs as si
+    from paper_2405_01248_amd.harness import DeviceStage
+    cfg = si.StageConfig("overflow", si.UNET, dtype, 1, 1, tokens, 64, 1, 64, 3, 8, 64)
+    inp = si.make_stage_inputs(cfg, seed=tokens)
+    p = inp["params"]
+    for k in ("ff_w1", "ff_b1", "ff_w2"):
+        p["block0." + k] = np.zeros_like(p["block0." + k])
+    p["block0.ff_w2"][0, 0] = 1.0
+    p["block0.ff_b1"][64] = 8.0                # gate of the first hidden column: gelu(8) = 8, gelu'(8) = 1
+    p["block0.ff_w1"][0, 0] = 4.0
+    inp["dy"][0, -1, 0] = 2.0 ** 124           # times 8, times 4: 2^129
+    ds = DeviceStage(cfg, inp)
+    ds.step()
+    torch.cuda.synchronize()
+    g = ds.results()["grads"]["block0.ln3_b"]
+    assert g[0] == np.inf and np.isfinite(g[1:]).all(), g[:4]
