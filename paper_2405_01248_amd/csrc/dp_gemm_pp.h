@@ -221,6 +221,14 @@ __device__ __forceinline__ void pp_main_loop(typename T::acc_t (&acc)[2][T::TM][
   wait_vmcnt<2 * LA + LB0 + 2 * LB1>();        // the first B0 and A0 are there
   barrier_nofence();
   fetch_b(0, H0);
+  if constexpr (MC) {
+    // the transposing loads are not in the compiler's books: a register it copies on the way into the loop has to hold its value by then
+    wait_lgkmcnt0();
+#pragma unroll
+    for (int j = 0; j < TN0; ++j)
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) { lds_arrived(rb[0][j][ks][0]); lds_arrived(rb[0][j][ks][1]); }
+  }
   if (trailing) barrier_nofence();
   for (int t = 0; t < nk; ++t) {
     const int st = t & 1;

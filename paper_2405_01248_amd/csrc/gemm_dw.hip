@@ -74,7 +74,8 @@ __global__ void __launch_bounds__(512, 2) gemm_dw_group_kernel(const DwGroup grp
     vb1[j] = 2u * ((uint32_t)(kt0 * 64 + k) * ldb + min(n0 + T::BN0 + c * 8, N - 8));
   }
   const bool ragged = k_end < nk * 64;
-  auto tail = [&](uint32_t v, int k, int t) { return ragged && t == nk - 1 && t * 64 + k >= k_end ? OUTSIDE : v; };
+  // (without a branch: the transposing loads of the other operand are outstanding)
+  auto tail = [&](uint32_t v, int k, int t) { return ((int)ragged & (int)(t == nk - 1) & (int)(t * 64 + k >= k_end)) ? OUTSIDE : v; };
   const bool do_colsum = p.colsum != nullptr && tile_n == 0 && wn == 0;
   typename T::acc_t acc[2][T::TM][T::TN];
   float csum[2][T::TM];
