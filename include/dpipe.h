@@ -167,11 +167,12 @@ typedef struct {
 /* Times every block's forward and backward (reps >= 1 repetitions each, hipEvents on the
  * stream; this call synchronises).  Same buffers as stage_fwd / stage_bwd; dparams are
  * overwritten.  Writes n_blocks rows.  The passes run as stage_fwd / stage_bwd run them, side stream included
- * (dp_stage_set_overlap), but the caller's stream waits for a block's side-stream work before the next block's
- * time stamp: a block's weight-gradient kernels are charged to that block, and sum_l (P^f_l + P^b_l) is the
- * time of the step up to what the per-block joins cost (Eq. 3 adds layer times up).  Two things are charged
- * to a neighbour: the context K/V projections of all U-Net blocks (issued at the start of the forward, in
- * block 0's span) and a block's weight transposes (issued one block ahead in the backward). */
+ * (dp_stage_set_overlap) and kernel for kernel, but the caller's stream waits for a block's side-stream work before the
+ * next block's time stamp: a block's weight-gradient kernels are charged to that block, and sum_l (P^f_l + P^b_l) is the
+ * time of the step up to what the per-block joins cost (Eq. 3 adds layer times up).  What a pass does for all its blocks
+ * together is shared out equally: the modulation vectors and the conditioning gradient of DiT blocks, the backward's
+ * weight transposes.  One thing is charged to a neighbour: the context K/V projections of all U-Net blocks where the
+ * side stream runs them (in block 0's span). */
 int dp_stage_profile(dp_stage* st, const void* const* params, const void* x, const void* ctx_or_cond, void* y,
                      const void* dy, void* dx, void* d_cond, void* const* dparams, void* workspace,
                      size_t workspace_bytes, int reps, dp_layer_cost* rows, int max_rows, int* n_rows,

@@ -79,12 +79,10 @@ bool gemm_dw_group_supported(const GemmArgs& a);
 // a.B, a.bias and a.out are not used.
 constexpr int GEMM_BATCH_MAX = 16;
 struct GemmBatch { int n; const void* B[GEMM_BATCH_MAX]; const void* bias[GEMM_BATCH_MAX]; void* out[GEMM_BATCH_MAX]; };
-// Gradient of a stage's conditioning vectors: parts of sum_b dm_b [batch, 6 d] W_b [6 d, d] for the given blocks, appended to ws after the *parts
-// there already; then d_cond = SiLU'(cond) * their sum.
+// Gradient of a stage's conditioning vectors: d_cond = SiLU'(cond) * sum over the blocks of dm_b [batch, 6 d] W_b [6 d, d].
 bool cond_grad_supported(int dtype, int batch, int d);
-size_t cond_grad_ws_bytes(int blocks, int batch, int d);      // for all blocks at once or one by one
-int launch_cond_grad(const void* const* dm, const void* const* w, int blocks, int batch, int d, float* ws, int* parts, hipStream_t s);
-int launch_cond_grad_finish(const float* ws, int parts, const void* cond, float* d_cond, int batch, int d, hipStream_t s);
+size_t cond_grad_ws_bytes(int blocks, int batch, int d);
+int launch_cond_grad(const void* const* dm, const void* const* w, int blocks, int batch, int d, float* ws, const void* cond, float* d_cond, hipStream_t s);
 bool gemm_few_rows_supported(const GemmArgs& a);
 int launch_gemm_few_rows(const GemmArgs& a, const GemmBatch& batch, hipStream_t s);
 bool gemm_geglu_fwd_supported(const GemmArgs& a);

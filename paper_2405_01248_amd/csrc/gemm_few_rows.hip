@@ -266,9 +266,10 @@ static int cond_grad_parts(int blocks, int d) {
 size_t cond_grad_ws_bytes(int blocks, int batch, int d) {
   size_t parts = 0;
   for (int b = 0; b < blocks; b += GEMM_BATCH_MAX) parts += cond_grad_parts(std::min(blocks - b, GEMM_BATCH_MAX), d);
-  return std::max(parts, (size_t)blocks * cond_grad_parts(1, d)) * batch * d * sizeof(float);
+  return parts * batch * d * sizeof(float);
 }
-int launch_cond_grad(const void* const* dm, const void* const* w, int blocks, int batch, int d, float* ws, int* parts, hipStream_t s) {
+int launch_cond_grad(const void* const* dm, const void* const* w, int blocks, int batch, int d, float* ws, const void* cond, float* d_cond, hipStream_t s) {
+  int parts = 0;
   if (!dm || !w || !ws || blocks < 1 || batch < 1 || !cond_grad_supported(BF16, batch, d)) return set_error(DP_EINVAL, "cond_grad: bad arguments");
   for (int b0 = 0; b0 < blocks; b0 += GEMM_BATCH_MAX) {
     CondGradParams p;
@@ -278,17 +279,15 @@ int launch_cond_grad(const void* const* dm, const void* const* w, int blocks, in
     const int np = cond_grad_parts(n, d);
     p.tiles_per_part = (p.tiles + np - 1) / np;
     for (int i = 0; i < n; ++i) { p.A[i] = (const bf16*)dm[b0 + i]; p.B[i] = (const bf16*)w[b0 + i]; }
-    p.partial = ws + (size_t)*parts * batch * d;
-    *parts += np;
+    p.partial = ws + (size_t)parts * batch * d;
+    parts += np;
     KScope ks(KK_GEMM_NN, 2.0 * batch * d * 6.0 * d * n, n * 2.0 * (6.0 * d * d + 6.0 * batch * d) + 4.0 * np * batch * d, s, batch, d, 6 * d * n);
     const dim3 grid((d + 127) / 128, np);
     if (batch <= 32) hipLaunchKernelGGL(cond_grad_kernel<1>, grid, dim3(256), 0, s, p);
     else hipLaunchKernelGGL(cond_grad_kernel<2>, grid, dim3(256), 0, s, p);
   }
-  return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "cond_grad launch failed");
-}
-int launch_cond_grad_finish(const float* ws, int parts, const void* cond, float* d_cond, int batch, int d, hipStream_t s) {
   const int n = batch * d;
+  KScope ks(KK_OTHER, 0.0, 4.0 * (parts + 1.0) * n + 2.0 * n, s, batch, d, parts);
   hipLaunchKernelGGL(cond_grad_finish_kernel, dim3((n + 127) / 128), dim3(256), 0, s, ws, parts, (const bf16*)cond, d_cond, n);
   return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "cond_grad launch failed");
 }

@@ -16,7 +16,8 @@
 
 namespace dp {
 
-struct ProfileHooks {            // optional per-block event recording
+// Optional event recording: entries 0 .. blocks at the blocks' boundaries, then the start and (backward) the end of the pass.
+struct ProfileHooks {
   std::vector<hipEvent_t>* ev = nullptr;
 };
 
@@ -687,7 +688,7 @@ static int run_stage_fwd(dp_stage* s, const void* const* params, const void* x, 
   const SplitK sk{sp.splitk, sp.splitk_bytes};
   const bool unet = s->d.kind == DP_BLOCK_UNET_XATTN_GEGLU;
   const int nb = s->d.n_blocks;
-  const size_t act = (size_t)s->T * s->d.d_model;
+  DP_TRY(record(ph, nb + 1, st));
   if (!unet) DP_TRY(launch_silu(s->d.dtype, cc, sp.sc_in, (size_t)s->d.batch * s->d.d_model, st));
   // the residual stream runs in fp32 inside the stage: widen the stage input once
   float* cur = (float*)(save ? (unet ? sp.ub[0].xin : sp.db[0].xin) : sp.pp2);
@@ -707,9 +708,9 @@ static int run_stage_fwd(dp_stage* s, const void* const* params, const void* x, 
     kv_batch = sd.end();
   }
   // DiT: the modulation vectors m = SiLU(cond) W_ada^T + b_ada of all blocks are as many rows as the batch has samples: one launch
-  // reads the blocks' weights together (not while profiling, where each block's row has to hold its own projection)
+  // reads the blocks' weights together
   bool mods = false;
-  if (!unet && !ph) {
+  if (!unet) {
     GemmArgs g = gemm_fwd(s->d.dtype, sp.sc_in, s->d.batch, s->d.d_model, nullptr, 6 * s->d.d_model, nullptr, nullptr);
     mods = gemm_few_rows_supported(g);
     for (int b0 = 0; mods && b0 < nb; b0 += GEMM_BATCH_MAX) {
@@ -759,6 +760,7 @@ static int run_stage_bwd(dp_stage* s, const void* const* params, const void* dy,
     DP_TRY(ensure_side_stream(s));
     sd.side = s->side; sd.ev = &s->events;
   }
+  DP_TRY(record(ph, nb + 1, st));
   // Transposed weight copies of all blocks, in one launch (a few for a long stage).
   std::vector<const void*> wt_ptrs((size_t)nb * s->per_block, nullptr);
   if (bs.wt) {
@@ -782,7 +784,6 @@ static int run_stage_bwd(dp_stage* s, const void* const* params, const void* dy,
   GradPair cur{s->es == 4 ? (float*)const_cast<void*>(dy) : (unet ? nullptr : bs.f[1]), const_cast<void*>(dy)};
   int ci = 1;   // index of the fp32 buffer that holds cur
   std::vector<const void*> dm(nb), w_ada(nb);
-  int cond_parts = 0;
   int batch[2] = {0, 0};      // last side batch that reads each of the two buffer sets
   for (int i = 0; i < nb; ++i) {
     const int b = nb - 1 - i;
@@ -803,17 +804,16 @@ static int run_stage_bwd(dp_stage* s, const void* const* params, const void* dy,
       DP_TRY(dit_block_bwd(*s, i == 0, P, WT, G, acc, cc, sp.sc_in, i == 0 ? cur.f : bs.f[ci], ci, dx_final, (float*)d_cond, i != 0, const_cast<void*>(dm[b]), sp.db[b],
                            b ? &sp.db[b - 1] : nullptr, bs, bs.set[i & 1], bs.set[(i + 1) & 1], sk, sd, &batch[i & 1], batch[(i + 1) & 1]));
     }
-    // d cond of this block where blocks are timed one by one, else of all blocks after the last
-    if (bs.cond_ws && (ph ? true : b == 0)) {
-      hipStream_t q = sd.begin();
-      DP_TRY(launch_cond_grad(&dm[b], &w_ada[b], ph ? 1 : nb, s->d.batch, s->d.d_model, bs.cond_ws, &cond_parts, q));
-      if (b == 0) DP_TRY(launch_cond_grad_finish(bs.cond_ws, cond_parts, cc, (float*)d_cond, s->d.batch, s->d.d_model, q));
-      sd.end();
-    }
     if (ph && ph->ev) sd.wait(sd.issued);      // per-block timing: charge a block's side work to that block
   }
-  sd.wait(sd.issued);                          // join: everything is ordered before later work on the caller's stream
   DP_TRY(record(ph, nb, st));
+  if (bs.cond_ws) {      // DiT: d cond from all blocks together
+    hipStream_t q = sd.begin();
+    DP_TRY(launch_cond_grad(dm.data(), w_ada.data(), nb, s->d.batch, s->d.d_model, bs.cond_ws, cc, (float*)d_cond, q));
+    sd.end();
+  }
+  sd.wait(sd.issued);                          // join: everything is ordered before later work on the caller's stream
+  DP_TRY(record(ph, nb + 2, st));
   return sd.err;
 }
 
@@ -1155,7 +1155,7 @@ int dp_stage_profile(dp_stage* st, const void* const* params, const void* x, con
   if (reps < 1 || max_rows < nb) return set_error(DP_EINVAL, "dp_stage_profile: reps < 1 or too few rows");
   hipStream_t s = (hipStream_t)hip_stream;
   EventSet esf, esb;
-  DP_TRY(esf.create(nb + 1)); DP_TRY(esb.create(nb + 1));
+  DP_TRY(esf.create(nb + 3)); DP_TRY(esb.create(nb + 3));
   std::vector<hipEvent_t>& ef = esf.ev;
   std::vector<hipEvent_t>& eb = esb.ev;
   std::vector<std::vector<float>> tf(nb), tb(nb);
@@ -1166,13 +1166,16 @@ int dp_stage_profile(dp_stage* st, const void* const* params, const void* x, con
     rc = run_stage_fwd(st, params, x, ctx_or_cond, y, workspace, 1, s, &hf);
     if (rc == DP_OK) rc = run_stage_bwd(st, params, dy, ctx_or_cond, dx, d_cond, dparams, 0, workspace, s, &hb);
     if (rc == DP_OK && hipStreamSynchronize(s) != hipSuccess) rc = set_error(DP_EHIP, "hipStreamSynchronize failed");
+    auto ms = [&](const std::vector<hipEvent_t>& e, int from, int to) {
+      float v = 0.f;
+      if (rc == DP_OK && hipEventElapsedTime(&v, e[from], e[to]) != hipSuccess) rc = set_error(DP_EHIP, "hipEventElapsedTime failed");
+      return v;
+    };
+    // what is done for all blocks together, before the first and after the last of them, goes to each in equal parts
+    const float f_all = ms(ef, nb + 1, 0) / (float)nb, b_all = (ms(eb, nb + 1, 0) + ms(eb, nb, nb + 2)) / (float)nb;
     for (int b = 0; b < nb && rc == DP_OK; ++b) {
-      float ms = 0.f;
-      if (hipEventElapsedTime(&ms, ef[b], ef[b + 1]) != hipSuccess) rc = set_error(DP_EHIP, "hipEventElapsedTime failed");
-      tf[b].push_back(ms);
-      // backward runs blocks in reverse: event i brackets block nb-1-i
-      if (rc == DP_OK && hipEventElapsedTime(&ms, eb[nb - 1 - b], eb[nb - b]) != hipSuccess) rc = set_error(DP_EHIP, "hipEventElapsedTime failed");
-      tb[b].push_back(ms);
+      tf[b].push_back(ms(ef, b, b + 1) + f_all);
+      tb[b].push_back(ms(eb, nb - 1 - b, nb - b) + b_all);      // backward runs blocks in reverse: event i brackets block nb-1-i
     }
   }
   if (rc != DP_OK) return rc;

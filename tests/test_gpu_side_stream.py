@@ -39,3 +39,19 @@ def test_overlap_and_saving_change_no_bit(cfg):
 
 def test_five_blocks_in_a_graph():
     capture_and_replay(FIVE_UNET)
+
+
+@pytest.mark.parametrize("cfg", [FIVE_UNET, FIVE_DIT, FIVE_DIT.replace(name="two_dit_bf16", n_blocks=2), FIVE_DIT.replace(name="dit_batch49", batch=49, tokens=5)],
+                         ids=lambda c: c.name)
+def test_profile_times_the_kernels_of_the_step(cfg):
+    import torch
+    from paper_2405_01248_amd import binding as B
+    ds, _ = _run(cfg)
+    launches = []
+    for run in (lambda: ds.step(self_cond=False),
+                lambda: ds.stage.profile(ds.params, ds.x, ds.cc, ds.y, ds.dy, ds.dx, ds.d_cond, ds.dparams, ds.ws, reps=1)):
+        B.ktime_begin(4096)
+        run()
+        torch.cuda.synchronize()
+        launches.append(sorted((r["kind"], r["m"], r["n"], r["k"]) for r in B.ktime_end(4096)))
+    assert launches[0] == launches[1]
