@@ -967,11 +967,13 @@ static float tile128_us(long tiles, int kt, bool heavy) {
 // The pass that adds z partial results; ln: and does the LayerNorm that would otherwise be a launch of its own.
 static float reduce_us(int rows, int N, int z, bool ln) { return (ln ? 0.5f : 5.0f) + (float)(z + 2) * (float)rows * (float)N * 1.5e-6f; }
 
+static bool heavy_epilogue(const GemmArgs& a) { return a.act || a.dact_pre || a.geglu; }
+
 // Split-K factor of a storage-dtype GEMM on 128x128 tiles (configuration 13) and its estimated time in us: rounds of 256
 // workgroups plus, where it is split, a second launch and the partial sums' traffic.  A stage on a small local batch (1024 rows,
 // 72 tiles, contractions of 3456 or 4608) spends 28-36 us in one of these projections unsplit, 22-27 us split by 3.  ln: the
 // second launch also does the LayerNorm that would otherwise be one of its own.
-static int splits_128(int rows, int N, int K, bool ln, float* us, bool heavy = false) {
+static int splits_128(int rows, int N, int K, bool ln, bool heavy, float* us) {
   const long tiles = (long)((rows + 127) / 128) * ((N + 127) / 128);
   const int kt = K / 64;
   int best = 1;
@@ -1012,7 +1014,9 @@ static float wave_us(const WaveCost& c, int rows, int N, int K, bool may_split, 
 // The same when the choice is made for `choice_rows` rows (GemmArgs::choice_rows) but M rows are computed.
 size_t gemm_epi_splitk_ws_bytes_for(int M, int N, int K, int choice_rows) {
   float us;
-  int sp = std::max(1, std::max(splits_128(choice_rows, N, K, false, &us), splits_128(choice_rows, N, K, true, &us)));
+  int sp = 1;
+  for (const bool ln : {false, true})
+    for (const bool heavy : {false, true}) sp = std::max(sp, splits_128(choice_rows, N, K, ln, heavy, &us));
   for (const WaveCost& c : kWave)
     for (const bool ln : {false, true}) {
       int w;
@@ -1081,7 +1085,7 @@ static int choose_cfg(int M, int N, int K, bool a_mc, bool b_mc, bool dtl_ok, bo
       float cost = (float)((tiles + kCUs - 1) / kCUs) * (c.fixed + (float)((K + 63) / 64) * c.per_kt);
       if (c.idx == 13) {
         cost = tile128_us(tiles, K / 64, heavy);
-        if (may_split) splits_128(M, N, K, ln, &cost, heavy);
+        if (may_split) splits_128(M, N, K, ln, heavy, &cost);
       }
       consider(c.idx, cost);
     }
@@ -1247,7 +1251,7 @@ static int launch_dtl_cfg(const GemmArgs& a, hipStream_t s) {
     const long rows_for_choice = a.choice_rows > 0 ? a.choice_rows : a.M;
     float us;
     splits = a.choice_rows < 0 ? 1 : choose_splits_epi(((rows_for_choice + BM - 1) / BM) * p.tiles_n, kt * BK / 64);
-    if (a.choice_rows >= 0 && BM == 128 && BN == 128 && BK == 64) splits = splits_128((int)rows_for_choice, a.N, a.K, a.ln_out != nullptr, &us);
+    if (a.choice_rows >= 0 && BM == 128 && BN == 128 && BK == 64) splits = splits_128((int)rows_for_choice, a.N, a.K, a.ln_out != nullptr, heavy_epilogue(a), &us);
   }
   static std::atomic<bool> attr_set{false};
   return launch_split(a, p, gemm_bf16_dtl_kernel<BM, BN, BK, STAGES, WGM, WGN, A_MC, B_MC>, WGM * WGN * 64, S::BYTES, attr_set, kt, splits, s);
@@ -1510,7 +1514,7 @@ static int chosen_cfg(const GemmArgs& a, int rows, bool may_split) {
   struct Entry { int rows, n, k, flags, cfg; };
   constexpr int ENTRIES = 64;
   static thread_local Entry table[ENTRIES] = {};        // n = 0: empty
-  const bool pp = !a.out_f32 && pp_kind(a) >= 0, any_order = a.choice_rows == 0, wave = any_order && !a.out_f32 && a.geglu != 1, dtl = dtl_addressable(a), heavy = a.act || a.dact_pre || a.geglu;
+  const bool pp = !a.out_f32 && pp_kind(a) >= 0, any_order = a.choice_rows == 0, wave = any_order && !a.out_f32 && a.geglu != 1, dtl = dtl_addressable(a), heavy = heavy_epilogue(a);
   const int flags = heavy << 8 | (a.a_mc != 0) | (a.b_mc != 0) << 1 | dtl << 2 | pp << 3 | any_order << 4 | may_split << 5 | (a.ln_out != nullptr) << 6 | wave << 7;
   Entry& e = table[((unsigned)rows * 0x9E3779B1u ^ (unsigned)a.N * 0x85EBCA77u ^ (unsigned)a.K * 0xC2B2AE3Du ^ (unsigned)flags * 0x27D4EB2Fu) >> 26];
   if (e.n == a.N && e.rows == rows && e.k == a.K && e.flags == flags) return e.cfg;
@@ -1528,7 +1532,7 @@ static int launch_invariant(const GemmArgs& a, bool may_split, hipStream_t s) {
   int z = 1;
   if (may_split && (cfg == 13 || cfg == 15)) {
     float us;
-    z = cfg == 13 ? splits_128(a.choice_rows, a.N, a.K, a.ln_out != nullptr, &us) : choose_splits_epi((long)((a.choice_rows + 63) / 64) * ((a.N + 63) / 64), kt);
+    z = cfg == 13 ? splits_128(a.choice_rows, a.N, a.K, a.ln_out != nullptr, heavy_epilogue(a), &us) : choose_splits_epi((long)((a.choice_rows + 63) / 64) * ((a.N + 63) / 64), kt);
   } else if (may_split && cfg >= 6 && cfg <= 16) {
     g.force_cfg = cfg + 1;       // another kind of tile with a split of its own
     return launch_gemm(g, s);
