@@ -1054,7 +1054,7 @@ int gemm_epi_split_rows(int N, int K) {
 //    direct-to-LDS tiles when they fill the CUs, else the register-staged kernel;
 //  - dW = dy^T x (both operands read through the transposing LDS load): register-staged 128x128 tiles,
 //    two workgroups per CU; 256x256 direct-to-LDS tiles for large M and N.
-static int choose_cfg(int M, int N, int K, bool a_mc, bool b_mc, bool dtl_ok, bool pp_ok, bool allow16 = true, bool may_split = false, bool ln = false, bool wave_ok = false, bool heavy = false) {
+static int choose_cfg(int M, int N, int K, bool a_mc, bool b_mc, bool dtl_ok, bool pp_ok, bool allow16 = true, bool may_split = false, bool ln = false, bool wave_ok = false, bool heavy = false, bool geglu_fwd = false) {
   const long t256x256 = (long)((M + 255) / 256) * ((N + 255) / 256);
   const long t256x128 = (long)((M + 255) / 256) * ((N + 127) / 128);
   const bool dtl32 = dtl_ok && K % 32 == 0, dtl64 = dtl_ok && K % 64 == 0;
@@ -1066,11 +1066,13 @@ static int choose_cfg(int M, int N, int K, bool a_mc, bool b_mc, bool dtl_ok, bo
     // 4x the workgroups of 128x128 ones, each with a quarter of the work per k-tile, and no split-K pass is needed.
     // Measured on the text encoder (samples/s at slices of 1 / 4 / 16): 1538 / 5617 / 19148 -> 1733 / 6490 / 20040; with more
     // 128x128 tiles than the limits below the larger tiles win again (16 samples, K = 3072: -6 % with 64x64 tiles).
-    if (dtl64 && !allow16 && (long)((M + 127) / 128) * ((N + 127) / 128) <= (K <= 1024 ? 100 : 24)) return 15;
+    if (dtl64 && !allow16 && !geglu_fwd && (long)((M + 127) / 128) * ((N + 127) / 128) <= (K <= 1024 ? 100 : 24)) return 15;
     // Otherwise the tile with the least estimated time: rounds over the 256 CUs x (fixed part of a tile + k-tiles x time of
     // one), both in us, fitted on MI355X over projections of 1024..32768 rows, 320..5120 columns, contractions of
     // 320..5120.  The alternating-group tiles hold one workgroup per CU; which of their widths wins is mostly a matter of how
     // full the last round is (8192 x 4608: 576 tiles of 256x256 are 2.25 rounds, 768 of 256x192 exactly 3 shorter ones).
+    // The fused GeGLU forward is chosen among the tiles that have it (100 x 9216 on 128x128 tiles of eight waves instead of four 19.4 -> 15.7 us,
+    // 2052 x 7680 on 256x128 ones instead of 256x256 62.0 -> 59.5, 4050 x 6144 the same way 58.6 -> 60).
     struct Cand { int idx, bm, bn; float fixed, per_kt; bool pp, need64; };
     static const Cand cands[] = {{17, 256, 256, 5.0f, 1.30f, true, false}, {19, 256, 192, 5.0f, 1.05f, true, false}, {20, 256, 160, 5.5f, 0.99f, true, false},
                                  {18, 256, 128, 5.0f, 0.72f, true, false}, {13, 128, 128, 0.f, 0.f, false, true}, {8, 128, 128, 5.0f, 0.75f, false, false},
@@ -1080,6 +1082,7 @@ static int choose_cfg(int M, int N, int K, bool a_mc, bool b_mc, bool dtl_ok, bo
     auto consider = [&](int idx, float cost) { if (best < 0 || cost < best_cost) { best = idx; best_cost = cost; } };
     for (const Cand& c : cands) {
       if (c.pp ? !pp_ok : (c.need64 ? !dtl64 : !dtl32)) continue;
+      if (geglu_fwd && (c.idx == 19 || c.idx == 20)) continue;      // its column permutation wants equal column halves, and the direct-to-LDS loaders
       if (c.idx == 20 && !allow16) continue;       // the 16x16x32 instruction sums a k-step of 32 at once: other bits than the 32x32x16 tiles
       const long tiles = (long)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
       float cost = (float)((tiles + kCUs - 1) / kCUs) * (c.fixed + (float)((K + 63) / 64) * c.per_kt);
@@ -1089,7 +1092,7 @@ static int choose_cfg(int M, int N, int K, bool a_mc, bool b_mc, bool dtl_ok, bo
       }
       consider(c.idx, cost);
     }
-    if (dtl64) {
+    if (dtl64 && !geglu_fwd) {
       const long tiles = (long)((M + 63) / 64) * ((N + 63) / 64);
       const int z = may_split ? choose_splits_epi(tiles, K / 64) : 1;
       consider(15, tile64_us(tiles, K / 64, z) + (z > 1 ? reduce_us(M, N, z, ln) : 0.f));
@@ -1514,11 +1517,11 @@ static int chosen_cfg(const GemmArgs& a, int rows, bool may_split) {
   struct Entry { int rows, n, k, flags, cfg; };
   constexpr int ENTRIES = 64;
   static thread_local Entry table[ENTRIES] = {};        // n = 0: empty
-  const bool pp = !a.out_f32 && pp_kind(a) >= 0, any_order = a.choice_rows == 0, wave = any_order && !a.out_f32 && a.geglu != 1, dtl = dtl_addressable(a), heavy = heavy_epilogue(a);
-  const int flags = heavy << 8 | (a.a_mc != 0) | (a.b_mc != 0) << 1 | dtl << 2 | pp << 3 | any_order << 4 | may_split << 5 | (a.ln_out != nullptr) << 6 | wave << 7;
+  const bool pp = !a.out_f32 && pp_kind(a) >= 0, any_order = a.choice_rows == 0, wave = any_order && !a.out_f32 && a.geglu != 1, dtl = dtl_addressable(a), heavy = heavy_epilogue(a), geglu_fwd = a.geglu == 1;
+  const int flags = geglu_fwd << 9 | heavy << 8 | (a.a_mc != 0) | (a.b_mc != 0) << 1 | dtl << 2 | pp << 3 | any_order << 4 | may_split << 5 | (a.ln_out != nullptr) << 6 | wave << 7;
   Entry& e = table[((unsigned)rows * 0x9E3779B1u ^ (unsigned)a.N * 0x85EBCA77u ^ (unsigned)a.K * 0xC2B2AE3Du ^ (unsigned)flags * 0x27D4EB2Fu) >> 26];
   if (e.n == a.N && e.rows == rows && e.k == a.K && e.flags == flags) return e.cfg;
-  e = Entry{rows, a.N, a.K, flags, choose_cfg(rows, a.N, a.K, a.a_mc != 0, a.b_mc != 0, dtl, pp, any_order, may_split, a.ln_out != nullptr, wave, heavy)};
+  e = Entry{rows, a.N, a.K, flags, choose_cfg(rows, a.N, a.K, a.a_mc != 0, a.b_mc != 0, dtl, pp, any_order, may_split, a.ln_out != nullptr, wave, heavy, geglu_fwd)};
   return e.cfg;
 }
 
@@ -1589,11 +1592,7 @@ int launch_gemm(const GemmArgs& a, hipStream_t s) {
     const bool forced = a.force_cfg > 0 && a.force_cfg <= kNumCfgs + 23;
     if (a.choice_rows > 0 && !forced && !a.a_mc && !a.b_mc) return launch_invariant(a, may_split, s);
     int cfg = forced ? a.force_cfg - 1 : chosen_cfg(a, a.M, may_split);
-    // the column permutation of the fused GeGLU lives in the direct-to-LDS loaders, and in tiles with equal column halves
-    if (a.geglu == 1 && (cfg < 6 || cfg == 11 || cfg == 15 || cfg == 16 || cfg > 18)) {
-      const long t256x256 = (long)((a.M + 255) / 256) * ((a.N + 255) / 256);
-      cfg = t256x256 >= 128 ? 17 : 8;
-    }
+    if (a.geglu == 1 && (cfg < 6 || cfg == 11 || cfg == 15 || cfg == 16 || cfg > 18)) return set_error(DP_EUNSUPPORTED, "gemm: the forced configuration does not have the fused GeGLU forward");
     switch (cfg) {
       case 1: return launch_bf16_layout<256, 128, 64, 4, 2>(a, s);
       case 2: return launch_bf16_layout<256, 256, 64, 2, 4>(a, s);

@@ -105,9 +105,10 @@ def test_dit_backward_by_width(heads, d_head, batch, tokens, blocks):
             assert rel_err(got["grads"][name], grads[name]) <= TOL_BF16, name
 
 
-@pytest.mark.parametrize("batch,tokens,heads", [(2, 77, 8), (1, 77, 20), (2, 1024, 10)])
+@pytest.mark.parametrize("batch,tokens,heads", [(2, 77, 8), (1, 77, 20), (2, 1024, 10), (4, 513, 4), (1, 513, 25)])
 def test_geglu_fusion_changes_no_bit_of_the_forward(batch, tokens, heads):
-    # sizes at which a plain projection takes tiles whose waves share the contraction, or 16x16 instructions: another order of additions
+    # sizes at which a plain projection takes tiles whose waves share the contraction, or 16x16 instructions: another order of additions; the
+    # fused one 128x128, 256x256 and 256x128 tiles
     import numpy as np
     import torch
     import synth_inputs as si
