@@ -262,7 +262,7 @@ __device__ __forceinline__ void pp_main_loop(typename T::acc_t (&acc)[2][T::TM][
 // One kernel per kind: what a kind does not use is not compiled into it, so the loops can be unrolled and all
 // global operands of a 32-row slab (residual, saved pre-activation, gate) are requested before the first of them is
 // needed; in the rolled, all-purpose epilogue each 8-column group waits for its own operands in turn.
-enum PpEpi { PE_PLAIN = 0, PE_F32, PE_RES, PE_RESH, PE_GATE, PE_ACT1, PE_ACT2, PE_ACT3, PE_DACT1, PE_DACT2, PE_GEGLU1, PE_GEGLU2, PE_COUNT };
+enum PpEpi { PE_PLAIN = 0, PE_F32, PE_RES, PE_RESH, PE_GATE, PE_ACT1, PE_ACT2, PE_ACT3, PE_DACT1, PE_DACT2, PE_GEGLU1, PE_GEGLU2 };
 
 template <int KIND> struct PpIn { f32x4 r0, r1; bf16x8 a, b; };
 
