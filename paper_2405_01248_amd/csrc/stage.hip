@@ -79,6 +79,7 @@ struct DitBuf {
   void *xin, *m, *h1, *qkv, *a, *o, *x1, *h2, *f1, *f, *f2;
   float *mean1, *rstd1, *lse, *mean2, *rstd2;
 };
+constexpr int SIDE_MIN_BLOCKS = 3;      // stages that use the side stream: see use_side_stream
 // A residual-stream gradient lives twice: fp32 (f) for the running sum and in the storage dtype (h) as a GEMM
 // operand (U-Net only).  For fp32 storage both point at the same buffer.
 struct GradPair { float* f; void* h; };
@@ -199,9 +200,13 @@ static void plan_bwd_scratch(Plan& p, const dp_stage& s, BwdScratch& b) {
   b.ln_partial_bytes = ln_bwd_partial_bytes((int)T, (int)d, unet ? (int)T : s.d.tokens);
   for (int i = 0; i < 2; ++i) {
     BwdSet& t = b.set[i];
-    if (i && (s.d.n_blocks == 1 || es == 4)) {
+    if (i && (s.d.n_blocks < SIDE_MIN_BLOCKS || es == 4)) {
+      // one stream: a block's work is done before the next block's begins, but for what a DiT block prepares for the one after it
       t = b.set[0];
-      if (!unet && s.d.n_blocks > 1) t.ln_partial[2] = (float*)p.take(b.ln_partial_bytes);      // written for the next block before this one's are summed
+      if (!unet && s.d.n_blocks > 1) {
+        t.ln_partial[2] = (float*)p.take(b.ln_partial_bytes);
+        if (es == 2) t.dg = p.take(T * d * es);      // (fp32: used up by then)
+      }
       continue;
     }
     t.dqkv = p.take(T * 3 * d * es);
@@ -227,8 +232,6 @@ static void plan_bwd_scratch(Plan& p, const dp_stage& s, BwdScratch& b) {
   b.partial_bytes = partial_need(s);
   b.partial = (float*)p.take(b.partial_bytes);
 }
-
-constexpr int SIDE_MIN_BLOCKS = 3;      // stages that use the side stream: see use_side_stream
 
 struct StagePlan {
   std::vector<UnetBuf> ub; std::vector<DitBuf> db;

@@ -21,3 +21,13 @@ def test_image_encoder_workspace_grows_with_the_samples():
         for lo, hi in ((0, len(layers)), (len(layers) - 3, len(layers))):
             sizes = [enc.workspace_bytes(lo, hi, n) for n in range(1, 40)]
             assert all(a <= b for a, b in zip(sizes, sizes[1:]))
+
+
+@pytest.mark.parametrize("kind", [B.KIND_UNET, B.KIND_DIT])
+def test_short_stages_hold_one_set_of_backward_buffers(kind):
+    # a second set is for stages that use the side stream; two blocks on one stream share theirs, but for what one hands to the next
+    t, d = 8 * 1024, 640
+    size = lambda blocks: B.Stage(kind, B.DP_BF16, blocks, 8, 1024, d, 10, 64, 77, 768, 4 * d).workspace_bytes(True)
+    second, later = size(2) - size(1), size(5) - size(4)
+    assert second - later <= t * d * 2 + (1 << 20) + (0 if kind == B.KIND_UNET else 16 * t * d // 2)
+    assert size(3) - size(2) > later + 4 * t * d * 2
