@@ -355,14 +355,19 @@ static void plan_image(const dp_image_encoder& e, void* base, int lb, int le, in
       attn_v = std::max(attn_v, group * HW); attn_s = std::max(attn_s, group * HW * HW);
     }
   }
-  b.ping = p.take(maxact * 2); b.pong = p.take(maxact * 2); b.t1 = p.take(maxact * 2); b.t2 = p.take(maxact * 2); b.t3 = p.take(maxact * 2);
-  b.gn_bytes = gn; b.gn = gn ? (float*)p.take(gn) : nullptr;
-  b.gnc_bytes = gnc; b.gnc = (float*)p.take(gnc); b.stat_of = nullptr; b.stat_blocks = 0;
+  b.ping = p.take(maxact * 2); b.pong = p.take(maxact * 2); b.t1 = p.take(maxact * 2);
+  // t2 and t3 are free while an attention layer runs: its buffers lie in their place
+  Plan q(base ? (char*)base + p.off : nullptr);
   if (attn_rows) {
     const size_t qb = attn_rows * attn_c * 2;
-    b.q = p.take(qb); b.k = p.take(qb); b.v = p.take(attn_v * attn_c * 2); b.a = p.take(qb);   // v: a group's values, transposed
-    b.scores = (float*)p.take(attn_s * 4); b.probs = p.take(attn_s * 2);
+    b.q = q.take(qb); b.k = q.take(qb); b.v = q.take(attn_v * attn_c * 2); b.a = q.take(qb);   // v: a group's values, transposed
+    b.scores = (float*)q.take(attn_s * 4); b.probs = q.take(attn_s * 2);
   } else { b.q = b.k = b.v = b.a = b.probs = nullptr; b.scores = nullptr; }
+  const size_t p0 = p.off;
+  b.t2 = p.take(maxact * 2); b.t3 = p.take(maxact * 2);
+  p.off = std::max(p.off, p0 + q.off);
+  b.gn_bytes = gn; b.gn = gn ? (float*)p.take(gn) : nullptr;
+  b.gnc_bytes = gnc; b.gnc = (float*)p.take(gnc); b.stat_of = nullptr; b.stat_blocks = 0;
   b.bytes = p.off;
 }
 

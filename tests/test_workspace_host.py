@@ -31,3 +31,12 @@ def test_short_stages_hold_one_set_of_backward_buffers(kind):
     second, later = size(2) - size(1), size(5) - size(4)
     assert second - later <= t * d * 2 + (1 << 20) + (0 if kind == B.KIND_UNET else 16 * t * d // 2)
     assert size(3) - size(2) > later + 4 * t * d * 2
+
+
+def test_attention_buffers_of_the_image_encoder_take_no_room_beside_the_large_layers():
+    from synth_inputs import vae_encoder_layers
+    layers = vae_encoder_layers(128, (1, 2, 4, 4), 8, 8)
+    size = lambda l, n: B.ImageEncoder(B.DP_BF16, 512, 512, 8, 32, l).workspace_bytes(0, len(l), n)
+    without = tuple(x for x in layers if x[0] != "attn")
+    for n in (1, 4, 8):
+        assert size(layers, n) <= size(without, n) + (1 << 20)
