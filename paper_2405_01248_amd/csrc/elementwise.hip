@@ -420,7 +420,7 @@ int launch_ln_bwd(const LnBwdArgs& a, hipStream_t s) {
   }
   int e;
   {
-    KScope ks(KK_LN_BWD, 0.0, a.rows * (double)a.d * (dtype_size(a.dtype) + 4.0 + (a.dres ? (a.dres_storage ? dtype_size(a.dtype) : 4.0) : 0.0) + (a.dx ? dtype_size(a.dtype) : 0.0) + (a.dx32 ? 4.0 : 0.0)) + 8.0 * a.rows, s, a.rows, a.d);
+    KScope ks(KK_LN_BWD, 0.0, a.rows * (double)a.d * (dtype_size(a.dtype) + 4.0 + (a.dres ? (a.dres_storage ? dtype_size(a.dtype) : 4.0) : 0.0) + (a.dx ? dtype_size(a.dtype) : 0.0) + (a.dx32 ? 4.0 : 0.0) + (a.gate ? 2.0 * dtype_size(a.dtype) : 0.0)) + 8.0 * a.rows, s, a.rows, a.d);
     e = a.dtype == BF16 ? ln_bwd_t<bf16>(a, rpb, nb, nchunk, partial, s) : ln_bwd_t<float>(a, rpb, nb, nchunk, partial, s);
   }
   if (e || !want_cols || a.defer_reduce) return e;
@@ -434,6 +434,7 @@ int launch_gate_bwd(const LnBwdArgs& a, hipStream_t s) {
   for (const void* q : ptrs) if (!q || ((uintptr_t)q % 16)) return set_error(DP_EALIGN, "gate_bwd: operands must be non-null and 16-byte aligned");
   const int wg_rows = ln_bwd_rows(a.rows, a.d), nchunk = (a.rows_per_batch + wg_rows - 1) / wg_rows;
   auto kern = a.dtype == BF16 ? gate_bwd_kernel<bf16> : gate_bwd_kernel<float>;
+  KScope ks(KK_OTHER, 0.0, a.rows * (double)a.d * (4.0 + 2.0 * dtype_size(a.dtype)), s, a.rows, a.d);
   hipLaunchKernelGGL(kern, dim3(nchunk, a.rows / a.rows_per_batch), dim3(ln_bwd_threads(a)), 0, s, a.d, a.rows_per_batch, wg_rows, (const float*)a.dres, gate_of(a));
   return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "gate_bwd launch failed");
 }

@@ -670,9 +670,12 @@ static int check_stage_call(const dp_stage* s, const void* const* params, const 
   return DP_OK;
 }
 
-// The side stream carries a block's weight gradients beside the next block's backward.  The first block's have nothing beside them, and what
-// does run together slows each other down: over 40 drawn stages of both kinds, 1 and 2 blocks took 0 to 29 % longer with it (median 3 %;
-// events and waits are most of a small stage's loss), 3 and more blocks 0 to 3 % less.
+// The side stream carries a block's weight gradients beside the next block's backward.  The first block's have nothing beside them, what does
+// run together slows each other down, and events and waits weigh on short kernels.  Step time with it against without, in %, at 1 / 2 / 3 / 5 / 8
+// blocks (batch x tokens x width): U-Net 8 x 4096 x 320 +1.3 / -0.4 / -0.9 / -1.2 / -1.4; 8 x 1024 x 640 +3.1 / +1.4 / +0.8 / +0.7 / +0.6;
+// 2 x 513 x 1280 +6.1 / +3.4 / +3.5 / +3.3 / +3.3; 2 x 256 x 640 +20 / +14 / +10 / +7 / +8; DiT 32 x 256 x 1152 +2.5 / +0.7 / +0.1 / +0.1 / +0.1;
+// 4 x 256 x 1152 +12 / +4.6 / +2.6 / +1.1 / +0.3.  So one and two blocks never use it.  From three on it pays for many rows and costs
+// stages of few: dp_stage_set_overlap(0) is for those.
 static bool use_side_stream(const dp_stage& s) { return s.overlap && s.es == 2 && s.d.n_blocks >= SIDE_MIN_BLOCKS; }
 
 static int ensure_side_stream(dp_stage* s) {

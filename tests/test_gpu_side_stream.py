@@ -55,3 +55,18 @@ def test_profile_times_the_kernels_of_the_step(cfg):
         torch.cuda.synchronize()
         launches.append(sorted((r["kind"], r["m"], r["n"], r["k"]) for r in B.ktime_end(4096)))
     assert launches[0] == launches[1]
+
+
+def test_timed_bytes_of_the_gated_branches():
+    # beside gradient, input, residual gradient and result a LayerNorm backward moves the gated branch it serves; the last block's has a kernel of its own
+    import torch
+    from paper_2405_01248_amd import binding as B
+    cfg = FIVE_DIT.replace(name="two_dit_bf16", n_blocks=2)
+    ds, _ = _run(cfg)
+    B.ktime_begin(4096)
+    ds.step()
+    torch.cuda.synchronize()
+    rows = B.ktime_end(4096)
+    t, d = cfg.batch * cfg.tokens, cfg.d_model
+    assert sorted(r["bytes"] for r in rows if r["kind"] == "ln_bwd") == [12 * t * d + 8 * t] + 3 * [18 * t * d + 8 * t]
+    assert sum(r["kind"] == "other" and (r["m"], r["n"]) == (t, d) and r["bytes"] == 8 * t * d for r in rows) == 1
