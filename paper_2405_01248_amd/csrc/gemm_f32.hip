@@ -17,23 +17,26 @@ namespace dp {
 struct GemmF32Params {
   const float* A; const float* B;
   int M, N, K, lda, ldb;
-  unsigned tiles, tiles_n;
+  int fold_m;                         // more tiles than a grid's first two dimensions take: the third counts row folds, then column folds
   float* colsum; int colsum_acc;      // A contraction-strided: sum of A over the contraction, per row of the output
   EpiParams<float> epi;
 };
 
-constexpr unsigned GEMM_F32_GRID_X = 1u << 22;      // tiles side by side in a launch's first dimension (its threads are counted in 32 bits)
-// WIDE: 16-byte loads along the contraction of an operand that has it contiguous (K and the leading dimensions are multiples of 4); else one
-// value at a time.
-template <int NW, bool A_MC, bool B_MC, bool WIDE>
+constexpr long GEMM_F32_GRID_X = 1l << 22, GEMM_F32_GRID_Y = 65535;      // (the threads of a grid's first dimension are counted in 32 bits)
+// ANY: contractions and leading dimensions that are not multiples of 4 (one value per load instead of 16 bytes along the contraction), and any
+// number of tiles.  A kernel of its own: looking for the folds costs each of a small stage's launches 0.1 to 0.3 us.
+template <int NW, bool A_MC, bool B_MC, bool ANY>
 __global__ void __launch_bounds__(NW * 64) gemm_f32_kernel(const GemmF32Params p) {
   constexpr int U = 4;                // chunks in flight per wave
   __shared__ float red[NW][32][33];
   __shared__ float csred[NW][32];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l16 = lane & 15, q = lane >> 4;
-  const unsigned id = blockIdx.y * GEMM_F32_GRID_X + blockIdx.x;
-  if (id >= p.tiles) return;
-  const int tile_m = id / p.tiles_n, tile_n = id % p.tiles_n, m0 = tile_m * 32, n0 = tile_n * 32, chunks = (p.K + 15) / 16;
+  int tile_m = blockIdx.y, tile_n = blockIdx.x;
+  if (ANY) {
+    tile_m += (int)(blockIdx.z % p.fold_m * GEMM_F32_GRID_Y); tile_n += (int)(blockIdx.z / p.fold_m * GEMM_F32_GRID_X);
+    if ((long)tile_m * 32 >= p.M || (long)tile_n * 32 >= p.N) return;
+  }
+  const int m0 = tile_m * 32, n0 = tile_n * 32, chunks = (p.K + 15) / 16;
   f32x4 acc[2][2];
   float cs[2] = {0.f, 0.f};
 #pragma unroll
@@ -46,7 +49,7 @@ __global__ void __launch_bounds__(NW * 64) gemm_f32_kernel(const GemmF32Params p
   // a lane's four contraction values of chunk c: k = 16 c + 4 q + 0..3, the same for both operands
   auto fetch = [&](const float* base, int ld, bool mc, int row, int c) {
     const int k = c * 16 + 4 * q;
-    if (WIDE && !mc) return *reinterpret_cast<const f32x4*>(base + (size_t)row * ld + min(k, p.K - 4));
+    if (!ANY && !mc) return *reinterpret_cast<const f32x4*>(base + (size_t)row * ld + min(k, p.K - 4));
     f32x4 v;
 #pragma unroll
     for (int t = 0; t < 4; ++t) v[t] = mc ? base[(size_t)min(k + t, p.K - 1) * ld + row] : base[(size_t)row * ld + min(k + t, p.K - 1)];
@@ -117,22 +120,23 @@ __global__ void __launch_bounds__(NW * 64) gemm_f32_kernel(const GemmF32Params p
   }
 }
 
-template <int NW, bool WIDE>
-static void launch_f32(const GemmF32Params& p, int a_mc, int b_mc, hipStream_t s) {
-  const dim3 grid(std::min(p.tiles, GEMM_F32_GRID_X), (p.tiles - 1) / GEMM_F32_GRID_X + 1), block(NW * 64);
-  if (a_mc && b_mc) hipLaunchKernelGGL((gemm_f32_kernel<NW, true, true, true>), grid, block, 0, s, p);      // nothing is loaded along the contraction
-  else if (a_mc) hipLaunchKernelGGL((gemm_f32_kernel<NW, true, false, WIDE>), grid, block, 0, s, p);
-  else if (b_mc) hipLaunchKernelGGL((gemm_f32_kernel<NW, false, true, WIDE>), grid, block, 0, s, p);
-  else hipLaunchKernelGGL((gemm_f32_kernel<NW, false, false, WIDE>), grid, block, 0, s, p);
+template <int NW, bool ANY>
+static void launch_f32(const GemmF32Params& p, int a_mc, int b_mc, dim3 grid, hipStream_t s) {
+  const dim3 block(NW * 64);
+  if (a_mc && b_mc) hipLaunchKernelGGL((gemm_f32_kernel<NW, true, true, ANY>), grid, block, 0, s, p);
+  else if (a_mc) hipLaunchKernelGGL((gemm_f32_kernel<NW, true, false, ANY>), grid, block, 0, s, p);
+  else if (b_mc) hipLaunchKernelGGL((gemm_f32_kernel<NW, false, true, ANY>), grid, block, 0, s, p);
+  else hipLaunchKernelGGL((gemm_f32_kernel<NW, false, false, ANY>), grid, block, 0, s, p);
 }
 
 int launch_gemm_f32(const GemmArgs& a, hipStream_t s) {
   const bool wide = (a.a_mc || (a.K % 4 == 0 && a.lda % 4 == 0 && (uintptr_t)a.A % 16 == 0)) && (a.b_mc || (a.K % 4 == 0 && a.ldb % 4 == 0 && (uintptr_t)a.B % 16 == 0));
-  const long tiles_n = ((long)a.N + 31) / 32, tiles = (((long)a.M + 31) / 32) * tiles_n;
-  if (tiles > 0x7fffffffL) return set_error(DP_EUNSUPPORTED, "gemm(f32): too many output tiles");
+  const long tiles_m = ((long)a.M + 31) / 32, tiles_n = ((long)a.N + 31) / 32;
+  const long fold_m = (tiles_m + GEMM_F32_GRID_Y - 1) / GEMM_F32_GRID_Y, fold_n = (tiles_n + GEMM_F32_GRID_X - 1) / GEMM_F32_GRID_X;
+  const dim3 grid((unsigned)std::min(tiles_n, GEMM_F32_GRID_X), (unsigned)std::min(tiles_m, GEMM_F32_GRID_Y), (unsigned)(fold_m * fold_n));
   GemmF32Params p;
   p.A = (const float*)a.A; p.B = (const float*)a.B;
-  p.M = a.M; p.N = a.N; p.K = a.K; p.lda = a.lda; p.ldb = a.ldb; p.tiles = (unsigned)tiles; p.tiles_n = (unsigned)tiles_n; p.colsum = a.colsum_out; p.colsum_acc = a.accumulate;
+  p.M = a.M; p.N = a.N; p.K = a.K; p.lda = a.lda; p.ldb = a.ldb; p.fold_m = (int)fold_m; p.colsum = a.colsum_out; p.colsum_acc = a.accumulate;
   EpiParams<float>& e = p.epi;
   e = EpiParams<float>();
   e.M = a.M; e.N = a.N; e.out = (float*)a.out; e.ldo = a.ldo; e.out32 = a.out_f32; e.ldo32 = a.ldo32; e.accumulate = a.accumulate;
@@ -142,8 +146,9 @@ int launch_gemm_f32(const GemmArgs& a, hipStream_t s) {
   e.residual = a.residual; e.ld_res = a.ld_res; e.out_scale = 1.0f;
   KScope ks(KK_GEMM_F32, 2.0 * a.M * a.N * a.K, 4.0 * ((double)a.M * a.K + (double)a.N * a.K + (double)a.M * a.N), s, a.M, a.N, a.K);
   // eight waves share a contraction that gives four of them more than two chunks each
-  if (a.K > 128) wide ? launch_f32<8, true>(p, a.a_mc, a.b_mc, s) : launch_f32<8, false>(p, a.a_mc, a.b_mc, s);
-  else wide ? launch_f32<4, true>(p, a.a_mc, a.b_mc, s) : launch_f32<4, false>(p, a.a_mc, a.b_mc, s);
+  const bool any = !wide || grid.z > 1;
+  if (a.K > 128) any ? launch_f32<8, true>(p, a.a_mc, a.b_mc, grid, s) : launch_f32<8, false>(p, a.a_mc, a.b_mc, grid, s);
+  else any ? launch_f32<4, true>(p, a.a_mc, a.b_mc, grid, s) : launch_f32<4, false>(p, a.a_mc, a.b_mc, grid, s);
   return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "gemm(f32) launch failed");
 }
 
