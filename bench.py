@@ -161,14 +161,16 @@ def pmc_traffic_bytes(workload, kind):
 
 
 MFMA_KINDS = {"gemm_nt", "gemm_nn", "gemm_tn", "attn_fwd", "attn_bwd_dq", "attn_bwd_dkv", "conv3x3"}
-KERNEL_NAMES = {"gemm_nt": "dp::gemm_bf16_dtl_kernel<..., A_MC=false, B_MC=false> (y = x W^T; dx = dy W on transposed weight copies)",
-                "gemm_nn": "dp::gemm_bf16_kernel<..., A_MC=false, B_MC=true> (dx = dy W)",
-                "gemm_tn": "dp::gemm_bf16_kernel<..., A_MC=true, B_MC=true> (dW = dy^T x)",
+KERNEL_NAMES = {"gemm_nt": "dp::gemm_pp_kernel, dp::gemm_wave_kernel, dp::gemm_bf16_dtl_kernel by size (y = x W^T; dx = dy W on transposed weight copies)",
+                "gemm_nn": "dp::cond_grad_kernel (gradient of the conditioning vectors), dp::gemm_bf16_kernel (dx = dy W)",
+                "gemm_tn": "dp::gemm_dw_group_kernel (dW = dy^T x, all of a block)",
                 "attn_fwd": "dp::attn_fwd_bf16_kernel", "attn_bwd_dq": "dp::attn_bwd_dq_bf16_kernel",
                 "attn_bwd_dkv": "dp::attn_bwd_dkv_bf16_kernel", "ln_fwd": "dp::ln_fwd_kernel", "ln_bwd": "dp::ln_bwd_kernel",
-                "geglu_fwd": "dp::geglu_fwd_kernel", "geglu_bwd": "dp::geglu_bwd_kernel", "reduce": "dp::colsum_kernel",
-                "conv3x3": "dp::conv3x3_bf16_kernel (implicit GEMM)", "groupnorm": "dp::gn_partial_kernel + gn_finalize_kernel + gn_apply_kernel",
-                "softmax_rows": "dp::softmax_rows_kernel"}
+                "geglu_fwd": "dp::geglu_fwd_kernel", "geglu_bwd": "dp::geglu_bwd_kernel",
+                "reduce": "dp::gemm_dw_reduce_kernel, dp::ln_bwd_reduce_kernel, dp::attn_dkv_reduce_kernel, dp::reduce_epilogue_kernel, dp::reduce_residual_ln_kernel",
+                "conv3x3": "dp::conv3x3_pp_kernel, dp::conv3x3_in8_kernel, dp::conv3x3_small_kernel by size (implicit GEMM)",
+                "groupnorm": "dp::gn_apply_kernel, dp::gn_finalize_kernel, dp::gn_partial_kernel, dp::gn_small_kernel",
+                "softmax_rows": "dp::softmax_rows_kernel", "gemm_fp8": "dp::gemm_pp_kernel (FP8)"}
 
 
 def kernel_roofline(workload, names, si, DeviceStage, DeviceEncoder, passes=3):
