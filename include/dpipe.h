@@ -71,12 +71,13 @@ void dp_stage_destroy(dp_stage* st);
 int dp_stage_param_count(const dp_stage* st);
 int dp_stage_param_shape(const dp_stage* st, int idx, int64_t shape[2], const char** name);
 
-/* stage_bwd runs the weight- and bias-gradient kernels and the per-call weight transposes (all off the
- * critical path) on a second, library-owned stream forked from and joined to hip_stream with events,
- * so that they overlap the activation-gradient chain; a saving stage_fwd of U-Net blocks runs the
- * context K/V projections of all blocks there.  Stages of fewer than three blocks, which gain nothing from it, run on
- * hip_stream alone in either case.  enabled = 0 issues everything on hip_stream in program order
- * (used when single kernels are to be timed); results are bit-identical either way.  Default 1. */
+/* Stages of three and more blocks (bf16): stage_bwd runs each block's weight-gradient work (dW, bias and LayerNorm
+ * parameter gradients, the conditioning gradient of DiT blocks) on a second, library-owned stream forked from and
+ * joined to hip_stream with events, beside the activation-gradient chain of the block before it; a saving stage_fwd of
+ * U-Net blocks runs the context K/V projections of all blocks there.  It pays for many rows (8 x 4096 x 320: 1 % of the step)
+ * and costs stages of few (2 x 256 x 640: 7 to 10 %).  enabled = 0 issues everything on hip_stream in program order
+ * (also for timing single kernels), as stages of one or two blocks do in either case; results are bit-identical either
+ * way.  Default 1. */
 int dp_stage_set_overlap(dp_stage* st, int enabled);
 
 /* Epilogue fusions of the U-Net block's GeGLU feed-forward (bf16 stages; the fp32 path never fuses).
@@ -125,13 +126,15 @@ int dp_encoder_param_shape(const dp_encoder* enc, int idx, int64_t shape[2], con
 /* Batch-invariant modes (mode 0, the default, is off).  In modes 1 and 2 a sample's result is bit-identical for
  * every num_samples -- what the partial-batch scheme of Sec. 5 (a layer's samples spread over bubbles of different
  * sizes, outputs concatenated) needs if the concatenation has to equal the full-batch result bit for bit.
- *   mode 1: tile shapes and split-K factors of every projection are chosen for one sample's rows instead of the
- *           slice's.  Full speed on slices of up to 4 samples, 12 % slower at 16, 33 % at 64; larger workspace.
+ *   mode 1: the parts every projection's contraction is cut into are chosen for one sample's rows instead of the
+ *           slice's; the tile, and whether the parts run side by side or one after the other in a workgroup, follow the
+ *           slice, since neither changes a bit.  Against mode 0 (12 layers of width 768) 7 % slower on 1 sample, as fast
+ *           on 4, 14 % slower on 16, 5 % on 64; larger workspace.
  *   mode 2: no split-K, and only tiles built on the 32x32x16 matrix instruction (their shape does not change the
- *           order in which an output element's products are added).  Full speed at 64 samples, 20 % slower on small slices.
+ *           order in which an output element's products are added).  60 % slower on 1 sample, 39 % on 4, 16 % on 16, 1 % on 64.
  * Set the mode before asking for the workspace size; any other value is DP_EINVAL. */
 int dp_encoder_set_batch_invariant(dp_encoder* enc, int mode);
-/* Workspace bytes for a call on at most max_samples samples (in the encoder's current mode). */
+/* Workspace bytes for a call on at most max_samples samples (in the encoder's current mode); never less for more samples. */
 size_t dp_encoder_workspace_bytes(const dp_encoder* enc, int max_samples);
 
 /* Runs layers [layer_begin, layer_end) on samples [sample_offset, sample_offset + num_samples)
@@ -400,10 +403,16 @@ int dp_schedule_search(const dp_layer_cost* rows, int n_rows, const dp_search_op
  * overwritten or accumulated into.  `workspace` (fp32 scratch of dp_op_gemm_workspace_bytes; may be
  * NULL, then nothing is split) serves a fixed-order split-K reduction: of the fp32 output, and of a
  * storage-dtype output with few tiles and a long contraction, whose bias is then applied by the
- * reduction pass.  tile_cfg = 0 picks the tile shape from (M,N,K); 1..15 force one (measurement and
- * tests only): 1..6 register-staged tiles, 7..15 direct-to-LDS tiles, which need K % 32 == 0
- * (7, 8, 9, 13, 15) or K % 64 == 0 (10, 11, 12, 14); 12 exists for a_kmajor = b_kmajor = 0 only.  A forced
- * configuration that does not fit the problem returns DP_EUNSUPPORTED without launching. */
+ * reduction pass.  bf16: leading dimensions and the contiguous extents multiples of 8; fp32: any size and leading
+ * dimension, fastest where K and the leading dimensions are multiples of 4.  tile_cfg = 0 picks the tile shape from
+ * (M,N,K); 1..29 force one (bf16; measurement and tests only):
+ *    1..6   register-staged tiles, any layout
+ *    7..15  direct-to-LDS tiles: K % 32 == 0 (7, 8, 9, 13, 15) or K % 64 == 0 (10, 11, 12, 14); 13 is 8, 12 is 21
+ *   16, 17  64x64 and 64x128 direct-to-LDS tiles: a_kmajor = b_kmajor = 0, K % 64 == 0
+ *   18..21  tiles of two alternating wave groups, 256 rows x 256, 128, 192, 160 columns: a_kmajor = b_kmajor = 0, out_is_f32 = 0
+ *   22..25  the weight-gradient tiles 256x256, 256x128, 128x256, 256x192: a_kmajor = b_kmajor = 1, out_is_f32 = 1
+ *   26..29  tiles whose waves share the contraction, 64x64, 64x96, 128x96, 128x128: as 18..21, K % 64 == 0
+ * A forced configuration that does not fit the problem returns DP_EUNSUPPORTED without launching. */
 size_t dp_op_gemm_workspace_bytes(int M, int N, int K);
 int dp_op_gemm(int dtype, const void* A, int lda, int a_kmajor, const void* B, int ldb, int b_kmajor, int M, int N, int K,
                const void* bias, void* C, int ldc, int out_is_f32, int accumulate, void* workspace, size_t workspace_bytes,

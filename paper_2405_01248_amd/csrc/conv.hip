@@ -3,8 +3,9 @@
 // w[o, tap * C_in + c], tap = 3u + v.  Rows of the product are output pixels, its contraction runs over the
 // nine taps times the input channels; the A operand is never materialised: every thread gathers its 16-byte
 // pieces of the input (8 channels of one pixel, which lie inside one tap because C_in is a multiple of 8)
-// straight from the tensor, with zeros where the tap falls into the padding.  Tiles are staged through
-// registers into padded LDS tiles (double buffered) and multiplied with v_mfma_f32_32x32x16_bf16; the
+// straight from the tensor, with zeros where the tap falls into the padding.  The kernel that takes every shape stages
+// its tiles through registers into padded LDS tiles (double buffered); the layers of an encoder run on the ones further
+// down, which copy to LDS directly.  v_mfma_f32_32x32x16_bf16 throughout; the
 // epilogue is the GEMM kernels' (bias, optional residual in the storage dtype).  This is the layer class of
 // the frozen image encoder (Sec. 2.1, Sec. 2.3: the non-trainable layers that take tens to hundreds of
 // milliseconds and are cut into partial batches, Sec. 5).

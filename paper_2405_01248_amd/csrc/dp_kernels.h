@@ -43,7 +43,7 @@ struct GemmArgs {
   // bias gradient, from the tiles the kernel stages anyway.  Only where gemm_colsum_supported() says so.
   float* colsum_out;
   int force_cfg;             // 0 = choose by shape; 1 + index forces a tile configuration (measurement only)
-  int choice_rows;           // > 0: tile configuration and split-K factor are chosen as if the problem had this many rows
+  int choice_rows;           // > 0: the parts of the contraction are chosen as if the problem had this many rows
                              // (a caller whose rows are independent samples gets the same arithmetic per row for any M);
                              // < 0: the same guarantee by other means: no split-K and 32x32x16 tiles only, shape chosen from M
   // GeGLU fused into the epilogue (bf16 only; bias is the only other epilogue term allowed):
@@ -180,7 +180,7 @@ struct LnArgs {
 };
 int launch_ln_fwd(const LnArgs& a, hipStream_t s);
 // x[r, :] += sum_z partial[z][r, :] (+ bias), then y[r, :] = LN(x[r, :]; gamma, beta, eps) in bf16: the split-K
-// reduction of a projection onto the fp32 residual stream and the LayerNorm that follows it, one wave per row.
+// reduction of a projection onto the fp32 residual stream and the LayerNorm that follows it, one workgroup per row.
 // partial: [splits][rows][d] fp32; d a multiple of 8, at most 2048.
 int launch_reduce_residual_ln(const float* partial, int splits, int rows, int d, const void* bias, float* x, void* y,
                               const void* gamma, const void* beta, float eps, hipStream_t s);

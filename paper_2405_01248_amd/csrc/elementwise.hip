@@ -1,7 +1,7 @@
 // Bandwidth-bound kernels of a stage: LayerNorm forward/backward (affine or adaLN
 // modulated), GeGLU, SiLU, gated-residual backward, column sums (bias gradients),
-// split-K partial reduction, embedding gather.  One wave per token row with 16-byte
-// accesses; all reductions are in a fixed order (no float atomics), so results are
+// split-K partial reduction, embedding gather.  16-byte accesses, one wave per token row or
+// columns per thread; all reductions are in a fixed order (no float atomics), so results are
 // run-to-run identical.  Templated on the storage type (bf16 or fp32); math is fp32.
 #include "dp_device.h"
 #include "dp_kernels.h"

@@ -1,13 +1,14 @@
 // GEMM kernels for the projections and MLPs of a stage (forward y = x W^T, backward
 // dx = dy W and dW = dy^T x), fp32 accumulation, with fused epilogues.
 //
-// bf16 path: MFMA 32x32x16 tiles fed from LDS.  An operand whose contraction index is
+// bf16 path: MFMA tiles fed from LDS.  An operand whose contraction index is
 // contiguous in memory is staged [rows][BK] and read with 16-byte LDS loads; an operand
-// whose contraction index is the slow one (weights in dx, both operands in dW) is staged
-// [BK][cols] exactly as it sits in HBM and read with the transposing LDS load, so no
-// transposed copy of a weight or activation is ever materialised.  Workgroup ids are
-// remapped so that the tiles running on one XCD (one L2) are neighbours in the output.
-// fp32 path: plain FMA tiles (used by the small fp32 configuration only).
+// whose contraction index is the slow one (both operands in dW, weights in dx where a stage
+// has no transposed copy of them) is staged [BK][cols] exactly as it sits in HBM and read with
+// the transposing LDS load.  Workgroup ids are remapped so that the tiles running on one XCD
+// (one L2) are neighbours in the output.
+// Elsewhere: the weight gradients of a block in one launch (gemm_dw.hip), at most 48 rows
+// (gemm_few_rows.hip), fp32 (gemm_f32.hip).
 #include "dp_device.h"
 #include "dp_kernels.h"
 #include "dp_errors.h"
@@ -758,9 +759,7 @@ constexpr int kCUs = 256;
 // workgroup of the launch resident at once (`slots` = CUs x workgroups per CU of the configuration), with
 // at least 8 64-deep k-tiles per split and at most 32 partial sums to reduce.  A launch that spills into a
 // second round loses what the extra splits gained (90 tiles of 256x256, one per CU: 2 splits run 10 %
-// faster than 4 on the bare GEMM).  Inside the stage these GEMMs run on the side stream under the main
-// stream's kernels and every policy tried, a split count that is not a power of two included, stays
-// within 0.5 % of the step time.
+// faster than 4).  (A stage's weight gradients go through gemm_dw.hip, whose plan covers a whole block.)
 static int choose_splits(long tiles, int kt, int slots) {
   const long cap = std::min<long>(std::min<long>(slots / std::max<long>(tiles, 1), kt / 8), 32);
   int s = 1;
@@ -878,8 +877,8 @@ int gemm_epi_split_rows(int N, int K) {
 
 // Picks the tile configuration (indices as in launch_gemm's switch), from sweeps of all GEMM shapes of
 // the five workloads on MI355X:
-//  - y = x W^T (both operands K-contiguous; also dx = dy W on transposed weight copies): the
-//    direct-to-LDS kernels, tile chosen by the cost model below;
+//  - y = x W^T (both operands K-contiguous; also dx = dy W on transposed weight copies): the tile with the least
+//    estimated time, among alternating wave groups, waves that share the contraction and the plain direct-to-LDS ones;
 //  - dx = dy W with W as stored (fp32-free fallback when no transposed copy exists): 256x256
 //    direct-to-LDS tiles when they fill the CUs, else the register-staged kernel;
 //  - dW = dy^T x (both operands read through the transposing LDS load): register-staged 128x128 tiles,

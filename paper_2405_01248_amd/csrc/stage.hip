@@ -62,7 +62,7 @@ struct dp_encoder {
   size_t es;
   // scratch of the split projections for up to (i + 1) * SPLITK_STEP rows, in every call of fewer rows too (mode 0; constant beyond the last entry)
   std::vector<size_t> splitk_bytes;
-  int batch_invariant = 0;   // 1: tile shapes and split-K factors chosen for one sample's rows; 2: no split-K, 32x32x16 tiles only
+  int batch_invariant = 0;   // 1: split-K factors chosen for one sample's rows; 2: no split-K, 32x32x16 tiles only
 };
 
 namespace dp {
