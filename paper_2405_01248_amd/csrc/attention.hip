@@ -13,6 +13,12 @@
 // The streamed tiles are copied global -> LDS directly (`buffer_load ... lds`) into unpadded tiles whose
 // 16-byte chunks are permuted per row, so that both ways of reading a tile stay free of bank conflicts.
 //
+// What bounds them (40 heads of 4096 tokens, width 64; counters): the power the card may draw.  Forward, dQ and dK/dV take 2.9, 3.6 and 5.0
+// million cycles (summed over 8 XCDs) at 1.87, 1.80 and 1.82 GHz, matrix pipes busy 45, 55 and 53 % of them; before the waits for the tile copies,
+// a quarter of the vector instructions and the bank conflicts of the row fragments were taken out it was 3.4, 4.3 and 6.1 million at up to 2.2 GHz:
+// 212 -> 192, 280 -> 249, 351 -> 337 us.  What is left per element of the scores is one fma, one exponential, a product (backward) or a sum
+// (forward) and half a conversion.
+//
 // fp32 path: one wave per query (or key) row, plain FMA; used by the small fp32
 // configuration only.
 #include "dp_device.h"
@@ -21,6 +27,7 @@
 #include "dp_ktime.h"
 #include <math.h>
 #include <algorithm>
+#include <type_traits>
 
 namespace dp {
 
@@ -38,6 +45,7 @@ struct AttnK {
   void* dq; int lddq;
   void* dk; int lddk;
   void* dv; int lddv;
+  int even;           // waves of a SIMD take turns (take_turns)
   int qsplits; float* dkv_partial;   // dK/dV kernel: query range split + fp32 partial outputs [2][qsplits][B * Nk][H * dh]
 };
 
@@ -48,15 +56,15 @@ constexpr float LN2 = 0.6931471805599453f;
 // at position pos of a row is chunk pos ^ key(row).  A tile is read two ways -- by rows as an MFMA A operand
 // (16 consecutive rows, one chunk each, per 256 bytes of LDS bandwidth) and through the transposing load (4
 // consecutive rows x 64 bytes) -- and the key keeps both conflict-free:
-//   DHP = 64 (128-byte rows): key = row bits (0, 2, 1): a bijection of row & 7 whose bit 2 is row bit 1, so
-//     8 consecutive rows land in 8 different positions and the 4 rows of a transposing read in 4 different
-//     64-byte bank groups;
+//   DHP = 64 (128-byte rows, two to the 256 bytes of a bank line): key = row bits (1, 2, 3), a bijection of the 8 rows that
+//     share a half of the line among 16 consecutive ones; its bit 2 is row bit 1, so the 4 rows of a transposing read lie in
+//     4 different 64-byte bank groups;
 //   DHP = 96 (192-byte rows): consecutive rows already start 192 bytes apart, i.e. in different 64-byte groups;
 //     rows r and r + 4 share one, so key = (row >> 2) & 3 moves them apart inside the group.
 template <int DHP> struct AttnTile;
 template <> struct AttnTile<64> {
   static constexpr int PIECES = 2;     // 1 KB copy instructions per wave and tile (16 rows)
-  static __device__ __forceinline__ int key(int row) { return (row & 1) | ((row & 4) >> 1) | ((row & 2) << 1); }
+  static __device__ __forceinline__ int key(int row) { return ((row & 8) >> 3) | ((row & 4) >> 1) | ((row & 2) << 1); }
 };
 template <> struct AttnTile<96> {
   static constexpr int PIECES = 3;
@@ -83,10 +91,10 @@ struct AttnTileCopy {
   }
   // rows row0 .. row0 + 63 of the slice behind r (the tile offset goes into the per-lane offset: only that
   // one is range-checked)
-  __device__ __forceinline__ void issue(rsrc_t r, int row0, int ld, bf16* stage, int wave) const {
+  __device__ __forceinline__ void issue(u32x4 r, int row0, int ld, bf16* stage, int wave) const {
 #pragma unroll
     for (int j = 0; j < T::PIECES; ++j)
-      async_copy_16B_buf(r, off[j] + (uint32_t)row0 * (uint32_t)ld * 2u, 0, stage + 16 * wave * DHP + 512 * j);
+      async_copy_16B_raw(r, off[j] + (uint32_t)row0 * (uint32_t)ld * 2u, lds_address(stage) + 2u * (16 * wave * DHP + 512 * j));
   }
 };
 
@@ -94,14 +102,14 @@ struct AttnTileCopy {
 // c) is at row[c] + 32 * DHP * t.  A transposed fragment in the slot order of frag_from_mc_accorder (rows
 // r0 .. r0 + 15 with r0 a multiple of 16, which leaves the keys alone; columns 32 * i .. + 31) is read as two
 // halves at tr_lo[i] + DHP * r0 and tr_hi[i] + DHP * r0 (8 rows apart).
-template <int DHP>
+template <int DHP, int KC>
 struct AttnFragOff {
   using T = AttnTile<DHP>;
-  int row[DHP / 16], tr_lo[DHP / 32], tr_hi[DHP / 32];
+  int row[KC], tr_lo[DHP / 32], tr_hi[DHP / 32];
   __device__ __forceinline__ void init(int lane) {
     const int g = lane >> 5, l32 = lane & 31, b = lane >> 4, j = lane & 15;
 #pragma unroll
-    for (int c = 0; c < DHP / 16; ++c) row[c] = l32 * DHP + 8 * ((2 * c + g) ^ T::key(l32));
+    for (int c = 0; c < KC; ++c) row[c] = l32 * DHP + 8 * ((2 * c + g) ^ T::key(l32));
     const int r = 4 * (b >> 1) + (j >> 2);
 #pragma unroll
     for (int i = 0; i < DHP / 32; ++i) {
@@ -129,6 +137,29 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16& v, int off) {
   return o;
 }
 
+// Among waves of one priority a SIMD serves the oldest first, so of the workgroups a CU holds one ends early and the last runs alone, at half the
+// rate.  Where all workgroups of a launch are resident at once, a wave's priority falls by one every second tile and wraps, which keeps them
+// together: 80 heads of 1024 tokens, 640 workgroups, forward 33.7 -> 31.3 us, dQ 45.2 -> 42.5, dK/dV 56.5 -> 52.7.  Where more wait to be
+// started, the staggered ends are what lets them start: 40 heads of 4096 tokens lose 5 % with it; one workgroup per CU has nothing to share.
+__device__ __forceinline__ void take_turns(int even, int i) {
+  if (even) {
+    const int turn = (i >> 1) & 3;
+    if (turn == 0) __builtin_amdgcn_s_setprio(3);
+    else if (turn == 1) __builtin_amdgcn_s_setprio(2);
+    else if (turn == 2) __builtin_amdgcn_s_setprio(1);
+    else __builtin_amdgcn_s_setprio(0);
+  }
+}
+
+// tile(i, stage) for i = first .. last - 1, the stages of LDS in turn and known to the compiler: the fragment reads then need no address
+// arithmetic and no registers beyond the offsets of AttnFragOff.
+template <class F> __device__ __forceinline__ void two_stages(int first, int last, F tile) {
+  for (int i = first; i < last; i += 2) {
+    tile(i, std::integral_constant<int, 0>());
+    if (i + 1 < last) tile(i + 1, std::integral_constant<int, 1>());
+  }
+}
+
 // Maps a linear workgroup id to (tile along the sequence, batch * head).  Hardware deals
 // consecutive ids round-robin to the 8 XCDs; with this map all tiles of one (batch, head) run
 // on the same XCD, so its K/V (or Q/dO) stream is fetched into one L2 only.
@@ -147,12 +178,12 @@ __device__ __forceinline__ void attn_block_map(int id, int ntiles, int BH, int& 
 
 // ------------------------------------------------------------------ forward (bf16)
 // A workgroup covers 128 queries (32 per wave) and walks the keys in 64-row tiles, two LDS stages.
-template <int DHP, bool CAUSAL>
-__global__ void __launch_bounds__(256, DHP == 64 ? 4 : 3) attn_fwd_bf16_kernel(const AttnK p) {
-  constexpr int KC = DHP / 16, DT = DHP / 32, BQ = 128, TILE = 64 * DHP;
+template <int DHP, int KC, bool CAUSAL>
+__global__ void __launch_bounds__(256, DHP == 64 && !CAUSAL ? 4 : 3) attn_fwd_bf16_kernel(const AttnK p) {
+  constexpr int DT = DHP / 32, BQ = 128, TILE = 64 * DHP;
   __shared__ __attribute__((aligned(1024))) bf16 Ks[2][TILE];
   __shared__ __attribute__((aligned(1024))) bf16 Vs[2][TILE];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 5, l32 = lane & 31;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 5, l32 = lane & 31;
   int qtile, bh;
   attn_block_map(blockIdx.x, (p.Nq + BQ - 1) / BQ, p.B * p.H, qtile, bh);
   const int b = bh / p.H, h = bh % p.H;
@@ -161,10 +192,10 @@ __global__ void __launch_bounds__(256, DHP == 64 ? 4 : 3) attn_fwd_bf16_kernel(c
   const bf16* qb = (const bf16*)p.q + (size_t)b * p.Nq * p.ldq + h * p.dh;
   const bf16* kb = (const bf16*)p.k + (size_t)b * p.Nk * p.ldk + h * p.dh;
   const bf16* vb = (const bf16*)p.v + (size_t)b * p.Nk * p.ldv + h * p.dh;
-  const rsrc_t kr = make_rsrc(kb, attn_slice_bytes(p.Nk, p.ldk, p.dh));
-  const rsrc_t vr = make_rsrc(vb, attn_slice_bytes(p.Nk, p.ldv, p.dh));
+  const u32x4 kr = make_raw_rsrc(kb, attn_slice_bytes(p.Nk, p.ldk, p.dh));
+  const u32x4 vr = make_raw_rsrc(vb, attn_slice_bytes(p.Nk, p.ldv, p.dh));
 
-  AttnFragOff<DHP> fo;
+  AttnFragOff<DHP, KC> fo;
   fo.init(lane);
   AttnTileCopy<DHP> ck, cv;
   ck.init(wave, lane, p.ldk, p.dh);
@@ -189,68 +220,80 @@ __global__ void __launch_bounds__(256, DHP == 64 ? 4 : 3) attn_fwd_bf16_kernel(c
 
   for (int kt = 0; kt < nkt; ++kt) {
     const int buf = kt & 1;
+    take_turns(p.even, kt);
     if (kt + 1 < nkt) {      // every wave left stage buf ^ 1 at the barrier that ended the previous iteration
       ck.issue(kr, (kt + 1) * 64, p.ldk, Ks[buf ^ 1], wave);
       cv.issue(vr, (kt + 1) * 64, p.ldv, Vs[buf ^ 1], wave);
     }
-    // S^T = K Q^T
     f32x16 s[2];
+    auto scores = [&]() {      // S^T = K Q^T
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+      for (int t = 0; t < 2; ++t)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) s[t][r] = 0.f;
+        for (int r = 0; r < 16; ++r) s[t][r] = 0.f;
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+      for (int t = 0; t < 2; ++t)
 #pragma unroll
-      for (int c = 0; c < KC; ++c) s[t] = mfma32(fo.row_frag(Ks[buf], t, c), qf[c], s[t]);
-    // online softmax, one query column per lane (shared with lane ^ 32).  Masking only in tiles that cross the
-    // end of the keys or the causal diagonal (one wave-uniform branch around a block of selects; a test per
-    // element would be compiled into a branch per element)
-    const bool edge = kt * 64 + 64 > p.Nk || (CAUSAL && kt * 64 + 63 > q0);
-    if (edge) {
+        for (int c = 0; c < KC; ++c) s[t] = mfma32(fo.row_frag(Ks[buf], t, c), qf[c], s[t]);
+      // Masking only in tiles that cross the end of the keys or the causal diagonal (one wave-uniform branch around a
+      // block of selects; a test per element would be compiled into a branch per element)
+      if (kt * 64 + 64 > p.Nk || (CAUSAL && kt * 64 + 63 > q0)) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int key = kt * 64 + 32 * t + acc_row(r, g);
+            const bool dead = key >= p.Nk || (CAUSAL && key > qi);
+            s[t][r] = dead ? -INFINITY : s[t][r];
+          }
+      }
+    };
+    // Online softmax, one query column per lane (shared with lane ^ 32).  The reference point m (scaled, log2 domain) only has to
+    // bound the exponents, not equal the maximum, so no maximum is formed per tile: the probabilities are taken relative to the
+    // old reference, and their sum, which is needed anyway and is at least the largest of them, tells whether some query of the wave
+    // has outgrown it.  Only then (wave-uniform; always at the first tile) the scores are formed again, the reference is moved to 2^8
+    // above the largest of them and the accumulators are rescaled.  Exact in the final O = acc / sum and LSE = ref + log sum.
+    float rs;
+    auto probabilities = [&]() {
+      const float mref = m == -INFINITY ? 0.f : m;
+      rs = 0.f;
 #pragma unroll
       for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int key = kt * 64 + 32 * t + acc_row(r, g);
-          const bool dead = key >= p.Nk || (CAUSAL && key > qi);
-          s[t][r] = dead ? -INFINITY : s[t][r];
+          const float e = __builtin_amdgcn_exp2f(fmaf(s[t][r], p.scale_log2, -mref));
+          s[t][r] = e;
+          rs += e;
         }
-    }
-    // running maximum over raw scores (the scale is positive, so it commutes with max)
-    float mx = -INFINITY;
+    };
+    auto move_reference = [&]() {
+      float mx = -INFINITY;      // over raw scores (the scale is positive, so it commutes with max)
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+      for (int t = 0; t < 2; ++t)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[t][r]);
-    mx = reduce_halves(mx, MaxOp());
-    mx = fmaxf(m, mx * p.scale_log2);                    // m is kept in the scaled (log2) domain
-    // The reference point only has to bound the exponents, not equal the maximum: it is moved (and the
-    // accumulators rescaled) when some query of the wave has outgrown it by 2^8; until then the
-    // probabilities of this tile are taken relative to the old one (at most 256, exact in the final
-    // O = acc / sum and LSE = ref + log sum).  Wave-uniform, so the rescale is skipped for most tiles.
-    const bool bump = __any(mx > m + 8.0f);
-    mx = bump ? mx : m;
-    const float mref = (mx == -INFINITY) ? 0.f : mx;
-    float rs = 0.f;
+        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[t][r]);
+      mx = fmaxf(m, fmaf(reduce_halves(mx, MaxOp()), p.scale_log2, 8.0f));
+      if (kt > 0) {
+        const float alpha = __builtin_amdgcn_exp2f(m - (mx == -INFINITY ? 0.f : mx));
+        lsum *= alpha;
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+        for (int i = 0; i < DT; ++i)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const float e = __builtin_amdgcn_exp2f(fmaf(s[t][r], p.scale_log2, -mref));
-        s[t][r] = e;
-        rs += e;
+          for (int r = 0; r < 16; ++r) oacc[i][r] *= alpha;
       }
-    if (bump) {
-      const float alpha = __builtin_amdgcn_exp2f(m - mref);
-      lsum *= alpha;
-#pragma unroll
-      for (int i = 0; i < DT; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) oacc[i][r] *= alpha;
+      m = mx;
+    };
+    scores();
+    if (kt == 0) move_reference();
+    probabilities();
+    if (__any(!(rs <= 256.f) || m == -INFINITY)) {
+      if (kt > 0) {
+        scores();
+        move_reference();
+        probabilities();
+      }
     }
     lsum += rs;
-    m = mx;
     // O^T += V^T P^T
 #pragma unroll
     for (int t = 0; t < 2; ++t)
@@ -285,12 +328,12 @@ __global__ void __launch_bounds__(256, DHP == 64 ? 4 : 3) attn_fwd_bf16_kernel(c
 }
 
 // ------------------------------------------------------------------ dQ (bf16)
-template <int DHP>
-__global__ void __launch_bounds__(256, DHP == 64 ? 4 : 2) attn_bwd_dq_bf16_kernel(const AttnK p) {
-  constexpr int KC = DHP / 16, DT = DHP / 32, TILE = 64 * DHP;
+template <int DHP, int KC>
+__global__ void __launch_bounds__(256, DHP == 64 ? 3 : 2) attn_bwd_dq_bf16_kernel(const AttnK p) {
+  constexpr int DT = DHP / 32, TILE = 64 * DHP;
   __shared__ __attribute__((aligned(1024))) bf16 Ks[2][TILE];
   __shared__ __attribute__((aligned(1024))) bf16 Vs[2][TILE];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 5, l32 = lane & 31;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 5, l32 = lane & 31;
   int qtile, bh;
   attn_block_map(blockIdx.x, (p.Nq + 127) / 128, p.B * p.H, qtile, bh);
   const int b = bh / p.H, h = bh % p.H;
@@ -298,12 +341,12 @@ __global__ void __launch_bounds__(256, DHP == 64 ? 4 : 2) attn_bwd_dq_bf16_kerne
   const bool qok = qi < p.Nq;
   const bf16* kb = (const bf16*)p.k + (size_t)b * p.Nk * p.ldk + h * p.dh;
   const bf16* vb = (const bf16*)p.v + (size_t)b * p.Nk * p.ldv + h * p.dh;
-  const rsrc_t kr = make_rsrc(kb, attn_slice_bytes(p.Nk, p.ldk, p.dh));
-  const rsrc_t vr = make_rsrc(vb, attn_slice_bytes(p.Nk, p.ldv, p.dh));
+  const u32x4 kr = make_raw_rsrc(kb, attn_slice_bytes(p.Nk, p.ldk, p.dh));
+  const u32x4 vr = make_raw_rsrc(vb, attn_slice_bytes(p.Nk, p.ldv, p.dh));
   const bf16* qrow = (const bf16*)p.q + ((size_t)b * p.Nq + qi) * p.ldq + h * p.dh;
   const bf16* dorow = (const bf16*)p.dout + ((size_t)b * p.Nq + qi) * p.lddo + h * p.dh;
 
-  AttnFragOff<DHP> fo;
+  AttnFragOff<DHP, KC> fo;
   fo.init(lane);
   AttnTileCopy<DHP> ck, cv;
   ck.init(wave, lane, p.ldk, p.dh);
@@ -335,6 +378,10 @@ __global__ void __launch_bounds__(256, DHP == 64 ? 4 : 2) attn_bwd_dq_bf16_kerne
     dlt = reduce_halves(dlt, AddOp());
     if (qok && g == 0) p.delta[sidx] = dlt;
   }
+  constexpr bool ONTO = KC < 6;      // dP - delta: the products accumulate onto -delta (the widest head has no registers for it)
+  f32x16 ndelta;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) ndelta[r] = ONTO ? -dlt : 0.f;
 
   f32x16 acc[DT];
 #pragma unroll
@@ -345,8 +392,9 @@ __global__ void __launch_bounds__(256, DHP == 64 ? 4 : 2) attn_bwd_dq_bf16_kerne
   const int nkt = (p.Nk + 63) / 64;
   wait_vmcnt<0>();
   __syncthreads();
-  for (int kt = 0; kt < nkt; ++kt) {
-    const int buf = kt & 1;
+  auto tile = [&](int kt, auto bc) {
+    take_turns(p.even, kt);
+    constexpr int buf = bc();
     if (kt + 1 < nkt) {      // every wave left stage buf ^ 1 at the barrier that ended the previous iteration
       ck.issue(kr, (kt + 1) * 64, p.ldk, Ks[buf ^ 1], wave);
       cv.issue(vr, (kt + 1) * 64, p.ldv, Vs[buf ^ 1], wave);
@@ -355,19 +403,16 @@ __global__ void __launch_bounds__(256, DHP == 64 ? 4 : 2) attn_bwd_dq_bf16_kerne
     // finite dS they get multiplies a zero K row in the dQ product.
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-      f32x16 s, dp;
+      f32x16 s, dp = ndelta;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) { s[r] = 0.f; dp[r] = 0.f; }
+      for (int r = 0; r < 16; ++r) s[r] = 0.f;
 #pragma unroll
       for (int c = 0; c < KC; ++c) {
         s = mfma32(fo.row_frag(Ks[buf], t, c), qf[c], s);
         dp = mfma32(fo.row_frag(Vs[buf], t, c), dof[c], dp);
       }
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const float pr = __builtin_amdgcn_exp2f(fmaf(s[r], p.scale_log2, -lse2));
-        s[r] = pr * (dp[r] - dlt);
-      }
+      for (int r = 0; r < 16; ++r) s[r] = __builtin_amdgcn_exp2f(fmaf(s[r], p.scale_log2, -lse2)) * (ONTO ? dp[r] : dp[r] - dlt);
 #pragma unroll
       for (int cc = 0; cc < 2; ++cc) {
         const bf16x8 dsf = pack8(s, 8 * cc);
@@ -377,7 +422,8 @@ __global__ void __launch_bounds__(256, DHP == 64 ? 4 : 2) attn_bwd_dq_bf16_kerne
     }
     wait_vmcnt<0>();
     __syncthreads();
-  }
+  };
+  two_stages(0, nkt, tile);
   if (qok) {
     bf16* ob = (bf16*)p.dq + ((size_t)b * p.Nq + qi) * p.lddq + h * p.dh;
 #pragma unroll
@@ -397,15 +443,16 @@ __global__ void __launch_bounds__(256, DHP == 64 ? 4 : 2) attn_bwd_dq_bf16_kerne
 
 // ------------------------------------------------------------------ dK, dV (bf16)
 // grid.x = ceil(Nk / 128) * qsplits; each wave owns 32 keys and walks its share of the query tiles.
-// MINW: waves per SIMD the register allocation aims at (3 costs d_head 64 a few spilled address registers).
-template <int DHP, int MINW>
-__global__ void __launch_bounds__(256, MINW) attn_bwd_dkv_bf16_kernel(const AttnK p) {
-  constexpr int KC = DHP / 16, DT = DHP / 32, TILE = 64 * DHP;
+// MINW: waves per SIMD, exactly: told only the least, the compiler schedules the variant of two for three as well, without the fragments
+// fetched ahead that two need (8 x 4096 queries, 77 keys: 102 us instead of 75).
+template <int DHP, int KC, int MINW>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MINW, MINW))) attn_bwd_dkv_bf16_kernel(const AttnK p) {
+  constexpr int DT = DHP / 32, TILE = 64 * DHP;
   __shared__ __attribute__((aligned(1024))) bf16 Qs[2][TILE];
   __shared__ __attribute__((aligned(1024))) bf16 Ds[2][TILE];
   __shared__ __attribute__((aligned(16))) float lse_s[2][64];
   __shared__ __attribute__((aligned(16))) float dlt_s[2][64];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 5, l32 = lane & 31;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 5, l32 = lane & 31;
   int ktile, bh;
   const int qs = blockIdx.x % p.qsplits;
   attn_block_map(blockIdx.x / p.qsplits, (p.Nk + 127) / 128, p.B * p.H, ktile, bh);
@@ -414,8 +461,8 @@ __global__ void __launch_bounds__(256, MINW) attn_bwd_dkv_bf16_kernel(const Attn
   const bool kok = ki < p.Nk;
   const bf16* qb = (const bf16*)p.q + (size_t)b * p.Nq * p.ldq + h * p.dh;
   const bf16* dob = (const bf16*)p.dout + (size_t)b * p.Nq * p.lddo + h * p.dh;
-  const rsrc_t qr = make_rsrc(qb, attn_slice_bytes(p.Nq, p.ldq, p.dh));
-  const rsrc_t dr = make_rsrc(dob, attn_slice_bytes(p.Nq, p.lddo, p.dh));
+  const u32x4 qr = make_raw_rsrc(qb, attn_slice_bytes(p.Nq, p.ldq, p.dh));
+  const u32x4 dr = make_raw_rsrc(dob, attn_slice_bytes(p.Nq, p.lddo, p.dh));
   const bf16* krow = (const bf16*)p.k + ((size_t)b * p.Nk + ki) * p.ldk + h * p.dh;
   const bf16* vrow = (const bf16*)p.v + ((size_t)b * p.Nk + ki) * p.ldv + h * p.dh;
   const float* lse_b = p.lse + ((size_t)b * p.H + h) * p.Nq;
@@ -424,7 +471,7 @@ __global__ void __launch_bounds__(256, MINW) attn_bwd_dkv_bf16_kernel(const Attn
   // this workgroup's share of the 64-query tiles
   const int nqt_all = (p.Nq + 63) / 64, tps = (nqt_all + p.qsplits - 1) / p.qsplits;
   const int qt0 = qs * tps, nqt = min(nqt_all, qt0 + tps);
-  AttnFragOff<DHP> fo;
+  AttnFragOff<DHP, KC> fo;
   fo.init(lane);
   AttnTileCopy<DHP> cq, cd;
   cq.init(wave, lane, p.ldq, p.dh);
@@ -433,16 +480,17 @@ __global__ void __launch_bounds__(256, MINW) attn_bwd_dkv_bf16_kernel(const Attn
     cq.issue(qr, qt0 * 64, p.ldq, Qs[0], wave);
     cd.issue(dr, qt0 * 64, p.lddo, Ds[0], wave);
   }
-  float r_lse = 0.f, r_dlt = 0.f;
+  // Statistics of a query tile: wave 0 fetches lse, wave 1 delta.  The value stays as loaded until the end of the tile before (a conversion
+  // behind the load would wait for it there, and with it for the tile copies issued ahead of it: 373 -> 356 us at 40 heads of 4096 tokens).
+  float stat = 0.f;
+  const float* stat_b = wave == 0 ? lse_b : dlt_b;
   auto load_stats = [&](int qt) {
-    if (tid < 64) {
-      const int qi = qt * 64 + tid;
-      r_lse = qi < p.Nq ? lse_b[qi] * LOG2E : INFINITY;
-      r_dlt = qi < p.Nq ? dlt_b[qi] : 0.f;
-    }
+    if (wave < 2) stat = stat_b[min((uint32_t)(qt * 64 + lane), (uint32_t)p.Nq - 1u)];
   };
-  auto store_stats = [&](int buf) {
-    if (tid < 64) { lse_s[buf][tid] = r_lse; dlt_s[buf][tid] = r_dlt; }
+  auto store_stats = [&](int qt, int buf) {
+    const bool ok = qt * 64 + lane < p.Nq;
+    if (wave == 0) lse_s[buf][lane] = ok ? stat * LOG2E : INFINITY;
+    if (wave == 1) dlt_s[buf][lane] = ok ? -stat : 0.f;
   };
   load_stats(qt0);
 
@@ -459,12 +507,13 @@ __global__ void __launch_bounds__(256, MINW) attn_bwd_dkv_bf16_kernel(const Attn
 #pragma unroll
     for (int r = 0; r < 16; ++r) { dkacc[i][r] = 0.f; dvacc[i][r] = 0.f; }
 
-  store_stats(0);
+  store_stats(qt0, 0);
   wait_vmcnt<0>();
   __syncthreads();
 
-  for (int qt = qt0; qt < nqt; ++qt) {
-    const int buf = (qt - qt0) & 1;
+  auto tile = [&](int qt, auto bc) {
+    take_turns(p.even, qt);
+    constexpr int buf = bc();
     const bool more = qt + 1 < nqt;
     if (more) {
       cq.issue(qr, (qt + 1) * 64, p.ldq, Qs[buf ^ 1], wave);
@@ -473,33 +522,35 @@ __global__ void __launch_bounds__(256, MINW) attn_bwd_dkv_bf16_kernel(const Attn
     }
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-      f32x16 s, dp;
+      if (MINW > 2) __builtin_amdgcn_sched_barrier(0);      // (the halves' fragments would overlap in registers, past the 168 of three waves per SIMD)
+      f32x16 s, dp;      // dP - delta: the products accumulate onto -delta
 #pragma unroll
-      for (int r = 0; r < 16; ++r) { s[r] = 0.f; dp[r] = 0.f; }
+      for (int r4 = 0; r4 < 4; ++r4) {
+        const f32x4 d4 = *reinterpret_cast<const f32x4*>(&dlt_s[buf][32 * t + 8 * r4 + 4 * g]);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) { s[4 * r4 + u] = 0.f; dp[4 * r4 + u] = d4[u]; }
+      }
 #pragma unroll
       for (int c = 0; c < KC; ++c) {
         s = mfma32(fo.row_frag(Qs[buf], t, c), kf[c], s);
         dp = mfma32(fo.row_frag(Ds[buf], t, c), vf[c], dp);
       }
-      f32x16 ds;
 #pragma unroll
       for (int r4 = 0; r4 < 4; ++r4) {
         const f32x4 l4 = *reinterpret_cast<const f32x4*>(&lse_s[buf][32 * t + 8 * r4 + 4 * g]);
-        const f32x4 d4 = *reinterpret_cast<const f32x4*>(&dlt_s[buf][32 * t + 8 * r4 + 4 * g]);
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
           const int r = 4 * r4 + u;
           // a lane whose key is past Nk computes garbage that stays in its own accumulator columns,
           // which are never stored; queries past Nq have lse = +inf, hence pr = 0
-          const float pr = __builtin_amdgcn_exp2f(fmaf(s[r], p.scale_log2, -l4[u]));
-          s[r] = pr;
-          ds[r] = pr * (dp[r] - d4[u]);
+          s[r] = __builtin_amdgcn_exp2f(fmaf(s[r], p.scale_log2, -l4[u]));
+          dp[r] *= s[r];
         }
       }
 #pragma unroll
       for (int cc = 0; cc < 2; ++cc) {
         const bf16x8 pf = pack8(s, 8 * cc);
-        const bf16x8 dsf = pack8(ds, 8 * cc);
+        const bf16x8 dsf = pack8(dp, 8 * cc);
 #pragma unroll
         for (int i = 0; i < DT; ++i) {
           dvacc[i] = mfma32(fo.tr_frag(Ds[buf], 32 * t + 16 * cc, i), pf, dvacc[i]);
@@ -507,10 +558,12 @@ __global__ void __launch_bounds__(256, MINW) attn_bwd_dkv_bf16_kernel(const Attn
         }
       }
     }
-    if (more) store_stats(buf ^ 1);
+    if (MINW > 2) __builtin_amdgcn_sched_barrier(0);
+    if (more) store_stats(qt + 1, buf ^ 1);
     wait_vmcnt<0>();
     __syncthreads();
-  }
+  };
+  two_stages(qt0, nqt, tile);
   if (kok && p.qsplits > 1) {
     // fp32 partial sums of this query range; reduced in a fixed order by attn_dkv_reduce_kernel
     const size_t hd = (size_t)p.H * p.dh, rows = (size_t)p.B * p.Nk;
@@ -688,7 +741,7 @@ static AttnK make_k(const AttnArgs& a) {
   k.q = a.q; k.ldq = a.ldq; k.k = a.k; k.ldk = a.ldk; k.v = a.v; k.ldv = a.ldv; k.o = a.o; k.ldo = a.ldo; k.lse = a.lse;
   k.dout = a.dout; k.lddo = a.lddo; k.delta = a.delta; k.dq = a.dq; k.lddq = a.lddq; k.dk = a.dk; k.lddk = a.lddk;
   k.dv = a.dv; k.lddv = a.lddv;
-  k.qsplits = 1; k.dkv_partial = nullptr;
+  k.even = 0; k.qsplits = 1; k.dkv_partial = nullptr;
   return k;
 }
 
@@ -719,23 +772,34 @@ static int check_attn(const AttnArgs& a, bool bwd) {
   return DP_OK;
 }
 
+// Whether `blocks` workgroups, `per_cu` of which fit a CU, are all resident and share CUs.
+static int takes_turns(long blocks, int per_cu) { return blocks > 256 && blocks <= 256L * per_cu; }
+
 size_t attn_dkv_ws_bytes(int B, int H, int Nk, int d_head) { return 2 * (size_t)16 * B * Nk * H * d_head * sizeof(float); }
+
+// Calls f(padded head width of the tiles, 16-column steps of the products over the head dimension): tiles are 64 or 96 columns wide for the
+// copies and the transposing reads, the steps end with the head (d_head 72: five of six).
+template <class F> static void attn_dispatch(int d_head, F f) {
+  using std::integral_constant;
+  if (d_head <= 48) f(integral_constant<int, 64>(), integral_constant<int, 3>());
+  else if (d_head <= 64) f(integral_constant<int, 64>(), integral_constant<int, 4>());
+  else if (d_head <= 80) f(integral_constant<int, 96>(), integral_constant<int, 5>());
+  else f(integral_constant<int, 96>(), integral_constant<int, 6>());
+}
 
 int launch_attn_fwd(const AttnArgs& a, hipStream_t s) {
   if (int e = check_attn(a, false)) return e;
-  const AttnK k = make_k(a);
+  AttnK k = make_k(a);
+  k.even = takes_turns((long)((a.Nq + 127) / 128) * a.B * a.H, a.d_head <= 64 ? 4 : 3);
   const double fl = 4.0 * a.B * a.H * (double)a.Nq * a.Nk * a.d_head;
   const double by = dtype_size(a.dtype) * (double)a.B * a.H * a.d_head * (2.0 * a.Nq + 2.0 * a.Nk);
   KScope ks(a.dtype == BF16 ? KK_ATTN_FWD : KK_ATTN_F32, fl, by, s, a.Nq, a.Nk, a.d_head);
   if (a.dtype == BF16) {
     dim3 grid(((a.Nq + 127) / 128) * a.B * a.H);
-    if (a.d_head <= 64) {
-      if (a.causal) hipLaunchKernelGGL((attn_fwd_bf16_kernel<64, true>), grid, dim3(256), 0, s, k);
-      else hipLaunchKernelGGL((attn_fwd_bf16_kernel<64, false>), grid, dim3(256), 0, s, k);
-    } else {
-      if (a.causal) hipLaunchKernelGGL((attn_fwd_bf16_kernel<96, true>), grid, dim3(256), 0, s, k);
-      else hipLaunchKernelGGL((attn_fwd_bf16_kernel<96, false>), grid, dim3(256), 0, s, k);
-    }
+    attn_dispatch(a.d_head, [&](auto dhp, auto kc) {
+      if (a.causal) hipLaunchKernelGGL((attn_fwd_bf16_kernel<dhp, kc, true>), grid, dim3(256), 0, s, k);
+      else hipLaunchKernelGGL((attn_fwd_bf16_kernel<dhp, kc, false>), grid, dim3(256), 0, s, k);
+    });
   } else {
     hipLaunchKernelGGL(attn_fwd_f32_kernel, dim3(a.Nq, a.B * a.H), dim3(64), (size_t)a.Nk * sizeof(float), s, k, a.causal);
   }
@@ -744,16 +808,16 @@ int launch_attn_fwd(const AttnArgs& a, hipStream_t s) {
 
 int launch_attn_bwd(const AttnArgs& a, hipStream_t s) {
   if (int e = check_attn(a, true)) return e;
-  const AttnK k = make_k(a);
+  AttnK k = make_k(a);
   if (a.dtype == BF16) {
+    k.even = takes_turns((long)((a.Nq + 127) / 128) * a.B * a.H, a.d_head <= 64 ? 3 : 2);
     dim3 gq(((a.Nq + 127) / 128) * a.B * a.H), gk(((a.Nk + 127) / 128) * a.B * a.H);
     // algorithmic backward work = 2x forward, split evenly between the two kernels for accounting
     const double fl = 4.0 * a.B * a.H * (double)a.Nq * a.Nk * a.d_head;
     const double by = 2.0 * (double)a.B * a.H * a.d_head * (3.0 * a.Nq + 2.0 * a.Nk);
     {
       KScope ks(KK_ATTN_BWD_DQ, fl, by, s, a.Nq, a.Nk, a.d_head);
-      if (a.d_head <= 64) hipLaunchKernelGGL(attn_bwd_dq_bf16_kernel<64>, gq, dim3(256), 0, s, k);
-      else hipLaunchKernelGGL(attn_bwd_dq_bf16_kernel<96>, gq, dim3(256), 0, s, k);
+      attn_dispatch(a.d_head, [&](auto dhp, auto kc) { hipLaunchKernelGGL((attn_bwd_dq_bf16_kernel<dhp, kc>), gq, dim3(256), 0, s, k); });
     }
     {
       // few key tiles (cross-attention to 77 keys): split the query range over more workgroups
@@ -764,16 +828,17 @@ int launch_attn_bwd(const AttnArgs& a, hipStream_t s) {
       if (base_blocks < 256) qsplit = (int)std::min<long>(std::min<long>(16, nqt / 2 > 0 ? nqt / 2 : 1), (512 + base_blocks - 1) / base_blocks);
       const size_t need = 2 * (size_t)qsplit * a.B * a.Nk * a.H * a.d_head * sizeof(float);
       if (qsplit > 1 && (!a.dkv_ws || a.dkv_ws_bytes < need || ((uintptr_t)a.dkv_ws % 16))) qsplit = 1;
+      k2.even = takes_turns((long)gk.x * qsplit, a.d_head <= 64 && qsplit == 1 && gk.x > 2 * 256 ? 3 : 2);
       k2.qsplits = qsplit; k2.dkv_partial = a.dkv_ws;
       dim3 gk2(gk.x * qsplit);
       {
         KScope ks(KK_ATTN_BWD_DKV, fl, by, s, a.Nq, a.Nk, a.d_head);
-        // Two workgroups per CU hold 512 at a time; a larger grid gains more from a third resident workgroup
-        // than the tighter register budget costs (1024 tokens, 640 workgroups: 120 -> 110 us for the whole
-        // backward), a smaller one only pays for it (77 keys: 43 -> 46 us)
-        if (a.d_head <= 64 && qsplit == 1 && gk.x > 2 * 256) hipLaunchKernelGGL((attn_bwd_dkv_bf16_kernel<64, 3>), gk2, dim3(256), 0, s, k2);
-        else if (a.d_head <= 64) hipLaunchKernelGGL((attn_bwd_dkv_bf16_kernel<64, 2>), gk2, dim3(256), 0, s, k2);
-        else hipLaunchKernelGGL((attn_bwd_dkv_bf16_kernel<96, 2>), gk2, dim3(256), 0, s, k2);
+        // Two workgroups per CU hold 512 at a time; a larger grid gains more from a third than the tighter register budget costs (80
+        // heads of 1024 tokens, 640 workgroups: 69 -> 53 us), a smaller one only pays for it (77 keys, 1024 queries: 24 -> 31 us)
+        attn_dispatch(a.d_head, [&](auto dhp, auto kc) {
+          if (dhp == 64 && qsplit == 1 && gk.x > 2 * 256) hipLaunchKernelGGL((attn_bwd_dkv_bf16_kernel<dhp, kc, dhp == 64 ? 3 : 2>), gk2, dim3(256), 0, s, k2);
+          else hipLaunchKernelGGL((attn_bwd_dkv_bf16_kernel<dhp, kc, 2>), gk2, dim3(256), 0, s, k2);
+        });
       }
       if (qsplit > 1) {
         const size_t rows = (size_t)a.B * a.Nk; const int hd = a.H * a.d_head;

@@ -1,0 +1,99 @@
+"""The attention kernels where a path of theirs begins or ends: tile edges of both sequences, every number of 16-column steps of the head, and
+inputs whose softmax reference has to move late, against the oracle's operations."""
+import numpy as np
+import pytest
+
+import synth_inputs as si
+from oracle import ops
+
+pytestmark = pytest.mark.gpu
+
+TOL_BF16 = 2e-2      # operands, probabilities and results in bf16 (2^-9 each), fp32 sums: max error over the largest element
+
+
+def _late_moves(logits):
+    """Replays the forward's rule on the oracle's logits: a wave (32 queries) moves its references at a tile of 64 keys when the probabilities that
+    one of its lanes adds up (32 keys: accumulator rows 8 i + 4 g .. + 3 of both halves for lane half g) exceed 2^8 relative to the old reference; the new
+    one is 2^8 above the largest score.  (steps after the first tile, moves among them)"""
+    s = np.asarray(logits) * 1.4426950408889634
+    s = s.reshape((-1,) + s.shape[-2:])
+    half = (np.arange(64) // 4) % 2
+    steps = moves = 0
+    for one in s:
+        for q0 in range(0, one.shape[0], 32):
+            blk = one[q0:q0 + 32]
+            ref = np.full(blk.shape[0], -np.inf)
+            for k0 in range(0, blk.shape[1], 64):
+                t = blk[:, k0:k0 + 64]
+                if k0 > 0:
+                    with np.errstate(over="ignore"):
+                        e = np.exp2(t - ref[:, None])
+                    h = half[:t.shape[1]]
+                    bump = bool(np.any(e[:, h == 0].sum(1) > 256) or np.any(e[:, h == 1].sum(1) > 256))
+                    steps += 1
+                    moves += bump
+                if k0 == 0 or bump:
+                    ref = np.maximum(ref, t.max(axis=1) + 8)
+    return steps, moves
+
+
+def _run(B_, H, Nq, Nk, dh, gain, shift, seed=5, backward=True):
+    import torch
+    from paper_2405_01248_amd import binding as B
+    from paper_2405_01248_amd.harness import _dev_to_np, _np_to_dev, rel_err
+    d = H * dh
+    q, k, v, do = si.make_attention_inputs(B_, H, Nq, Nk, dh, seed=seed, gain=gain, row_shift=shift)
+    dq_, dk_, dv_, ddo = (_np_to_dev(t, "bf16") for t in (q, k, v, do))
+    o = torch.zeros((B_, Nq, d), dtype=torch.bfloat16, device="cuda:0")
+    lse = torch.zeros((B_, H, Nq), dtype=torch.float32, device="cuda:0")
+    scale = 1.0 / np.sqrt(dh)
+    B.op_attention_fwd(B.DP_BF16, B_, H, Nq, Nk, dh, False, scale, dq_, d, dk_, d, dv_, d, o, d, lse)
+    torch.cuda.synchronize()
+    errs = {"o": rel_err(_dev_to_np(o), ops.attention_fwd(q, k, v, H, False))}
+    if backward:
+        gq, gk, gv = (torch.zeros_like(t) for t in (dq_, dk_, dv_))
+        delta = torch.zeros((B_, H, Nq), dtype=torch.float32, device="cuda:0")
+        B.op_attention_bwd(B.DP_BF16, B_, H, Nq, Nk, dh, scale, dq_, d, dk_, d, dv_, d, o, d, lse, ddo, d, delta, gq, d, gk, d, gv, d)
+        torch.cuda.synchronize()
+        for n, g, r in zip(("dq", "dk", "dv"), (gq, gk, gv), ops.attention_bwd(do, q, k, v, H, False)):
+            errs[n] = rel_err(_dev_to_np(g), r)
+    return q, k, errs
+
+
+@pytest.mark.parametrize("dh", [8, 40, 48, 56, 64, 72, 80, 88, 96])
+@pytest.mark.parametrize("Nq,Nk", [(1, 1), (33, 65), (129, 64), (64, 129), (191, 257)])
+def test_edges_of_tiles_and_heads(Nq, Nk, dh):
+    _, _, errs = _run(1, 2, Nq, Nk, dh, 1.0, 0.0)
+    print(f"\n[attention q{Nq} k{Nk} dh{dh}] {errs}", flush=True)
+    if Nk == 1:      # one key: the probabilities are 1 and dS = dP - delta is 0 but for the rounding of O, which a relative error of dq, dk would show
+        errs.pop("dq"), errs.pop("dk")
+    assert max(errs.values()) <= TOL_BF16, errs
+
+
+@pytest.mark.parametrize("case", [(1, 3, 200, 449, 64, 16.0, 80.0), (1, 2, 160, 384, 72, 8.0, 40.0), (1, 2, 96, 320, 40, 16.0, 0.0)])
+def test_late_moves_of_the_softmax_reference(case):
+    from softmax_schedule import head_logits
+    q, k, errs = _run(*case)
+    steps, moves = _late_moves(head_logits(q, k, case[1]))
+    print(f"\n[attention late moves {case}] {moves} of {steps} steps, {errs}", flush=True)
+    assert moves > 0, "the inputs do not reach the path"
+    assert max(errs.values()) <= TOL_BF16, errs
+
+
+@pytest.mark.parametrize("heads,tokens", [(72, 512), (264, 128)])
+def test_waves_that_take_turns_give_the_same_bits(heads, tokens):
+    """More workgroups than CUs, all resident: wave priorities rotate.  They change the order in time and nothing else: the first head alone (few workgroups, no
+    turns) has the same bits."""
+    import torch
+    from paper_2405_01248_amd import binding as B
+    dh, d = 64, heads * 64
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    q, k, v = (torch.randn((tokens, d), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(3))
+    outs = []
+    for h in (heads, 1):
+        o = torch.zeros((tokens, d), dtype=torch.bfloat16, device="cuda")
+        lse = torch.zeros((h, tokens), dtype=torch.float32, device="cuda")
+        B.op_attention_fwd(B.DP_BF16, 1, h, tokens, tokens, dh, False, dh ** -0.5, q, d, k, d, v, d, o, d, lse)
+        torch.cuda.synchronize()
+        outs.append(o[:, :dh].clone())
+    assert torch.equal(outs[0], outs[1])
