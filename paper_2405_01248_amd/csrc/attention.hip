@@ -27,6 +27,7 @@
 #include "dp_ktime.h"
 #include <math.h>
 #include <algorithm>
+#include <atomic>
 #include <type_traits>
 
 namespace dp {
@@ -107,16 +108,16 @@ struct AttnFragOff {
   using T = AttnTile<DHP>;
   int row[KC], tr_lo[DHP / 32], tr_hi[DHP / 32];
   __device__ __forceinline__ void init(int lane) {
-    const int g = lane >> 5, l32 = lane & 31, b = lane >> 4, j = lane & 15;
+    const int g = lane >> 5, l32 = lane & 31;
 #pragma unroll
     for (int c = 0; c < KC; ++c) row[c] = l32 * DHP + 8 * ((2 * c + g) ^ T::key(l32));
-    const int r = 4 * (b >> 1) + (j >> 2);
 #pragma unroll
-    for (int i = 0; i < DHP / 32; ++i) {
-      const int chunk = 4 * i + 2 * (b & 1) + ((j & 3) >> 1);
-      tr_lo[i] = r * DHP + 8 * (chunk ^ T::key(r)) + 4 * (j & 1);
-      tr_hi[i] = (r + 8) * DHP + 8 * (chunk ^ T::key(r + 8)) + 4 * (j & 1);
-    }
+    for (int i = 0; i < DHP / 32; ++i) transposed(lane, i, tr_lo[i], tr_hi[i]);
+  }
+  static __device__ __forceinline__ void transposed(int lane, int i, int& lo, int& hi) {
+    const int b = lane >> 4, j = lane & 15, r = 4 * (b >> 1) + (j >> 2), chunk = 4 * i + 2 * (b & 1) + ((j & 3) >> 1);
+    lo = r * DHP + 8 * (chunk ^ T::key(r)) + 4 * (j & 1);
+    hi = (r + 8) * DHP + 8 * (chunk ^ T::key(r + 8)) + 4 * (j & 1);
   }
   __device__ __forceinline__ bf16x8 row_frag(const bf16* tile, int t, int c) const {
     return *reinterpret_cast<const bf16x8*>(tile + row[c] + 32 * DHP * t);
@@ -441,6 +442,45 @@ __global__ void __launch_bounds__(256, DHP == 64 ? 3 : 2) attn_bwd_dq_bf16_kerne
   }
 }
 
+// A wave's dK and dV (lane: key ki): fp32 parts of a query share, reduced in a fixed order by attn_dkv_reduce_kernel, or the result.
+template <int DT>
+__device__ __forceinline__ void attn_store_dkv(const AttnK& p, const f32x16 (&dkacc)[DT], const f32x16 (&dvacc)[DT], int qs, int b, int h, int ki, bool kok, int g) {
+  if (kok && p.qsplits > 1) {
+    const size_t hd = (size_t)p.H * p.dh, rows = (size_t)p.B * p.Nk;
+    float* pk = p.dkv_partial + ((size_t)qs * rows + (size_t)b * p.Nk + ki) * hd + h * p.dh;
+    float* pv = pk + (size_t)p.qsplits * rows * hd;
+#pragma unroll
+    for (int i = 0; i < DT; ++i)
+#pragma unroll
+      for (int r4 = 0; r4 < 4; ++r4) {
+        const int col = 32 * i + 8 * r4 + 4 * g;
+        if (col < p.dh) {
+          f32x4 ok_, ov;
+#pragma unroll
+          for (int u = 0; u < 4; ++u) { ok_[u] = dkacc[i][4 * r4 + u] * p.scale; ov[u] = dvacc[i][4 * r4 + u]; }
+          *reinterpret_cast<f32x4*>(pk + col) = ok_;
+          *reinterpret_cast<f32x4*>(pv + col) = ov;
+        }
+      }
+  } else if (kok) {
+    bf16* dkb = (bf16*)p.dk + ((size_t)b * p.Nk + ki) * p.lddk + h * p.dh;
+    bf16* dvb = (bf16*)p.dv + ((size_t)b * p.Nk + ki) * p.lddv + h * p.dh;
+#pragma unroll
+    for (int i = 0; i < DT; ++i)
+#pragma unroll
+      for (int r4 = 0; r4 < 4; ++r4) {
+        const int col = 32 * i + 8 * r4 + 4 * g;
+        if (col < p.dh) {
+          bf16x4 ok_, ov;
+#pragma unroll
+          for (int u = 0; u < 4; ++u) { ok_[u] = (bf16)(dkacc[i][4 * r4 + u] * p.scale); ov[u] = (bf16)dvacc[i][4 * r4 + u]; }
+          *reinterpret_cast<bf16x4*>(dkb + col) = ok_;
+          *reinterpret_cast<bf16x4*>(dvb + col) = ov;
+        }
+      }
+  }
+}
+
 // ------------------------------------------------------------------ dK, dV (bf16)
 // grid.x = ceil(Nk / 128) * qsplits; each wave owns 32 keys and walks its share of the query tiles.
 // MINW: waves per SIMD, exactly: told only the least, the compiler schedules the variant of two for three as well, without the fragments
@@ -564,41 +604,223 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MINW, 
     __syncthreads();
   };
   two_stages(qt0, nqt, tile);
-  if (kok && p.qsplits > 1) {
-    // fp32 partial sums of this query range; reduced in a fixed order by attn_dkv_reduce_kernel
-    const size_t hd = (size_t)p.H * p.dh, rows = (size_t)p.B * p.Nk;
-    float* pk = p.dkv_partial + ((size_t)qs * rows + (size_t)b * p.Nk + ki) * hd + h * p.dh;
-    float* pv = pk + (size_t)p.qsplits * rows * hd;
+  attn_store_dkv<DT>(p, dkacc, dvacc, qs, b, h, ki, kok, g);
+}
+
+// ------------------------------------------------------------------ dQ, dK, dV at once (bf16, at most 32 NW keys)
+// A workgroup has all keys of its (batch, head), 32 per wave, and walks the queries (of its share) in tiles of 64: scores, dP and the
+// exponentials are formed once where the two kernels above form them twice, and delta and the statistics need no pass of their own.
+// Per tile: every wave adds to its keys' dK and dV and leaves dS in LDS ([key][query], the layout of a 64-wide tile); behind a barrier
+// the dQ of the tile, 2 DHP / 32 blocks of 32 x 32, is formed from it and the keys in LDS, by as many waves, while the next
+// tile's delta = rowsum(dO * O) is formed from its O (registers, fetched a tile ahead) and its dO (LDS).
+//
+// Why: what these kernels are bound by, power and issue slots, is spent in proportion to the products, five instead of seven, and the
+// exponentials, one instead of two.  Both kernels -> this one, inside a step: 32 x 16 heads of 256 tokens, width 72, 91 -> 68 us; 77 keys and
+// 8 x 5 heads of 4096 queries 59 -> 40, 8 x 10 of 1024 40 -> 22, 2 x 20 of 513 23 -> 15.  A workgroup of the first shape takes 32 us: 6 until the
+// keys are there (K and V are read by rows through LDS; fragments straight from memory took 9), 5.4 per tile of which 3 are the products of the
+// first part, 3 to store.
+template <int DHP, int NW> struct AttnShort {
+  static constexpr int TILE = 64 * DHP, K = 32 * NW * DHP, DS = 32 * NW * 64;                            // elements
+  static_assert(K <= 2 * TILE + DS, "V passes through the second stage and dS");
+  static constexpr size_t BYTES = (size_t)(K + 4 * TILE + DS) * sizeof(bf16) + 2 * 64 * sizeof(float);
+};
+template <int DHP, int KC, int NW>
+__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) attn_bwd_short_bf16_kernel(const AttnK p) {
+  using S = AttnShort<DHP, NW>;
+  constexpr int DT = DHP / 32, TILE = S::TILE;
+  constexpr bool TIGHT = false;      // 256 registers: the two halves of a tile must not be scheduled into each other
+  constexpr int LPR = DHP == 64 ? 8 : 16, RPP = 64 / LPR, PASSES = 64 / (NW * RPP);      // delta: lanes a row, rows a pass of a wave
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  // what the products of every tile read comes first: an LDS instruction reaches 64 KB past its base register
+  bf16* const QD = reinterpret_cast<bf16*>(smem);      // two stages of Q and dO
+  bf16* const dS = QD + 4 * TILE;
+  bf16* const Vt = QD + 2 * TILE;                      // V on its way to the registers: where the second stage and dS will be
+  bf16* const Kt = dS + S::DS;
+  float* const lse_s = reinterpret_cast<float*>(Kt + S::K);
+  float* const dlt_s = lse_s + 64;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 5, l32 = lane & 31;
+  int qs, bh;
+  attn_block_map(blockIdx.x, p.qsplits, p.B * p.H, qs, bh);
+  const int b = bh / p.H, h = bh % p.H, ki = 32 * wave + l32, groups = (p.Nk + 31) / 32;      // (a wave past the last group has copies, dQ and delta)
+  const bool kok = ki < p.Nk;
+  const bf16* qb = (const bf16*)p.q + (size_t)b * p.Nq * p.ldq + h * p.dh;
+  const bf16* dob = (const bf16*)p.dout + (size_t)b * p.Nq * p.lddo + h * p.dh;
+  const bf16* ob = (const bf16*)p.o + (size_t)b * p.Nq * p.ldo + h * p.dh;
+  const bf16* kb = (const bf16*)p.k + (size_t)b * p.Nk * p.ldk + h * p.dh;
+  const bf16* vb = (const bf16*)p.v + (size_t)b * p.Nk * p.ldv + h * p.dh;
+  const float* lse_b = p.lse + ((size_t)b * p.H + h) * p.Nq;
+  const u32x4 qr = make_raw_rsrc(qb, attn_slice_bytes(p.Nq, p.ldq, p.dh)), dr = make_raw_rsrc(dob, attn_slice_bytes(p.Nq, p.lddo, p.dh));
+  const u32x4 kr = make_raw_rsrc(kb, attn_slice_bytes(p.Nk, p.ldk, p.dh)), vr = make_raw_rsrc(vb, attn_slice_bytes(p.Nk, p.ldv, p.dh));
+  const int nqt_all = (p.Nq + 63) / 64, tps = (nqt_all + p.qsplits - 1) / p.qsplits;
+  const int qt0 = qs * tps, nqt = min(nqt_all, qt0 + tps);      // no share is empty
+
+  AttnFragOff<DHP, KC> fo;
+  fo.init(lane);
+  // four waves copy a query tile of both kinds, eight one kind each
+  AttnTileCopy<DHP> ck, cv, cq, cd;
+  ck.init(wave, lane, p.ldk, p.dh);
+  cv.init(wave, lane, p.ldv, p.dh);
+  cq.init(wave & 3, lane, p.ldq, p.dh);
+  cd.init(wave & 3, lane, p.lddo, p.dh);
+  auto issue = [&](int qt) {
+    const int at = (qt - qt0) & 1;
+    if (NW == 4 || wave < 4) cq.issue(qr, qt * 64, p.ldq, QD + at * 2 * TILE, wave & 3);
+    if (NW == 4 || wave >= 4) cd.issue(dr, qt * 64, p.lddo, QD + (at * 2 + 1) * TILE, wave & 3);
+  };
+  // O and the logarithms of the sums of a tile, kept as loaded until delta is due
+  bf16x8 of[PASSES];
+  float stat = 0.f;
+  const int drow = wave * RPP + lane / LPR, dchunk = lane % LPR;
+  auto load_o = [&](int qt) {
 #pragma unroll
-    for (int i = 0; i < DT; ++i)
+    for (int i = 0; i < PASSES; ++i) {
+      const int q = qt * 64 + i * NW * RPP + drow;
+      of[i] = ld8(ob + (size_t)q * p.ldo + 8 * dchunk, q < p.Nq && 8 * dchunk < p.dh);
+    }
+    if (wave == 0) stat = lse_b[min((uint32_t)(qt * 64 + lane), (uint32_t)p.Nq - 1u)];
+  };
+  auto statistics = [&](int qt) {
+    const bf16* tile = QD + (((qt - qt0) & 1) * 2 + 1) * TILE;
 #pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) {
-        const int col = 32 * i + 8 * r4 + 4 * g;
-        if (col < p.dh) {
-          f32x4 ok_, ov;
+    for (int i = 0; i < PASSES; ++i) {
+      const int row = i * NW * RPP + drow;
+      float v = 0.f;
+      if (dchunk < DHP / 8) {
+        const bf16x8 df = *reinterpret_cast<const bf16x8*>(tile + row * DHP + 8 * (dchunk ^ AttnTile<DHP>::key(row)));
 #pragma unroll
-          for (int u = 0; u < 4; ++u) { ok_[u] = dkacc[i][4 * r4 + u] * p.scale; ov[u] = dvacc[i][4 * r4 + u]; }
-          *reinterpret_cast<f32x4*>(pk + col) = ok_;
-          *reinterpret_cast<f32x4*>(pv + col) = ov;
-        }
+        for (int u = 0; u < 8; ++u) v = fmaf((float)of[i][u], (float)df[u], v);
       }
-  } else if (kok) {
-    bf16* dkb = (bf16*)p.dk + ((size_t)b * p.Nk + ki) * p.lddk + h * p.dh;
-    bf16* dvb = (bf16*)p.dv + ((size_t)b * p.Nk + ki) * p.lddv + h * p.dh;
+      v += lane_dpp<0xB1>(v);       // quad_perm:[1,0,3,2]
+      v += lane_dpp<0x4E>(v);       // quad_perm:[2,3,0,1]
+      v += lane_dpp<0x141>(v);      // row_half_mirror: the other quad of eight
+      if (LPR == 16) v += lane_dpp<0x128>(v);      // row_ror:8
+      if (dchunk == 0) dlt_s[row] = -v;
+    }
+    if (wave == 0) lse_s[lane] = qt * 64 + lane < p.Nq ? stat * LOG2E : INFINITY;
+  };
+
+  ck.issue(kr, 0, p.ldk, Kt, wave);
+  cv.issue(vr, 0, p.ldv, Vt, wave);
+  ck.issue(kr, 16 * NW, p.ldk, Kt + 16 * NW * DHP, wave);
+  cv.issue(vr, 16 * NW, p.ldv, Vt + 16 * NW * DHP, wave);
+  issue(qt0);
+  load_o(qt0);
+  f32x16 dkacc[DT], dvacc[DT];
 #pragma unroll
-    for (int i = 0; i < DT; ++i)
+  for (int i = 0; i < DT; ++i)
 #pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) {
-        const int col = 32 * i + 8 * r4 + 4 * g;
-        if (col < p.dh) {
-          bf16x4 ok_, ov;
+    for (int r = 0; r < 16; ++r) { dkacc[i][r] = 0.f; dvacc[i][r] = 0.f; }
+  wait_vmcnt<0>();
+  __syncthreads();
+  bf16x8 kf[KC], vf[KC];      // rows past the last key are zero
 #pragma unroll
-          for (int u = 0; u < 4; ++u) { ok_[u] = (bf16)(dkacc[i][4 * r4 + u] * p.scale); ov[u] = (bf16)dvacc[i][4 * r4 + u]; }
-          *reinterpret_cast<bf16x4*>(dkb + col) = ok_;
-          *reinterpret_cast<bf16x4*>(dvb + col) = ov;
-        }
-      }
+  for (int c = 0; c < KC; ++c) {
+    kf[c] = fo.row_frag(Kt + 32 * wave * DHP, 0, c);
+    vf[c] = fo.row_frag(Vt + 32 * wave * DHP, 0, c);
   }
+  statistics(qt0);
+  lds_barrier();
+  if (wave >= groups) {      // keys that are not there: the products for dQ run over all of them
+#pragma unroll
+    for (int i = 0; i < 4; ++i) *reinterpret_cast<u32x4*>(dS + 32 * wave * 64 + 512 * i + 8 * lane) = u32x4{0u, 0u, 0u, 0u};
+  }
+  if (qt0 + 1 < nqt) {
+    issue(qt0 + 1);
+    load_o(qt0 + 1);
+  }
+
+  auto frag = [](const bf16* lo, const bf16* hi) {
+    const bf16x4 a = lds_read_tr(lo), c = lds_read_tr(hi);
+    return __builtin_shufflevector(a, c, 0, 1, 2, 3, 4, 5, 6, 7);
+  };
+  auto tile = [&](int qt, auto bc) {
+    const bf16* Q = QD + bc() * 2 * TILE;
+    const bf16* D = Q + TILE;
+    if (wave < groups) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        if (TIGHT) __builtin_amdgcn_sched_barrier(0);
+        f32x16 s, dp;      // dP - delta: the products accumulate onto -delta
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4) {
+          const f32x4 d4 = *reinterpret_cast<const f32x4*>(dlt_s + 32 * t + 8 * r4 + 4 * g);
+#pragma unroll
+          for (int u = 0; u < 4; ++u) { s[4 * r4 + u] = 0.f; dp[4 * r4 + u] = d4[u]; }
+        }
+#pragma unroll
+        for (int c = 0; c < KC; ++c) {
+          s = mfma32(fo.row_frag(Q, t, c), kf[c], s);
+          dp = mfma32(fo.row_frag(D, t, c), vf[c], dp);
+        }
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4) {
+          const f32x4 l4 = *reinterpret_cast<const f32x4*>(lse_s + 32 * t + 8 * r4 + 4 * g);
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int r = 4 * r4 + u;
+            s[r] = __builtin_amdgcn_exp2f(fmaf(s[r], p.scale_log2, -l4[u]));      // queries past Nq have lse = +inf, hence 0
+            dp[r] *= s[r];
+          }
+        }
+#pragma unroll
+        for (int cc = 0; cc < 2; ++cc) {
+          const bf16x8 pf = pack8(s, 8 * cc);
+          const bf16x8 dsf = pack8(dp, 8 * cc);
+          // a key past Nk computes garbage that stays in its own columns of dK and dV, which are never stored; its dS meets a zero
+          // row of K, so it only has to be finite
+#pragma unroll
+          for (int q4 = 0; q4 < 2; ++q4) {
+            const bf16x4 v = q4 ? __builtin_shufflevector(dsf, dsf, 4, 5, 6, 7) : __builtin_shufflevector(dsf, dsf, 0, 1, 2, 3);
+            *reinterpret_cast<u32x2*>(dS + ki * 64 + 8 * ((4 * t + 2 * cc + q4) ^ AttnTile<64>::key(l32)) + 4 * g) =
+                kok ? __builtin_bit_cast(u32x2, v) : u32x2{0u, 0u};
+          }
+#pragma unroll
+          for (int i = 0; i < DT; ++i) {
+            dvacc[i] = mfma32(fo.tr_frag(D, 32 * t + 16 * cc, i), pf, dvacc[i]);
+            dkacc[i] = mfma32(fo.tr_frag(Q, 32 * t + 16 * cc, i), dsf, dkacc[i]);
+          }
+        }
+      }
+    }
+    if (TIGHT) __builtin_amdgcn_sched_barrier(0);
+    wait_vmcnt<0>();
+    __syncthreads();      // dS is there, and the next tile
+    const bool more = qt + 1 < nqt;
+    if (more) statistics(qt + 1);
+    if (qt + 2 < nqt) {
+      issue(qt + 2);
+      load_o(qt + 2);
+    }
+    // dQ of the tile: blocks of 32 columns (di) x 32 queries (dt)
+    for (int n = wave; n < 2 * DT; n += NW) {
+      const int di = n % DT, dt = n / DT;
+      int kt_lo, kt_hi, ds_lo, ds_hi;
+      AttnFragOff<DHP, KC>::transposed(lane, di, kt_lo, kt_hi);
+      AttnFragOff<64, KC>::transposed(lane, dt, ds_lo, ds_hi);
+      f32x16 acc;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+#pragma unroll
+      for (int r = 0; r < 32 * NW; r += 16) acc = mfma32(frag(Kt + kt_lo + r * DHP, Kt + kt_hi + r * DHP), frag(dS + ds_lo + r * 64, dS + ds_hi + r * 64), acc);
+      const int q = qt * 64 + 32 * dt + l32;
+      if (q < p.Nq) {
+        bf16* o = (bf16*)p.dq + ((size_t)b * p.Nq + q) * p.lddq + h * p.dh;
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4) {
+          const int col = 32 * di + 8 * r4 + 4 * g;
+          if (col < p.dh) {
+            bf16x4 v;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = (bf16)(acc[4 * r4 + u] * p.scale);
+            *reinterpret_cast<bf16x4*>(o + col) = v;
+          }
+        }
+      }
+    }
+    lds_barrier();      // dS has been read, the statistics of the next tile are there
+  };
+  two_stages(qt0, nqt, tile);
+  attn_store_dkv<DT>(p, dkacc, dvacc, qs, b, h, ki, kok, g);
 }
 
 // dk[row, col] = sum_qs partial_k[qs][row][col] (ascending qs), same for dv; 4 columns per thread.
@@ -806,9 +1028,52 @@ int launch_attn_fwd(const AttnArgs& a, hipStream_t s) {
   return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "attention forward launch failed");
 }
 
+static size_t dkv_partial_bytes(const AttnArgs& a, int qsplit) { return 2 * (size_t)qsplit * a.B * a.Nk * a.H * a.d_head * sizeof(float); }
+static bool dkv_ws_fits(const AttnArgs& a, int qsplit) { return qsplit <= 1 || (a.dkv_ws && a.dkv_ws_bytes >= dkv_partial_bytes(a, qsplit) && (uintptr_t)a.dkv_ws % 16 == 0); }
+static void launch_dkv_reduce(const AttnArgs& a, int qsplit, hipStream_t s) {
+  const size_t rows = (size_t)a.B * a.Nk; const int hd = a.H * a.d_head;
+  KScope ks(KK_REDUCE, 0.0, (double)dkv_partial_bytes(a, qsplit) + 4.0 * rows * hd, s, (int)rows, hd, qsplit);
+  hipLaunchKernelGGL(attn_dkv_reduce_kernel, dim3((rows * (hd / 4) + 255) / 256), dim3(256), 0, s, a.dkv_ws, qsplit, rows, hd,
+                     (bf16*)a.dk, a.lddk, (bf16*)a.dv, a.lddv);
+}
+
+// Whether the backward runs as one kernel: all keys fit a workgroup.
+static bool attn_short(const AttnArgs& a) { return a.Nk <= 256; }
+template <int DHP, int KC, int NW>
+static int launch_short(const AttnArgs& a, AttnK k, hipStream_t s) {
+  auto kern = attn_bwd_short_bf16_kernel<DHP, KC, NW>;
+  constexpr size_t BYTES = AttnShort<DHP, NW>::BYTES;
+  static std::atomic<bool> attr_set{false};      // setting it twice is harmless; the flag only saves the call
+  if (!attr_set.load(std::memory_order_acquire)) {
+    if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)BYTES) != hipSuccess) return set_error(DP_EHIP, "hipFuncSetAttribute(attention) failed");
+    attr_set.store(true, std::memory_order_release);
+  }
+  // shares of the queries while workgroups fit the CUs beside each other, of two tiles at least
+  const long blocks = (long)a.B * a.H;
+  const int nqt = (a.Nq + 63) / 64, resident = 256 * (BYTES <= 80 * 1024 ? 2 : 1);
+  int qsplit = (int)std::max<long>(1, std::min<long>(std::min<long>(16, nqt / 2), (resident + blocks - 1) / blocks));
+  if (blocks >= 256 || !dkv_ws_fits(a, qsplit)) qsplit = 1;
+  const int tps = (nqt + qsplit - 1) / qsplit;
+  qsplit = (nqt + tps - 1) / tps;
+  k.qsplits = qsplit; k.dkv_partial = a.dkv_ws;
+  {
+    // algorithmic work of the whole backward, 2x the forward's
+    KScope ks(KK_ATTN_BWD_DKV, 8.0 * a.B * a.H * (double)a.Nq * a.Nk * a.d_head, 2.0 * (double)a.B * a.H * a.d_head * (4.0 * a.Nq + 4.0 * a.Nk), s, a.Nq, a.Nk, a.d_head);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(blocks * qsplit)), dim3(NW * 64), BYTES, s, k);
+  }
+  if (qsplit > 1) launch_dkv_reduce(a, qsplit, s);
+  return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "attention backward launch failed");
+}
+static int launch_attn_bwd_short(const AttnArgs& a, const AttnK& k, hipStream_t s) {
+  int rc = DP_OK;
+  attn_dispatch(a.d_head, [&](auto dhp, auto kc) { rc = a.Nk <= 128 ? launch_short<dhp, kc, 4>(a, k, s) : launch_short<dhp, kc, 8>(a, k, s); });
+  return rc;
+}
+
 int launch_attn_bwd(const AttnArgs& a, hipStream_t s) {
   if (int e = check_attn(a, true)) return e;
   AttnK k = make_k(a);
+  if (a.dtype == BF16 && attn_short(a)) return launch_attn_bwd_short(a, k, s);
   if (a.dtype == BF16) {
     k.even = takes_turns((long)((a.Nq + 127) / 128) * a.B * a.H, a.d_head <= 64 ? 3 : 2);
     dim3 gq(((a.Nq + 127) / 128) * a.B * a.H), gk(((a.Nk + 127) / 128) * a.B * a.H);
@@ -826,8 +1091,7 @@ int launch_attn_bwd(const AttnArgs& a, hipStream_t s) {
       const int nqt = (a.Nq + 63) / 64;
       int qsplit = 1;
       if (base_blocks < 256) qsplit = (int)std::min<long>(std::min<long>(16, nqt / 2 > 0 ? nqt / 2 : 1), (512 + base_blocks - 1) / base_blocks);
-      const size_t need = 2 * (size_t)qsplit * a.B * a.Nk * a.H * a.d_head * sizeof(float);
-      if (qsplit > 1 && (!a.dkv_ws || a.dkv_ws_bytes < need || ((uintptr_t)a.dkv_ws % 16))) qsplit = 1;
+      if (!dkv_ws_fits(a, qsplit)) qsplit = 1;
       k2.even = takes_turns((long)gk.x * qsplit, a.d_head <= 64 && qsplit == 1 && gk.x > 2 * 256 ? 3 : 2);
       k2.qsplits = qsplit; k2.dkv_partial = a.dkv_ws;
       dim3 gk2(gk.x * qsplit);
@@ -840,12 +1104,7 @@ int launch_attn_bwd(const AttnArgs& a, hipStream_t s) {
           else hipLaunchKernelGGL((attn_bwd_dkv_bf16_kernel<dhp, kc, 2>), gk2, dim3(256), 0, s, k2);
         });
       }
-      if (qsplit > 1) {
-        const size_t rows = (size_t)a.B * a.Nk; const int hd = a.H * a.d_head;
-        KScope ks(KK_REDUCE, 0.0, (double)need + 4.0 * rows * hd, s, (int)rows, hd, qsplit);
-        hipLaunchKernelGGL(attn_dkv_reduce_kernel, dim3((rows * (hd / 4) + 255) / 256), dim3(256), 0, s, a.dkv_ws, qsplit, rows, hd,
-                           (bf16*)a.dk, a.lddk, (bf16*)a.dv, a.lddv);
-      }
+      if (qsplit > 1) launch_dkv_reduce(a, qsplit, s);
     }
   } else {
     hipLaunchKernelGGL(attn_bwd_dq_f32_kernel, dim3(a.Nq, a.B * a.H), dim3(64), (size_t)a.Nk * sizeof(float), s, k);

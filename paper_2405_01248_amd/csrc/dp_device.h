@@ -134,6 +134,13 @@ __device__ __forceinline__ void barrier_nofence() {
   asm volatile("" ::: "memory");
 }
 
+// The same for data handed over in LDS: waits for this wave's LDS operations, not for its copies and stores.
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("" ::: "memory");
+  wait_lgkmcnt0();
+  barrier_nofence();
+}
+
 __device__ __forceinline__ bf16x8 zero8() {
   u32x4 z = {0, 0, 0, 0};
   return __builtin_bit_cast(bf16x8, z);

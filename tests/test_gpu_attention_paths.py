@@ -70,6 +70,18 @@ def test_edges_of_tiles_and_heads(Nq, Nk, dh):
     assert max(errs.values()) <= TOL_BF16, errs
 
 
+@pytest.mark.parametrize("dh", [40, 64, 72, 96])
+@pytest.mark.parametrize("Nk", [1, 31, 32, 77, 96, 127, 128, 129, 160, 225, 255, 256, 257])
+def test_backward_with_all_keys_in_a_workgroup(Nk, dh):
+    """Up to 256 keys: one kernel, four or eight waves of 32 keys, of which the last may be partly filled or empty."""
+    for Nq in (1, 64, 65, 200):
+        _, _, errs = _run(1, 2, Nq, Nk, dh, 1.0, 0.0, seed=Nk + Nq)
+        print(f"\n[attention q{Nq} k{Nk} dh{dh}] {errs}", flush=True)
+        if Nk == 1:
+            errs.pop("dq"), errs.pop("dk")
+        assert max(errs.values()) <= TOL_BF16, errs
+
+
 @pytest.mark.parametrize("case", [(1, 3, 200, 449, 64, 16.0, 80.0), (1, 2, 160, 384, 72, 8.0, 40.0), (1, 2, 96, 320, 40, 16.0, 0.0)])
 def test_late_moves_of_the_softmax_reference(case):
     from softmax_schedule import head_logits
