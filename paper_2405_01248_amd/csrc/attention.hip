@@ -400,8 +400,8 @@ __global__ void __launch_bounds__(256, DHP == 64 ? 3 : 2) attn_bwd_dq_bf16_kerne
       ck.issue(kr, (kt + 1) * 64, p.ldk, Ks[buf ^ 1], wave);
       cv.issue(vr, (kt + 1) * 64, p.ldv, Vs[buf ^ 1], wave);
     }
-    // Keys past Nk need no masking here: their K and V rows are zero in LDS, so dP = 0 and the
-    // finite dS they get multiplies a zero K row in the dQ product.
+    // Keys past Nk: their K and V rows are zero in LDS, so their dS multiplies a zero K row; it only has to be finite, which the exponential
+    // is not where all logits of a query lie below -88
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
       f32x16 s, dp = ndelta;
@@ -411,6 +411,10 @@ __global__ void __launch_bounds__(256, DHP == 64 ? 3 : 2) attn_bwd_dq_bf16_kerne
       for (int c = 0; c < KC; ++c) {
         s = mfma32(fo.row_frag(Ks[buf], t, c), qf[c], s);
         dp = mfma32(fo.row_frag(Vs[buf], t, c), dof[c], dp);
+      }
+      if (kt * 64 + 64 > p.Nk) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s[r] = kt * 64 + 32 * t + acc_row(r, g) < p.Nk ? s[r] : -INFINITY;
       }
 #pragma unroll
       for (int r = 0; r < 16; ++r) s[r] = __builtin_amdgcn_exp2f(fmaf(s[r], p.scale_log2, -lse2)) * (ONTO ? dp[r] : dp[r] - dlt);
@@ -1037,8 +1041,16 @@ static void launch_dkv_reduce(const AttnArgs& a, int qsplit, hipStream_t s) {
                      (bf16*)a.dk, a.lddk, (bf16*)a.dv, a.lddv);
 }
 
-// Whether the backward runs as one kernel: all keys fit a workgroup.
-static bool attn_short(const AttnArgs& a) { return a.Nk <= 256; }
+// Shares of the queries for the kernel that has all keys in a workgroup, `resident` of which run at a time: as many as run beside each other, of
+// two tiles at least.
+static int short_shares(const AttnArgs& a, int resident) {
+  const long blocks = (long)a.B * a.H;
+  const int nqt = (a.Nq + 63) / 64;
+  return blocks >= 256 ? 1 : (int)std::max<long>(1, std::min<long>(std::min<long>(16, nqt / 2), (resident + blocks - 1) / blocks));
+}
+// Whether the backward runs as one kernel: all keys fit a workgroup, and the queries can be shared out or are few.  Without scratch for the
+// shares' sums 8 x 5 heads of 4096 queries and 77 keys would walk 64 tiles on 40 CUs: 121 us, two kernels 97; 8 x 10 of 1024: 36 and 37.
+static bool attn_short(const AttnArgs& a) { return a.Nk <= 256 && ((long)a.B * a.H >= 256 || a.Nq <= 24 * 64 || dkv_ws_fits(a, short_shares(a, 512))); }
 template <int DHP, int KC, int NW>
 static int launch_short(const AttnArgs& a, AttnK k, hipStream_t s) {
   auto kern = attn_bwd_short_bf16_kernel<DHP, KC, NW>;
@@ -1048,11 +1060,10 @@ static int launch_short(const AttnArgs& a, AttnK k, hipStream_t s) {
     if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)BYTES) != hipSuccess) return set_error(DP_EHIP, "hipFuncSetAttribute(attention) failed");
     attr_set.store(true, std::memory_order_release);
   }
-  // shares of the queries while workgroups fit the CUs beside each other, of two tiles at least
   const long blocks = (long)a.B * a.H;
-  const int nqt = (a.Nq + 63) / 64, resident = 256 * (BYTES <= 80 * 1024 ? 2 : 1);
-  int qsplit = (int)std::max<long>(1, std::min<long>(std::min<long>(16, nqt / 2), (resident + blocks - 1) / blocks));
-  if (blocks >= 256 || !dkv_ws_fits(a, qsplit)) qsplit = 1;
+  const int nqt = (a.Nq + 63) / 64;
+  int qsplit = short_shares(a, 256 * (BYTES <= 80 * 1024 ? 2 : 1));
+  if (!dkv_ws_fits(a, qsplit)) qsplit = 1;
   const int tps = (nqt + qsplit - 1) / qsplit;
   qsplit = (nqt + tps - 1) / tps;
   k.qsplits = qsplit; k.dkv_partial = a.dkv_ws;

@@ -82,6 +82,16 @@ def test_backward_with_all_keys_in_a_workgroup(Nk, dh):
         assert max(errs.values()) <= TOL_BF16, errs
 
 
+@pytest.mark.parametrize("Nk,dh", [(77, 64), (200, 72), (300, 64), (300, 72), (300, 96)])
+def test_rows_of_very_low_logits_meet_keys_that_are_not_there(Nk, dh):
+    """Rows shifted by up to +-200: where all logits of a row lie below -88 the probability of a padded key (score 0) overflows."""
+    q, k, errs = _run(1, 2, 150, Nk, dh, 1.001, 200.0)
+    from softmax_schedule import head_logits
+    assert head_logits(q, k, 2).max(axis=-1).min() < -90
+    print(f"\n[attention low logits k{Nk} dh{dh}] {errs}", flush=True)
+    assert all(np.isfinite(e) for e in errs.values()) and max(errs.values()) <= TOL_BF16, errs
+
+
 @pytest.mark.parametrize("case", [(1, 3, 200, 449, 64, 16.0, 80.0), (1, 2, 160, 384, 72, 8.0, 40.0), (1, 2, 96, 320, 40, 16.0, 0.0)])
 def test_late_moves_of_the_softmax_reference(case):
     from softmax_schedule import head_logits
