@@ -564,25 +564,32 @@ __global__ void __launch_bounds__(512, 2) gemm_pp_strided_kernel(GemmBf16Params 
 // w, w + NW, ... of the workgroup's range, from a stage of LDS of its own, and the NW partial tiles are added at the end, in wave order.
 // Why: a 64x64 tile split 2x2 among four waves is bound by LDS (each wave reads 2 fragments per MFMA: 32 KB read and 16 KB written per k-tile,
 // 0.23 us) and by its barriers; here a k-tile is read once (16 KB, 4 fragments for 4 MFMAs) and no wave ever waits for another before the
-// end.  A wave holds one k-tile in registers and one on its way to LDS; the other waves of the CU hide the latency.
+// end.  A wave holds one k-tile in registers and one on its way to LDS, two where a CU has a single workgroup of 64x64 (the stages then leave no
+// room for another); the other waves of the CU hide the latency.  What a launch of few tiles spends beside that is its beginning and
+// end: 77 x 3072, K = 768 took 6.6 us, 1.0 until the copies were issued, 2.1 for three k-tiles, 2.5 to add up 32 rows at a time with every
+// epilogue in one kernel.  With a kernel per kind of epilogue, its operands requested ahead and 64 rows at a time: 7.4 -> 6.3 us a launch,
+// 1024 x 1152, K = 1152 / 4608: 10.2 -> 9.1 / 20.2 -> 18.9; steps of the text encoder on one sample 525 -> 470 us, of seven DiT blocks
+// 4 x 256 x 1152 2287 -> 2163, of a U-Net block 2 x 513 x 1280 (three passes, two micro-batches) 1321 -> 1238.
 // What bounds it is fetching operands, about 20 TB/s over all CUs, so the widest tile that still gives one workgroup per CU is taken (kWave).
 // Measured (M x N, K; us, 64x64 tiles split 2x2 or 128x128 ones with split-K before): 1026 x 1280, 3840: 27 -> 19, 10240: 66 -> 40;
 // 1024 x 1152, 4608: 32 -> 20; 2048 x 1152, 4608: 37 -> 30; 924 x 768, 3072: 21 -> 12.5.
-template <int NW_, int TM_, int TN_>
+// ST: k-tiles of a wave on their way to LDS.  RP: rows of the tile that are added up at a time.
+template <int NW_, int TM_, int TN_, int ST_ = 1>
 struct WaveTile {
-  static constexpr int NW = NW_, TM = TM_, TN = TN_, BM = 32 * TM, BN = 32 * TN, LD = BN + 4, A_BYTES = BM * 128, REGION = (BM + BN) * 128;
-  static constexpr size_t SLAB = (size_t)32 * LD * 4, BYTES = NW * (REGION > SLAB ? REGION : SLAB);
+  static constexpr int NW = NW_, TM = TM_, TN = TN_, ST = ST_, BM = 32 * TM, BN = 32 * TN, LD = BN + 4, A_BYTES = BM * 128, REGION = (BM + BN) * 128;
+  static constexpr int RP = TN == 3 && TM == 2 ? 32 : 64, GROUPS = RP * BN / 8, ITEMS = (GROUPS + NW * 64 - 1) / (NW * 64);      // groups of eight columns of a pass, and per thread
+  static constexpr size_t SLAB = (size_t)NW * RP * LD * 4, STAGES = (size_t)NW * ST * REGION, BYTES = STAGES > SLAB ? STAGES : SLAB;
+  static_assert(BM % RP == 0 && BYTES <= 160 * 1024, "tile shape");
 };
-template <class T>
+template <class T, int KIND>
 __global__ void __launch_bounds__(T::NW * 64, T::TM * T::TN <= 6 ? 2 : 1) gemm_wave_kernel(const GemmBf16Params p) {
-  constexpr int NW = T::NW, TM = T::TM, TN = T::TN, LD = T::LD;
+  constexpr int NW = T::NW, TM = T::TM, TN = T::TN, LD = T::LD, ST = T::ST, COPIES = 4 * (TM + TN);
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 5, l32 = lane & 31;
   int tile_m, tile_n;
   tile_of_block(blockIdx.x, p.tiles_m, p.tiles_n, p.group_m, tile_m, tile_n);
   const int m0 = tile_m * T::BM, n0 = tile_n * T::BN;
   const int kt_begin = blockIdx.z * p.k_tiles_per_split, kt_end = min(p.K / 64, kt_begin + p.k_tiles_per_split);
-  const rsrc_t ra = make_rsrc(p.A, p.a_bytes), rb = make_rsrc(p.B, p.b_bytes);
   uint32_t va[4 * TM], vb[4 * TN];
 #pragma unroll
   for (int j = 0; j < 4 * TM; ++j) {
@@ -594,12 +601,17 @@ __global__ void __launch_bounds__(T::NW * 64, T::TM * T::TN <= 6 ? 2 : 1) gemm_w
     const int r = 8 * j + (lane >> 3), c = (lane & 7) ^ kc_key<64>(r);
     vb[j] = 2u * ((uint32_t)min(n0 + r, p.N - 1) * p.ldb + c * 8);
   }
-  unsigned char* own = smem_raw + wave * T::REGION;
-  auto issue = [&](int t) {
+  unsigned char* own = smem_raw + wave * (ST * T::REGION);
+  // copies of k-tile t (past the last one: issued all the same, since the waits count them, from outside the buffers)
+  auto issue = [&](int t, int stage) {
+    const bool in = t < kt_end;
+    const rsrc_t ra = make_rsrc(p.A, in ? p.a_bytes : 0u), rb = make_rsrc(p.B, in ? p.b_bytes : 0u);
+    const uint32_t off = in ? (uint32_t)t * 128u : 0u;
+    unsigned char* dst = own + stage * T::REGION;
 #pragma unroll
-    for (int j = 0; j < 4 * TM; ++j) async_copy_16B_buf(ra, va[j], (uint32_t)t * 128u, own + j * 1024);
+    for (int j = 0; j < 4 * TM; ++j) async_copy_16B_buf(ra, va[j], off, dst + j * 1024);
 #pragma unroll
-    for (int j = 0; j < 4 * TN; ++j) async_copy_16B_buf(rb, vb[j], (uint32_t)t * 128u, own + T::A_BYTES + j * 1024);
+    for (int j = 0; j < 4 * TN; ++j) async_copy_16B_buf(rb, vb[j], off, dst + T::A_BYTES + j * 1024);
   };
   f32x16 acc[TM][TN];
 #pragma unroll
@@ -608,62 +620,86 @@ __global__ void __launch_bounds__(T::NW * 64, T::TM * T::TN <= 6 ? 2 : 1) gemm_w
     for (int j = 0; j < TN; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-  int t = kt_begin + wave;
-  if (t < kt_end) issue(t);
-#pragma unroll 1
-  for (; t < kt_end; t += NW) {
+  auto k_tile = [&](int t, int stage) {
     bf16x8 fa[4][TM], fb[4][TN];
-    wait_vmcnt<0>();
+    wait_vmcnt<(ST - 1) * COPIES>();
+    const unsigned char* src = own + stage * T::REGION;
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
         const int r = 32 * i + l32;
-        fa[ks][i] = *reinterpret_cast<const bf16x8*>(own + r * 128 + ((2 * ks + g) ^ kc_key<64>(r)) * 16);
+        fa[ks][i] = *reinterpret_cast<const bf16x8*>(src + r * 128 + ((2 * ks + g) ^ kc_key<64>(r)) * 16);
       }
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
         const int r = 32 * j + l32;
-        fb[ks][j] = *reinterpret_cast<const bf16x8*>(own + T::A_BYTES + r * 128 + ((2 * ks + g) ^ kc_key<64>(r)) * 16);
+        fb[ks][j] = *reinterpret_cast<const bf16x8*>(src + T::A_BYTES + r * 128 + ((2 * ks + g) ^ kc_key<64>(r)) * 16);
       }
     }
     wait_lgkmcnt0();
-    if (t + NW < kt_end) issue(t + NW);
+    if (ST > 1 || t + NW < kt_end) issue(t + ST * NW, stage);
+    __builtin_amdgcn_sched_barrier(0);      // (all copies before the products: they are what the next k-tile waits for)
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j) acc[i][j] = mfma32(fb[ks][j], fa[ks][i], acc[i][j]);      // transposed: a lane gets four neighbouring columns of a row
+  };
+  int t = kt_begin + wave;
+#pragma unroll
+  for (int i = 0; i < ST; ++i) issue(t + i * NW, i);
+#pragma unroll 1
+  for (; t < kt_end; t += ST * NW) {
+#pragma unroll
+    for (int i = 0; i < ST; ++i)
+      if (i == 0 || t + i * NW < kt_end) k_tile(t + i * NW, i);
   }
+  // The partial tiles meet in LDS, RP rows at a time; what the epilogue reads beside them is requested before.
   float* slab = reinterpret_cast<float*>(smem_raw);
+  constexpr int CH = T::BN / 8;
 #pragma unroll
-  for (int i = 0; i < TM; ++i) {
+  for (int pass = 0; pass < T::BM / T::RP; ++pass) {
+    PpIn<KIND> in[T::ITEMS];
+    bf16x8 bias[T::ITEMS];
+#pragma unroll
+    for (int it = 0; it < T::ITEMS; ++it) {
+      const int x = min(it * NW * 64 + tid, T::GROUPS - 1), m = m0 + pass * T::RP + x / CH, n = n0 + x % CH * 8;
+      pp_load<KIND>(p.epi, m, n, in[it]);
+      bias[it] = KIND != PE_F32 && p.epi.bias ? *reinterpret_cast<const bf16x8*>(p.epi.bias + min(n, p.epi.N - 8)) : zero8();
+    }
+    if (pass == 0) wait_vmcnt<0>();      // (copies from outside the buffers may still be under way to where the slab will be)
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+    for (int i = 0; i < T::RP / 32; ++i)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        f32x4 v;
+      for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = acc[i][j][4 * q + u];
-        *reinterpret_cast<f32x4*>(slab + (wave * 32 + l32) * LD + 32 * j + 8 * q + 4 * g) = v;
-      }
+        for (int q = 0; q < 4; ++q) {
+          f32x4 v;
+#pragma unroll
+          for (int u = 0; u < 4; ++u) v[u] = acc[pass * (T::RP / 32) + i][j][4 * q + u];
+          *reinterpret_cast<f32x4*>(slab + (wave * T::RP + 32 * i + l32) * LD + 32 * j + 8 * q + 4 * g) = v;
+        }
     __syncthreads();
-    for (int x = tid; x < 4 * T::BN; x += NW * 64) {
-      const int row = x / (T::BN / 8), c = x % (T::BN / 8) * 8, m = m0 + 32 * i + row, n = n0 + c;
-      if (m >= p.epi.M || n >= p.epi.N) continue;
-      float v[8];
+#pragma unroll
+    for (int it = 0; it < T::ITEMS; ++it) {
+      const int x = it * NW * 64 + tid, row = x / CH, c = x % CH * 8, m = m0 + pass * T::RP + row, n = n0 + c;
+      if (T::GROUPS % (NW * 64) != 0 && x >= T::GROUPS) continue;
+      float v[8], bv[8];
       const float* src = slab + row * LD + c;
       *reinterpret_cast<f32x4*>(&v[0]) = *reinterpret_cast<const f32x4*>(src);
       *reinterpret_cast<f32x4*>(&v[4]) = *reinterpret_cast<const f32x4*>(src + 4);
 #pragma unroll
       for (int w = 1; w < NW; ++w) {
-        const f32x4 y0 = *reinterpret_cast<const f32x4*>(src + w * 32 * LD), y1 = *reinterpret_cast<const f32x4*>(src + w * 32 * LD + 4);
+        const f32x4 y0 = *reinterpret_cast<const f32x4*>(src + w * T::RP * LD), y1 = *reinterpret_cast<const f32x4*>(src + w * T::RP * LD + 4);
 #pragma unroll
         for (int u = 0; u < 4; ++u) { v[u] += y0[u]; v[4 + u] += y1[u]; }
       }
-      epi_vec8(p.epi, m, n, v);
+#pragma unroll
+      for (int u = 0; u < 8; ++u) bv[u] = (float)bias[it][u];
+      if (m < p.epi.M && n < p.epi.N) pp_finish<KIND>(p.epi, m, n, v, in[it], bv);
     }
   }
 }
@@ -814,23 +850,23 @@ static int splits_128(int rows, int N, int K, bool ln, bool heavy, float* us) {
 }
 
 
-// Tiles whose waves share the contraction (gemm_wave_kernel): fixed part of a tile, and the time of a k-tile of the workgroup, which grows
-// with the number of tiles in flight since what bounds it is the rate at which all CUs together fetch operands (about 20 TB/s).  us,
-// fitted on MI355X over 77..4928 rows, 640..10240 columns, contractions of 640..10240.
-struct WaveCost { int bm, bn; bool two_on_cu; float fixed, per_kt, per_kt_tile; };
-static const WaveCost kWave[] = {{64, 64, true, 5.8f, 0.070f, 0.00040f}, {64, 96, false, 7.0f, 0.115f, 0.00040f}, {128, 96, false, 9.0f, 0.115f, 0.00091f}, {128, 128, false, 9.6f, 0.20f, 0.0010f}};
+// Tiles whose waves share the contraction (gemm_wave_kernel): fixed part of a tile, which grows a little with the number of tiles, and the time
+// of a k-tile of the workgroup, a quarter of a wave's, each of which waits for memory; two: the same where a CU holds two tiles at a time.  us,
+// fitted on MI355X over 77..4928 rows, 640..10240 columns, contractions of 640..10240 (within 8 % but for two_per_kt of long contractions).
+struct WaveCost { int bm, bn; float fixed, per_tile, per_kt, per_kt_tile, two_fixed, two_per_kt; };
+static const WaveCost kWave[] = {{64, 64, 3.6f, 0.005f, 0.173f, 0.f, 4.1f, 0.34f}, {64, 96, 3.7f, 0.0075f, 0.212f, 0.f, 5.6f, 0.45f},
+                                 {128, 96, 6.8f, 0.005f, 0.255f, 0.0003f, 0.f, 0.f}, {128, 128, 8.0f, 0.015f, 0.325f, 0.0002f, 0.f, 0.f}};
 // Estimated time; splits: parts the contraction is cut into beyond the waves of a workgroup, where few tiles would each walk a long one.
 static float wave_us(const WaveCost& c, int rows, int N, int K, bool may_split, bool ln, int* splits) {
   const int kt = K / 64;
   const int tiles_n = (N + c.bn - 1) / c.bn;
   const int tiles = (int)std::min<long>((long)((rows + c.bm - 1) / c.bm) * tiles_n, 1 << 24);
   auto time = [&](int z) {
-    const int n = tiles * z;
-    // more than 256 of the smallest tiles: two on a CU
-    const bool two = n > kCUs && c.two_on_cu;
-    const float per_kt = two ? 0.32f : std::max(0.13f, c.per_kt + c.per_kt_tile * (float)std::min(n, kCUs));
-    const float rounds = two ? std::max(1.0f, (float)n / 512.0f) : (float)((n + kCUs - 1) / kCUs);
-    return rounds * (c.fixed + (float)((kt + z - 1) / z) * per_kt) + (two && n > 2 * kCUs ? 2.2f : 0.f) + (z > 1 ? reduce_us(rows, N, z, ln) : 0.f);
+    const int n = tiles * z, part = (kt + z - 1) / z;
+    const float reduce = z > 1 ? reduce_us(rows, N, z, ln) : 0.f;
+    if (n > kCUs && c.two_fixed > 0.f) return std::max(1.0f, (float)n / 512.0f) * (c.two_fixed + (float)part * c.two_per_kt) + (n > 2 * kCUs ? 1.0f : 0.f) + reduce;
+    const float live = (float)std::min(n, kCUs);
+    return (float)((n + kCUs - 1) / kCUs) * (c.fixed + c.per_tile * live + (float)part * (c.per_kt + c.per_kt_tile * live)) + reduce;
   };
   float best = 0.f;
   *splits = 1;
@@ -1274,14 +1310,34 @@ static int launch_pp(const GemmArgs& a, hipStream_t s) {
   }
 }
 
+template <class T, int KIND>
+static int launch_wave_kind(const GemmArgs& a, GemmBf16Params& p, int splits, hipStream_t s) {
+  static std::atomic<bool> attr_set{false};
+  return launch_split(a, p, gemm_wave_kernel<T, KIND>, T::NW * 64, T::BYTES, attr_set, a.K / 64, splits, s);
+}
 template <class T>
+static int launch_wave_tile(const GemmArgs& a, int splits, hipStream_t s) {
+  GemmBf16Params p = pp_params<T>(a);
+  if (splits > 1) return launch_wave_kind<T, PE_F32>(a, p, splits, s);
+  switch (pp_kind(a)) {
+#define DP_WAVE_CASE(k_) case k_: return launch_wave_kind<T, k_>(a, p, 1, s)
+    DP_WAVE_CASE(PE_PLAIN); DP_WAVE_CASE(PE_RES); DP_WAVE_CASE(PE_RESH); DP_WAVE_CASE(PE_GATE); DP_WAVE_CASE(PE_ACT1); DP_WAVE_CASE(PE_ACT2);
+    DP_WAVE_CASE(PE_ACT3); DP_WAVE_CASE(PE_DACT1); DP_WAVE_CASE(PE_DACT2); DP_WAVE_CASE(PE_GEGLU2);
+#undef DP_WAVE_CASE
+    default: return set_error(DP_EUNSUPPORTED, "gemm: the forced configuration does not have this epilogue");
+  }
+}
+// T1: the same tile with one k-tile less on its way, two workgroups of which fit a CU.
+template <class T, class T1>
 static int launch_wave(const GemmArgs& a, const WaveCost& c, hipStream_t s) {
   if (a.a_mc || a.b_mc || a.out_f32 || a.geglu == 1 || a.K % 64 || !dtl_addressable(a)) return set_error(DP_EUNSUPPORTED, "gemm: the forced configuration needs contraction-contiguous operands, K % 64 == 0 and a storage-dtype output");
-  GemmBf16Params p = pp_params<T>(a);
   int splits = 1;
   if (a.splitk_ws && a.choice_rows == 0) wave_us(c, a.M, a.N, a.K, true, a.ln_out != nullptr, &splits);
-  static std::atomic<bool> attr_set{false};
-  return launch_split(a, p, gemm_wave_kernel<T>, T::NW * 64, T::BYTES, attr_set, a.K / 64, splits, s);
+  if (splits > 1 && a.splitk_ws_bytes < (size_t)splits * a.M * a.N * sizeof(float)) splits = 1;
+  const int kps = (a.K / 64 + splits - 1) / splits;
+  splits = (a.K / 64 + kps - 1) / kps;
+  const long tiles = (long)((a.M + T::BM - 1) / T::BM) * ((a.N + T::BN - 1) / T::BN) * splits;
+  return std::is_same<T, T1>::value || tiles <= kCUs ? launch_wave_tile<T>(a, splits, s) : launch_wave_tile<T1>(a, splits, s);
 }
 
 template <int BM, int BN, int BK, int STAGES, int WGM, int WGN>
@@ -1320,7 +1376,7 @@ static int chosen_cfg(const GemmArgs& a, int rows, bool may_split) {
   struct Entry { int rows, n, k, flags, cfg; };
   constexpr int ENTRIES = 64;
   static thread_local Entry table[ENTRIES] = {};        // n = 0: empty
-  const bool pp = !a.out_f32 && pp_kind(a) >= 0, any_order = a.choice_rows == 0, wave = any_order && !a.out_f32 && a.geglu != 1, dtl = dtl_addressable(a), heavy = heavy_epilogue(a), geglu_fwd = a.geglu == 1;
+  const bool pp = !a.out_f32 && pp_kind(a) >= 0, any_order = a.choice_rows == 0, wave = any_order && pp && a.geglu != 1, dtl = dtl_addressable(a), heavy = heavy_epilogue(a), geglu_fwd = a.geglu == 1;
   const int flags = geglu_fwd << 9 | heavy << 8 | (a.a_mc != 0) | (a.b_mc != 0) << 1 | dtl << 2 | pp << 3 | any_order << 4 | may_split << 5 | (a.ln_out != nullptr) << 6 | wave << 7;
   Entry& e = table[((unsigned)rows * 0x9E3779B1u ^ (unsigned)a.N * 0x85EBCA77u ^ (unsigned)a.K * 0xC2B2AE3Du ^ (unsigned)flags * 0x27D4EB2Fu) >> 26];
   if (e.n == a.N && e.rows == rows && e.k == a.K && e.flags == flags) return e.cfg;
@@ -1424,10 +1480,10 @@ int launch_gemm(const GemmArgs& a, hipStream_t s) {
       case 11: case 20:
         if (cfg == 11 && a.K % 64) return set_error(DP_EUNSUPPORTED, "gemm: the forced 256x160 configuration needs K % 64 == 0");
         return launch_pp<PpTile<256, 96, 64, 4, 2, 16>>(a, s);
-      case 25: return launch_wave<WaveTile<4, 2, 2>>(a, kWave[0], s);
-      case 26: return launch_wave<WaveTile<4, 2, 3>>(a, kWave[1], s);
-      case 27: return launch_wave<WaveTile<4, 4, 3>>(a, kWave[2], s);
-      case 28: return launch_wave<WaveTile<4, 4, 4>>(a, kWave[3], s);
+      case 25: return launch_wave<WaveTile<4, 2, 2, 2>, WaveTile<4, 2, 2>>(a, kWave[0], s);
+      case 26: return launch_wave<WaveTile<4, 2, 3>, WaveTile<4, 2, 3>>(a, kWave[1], s);
+      case 27: return launch_wave<WaveTile<4, 4, 3>, WaveTile<4, 4, 3>>(a, kWave[2], s);
+      case 28: return launch_wave<WaveTile<4, 4, 4>, WaveTile<4, 4, 4>>(a, kWave[3], s);
       default: break;
     }
     return launch_bf16_layout<128, 128, 64, 2, 2>(a, s);

@@ -27,6 +27,15 @@ def test_tiles_whose_waves_share_the_contraction(tile_cfg):
         assert e <= TOL_BF16
 
 
+@pytest.mark.parametrize("K", [64, 256, 320, 512, 576, 832, 1088])
+def test_waves_with_one_and_two_k_tiles_on_their_way(K):
+    # up to 256 tiles of 64x64 a wave has two k-tiles on their way to LDS, beyond one: 1, 2, 3, 4, 5 k-tiles of the first wave, fewer of the others
+    for M, N in [(70, 136), (1100, 1048)]:
+        e = _gemm_case("nt", M, N, K, 26, seed=M + K)
+        print(f"\n[gemm nt cfg 26 {M}x{N}x{K}] rel err {e:.2e}", flush=True)
+        assert e <= TOL_BF16
+
+
 @pytest.mark.parametrize("tile_cfg", [22, 23, 24, 25])
 @pytest.mark.parametrize("accumulate", [False, True])
 def test_weight_gradient_tiles(tile_cfg, accumulate):
