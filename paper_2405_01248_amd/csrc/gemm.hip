@@ -852,9 +852,9 @@ static int splits_128(int rows, int N, int K, bool ln, bool heavy, float* us) {
 
 // Tiles whose waves share the contraction (gemm_wave_kernel): fixed part of a tile, which grows a little with the number of tiles, and the time
 // of a k-tile of the workgroup, a quarter of a wave's, each of which waits for memory; two: the same where a CU holds two tiles at a time.  us,
-// fitted on MI355X over 77..4928 rows, 640..10240 columns, contractions of 640..10240 (within 8 % but for two_per_kt of long contractions).
+// fitted on MI355X over 77..4928 rows, 640..10240 columns, contractions of 640..10240 (within 8 %; two_per_kt, which grows with the contraction, on the dear side).
 struct WaveCost { int bm, bn; float fixed, per_tile, per_kt, per_kt_tile, two_fixed, two_per_kt; };
-static const WaveCost kWave[] = {{64, 64, 3.6f, 0.005f, 0.173f, 0.f, 4.1f, 0.34f}, {64, 96, 3.7f, 0.0075f, 0.212f, 0.f, 5.6f, 0.45f},
+static const WaveCost kWave[] = {{64, 64, 3.6f, 0.005f, 0.173f, 0.f, 4.1f, 0.36f}, {64, 96, 3.7f, 0.0075f, 0.212f, 0.f, 5.6f, 0.50f},
                                  {128, 96, 6.8f, 0.005f, 0.255f, 0.0003f, 0.f, 0.f}, {128, 128, 8.0f, 0.015f, 0.325f, 0.0002f, 0.f, 0.f}};
 // Estimated time; splits: parts the contraction is cut into beyond the waves of a workgroup, where few tiles would each walk a long one.
 static float wave_us(const WaveCost& c, int rows, int N, int K, bool may_split, bool ln, int* splits) {
