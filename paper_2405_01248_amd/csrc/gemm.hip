@@ -267,7 +267,10 @@ template <int BK> __device__ __forceinline__ int kc_key(int r) { return BK == 32
 // long as it is the same for both operands, which it is by symmetry.
 // SEG: the sums of the contraction's segments of k_tiles_per_split k-tiles are formed apart and added in order, the additions of a split-K
 // launch and its reduction without the partial tiles' way through memory.
-template <int BM, int BN, int BK, int STAGES, int WGM, int WGN, bool A_MC, bool B_MC, bool FP8 = false, bool SEG = false>
+// KIND: the kind of epilogue (PpEpi), whose operands are then requested before the main loop; -1: any, each group of columns requests its own when
+// its turn comes.  Few tiles of a short
+// contraction end with two to four such waits one after the other: 12 layers on 924 rows of width 768 in the batch-invariant mode 843 -> 811 us.
+template <int BM, int BN, int BK, int STAGES, int WGM, int WGN, bool A_MC, bool B_MC, bool FP8 = false, bool SEG = false, int KIND = -1>
 __global__ void __launch_bounds__(WGM * WGN * 64)
 gemm_bf16_dtl_kernel(const GemmBf16Params p) {
   using S = DtlSmem<BM, BN, BK, STAGES, WGM, WGN>;
@@ -335,6 +338,21 @@ gemm_bf16_dtl_kernel(const GemmBf16Params p) {
         async_copy_16B_buf(rb, vb[j], (uint32_t)(t_) * b_step, st_ + S::A_BYTES + (wave * B_LOADS + j) * 1024);       \
   }
 #define DP_DTL_ISSUE(t_) DP_DTL_ISSUE_PART(t_, 0, 1)
+
+  // What the epilogue reads beside the sums: a lane has the same eight columns of every (512 / WN)-th row
+  constexpr int EPI = KIND < 0 ? PE_PLAIN : KIND, CH = WN / 8, NIT = 32 * CH / 64;
+  static_assert(KIND < 0 || 64 % CH == 0, "epilogue by kind");
+  PpIn<EPI> in[KIND < 0 ? 1 : TM][KIND < 0 ? 1 : NIT];
+  float bias[8];
+  if constexpr (KIND >= 0) {
+    const int n = n0 + wn0 + lane % CH * 8;
+    pp_bias(KIND == PE_F32 ? nullptr : p.epi.bias, min(n, p.N - 8), bias);
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int it = 0; it < NIT; ++it) pp_load<EPI>(p.epi, m0 + wm0 + i * 32 + (it * 64 + lane) / CH, n, in[i][it]);
+    __builtin_amdgcn_sched_barrier(0);
+  }
 
   f32x16 acc[TM][TN];
 #pragma unroll
@@ -487,7 +505,27 @@ gemm_bf16_dtl_kernel(const GemmBf16Params p) {
   __syncthreads();   // every wave is done with the operand tiles before they are reused below
 
   float* Cw = reinterpret_cast<float*>(smem_raw) + wave * 32 * S::C_LD;
-  wave_epilogue<TM, TN, WN, S::C_LD>(acc, Cw, p.epi, m0 + wm0, n0 + wn0, lane);
+  if constexpr (KIND < 0) {
+    wave_epilogue<TM, TN, WN, S::C_LD>(acc, Cw, p.epi, m0 + wm0, n0 + wn0, lane);
+  } else {
+    const int n = n0 + wn0 + lane % CH * 8;
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) Cw[acc_row(r, g) * S::C_LD + j * 32 + l32] = acc[i][j][r];
+      asm volatile("" ::: "memory");
+#pragma unroll
+      for (int it = 0; it < NIT; ++it) {
+        const int row = (it * 64 + lane) / CH, m = m0 + wm0 + i * 32 + row;
+        float v[8];
+        pp_slab_row(&Cw[row * S::C_LD + lane % CH * 8], v);
+        if (m < p.epi.M && n < p.epi.N) pp_finish<EPI>(p.epi, m, n, v, in[i][it], bias);
+      }
+      asm volatile("" ::: "memory");
+    }
+  }
 }
 
 // ------------------------------------------------------------------ bf16 / fp8 MFMA kernel, alternating wave groups
@@ -1121,6 +1159,19 @@ static int launch_dtl_cfg(const GemmArgs& a, hipStream_t s) {
     splits = a.choice_rows < 0 ? 1 : choose_splits_epi(((rows_for_choice + BM - 1) / BM) * p.tiles_n, kt * BK / 64);
     if (a.choice_rows >= 0 && BM == 128 && BN == 128 && BK == 64) splits = splits_128((int)rows_for_choice, a.N, a.K, a.ln_out != nullptr, heavy_epilogue(a), &us);
   }
+  if constexpr (!A_MC && !B_MC && BK == 64 && STAGES == 3 && ((BM == 64 && BN == 64) || (BM == 128 && BN == 128 && WGM == 4))) {
+    if (splits > 1 && a.splitk_ws_bytes < (size_t)splits * a.M * a.N * sizeof(float) && a.choice_rows <= 0) splits = 1;
+    const int kind = a.out_f32 || splits > 1 ? PE_F32 : pp_kind(a);
+    switch (kind) {
+#define DP_DTL_CASE(k_) case k_: { \
+        static std::atomic<bool> set{false}; \
+        return launch_split(a, p, gemm_bf16_dtl_kernel<BM, BN, BK, STAGES, WGM, WGN, A_MC, B_MC, false, false, k_>, WGM * WGN * 64, S::BYTES, set, kt, splits, s); }
+      DP_DTL_CASE(PE_PLAIN) DP_DTL_CASE(PE_F32) DP_DTL_CASE(PE_RES) DP_DTL_CASE(PE_RESH) DP_DTL_CASE(PE_GATE) DP_DTL_CASE(PE_ACT1) DP_DTL_CASE(PE_ACT2)
+      DP_DTL_CASE(PE_ACT3) DP_DTL_CASE(PE_DACT1) DP_DTL_CASE(PE_DACT2) DP_DTL_CASE(PE_GEGLU2)
+#undef DP_DTL_CASE
+      default: break;      // the fused GeGLU forward, and combinations no kind has
+    }
+  }
   static std::atomic<bool> attr_set{false};
   return launch_split(a, p, gemm_bf16_dtl_kernel<BM, BN, BK, STAGES, WGM, WGN, A_MC, B_MC>, WGM * WGN * 64, S::BYTES, attr_set, kt, splits, s);
 }
@@ -1135,12 +1186,21 @@ static int launch_segments(const GemmArgs& a, int splits, hipStream_t s) {
   const bool ln = reduction_does_ln(a);
   if (ln && (!a.splitk_ws || a.splitk_ws_bytes < (size_t)a.M * a.N * sizeof(float))) return set_error(DP_EWORKSPACE, "gemm: split-K workspace too small for the split chosen from choice_rows");
   if (ln) p.epi.partial = a.splitk_ws;      // the sums, for the pass that adds bias and residual and normalises (the same one as after a split launch)
-  auto kern = gemm_bf16_dtl_kernel<BM, BN, BK, STAGES, WGM, WGN, false, false, false, true>;
-  static std::atomic<bool> attr_set{false};
-  DP_TRY(set_lds_limit((const void*)kern, S::BYTES, attr_set));
-  {
+  auto launch = [&](auto kind) {
+    auto kern = gemm_bf16_dtl_kernel<BM, BN, BK, STAGES, WGM, WGN, false, false, false, true, kind>;
+    static std::atomic<bool> attr_set{false};
+    DP_TRY(set_lds_limit((const void*)kern, S::BYTES, attr_set));
     KScope ks(KK_GEMM_NT, 2.0 * a.M * a.N * a.K, gemm_tensor_bytes(a), s, a.M, a.N, a.K);
     hipLaunchKernelGGL(kern, dim3(p.tiles_m * p.tiles_n), dim3(WGM * WGN * 64), S::BYTES, s, p);
+    return (int)DP_OK;
+  };
+  // (the kinds that the encoder's projections have)
+  switch (ln ? PE_F32 : pp_kind(a)) {
+    case PE_F32: DP_TRY(launch(std::integral_constant<int, PE_F32>())); break;
+    case PE_PLAIN: DP_TRY(launch(std::integral_constant<int, PE_PLAIN>())); break;
+    case PE_RES: DP_TRY(launch(std::integral_constant<int, PE_RES>())); break;
+    case PE_ACT3: DP_TRY(launch(std::integral_constant<int, PE_ACT3>())); break;
+    default: DP_TRY(launch(std::integral_constant<int, -1>())); break;
   }
   if (hipGetLastError() != hipSuccess) return set_error(DP_EHIP, "gemm launch failed");
   if (a.ln_applied) *a.ln_applied = ln;
@@ -1177,7 +1237,7 @@ static int launch_fp8_cfg(const Fp8GemmArgs& a, hipStream_t s) {
   using S = DtlSmem<BM, BN, BK, STAGES, WGM, WGN>;
   GemmBf16Params p = fp8_params(a, BM, BN);
   p.k_tiles_per_split = p.K / BK;
-  auto kern = gemm_bf16_dtl_kernel<BM, BN, BK, STAGES, WGM, WGN, false, false, true>;
+  auto kern = gemm_bf16_dtl_kernel<BM, BN, BK, STAGES, WGM, WGN, false, false, true, false, PE_PLAIN>;
   static std::atomic<bool> attr_set{false};
   DP_TRY(set_lds_limit((const void*)kern, S::BYTES, attr_set));
   KScope ks(KK_GEMM_FP8, 2.0 * a.M * a.N * a.K, (double)a.M * a.K + (double)a.N * a.K + 2.0 * a.M * a.N, s, a.M, a.N, a.K);
