@@ -20,9 +20,21 @@
 
 namespace dp {
 
+// Quotient by a divisor known at launch, for numerators below 2^31: three instructions instead of the thirty of a division.
+struct FastDiv { uint32_t mul, shift; };
+static FastDiv make_fast_div(int d) {
+  FastDiv f;
+  f.shift = 0;
+  while ((1ull << f.shift) < (unsigned)d) ++f.shift;
+  f.mul = (uint32_t)((((1ull << f.shift) - (unsigned)d) << 32) / (unsigned)d + 1);
+  return f;
+}
+__device__ __forceinline__ int fast_div(int n, FastDiv f) { return (int)((__umulhi((uint32_t)n, f.mul) + (uint32_t)n) >> f.shift); }
+
 struct ConvParams {
   const bf16* x; const bf16* w;
   int H, W, Cin, Ho, Wo, stride;
+  FastDiv by_px, by_wo;          // Ho * Wo, Wo
   int M, N, K;                   // output pixels, output channels, 9 * C_in
   int tiles_m, tiles_n, group_m;
   int taps_uniform;              // C_in % 64 == 0: a 64-deep k-tile lies inside one filter tap
@@ -162,15 +174,11 @@ __global__ void __launch_bounds__(WGM * WGN * 64) conv3x3_bf16_kernel(const Conv
 // the 9-bit set of taps that fall inside the image for that pixel (empty for rows past M).
 __device__ __forceinline__ void conv_pixel(const ConvParams& p, int m0, int row, int lane, int& base, unsigned& taps) {
   const int gm = m0 + row, q = min(gm, p.M - 1), c = pp_piece_chunk(row, lane);
-  const int b = q / (p.Ho * p.Wo), rem = q - b * (p.Ho * p.Wo), ho = rem / p.Wo, wo = rem - ho * p.Wo;
+  const int b = fast_div(q, p.by_px), rem = q - b * (p.Ho * p.Wo), ho = fast_div(rem, p.by_wo), wo = rem - ho * p.Wo;
   const int hc = ho * p.stride, wc = wo * p.stride;
   base = (int)(2u * ((uint32_t)((b * p.H + hc) * p.W + wc) * (uint32_t)p.Cin + (uint32_t)c * 8u));
-  unsigned m = 0;
-#pragma unroll
-  for (int tap = 0; tap < 9; ++tap) {
-    const int hi = hc + tap / 3 - 1, wi = wc + tap % 3 - 1;
-    m |= (unsigned)((unsigned)hi < (unsigned)p.H && (unsigned)wi < (unsigned)p.W) << tap;
-  }
+  const unsigned cols = (wc > 0 ? 1u : 0u) | 2u | (wc + 1 < p.W ? 4u : 0u);      // (the centre tap is always inside)
+  const unsigned m = (hc > 0 ? cols : 0u) | cols << 3 | (hc + 1 < p.H ? cols << 6 : 0u);
   taps = gm < p.M ? m : 0u;
 }
 
@@ -218,52 +226,72 @@ __device__ __forceinline__ void conv_reduce_rows(float (&v)[16], int lane, float
 
 // Epilogue of one band: the 32 rows x W columns of fp32 values at Cw.  row0, col0: output row and column of the band; column(lc): the
 // output column of slab column lc, relative to col0 (and to stat).  stat: where the band's sums go, the sums of squares ld later.
+template <int W> struct ConvBand {      // lanes by chunk of eight channels and row; rows per pass over the band and passes
+  static constexpr int CH = W / 8, RPI = 64 / CH, NIT = 32 / RPI;
+};
+// The band's residual.  A wave requests that of both its bands before it begins with the first: one after the other, each wait of 2 to 3 us for memory
+// was a quarter of the epilogue.
 template <int W, class Column>
+__device__ __forceinline__ void conv_band_request(const ConvParams& p, int row0, int col0, int lane, bf16x8 (&o)[ConvBand<W>::NIT], Column column) {
+  using B = ConvBand<W>;
+  const EpiParams<bf16>& e = p.epi;
+  const int n = min(col0 + column((lane % B::CH) * 8), e.N - 8), r = row0 + lane / B::CH;
+#pragma unroll
+  for (int it = 0; it < B::NIT; ++it) o[it] = *reinterpret_cast<const bf16x8*>((const bf16*)e.residual + (size_t)min(r + it * B::RPI, e.M - 1) * e.ld_res + n);
+}
+template <int W, bool RES, class Column>
 __device__ __forceinline__ void conv_band_epilogue(const ConvParams& p, const float* Cw, int c_ld, int row0, int col0, int lane, float* stat, int ld,
-                                                   Column column) {
-  constexpr int CH = W / 8, RPI = 64 / CH, NIT = 32 / RPI;      // rows per pass over the band and passes
+                                                   bf16x8 (&o)[ConvBand<W>::NIT], Column column) {
+  constexpr int CH = ConvBand<W>::CH, RPI = ConvBand<W>::RPI, NIT = ConvBand<W>::NIT;
   static_assert(RPI == 4 || RPI == 8 || RPI == 16, "band shape");
   const EpiParams<bf16>& e = p.epi;
   const int lc = (lane % CH) * 8, lr = lane / CH, nt = column(lc), n = col0 + nt;
   float bias[8];
   pp_bias(e.bias, min(n, e.N - 8), bias);
-  bf16x8 o[NIT];
-#pragma unroll
-  for (int it = 0; it < NIT; ++it)
-    o[it] = e.residual ? *reinterpret_cast<const bf16x8*>((const bf16*)e.residual + (size_t)min(row0 + it * RPI + lr, e.M - 1) * e.ld_res + min(n, e.N - 8)) : zero8();
+  bf16* out = e.out + (size_t)(row0 + lr) * e.ldo + n;
 #pragma unroll
   for (int it = 0; it < NIT; ++it) {
-    const int m = row0 + it * RPI + lr;
     float v[8];
     pp_slab_row(&Cw[(it * RPI + lr) * c_ld + lc], v);
 #pragma unroll
-    for (int t = 0; t < 8; ++t) o[it][t] = (bf16)((v[t] + bias[t]) + (float)o[it][t]);
-    if (m < e.M && n < e.N) *reinterpret_cast<bf16x8*>(e.out + (size_t)m * e.ldo + n) = o[it];
+    for (int t = 0; t < 8; ++t) o[it][t] = (bf16)(RES ? (v[t] + bias[t]) + (float)o[it][t] : v[t] + bias[t]);
+    if (row0 + it * RPI + lr < e.M && n < e.N) *reinterpret_cast<bf16x8*>(out + (size_t)(it * RPI) * e.ldo) = o[it];
   }
   if (!p.gn_partial) return;      // otherwise every row exists
-  // sums over the rows with equal r % 8, ascending; then pairwise over the bits of r % 8
-  float v[RPI == 4 ? 2 : 1][16];
+  // sums over the rows with equal r % 8: r and r + 8 in one instruction, onto them r + 16 and r + 24; then pairwise over the bits of r % 8
+  constexpr int PAR = RPI == 4 ? 2 : 1;
+  float v[PAR][16];
 #pragma unroll
   for (int t = 0; t < 16; ++t)
 #pragma unroll
-    for (int a = 0; a < (RPI == 4 ? 2 : 1); ++a) v[a][t] = 0.f;
+    for (int a = 0; a < PAR; ++a) v[a][t] = 0.f;
+  const bf16x2 one = {(bf16)1.f, (bf16)1.f};
 #pragma unroll
-  for (int it = 0; it < NIT; ++it)
+  for (int a = 0; a < PAR; ++a)
 #pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      const float f = (float)o[it][t];
-      float& cs = v[RPI == 4 ? it % 2 : 0][t];
-      float& cq = v[RPI == 4 ? it % 2 : 0][t + 8];
+    for (int half = 0; half < 2; ++half) {
+      const int i0 = RPI == 4 ? 4 * half + a : (RPI == 8 ? 2 * half : half), i1 = RPI == 4 ? i0 + 2 : i0 + 1;
+      u32x4 x = __builtin_bit_cast(u32x4, o[i0]), y = x;
       if constexpr (RPI == 16) {      // rows lr and lr + 8 of this pass lie in the two halves of the wave
-        const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, f), __builtin_bit_cast(uint32_t, f), false, false);
-        const uint32_t lo = r[0], hi = r[1];
-        const float f0 = __builtin_bit_cast(float, lo), f1 = __builtin_bit_cast(float, hi);
-        cs = (cs + f0) + f1; cq = fmaf(f1, f1, fmaf(f0, f0, cq));
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const auto r = __builtin_amdgcn_permlane32_swap(x[j], x[j], false, false);
+          const uint32_t lo = r[0], hi = r[1];
+          x[j] = lo; y[j] = hi;
+        }
       } else {
-        cs += f; cq = fmaf(f, f, cq);
+        y = __builtin_bit_cast(u32x4, o[i1 < NIT ? i1 : 0]);
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const bf16x2 c0 = __builtin_bit_cast(bf16x2, __builtin_amdgcn_perm(y[j], x[j], 0x05040100u)), c1 = __builtin_bit_cast(bf16x2, __builtin_amdgcn_perm(y[j], x[j], 0x07060302u));
+        v[a][2 * j] = __builtin_amdgcn_fdot2_f32_bf16(c0, one, v[a][2 * j], false);
+        v[a][2 * j + 1] = __builtin_amdgcn_fdot2_f32_bf16(c1, one, v[a][2 * j + 1], false);
+        v[a][8 + 2 * j] = __builtin_amdgcn_fdot2_f32_bf16(c0, c0, v[a][8 + 2 * j], false);
+        v[a][9 + 2 * j] = __builtin_amdgcn_fdot2_f32_bf16(c1, c1, v[a][9 + 2 * j], false);
       }
     }
-  if constexpr (RPI == 4) {
+  if constexpr (PAR == 2) {
 #pragma unroll
     for (int t = 0; t < 16; ++t) v[0][t] += v[1][t];
   }
@@ -281,7 +309,7 @@ __device__ __forceinline__ void conv_store_stats(const ConvParams& p, const floa
   }
 }
 
-template <class T>
+template <class T, bool RES>
 __global__ void __launch_bounds__(512, 2) conv3x3_pp_kernel(const ConvParams p, uint32_t x_bytes, uint32_t w_bytes) {
   constexpr uint32_t OUTSIDE = 0xFFFFFFF0u;          // an offset past any buffer this kernel accepts: the copy delivers zeros
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
@@ -345,6 +373,12 @@ __global__ void __launch_bounds__(512, 2) conv3x3_pp_kernel(const ConvParams p, 
   static_assert(T::SM == 32 && T::WGM * 2 * 32 == T::BM, "epilogue shape");
   float* Cw = reinterpret_cast<float*>(smem_raw) + wave * 32 * T::C_LD;
   float* stat = reinterpret_cast<float*>(smem_raw + T::EPI_BYTES);      // [band][sum | sum of squares][BN], past the slabs
+  auto column = [&](int lc) { return lc < T::SN0 ? wn * T::SN0 + lc : T::BN0 + wn * T::SN1 + lc - T::SN0; };
+  bf16x8 o[2][ConvBand<T::W>::NIT];
+  if constexpr (RES) {
+#pragma unroll
+    for (int ha = 0; ha < 2; ++ha) conv_band_request<T::W>(p, m0 + ha * (T::BM / 2) + wm * 32, n0, lane, o[ha], column);
+  }
 #pragma unroll
   for (int ha = 0; ha < 2; ++ha) {
 #pragma unroll
@@ -352,8 +386,7 @@ __global__ void __launch_bounds__(512, 2) conv3x3_pp_kernel(const ConvParams p, 
 #pragma unroll
       for (int r = 0; r < 16; ++r) Cw[acc_row(r, lane >> 5) * T::C_LD + j * 32 + (lane & 31)] = acc[ha][0][j][r];
     asm volatile("" ::: "memory");
-    conv_band_epilogue<T::W>(p, Cw, T::C_LD, m0 + ha * (T::BM / 2) + wm * 32, n0, lane, stat + (size_t)(ha * T::WGM + wm) * 2 * T::BN, T::BN,
-                             [&](int lc) { return lc < T::SN0 ? wn * T::SN0 + lc : T::BN0 + wn * T::SN1 + lc - T::SN0; });
+    conv_band_epilogue<T::W, RES>(p, Cw, T::C_LD, m0 + ha * (T::BM / 2) + wm * 32, n0, lane, stat + (size_t)(ha * T::WGM + wm) * 2 * T::BN, T::BN, o[ha], column);
     asm volatile("" ::: "memory");
   }
   if (!p.gn_partial) return;
@@ -377,7 +410,7 @@ struct ConvSmallTile {
   static_assert(WM == 32 && WN % 32 == 0 && A_BYTES % (1024 * NW) == 0 && B_BYTES % (1024 * NW) == 0, "tile shape");
 };
 
-template <class T>
+template <class T, bool RES>
 __global__ void __launch_bounds__(T::NW * 64) conv3x3_small_kernel(const ConvParams p, uint32_t x_bytes, uint32_t w_bytes) {
   constexpr uint32_t OUTSIDE = 0xFFFFFFF0u;
   constexpr int LA = T::LA, LB = T::LB;
@@ -461,13 +494,15 @@ __global__ void __launch_bounds__(T::NW * 64) conv3x3_small_kernel(const ConvPar
   __syncthreads();
   float* Cw = reinterpret_cast<float*>(smem_raw) + wave * 32 * T::C_LD;
   float* stat = reinterpret_cast<float*>(smem_raw + T::EPI_BYTES);      // [band][sum | sum of squares][BN], past the slabs
+  auto column = [](int lc) { return lc; };
+  bf16x8 o[ConvBand<T::WN>::NIT];
+  if constexpr (RES) conv_band_request<T::WN>(p, m0 + wm * 32, n0 + wn * T::WN, lane, o, column);
 #pragma unroll
   for (int j = 0; j < T::TN; ++j)
 #pragma unroll
     for (int r = 0; r < 16; ++r) Cw[acc_row(r, g) * T::C_LD + j * 32 + l32] = acc[j][r];
   asm volatile("" ::: "memory");
-  conv_band_epilogue<T::WN>(p, Cw, T::C_LD, m0 + wm * 32, n0 + wn * T::WN, lane, stat + (size_t)wm * 2 * T::BN + wn * T::WN, T::BN,
-                            [](int lc) { return lc; });
+  conv_band_epilogue<T::WN, RES>(p, Cw, T::C_LD, m0 + wm * 32, n0 + wn * T::WN, lane, stat + (size_t)wm * 2 * T::BN + wn * T::WN, T::BN, o, column);
   if (!p.gn_partial) return;
   __syncthreads();
   conv_store_stats<T::BM, T::BN>(p, stat, tile_m, n0, m0, tid, T::NW * 64);
@@ -509,7 +544,7 @@ __global__ void __launch_bounds__(256, 4) conv3x3_in8_kernel(const ConvParams p,
   bf16x8 px[5];
   auto fetch = [&](int row0) {
     const int gm = row0 + l32, q = min(gm, p.M - 1), hw = p.Ho * p.Wo;
-    const int b = q / hw, rem = q - b * hw, ho = rem / p.Wo, wo = rem - ho * p.Wo;
+    const int b = fast_div(q, p.by_px), rem = q - b * hw, ho = fast_div(rem, p.by_wo), wo = rem - ho * p.Wo;
     const int hc = ho * p.stride, wc = wo * p.stride, base = (b * p.H + hc) * p.W + wc;
 #pragma unroll
     for (int s = 0; s < 5; ++s) {
@@ -600,6 +635,16 @@ __global__ void __launch_bounds__(256, 4) conv3x3_in8_kernel(const ConvParams p,
   }
 }
 
+template <class Kern>
+static int launch_conv_kernel(Kern kern, std::atomic<bool>& attr_set, long n, int threads, size_t lds, const ConvParams& p, size_t x_bytes, size_t w_bytes, hipStream_t s) {
+  if (!attr_set.load(std::memory_order_acquire)) {   // setting it twice is harmless; the flag only saves the call
+    if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+      return set_error(DP_EHIP, "hipFuncSetAttribute(conv) failed");
+    attr_set.store(true, std::memory_order_release);
+  }
+  hipLaunchKernelGGL(kern, dim3((unsigned)n), dim3(threads), lds, s, p, (uint32_t)x_bytes, (uint32_t)w_bytes);
+  return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "conv launch failed");
+}
 template <class T>
 static int launch_conv_pp(ConvParams& p, size_t x_bytes, size_t w_bytes, hipStream_t s) {
   constexpr size_t LDS = T::EPI_BYTES + (size_t)T::BM / 32 * 2 * T::BN * 4 > T::BYTES ? T::EPI_BYTES + (size_t)T::BM / 32 * 2 * T::BN * 4 : T::BYTES;
@@ -608,15 +653,9 @@ static int launch_conv_pp(ConvParams& p, size_t x_bytes, size_t w_bytes, hipStre
   // whole tile-rows per XCD: the tiles that share a band of input pixels run on one L2
   const long n = (long)p.tiles_m * p.tiles_n, ppx = (n + 7) / 8;
   p.group_m = (int)std::max<long>(1, std::min<long>((ppx + p.tiles_n / 2) / p.tiles_n, p.tiles_m));
-  auto kern = conv3x3_pp_kernel<T>;
-  static std::atomic<bool> attr_set{false};   // setting it twice is harmless; the flag only saves the call
-  if (!attr_set.load(std::memory_order_acquire)) {
-    if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS) != hipSuccess)
-      return set_error(DP_EHIP, "hipFuncSetAttribute(conv) failed");
-    attr_set.store(true, std::memory_order_release);
-  }
-  hipLaunchKernelGGL(kern, dim3((unsigned)n), dim3(512), LDS, s, p, (uint32_t)x_bytes, (uint32_t)w_bytes);
-  return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "conv launch failed");
+  static std::atomic<bool> set_res{false}, set_plain{false};
+  return p.epi.residual ? launch_conv_kernel(conv3x3_pp_kernel<T, true>, set_res, n, 512, LDS, p, x_bytes, w_bytes, s)
+                        : launch_conv_kernel(conv3x3_pp_kernel<T, false>, set_plain, n, 512, LDS, p, x_bytes, w_bytes, s);
 }
 
 template <int BM, int BN, int WGM, int WGN>
@@ -638,15 +677,9 @@ static int launch_conv_small(ConvParams& p, size_t x_bytes, size_t w_bytes, hipS
   p.tiles_m = (p.M + T::BM - 1) / T::BM; p.tiles_n = (p.N + T::BN - 1) / T::BN;
   const long n = (long)p.tiles_m * p.tiles_n, ppx = (n + 7) / 8;
   p.group_m = (int)std::max<long>(1, std::min<long>((ppx + p.tiles_n / 2) / p.tiles_n, p.tiles_m));
-  auto kern = conv3x3_small_kernel<T>;
-  static std::atomic<bool> attr_set{false};   // setting it twice is harmless; the flag only saves the call
-  if (!attr_set.load(std::memory_order_acquire)) {
-    if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)T::BYTES) != hipSuccess)
-      return set_error(DP_EHIP, "hipFuncSetAttribute(conv) failed");
-    attr_set.store(true, std::memory_order_release);
-  }
-  hipLaunchKernelGGL(kern, dim3((unsigned)n), dim3(T::NW * 64), T::BYTES, s, p, (uint32_t)x_bytes, (uint32_t)w_bytes);
-  return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "conv launch failed");
+  static std::atomic<bool> set_res{false}, set_plain{false};
+  return p.epi.residual ? launch_conv_kernel(conv3x3_small_kernel<T, true>, set_res, n, T::NW * 64, T::BYTES, p, x_bytes, w_bytes, s)
+                        : launch_conv_kernel(conv3x3_small_kernel<T, false>, set_plain, n, T::NW * 64, T::BYTES, p, x_bytes, w_bytes, s);
 }
 
 template <int TN>
@@ -675,6 +708,7 @@ int launch_conv3x3(const ConvArgs& a, hipStream_t s) {
   p.x = (const bf16*)a.x; p.w = (const bf16*)a.w;
   p.H = a.H; p.W = a.W; p.Cin = a.Cin; p.Ho = Ho; p.Wo = Wo; p.stride = a.stride;
   p.M = (int)M; p.N = a.Cout; p.K = 9 * a.Cin;
+  p.by_px = make_fast_div(Ho * Wo); p.by_wo = make_fast_div(Wo);
   p.taps_uniform = a.Cin % 64 == 0;
   p.gn_partial = nullptr; p.gn_block = 256;
   if (a.gn_applied) *a.gn_applied = 0;
