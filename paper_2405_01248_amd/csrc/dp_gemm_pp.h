@@ -67,7 +67,12 @@ __device__ __forceinline__ uint32_t pp_mc_offset(int col0, int lane) {
 // outside the buffers, so that they move nothing.
 // MC: both operands have the contraction strided.  colsum (MC only): a wave-uniform flag; csum[half][i] then receives
 // the sum over the contraction of row i of the wave's part of A (this lane's k-slots; lanes l and l + 32 hold the two halves).
-template <class T, bool FP8, bool MC, class CopyA, class CopyB>
+// AHEAD: the copies of k-tile 0 (pp_first_k_tile) are on their way already.
+template <class T, class CopyA, class CopyB>
+__device__ __forceinline__ void pp_first_k_tile(unsigned char* smem, CopyA copy_a, CopyB copy_b) {
+  copy_b(std::integral_constant<int, 0>(), 0, smem + T::OB0); copy_a(0, 0, smem); copy_b(std::integral_constant<int, 1>(), 0, smem + T::OB1); copy_a(1, 0, smem + T::A_HALF);
+}
+template <class T, bool FP8, bool MC, bool AHEAD = false, class CopyA, class CopyB>
 __device__ __forceinline__ void pp_main_loop(typename T::acc_t (&acc)[2][T::TM][T::TN], unsigned char* smem, int nk, int wm, int wn, bool trailing,
                                              int lane, CopyA copy_a, CopyB copy_b, bool colsum, float (&csum)[2][T::TM]) {
   constexpr int TM = T::TM, TN0 = T::TN0, LA = T::LA, LB0 = T::LB0, LB1 = T::LB1, FR = T::FR;
@@ -216,7 +221,7 @@ __device__ __forceinline__ void pp_main_loop(typename T::acc_t (&acc)[2][T::TM][
   constexpr std::integral_constant<int, 0> H0{};
   constexpr std::integral_constant<int, 1> H1{};
 
-  copy_b(H0, 0, stage_of(0) + T::OB0); copy_a(0, 0, stage_of(0)); copy_b(H1, 0, stage_of(0) + T::OB1); copy_a(1, 0, stage_of(0) + T::A_HALF);
+  if constexpr (!AHEAD) pp_first_k_tile<T>(smem, copy_a, copy_b);
   copy_b(H0, 1, stage_of(1) + T::OB0); copy_a(0, 1, stage_of(1)); copy_b(H1, 1, stage_of(1) + T::OB1);
   wait_vmcnt<2 * LA + LB0 + 2 * LB1>();        // the first B0 and A0 are there
   barrier_nofence();
@@ -295,6 +300,14 @@ __device__ __forceinline__ void pp_load(const EpiParams<bf16>& e, int m, int n, 
   }
 }
 
+// Takes delivery of the operands ahead of the branch around their use.  Behind the branch alone, the compiler would have to count them as on their way still
+// when their registers are used again, which in a kernel that walks over tiles is inside the main loop: a wait on each k-tile.
+template <int KIND>
+__device__ __forceinline__ void pp_arrived(PpIn<KIND>& in) {
+  if constexpr (KIND == PE_F32 || KIND == PE_RES || KIND == PE_GATE) asm volatile("" : "+v"(in.r0), "+v"(in.r1));
+  if constexpr (KIND == PE_RESH || KIND == PE_GATE || KIND == PE_DACT1 || KIND == PE_DACT2 || KIND == PE_GEGLU2) asm volatile("" : "+v"(in.a));
+  if constexpr (KIND == PE_GEGLU2) asm volatile("" : "+v"(in.b));
+}
 template <int KIND>
 __device__ __forceinline__ void pp_finish(const EpiParams<bf16>& e, int m, int n, float (&v)[8], const PpIn<KIND>& in, const float (&bias)[8]) {
   if constexpr (KIND == PE_F32) {
@@ -373,44 +386,59 @@ __device__ __forceinline__ void pp_slab_row(const float* p, float (&v)[8]) {
 
 // A wave turns its accumulators through LDS, 32 rows x W columns at a time, into 8 consecutive columns per lane.  Its two
 // column parts lie in different halves of the tile; the fused GeGLU forward has the values of an output in the first and
-// their gates in the second half (the B loader sees to that).
-template <class T, int KIND>
+// their gates in the second half (the B loader sees to that).  RPS: rows per slab.  ahead(): called once the operands of the first slab are requested.
+template <class T, int KIND, int RPS = 32, class Ahead>
 __device__ __forceinline__ void pp_epilogue(const typename T::acc_t (&acc)[2][T::TM][T::TN], unsigned char* smem, const EpiParams<bf16>& e, int m0, int n0,
-                                            int wave, int wm, int wn, int lane) {
-  float* Cw = reinterpret_cast<float*>(smem) + wave * 32 * T::C_LD;
+                                            int wave, int wm, int wn, int lane, Ahead ahead) {
+  float* Cw = reinterpret_cast<float*>(smem) + wave * RPS * T::C_LD;
   constexpr bool GG1 = KIND == PE_GEGLU1;
   static_assert(!GG1 || T::SN0 == T::SN1, "the fused GeGLU needs equal column halves");
-  constexpr int CH = (GG1 ? T::SN0 : T::W) / 8, NIT = (32 * CH + 63) / 64;
+  constexpr int CH = (GG1 ? T::SN0 : T::W) / 8, NIT = (RPS * CH + 63) / 64, PARTS = 32 / RPS;
+  static_assert(RPS == 32 || (RPS == 16 && T::FR == 32 && RPS * CH % 64 == 0), "slab");
   constexpr bool FIXED = 64 % CH == 0;              // a lane keeps its columns over the rows of a slab
   const int n_end = GG1 ? e.geglu_inner : e.N;
   auto column = [&](int lc) { return GG1 ? n0 / 2 + wn * T::SN0 + lc : n0 + (lc < T::SN0 ? wn * T::SN0 + lc : T::BN0 + wn * T::SN1 + lc - T::SN0); };
   float bias[8], bias_g[8];
-  if (FIXED) pp_bias(e.bias, min(column((lane % CH) * 8), n_end - 8), bias);
-  if (GG1) pp_bias(e.bias ? e.bias + e.geglu_inner : nullptr, min(column((lane % CH) * 8), n_end - 8), bias_g);
+  // Otherwise the bias of every pass is requested here.  Beside its use, each request stands behind the stores of the pass before, and memory operations
+  // are counted in order: the pass waits until those stores are in memory.
+  bf16x8 bias_it[FIXED ? 1 : NIT];
+  {
+    const rsrc_t rb = make_rsrc(e.bias, e.bias ? 2u * (uint32_t)n_end : 0u);      // (no bias: a buffer of no size reads as zeros)
 #pragma unroll
-  for (int s = 0; s < 2 * T::SM / 32; ++s) {
-    const int ha = s / (T::SM / 32), i32 = s % (T::SM / 32);
-    const int row0 = m0 + ha * (T::BM / 2) + wm * T::SM + i32 * 32;
+    for (int it = 0; it < (FIXED ? 1 : NIT); ++it) bias_it[it] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rb, 2 * column(((it * 64 + lane) % CH) * 8), 0, 0));
+  }
+  bf16x8 bias_g_it;
+  if constexpr (GG1) bias_g_it = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(make_rsrc(e.bias ? e.bias + e.geglu_inner : nullptr, e.bias ? 2u * (uint32_t)n_end : 0u), 2 * column((lane % CH) * 8), 0, 0));
+#pragma unroll
+  for (int s = 0; s < 2 * T::SM / RPS; ++s) {
+    const int ha = s / (T::SM / RPS), i32 = s / PARTS % (T::SM / 32), part = s % PARTS;
+    const int row0 = m0 + ha * (T::BM / 2) + wm * T::SM + i32 * 32 + part * RPS;
     PpIn<KIND> in[NIT];
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
       const int id = it * 64 + lane;
-      pp_load<KIND>(e, row0 + min(id / CH, 31), column((id % CH) * 8), in[it]);
+      pp_load<KIND>(e, row0 + min(id / CH, RPS - 1), column((id % CH) * 8), in[it]);
+    }
+    if (s == 0) {
+      ahead();
+#pragma unroll
+      for (int t = 0; t < 8; ++t) { bias[t] = (float)bias_it[0][t]; if constexpr (GG1) bias_g[t] = (float)bias_g_it[t]; }
     }
 #pragma unroll
     for (int j = 0; j < T::TN; ++j)
 #pragma unroll
       for (int i = 0; i < 32 / T::FR; ++i)
 #pragma unroll
-        for (int r = 0; r < T::ACC_REGS; ++r) {
-          const int row = T::FR == 32 ? acc_row(r, lane >> 5) : i * 16 + 4 * (lane >> 4) + r;
+        for (int r = part * (T::ACC_REGS / PARTS); r < (part + 1) * (T::ACC_REGS / PARTS); ++r) {
+          const int row = T::FR == 32 ? acc_row(r, lane >> 5) - part * RPS : i * 16 + 4 * (lane >> 4) + r;
           Cw[row * T::C_LD + j * T::FR + lane % T::FR] = acc[ha][i32 * (32 / T::FR) + i][j][r];
         }
     asm volatile("" ::: "memory");
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
       const int id = it * 64 + lane, lr = id / CH, lc = (id % CH) * 8, m = row0 + lr, n = column(lc);
-      if (32 * CH % 64 != 0 && lr >= 32) continue;
+      pp_arrived<KIND>(in[it]);
+      if (RPS * CH % 64 != 0 && lr >= RPS) continue;
       float v[8];
       pp_slab_row(&Cw[lr * T::C_LD + lc], v);
       if constexpr (GG1) {
@@ -431,7 +459,10 @@ __device__ __forceinline__ void pp_epilogue(const typename T::acc_t (&acc)[2][T:
           *reinterpret_cast<bf16x8*>(e.out + (size_t)m * e.ldo + n) = o;
         }
       } else {
-        if (!FIXED) pp_bias(e.bias, min(n, n_end - 8), bias);
+        if constexpr (!FIXED) {
+#pragma unroll
+          for (int t = 0; t < 8; ++t) bias[t] = (float)bias_it[it][t];
+        }
         if (m < e.M && n < n_end) pp_finish<KIND>(e, m, n, v, in[it], bias);
       }
     }

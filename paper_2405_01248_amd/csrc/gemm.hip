@@ -531,62 +531,100 @@ gemm_bf16_dtl_kernel(const GemmBf16Params p) {
 // ------------------------------------------------------------------ bf16 / fp8 MFMA kernel, alternating wave groups
 // y = x W^T on contraction-contiguous operands with the main loop of dp_gemm_pp.h.  KTAIL: K is not a multiple of the k-tile;
 // chunks of the last k-tile past K are fetched from outside the buffers (zeros) in both operands.
-template <class T, int KIND, bool FP8, bool KTAIL>
+// WALK: a workgroup takes the tiles blockIdx.x, + gridDim.x, ... and issues the first copies of the next tile before the epilogue of the present one, whose
+// slabs lie behind the first stage.  A round of tiles spends 1.1 us between one workgroup and the next and 1.7 until the first k-tile is there, beside 10 us of main
+// loop and 2.6 of epilogue (8-bit product of 8192 x 4608, K = 1152).  How much of the 2.8 us is gained depends on the clock, which falls as the matrix
+// cores idle less: that product with its quantisation 57.1 -> 49.5 us (bias requested ahead
+// included, alone 61.3 -> 58.1); steps of seven DiT blocks 32 x 256 x 1152 10340 -> 10080, of two U-Net blocks 8 x 1024 x 640 1700 -> 1692, 8 x 4096 x 320
+// 3381 -> 3367; the convolution of the image encoder 10297 -> 10268 (8 x 512 x 512) and 1143 -> 1149 (384 x 328): not taken there.
+template <class T> struct PpWalk {
+  static constexpr size_t slab(int rows) { return (size_t)T::NW * rows * T::C_LD * 4; }
+  static constexpr int RPS = T::FR == 32 ? 16 : 32;
+  static constexpr size_t BYTES = T::STAGE + (slab(RPS) > T::STAGE ? slab(RPS) : (size_t)T::STAGE);
+  static_assert(BYTES <= 160 * 1024, "tile shape");
+};
+template <class T, int KIND, bool FP8, bool KTAIL, bool WALK = false>
 __device__ __forceinline__ void gemm_pp_body(const GemmBf16Params& p) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave / T::WGN, wn = wave % T::WGN;
-  int tile_m, tile_n;
-  tile_of_block(blockIdx.x, p.tiles_m, p.tiles_n, p.group_m, tile_m, tile_n);
-  const int m0 = tile_m * T::BM, n0 = tile_n * T::BN;
   const int nk = (p.K + T::BK - 1) / T::BK;
   constexpr uint32_t OUTSIDE = 0xFFFFFFF0u;
   // rows past the edge are fetched from the last valid one: they only feed outputs that are never stored
   uint32_t va[2][T::LA], vb0[T::LB0], vb1[T::LB1];
-#pragma unroll
-  for (int h = 0; h < 2; ++h)
-#pragma unroll
-    for (int j = 0; j < T::LA; ++j) {
-      const int r = pp_piece_row(wave * T::LA + j, lane), c = pp_piece_chunk(r, lane);
-      va[h][j] = 2u * ((uint32_t)min(m0 + h * (T::BM / 2) + r, p.M - 1) * p.lda + c * 8);
-    }
+  int m0, n0, n_kt = nk;      // n_kt: 0 once there is no further tile; its copies then read nothing
   auto piece_b = [&](int h, int j) { return min(wave * (h ? T::LB1 : T::LB0) + j, (h ? T::B1_BYTES : T::B0_BYTES) / 1024 - 1); };
-  auto offset_b = [&](int h, int j) {
-    const int r = pp_piece_row(piece_b(h, j), lane), c = pp_piece_chunk(r, lane);
-    const int row = KIND == PE_GEGLU1 ? h * p.epi.geglu_inner + min(n0 / 2 + r, p.epi.geglu_inner - 1) : min(n0 + h * T::BN0 + r, p.N - 1);
-    return 2u * ((uint32_t)row * p.ldb + c * 8);
+  auto set_tile = [&](int id) {
+    int tile_m, tile_n, ln = lane;
+    if constexpr (WALK) asm volatile("" : "+v"(ln));      // what follows from the lane alone is formed again for each tile: it would take registers from the loop
+    tile_of_block(id, p.tiles_m, p.tiles_n, p.group_m, tile_m, tile_n);
+    m0 = tile_m * T::BM; n0 = tile_n * T::BN;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int j = 0; j < T::LA; ++j) {
+        const int r = pp_piece_row(wave * T::LA + j, ln), c = pp_piece_chunk(r, ln);
+        va[h][j] = 2u * ((uint32_t)min(m0 + h * (T::BM / 2) + r, p.M - 1) * p.lda + c * 8);
+      }
+    auto offset_b = [&](int h, int j) {
+      const int r = pp_piece_row(piece_b(h, j), ln), c = pp_piece_chunk(r, ln);
+      const int row = KIND == PE_GEGLU1 ? h * p.epi.geglu_inner + min(n0 / 2 + r, p.epi.geglu_inner - 1) : min(n0 + h * T::BN0 + r, p.N - 1);
+      return 2u * ((uint32_t)row * p.ldb + c * 8);
+    };
+#pragma unroll
+    for (int j = 0; j < T::LB0; ++j) vb0[j] = offset_b(0, j);
+#pragma unroll
+    for (int j = 0; j < T::LB1; ++j) vb1[j] = offset_b(1, j);
   };
-#pragma unroll
-  for (int j = 0; j < T::LB0; ++j) vb0[j] = offset_b(0, j);
-#pragma unroll
-  for (int j = 0; j < T::LB1; ++j) vb1[j] = offset_b(1, j);
   const int k_last = p.K - (nk - 1) * T::BK;         // columns of the last k-tile
   auto tail = [&](uint32_t v, int piece, int t) {
     if (!KTAIL || t != nk - 1) return v;
     const int r = pp_piece_row(piece, lane);
     return pp_piece_chunk(r, lane) * 8 < k_last ? v : OUTSIDE;
   };
+  auto copy_a = [&](int h, int t, unsigned char* dst) {
+    const rsrc_t r = make_rsrc(p.A, t < n_kt ? p.a_bytes : 0u);
+    const uint32_t off = t < n_kt ? (uint32_t)t * (2u * T::BK) : 0u;
+#pragma unroll
+    for (int j = 0; j < T::LA; ++j) async_copy_16B_buf(r, tail(va[h][j], wave * T::LA + j, t), off, dst + (wave * T::LA + j) * 1024);
+  };
+  auto copy_b = [&](auto hc, int t, unsigned char* dst) {
+    constexpr int h = decltype(hc)::value;
+    const rsrc_t r = make_rsrc(p.B, t < n_kt ? p.b_bytes : 0u);
+    const uint32_t off = t < n_kt ? (uint32_t)t * (2u * T::BK) : 0u;
+#pragma unroll
+    for (int j = 0; j < (h ? T::LB1 : T::LB0); ++j)
+      async_copy_16B_buf(r, tail(h ? vb1[h ? j : 0] : vb0[h ? 0 : j], piece_b(h, j), t), off, dst + piece_b(h, j) * 1024);
+  };
   typename T::acc_t acc[2][T::TM][T::TN];
   float csum[2][T::TM];
-  pp_main_loop<T, FP8, false>(acc, smem_raw, nk, wm, wn, wave >= 4, lane,
-      [&](int h, int t, unsigned char* dst) {
-        const rsrc_t r = make_rsrc(p.A, t < nk ? p.a_bytes : 0u);
-        const uint32_t off = t < nk ? (uint32_t)t * (2u * T::BK) : 0u;
-#pragma unroll
-        for (int j = 0; j < T::LA; ++j) async_copy_16B_buf(r, tail(va[h][j], wave * T::LA + j, t), off, dst + (wave * T::LA + j) * 1024);
-      },
-      [&](auto hc, int t, unsigned char* dst) {
-        constexpr int h = decltype(hc)::value;
-        const rsrc_t r = make_rsrc(p.B, t < nk ? p.b_bytes : 0u);
-        const uint32_t off = t < nk ? (uint32_t)t * (2u * T::BK) : 0u;
-#pragma unroll
-        for (int j = 0; j < (h ? T::LB1 : T::LB0); ++j)
-          async_copy_16B_buf(r, tail(h ? vb1[h ? j : 0] : vb0[h ? 0 : j], piece_b(h, j), t), off, dst + piece_b(h, j) * 1024);
-      }, false, csum);
-  pp_epilogue<T, KIND>(acc, smem_raw, p.epi, m0, n0, wave, wm, wn, lane);
+  set_tile(blockIdx.x);
+  if constexpr (!WALK) {
+    pp_main_loop<T, FP8, false>(acc, smem_raw, nk, wm, wn, wave >= 4, lane, copy_a, copy_b, false, csum);
+    pp_epilogue<T, KIND, 32>(acc, smem_raw, p.epi, m0, n0, wave, wm, wn, lane, []() {});
+  } else {
+    const int n_tiles = p.tiles_m * p.tiles_n;
+    pp_first_k_tile<T>(smem_raw, copy_a, copy_b);
+    for (int id = blockIdx.x;;) {
+      pp_main_loop<T, FP8, false, true>(acc, smem_raw, nk, wm, wn, wave >= 4, lane, copy_a, copy_b, false, csum);
+      id += gridDim.x;
+      int le = lane;
+      asm volatile("" : "+v"(le));
+      // (Without a further tile as copies of nothing: behind a branch, the compiler would have to take the shorter count of what is on its way and
+      // wait for the copies before the operands of the epilogue are used.)
+      pp_epilogue<T, KIND, PpWalk<T>::RPS>(acc, smem_raw + T::STAGE, p.epi, m0, n0, wave, wm, wn, le, [&]() {
+        n_kt = id < n_tiles ? nk : 0;
+        set_tile(min(id, n_tiles - 1));
+        pp_first_k_tile<T>(smem_raw, copy_a, copy_b);
+      });
+      if (id >= n_tiles) break;
+      lds_barrier();      // the second stage is free again
+    }
+    wait_vmcnt<0>();      // no copy outlives its LDS
+  }
 }
-template <class T, int KIND, bool FP8, bool KTAIL>
-__global__ void __launch_bounds__(512, 2) gemm_pp_kernel(const GemmBf16Params p) { gemm_pp_body<T, KIND, FP8, KTAIL>(p); }
+template <class T, int KIND, bool FP8, bool KTAIL, bool WALK = false>
+__global__ void __launch_bounds__(512, 2) gemm_pp_kernel(const GemmBf16Params p) { gemm_pp_body<T, KIND, FP8, KTAIL, WALK>(p); }
 // Several products of one shape, operands and outputs at fixed distances (elements): problem blockIdx.y.
 struct GemmStrides { long a, b, out; };
 template <class T, int KIND, bool KTAIL>
@@ -1209,6 +1247,16 @@ static int launch_segments(const GemmArgs& a, int splits, hipStream_t s) {
 
 template <class T, int KIND, bool FP8, bool KTAIL>
 static int launch_pp_kernel(const GemmBf16Params& p, hipStream_t s) {
+  // up to one tile per CU there is nothing to walk to, and a part of a k-tile is rare
+  if constexpr (!KTAIL) {
+    if (p.tiles_m * p.tiles_n > kCUs) {
+      auto kern = gemm_pp_kernel<T, KIND, FP8, KTAIL, true>;
+      static std::atomic<bool> walk_set{false};
+      DP_TRY(set_lds_limit((const void*)kern, PpWalk<T>::BYTES, walk_set));
+      hipLaunchKernelGGL(kern, dim3(kCUs), dim3(512), PpWalk<T>::BYTES, s, p);
+      return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "gemm launch failed");
+    }
+  }
   auto kern = gemm_pp_kernel<T, KIND, FP8, KTAIL>;
   static std::atomic<bool> attr_set{false};
   DP_TRY(set_lds_limit((const void*)kern, T::BYTES, attr_set));

@@ -110,7 +110,7 @@ __global__ void __launch_bounds__(512, 2) gemm_dw_group_kernel(const DwGroup grp
   EpiParams<bf16> e{};
   e.M = M; e.N = N; e.out32 = e0.out; e.ldo32 = N; e.accumulate = e0.accumulate;
   e.partial = e0.splits > 1 ? e0.partial + (size_t)split * M * N : nullptr;
-  pp_epilogue<T, PE_F32>(acc, smem_raw, e, m0, n0, wave, wm, wn, lane);
+  pp_epilogue<T, PE_F32>(acc, smem_raw, e, m0, n0, wave, wm, wn, lane, []() {});
 }
 
 // out (+)= sum of the partial planes in ascending order, for every split problem of the group and its column sums.

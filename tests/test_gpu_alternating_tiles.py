@@ -18,6 +18,32 @@ def test_forward_tiles(tile_cfg):
         assert e <= TOL_BF16
 
 
+@pytest.mark.parametrize("K", [64, 128, 320])
+@pytest.mark.parametrize("tile_cfg,width", [(18, 256), (19, 128), (20, 192), (21, 160)])
+def test_workgroups_that_walk_over_tiles(tile_cfg, width, K):
+    # beyond 256 tiles: two of 256 workgroups take a second tile; all but two take a second one, ragged on both sides; 1, 2 and 5 k-tiles
+    for M, N in [(43 * 256, 6 * width), (34 * 256 - 3, 15 * width - 8)]:
+        e = _gemm_case("nt", M, N, K, tile_cfg, seed=M + K)
+        print(f"\n[gemm nt cfg {tile_cfg} {M}x{N}x{K}] rel err {e:.2e}", flush=True)
+        assert e <= TOL_BF16
+
+
+@pytest.mark.parametrize("kind", ["dit", "unet"])
+def test_stage_of_more_tiles_than_compute_units(kind):
+    # the kinds of epilogue of a stage behind workgroups that walk over tiles: 259 row tiles, the last one ragged
+    import torch
+    import synth_inputs as si
+    from paper_2405_01248_amd.harness import DeviceStage
+    from test_gpu_parity import _compare, _oracle_stage
+    ctx = (0, 0) if kind == "dit" else (8, 64)
+    cfg = si.StageConfig("walk_" + kind, si.DIT if kind == "dit" else si.UNET, "bf16", 1, 331, 200, 128, 2, 64, *ctx, 512, 1e-6 if kind == "dit" else 1e-5, int(kind == "dit"))
+    inp = si.make_stage_inputs(cfg, seed=3)
+    ds = DeviceStage(cfg, inp)
+    ds.step()
+    torch.cuda.synchronize()
+    _compare(cfg, ds.results(), _oracle_stage(cfg, inp))
+
+
 @pytest.mark.parametrize("tile_cfg", [26, 27, 28, 29])
 def test_tiles_whose_waves_share_the_contraction(tile_cfg):
     # fewer k-tiles than waves, as many, one more; a part of a tile and ragged edges
