@@ -22,20 +22,17 @@ struct GemmF32Params {
   EpiParams<float> epi;
 };
 
+// problems of a grouped launch, and the tiles from which a problem fills the chip several times over by itself
+constexpr int GEMM_F32_GROUP_MAX = 8, GEMM_F32_GROUP_TILES = 4096;
 constexpr long GEMM_F32_GRID_X = 1l << 22, GEMM_F32_GRID_Y = 65535;      // (the threads of a grid's first dimension are counted in 32 bits)
-// ANY: contractions and leading dimensions that are not multiples of 4 (one value per load instead of 16 bytes along the contraction), and any
+// One tile.  ANY: contractions and leading dimensions that are not multiples of 4 (one value per load instead of 16 bytes along the contraction), and any
 // number of tiles.  A kernel of its own: looking for the folds costs each of a small stage's launches 0.1 to 0.3 us.
 template <int NW, bool A_MC, bool B_MC, bool ANY>
-__global__ void __launch_bounds__(NW * 64) gemm_f32_kernel(const GemmF32Params p) {
+__device__ __forceinline__ void gemm_f32_tile(const GemmF32Params& p, int tile_m, int tile_n) {
   constexpr int U = 4;                // chunks in flight per wave
   __shared__ float red[NW][32][33];
   __shared__ float csred[NW][32];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l16 = lane & 15, q = lane >> 4;
-  int tile_m = blockIdx.y, tile_n = blockIdx.x;
-  if (ANY) {
-    tile_m += (int)(blockIdx.z % p.fold_m * GEMM_F32_GRID_Y); tile_n += (int)(blockIdx.z / p.fold_m * GEMM_F32_GRID_X);
-    if ((long)tile_m * 32 >= p.M || (long)tile_n * 32 >= p.N) return;
-  }
   const int m0 = tile_m * 32, n0 = tile_n * 32, chunks = (p.K + 15) / 16;
   f32x4 acc[2][2];
   float cs[2] = {0.f, 0.f};
@@ -120,6 +117,26 @@ __global__ void __launch_bounds__(NW * 64) gemm_f32_kernel(const GemmF32Params p
   }
 }
 
+template <int NW, bool A_MC, bool B_MC, bool ANY>
+__global__ void __launch_bounds__(NW * 64) gemm_f32_kernel(const GemmF32Params p) {
+  int tile_m = blockIdx.y, tile_n = blockIdx.x;
+  if (ANY) {
+    tile_m += (int)(blockIdx.z % p.fold_m * GEMM_F32_GRID_Y); tile_n += (int)(blockIdx.z / p.fold_m * GEMM_F32_GRID_X);
+    if ((long)tile_m * 32 >= p.M || (long)tile_n * 32 >= p.N) return;
+  }
+  gemm_f32_tile<NW, A_MC, B_MC, ANY>(p, tile_m, tile_n);
+}
+// Several weight gradients (both operands contraction-strided) in one launch: problem i has the workgroups from first[i] on.
+struct GemmF32Group { GemmF32Params p[GEMM_F32_GROUP_MAX]; int first[GEMM_F32_GROUP_MAX], n; };
+template <int NW>
+__global__ void __launch_bounds__(NW * 64) gemm_f32_group_kernel(const GemmF32Group g) {
+  int i = 0;
+  while (i + 1 < g.n && (int)blockIdx.x >= g.first[i + 1]) ++i;
+  const GemmF32Params& p = g.p[i];
+  const int tiles_n = (p.N + 31) / 32, id = blockIdx.x - g.first[i];
+  gemm_f32_tile<NW, true, true, false>(p, id / tiles_n, id % tiles_n);
+}
+
 template <int NW, bool ANY>
 static void launch_f32(const GemmF32Params& p, int a_mc, int b_mc, dim3 grid, hipStream_t s) {
   const dim3 block(NW * 64);
@@ -129,14 +146,10 @@ static void launch_f32(const GemmF32Params& p, int a_mc, int b_mc, dim3 grid, hi
   else hipLaunchKernelGGL((gemm_f32_kernel<NW, false, false, ANY>), grid, block, 0, s, p);
 }
 
-int launch_gemm_f32(const GemmArgs& a, hipStream_t s) {
-  const bool wide = (a.a_mc || (a.K % 4 == 0 && a.lda % 4 == 0 && (uintptr_t)a.A % 16 == 0)) && (a.b_mc || (a.K % 4 == 0 && a.ldb % 4 == 0 && (uintptr_t)a.B % 16 == 0));
-  const long tiles_m = ((long)a.M + 31) / 32, tiles_n = ((long)a.N + 31) / 32;
-  const long fold_m = (tiles_m + GEMM_F32_GRID_Y - 1) / GEMM_F32_GRID_Y, fold_n = (tiles_n + GEMM_F32_GRID_X - 1) / GEMM_F32_GRID_X;
-  const dim3 grid((unsigned)std::min(tiles_n, GEMM_F32_GRID_X), (unsigned)std::min(tiles_m, GEMM_F32_GRID_Y), (unsigned)(fold_m * fold_n));
+static GemmF32Params f32_params(const GemmArgs& a) {
   GemmF32Params p;
   p.A = (const float*)a.A; p.B = (const float*)a.B;
-  p.M = a.M; p.N = a.N; p.K = a.K; p.lda = a.lda; p.ldb = a.ldb; p.fold_m = (int)fold_m; p.colsum = a.colsum_out; p.colsum_acc = a.accumulate;
+  p.M = a.M; p.N = a.N; p.K = a.K; p.lda = a.lda; p.ldb = a.ldb; p.fold_m = 1; p.colsum = a.colsum_out; p.colsum_acc = a.accumulate;
   EpiParams<float>& e = p.epi;
   e = EpiParams<float>();
   e.M = a.M; e.N = a.N; e.out = (float*)a.out; e.ldo = a.ldo; e.out32 = a.out_f32; e.ldo32 = a.ldo32; e.accumulate = a.accumulate;
@@ -144,12 +157,54 @@ int launch_gemm_f32(const GemmArgs& a, hipStream_t s) {
   e.dact_pre = (const float*)a.dact_pre; e.ld_dact = a.ld_dact; e.dact_kind = a.dact_kind;
   e.gate = (const float*)a.gate; e.gate_ld = a.gate_ld; e.rows_per_batch = a.rows_per_batch > 0 ? a.rows_per_batch : 1;
   e.residual = a.residual; e.ld_res = a.ld_res; e.out_scale = 1.0f;
+  return p;
+}
+int launch_gemm_f32(const GemmArgs& a, hipStream_t s) {
+  const bool wide = (a.a_mc || (a.K % 4 == 0 && a.lda % 4 == 0 && (uintptr_t)a.A % 16 == 0)) && (a.b_mc || (a.K % 4 == 0 && a.ldb % 4 == 0 && (uintptr_t)a.B % 16 == 0));
+  const long tiles_m = ((long)a.M + 31) / 32, tiles_n = ((long)a.N + 31) / 32;
+  const long fold_m = (tiles_m + GEMM_F32_GRID_Y - 1) / GEMM_F32_GRID_Y, fold_n = (tiles_n + GEMM_F32_GRID_X - 1) / GEMM_F32_GRID_X;
+  const dim3 grid((unsigned)std::min(tiles_n, GEMM_F32_GRID_X), (unsigned)std::min(tiles_m, GEMM_F32_GRID_Y), (unsigned)(fold_m * fold_n));
+  GemmF32Params p = f32_params(a);
+  p.fold_m = (int)fold_m;
   KScope ks(KK_GEMM_F32, 2.0 * a.M * a.N * a.K, 4.0 * ((double)a.M * a.K + (double)a.N * a.K + (double)a.M * a.N), s, a.M, a.N, a.K);
   // eight waves share a contraction that gives four of them more than two chunks each
   const bool any = !wide || grid.z > 1;
   if (a.K > 128) any ? launch_f32<8, true>(p, a.a_mc, a.b_mc, grid, s) : launch_f32<8, false>(p, a.a_mc, a.b_mc, grid, s);
   else any ? launch_f32<4, true>(p, a.a_mc, a.b_mc, grid, s) : launch_f32<4, false>(p, a.a_mc, a.b_mc, grid, s);
   return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "gemm(f32) launch failed");
+}
+
+// Weight gradients whose operands are all there, one launch for those of each number of waves: each alone fills a few of the CUs and costs 3.2 to 5 us of
+// dependent launch.  Every tile is computed as by a launch of its own, so no bit changes.
+int launch_gemm_f32_group(const GemmArgs* a, int n, hipStream_t s) {
+  for (int wide = 0; wide < 2; ++wide) {
+    GemmF32Group g;
+    long total = 0;
+    double flops = 0.0, bytes = 0.0;
+    const GemmArgs* first = nullptr;
+    g.n = 0;
+    auto flush = [&]() {
+      if (!g.n) return (int)DP_OK;
+      KScope ks(KK_GEMM_F32, flops, bytes, s, first->M, first->N, first->K);
+      if (wide) hipLaunchKernelGGL(gemm_f32_group_kernel<8>, dim3((unsigned)total), dim3(512), 0, s, g);
+      else hipLaunchKernelGGL(gemm_f32_group_kernel<4>, dim3((unsigned)total), dim3(256), 0, s, g);
+      g.n = 0; total = 0; flops = bytes = 0.0;
+      return hipGetLastError() == hipSuccess ? (int)DP_OK : set_error(DP_EHIP, "gemm(f32) launch failed");
+    };
+    for (int i = 0; i < n; ++i) {
+      if ((a[i].K > 128) != (wide == 1)) continue;
+      const long tiles = (((long)a[i].M + 31) / 32) * (((long)a[i].N + 31) / 32);
+      if (tiles > GEMM_F32_GROUP_TILES || !a[i].a_mc || !a[i].b_mc) { DP_TRY(launch_gemm(a[i], s)); continue; }
+      if (g.n == GEMM_F32_GROUP_MAX || total + tiles > GEMM_F32_GRID_X) DP_TRY(flush());
+      if (!g.n) first = &a[i];
+      g.first[g.n] = (int)total; g.p[g.n++] = f32_params(a[i]);
+      total += tiles;
+      flops += 2.0 * a[i].M * a[i].N * a[i].K;
+      bytes += 4.0 * ((double)a[i].M * a[i].K + (double)a[i].N * a[i].K + (double)a[i].M * a[i].N);
+    }
+    DP_TRY(flush());
+  }
+  return DP_OK;
 }
 
 }  // namespace dp

@@ -346,21 +346,20 @@ struct Side {
   }
 };
 
-// Weight- and bias-gradient work of one block.  bf16 stages collect it and launch it for the whole block (flush); otherwise, and
-// where a problem does not fit the grouped kernel, every piece is launched as it comes.
+// Weight- and bias-gradient work of one block, collected and launched together (flush); where a bf16 problem does not fit the grouped kernel, every
+// piece by itself.
 struct BlockGrads {
   const dp_stage& s; BwdScratch& b; hipStream_t st; int acc;
   GemmArgs dw[DW_GROUP_MAX]; int n_dw = 0;
   LnBwdArgs ln[LN_REDUCE_MAX]; int n_ln = 0;
-  bool defer;
-  BlockGrads(const dp_stage& s_, BwdScratch& b_, hipStream_t st_, int acc_) : s(s_), b(b_), st(st_), acc(acc_), defer(s_.es == 2) {}
+  BlockGrads(const dp_stage& s_, BwdScratch& b_, hipStream_t st_, int acc_) : s(s_), b(b_), st(st_), acc(acc_) {}
 
   // dW[N, K] = gy[M, N]^T x[M, K], and db[N] = column sums of gy
   int weight(const void* gy, int M, int N, const void* x, int K, float* dW, float* db) {
     GemmArgs g = gemm_dw(s.d.dtype, gy, M, N, x, K, dW, acc, b.partial, b.partial_bytes);
     g.colsum_out = db;
-    if (defer) { dw[n_dw++] = g; return DP_OK; }
-    return one(g, st);
+    dw[n_dw++] = g;
+    return DP_OK;
   }
   int one(GemmArgs g, hipStream_t q) {
     float* db = g.colsum_out;
@@ -381,6 +380,11 @@ struct BlockGrads {
     return DP_OK;
   }
   int flush_dw(hipStream_t q) {
+    if (s.es == 4) {
+      DP_TRY(launch_gemm_f32_group(dw, n_dw, q));
+      n_dw = 0;
+      return DP_OK;
+    }
     bool group = n_dw > 0;
     for (int i = 0; i < n_dw; ++i) group = group && gemm_dw_group_supported(dw[i]);
     if (group) DP_TRY(launch_gemm_dw_group(dw, n_dw, s.dw_plan, q));
@@ -521,6 +525,7 @@ static int unet_block_bwd(const dp_stage& s, const void* const* P, const void* c
   DP_TRY(launch_attn_bwd(a, st));
   DP_TRY(bg.weight(t.dq2, T, d, u.h2, d, gf(U_WQ2), nullptr));
   DP_TRY(proj(gemm_dx(dt, t.dq2, T, d, P[U_WQ2], WT[U_WQ2], d, b.dh)));
+  if (f32) DP_TRY(bg.flush_dw(st));      // dx1 takes the place of dy, of which fp32 stages have no copy
   lb.dy = b.dh; lb.x = u.x1; lb.mean = u.mean2; lb.rstd = u.rstd2; lb.gamma = P[U_LN2_G]; lb.dres = dx2.f; lb.dres_storage = 0; set_dx(lb, dx1);
   lb.dgamma = gf(U_LN2_G); lb.dbeta = gf(U_LN2_B);
   DP_TRY(bg.layer_norm(lb, t.ln_partial[1]));
@@ -539,6 +544,7 @@ static int unet_block_bwd(const dp_stage& s, const void* const* P, const void* c
   if (dx_final) { lb.dx = dx_final; lb.dx32 = nullptr; } else set_dx(lb, out);
   lb.dgamma = gf(U_LN1_G); lb.dbeta = gf(U_LN1_B);
   DP_TRY(bg.layer_norm(lb, t.ln_partial[0]));
+  if (f32) DP_TRY(bg.flush_dw(st));      // (as above: the next block overwrites dx1)
   hipStream_t q = sd.begin();
   DP_TRY(bg.flush_dw(q));
   DP_TRY(bg.flush_ln(q));
@@ -627,6 +633,7 @@ static int dit_block_bwd(const dp_stage& s, bool last, const void* const* P, con
   DP_TRY(launch_attn_bwd(a, st));
   DP_TRY(bg.weight(t.dqkv, T, 3 * d, u.h1, d, gf(D_WQKV), gf(D_BQKV)));
   DP_TRY(proj(gemm_dx(dt, t.dqkv, T, 3 * d, P[D_WQKV], WT[D_WQKV], d, b.dh)));
+  if (es == 4) DP_TRY(bg.flush_dw(st));      // fp32 stages have one dg: what follows prepares the next block's there
   lb.dy = b.dh; lb.x = u.xin; lb.mean = u.mean1; lb.rstd = u.rstd1; lb.scale = at(u.m, d, es); lb.dres = dx1;
   if (dx_final) { lb.dx = dx_final; lb.dx32 = nullptr; } else lb.dx32 = b.f[c];
   lb.dscale = at(dm, d, es); lb.dshift = dm;
@@ -642,7 +649,6 @@ static int dit_block_bwd(const dp_stage& s, bool last, const void* const* P, con
   // the blocks in issue order, or formed for all blocks after the last); nothing on the main stream reads their results
   hipStream_t q = sd.begin();
   DP_TRY(bg.flush_ln(q));
-  bg.st = q;
   DP_TRY(bg.weight(dm, B, 6 * d, sc_in, d, gf(D_ADA_W), gf(D_ADA_B)));
   DP_TRY(bg.flush_dw(q));
   if (!b.cond_ws) {

@@ -115,6 +115,23 @@ def test_f32_gemm(layout, M, N, K):
     assert float(np.abs(out.cpu().numpy() - ref).max() / np.abs(ref).max()) <= 1e-5
 
 
+@pytest.mark.parametrize("kind,batch,tokens,blocks", [("unet", 1, 128, 3), ("unet", 3, 43, 2), ("dit", 2, 64, 3), ("dit", 5, 26, 2)])
+def test_f32_weight_gradients_in_one_launch(kind, batch, tokens, blocks):
+    # contractions of 128 (four waves) and of 129 and 130 (eight, ragged), of the context and the conditioning beside them; several blocks, whose
+    # buffers lie in each other's place; widths that are no multiple of a tile
+    import torch
+    import synth_inputs as si
+    from paper_2405_01248_amd.harness import DeviceStage
+    from test_gpu_parity import _compare, _oracle_stage
+    ctx = (7, 40) if kind == "unet" else (0, 0)
+    cfg = si.StageConfig("f32_dw_" + kind, si.UNET if kind == "unet" else si.DIT, "f32", blocks, batch, tokens, 48, 2, 24, *ctx, 72, 1e-5 if kind == "unet" else 1e-6, int(kind == "dit"))
+    inp = si.make_stage_inputs(cfg, seed=tokens)
+    ds = DeviceStage(cfg, inp)
+    ds.step()
+    torch.cuda.synchronize()
+    _compare(cfg, ds.results(), _oracle_stage(cfg, inp))
+
+
 @pytest.mark.parametrize("heads,d_head,batch,tokens,blocks", [(1, 64, 3, 9, 17), (9, 72, 33, 7, 2), (25, 80, 2, 5, 1)])
 def test_dit_backward_by_width(heads, d_head, batch, tokens, blocks):
     # LayerNorm backward with the gated branch in it: one wave and four per row, ragged rows; the conditioning gradient: less than a column
