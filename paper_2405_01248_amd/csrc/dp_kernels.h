@@ -65,7 +65,8 @@ int launch_gemm(const GemmArgs& a, hipStream_t s);
 // `count` products y = x W^T (+ bias; storage-dtype or fp32 output, choice_rows < 0), operands and outputs at these distances in elements
 int launch_gemm_strided(const GemmArgs& a, int count, long stride_a, long stride_b, long stride_out, hipStream_t s);
 int launch_gemm_f32(const GemmArgs& a, hipStream_t s);      // the fp32 part of launch_gemm
-int launch_gemm_f32_group(const GemmArgs* a, int n, hipStream_t s);      // fp32 weight gradients, n of them, in as few launches as they allow
+int launch_gemm_f32_group(const GemmArgs* a, int n, hipStream_t s);      // n independent fp32 products in as few launches as they allow
+bool gemm_f32_geglu_supported(const GemmArgs& a);
 // Bytes from the first to one past the last element of a bf16 operand; rows x inner elements, row stride ld.
 static inline size_t operand_extent_bytes(int rows, int inner, int ld) { return 2 * ((size_t)(rows - 1) * ld + inner); }
 // Several weight gradients dW = dy^T x (a_mc, b_mc, out_f32; colsum_out and accumulate as in launch_gemm) in one launch, with

@@ -27,21 +27,35 @@ constexpr int GEMM_F32_GROUP_MAX = 8, GEMM_F32_GROUP_TILES = 4096;
 constexpr long GEMM_F32_GRID_X = 1l << 22, GEMM_F32_GRID_Y = 65535;      // (the threads of a grid's first dimension are counted in 32 bits)
 // One tile.  ANY: contractions and leading dimensions that are not multiples of 4 (one value per load instead of 16 bytes along the contraction), and any
 // number of tiles.  A kernel of its own: looking for the folds costs each of a small stage's launches 0.1 to 0.3 us.
-template <int NW, bool A_MC, bool B_MC, bool ANY>
+// GG: the GeGLU around the product.  1, forward: the tile's columns of the values and of the gates, summed one after the other through the same LDS;
+// stores both and value * gelu(gate).  2, backward: the product is the gradient of value * gelu(gate); stores those of the values and of the gates.
+template <int NW, bool A_MC, bool B_MC, bool ANY, int GG = 0>
 __device__ __forceinline__ void gemm_f32_tile(const GemmF32Params& p, int tile_m, int tile_n) {
-  constexpr int U = 4;                // chunks in flight per wave
+  constexpr int U = GG == 1 ? 2 : 4;  // chunks in flight per wave
+  constexpr int BJ = GG == 1 ? 4 : 2, E = 1024 / (NW * 64);
   __shared__ float red[NW][32][33];
   __shared__ float csred[NW][32];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l16 = lane & 15, q = lane >> 4;
   const int m0 = tile_m * 32, n0 = tile_n * 32, chunks = (p.K + 15) / 16;
-  f32x4 acc[2][2];
+  f32x4 acc[2][BJ];
   float cs[2] = {0.f, 0.f};
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < BJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   const int am[2] = {min(m0 + l16, p.M - 1), min(m0 + 16 + l16, p.M - 1)};
-  const int bn[2] = {min(n0 + l16, p.N - 1), min(n0 + 16 + l16, p.N - 1)};
+  int bn[BJ];
+#pragma unroll
+  for (int j = 0; j < BJ; ++j) bn[j] = min(n0 + 16 * (j & 1) + l16, p.N - 1) + (j >> 1) * p.epi.geglu_inner;
+  float u0[GG == 2 ? E : 1], u1[GG == 2 ? E : 1];      // the saved values and gates
+  if constexpr (GG == 2) {
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int id = tid + e * NW * 64;
+      const float* u = p.epi.geglu_u + (size_t)min(m0 + id / 32, p.M - 1) * p.epi.ld_geglu + min(n0 + id % 32, p.N - 1);
+      u0[e] = u[0]; u1[e] = u[p.epi.geglu_inner];
+    }
+  }
   const bool do_cs = A_MC && p.colsum != nullptr && tile_n == 0;
   // a lane's four contraction values of chunk c: k = 16 c + 4 q + 0..3, the same for both operands
   auto fetch = [&](const float* base, int ld, bool mc, int row, int c) {
@@ -53,13 +67,13 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmF32Params& p, int tile_m
     return v;
   };
   for (int c0 = wave; c0 < chunks; c0 += NW * U) {
-    f32x4 a[U][2], b[U][2];
+    f32x4 a[U][2], b[U][BJ];
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
+      for (int i = 0; i < BJ; ++i) {
         const int c = min(c0 + NW * u, chunks - 1);      // a chunk past the wave's last one is fetched, but not multiplied
-        a[u][i] = fetch(p.A, p.lda, A_MC, am[i], c);
+        if (i < 2) a[u][i] = fetch(p.A, p.lda, A_MC, am[i], c);
         b[u][i] = fetch(p.B, p.ldb, B_MC, bn[i], c);
       }
 #pragma unroll
@@ -68,29 +82,39 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmF32Params& p, int tile_m
       if (c >= chunks) continue;
       if (c * 16 + 16 > p.K) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < BJ; ++i)
 #pragma unroll
           for (int t = 0; t < 4; ++t)
-            if (c * 16 + 4 * q + t >= p.K) { a[u][i][t] = 0.f; b[u][i][t] = 0.f; }
+            if (c * 16 + 4 * q + t >= p.K) { if (i < 2) a[u][i][t] = 0.f; b[u][i][t] = 0.f; }
       }
 #pragma unroll
       for (int t = 0; t < 4; ++t)
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
-          for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][i][t], b[u][j][t], acc[i][j], 0, 0, 0);
+          for (int j = 0; j < BJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][i][t], b[u][j][t], acc[i][j], 0, 0, 0);
       if (do_cs) {
 #pragma unroll
         for (int i = 0; i < 2; ++i) cs[i] += (a[u][i][0] + a[u][i][1]) + (a[u][i][2] + a[u][i][3]);
       }
     }
   }
+  auto put = [&](int half) {
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+      for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) red[wave][16 * i + 4 * q + r][16 * j + l16] = acc[i][j][r];
+        for (int r = 0; r < 4; ++r) red[wave][16 * i + 4 * q + r][16 * j + l16] = acc[i][2 * half + j][r];
+  };
+  auto total = [&](int e) {
+    const int id = tid + e * NW * 64, r = id / 32, c = id % 32;
+    float v = red[0][r][c];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) v += red[w][r][c];
+    return v;
+  };
+  put(0);
   if (do_cs) {
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
@@ -100,13 +124,33 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmF32Params& p, int tile_m
     }
   }
   __syncthreads();
+  float value[GG == 1 ? E : 1];
+  if constexpr (GG == 1) {
 #pragma unroll
-  for (int e = 0; e < 1024 / (NW * 64); ++e) {
-    const int id = tid + e * NW * 64, r = id / 32, c = id % 32;
-    float v = red[0][r][c];
+    for (int e = 0; e < E; ++e) value[e] = total(e);
+    __syncthreads();
+    put(1);
+    __syncthreads();
+  }
 #pragma unroll
-    for (int w = 1; w < NW; ++w) v += red[w][r][c];
-    epi_store<float>(p.epi, m0 + r, n0 + c, v);
+  for (int e = 0; e < E; ++e) {
+    const int id = tid + e * NW * 64, m = m0 + id / 32, n = n0 + id % 32;
+    const float v = total(e);
+    if constexpr (GG == 0) epi_store<float>(p.epi, m, n, v);
+    if (GG && m < p.M && n < p.N) {
+      const int inner = p.epi.geglu_inner;
+      float* o = p.epi.out + (size_t)m * p.epi.ldo + n;
+      if constexpr (GG == 1) {
+        const float uv = value[e] + (p.epi.bias ? p.epi.bias[n] : 0.f), ug = v + (p.epi.bias ? p.epi.bias[inner + n] : 0.f);
+        if (p.epi.pre_out) {
+          float* u = p.epi.pre_out + (size_t)m * p.epi.ld_pre + n;
+          u[0] = uv; u[inner] = ug;
+        }
+        *o = uv * gelu_erf_f(ug);
+      } else {
+        o[0] = v * gelu_erf_f(u1[e]); o[inner] = v * u0[e] * gelu_erf_grad_f(u1[e]);
+      }
+    }
   }
   if (do_cs && tid < 32 && m0 + tid < p.M) {
     float s = csred[0][tid];
@@ -126,15 +170,17 @@ __global__ void __launch_bounds__(NW * 64) gemm_f32_kernel(const GemmF32Params p
   }
   gemm_f32_tile<NW, A_MC, B_MC, ANY>(p, tile_m, tile_n);
 }
-// Several weight gradients (both operands contraction-strided) in one launch: problem i has the workgroups from first[i] on.
+template <int NW, bool B_MC, int GG>
+__global__ void __launch_bounds__(NW * 64) gemm_f32_geglu_kernel(const GemmF32Params p) { gemm_f32_tile<NW, false, B_MC, false, GG>(p, blockIdx.y, blockIdx.x); }
+// Several products in one launch, both operands contraction-strided (MC) or neither: problem i has the workgroups from first[i] on.
 struct GemmF32Group { GemmF32Params p[GEMM_F32_GROUP_MAX]; int first[GEMM_F32_GROUP_MAX], n; };
-template <int NW>
+template <int NW, bool MC>
 __global__ void __launch_bounds__(NW * 64) gemm_f32_group_kernel(const GemmF32Group g) {
   int i = 0;
   while (i + 1 < g.n && (int)blockIdx.x >= g.first[i + 1]) ++i;
   const GemmF32Params& p = g.p[i];
   const int tiles_n = (p.N + 31) / 32, id = blockIdx.x - g.first[i];
-  gemm_f32_tile<NW, true, true, false>(p, id / tiles_n, id % tiles_n);
+  gemm_f32_tile<NW, MC, MC, false>(p, id / tiles_n, id % tiles_n);
 }
 
 template <int NW, bool ANY>
@@ -146,6 +192,16 @@ static void launch_f32(const GemmF32Params& p, int a_mc, int b_mc, dim3 grid, hi
   else hipLaunchKernelGGL((gemm_f32_kernel<NW, false, false, ANY>), grid, block, 0, s, p);
 }
 
+// 16-byte loads along the contraction
+static bool f32_wide(const GemmArgs& a) {
+  return (a.a_mc || (a.K % 4 == 0 && a.lda % 4 == 0 && (uintptr_t)a.A % 16 == 0)) && (a.b_mc || (a.K % 4 == 0 && a.ldb % 4 == 0 && (uintptr_t)a.B % 16 == 0));
+}
+// The fused GeGLU (GemmArgs::geglu 1 and 2): a launch less, 2.6 us and the gap behind it, and no trip of the gradient through memory.  The products of
+// these sizes are bound by latency, so a tile of values and gates takes hardly longer than one of either.
+bool gemm_f32_geglu_supported(const GemmArgs& a) {
+  const long rows = ((long)a.M + 31) / 32, cols = ((long)a.geglu_inner + 31) / 32;
+  return a.dtype == F32 && !a.a_mc && a.geglu_inner > 0 && f32_wide(a) && rows <= GEMM_F32_GRID_Y && cols <= GEMM_F32_GRID_X && (a.geglu == 2 ? a.N == a.geglu_inner : !a.b_mc && a.N == 2 * a.geglu_inner);
+}
 static GemmF32Params f32_params(const GemmArgs& a) {
   GemmF32Params p;
   p.A = (const float*)a.A; p.B = (const float*)a.B;
@@ -157,16 +213,26 @@ static GemmF32Params f32_params(const GemmArgs& a) {
   e.dact_pre = (const float*)a.dact_pre; e.ld_dact = a.ld_dact; e.dact_kind = a.dact_kind;
   e.gate = (const float*)a.gate; e.gate_ld = a.gate_ld; e.rows_per_batch = a.rows_per_batch > 0 ? a.rows_per_batch : 1;
   e.residual = a.residual; e.ld_res = a.ld_res; e.out_scale = 1.0f;
+  e.geglu_inner = a.geglu_inner; e.geglu_u = (const float*)a.geglu_u; e.ld_geglu = a.ld_geglu;
   return p;
 }
 int launch_gemm_f32(const GemmArgs& a, hipStream_t s) {
-  const bool wide = (a.a_mc || (a.K % 4 == 0 && a.lda % 4 == 0 && (uintptr_t)a.A % 16 == 0)) && (a.b_mc || (a.K % 4 == 0 && a.ldb % 4 == 0 && (uintptr_t)a.B % 16 == 0));
+  const bool wide = f32_wide(a);
   const long tiles_m = ((long)a.M + 31) / 32, tiles_n = ((long)a.N + 31) / 32;
   const long fold_m = (tiles_m + GEMM_F32_GRID_Y - 1) / GEMM_F32_GRID_Y, fold_n = (tiles_n + GEMM_F32_GRID_X - 1) / GEMM_F32_GRID_X;
   const dim3 grid((unsigned)std::min(tiles_n, GEMM_F32_GRID_X), (unsigned)std::min(tiles_m, GEMM_F32_GRID_Y), (unsigned)(fold_m * fold_n));
   GemmF32Params p = f32_params(a);
   p.fold_m = (int)fold_m;
   KScope ks(KK_GEMM_F32, 2.0 * a.M * a.N * a.K, 4.0 * ((double)a.M * a.K + (double)a.N * a.K + (double)a.M * a.N), s, a.M, a.N, a.K);
+  if (a.geglu) {
+    if (!gemm_f32_geglu_supported(a)) return set_error(DP_EUNSUPPORTED, "gemm(f32): fused GeGLU not available for this problem");
+    p.N = p.epi.N = a.geglu_inner;
+    const dim3 half((unsigned)((a.geglu_inner + 31) / 32), (unsigned)tiles_m), block(a.K > 128 ? 512 : 256);
+    auto kern = a.K > 128 ? (a.geglu == 1 ? gemm_f32_geglu_kernel<8, false, 1> : (a.b_mc ? gemm_f32_geglu_kernel<8, true, 2> : gemm_f32_geglu_kernel<8, false, 2>))
+                          : (a.geglu == 1 ? gemm_f32_geglu_kernel<4, false, 1> : (a.b_mc ? gemm_f32_geglu_kernel<4, true, 2> : gemm_f32_geglu_kernel<4, false, 2>));
+    hipLaunchKernelGGL(kern, half, block, 0, s, p);
+    return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "gemm(f32) launch failed");
+  }
   // eight waves share a contraction that gives four of them more than two chunks each
   const bool any = !wide || grid.z > 1;
   if (a.K > 128) any ? launch_f32<8, true>(p, a.a_mc, a.b_mc, grid, s) : launch_f32<8, false>(p, a.a_mc, a.b_mc, grid, s);
@@ -174,10 +240,12 @@ int launch_gemm_f32(const GemmArgs& a, hipStream_t s) {
   return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "gemm(f32) launch failed");
 }
 
-// Weight gradients whose operands are all there, one launch for those of each number of waves: each alone fills a few of the CUs and costs 3.2 to 5 us of
-// dependent launch.  Every tile is computed as by a launch of its own, so no bit changes.
+// Products whose operands are all there, one launch for those of each layout and number of waves: each alone fills a few of the CUs and costs 3.2 to 5 us of
+// dependent launch (a block's seven weight gradients in two launches instead of seven: step of a U-Net block 2 x 64 x 64 144 -> 128.5 us).
+// Every tile is computed as by a launch of its own, so no bit changes.
 int launch_gemm_f32_group(const GemmArgs* a, int n, hipStream_t s) {
-  for (int wide = 0; wide < 2; ++wide) {
+  for (int kind = 0; kind < 4; ++kind) {
+    const bool eight = kind & 1, mc = kind & 2;
     GemmF32Group g;
     long total = 0;
     double flops = 0.0, bytes = 0.0;
@@ -186,15 +254,15 @@ int launch_gemm_f32_group(const GemmArgs* a, int n, hipStream_t s) {
     auto flush = [&]() {
       if (!g.n) return (int)DP_OK;
       KScope ks(KK_GEMM_F32, flops, bytes, s, first->M, first->N, first->K);
-      if (wide) hipLaunchKernelGGL(gemm_f32_group_kernel<8>, dim3((unsigned)total), dim3(512), 0, s, g);
-      else hipLaunchKernelGGL(gemm_f32_group_kernel<4>, dim3((unsigned)total), dim3(256), 0, s, g);
+      auto kern = eight ? (mc ? gemm_f32_group_kernel<8, true> : gemm_f32_group_kernel<8, false>) : (mc ? gemm_f32_group_kernel<4, true> : gemm_f32_group_kernel<4, false>);
+      hipLaunchKernelGGL(kern, dim3((unsigned)total), dim3(eight ? 512 : 256), 0, s, g);
       g.n = 0; total = 0; flops = bytes = 0.0;
       return hipGetLastError() == hipSuccess ? (int)DP_OK : set_error(DP_EHIP, "gemm(f32) launch failed");
     };
     for (int i = 0; i < n; ++i) {
-      if ((a[i].K > 128) != (wide == 1)) continue;
+      if ((a[i].K > 128) != eight || (a[i].a_mc != 0) != mc) continue;
       const long tiles = (((long)a[i].M + 31) / 32) * (((long)a[i].N + 31) / 32);
-      if (tiles > GEMM_F32_GROUP_TILES || !a[i].a_mc || !a[i].b_mc) { DP_TRY(launch_gemm(a[i], s)); continue; }
+      if (tiles > GEMM_F32_GROUP_TILES || (a[i].b_mc != 0) != mc || !f32_wide(a[i])) { DP_TRY(launch_gemm(a[i], s)); continue; }
       if (g.n == GEMM_F32_GROUP_MAX || total + tiles > GEMM_F32_GRID_X) DP_TRY(flush());
       if (!g.n) first = &a[i];
       g.first[g.n] = (int)total; g.p[g.n++] = f32_params(a[i]);

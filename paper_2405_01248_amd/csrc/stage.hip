@@ -436,7 +436,10 @@ static int unet_block_fwd(const dp_stage& s, const void* const* P, const float* 
   if (x_storage) { ln.x = x_storage; ln.x_f32 = dt == F32; ln.x32_out = const_cast<float*>(x); }
   DP_TRY(launch_ln_fwd(ln, st));
   ln.x_f32 = 1; ln.x32_out = nullptr;
-  DP_TRY(proj(gemm_fwd(dt, u.h1, T, d, P[U_WQKV], 3 * d, nullptr, u.qkv)));
+  const GemmArgs first[] = {gemm_fwd(dt, u.h1, T, d, P[U_WQKV], 3 * d, nullptr, u.qkv), gemm_fwd(dt, ctx, Tc, dc, P[U_WKV2], 2 * d, nullptr, u.kv2)};
+  const bool both = dt == F32 && !kv_side;      // the context's projection depends on nothing before it
+  if (both) DP_TRY(launch_gemm_f32_group(first, 2, st));
+  else DP_TRY(proj(first[0]));
   AttnArgs a = attn_base(s);
   a.Nk = s.d.tokens; a.q = u.qkv; a.k = at(u.qkv, d, es); a.v = at(u.qkv, 2 * d, es); a.ldq = a.ldk = a.ldv = 3 * d;
   a.o = u.a1; a.ldo = d; a.lse = u.lse1;
@@ -449,7 +452,7 @@ static int unet_block_fwd(const dp_stage& s, const void* const* P, const float* 
   DP_TRY(launch_ln_fwd(ln, st));
   DP_TRY(proj(gemm_fwd(dt, u.h2, T, d, P[U_WQ2], d, nullptr, u.q2)));
   if (kv_side) kv_side->wait(kv_batch);
-  else DP_TRY(proj(gemm_fwd(dt, ctx, Tc, dc, P[U_WKV2], 2 * d, nullptr, u.kv2)));
+  else if (!both) DP_TRY(proj(first[1]));
   a = attn_base(s);
   a.Nk = s.d.ctx_tokens; a.q = u.q2; a.ldq = d; a.k = u.kv2; a.v = at(u.kv2, d, es); a.ldk = a.ldv = 2 * d;
   a.o = u.a2; a.ldo = d; a.lse = u.lse2;
@@ -465,7 +468,7 @@ static int unet_block_fwd(const dp_stage& s, const void* const* P, const float* 
     GemmArgs f = gemm_fwd(dt, u.h3, T, d, P[U_W1], 2 * inner, P[U_B1], u.g);
     f.ldo = inner; f.pre_out = u.u; f.ld_pre = 2 * inner; f.geglu = 1; f.geglu_inner = inner;
     const bool can_fuse = gemm_geglu_fwd_supported(f);
-    if ((s.fuse & 1) && can_fuse) {
+    if ((s.fuse & 1) && (can_fuse || gemm_f32_geglu_supported(f))) {
       DP_TRY(proj(f));
     } else {
       GemmArgs v = gemm_fwd(dt, u.h3, T, d, P[U_W1], 2 * inner, P[U_B1], u.u);
@@ -497,11 +500,11 @@ static int unet_block_bwd(const dp_stage& s, const void* const* P, const void* c
   BlockGrads bg(s, b, st, acc);
   // ---- feed-forward
   DP_TRY(bg.weight(dy.h, T, d, u.g, inner, gf(U_W2), gf(U_B2)));
-  if (dt == BF16 && (s.fuse & 2)) {
-    // dg = dy W2 never reaches memory: the GEMM epilogue turns it into du = [dg gelu(gate) | dg value gelu'(gate)]
-    GemmArgs f = gemm_dx(dt, dy.h, T, d, P[U_W2], WT[U_W2], inner, t.du);
-    f.ldo = 2 * inner; f.geglu = 2; f.geglu_inner = inner; f.geglu_u = u.u; f.ld_geglu = 2 * inner;
-    DP_TRY(proj(f));
+  // dg = dy W2 never reaches memory: the GEMM epilogue turns it into du = [dg gelu(gate) | dg value gelu'(gate)]
+  GemmArgs dg = gemm_dx(dt, dy.h, T, d, P[U_W2], WT[U_W2], inner, t.du);
+  dg.ldo = 2 * inner; dg.geglu = 2; dg.geglu_inner = inner; dg.geglu_u = u.u; dg.ld_geglu = 2 * inner;
+  if ((s.fuse & 2) && (dt == BF16 || gemm_f32_geglu_supported(dg))) {
+    DP_TRY(proj(dg));
   } else {
     DP_TRY(proj(gemm_dx(dt, dy.h, T, d, P[U_W2], WT[U_W2], inner, b.dg_raw)));
     DP_TRY(launch_geglu_bwd(dt, b.dg_raw, u.u, t.du, T, inner, st));
