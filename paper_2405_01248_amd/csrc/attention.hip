@@ -851,6 +851,8 @@ __global__ void attn_dkv_reduce_kernel(const float* __restrict__ partial, int qs
 // ------------------------------------------------------------------ fp32 path (one wave per row)
 constexpr int F32_MAX_DH = 256;
 
+// Small problems: bound by the latency of one load after the other, so the loops request sixteen values at a time (order of the sums as written).  2 x 64
+// rows, 4 heads of 16: 6.0 -> 5.0 us forward, 4.9 -> 4.3 dQ; the dK/dV kernel, which reads two operands a step, takes 10.7 instead of 6.2 that way.
 __global__ void __launch_bounds__(64) attn_fwd_f32_kernel(const AttnK p, int causal) {
   extern __shared__ float sc[];        // [Nk]
   __shared__ float qs[F32_MAX_DH];
@@ -863,6 +865,7 @@ __global__ void __launch_bounds__(64) attn_fwd_f32_kernel(const AttnK p, int cau
   float mx = -INFINITY;
   for (int j = lane; j < p.Nk; j += 64) {
     float s = 0.f;
+#pragma unroll 16
     for (int t = 0; t < p.dh; ++t) s = fmaf(qs[t], kb[(size_t)j * p.ldk + t], s);
     s *= p.scale;
     if (causal && j > i) s = -INFINITY;
@@ -881,6 +884,7 @@ __global__ void __launch_bounds__(64) attn_fwd_f32_kernel(const AttnK p, int cau
   float* o = (float*)p.o + ((size_t)b * p.Nq + i) * p.ldo + h * p.dh;
   for (int t = lane; t < p.dh; t += 64) {
     float a = 0.f;
+#pragma unroll 16
     for (int j = 0; j < p.Nk; ++j) a = fmaf(sc[j], vb[(size_t)j * p.ldv + t], a);
     o[t] = a / sum;
   }
@@ -907,6 +911,7 @@ __global__ void __launch_bounds__(64) attn_bwd_dq_f32_kernel(const AttnK p) {
   __syncthreads();
   for (int j = lane; j < p.Nk; j += 64) {
     float s = 0.f, dp = 0.f;
+#pragma unroll 16
     for (int t = 0; t < p.dh; ++t) {
       s = fmaf(qs[t], kb[(size_t)j * p.ldk + t], s);
       dp = fmaf(dos[t], vb[(size_t)j * p.ldv + t], dp);
@@ -917,6 +922,7 @@ __global__ void __launch_bounds__(64) attn_bwd_dq_f32_kernel(const AttnK p) {
   float* dq = (float*)p.dq + ((size_t)b * p.Nq + i) * p.lddq + h * p.dh;
   for (int t = lane; t < p.dh; t += 64) {
     float a = 0.f;
+#pragma unroll 16
     for (int j = 0; j < p.Nk; ++j) a = fmaf(sc[j], kb[(size_t)j * p.ldk + t], a);
     dq[t] = a * p.scale;
   }
