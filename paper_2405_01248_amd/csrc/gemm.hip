@@ -995,7 +995,7 @@ int gemm_epi_split_rows(int N, int K) {
 //    direct-to-LDS tiles when they fill the CUs, else the register-staged kernel;
 //  - dW = dy^T x (both operands read through the transposing LDS load): register-staged 128x128 tiles,
 //    two workgroups per CU; 256x256 direct-to-LDS tiles for large M and N.
-static int choose_cfg(int M, int N, int K, bool a_mc, bool b_mc, bool dtl_ok, bool pp_ok, bool allow16 = true, bool may_split = false, bool ln = false, bool wave_ok = false, bool heavy = false, bool geglu_fwd = false) {
+static int choose_cfg(int M, int N, int K, bool a_mc, bool b_mc, bool dtl_ok, bool pp_ok, bool allow16 = true, bool may_split = false, bool ln = false, bool wave_ok = false, bool heavy = false, bool geglu_fwd = false, bool onto_f32 = false) {
   const long t256x256 = (long)((M + 255) / 256) * ((N + 255) / 256);
   const long t256x128 = (long)((M + 255) / 256) * ((N + 127) / 128);
   const bool dtl32 = dtl_ok && K % 32 == 0, dtl64 = dtl_ok && K % 64 == 0;
@@ -1018,6 +1018,11 @@ static int choose_cfg(int M, int N, int K, bool a_mc, bool b_mc, bool dtl_ok, bo
     static const Cand cands[] = {{17, 256, 256, 5.0f, 1.30f, true, false}, {19, 256, 192, 5.0f, 1.05f, true, false}, {20, 256, 160, 5.5f, 0.99f, true, false},
                                  {18, 256, 128, 5.0f, 0.72f, true, false}, {13, 128, 128, 0.f, 0.f, false, true}, {8, 128, 128, 5.0f, 0.75f, false, false},
                                  {6, 256, 256, 5.0f, 1.70f, false, false}, {9, 256, 128, 5.0f, 0.85f, false, true}};
+    // A product that is added to an fp32 tensor reads and writes 8 bytes an output.  Tiles of 128 rows do so when all of them are at their ends together, the
+    // 256-row ones in their rounds, the waves that share a contraction request what they read ahead (4928 x 768 in the text encoder, us: 128x128, K = 768 / 3072
+    // 10.7 -> 16.5 / 31 -> 38; 256x128, K = 768 13.5 -> 17.5; 128x128 of such waves, K = 3072 30.7 -> 31.8).  Text encoder of
+    // width 768 on 48 / 56 / 64 / 66 / 72 samples: 1336 / 1576 / 1672 / 1700 / 1883 us without these terms, 1307 / 1472 / 1566 / 1592 / 1887 with them.
+    const float outputs = onto_f32 ? (float)M * (float)N * 1e-6f : 0.f;
     int best = -1;
     float best_cost = 0.f;
     auto consider = [&](int idx, float cost) { if (best < 0 || cost < best_cost) { best = idx; best_cost = cost; } };
@@ -1026,22 +1031,25 @@ static int choose_cfg(int M, int N, int K, bool a_mc, bool b_mc, bool dtl_ok, bo
       if (geglu_fwd && (c.idx == 19 || c.idx == 20)) continue;      // its column permutation wants equal column halves, and the direct-to-LDS loaders
       if (c.idx == 20 && !allow16) continue;       // the 16x16x32 instruction sums a k-step of 32 at once: other bits than the 32x32x16 tiles
       const long tiles = (long)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
-      float cost = (float)((tiles + kCUs - 1) / kCUs) * (c.fixed + (float)((K + 63) / 64) * c.per_kt);
+      float cost = (float)((tiles + kCUs - 1) / kCUs) * (c.fixed + (float)((K + 63) / 64) * c.per_kt) + 0.9f * outputs;
       if (c.idx == 13) {
+        int z = 1;
         cost = tile128_us(tiles, K / 64, heavy);
-        if (may_split) splits_128(M, N, K, ln, heavy, &cost);
+        if (may_split) z = splits_128(M, N, K, ln, heavy, &cost);
+        if (z == 1) cost += 1.4f * outputs;
       }
       consider(c.idx, cost);
     }
     if (dtl64 && !geglu_fwd) {
       const long tiles = (long)((M + 63) / 64) * ((N + 63) / 64);
       const int z = may_split ? choose_splits_epi(tiles, K / 64) : 1;
-      consider(15, tile64_us(tiles, K / 64, z) + (z > 1 ? reduce_us(M, N, z, ln) : 0.f));
+      consider(15, tile64_us(tiles, K / 64, z) + (z > 1 ? reduce_us(M, N, z, ln) : outputs));
     }
     if (dtl64 && wave_ok)
       for (int i = 0; i < (int)(sizeof(kWave) / sizeof(kWave[0])); ++i) {
         int splits;
-        consider(25 + i, wave_us(kWave[i], M, N, K, may_split, ln, &splits));
+        const float us = wave_us(kWave[i], M, N, K, may_split, ln, &splits);
+        consider(25 + i, us + (splits > 1 ? 0.f : (kWave[i].bm == 64 ? 0.8f : 0.3f) * outputs));
       }
     if (best >= 0) return best;
     return t256x128 >= 128 ? 1 : 0;
@@ -1485,10 +1493,11 @@ static int chosen_cfg(const GemmArgs& a, int rows, bool may_split) {
   constexpr int ENTRIES = 64;
   static thread_local Entry table[ENTRIES] = {};        // n = 0: empty
   const bool pp = !a.out_f32 && pp_kind(a) >= 0, any_order = a.choice_rows == 0, wave = any_order && pp && a.geglu != 1, dtl = dtl_addressable(a), heavy = heavy_epilogue(a), geglu_fwd = a.geglu == 1;
-  const int flags = geglu_fwd << 9 | heavy << 8 | (a.a_mc != 0) | (a.b_mc != 0) << 1 | dtl << 2 | pp << 3 | any_order << 4 | may_split << 5 | (a.ln_out != nullptr) << 6 | wave << 7;
+  const bool onto_f32 = any_order && a.residual && a.residual_f32;
+  const int flags = onto_f32 << 10 | geglu_fwd << 9 | heavy << 8 | (a.a_mc != 0) | (a.b_mc != 0) << 1 | dtl << 2 | pp << 3 | any_order << 4 | may_split << 5 | (a.ln_out != nullptr) << 6 | wave << 7;
   Entry& e = table[((unsigned)rows * 0x9E3779B1u ^ (unsigned)a.N * 0x85EBCA77u ^ (unsigned)a.K * 0xC2B2AE3Du ^ (unsigned)flags * 0x27D4EB2Fu) >> 26];
   if (e.n == a.N && e.rows == rows && e.k == a.K && e.flags == flags) return e.cfg;
-  e = Entry{rows, a.N, a.K, flags, choose_cfg(rows, a.N, a.K, a.a_mc != 0, a.b_mc != 0, dtl, pp, any_order, may_split, a.ln_out != nullptr, wave, heavy, geglu_fwd)};
+  e = Entry{rows, a.N, a.K, flags, choose_cfg(rows, a.N, a.K, a.a_mc != 0, a.b_mc != 0, dtl, pp, any_order, may_split, a.ln_out != nullptr, wave, heavy, geglu_fwd, onto_f32)};
   return e.cfg;
 }
 
