@@ -165,7 +165,7 @@ KERNEL_NAMES = {"gemm_nt": "dp::gemm_pp_kernel, dp::gemm_wave_kernel, dp::gemm_b
                 "gemm_nn": "dp::cond_grad_kernel (gradient of the conditioning vectors), dp::gemm_bf16_kernel (dx = dy W)",
                 "gemm_tn": "dp::gemm_dw_group_kernel (dW = dy^T x, all of a block)",
                 "attn_fwd": "dp::attn_fwd_bf16_kernel", "attn_bwd_dq": "dp::attn_bwd_dq_bf16_kernel",
-                "attn_bwd_dkv": "dp::attn_bwd_dkv_bf16_kernel", "ln_fwd": "dp::ln_fwd_kernel", "ln_bwd": "dp::ln_bwd_kernel",
+                "attn_bwd_dkv": "dp::attn_bwd_dkv_bf16_kernel, dp::attn_bwd_short_bf16_kernel (all gradients, up to 256 keys)", "ln_fwd": "dp::ln_fwd_kernel", "ln_bwd": "dp::ln_bwd_kernel",
                 "geglu_fwd": "dp::geglu_fwd_kernel", "geglu_bwd": "dp::geglu_bwd_kernel",
                 "reduce": "dp::gemm_dw_reduce_kernel, dp::ln_bwd_reduce_kernel, dp::attn_dkv_reduce_kernel, dp::reduce_epilogue_kernel, dp::reduce_residual_ln_kernel",
                 "conv3x3": "dp::conv3x3_pp_kernel, dp::conv3x3_in8_kernel, dp::conv3x3_small_kernel by size (implicit GEMM)",
