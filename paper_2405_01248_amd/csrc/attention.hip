@@ -891,11 +891,8 @@ __global__ void __launch_bounds__(64) attn_fwd_f32_kernel(const AttnK p, int cau
   if (p.lse && lane == 0) p.lse[((size_t)b * p.H + h) * p.Nq + i] = mx + logf(sum);
 }
 
-__global__ void __launch_bounds__(64) attn_bwd_dq_f32_kernel(const AttnK p) {
-  extern __shared__ float sc[];        // [Nk]
-  __shared__ float qs[F32_MAX_DH];
-  __shared__ float dos[F32_MAX_DH];
-  const int lane = threadIdx.x, i = blockIdx.x, b = blockIdx.y / p.H, h = blockIdx.y % p.H;
+__device__ __forceinline__ void attn_bwd_dq_f32_row(const AttnK& p, int i, float* sc, float* qs, float* dos) {      // sc: [Nk]
+  const int lane = threadIdx.x, b = blockIdx.y / p.H, h = blockIdx.y % p.H;
   const float* q = (const float*)p.q + ((size_t)b * p.Nq + i) * p.ldq + h * p.dh;
   const float* dor = (const float*)p.dout + ((size_t)b * p.Nq + i) * p.lddo + h * p.dh;
   const float* kb = (const float*)p.k + (size_t)b * p.Nk * p.ldk + h * p.dh;
@@ -928,11 +925,10 @@ __global__ void __launch_bounds__(64) attn_bwd_dq_f32_kernel(const AttnK p) {
   }
 }
 
-__global__ void __launch_bounds__(64) attn_bwd_dkv_f32_kernel(const AttnK p) {
-  extern __shared__ float sc[];        // [2][Nq]: p, ds
-  __shared__ float ks[F32_MAX_DH];
-  __shared__ float vs[F32_MAX_DH];
-  const int lane = threadIdx.x, j = blockIdx.x, b = blockIdx.y / p.H, h = blockIdx.y % p.H;
+// OWN_DELTA: forms delta itself, four sums side by side, instead of reading what the dQ kernel left.
+template <bool OWN_DELTA>
+__device__ __forceinline__ void attn_bwd_dkv_f32_row(const AttnK& p, int j, float* sc, float* ks, float* vs) {      // sc: [2][Nq], p and ds
+  const int lane = threadIdx.x, b = blockIdx.y / p.H, h = blockIdx.y % p.H;
   const float* kr = (const float*)p.k + ((size_t)b * p.Nk + j) * p.ldk + h * p.dh;
   const float* vr = (const float*)p.v + ((size_t)b * p.Nk + j) * p.ldv + h * p.dh;
   const float* qb = (const float*)p.q + (size_t)b * p.Nq * p.ldq + h * p.dh;
@@ -943,14 +939,36 @@ __global__ void __launch_bounds__(64) attn_bwd_dkv_f32_kernel(const AttnK p) {
   __syncthreads();
   float* pp = sc; float* dsp = sc + p.Nq;
   for (int i = lane; i < p.Nq; i += 64) {
-    float s = 0.f, dp = 0.f;
-    for (int t = 0; t < p.dh; ++t) {
-      s = fmaf(qb[(size_t)i * p.ldq + t], ks[t], s);
-      dp = fmaf(dob[(size_t)i * p.lddo + t], vs[t], dp);
+    float s = 0.f, dp = 0.f, dlt = 0.f;
+    if constexpr (OWN_DELTA) {
+      const float* ob = (const float*)p.o + ((size_t)b * p.Nq + i) * p.ldo + h * p.dh;
+      float part[4] = {0.f, 0.f, 0.f, 0.f};
+      int t = 0;
+      for (; t + 4 <= p.dh; t += 4)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const float dor = dob[(size_t)i * p.lddo + t + u];
+          s = fmaf(qb[(size_t)i * p.ldq + t + u], ks[t + u], s);
+          dp = fmaf(dor, vs[t + u], dp);
+          part[u] = fmaf(dor, ob[t + u], part[u]);
+        }
+      for (; t < p.dh; ++t) {
+        const float dor = dob[(size_t)i * p.lddo + t];
+        s = fmaf(qb[(size_t)i * p.ldq + t], ks[t], s);
+        dp = fmaf(dor, vs[t], dp);
+        part[0] = fmaf(dor, ob[t], part[0]);
+      }
+      dlt = (part[0] + part[1]) + (part[2] + part[3]);
+    } else {
+      for (int t = 0; t < p.dh; ++t) {
+        s = fmaf(qb[(size_t)i * p.ldq + t], ks[t], s);
+        dp = fmaf(dob[(size_t)i * p.lddo + t], vs[t], dp);
+      }
+      dlt = dlt_b[i];
     }
     const float pr = expf(s * p.scale - lse_b[i]);
     pp[i] = pr;
-    dsp[i] = pr * (dp - dlt_b[i]);
+    dsp[i] = pr * (dp - dlt);
   }
   __syncthreads();
   float* dk = (float*)p.dk + ((size_t)b * p.Nk + j) * p.lddk + h * p.dh;
@@ -964,6 +982,24 @@ __global__ void __launch_bounds__(64) attn_bwd_dkv_f32_kernel(const AttnK p) {
     dk[t] = a * p.scale;
     dv[t] = c;
   }
+}
+
+__global__ void __launch_bounds__(64) attn_bwd_dq_f32_kernel(const AttnK p) {
+  extern __shared__ float sc[];
+  __shared__ float qs[F32_MAX_DH], dos[F32_MAX_DH];
+  attn_bwd_dq_f32_row(p, blockIdx.x, sc, qs, dos);
+}
+__global__ void __launch_bounds__(64) attn_bwd_dkv_f32_kernel(const AttnK p) {
+  extern __shared__ float sc[];
+  __shared__ float ks[F32_MAX_DH], vs[F32_MAX_DH];
+  attn_bwd_dkv_f32_row<false>(p, blockIdx.x, sc, ks, vs);
+}
+// Both in one launch: workgroups 0 .. Nk - 1 take keys, which are the longer work, the others queries.
+__global__ void __launch_bounds__(64) attn_bwd_both_f32_kernel(const AttnK p) {
+  extern __shared__ float sc[];
+  __shared__ float r0[F32_MAX_DH], r1[F32_MAX_DH];
+  if ((int)blockIdx.x < p.Nk) attn_bwd_dkv_f32_row<true>(p, blockIdx.x, sc, r0, r1);
+  else attn_bwd_dq_f32_row(p, blockIdx.x - p.Nk, sc, r0, r1);
 }
 
 // ------------------------------------------------------------------ host side
@@ -1129,6 +1165,13 @@ int launch_attn_bwd(const AttnArgs& a, hipStream_t s) {
       if (qsplit > 1) launch_dkv_reduce(a, qsplit, s);
     }
   } else {
+    // One launch where the dK/dV workgroups are at most two per CU and their loops short: forming delta costs each of them half as many loads again.  B x H, queries x
+    // keys, width: 2 x 4, 64 x 64, 16 12.0 -> 9.8 us; 2 x 2, 128 x 128, 16 15.6 -> 12.1; 4 x 5, 256 x 16, 32 24.4 -> 23.5; beyond the lines 4 x 4, 200 x 77, 24 44.6 -> 50.9;
+    // 1 x 1, 1024 x 1024, 64 173 -> 204.  Step of a U-Net block 2 x 64 x 64: 119 -> 112.5 us.
+    if ((long)a.Nk * a.B * a.H <= 512 && a.Nq <= 256) {
+      hipLaunchKernelGGL(attn_bwd_both_f32_kernel, dim3(a.Nk + a.Nq, a.B * a.H), dim3(64), std::max((size_t)a.Nk, (size_t)2 * a.Nq) * sizeof(float), s, k);
+      return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "attention backward launch failed");
+    }
     hipLaunchKernelGGL(attn_bwd_dq_f32_kernel, dim3(a.Nq, a.B * a.H), dim3(64), (size_t)a.Nk * sizeof(float), s, k);
     hipLaunchKernelGGL(attn_bwd_dkv_f32_kernel, dim3(a.Nk, a.B * a.H), dim3(64), (size_t)2 * a.Nq * sizeof(float), s, k);
   }

@@ -119,3 +119,33 @@ def test_waves_that_take_turns_give_the_same_bits(heads, tokens):
         torch.cuda.synchronize()
         outs.append(o[:, :dh].clone())
     assert torch.equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("B,H,Nq,Nk,dh", [(1, 1, 1, 1, 1), (2, 4, 64, 64, 16), (1, 3, 65, 63, 7), (1, 2, 256, 256, 24), (1, 2, 257, 256, 24), (1, 1, 5, 512, 33), (1, 1, 5, 513, 33), (2, 1, 130, 9, 200)])
+def test_f32_backward_in_one_launch_and_in_two(B, H, Nq, Nk, dh):
+    # one launch up to 512 keys over batch and heads and 256 queries, two beyond; widths that are no multiple of four, rows wider than the heads
+    import torch
+    from paper_2405_01248_amd import binding as bd
+    g = torch.Generator().manual_seed(Nq * 1000 + Nk)
+    d, ld = H * dh, H * dh + 3
+    q, k, v, do = (torch.randn(B, n, ld, generator=g) for n in (Nq, Nk, Nk, Nq))
+    scale = dh ** -0.5
+    Q, K, V, DO = (x[..., :d].double().reshape(B, -1, H, dh).transpose(1, 2).contiguous() for x in (q, k, v, do))
+    S = (Q @ K.transpose(2, 3).contiguous() * scale).softmax(-1)
+    O = S @ V
+    dS = S * (DO @ V.transpose(2, 3).contiguous() - (DO * O).sum(-1, keepdim=True))
+    want = {"o": O, "dq": dS @ K * scale, "dk": dS.transpose(2, 3).contiguous() @ Q * scale, "dv": S.transpose(2, 3).contiguous() @ DO}
+    q, k, v, do = (x.cuda() for x in (q, k, v, do))
+    o, dq, dk, dv = torch.full_like(q, 7.0), torch.full_like(q, 7.0), torch.full_like(k, 7.0), torch.full_like(v, 7.0)
+    lse, delta = torch.empty(B, H, Nq, device="cuda"), torch.empty(B, H, Nq, device="cuda")
+    bd.op_attention_fwd(bd.DP_F32, B, H, Nq, Nk, dh, False, scale, q, ld, k, ld, v, ld, o, ld, lse)
+    bd.op_attention_bwd(bd.DP_F32, B, H, Nq, Nk, dh, scale, q, ld, k, ld, v, ld, o, ld, lse, do, ld, delta, dq, ld, dk, ld, dv, ld)
+    torch.cuda.synchronize()
+    for name, x in (("o", o), ("dq", dq), ("dk", dk), ("dv", dv)):
+        x = x.cpu()
+        assert (x[..., d:] == 7.0).all(), name
+        got, ref = x[..., :d].double().reshape(B, -1, H, dh).transpose(1, 2), want[name]
+        # sums of at most 513 terms in fp32, logits of a few units: 513 eps / 2 would be 3e-5 if every rounding had the same sign; a gradient that
+        # cancels (one key: dS = 0) is held against the size of its terms instead
+        size = max(float(ref.norm()), 1e-2 * float(DO.norm()))
+        assert float((got - ref).norm()) <= 3e-5 * size, name
