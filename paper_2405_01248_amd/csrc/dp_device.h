@@ -107,8 +107,10 @@ __device__ __forceinline__ void async_copy_16B_buf(rsrc_t r, uint32_t lane_off, 
 // The same copy as an instruction the compiler knows nothing about.  It keeps books of the builtin's copies and waits (vmcnt) before an LDS read
 // that might touch what one of them writes: with two stages of one array, or for a transposing load, that is every read, and the copies a tile
 // ahead are waited for before the present tile is begun.  The caller waits (wait_vmcnt and a barrier) before the data is read; lds is a
-// wave-uniform LDS address, the s_nop the distance that M0 needs from its reader.  Not together with the builtin in one kernel: M0 is a
-// reserved register, which the clobber list names but the compiler does not promise to preserve or to set again.
+// wave-uniform LDS address.  The s_mov and the s_nop are the five wait states that a buffer load needs behind a vector instruction that writes a
+// scalar register it reads (a spilled part of the descriptor read back, say), which the compiler does not add for operands of inline assembly; M0 needs one of
+// them.  Not together with the builtin in one kernel: M0 is a reserved register, which the clobber list names but the compiler does not promise to
+// preserve or to set again.
 __device__ __forceinline__ u32x4 make_raw_rsrc(const void* base, uint32_t bytes) {
   const uint64_t a = (uint64_t)(uintptr_t)base;
   return u32x4{(uint32_t)a, (uint32_t)(a >> 32) & 0xFFFFu, bytes, 0x00020000u};
@@ -116,7 +118,7 @@ __device__ __forceinline__ u32x4 make_raw_rsrc(const void* base, uint32_t bytes)
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void async_copy_16B_raw(u32x4 r, uint32_t lane_off, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" : : "v"(lane_off), "s"(r), "s"(lds) : "m0", "memory");
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" : : "v"(lane_off), "s"(r), "s"(lds) : "m0", "memory");
 }
 #pragma clang diagnostic pop
 // Wait until at most N of this wave's vector-memory operations are outstanding (lgkmcnt / expcnt untouched).
