@@ -633,7 +633,6 @@ template <int DHP, int KC, int NW>
 __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) attn_bwd_short_bf16_kernel(const AttnK p) {
   using S = AttnShort<DHP, NW>;
   constexpr int DT = DHP / 32, TILE = S::TILE;
-  constexpr bool TIGHT = false;      // 256 registers: the two halves of a tile must not be scheduled into each other
   constexpr int LPR = DHP == 64 ? 8 : 16, RPP = 64 / LPR, PASSES = 64 / (NW * RPP);      // delta: lanes a row, rows a pass of a wave
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   // what the products of every tile read comes first: an LDS instruction reaches 64 KB past its base register
@@ -744,7 +743,6 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2,
     if (wave < groups) {
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
-        if (TIGHT) __builtin_amdgcn_sched_barrier(0);
         f32x16 s, dp;      // dP - delta: the products accumulate onto -delta
 #pragma unroll
         for (int r4 = 0; r4 < 4; ++r4) {
@@ -787,7 +785,6 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2,
         }
       }
     }
-    if (TIGHT) __builtin_amdgcn_sched_barrier(0);
     wait_vmcnt<0>();
     __syncthreads();      // dS is there, and the next tile
     const bool more = qt + 1 < nqt;
