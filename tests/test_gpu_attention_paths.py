@@ -149,3 +149,23 @@ def test_f32_backward_in_one_launch_and_in_two(B, H, Nq, Nk, dh):
         # cancels (one key: dS = 0) is held against the size of its terms instead
         size = max(float(ref.norm()), 1e-2 * float(DO.norm()))
         assert float((got - ref).norm()) <= 3e-5 * size, name
+
+
+@pytest.mark.parametrize("dh", [40, 64, 72, 80, 96])
+@pytest.mark.parametrize("tokens,ctx,shares", [(250, 77, 2), (293, 129, 2), (421, 77, 3), (421, 256, 3), (2100, 77, 11), (2100, 200, 11)])
+def test_shares_of_the_queries_with_all_keys_in_a_workgroup(dh, tokens, ctx, shares):
+    """Cross-attention of a stage, which has scratch for the shares' sums.  4 query tiles in shares of 2 and 2, 5 in 3 and 2, 7 in 3, 3 and 1, 33 in eleven of 3,
+    the last tile partly filled; three to six 16-wide steps over the head; four and eight waves."""
+    import torch
+    from paper_2405_01248_amd import binding as B
+    from paper_2405_01248_amd.harness import DeviceStage
+    from test_gpu_parity import _compare, _oracle_stage
+    cfg = si.StageConfig(f"shares_q{tokens}_k{ctx}_dh{dh}", si.UNET, "bf16", 1, 1, tokens, 2 * dh, 2, dh, ctx, 64, 128)
+    inp = si.make_stage_inputs(cfg, seed=tokens + dh)
+    ds = DeviceStage(cfg, inp)
+    B.ktime_begin(256)
+    ds.step()
+    torch.cuda.synchronize()
+    rows = B.ktime_end(256)
+    assert [r["k"] for r in rows if r["kind"] == "reduce" and (r["m"], r["n"]) == (ctx, 2 * dh)] == [shares], rows
+    _compare(cfg, ds.results(), _oracle_stage(cfg, inp))
