@@ -1125,6 +1125,19 @@ static int launch_attn_bwd_short(const AttnArgs& a, const AttnK& k, hipStream_t 
   return rc;
 }
 
+// Whether a result of the fp32 backward lies in the place of something that it reads.  dQ over O, dK over K and dV over V are fine for the two kernels one after
+// the other, each of which reads of those rows only what it replaces; side by side, one would overwrite what the other still reads.
+static bool writes_over_inputs(const AttnArgs& a) {
+  struct Span { uintptr_t first, end; };
+  auto span = [&](const void* x, int n, int ld) { return Span{(uintptr_t)x, (uintptr_t)x + (((size_t)a.B * n - 1) * ld + (size_t)a.H * a.d_head) * sizeof(float)}; };
+  const Span in[] = {span(a.q, a.Nq, a.ldq), span(a.k, a.Nk, a.ldk), span(a.v, a.Nk, a.ldv), span(a.o, a.Nq, a.ldo), span(a.dout, a.Nq, a.lddo)};
+  const Span out[] = {span(a.dq, a.Nq, a.lddq), span(a.dk, a.Nk, a.lddk), span(a.dv, a.Nk, a.lddv)};
+  for (const Span& i : in)
+    for (const Span& o : out)
+      if (i.first < o.end && o.first < i.end) return true;
+  return false;
+}
+
 int launch_attn_bwd(const AttnArgs& a, hipStream_t s) {
   if (int e = check_attn(a, true)) return e;
   AttnK k = make_k(a);
@@ -1165,7 +1178,7 @@ int launch_attn_bwd(const AttnArgs& a, hipStream_t s) {
     // One launch where the dK/dV workgroups are at most two per CU and their loops short: forming delta costs each of them half as many loads again.  B x H, queries x
     // keys, width: 2 x 4, 64 x 64, 16 12.0 -> 9.8 us; 2 x 2, 128 x 128, 16 15.6 -> 12.1; 4 x 5, 256 x 16, 32 24.4 -> 23.5; beyond the lines 4 x 4, 200 x 77, 24 44.6 -> 50.9;
     // 1 x 1, 1024 x 1024, 64 173 -> 204.  Step of a U-Net block 2 x 64 x 64: 119 -> 112.5 us.
-    if ((long)a.Nk * a.B * a.H <= 512 && a.Nq <= 256) {
+    if ((long)a.Nk * a.B * a.H <= 512 && a.Nq <= 256 && !writes_over_inputs(a)) {
       hipLaunchKernelGGL(attn_bwd_both_f32_kernel, dim3(a.Nk + a.Nq, a.B * a.H), dim3(64), std::max((size_t)a.Nk, (size_t)2 * a.Nq) * sizeof(float), s, k);
       return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "attention backward launch failed");
     }
