@@ -20,7 +20,9 @@
 
 namespace dp {
 
-// Quotient by a divisor known at launch, for numerators below 2^31: three instructions instead of the thirty of a division.
+// Quotient by a divisor known at launch, for numerators below 2^31: three instructions instead of the thirty of a division.  The method is that of Granlund and
+// Montgomery (Division by Invariant Integers using Multiplication, 1994): with 2^shift the power of two not below d and mul = floor(2^32 (2^shift - d) / d) + 1, the
+// quotient is (floor(mul n / 2^32) + n) / 2^shift, whose sum stays below 2^32.
 struct FastDiv { uint32_t mul, shift; };
 static FastDiv make_fast_div(int d) {
   FastDiv f;
