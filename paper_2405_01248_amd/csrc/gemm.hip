@@ -534,9 +534,10 @@ gemm_bf16_dtl_kernel(const GemmBf16Params p) {
 // WALK: a workgroup takes the tiles blockIdx.x, + gridDim.x, ... and issues the first copies of the next tile before the epilogue of the present one, whose
 // slabs lie behind the first stage.  A round of tiles spends 1.1 us between one workgroup and the next and 1.7 until the first k-tile is there, beside 10 us of main
 // loop and 2.6 of epilogue (8-bit product of 8192 x 4608, K = 1152).  How much of the 2.8 us is gained depends on the clock, which falls as the matrix
-// cores idle less: that product with its quantisation 57.1 -> 49.5 us (bias requested ahead
-// included, alone 61.3 -> 58.1); steps of seven DiT blocks 32 x 256 x 1152 10340 -> 10080, of two U-Net blocks 8 x 1024 x 640 1700 -> 1692, 8 x 4096 x 320
-// 3381 -> 3367; the convolution of the image encoder 10297 -> 10268 (8 x 512 x 512) and 1143 -> 1149 (384 x 328): not taken there.
+// cores idle less.  A pass among others, against the same code with a workgroup per tile, in turn on one card and on another: that product with its
+// quantisation 54.3 -> 53.5 and 55.4 -> 53.6 us (60.6 -> 53.4 together with the bias requested ahead in pp_epilogue); seven DiT blocks 32 x 256 x 1152
+// 10012 -> 9813 and 10049 -> 9658; two U-Net blocks 8 x 1024 x 640 1628 -> 1622, 8 x 4096 x 320 3256 -> 3240; the convolution of the image encoder
+// 10297 -> 10268 (8 x 512 x 512) and 1143 -> 1149 (384 x 328): not taken there.
 template <class T> struct PpWalk {
   static constexpr size_t slab(int rows) { return (size_t)T::NW * rows * T::C_LD * 4; }
   static constexpr int RPS = T::FR == 32 ? 16 : 32;
