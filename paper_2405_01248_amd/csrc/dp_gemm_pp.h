@@ -29,6 +29,7 @@ typedef __attribute__((ext_vector_type(8))) int i32x8;
 template <int BM_, int BN0_, int BN1_, int WGM_, int WGN_, int FR_ = 32>
 struct PpTile {
   static constexpr int BM = BM_, BN0 = BN0_, BN1 = BN1_, BN = BN0_ + BN1_, BK = 64, WGM = WGM_, WGN = WGN_, NW = WGM * WGN, FR = FR_;
+  typedef PpTile<BM_, BN0_, BN1_, WGM_, WGN_, 16> On16;                              // the same tile on the smaller instruction
   static constexpr int SM = BM / 2 / WGM, SN0 = BN0 / WGN, SN1 = BN1 / WGN;         // a wave's share of a row half and of the column halves
   static constexpr int TM = SM / FR, TN0 = SN0 / FR, TN1 = SN1 / FR, TN = TN0 + TN1, TNM = TN0 > TN1 ? TN0 : TN1;
   static constexpr int A_HALF = BM / 2 * 128, B0_BYTES = BN0 * 128, B1_BYTES = BN1 * 128, STAGE = 2 * A_HALF + B0_BYTES + B1_BYTES;
@@ -394,7 +395,7 @@ __device__ __forceinline__ void pp_epilogue(const typename T::acc_t (&acc)[2][T:
   constexpr bool GG1 = KIND == PE_GEGLU1;
   static_assert(!GG1 || T::SN0 == T::SN1, "the fused GeGLU needs equal column halves");
   constexpr int CH = (GG1 ? T::SN0 : T::W) / 8, NIT = (RPS * CH + 63) / 64, PARTS = 32 / RPS;
-  static_assert(RPS == 32 || (RPS == 16 && T::FR == 32 && RPS * CH % 64 == 0), "slab");
+  static_assert(RPS == 32 || (RPS == 16 && RPS * CH % 64 == 0), "slab");
   constexpr bool FIXED = 64 % CH == 0;              // a lane keeps its columns over the rows of a slab
   const int n_end = GG1 ? e.geglu_inner : e.N;
   auto column = [&](int lc) { return GG1 ? n0 / 2 + wn * T::SN0 + lc : n0 + (lc < T::SN0 ? wn * T::SN0 + lc : T::BN0 + wn * T::SN1 + lc - T::SN0); };
@@ -427,10 +428,10 @@ __device__ __forceinline__ void pp_epilogue(const typename T::acc_t (&acc)[2][T:
 #pragma unroll
     for (int j = 0; j < T::TN; ++j)
 #pragma unroll
-      for (int i = 0; i < 32 / T::FR; ++i)
+      for (int i = T::FR == 32 ? 0 : part * (2 / PARTS); i < (T::FR == 32 ? 1 : (part + 1) * (2 / PARTS)); ++i)
 #pragma unroll
-        for (int r = part * (T::ACC_REGS / PARTS); r < (part + 1) * (T::ACC_REGS / PARTS); ++r) {
-          const int row = T::FR == 32 ? acc_row(r, lane >> 5) - part * RPS : i * 16 + 4 * (lane >> 4) + r;
+        for (int r = T::FR == 32 ? part * (16 / PARTS) : 0; r < (T::FR == 32 ? (part + 1) * (16 / PARTS) : 4); ++r) {
+          const int row = (T::FR == 32 ? acc_row(r, lane >> 5) : i * 16 + 4 * (lane >> 4) + r) - part * RPS;
           Cw[row * T::C_LD + j * T::FR + lane % T::FR] = acc[ha][i32 * (32 / T::FR) + i][j][r];
         }
     asm volatile("" ::: "memory");

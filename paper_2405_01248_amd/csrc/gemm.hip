@@ -540,7 +540,7 @@ gemm_bf16_dtl_kernel(const GemmBf16Params p) {
 // 10297 -> 10268 (8 x 512 x 512) and 1143 -> 1149 (384 x 328): not taken there.
 template <class T> struct PpWalk {
   static constexpr size_t slab(int rows) { return (size_t)T::NW * rows * T::C_LD * 4; }
-  static constexpr int RPS = T::FR == 32 ? 16 : 32;
+  static constexpr int RPS = T::W % 32 == 0 ? 16 : 32;
   static constexpr size_t BYTES = T::STAGE + (slab(RPS) > T::STAGE ? slab(RPS) : (size_t)T::STAGE);
   static_assert(BYTES <= 160 * 1024, "tile shape");
 };
@@ -1351,9 +1351,21 @@ static int pp_kind(const GemmArgs& a) {
   return PE_PLAIN;
 }
 
+// Which instruction.  With all CUs busy the clock is set by the power that the matrix cores draw: a loop of v_mfma_f32_16x16x32 on normally distributed
+// operands runs at 2.09 GHz (2.06 PFLOP/s) where the same products by 32x32x16 hold 1.81 (1.81).  256x256 and 256x192 tiles, which come nearest to that:
+// 8192^3 781 -> 755 and 899 -> 854 us on one card; steps of two U-Net blocks 8 x 4096 x 320, seven DiT blocks 32 x 256 x 1152 and the text encoder on 64 samples
+// 3397 -> 3360, 10073 -> 9940 and 1549 -> 1487 us there, on a card whose clock falls less 3236 -> 3230, 9672 -> 9585 and 1477 -> 1469.  Tiles of
+// 128 columns wait for their operands (8192 x 5120, K = 640: 75 us either way) and keep the larger instruction, as do calls that have to agree bit for bit with
+// other tiles (choice_rows, and the fused GeGLU forward, whose bits are those of the separate kernels): the smaller one adds up 32 products at a time.
 template <class T, int KIND>
-static int launch_pp_kind(const GemmBf16Params& p, hipStream_t s) {
-  return p.K % T::BK ? launch_pp_kernel<T, KIND, false, true>(p, s) : launch_pp_kernel<T, KIND, false, false>(p, s);
+static int launch_pp_kind(const GemmBf16Params& p, bool any_order, hipStream_t s) {
+  if (p.K % T::BK) return launch_pp_kernel<T, KIND, false, true>(p, s);
+  if constexpr (T::BN >= 192 && KIND != PE_GEGLU1) {
+    constexpr bool ORDERED = KIND == PE_PLAIN || KIND == PE_RES || KIND == PE_RESH || KIND == PE_ACT3;      // the kinds that such calls have
+    if (any_order || !ORDERED) return launch_pp_kernel<typename T::On16, KIND, false, false>(p, s);
+    if constexpr (ORDERED) return launch_pp_kernel<T, KIND, false, false>(p, s);
+  }
+  return launch_pp_kernel<T, KIND, false, false>(p, s);
 }
 
 template <class T>
@@ -1415,14 +1427,15 @@ static int launch_pp(const GemmArgs& a, hipStream_t s) {
   const int kind = pp_kind(a);
   if (kind < 0) return set_error(DP_EUNSUPPORTED, "gemm: the forced configuration does not have this epilogue");
   const GemmBf16Params p = pp_params<T>(a);
+  const bool any_order = a.choice_rows == 0;
   KScope ks(KK_GEMM_NT, 2.0 * a.M * a.N * a.K, gemm_tensor_bytes(a), s, a.M, a.N, a.K);
   switch (kind) {
-#define DP_PP_CASE(k_) case k_: return launch_pp_kind<T, k_>(p, s)
+#define DP_PP_CASE(k_) case k_: return launch_pp_kind<T, k_>(p, any_order, s)
     DP_PP_CASE(PE_PLAIN); DP_PP_CASE(PE_RES); DP_PP_CASE(PE_RESH); DP_PP_CASE(PE_GATE); DP_PP_CASE(PE_ACT1); DP_PP_CASE(PE_ACT2);
     DP_PP_CASE(PE_ACT3); DP_PP_CASE(PE_DACT1); DP_PP_CASE(PE_DACT2); DP_PP_CASE(PE_GEGLU2);
 #undef DP_PP_CASE
     case PE_GEGLU1:
-      if constexpr (T::SN0 == T::SN1) return launch_pp_kind<T, PE_GEGLU1>(p, s);
+      if constexpr (T::SN0 == T::SN1) return launch_pp_kind<T, PE_GEGLU1>(p, any_order, s);
     default: return set_error(DP_EUNSUPPORTED, "gemm: epilogue kind");
   }
 }
