@@ -174,16 +174,18 @@ template <class Op> __device__ __forceinline__ float reduce_halves(float v, Op o
   const uint32_t lo = r[0], hi = r[1];
   return op(__builtin_bit_cast(float, lo), __builtin_bit_cast(float, hi));
 }
-template <class Op> __device__ __forceinline__ float wave_reduce(float v, Op op) {
-  v = reduce_halves(v, op);
+template <class Op> __device__ __forceinline__ float reduce_row_pairs(float v, Op op) {   // over lanes i and i ^ 16
   const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, v), __builtin_bit_cast(uint32_t, v), false, false);
   const uint32_t lo = r[0], hi = r[1];
-  v = op(__builtin_bit_cast(float, lo), __builtin_bit_cast(float, hi));
+  return op(__builtin_bit_cast(float, lo), __builtin_bit_cast(float, hi));
+}
+template <class Op> __device__ __forceinline__ float reduce_row(float v, Op op) {         // over a row of 16 lanes
   v = op(v, lane_dpp<0x128>(v));      // row_ror:8
   v = op(v, lane_dpp<0x124>(v));      // row_ror:4
   v = op(v, lane_dpp<0x4E>(v));       // quad_perm:[2,3,0,1]
   return op(v, lane_dpp<0xB1>(v));    // quad_perm:[1,0,3,2]
 }
+template <class Op> __device__ __forceinline__ float wave_reduce(float v, Op op) { return reduce_row(reduce_row_pairs(reduce_halves(v, op), op), op); }
 struct AddOp { __device__ __forceinline__ float operator()(float a, float b) const { return a + b; } };
 struct MaxOp { __device__ __forceinline__ float operator()(float a, float b) const { return fmaxf(a, b); } };
 __device__ __forceinline__ float wave_sum(float v) { return wave_reduce(v, AddOp()); }

@@ -8,6 +8,8 @@
 #include "dp_errors.h"
 #include "dp_ktime.h"
 
+#include <type_traits>
+
 namespace dp {
 
 template <typename T> struct Vec;
@@ -36,87 +38,119 @@ template <int V> __device__ __forceinline__ void store_f32(float* p, const float
   for (int i = 0; i < V; i += 4) *reinterpret_cast<f32x4*>(p + i) = *reinterpret_cast<const f32x4*>(in + i);
 }
 
-constexpr int LN_MAXCH = 4;   // a lane holds up to 4 vectors of the row: d <= 64 * 4 * Vec::N
+// ------------------------------------------------------------------ rows of a LayerNorm
+// L lanes share a row (256 / L rows per workgroup at a time); lane l has columns 4 (c L + l) .. + 3 for c = 0 .. NC - 1, so every access of a group
+// is L x 16 bytes in a row (fp32) and only the last chunk can be partly empty.  A wave of several rows asks for more bytes at a time and
+// adds up fewer lanes; a row's lanes are all in one wave, so nothing waits at a barrier.
+constexpr int LN_MAX_CHUNKS = 8;      // d <= 64 * 4 * 8
+struct LnShape { int lanes, chunks; };
+static LnShape ln_shape(int rows, int d) {
+  int l = d <= 384 ? 16 : (d <= 768 ? 32 : 64);
+  while (l < 64 && l * 4 < d && rows / (256 / l) < 1024) l *= 2;      // few rows: more of them side by side
+  return {l, (d + 4 * l - 1) / (4 * l)};
+}
+template <int FIRST, int LAST, class F> static void ln_with_chunks(int n, F f) {
+  if constexpr (FIRST <= LAST) {
+    if (n == FIRST) f(std::integral_constant<int, FIRST>());
+    else ln_with_chunks<FIRST + 1, LAST>(n, f);
+  }
+}
+// f(lanes, chunks) for the shapes that ln_shape() gives
+template <class F> static void ln_dispatch(LnShape sh, F f) {
+  using std::integral_constant;
+  if (sh.lanes == 16) ln_with_chunks<1, 6>(sh.chunks, [&](auto c) { f(integral_constant<int, 16>(), c); });
+  else if (sh.lanes == 32) ln_with_chunks<1, 6>(sh.chunks, [&](auto c) { f(integral_constant<int, 32>(), c); });
+  else ln_with_chunks<1, LN_MAX_CHUNKS>(sh.chunks, [&](auto c) { f(integral_constant<int, 64>(), c); });
+}
+template <int L> __device__ __forceinline__ float ln_row_sum(float v) {      // over the L lanes of a row
+  if constexpr (L == 64) v = reduce_halves(v, AddOp());
+  if constexpr (L >= 32) v = reduce_row_pairs(v, AddOp());
+  return reduce_row(v, AddOp());
+}
+template <typename T> struct Vec4 { typedef __attribute__((ext_vector_type(4))) T type; };
+template <typename T> __device__ __forceinline__ typename Vec4<T>::type load4(const T* p) { return *reinterpret_cast<const typename Vec4<T>::type*>(p); }
+template <typename T> __device__ __forceinline__ void store4(T* p, const float* in) {
+  typename Vec4<T>::type v;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] = from_f<T>(in[i]);
+  *reinterpret_cast<typename Vec4<T>::type*>(p) = v;
+}
 
 // ------------------------------------------------------------------ LayerNorm forward
-template <typename TX, typename T>
+// Bound by memory.  With a wave per row and eight columns a lane, the second chunk of 640 columns had 16 of 64 lanes: 32768 x 320 16.9 -> 12.5 us,
+// 8192 x 640 10.0 -> 8.3, 8192 x 1152 14.6 -> 12.7, 4928 x 768 6.6 -> 5.8.
+template <typename TX, typename T, int L, int NC>
 __global__ void __launch_bounds__(256) ln_fwd_kernel(int rows, int d, float eps, const TX* __restrict__ x, T* __restrict__ y,
                                                      const T* __restrict__ gamma, const T* __restrict__ beta,
                                                      const T* __restrict__ scale, const T* __restrict__ shift, int mod_ld,
                                                      int rows_per_batch, float* __restrict__ mean, float* __restrict__ rstd,
                                                      float* __restrict__ x32_out) {
-  constexpr int V = Vec<T>::N;
-  const int lane = threadIdx.x & 63, row = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= rows) return;
-  const TX* xr = x + (size_t)row * d;
-  float v[LN_MAXCH][V];
-  float s = 0.f;
+  const int l = threadIdx.x % L, row_wanted = blockIdx.x * (256 / L) + threadIdx.x / L, row = min(row_wanted, rows - 1);
+  const bool live = row_wanted < rows;
+  const size_t at = (size_t)row * d;
+  auto column = [&](int c) { return (c * L + l) * 4; };
+  auto on = [&](int c) { return c + 1 < NC || column(c) < d; };
+  typename Vec4<TX>::type xr[NC];
 #pragma unroll
-  for (int c = 0; c < LN_MAXCH; ++c) {
-    const int col = (c * 64 + lane) * V;
-    if (col < d) {
-      if (sizeof(TX) == 4) load_f32<V>(reinterpret_cast<const float*>(xr + col), v[c]);
-      else load_vec<T>(reinterpret_cast<const T*>(xr + col), v[c]);
-      if (x32_out) store_f32<V>(x32_out + (size_t)row * d + col, v[c]);
-#pragma unroll
-      for (int i = 0; i < V; ++i) s += v[c][i];
-    }
-  }
+  for (int c = 0; c < NC; ++c)
+    if (on(c)) xr[c] = load4(x + at + column(c));
   // gain and shift are fetched right behind the row, not after the two reductions: on a few rows the kernel's
   // time is its chain of memory round trips
-  using VT = typename Vec<T>::type;
-  VT ga[LN_MAXCH], sh[LN_MAXCH];
+  typename Vec4<T>::type ga[NC], sh[NC];
   const size_t mrow = scale ? (size_t)(row / rows_per_batch) * mod_ld : 0;
   const T* gsrc = scale ? scale + mrow : gamma;
   const T* ssrc = scale ? shift + mrow : beta;
 #pragma unroll
-  for (int c = 0; c < LN_MAXCH; ++c) {
-    const int col = (c * 64 + lane) * V;
-    if (col < d && gsrc) {
-      ga[c] = *reinterpret_cast<const VT*>(gsrc + col);
-      sh[c] = *reinterpret_cast<const VT*>(ssrc + col);
-    }
+  for (int c = 0; c < NC; ++c)
+    if (on(c) && gsrc) { ga[c] = load4(gsrc + column(c)); sh[c] = load4(ssrc + column(c)); }
+  float v[NC][4], s = 0.f;
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    if (!on(c)) continue;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { v[c][i] = to_f<TX>(xr[c][i]); s += v[c][i]; }
+    if (x32_out && live) store4(x32_out + at + column(c), v[c]);
   }
-  const float mu = wave_sum(s) / d;
+  const float mu = ln_row_sum<L>(s) / d;
   float q = 0.f;
 #pragma unroll
-  for (int c = 0; c < LN_MAXCH; ++c) {
-    const int col = (c * 64 + lane) * V;
-    if (col < d) {
+  for (int c = 0; c < NC; ++c) {
+    if (!on(c)) continue;
 #pragma unroll
-      for (int i = 0; i < V; ++i) { v[c][i] -= mu; q += v[c][i] * v[c][i]; }
-    }
+    for (int i = 0; i < 4; ++i) { v[c][i] -= mu; q += v[c][i] * v[c][i]; }
   }
-  const float rs = rsqrtf(wave_sum(q) / d + eps);
-  if (lane == 0) {
+  const float rs = rsqrtf(ln_row_sum<L>(q) / d + eps);
+  if (!live) return;
+  if (l == 0) {
     if (mean) mean[row] = mu;
     if (rstd) rstd[row] = rs;
   }
 #pragma unroll
-  for (int c = 0; c < LN_MAXCH; ++c) {
-    const int col = (c * 64 + lane) * V;
-    if (col < d) {
-      float o[V];
-      if (scale) {
+  for (int c = 0; c < NC; ++c) {
+    if (!on(c)) continue;
+    float o[4];
+    if (scale) {
 #pragma unroll
-        for (int i = 0; i < V; ++i) o[i] = v[c][i] * rs * (1.0f + to_f<T>(ga[c][i])) + to_f<T>(sh[c][i]);
-      } else if (gamma) {
+      for (int i = 0; i < 4; ++i) o[i] = v[c][i] * rs * (1.0f + to_f<T>(ga[c][i])) + to_f<T>(sh[c][i]);
+    } else if (gamma) {
 #pragma unroll
-        for (int i = 0; i < V; ++i) o[i] = v[c][i] * rs * to_f<T>(ga[c][i]) + to_f<T>(sh[c][i]);
-      } else {
+      for (int i = 0; i < 4; ++i) o[i] = v[c][i] * rs * to_f<T>(ga[c][i]) + to_f<T>(sh[c][i]);
+    } else {
 #pragma unroll
-        for (int i = 0; i < V; ++i) o[i] = v[c][i] * rs;
-      }
-      store_vec<T>(y + (size_t)row * d + col, o);
+      for (int i = 0; i < 4; ++i) o[i] = v[c][i] * rs;
     }
+    store4(y + at + column(c), o);
   }
 }
 
 template <typename TX, typename T>
 static int ln_fwd_t(const LnArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL((ln_fwd_kernel<TX, T>), dim3((a.rows + 3) / 4), dim3(256), 0, s, a.rows, a.d, a.eps, (const TX*)a.x, (T*)a.y,
-                     (const T*)a.gamma, (const T*)a.beta, (const T*)a.scale, (const T*)a.shift, a.mod_ld,
-                     a.rows_per_batch > 0 ? a.rows_per_batch : a.rows, a.mean, a.rstd, a.x32_out);
+  ln_dispatch(ln_shape(a.row_invariant ? 0 : a.rows, a.d), [&](auto l, auto nc) {
+    constexpr int ROWS = 256 / l;
+    hipLaunchKernelGGL((ln_fwd_kernel<TX, T, l, nc>), dim3((a.rows + ROWS - 1) / ROWS), dim3(256), 0, s, a.rows, a.d, a.eps, (const TX*)a.x, (T*)a.y,
+                       (const T*)a.gamma, (const T*)a.beta, (const T*)a.scale, (const T*)a.shift, a.mod_ld,
+                       a.rows_per_batch > 0 ? a.rows_per_batch : a.rows, a.mean, a.rstd, a.x32_out);
+  });
   return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "ln_fwd launch failed");
 }
 
@@ -190,7 +224,7 @@ int launch_reduce_residual_ln(const float* partial, int splits, int rows, int d,
 static int check_ln_dim(int dtype, int d) {
   const int V = dtype == BF16 ? 8 : 4;
   if (d <= 0 || d % V) return set_error(DP_EUNSUPPORTED, "layernorm: d must be a positive multiple of 8 (bf16) / 4 (fp32)");
-  if (d > 64 * LN_MAXCH * V) return set_error(DP_EUNSUPPORTED, "layernorm: d too large (max 2048 bf16 / 1024 fp32)");
+  if (d > 256 * V) return set_error(DP_EUNSUPPORTED, "layernorm: d too large (max 2048 bf16 / 1024 fp32)");
   return DP_OK;
 }
 
@@ -239,39 +273,45 @@ __global__ void __launch_bounds__(256) gate_bwd_kernel(int d, int rows_per_batch
   store_f32<V>(gt.partial + ((size_t)b * gridDim.x + blockIdx.x) * 2 * d + col, hsum);
 }
 
-// grid = (chunks_per_batch, n_batches); a thread owns V columns of all rows of its workgroup (as many waves as a row has 64-lane
+// grid = (chunks_per_batch, n_batches); a thread owns four columns of all rows of its workgroup (as many waves as a row has 64-lane
 // chunks), so the column sums need no exchange; the rows' sums meet in LDS.  partial: [batch][chunk][2][d].
 // The kernel moves ~16 bytes per element and is bound by how much of that is outstanding: LNB_AT_ONCE rows are loaded before the first is used.
-// (With whole rows per wave a row of 1152 needed 242 registers; 1024 x 1152 8.8 us, 8192 x 1152 28.8 us; now 9.0 and 26 to 30 us, 32768 x 320 40.6 -> 31.6.)
+// (With whole rows per wave a row of 1152 needed 242 registers; 1024 x 1152 8.8 us, 8192 x 1152 28.8 us; now 9.0 and 26 to 30 us, 32768 x 320 40.6 -> 31.6.
+// With eight columns a thread, 80 of 128 lanes had any of 640: U-Net blocks 8 x 1024 x 640 1655 -> 1645 us, 8 x 4096 x 320 3266 -> 3255, and four rows ahead
+// are no faster.  With a row's columns inside one wave, as in the forward, a workgroup has all its rows at once and nothing behind them: 8192 x 640 19.3 -> 26.5 us.)
 //
 // GATE: the result is also the gradient of a gated branch's sum, x_next = x + gate_b * branch: dbranch = result * gate_b, and per
 // workgroup the column sums of result * branch (gate_partial, [batch][chunk][2][d], one of the two).  A kernel of its own for it reads the
 // result again: 7.9 us at 1024 x 1152, 18.9 us at 8192 x 1152, against 2.5 and 14 to 18 here.
 constexpr int LNB_AT_ONCE = 2;
 template <typename T, bool GATE>
-__global__ void __launch_bounds__(256, 2) ln_bwd_kernel(int d, int rows_per_batch, int wg_rows, const T* __restrict__ dy, const float* __restrict__ x,
+__global__ void __launch_bounds__(512, 2) ln_bwd_kernel(int d, int rows_per_batch, int wg_rows, const T* __restrict__ dy, const float* __restrict__ x,
                                                         const float* __restrict__ mean, const float* __restrict__ rstd,
                                                         const T* __restrict__ gamma, const T* __restrict__ scale, int mod_ld,
                                                         const float* __restrict__ dres, const T* __restrict__ dres_t,
                                                         T* __restrict__ dx, float* __restrict__ dx32, float* __restrict__ partial, const GateBwd gt) {
-  constexpr int V = Vec<T>::N, R = LNB_AT_ONCE;
-  using VT = typename Vec<T>::type;
-  __shared__ float red[2][4][2 * R];
+  constexpr int V = 4, R = LNB_AT_ONCE;
+  using VT = typename Vec4<T>::type;
+  __shared__ float red[2][8][2 * R];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, waves = blockDim.x >> 6, b = blockIdx.y, col = tid * V;
   const bool on = col < d;
   const int r_begin = blockIdx.x * wg_rows, r_end = min(rows_per_batch, r_begin + wg_rows);
+  auto widen = [](VT v, float (&out)[V]) {
+#pragma unroll
+    for (int i = 0; i < V; ++i) out[i] = to_f<T>(v[i]);
+  };
   float gsum[V], bsum[V], gain[V], hsum[V], gate[V];
 #pragma unroll
   for (int i = 0; i < V; ++i) { gsum[i] = 0.f; bsum[i] = 0.f; gain[i] = 1.f; hsum[i] = 0.f; gate[i] = 0.f; }
   if (on) {
     if (scale) {
-      load_vec<T>(scale + (size_t)b * mod_ld + col, gain);
+      widen(load4(scale + (size_t)b * mod_ld + col), gain);
 #pragma unroll
       for (int i = 0; i < V; ++i) gain[i] += 1.0f;
     } else if (gamma) {
-      load_vec<T>(gamma + col, gain);
+      widen(load4(gamma + col), gain);
     }
-    if constexpr (GATE) load_vec<T>((const T*)gt.gate + (size_t)b * gt.gate_ld + col, gate);
+    if constexpr (GATE) widen(load4((const T*)gt.gate + (size_t)b * gt.gate_ld + col), gate);
   }
   const float inv_d = 1.0f / d;
   int turn = 0;
@@ -340,10 +380,10 @@ __global__ void __launch_bounds__(256, 2) ln_bwd_kernel(int d, int rows_per_batc
         float ob[V];
 #pragma unroll
         for (int i = 0; i < V; ++i) { hsum[i] = fmaf(v[i], to_f<T>(br[k][i]), hsum[i]); ob[i] = v[i] * gate[i]; }
-        store_vec<T>((T*)gt.dbranch + o, ob);
+        store4((T*)gt.dbranch + o, ob);
       }
       if (dx32) store_f32<V>(dx32 + o, v);
-      if (dx) store_vec<T>(dx + o, v);
+      if (dx) store4(dx + o, v);
     }
   }
   if (!on) return;
@@ -353,35 +393,41 @@ __global__ void __launch_bounds__(256, 2) ln_bwd_kernel(int d, int rows_per_batc
 }
 
 // out_k[b * ld + col] = (acc ? old : 0) + sum_chunks partial[b][chunk][k][col], k = 0 (gain grad), 1 (shift grad).
-// grid = (ceil(2d / COLS), n_batches); COLS columns x 1024 / COLS chunk groups per workgroup; every thread sums
-// its chunks in ascending order and the group sums are added in ascending order (fixed order).  Fewer columns
-// per workgroup mean more workgroups: the unbatched reduction of a narrow model (2d = 640 columns, 1024 chunks)
-// ran on 20 workgroups with 32 columns each and took 21 us; with 8 it runs on 80.
-// blockIdx.z: one of several LayerNorms of the same shape.
-// Out: float, or the storage dtype for modulation gradients.
+// grid = (ceil(2d / COLS), n_batches); a thread sums four columns of every GROUPS-th chunk in ascending order, then the groups are added in ascending
+// order, in eight parts (fixed order).  blockIdx.z: one of several LayerNorms of the same shape.  32 samples of 32 chunks of 1152, three
+// LayerNorms: 6912 workgroups of 1024 threads that read a value each took 18.9 us, beside the main stream of a stage 140, now 12 and 27; 1024 chunks of 320 12 -> 6.
 struct LnReduceSet { const float* partial[LN_REDUCE_MAX]; void* out0[LN_REDUCE_MAX]; void* out1[LN_REDUCE_MAX]; };
-template <int COLS, typename Out>
-__global__ void __launch_bounds__(1024) ln_bwd_reduce_kernel(const LnReduceSet set, int nchunk, int d, int ld, int accumulate) {
+template <int THREADS, int COLS, typename Out>
+__global__ void __launch_bounds__(THREADS) ln_bwd_reduce_kernel(const LnReduceSet set, int nchunk, int d, int ld, int accumulate) {
   const float* __restrict__ partial = set.partial[blockIdx.z];
   Out* out0 = (Out*)set.out0[blockIdx.z];
   Out* out1 = (Out*)set.out1[blockIdx.z];
-  constexpr int GROUPS = 1024 / COLS;
-  __shared__ float red[GROUPS][COLS + 1];
-  const int lc = threadIdx.x % COLS, grp = threadIdx.x / COLS;
-  const int col = blockIdx.x * COLS + lc, b = blockIdx.y;     // col indexes the [2][d] row of a chunk
-  float s = 0.f;
+  constexpr int GROUPS = THREADS / (COLS / 4), PARTS = THREADS / COLS < 8 ? THREADS / COLS : 8, PER = GROUPS / PARTS;
+  static_assert(GROUPS % PARTS == 0 && THREADS % COLS == 0, "reduction shape");
+  __shared__ __attribute__((aligned(16))) float red[GROUPS][COLS + 4];
+  __shared__ float part[PARTS][COLS];
+  const int tid = threadIdx.x, lc = tid % (COLS / 4) * 4, grp = tid / (COLS / 4), b = blockIdx.y, col = blockIdx.x * COLS + lc;     // col indexes the [2][d] row of a chunk
+  f32x4 s = {0.f, 0.f, 0.f, 0.f};
   if (col < 2 * d) {
     const float* p = partial + (size_t)b * nchunk * 2 * d + col;
 #pragma unroll 8
-    for (int c = grp; c < nchunk; c += GROUPS) s += p[(size_t)c * 2 * d];
+    for (int c = grp; c < nchunk; c += GROUPS) s += *reinterpret_cast<const f32x4*>(p + (size_t)c * 2 * d);
   }
-  red[grp][lc] = s;
+  *reinterpret_cast<f32x4*>(&red[grp][lc]) = s;
   __syncthreads();
-  if (grp == 0 && col < 2 * d) {
+  if (tid < COLS * PARTS) {
     float t = 0.f;
-#pragma unroll 8
-    for (int g = 0; g < GROUPS; ++g) t += red[g][lc];
-    Out* o = (col < d ? out0 + col : out1 + (col - d)) + (size_t)b * ld;
+#pragma unroll
+    for (int g = 0; g < PER; ++g) t += red[tid / COLS * PER + g][tid % COLS];
+    part[tid / COLS][tid % COLS] = t;
+  }
+  __syncthreads();
+  const int oc = blockIdx.x * COLS + tid;
+  if (tid < COLS && oc < 2 * d) {
+    float t = 0.f;
+#pragma unroll
+    for (int g = 0; g < PARTS; ++g) t += part[g][tid];
+    Out* o = (oc < d ? out0 + oc : out1 + (oc - d)) + (size_t)b * ld;
     *o = from_f<Out>(accumulate ? to_f<Out>(*o) + t : t);
   }
 }
@@ -398,7 +444,7 @@ static int ln_bwd_threads(const LnBwdArgs& a) { return (a.d / (a.dtype == BF16 ?
 template <typename T>
 static int ln_bwd_t(const LnBwdArgs& a, int rpb, int nb, int nchunk, float* partial, hipStream_t s) {
   auto kern = a.gate ? ln_bwd_kernel<T, true> : ln_bwd_kernel<T, false>;
-  hipLaunchKernelGGL(kern, dim3(nchunk, nb), dim3(ln_bwd_threads(a)), 0, s, a.d, rpb, ln_bwd_rows(a.rows, a.d), (const T*)a.dy,
+  hipLaunchKernelGGL(kern, dim3(nchunk, nb), dim3((a.d / 4 + 63) / 64 * 64), 0, s, a.d, rpb, ln_bwd_rows(a.rows, a.d), (const T*)a.dy,
                      (const float*)a.x, a.mean, a.rstd, (const T*)a.gamma, (const T*)a.scale, a.mod_ld,
                      a.dres_storage ? nullptr : (const float*)a.dres, a.dres_storage ? (const T*)a.dres : nullptr, (T*)a.dx, a.dx32, partial, gate_of(a));
   return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "ln_bwd launch failed");
@@ -458,11 +504,9 @@ int launch_ln_bwd_reduce(const LnBwdArgs* a, int n, hipStream_t s) {
   const int nb = a[0].rows / rpb, wg_rows = ln_bwd_rows(a[0].rows, d), nchunk = (rpb + wg_rows - 1) / wg_rows;
   KScope ks(KK_REDUCE, 0.0, (double)n * nb * nchunk * 2 * d * 4, s, nchunk, 2 * d);
   if (modulated)
-    hipLaunchKernelGGL((a[0].dtype == BF16 ? ln_bwd_reduce_kernel<32, bf16> : ln_bwd_reduce_kernel<32, float>), dim3((2 * d + 31) / 32, nb, n), dim3(1024), 0, s, set, nchunk, d, a[0].dmod_ld, 0);
-  else if (2 * d <= 1024)
-    hipLaunchKernelGGL((ln_bwd_reduce_kernel<8, float>), dim3((2 * d + 7) / 8, 1, n), dim3(1024), 0, s, set, nchunk, d, d, a[0].accumulate);
+    hipLaunchKernelGGL((a[0].dtype == BF16 ? ln_bwd_reduce_kernel<256, 64, bf16> : ln_bwd_reduce_kernel<256, 64, float>), dim3((2 * d + 63) / 64, nb, n), dim3(256), 0, s, set, nchunk, d, a[0].dmod_ld, 0);
   else
-    hipLaunchKernelGGL((ln_bwd_reduce_kernel<16, float>), dim3((2 * d + 15) / 16, 1, n), dim3(1024), 0, s, set, nchunk, d, d, a[0].accumulate);
+    hipLaunchKernelGGL((ln_bwd_reduce_kernel<1024, 32, float>), dim3((2 * d + 31) / 32, 1, n), dim3(1024), 0, s, set, nchunk, d, d, a[0].accumulate);
   return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "ln_bwd_reduce launch failed");
 }
 

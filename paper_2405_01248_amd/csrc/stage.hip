@@ -876,7 +876,7 @@ static int encoder_block(const dp_encoder& e, const void* const* P, float* x, in
   const size_t es = e.es;
   const bool fuse_ln = dt == DP_BF16;
   LnArgs ln; memset(&ln, 0, sizeof(ln));
-  ln.dtype = dt; ln.rows = R; ln.d = d; ln.eps = e.d.ln_eps; ln.x_f32 = 1;
+  ln.dtype = dt; ln.rows = R; ln.d = d; ln.eps = e.d.ln_eps; ln.x_f32 = 1; ln.row_invariant = 1;
   ln.x = x; ln.y = w.h; ln.gamma = P[E_LN1_G]; ln.beta = P[E_LN1_B];
   if (!h_ready) DP_TRY(launch_ln_fwd(ln, st));
   const int choice_rows = e.batch_invariant == 1 ? seq : (e.batch_invariant == 2 ? -1 : 0);
@@ -960,7 +960,7 @@ static int encoder_run(const dp_encoder& e, const void* const* params, const int
     DP_TRY(mark(nl + 1));
     const void* const* P = params + 2 + (size_t)nl * E_PER_LAYER;
     LnArgs ln; memset(&ln, 0, sizeof(ln));
-    ln.dtype = dt; ln.rows = R; ln.d = d; ln.eps = e.d.ln_eps;
+    ln.dtype = dt; ln.rows = R; ln.d = d; ln.eps = e.d.ln_eps; ln.row_invariant = 1;
     ln.x = blocks ? (const void*)w.res : (const void*)x; ln.x_f32 = blocks ? 1 : 0; ln.y = x; ln.gamma = P[0]; ln.beta = P[1];
     DP_TRY(launch_ln_fwd(ln, st));
   }
