@@ -36,7 +36,7 @@ struct PpTile {
   static constexpr int OB0 = 2 * A_HALF, OB1 = OB0 + B0_BYTES;                        // stage: A0 A1 B0 B1
   // copies per wave of one half; where the pieces of a half do not divide evenly the surplus slots repeat the last piece
   static constexpr int LA = A_HALF / 1024 / NW, LB0 = (B0_BYTES / 1024 + NW - 1) / NW, LB1 = (B1_BYTES / 1024 + NW - 1) / NW;
-  static constexpr int W = SN0 + SN1, C_LD = W + 8;                                  // epilogue slab of a wave: 32 rows x W columns
+  static constexpr int W = SN0 + SN1, C_LD = W + (FR == 16 ? 4 : 8);                 // epilogue slab of a wave: 32 rows x W columns
   static constexpr size_t EPI_BYTES = (size_t)NW * 32 * C_LD * 4;
   static constexpr size_t BYTES = 2 * (size_t)STAGE > EPI_BYTES ? 2 * (size_t)STAGE : EPI_BYTES;
   typedef typename std::conditional<FR == 32, f32x16, f32x4>::type acc_t;
@@ -190,7 +190,7 @@ __device__ __forceinline__ void pp_main_loop(typename T::acc_t (&acc)[2][T::TM][
           auto& c = acc[ha][i][(h ? TN0 : 0) + j];
           if constexpr (FP8) c = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(qa[i][ks], qb[h][j][ks], c, 0, 0, 0, 127, 0, 127);
           else if constexpr (FR == 32) c = mfma32(fa[i][ks], fb[h][j][ks], c);
-          else c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i][ks], fb[h][j][ks], c, 0, 0, 0);
+          else c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[h][j][ks], fa[i][ks], c, 0, 0, 0);      // transposed: see pp_acc_to_slab
         }
     if constexpr (MC && h == 0) {
       // the bias gradient beside a weight gradient: vector work of a few workgroups under their matrix work
@@ -385,6 +385,25 @@ __device__ __forceinline__ void pp_slab_row(const float* p, float (&v)[8]) {
   *reinterpret_cast<f32x4*>(&v[4]) = *reinterpret_cast<const f32x4*>(p + 4);
 }
 
+// Rows part * RPS .. + RPS - 1 of the 32 rows i32 of a wave's row half, on their way from its accumulators to its slab.  On the 16x16x32 instruction
+// the products are formed transposed (weights as the row operand), so that a lane has one row and four neighbouring columns: one write of 16 bytes where
+// it took four of 4.  8192 x 1920, K = 640 on 256x256 tiles 25.0 -> 24.1 us, 8192 x 5120 on 256x192 73.7 -> 71.3.  A lane of the 32x32x16 one would have
+// rows of both slabs of 16, half of the lanes writing at a time: 8192 x 5120 on 256x128 75.0 -> 77.8 us, the 8-bit product of 8192 x 4608 47.5 -> 50.
+template <class T, int RPS>
+__device__ __forceinline__ void pp_acc_to_slab(float* Cw, const typename T::acc_t (&acc)[T::TM][T::TN], int i32, int part, int lane) {
+  if constexpr (T::FR == 16) {
+#pragma unroll
+    for (int i = RPS == 32 ? 0 : part; i < (RPS == 32 ? 2 : part + 1); ++i)
+#pragma unroll
+      for (int j = 0; j < T::TN; ++j) *reinterpret_cast<f32x4*>(Cw + (i * 16 + lane % 16 - part * RPS) * T::C_LD + j * 16 + 4 * (lane / 16)) = acc[2 * i32 + i][j];
+  } else {
+#pragma unroll
+    for (int j = 0; j < T::TN; ++j)
+#pragma unroll
+      for (int r = part * (RPS / 2); r < (part + 1) * (RPS / 2); ++r) Cw[(acc_row(r, lane >> 5) - part * RPS) * T::C_LD + j * 32 + lane % 32] = acc[i32][j][r];
+  }
+}
+
 // A wave turns its accumulators through LDS, 32 rows x W columns at a time, into 8 consecutive columns per lane.  Its two
 // column parts lie in different halves of the tile; the fused GeGLU forward has the values of an output in the first and
 // their gates in the second half (the B loader sees to that).  RPS: rows per slab.  ahead(): called once the operands of the first slab are requested.
@@ -425,15 +444,7 @@ __device__ __forceinline__ void pp_epilogue(const typename T::acc_t (&acc)[2][T:
 #pragma unroll
       for (int t = 0; t < 8; ++t) { bias[t] = (float)bias_it[0][t]; if constexpr (GG1) bias_g[t] = (float)bias_g_it[t]; }
     }
-#pragma unroll
-    for (int j = 0; j < T::TN; ++j)
-#pragma unroll
-      for (int i = T::FR == 32 ? 0 : part * (2 / PARTS); i < (T::FR == 32 ? 1 : (part + 1) * (2 / PARTS)); ++i)
-#pragma unroll
-        for (int r = T::FR == 32 ? part * (16 / PARTS) : 0; r < (T::FR == 32 ? (part + 1) * (16 / PARTS) : 4); ++r) {
-          const int row = (T::FR == 32 ? acc_row(r, lane >> 5) : i * 16 + 4 * (lane >> 4) + r) - part * RPS;
-          Cw[row * T::C_LD + j * T::FR + lane % T::FR] = acc[ha][i32 * (32 / T::FR) + i][j][r];
-        }
+    pp_acc_to_slab<T, RPS>(Cw, acc[ha], i32, part, lane);
     asm volatile("" ::: "memory");
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {

@@ -1356,14 +1356,14 @@ static int pp_kind(const GemmArgs& a) {
 // 8192^3 781 -> 755 and 899 -> 854 us on one card; steps of two U-Net blocks 8 x 4096 x 320, seven DiT blocks 32 x 256 x 1152 and the text encoder on 64 samples
 // 3397 -> 3360, 10073 -> 9940 and 1549 -> 1487 us there, on a card whose clock falls less 3236 -> 3230, 9672 -> 9585 and 1477 -> 1469.  Tiles of
 // 128 columns wait for their operands (8192 x 5120, K = 640: 75 us either way) and keep the larger instruction, as do calls that have to agree bit for bit with
-// other tiles (choice_rows, and the fused GeGLU forward, whose bits are those of the separate kernels): the smaller one adds up 32 products at a time.
+// other tiles (choice_rows, and the fused GeGLU forward, whose bits are those of the separate kernels): the smaller one adds up 32 products at a time.  While
+// CUs idle the clock is high and the larger one ahead: K = 1152 on 96 / 128 / 160 / 192 / 256 tiles of 256x256 27.0 / 26.6 / 29.0 / 31.5 / 36.4 us against 28.6 /
+// 28.2 / 29.1 / 30.8 / 34.7.
 template <class T, int KIND>
 static int launch_pp_kind(const GemmBf16Params& p, bool any_order, hipStream_t s) {
   if (p.K % T::BK) return launch_pp_kernel<T, KIND, false, true>(p, s);
   if constexpr (T::BN >= 192 && KIND != PE_GEGLU1) {
-    constexpr bool ORDERED = KIND == PE_PLAIN || KIND == PE_RES || KIND == PE_RESH || KIND == PE_ACT3;      // the kinds that such calls have
-    if (any_order || !ORDERED) return launch_pp_kernel<typename T::On16, KIND, false, false>(p, s);
-    if constexpr (ORDERED) return launch_pp_kernel<T, KIND, false, false>(p, s);
+    if (any_order && p.tiles_m * p.tiles_n >= 160) return launch_pp_kernel<typename T::On16, KIND, false, false>(p, s);
   }
   return launch_pp_kernel<T, KIND, false, false>(p, s);
 }
