@@ -91,6 +91,7 @@ bool gemm_geglu_fwd_supported(const GemmArgs& a);
 bool gemm_colsum_supported(const GemmArgs& a);
 size_t gemm_splitk_ws_bytes(int M, int N, int K);   // upper bound for out_f32 GEMMs
 size_t gemm_epi_splitk_ws_bytes(int M, int N, int K);   // same for storage-dtype outputs (0: such a GEMM is never split)
+bool gemm_takes_stored_weight(const GemmArgs& a);        // b_mc = 1 as good as a transposed copy (see gemm.hip)
 size_t gemm_epi_splitk_ws_bytes_for(int M, int N, int K, int choice_rows);   // with GemmArgs::choice_rows
 int gemm_epi_split_rows(int N, int K);   // no such GEMM of more rows is split
 

@@ -658,7 +658,11 @@ struct WaveTile {
   static constexpr size_t SLAB = (size_t)NW * RP * LD * 4, STAGES = (size_t)NW * ST * REGION, BYTES = STAGES > SLAB ? STAGES : SLAB;
   static_assert(BM % RP == 0 && BYTES <= 160 * 1024, "tile shape");
 };
-template <class T, int KIND>
+// B_MC: dx = dy W with the weights as they are stored, [contraction][columns]; their tile is read with the transposing LDS load.  Against
+// a transposed copy (us): 64x64 and 128x128 tiles the same, 64x96, whose rows of 192 bytes begin inside cache lines, 4 to 9 % more (1024 x 1152, K = 4608 19.5 and
+// 20.8; 1026 x 1280, K = 3840 18.2 and 20.3), less than the copy costs (4 N K bytes at 6.3 TB/s: 3.4 and 3.1): a U-Net block 2 x 513 x 1280, two micro-batches of
+// three passes 1279 -> 1256, seven DiT blocks 4 x 256 x 1152 2163 -> 2150.
+template <class T, int KIND, bool B_MC = false>
 __global__ void __launch_bounds__(T::NW * 64, T::TM * T::TN <= 6 ? 2 : 1) gemm_wave_kernel(const GemmBf16Params p) {
   constexpr int NW = T::NW, TM = T::TM, TN = T::TN, LD = T::LD, ST = T::ST, COPIES = 4 * (TM + TN);
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
@@ -675,20 +679,29 @@ __global__ void __launch_bounds__(T::NW * 64, T::TM * T::TN <= 6 ? 2 : 1) gemm_w
   }
 #pragma unroll
   for (int j = 0; j < 4 * TN; ++j) {
-    const int r = 8 * j + (lane >> 3), c = (lane & 7) ^ kc_key<64>(r);
-    vb[j] = 2u * ((uint32_t)min(n0 + r, p.N - 1) * p.ldb + c * 8);
+    if constexpr (B_MC) {
+      constexpr int CHUNKS = T::BN / 8;
+      const int o = 64 * j + lane, k = o / CHUNKS, c = pp_mc_swz<T::BN>(o % CHUNKS, k);
+      vb[j] = 2u * ((uint32_t)k * p.ldb + min(n0 + c * 8, p.N - 8));
+    } else {
+      const int r = 8 * j + (lane >> 3), c = (lane & 7) ^ kc_key<64>(r);
+      vb[j] = 2u * ((uint32_t)min(n0 + r, p.N - 1) * p.ldb + c * 8);
+    }
   }
+  uint32_t ob[TN];
+#pragma unroll
+  for (int j = 0; j < TN; ++j) ob[j] = B_MC ? pp_mc_offset<T::BN>(32 * j, lane) : 0;
   unsigned char* own = smem_raw + wave * (ST * T::REGION);
   // copies of k-tile t (past the last one: issued all the same, since the waits count them, from outside the buffers)
   auto issue = [&](int t, int stage) {
     const bool in = t < kt_end;
     const rsrc_t ra = make_rsrc(p.A, in ? p.a_bytes : 0u), rb = make_rsrc(p.B, in ? p.b_bytes : 0u);
-    const uint32_t off = in ? (uint32_t)t * 128u : 0u;
+    const uint32_t off = in ? (uint32_t)t * 128u : 0u, off_b = B_MC ? off * (uint32_t)p.ldb : off;
     unsigned char* dst = own + stage * T::REGION;
 #pragma unroll
     for (int j = 0; j < 4 * TM; ++j) async_copy_16B_buf(ra, va[j], off, dst + j * 1024);
 #pragma unroll
-    for (int j = 0; j < 4 * TN; ++j) async_copy_16B_buf(rb, vb[j], off, dst + T::A_BYTES + j * 1024);
+    for (int j = 0; j < 4 * TN; ++j) async_copy_16B_buf(rb, vb[j], off_b, dst + T::A_BYTES + j * 1024);
   };
   f32x16 acc[TM][TN];
 #pragma unroll
@@ -699,8 +712,19 @@ __global__ void __launch_bounds__(T::NW * 64, T::TM * T::TN <= 6 ? 2 : 1) gemm_w
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
   auto k_tile = [&](int t, int stage) {
     bf16x8 fa[4][TM], fb[4][TN];
+    u32x2 raw[4][TN][2];
     wait_vmcnt<(ST - 1) * COPIES>();
     const unsigned char* src = own + stage * T::REGION;
+    if constexpr (B_MC) {
+      static_for<4>([&](auto ks) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          const uint32_t at = lds_address(src) + T::A_BYTES + ob[j];
+          lds_read_tr_raw<ks * 32 * T::BN>(raw[ks][j][0], at);
+          lds_read_tr_raw<(ks * 16 + 4) * 2 * T::BN>(raw[ks][j][1], at);
+        }
+      });
+    }
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
 #pragma unroll
@@ -709,12 +733,21 @@ __global__ void __launch_bounds__(T::NW * 64, T::TM * T::TN <= 6 ? 2 : 1) gemm_w
         fa[ks][i] = *reinterpret_cast<const bf16x8*>(src + r * 128 + ((2 * ks + g) ^ kc_key<64>(r)) * 16);
       }
 #pragma unroll
-      for (int j = 0; j < TN; ++j) {
+      for (int j = 0; j < (B_MC ? 0 : TN); ++j) {
         const int r = 32 * j + l32;
         fb[ks][j] = *reinterpret_cast<const bf16x8*>(src + T::A_BYTES + r * 128 + ((2 * ks + g) ^ kc_key<64>(r)) * 16);
       }
     }
     wait_lgkmcnt0();
+    if constexpr (B_MC) {
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          lds_arrived(raw[ks][j][0]); lds_arrived(raw[ks][j][1]);
+          fb[ks][j] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(raw[ks][j][0], raw[ks][j][1], 0, 1, 2, 3));
+        }
+    }
     if (ST > 1 || t + NW < kt_end) issue(t + ST * NW, stage);
     __builtin_amdgcn_sched_barrier(0);      // (all copies before the products: they are what the next k-tile waits for)
 #pragma unroll
@@ -1440,14 +1473,27 @@ static int launch_pp(const GemmArgs& a, hipStream_t s) {
   }
 }
 
-template <class T, int KIND>
+template <class T, int KIND, bool B_MC = false>
 static int launch_wave_kind(const GemmArgs& a, GemmBf16Params& p, int splits, hipStream_t s) {
   static std::atomic<bool> attr_set{false};
-  return launch_split(a, p, gemm_wave_kernel<T, KIND>, T::NW * 64, T::BYTES, attr_set, a.K / 64, splits, s);
+  return launch_split(a, p, gemm_wave_kernel<T, KIND, B_MC>, T::NW * 64, T::BYTES, attr_set, a.K / 64, splits, s);
 }
+// The kinds of a backward pass, which the tiles above have for weights as they are stored.
+static bool wave_stored_kind(int kind) { return kind == PE_PLAIN || kind == PE_DACT1 || kind == PE_DACT2 || kind == PE_GEGLU2; }
 template <class T>
 static int launch_wave_tile(const GemmArgs& a, int splits, hipStream_t s) {
   GemmBf16Params p = pp_params<T>(a);
+  if (a.b_mc) {
+    p.b_bytes = (uint32_t)operand_extent_bytes(a.K, a.N, a.ldb);
+    if (splits > 1) return launch_wave_kind<T, PE_F32, true>(a, p, splits, s);
+    switch (pp_kind(a)) {
+      case PE_PLAIN: return launch_wave_kind<T, PE_PLAIN, true>(a, p, 1, s);
+      case PE_DACT1: return launch_wave_kind<T, PE_DACT1, true>(a, p, 1, s);
+      case PE_DACT2: return launch_wave_kind<T, PE_DACT2, true>(a, p, 1, s);
+      case PE_GEGLU2: return launch_wave_kind<T, PE_GEGLU2, true>(a, p, 1, s);
+      default: return set_error(DP_EUNSUPPORTED, "gemm: the forced configuration does not have this epilogue for weights as they are stored");
+    }
+  }
   if (splits > 1) return launch_wave_kind<T, PE_F32>(a, p, splits, s);
   switch (pp_kind(a)) {
 #define DP_WAVE_CASE(k_) case k_: return launch_wave_kind<T, k_>(a, p, 1, s)
@@ -1460,7 +1506,7 @@ static int launch_wave_tile(const GemmArgs& a, int splits, hipStream_t s) {
 // T1: the same tile with one k-tile less on its way, two workgroups of which fit a CU.
 template <class T, class T1>
 static int launch_wave(const GemmArgs& a, const WaveCost& c, hipStream_t s) {
-  if (a.a_mc || a.b_mc || a.out_f32 || a.geglu == 1 || a.K % 64 || !dtl_addressable(a)) return set_error(DP_EUNSUPPORTED, "gemm: the forced configuration needs contraction-contiguous operands, K % 64 == 0 and a storage-dtype output");
+  if (a.a_mc || a.out_f32 || a.geglu == 1 || a.K % 64 || !dtl_addressable(a)) return set_error(DP_EUNSUPPORTED, "gemm: the forced configuration needs a contraction-contiguous row operand, K % 64 == 0 and a storage-dtype output");
   int splits = 1;
   if (a.splitk_ws && a.choice_rows == 0) wave_us(c, a.M, a.N, a.K, true, a.ln_out != nullptr, &splits);
   if (splits > 1 && a.splitk_ws_bytes < (size_t)splits * a.M * a.N * sizeof(float)) splits = 1;
@@ -1547,6 +1593,20 @@ static int launch_invariant(const GemmArgs& a, bool may_split, hipStream_t s) {
   return seg64 <= seg128 ? launch_segments<64, 64, 64, 3, 2, 2>(a, z, s) : launch_segments<128, 128, 64, 3, 4, 2>(a, z, s);
 }
 
+// Whether dx = dy W is as fast on the weights as they are stored as on a transposed copy: where the copy's product would run on tiles whose waves share the
+// contraction.
+bool gemm_takes_stored_weight(const GemmArgs& a) {
+  if (a.dtype != BF16 || a.a_mc || a.out_f32 || a.choice_rows || a.K % 64 || a.N % 8 || !wave_stored_kind(pp_kind(a))) return false;
+  GemmArgs g = a;
+  g.b_mc = 0; g.ldb = a.K;
+  if (!dtl_addressable(g)) return false;
+  g.b_mc = 1; g.ldb = a.N;
+  if (!dtl_addressable(g)) return false;
+  g.b_mc = 0; g.ldb = a.K;
+  const int cfg = chosen_cfg(g, a.M, a.splitk_ws != nullptr);
+  return cfg >= 25 && cfg <= 28;
+}
+
 int launch_gemm(const GemmArgs& a, hipStream_t s) {
   if (a.ln_applied) *a.ln_applied = 0;
   if (a.M <= 0 || a.N <= 0 || a.K <= 0) return set_error(DP_EINVAL, "gemm: non-positive size");
@@ -1582,6 +1642,11 @@ int launch_gemm(const GemmArgs& a, hipStream_t s) {
     const bool forced = a.force_cfg > 0 && a.force_cfg <= kNumCfgs + 23;
     if (a.choice_rows > 0 && !forced && !a.a_mc && !a.b_mc) return launch_invariant(a, may_split, s);
     int cfg = forced ? a.force_cfg - 1 : chosen_cfg(a, a.M, may_split);
+    if (!forced && a.b_mc && a.ldb == a.N && gemm_takes_stored_weight(a)) {
+      GemmArgs g = a;
+      g.b_mc = 0; g.ldb = a.K;
+      cfg = chosen_cfg(g, a.M, may_split);
+    }
     if (a.geglu == 1 && (cfg < 6 || cfg == 11 || cfg == 15 || cfg == 16 || cfg > 18)) return set_error(DP_EUNSUPPORTED, "gemm: the forced configuration does not have the fused GeGLU forward");
     // (11 and 12 name tiles that are there under 20 and 7 as well: callers may force them)
     switch (cfg) {

@@ -418,6 +418,17 @@ struct SplitK {
   int launch(GemmArgs g, hipStream_t st) const { g.splitk_ws = ws; g.splitk_ws_bytes = bytes; return launch_gemm(g, st); }
 };
 
+// Whether the activation-gradient product of a weight matrix runs on the matrix as it is stored, which then needs no transposed copy.  The product as
+// the block's backward forms it, with its epilogue.
+static bool reads_stored_weight(const dp_stage& s, const WtEntry& e, const SplitK& sk) {
+  GemmArgs g = gemm_dx(s.d.dtype, nullptr, s.T, e.rows, nullptr, nullptr, e.cols, nullptr);
+  g.splitk_ws = sk.ws; g.splitk_ws_bytes = sk.bytes;
+  const bool unet = s.d.kind == DP_BLOCK_UNET_XATTN_GEGLU;
+  if (unet && e.param == U_W2 && (s.fuse & 2)) g.geglu = 2;
+  if (!unet && e.param == D_FC2_W) { g.dact_pre = &e; g.dact_kind = s.d.gelu_tanh ? 2 : 1; }      // (only that there is one)
+  return gemm_takes_stored_weight(g);
+}
+
 // ============================================================ U-Net stage
 // x: fp32 block input.  y: fp32 (next block's input) unless y_is_out (storage dtype, the stage output).
 // kv_side: the context K/V projection of this block was issued on the side stream as batch kv_batch
@@ -780,7 +791,9 @@ static int run_stage_bwd(dp_stage* s, const void* const* params, const void* dy,
   std::vector<const void*> wt_ptrs((size_t)nb * s->per_block, nullptr);
   if (bs.wt) {
     WtEntry we[8];
-    const int nw = wt_entries(*s, we);
+    int nw = 0;
+    for (int i = 0, n = wt_entries(*s, we); i < n; ++i)
+      if (!reads_stored_weight(*s, we[i], sk)) we[nw++] = we[i];
     TransposeBatch tb; tb.n = 0;
     size_t off = 0;
     for (int b = 0; b < nb; ++b) {
@@ -790,7 +803,7 @@ static int run_stage_bwd(dp_stage* s, const void* const* params, const void* dy,
         wt_ptrs[(size_t)b * s->per_block + we[i].param] = dst;
         off += ((size_t)we[i].rows * we[i].cols + 127) / 128 * 128;
       }
-      if (tb.n + nw > kTransposeMax || b == nb - 1) { DP_TRY(launch_transpose16_batch(tb, st)); tb.n = 0; }
+      if (tb.n && (tb.n + nw > kTransposeMax || b == nb - 1)) { DP_TRY(launch_transpose16_batch(tb, st)); tb.n = 0; }
     }
   }
   // dy as a gradient pair: the caller's tensor as GEMM operand and, in fp32 stages, as the running sum; a widened copy only

@@ -54,12 +54,13 @@ def test_stage_of_more_tiles_than_compute_units(kind):
     _compare(cfg, ds.results(), _oracle_stage(cfg, inp))
 
 
+@pytest.mark.parametrize("layout", ["nt", "nn"])
 @pytest.mark.parametrize("tile_cfg", [26, 27, 28, 29])
-def test_tiles_whose_waves_share_the_contraction(tile_cfg):
-    # fewer k-tiles than waves, as many, one more; a part of a tile and ragged edges
+def test_tiles_whose_waves_share_the_contraction(tile_cfg, layout):
+    # fewer k-tiles than waves, as many, one more; a part of a tile and ragged edges; weights [out, in] and as a product dx = dy W finds them
     for M, N, K in [(8, 8, 64), (64, 96, 256), (77, 264, 320), (129, 136, 192), (300, 520, 1088)]:
-        e = _gemm_case("nt", M, N, K, tile_cfg, seed=M + K)
-        print(f"\n[gemm nt cfg {tile_cfg} {M}x{N}x{K}] rel err {e:.2e}", flush=True)
+        e = _gemm_case(layout, M, N, K, tile_cfg, seed=M + K)
+        print(f"\n[gemm {layout} cfg {tile_cfg} {M}x{N}x{K}] rel err {e:.2e}", flush=True)
         assert e <= TOL_BF16
 
 
@@ -67,7 +68,7 @@ def test_tiles_whose_waves_share_the_contraction(tile_cfg):
 def test_waves_with_one_and_two_k_tiles_on_their_way(K):
     # up to 256 tiles of 64x64 a wave has two k-tiles on their way to LDS, beyond one: 1, 2, 3, 4, 5 k-tiles of the first wave, fewer of the others
     for M, N in [(70, 136), (1100, 1048)]:
-        e = _gemm_case("nt", M, N, K, 26, seed=M + K)
+        e = max(_gemm_case(layout, M, N, K, 26, seed=M + K) for layout in ("nt", "nn"))
         print(f"\n[gemm nt cfg 26 {M}x{N}x{K}] rel err {e:.2e}", flush=True)
         assert e <= TOL_BF16
 
