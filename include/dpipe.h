@@ -406,13 +406,13 @@ int dp_schedule_search(const dp_layer_cost* rows, int n_rows, const dp_search_op
  * storage-dtype output with few tiles and a long contraction, whose bias is then applied by the
  * reduction pass.  bf16: leading dimensions and the contiguous extents multiples of 8; fp32: any size and leading
  * dimension, fastest where K and the leading dimensions are multiples of 4.  tile_cfg = 0 picks the tile shape from
- * (M,N,K); 1..29 force one (bf16; measurement and tests only):
+ * (M,N,K); 1..32 force one (bf16; measurement and tests only):
  *    1..6   register-staged tiles, any layout
  *    7..15  direct-to-LDS tiles: K % 32 == 0 (7, 8, 9, 13, 15) or K % 64 == 0 (10, 11, 12, 14); 13 is 8, 12 is 21
  *   16, 17  64x64 and 64x128 direct-to-LDS tiles: a_kmajor = b_kmajor = 0, K % 64 == 0
  *   18..21  tiles of two alternating wave groups, 256 rows x 256, 128, 192, 160 columns: a_kmajor = b_kmajor = 0, out_is_f32 = 0
  *   22..25  the weight-gradient tiles 256x256, 256x128, 128x256, 256x192: a_kmajor = b_kmajor = 1, out_is_f32 = 1
- *   26..29  tiles whose waves share the contraction, 64x64, 64x96, 128x96, 128x128: as 18..21, K % 64 == 0
+ *   26..32  tiles whose waves share the contraction, 64x64, 64x96, 128x96, 128x128, 32x32, 32x64, 32x96: as 18..21, K % 64 == 0
  * A forced configuration that does not fit the problem returns DP_EUNSUPPORTED without launching. */
 size_t dp_op_gemm_workspace_bytes(int M, int N, int K);
 int dp_op_gemm(int dtype, const void* A, int lda, int a_kmajor, const void* B, int ldb, int b_kmajor, int M, int N, int K,

@@ -53,9 +53,9 @@ __device__ __forceinline__ int pp_piece_chunk(int row, int lane) { return (lane 
 // ---- operands with the contraction strided (dW = dy^T x): 64 k-rows of COLS columns, read with the transposing LDS load.
 // The four k-rows that 32 lanes of that load touch have to lie in four different 64-byte bank groups: chunk c of k-row k sits
 // at c ^ 4 (k & 3), in rows of only 128 bytes (which alternate between the two halves of the banks by themselves) at c ^ 4 ((k >> 1) & 1); rows of 192 bytes
-// begin in four different groups as they are.
+// begin in four different groups as they are, and rows of 64 bytes are those groups.
 template <int COLS> __device__ __forceinline__ int pp_mc_swz(int c, int k) {
-  static_assert(COLS % 64 == 0 || COLS == 96, "row length");
+  static_assert(COLS % 64 == 0 || COLS == 96 || COLS == 32, "row length");
   return COLS % 128 == 0 ? c ^ (4 * (k & 3)) : (COLS % 64 == 0 ? c ^ (4 * ((k >> 1) & 1)) : c);
 }
 template <int COLS> __device__ __forceinline__ int pp_mc_piece_k(int piece, int lane) { return piece * (512 / COLS) + lane / (COLS / 8); }

@@ -650,11 +650,16 @@ __global__ void __launch_bounds__(512, 2) gemm_pp_strided_kernel(GemmBf16Params 
 // What bounds it is fetching operands, about 20 TB/s over all CUs, so the widest tile that still gives one workgroup per CU is taken (kWave).
 // Measured (M x N, K; us, 64x64 tiles split 2x2 or 128x128 ones with split-K before): 1026 x 1280, 3840: 27 -> 19, 10240: 66 -> 40;
 // 1024 x 1152, 4608: 32 -> 20; 2048 x 1152, 4608: 37 -> 30; 924 x 768, 3072: 21 -> 12.5.
+// Outputs of few tiles leave most CUs without one, and a CU fetches about 0.1 KB per ns however many tiles there are: 32 rows with eight waves, which
+// have as much on its way to LDS in the first round trip as four of 64x64, on the widest of 32, 64, 96 columns that gives every CU at most one tile
+// (us, 64x64 tiles with four waves, split further where it paid -> 32 rows: 80 x 2304, K = 768 6.2 -> 3.9, K = 3072 and 768 columns 10.0 -> 6.6, 160 x 3072, 768
+// 6.4 -> 5.0, 312 x 768, 3072 11.9 -> 7.0, 616 x 768, 768 6.3 -> 4.9, 928 x 768, 768 6.4 -> 5.9; with 12 or 16 waves, or two k-tiles each on its way, no
+// better).  The text encoder on one sample 423 -> 337 us.
 // ST: k-tiles of a wave on their way to LDS.  RP: rows of the tile that are added up at a time.
 template <int NW_, int TM_, int TN_, int ST_ = 1>
 struct WaveTile {
   static constexpr int NW = NW_, TM = TM_, TN = TN_, ST = ST_, BM = 32 * TM, BN = 32 * TN, LD = BN + 4, A_BYTES = BM * 128, REGION = (BM + BN) * 128;
-  static constexpr int RP = TN == 3 && TM == 2 ? 32 : 64, GROUPS = RP * BN / 8, ITEMS = (GROUPS + NW * 64 - 1) / (NW * 64);      // groups of eight columns of a pass, and per thread
+  static constexpr int RP = TM == 1 || (TN == 3 && TM == 2) ? 32 : 64, GROUPS = RP * BN / 8, ITEMS = (GROUPS + NW * 64 - 1) / (NW * 64);      // groups of eight columns of a pass, and per thread
   static constexpr size_t SLAB = (size_t)NW * RP * LD * 4, STAGES = (size_t)NW * ST * REGION, BYTES = STAGES > SLAB ? STAGES : SLAB;
   static_assert(BM % RP == 0 && BYTES <= 160 * 1024, "tile shape");
 };
@@ -663,7 +668,7 @@ struct WaveTile {
 // 20.8; 1026 x 1280, K = 3840 18.2 and 20.3), less than the copy costs (4 N K bytes at 6.3 TB/s: 3.4 and 3.1): a U-Net block 2 x 513 x 1280, two micro-batches of
 // three passes 1279 -> 1256, seven DiT blocks 4 x 256 x 1152 2163 -> 2150.
 template <class T, int KIND, bool B_MC = false>
-__global__ void __launch_bounds__(T::NW * 64, T::TM * T::TN <= 6 ? 2 : 1) gemm_wave_kernel(const GemmBf16Params p) {
+__global__ void __launch_bounds__(T::NW * 64, T::TM * T::TN == 1 ? 4 : (T::TM * T::TN <= 6 ? 2 : 1)) gemm_wave_kernel(const GemmBf16Params p) {
   constexpr int NW = T::NW, TM = T::TM, TN = T::TN, LD = T::LD, ST = T::ST, COPIES = 4 * (TM + TN);
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 5, l32 = lane & 31;
@@ -962,10 +967,12 @@ static int splits_128(int rows, int N, int K, bool ln, bool heavy, float* us) {
 
 // Tiles whose waves share the contraction (gemm_wave_kernel): fixed part of a tile, which grows a little with the number of tiles, and the time
 // of a k-tile of the workgroup, a quarter of a wave's, each of which waits for memory; two: the same where a CU holds two tiles at a time.  us,
-// fitted on MI355X over 77..4928 rows, 640..10240 columns, contractions of 640..10240 (within 8 %; two_per_kt, which grows with the contraction, on the dear side).
+// fitted on MI355X over 77..4928 rows, 640..10240 columns, contractions of 640..10240 (within 8 %; two_per_kt, which grows with the contraction, on the dear side);
+// 32 rows over 80..1232 rows, 512..4096 columns, contractions of 512..4096, beyond 512 tiles, where they are never the best, on the dear side too.
 struct WaveCost { int bm, bn; float fixed, per_tile, per_kt, per_kt_tile, two_fixed, two_per_kt; };
 static const WaveCost kWave[] = {{64, 64, 3.6f, 0.005f, 0.173f, 0.f, 4.1f, 0.36f}, {64, 96, 3.7f, 0.0075f, 0.212f, 0.f, 5.6f, 0.50f},
-                                 {128, 96, 6.8f, 0.005f, 0.255f, 0.0003f, 0.f, 0.f}, {128, 128, 8.0f, 0.015f, 0.325f, 0.0002f, 0.f, 0.f}};
+                                 {128, 96, 6.8f, 0.005f, 0.255f, 0.0003f, 0.f, 0.f}, {128, 128, 8.0f, 0.015f, 0.325f, 0.0002f, 0.f, 0.f},
+                                 {32, 32, 2.6f, 0.0013f, 0.083f, 0.f, 3.1f, 0.166f}, {32, 64, 3.1f, 0.0013f, 0.1245f, 0.f, 5.0f, 0.25f}, {32, 96, 3.3f, 0.0017f, 0.171f, 0.f, 5.5f, 0.34f}};
 // Estimated time; splits: parts the contraction is cut into beyond the waves of a workgroup, where few tiles would each walk a long one.
 static float wave_us(const WaveCost& c, int rows, int N, int K, bool may_split, bool ln, int* splits) {
   const int kt = K / 64;
@@ -1083,7 +1090,7 @@ static int choose_cfg(int M, int N, int K, bool a_mc, bool b_mc, bool dtl_ok, bo
       for (int i = 0; i < (int)(sizeof(kWave) / sizeof(kWave[0])); ++i) {
         int splits;
         const float us = wave_us(kWave[i], M, N, K, may_split, ln, &splits);
-        consider(25 + i, us + (splits > 1 ? 0.f : (kWave[i].bm == 64 ? 0.8f : 0.3f) * outputs));
+        consider(25 + i, us + (splits > 1 ? 0.f : (kWave[i].bm <= 64 ? 0.8f : 0.3f) * outputs));
       }
     if (best >= 0) return best;
     return t256x128 >= 128 ? 1 : 0;
@@ -1604,7 +1611,7 @@ bool gemm_takes_stored_weight(const GemmArgs& a) {
   if (!dtl_addressable(g)) return false;
   g.b_mc = 0; g.ldb = a.K;
   const int cfg = chosen_cfg(g, a.M, a.splitk_ws != nullptr);
-  return cfg >= 25 && cfg <= 28;
+  return cfg >= 25 && cfg <= 31;
 }
 
 int launch_gemm(const GemmArgs& a, hipStream_t s) {
@@ -1639,7 +1646,7 @@ int launch_gemm(const GemmArgs& a, hipStream_t s) {
       }
     }
     const bool may_split = !a.out_f32 && a.splitk_ws && a.geglu != 1 && a.choice_rows >= 0;
-    const bool forced = a.force_cfg > 0 && a.force_cfg <= kNumCfgs + 23;
+    const bool forced = a.force_cfg > 0 && a.force_cfg <= kNumCfgs + 26;
     if (a.choice_rows > 0 && !forced && !a.a_mc && !a.b_mc) return launch_invariant(a, may_split, s);
     int cfg = forced ? a.force_cfg - 1 : chosen_cfg(a, a.M, may_split);
     if (!forced && a.b_mc && a.ldb == a.N && gemm_takes_stored_weight(a)) {
@@ -1680,6 +1687,9 @@ int launch_gemm(const GemmArgs& a, hipStream_t s) {
       case 26: return launch_wave<WaveTile<4, 2, 3>, WaveTile<4, 2, 3>>(a, kWave[1], s);
       case 27: return launch_wave<WaveTile<4, 4, 3>, WaveTile<4, 4, 3>>(a, kWave[2], s);
       case 28: return launch_wave<WaveTile<4, 4, 4>, WaveTile<4, 4, 4>>(a, kWave[3], s);
+      case 29: return launch_wave<WaveTile<8, 1, 1>, WaveTile<8, 1, 1>>(a, kWave[4], s);
+      case 30: return launch_wave<WaveTile<8, 1, 2>, WaveTile<8, 1, 2>>(a, kWave[5], s);
+      case 31: return launch_wave<WaveTile<8, 1, 3>, WaveTile<8, 1, 3>>(a, kWave[6], s);
       default: break;
     }
     return launch_bf16_layout<128, 128, 64, 2, 2>(a, s);

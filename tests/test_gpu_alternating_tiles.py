@@ -64,6 +64,16 @@ def test_tiles_whose_waves_share_the_contraction(tile_cfg, layout):
         assert e <= TOL_BF16
 
 
+@pytest.mark.parametrize("layout", ["nt", "nn"])
+@pytest.mark.parametrize("tile_cfg,width", [(30, 32), (31, 64), (32, 96)])
+def test_32_rows_with_eight_waves_that_share_the_contraction(tile_cfg, width, layout):
+    # fewer k-tiles than waves, as many, one more, two rounds; one row more and less than a tile, a ragged column edge, one CU with two tiles
+    for M, N, K in [(8, 8, 64), (32, width, 512), (33, width + 8, 576), (77, 3 * width - 8, 1024), (65, 264 * width // 2, 320), (31, 520, 1088)]:
+        e = _gemm_case(layout, M, N, K, tile_cfg, seed=M + K)
+        print(f"\n[gemm {layout} cfg {tile_cfg} {M}x{N}x{K}] rel err {e:.2e}", flush=True)
+        assert e <= TOL_BF16
+
+
 @pytest.mark.parametrize("K", [64, 256, 320, 512, 576, 832, 1088])
 def test_waves_with_one_and_two_k_tiles_on_their_way(K):
     # up to 256 tiles of 64x64 a wave has two k-tiles on their way to LDS, beyond one: 1, 2, 3, 4, 5 k-tiles of the first wave, fewer of the others
