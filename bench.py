@@ -162,7 +162,7 @@ def pmc_traffic_bytes(workload, kind):
 
 MFMA_KINDS = {"gemm_nt", "gemm_nn", "gemm_tn", "attn_fwd", "attn_bwd_dq", "attn_bwd_dkv", "conv3x3"}
 KERNEL_NAMES = {"gemm_nt": "dp::gemm_pp_kernel, dp::gemm_wave_kernel, dp::gemm_bf16_dtl_kernel by size (y = x W^T; dx = dy W on transposed weight copies)",
-                "gemm_nn": "dp::cond_grad_kernel (gradient of the conditioning vectors), dp::gemm_bf16_kernel (dx = dy W)",
+                "gemm_nn": "dp::cond_grad_kernel (gradient of the conditioning vectors), dp::gemm_wave_kernel (dx = dy W on few rows), dp::gemm_bf16_kernel",
                 "gemm_tn": "dp::gemm_dw_group_kernel (dW = dy^T x, all of a block)",
                 "attn_fwd": "dp::attn_fwd_bf16_kernel, dp::attn_fwd_short_bf16_kernel (up to 128 keys)", "attn_bwd_dq": "dp::attn_bwd_dq_bf16_kernel",
                 "attn_bwd_dkv": "dp::attn_bwd_dkv_bf16_kernel, dp::attn_bwd_short_bf16_kernel (all gradients, up to 256 keys)", "ln_fwd": "dp::ln_fwd_kernel", "ln_bwd": "dp::ln_bwd_kernel",

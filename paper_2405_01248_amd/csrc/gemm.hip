@@ -4,7 +4,7 @@
 // bf16 path: MFMA tiles fed from LDS.  An operand whose contraction index is
 // contiguous in memory is staged [rows][BK] and read with 16-byte LDS loads; an operand
 // whose contraction index is the slow one (both operands in dW, weights in dx where a stage
-// has no transposed copy of them) is staged [BK][cols] exactly as it sits in HBM and read with
+// reads them as they are stored) is staged [BK][cols] exactly as it sits in HBM and read with
 // the transposing LDS load.  Workgroup ids are remapped so that the tiles running on one XCD
 // (one L2) are neighbours in the output.
 // Elsewhere: the weight gradients of a block in one launch (gemm_dw.hip), at most 48 rows
@@ -1032,8 +1032,8 @@ int gemm_epi_split_rows(int N, int K) {
 // the five workloads on MI355X:
 //  - y = x W^T (both operands K-contiguous; also dx = dy W on transposed weight copies): the tile with the least
 //    estimated time, among alternating wave groups, waves that share the contraction and the plain direct-to-LDS ones;
-//  - dx = dy W with W as stored (fp32-free fallback when no transposed copy exists): 256x256
-//    direct-to-LDS tiles when they fill the CUs, else the register-staged kernel;
+//  - dx = dy W with W as stored: waves that share the contraction where the transposed copy's product would run on them
+//    (gemm_takes_stored_weight); else 256x256 direct-to-LDS tiles when they fill the CUs, or the register-staged kernel;
 //  - dW = dy^T x (both operands read through the transposing LDS load): register-staged 128x128 tiles,
 //    two workgroups per CU; 256x256 direct-to-LDS tiles for large M and N.
 static int choose_cfg(int M, int N, int K, bool a_mc, bool b_mc, bool dtl_ok, bool pp_ok, bool allow16 = true, bool may_split = false, bool ln = false, bool wave_ok = false, bool heavy = false, bool geglu_fwd = false, bool onto_f32 = false) {

@@ -30,10 +30,11 @@ struct DwProblem {
 };
 struct DwGroup { DwProblem p[DW_GROUP_MAX]; int n, total; };
 
-// What bounds it: the transposing LDS reads (about 75 B per clock and CU against 128 or more of the plain ones), which keep the
-// matrix pipe at two thirds with 256x256 tiles; hence the tile with the least fragment bytes per FLOP wherever the
-// outputs are large enough.  Inside a stage the operand fetches stand beside them: a launch reads 972 MB past the L2s for 302 MB of operands (a DiT block
-// 32 x 256 x 1152, 263 us, 4.1 TB/s with what it writes) or 862 for 254 (a U-Net block 8 x 1024 x 640, 156 us, 5.7 TB/s); which of the two binds is not separated.
+// What bounds it: fetching operands.  A CU takes 152 B per ns from the L2, 85 past it and 51 from memory, however many k-tiles are on their way and whatever
+// the rows' stride, and a k-tile of 256x128 is 48 KB beside 0.53 us of matrix work; the transposing LDS reads (208 B per clock and CU, the plain ones 250)
+// come to half of that.  Hence the tile with the least operand bytes per FLOP wherever the outputs are large enough.  A launch reads 972 MB past the L2s
+// for 302 MB of operands (a DiT block 32 x 256 x 1152, 263 us, 4.1 TB/s with what it writes) or 862 for 254 (a U-Net block 8 x 1024 x 640, 156 us, 5.7 TB/s).
+// Tiles dealt to the XCDs nearer to square, or their k-tiles taken in turned order inside windows of 2, 4 or 8, gave within 0.5 % either way.
 template <class T>
 __global__ void __launch_bounds__(512, 2) gemm_dw_group_kernel(const DwGroup grp) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];

@@ -166,7 +166,7 @@ static size_t partial_need(const dp_stage& s) {
   return n;
 }
 
-// Weight matrices whose activation-gradient GEMM (dx = dy W) reads a transposed copy: for each, the
+// Weight matrices whose activation-gradient GEMM (dx = dy W) reads a transposed copy unless reads_stored_weight() says otherwise: for each, the
 // index in the block's parameter list and its shape [out features, in features].
 struct WtEntry { int param, rows, cols; };
 static int wt_entries(const dp_stage& s, WtEntry* e) {
@@ -294,8 +294,8 @@ static GemmArgs gemm_fwd(int dtype, const void* x, int M, int K, const void* W, 
   g.A = x; g.B = W; g.M = M; g.N = N; g.K = K; g.lda = K; g.ldb = K; g.out = y; g.ldo = N; g.bias = bias;
   return g;
 }
-// dx[M,K] = dy[M,N] W[N,K]; when a transposed copy Wt[K,N] exists the product runs on it, with both
-// operands contraction-contiguous (no transposing LDS reads, which are the slow ones)
+// dx[M,K] = dy[M,N] W[N,K]; when a transposed copy Wt[K,N] exists the product runs on it, with both operands contraction-contiguous, which the
+// tiles of 256 rows need
 static GemmArgs gemm_dx(int dtype, const void* dy, int M, int N, const void* W, const void* Wt, int K, void* dx) {
   GemmArgs g = gemm_base(dtype);
   g.A = dy; g.M = M; g.N = K; g.K = N; g.lda = N; g.out = dx; g.ldo = K;
