@@ -326,10 +326,10 @@ gemm_bf16_dtl_kernel(const GemmBf16Params p) {
   }
   const uint32_t a_step = 2u * (A_MC ? (uint32_t)BK * p.lda : BK), b_step = 2u * (B_MC ? (uint32_t)BK * p.ldb : BK);
 
-  // Copies of k-tile t_ whose index j (A pieces first, then B) satisfies j % parts_ == part_.
-#define DP_DTL_ISSUE_PART(t_, part_, parts_)                                                                          \
+  // Copies of k-tile t_, to buffer buf_, whose index j (A pieces first, then B) satisfies j % parts_ == part_.
+#define DP_DTL_ISSUE_PART(t_, buf_, part_, parts_)                                                                    \
   {                                                                                                                   \
-    unsigned char* st_ = smem_raw + ((t_) % STAGES) * S::STAGE;                                                       \
+    unsigned char* st_ = smem_raw + (buf_) * S::STAGE;                                                                \
     _Pragma("unroll") for (int j = 0; j < A_LOADS; ++j)                                                               \
       if (j % (parts_) == (part_))                                                                                    \
         async_copy_16B_buf(ra, va[j], (uint32_t)(t_) * a_step, st_ + (wave * A_LOADS + j) * 1024);                    \
@@ -337,7 +337,6 @@ gemm_bf16_dtl_kernel(const GemmBf16Params p) {
       if ((A_LOADS + j) % (parts_) == (part_))                                                                        \
         async_copy_16B_buf(rb, vb[j], (uint32_t)(t_) * b_step, st_ + S::A_BYTES + (wave * B_LOADS + j) * 1024);       \
   }
-#define DP_DTL_ISSUE(t_) DP_DTL_ISSUE_PART(t_, 0, 1)
 
   // What the epilogue reads beside the sums: a lane has the same eight columns of every (512 / WN)-th row
   constexpr int EPI = KIND < 0 ? PE_PLAIN : KIND, CH = WN / 8, NIT = 32 * CH / 64;
@@ -417,14 +416,11 @@ gemm_bf16_dtl_kernel(const GemmBf16Params p) {
   // texture addresser together while the MFMA pipes drain) but spread over the k-steps of
   // k-tile t + 1, a few per MFMA group; they still run STAGES - 2 k-tiles ahead of their use.
   constexpr int PART_LAST = LOADS / KS;   // number of copies with index % KS == KS - 1
-  static_assert(STAGES >= 3 && STAGES <= 4 && 3 * LOADS < 64, "pipeline shape");
-  for (int t = 0; t < STAGES && t < nk; ++t) DP_DTL_ISSUE(t);
+  static_assert(STAGES >= 3 && (STAGES - 1) * LOADS < 64, "pipeline shape");
+  for (int t = 0; t < STAGES && t < nk; ++t) DP_DTL_ISSUE_PART(t, t, 0, 1);
   {
     const int y = min(nk, STAGES) - 1;
-    if (y >= 3) wait_vmcnt<3 * LOADS>();
-    else if (y == 2) wait_vmcnt<2 * LOADS>();
-    else if (y == 1) wait_vmcnt<LOADS>();
-    else wait_vmcnt<0>();
+    static_for<STAGES>([&](auto n) { if (y == n) wait_vmcnt<n * LOADS>(); });
   }
   barrier_nofence();
   DP_DTL_FRAGS(0, 0, 0);
@@ -445,8 +441,12 @@ gemm_bf16_dtl_kernel(const GemmBf16Params p) {
         }
     ++segments; seg_left = p.k_tiles_per_split;
   };
+  // buffers of k-tile t and its neighbours; the remainder by 3 is counted, which is 1 to 5 % faster, that by 4 is not, which is 1 to 7 % faster
+  constexpr bool POW2 = (STAGES & (STAGES - 1)) == 0;
+  int st = 0;
   for (int t = 0; t + 1 < nk; ++t) {
-    const int st = t % STAGES;
+    if (POW2) st = t % STAGES;
+    const int next = POW2 ? (t + 1) % STAGES : (st + 1 == STAGES ? 0 : st + 1), prev = POW2 ? (t - 1 + STAGES) % STAGES : (st == 0 ? STAGES - 1 : st - 1);
     const bool refill = t >= 1 && t - 1 + STAGES < nk;   // k-tile t - 1 + STAGES goes into the buffer k-tile t - 1 left
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
@@ -457,12 +457,10 @@ gemm_bf16_dtl_kernel(const GemmBf16Params p) {
         // copies younger than k-tile t + 1 that may stay in flight: whole k-tiles t + 2 .. t - 2 + STAGES
         // and the parts of k-tile t - 1 + STAGES issued so far (never more than are really there)
         const int avail = nk - 2 - t;
-        if (STAGES == 4 && avail >= 2) wait_vmcnt<2 * LOADS - PART_LAST>();
-        else if (STAGES == 4 && avail == 1) wait_vmcnt<LOADS>();
-        else if (STAGES == 3 && avail >= 1) wait_vmcnt<LOADS - PART_LAST>();
-        else wait_vmcnt<0>();
+        if (avail >= STAGES - 2) wait_vmcnt<(STAGES - 2) * LOADS - PART_LAST>();
+        else static_for<STAGES - 2>([&](auto n) { if (avail == n) wait_vmcnt<n * LOADS>(); });
         barrier_nofence();
-        DP_DTL_FRAGS((t + 1) % STAGES, 0, 0);
+        DP_DTL_FRAGS(next, 0, 0);
       }
       if (INTERLEAVE && ks + 1 < KS) {
         // 64-deep k-tiles: the scheduler may place one fragment read behind each MFMA instead of issuing the whole
@@ -476,13 +474,14 @@ gemm_bf16_dtl_kernel(const GemmBf16Params p) {
       }
       DP_DTL_MFMAS(ks & 1);
       __builtin_amdgcn_sched_barrier(0);
-      if (refill) DP_DTL_ISSUE_PART(t - 1 + STAGES, ks, KS);
+      if (refill) DP_DTL_ISSUE_PART(t - 1 + STAGES, prev, ks, KS);
       __builtin_amdgcn_sched_barrier(0);
     }
     if (SEG && --seg_left == 0) close_segment();
+    st = next;
   }
+  if (POW2) st = (nk - 1) % STAGES;
   {
-    const int st = (nk - 1) % STAGES;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
       if (ks + 1 < KS) DP_DTL_FRAGS(st, ks + 1, (ks + 1) & 1);
@@ -493,7 +492,6 @@ gemm_bf16_dtl_kernel(const GemmBf16Params p) {
   }
 #undef DP_DTL_FRAGS
 #undef DP_DTL_MFMAS
-#undef DP_DTL_ISSUE
 #undef DP_DTL_ISSUE_PART
   if (SEG) {
     close_segment();
@@ -1231,23 +1229,26 @@ static int dtl_params(const GemmArgs& a, GemmBf16Params& p) {
   return DP_OK;
 }
 
+// Parts that the contraction is cut into on BM x BN tiles, `slots` of which the chip holds.
+template <int BM, int BN, int BK>
+static int dtl_splits(const GemmArgs& a, int slots) {
+  const long tiles_n = (a.N + BN - 1) / BN;
+  const int kt = a.K / BK;
+  if (a.out_f32) return choose_splits((a.M + BM - 1) / BM * tiles_n, kt * BK / 64, slots);
+  if (!a.splitk_ws || a.geglu == 1 || a.choice_rows < 0) return 1;
+  const long rows = a.choice_rows > 0 ? a.choice_rows : a.M;
+  float us;
+  const int splits = BM == 128 && BN == 128 && BK == 64 ? splits_128((int)rows, a.N, a.K, a.ln_out != nullptr, heavy_epilogue(a), &us) : choose_splits_epi((rows + BM - 1) / BM * tiles_n, kt * BK / 64);
+  return a.choice_rows > 0 || a.splitk_ws_bytes >= (size_t)splits * a.M * a.N * sizeof(float) ? splits : 1;
+}
+
 template <int BM, int BN, int BK, int STAGES, int WGM, int WGN, bool A_MC, bool B_MC>
 static int launch_dtl_cfg(const GemmArgs& a, hipStream_t s) {
   using S = DtlSmem<BM, BN, BK, STAGES, WGM, WGN>;
   GemmBf16Params p;
   DP_TRY((dtl_params<BM, BN, A_MC, B_MC>(a, p)));
-  const int kt = a.K / BK;
-  int splits = 1;
-  if (a.out_f32) {
-    splits = choose_splits((long)p.tiles_m * p.tiles_n, kt * BK / 64, S::BYTES <= 80 * 1024 ? 2 * kCUs : kCUs);
-  } else if (a.splitk_ws && a.geglu != 1) {
-    const long rows_for_choice = a.choice_rows > 0 ? a.choice_rows : a.M;
-    float us;
-    splits = a.choice_rows < 0 ? 1 : choose_splits_epi(((rows_for_choice + BM - 1) / BM) * p.tiles_n, kt * BK / 64);
-    if (a.choice_rows >= 0 && BM == 128 && BN == 128 && BK == 64) splits = splits_128((int)rows_for_choice, a.N, a.K, a.ln_out != nullptr, heavy_epilogue(a), &us);
-  }
-  if constexpr (!A_MC && !B_MC && BK == 64 && STAGES == 3 && ((BM == 64 && BN == 64) || (BM == 128 && BN == 128 && WGM == 4))) {
-    if (splits > 1 && a.splitk_ws_bytes < (size_t)splits * a.M * a.N * sizeof(float) && a.choice_rows <= 0) splits = 1;
+  const int kt = a.K / BK, splits = dtl_splits<BM, BN, BK>(a, S::BYTES <= 80 * 1024 ? 2 * kCUs : kCUs);
+  if constexpr (!A_MC && !B_MC && BK == 64 && ((BM == 64 && BN == 64) || (BM == 128 && BN == 128 && WGM == 4))) {
     const int kind = a.out_f32 || splits > 1 ? PE_F32 : pp_kind(a);
     switch (kind) {
 #define DP_DTL_CASE(k_) case k_: { \
@@ -1597,7 +1598,8 @@ static int launch_invariant(const GemmArgs& a, bool may_split, hipStream_t s) {
     g.force_cfg = cfg + 1;
     return launch_gemm(g, s);
   }
-  return seg64 <= seg128 ? launch_segments<64, 64, 64, 3, 2, 2>(a, z, s) : launch_segments<128, 128, 64, 3, 4, 2>(a, z, s);
+  if (seg64 <= seg128) return t64 <= 2 * kCUs ? launch_segments<64, 64, 64, 4, 2, 2>(a, z, s) : launch_segments<64, 64, 64, 3, 2, 2>(a, z, s);
+  return launch_segments<128, 128, 64, 4, 4, 2>(a, z, s);
 }
 
 // Whether dx = dy W is as fast on the weights as they are stored as on a transposed copy: where the copy's product would run on tiles whose waves share the
@@ -1667,14 +1669,20 @@ int launch_gemm(const GemmArgs& a, hipStream_t s) {
       case 8: return launch_dtl_layout<128, 128, 32, 4, 2, 2>(a, s);
       case 9: return launch_dtl_layout<256, 128, 64, 3, 4, 2>(a, s);
       case 10: return launch_dtl_layout<128, 128, 64, 3, 2, 2>(a, s);
-      case 13: return launch_dtl_layout<128, 128, 64, 3, 4, 2>(a, s);   // eight waves on a 128x128 tile
+      case 13: return launch_dtl_layout<128, 128, 64, 4, 4, 2>(a, s);   // eight waves on a 128x128 tile; three buffers instead of four, one workgroup a CU either way: 4 to 8 % more
       case 14: return launch_dtl_layout<128, 128, 32, 4, 4, 2>(a, s);
       // small tiles: many workgroups for problems of a few hundred rows (contraction-contiguous operands only: the chunk
       // permutation of a contraction-strided tile needs at least 128 columns)
+      // Four buffers beside three of 64x64 are a k-tile more on its way, but two workgroups a CU instead of three (us, contraction 768 / 3072, 72 to 348
+      // tiles: 7.0 -> 6.2 / 20.1 -> 16.2, 22.9 -> 20.4; 540 tiles 9.3 -> 11.8).
       case 15:
       case 16:
         if (a.a_mc || a.b_mc || a.K % 64) return set_error(DP_EUNSUPPORTED, "gemm: the forced 64-row configurations need contraction-contiguous operands and K % 64 == 0");
-        return cfg == 15 ? launch_dtl_cfg<64, 64, 64, 3, 2, 2, false, false>(a, s) : launch_dtl_cfg<64, 128, 64, 3, 2, 2, false, false>(a, s);
+        if (cfg == 15) {
+          const long tiles = (long)((a.M + 63) / 64) * ((a.N + 63) / 64) * dtl_splits<64, 64, 64>(a, 2 * kCUs);
+          return tiles <= 2 * kCUs ? launch_dtl_cfg<64, 64, 64, 4, 2, 2, false, false>(a, s) : launch_dtl_cfg<64, 64, 64, 3, 2, 2, false, false>(a, s);
+        }
+        return launch_dtl_cfg<64, 128, 64, 3, 2, 2, false, false>(a, s);
       case 17: return launch_pp<PpTile<256, 128, 128, 4, 2>>(a, s);
       case 18: return launch_pp<PpTile<256, 64, 64, 4, 2>>(a, s);
       case 19: return launch_pp<PpTile<256, 128, 64, 4, 2>>(a, s);
