@@ -1173,9 +1173,12 @@ int launch_attn_fwd(const AttnArgs& a, hipStream_t s) {
         else launch(integral_constant<int, 4>());
         return;
       }
-      // The causal mask costs the kernel of four waves per SIMD two spilled registers (width 64, with four -> three: 768 heads of 256 tokens
-      // 28.7 -> 26.7 us, 384 of 512 38.1 -> 37.0, 192 of 1024 56.5 -> 54.9)
-      if (a.causal) hipLaunchKernelGGL((attn_fwd_bf16_kernel<dhp, kc, true, 3>), grid, dim3(256), 0, s, k);
+      // The causal mask costs the kernel of four waves per SIMD two spilled registers at widths above 48: it is for the launches that a CU holds with
+      // four workgroups and not with three, which would start in two rounds (three -> four: 400 heads of 256 tokens 20.1 -> 17.6 us, 512 20.3 -> 19.0, 200
+      // of 512 27.9 -> 23.2, 256 28.4 -> 24.6, 128 of 1024 37.9 -> 37.0; on either side 384 of 256 15.2 and 15.3, 520 21.8 -> 24.2, 600 22.8 -> 25.3)
+      constexpr bool FOUR = dhp == 64 && kc == 4;
+      if (FOUR && a.causal && grid.x > 3 * 256 && grid.x <= 4 * 256) hipLaunchKernelGGL((attn_fwd_bf16_kernel<dhp, kc, true, FOUR ? 4 : 3>), grid, dim3(256), 0, s, k);
+      else if (a.causal) hipLaunchKernelGGL((attn_fwd_bf16_kernel<dhp, kc, true, 3>), grid, dim3(256), 0, s, k);
       else hipLaunchKernelGGL((attn_fwd_bf16_kernel<dhp, kc, false, dhp == 64 ? 4 : 3>), grid, dim3(256), 0, s, k);
     });
   } else {

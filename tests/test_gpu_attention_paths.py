@@ -102,23 +102,40 @@ def test_late_moves_of_the_softmax_reference(case):
     assert max(errs.values()) <= TOL_BF16, errs
 
 
+def _heads_of_one_batch(heads, tokens, causal, dh=64, keys=None):
+    """The first head's rows of a launch with all heads and of one with that head alone, on the same operands."""
+    import torch
+    from paper_2405_01248_amd import binding as B
+    d, keys = heads * dh, keys or tokens
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    q, k, v = (torch.randn((n, d), generator=gen, device="cuda").to(torch.bfloat16) for n in (tokens, keys, keys))
+    outs = []
+    for h in (heads, 1):
+        o = torch.zeros((tokens, d), dtype=torch.bfloat16, device="cuda")
+        lse = torch.zeros((h, tokens), dtype=torch.float32, device="cuda")
+        B.op_attention_fwd(B.DP_BF16, 1, h, tokens, keys, dh, causal, dh ** -0.5, q, d, k, d, v, d, o, d, lse)
+        torch.cuda.synchronize()
+        outs.append((o[:, :dh].clone(), lse[0].clone()))
+    return outs
+
+
 @pytest.mark.parametrize("heads,tokens", [(72, 512), (264, 128)])
 def test_waves_that_take_turns_give_the_same_bits(heads, tokens):
     """More workgroups than CUs, all resident: wave priorities rotate.  They change the order in time and nothing else: the first head alone (few workgroups, no
     turns) has the same bits."""
     import torch
-    from paper_2405_01248_amd import binding as B
-    dh, d = 64, heads * 64
-    gen = torch.Generator(device="cuda").manual_seed(3)
-    q, k, v = (torch.randn((tokens, d), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(3))
-    outs = []
-    for h in (heads, 1):
-        o = torch.zeros((tokens, d), dtype=torch.bfloat16, device="cuda")
-        lse = torch.zeros((h, tokens), dtype=torch.float32, device="cuda")
-        B.op_attention_fwd(B.DP_BF16, 1, h, tokens, tokens, dh, False, dh ** -0.5, q, d, k, d, v, d, o, d, lse)
-        torch.cuda.synchronize()
-        outs.append(o[:, :dh].clone())
-    assert torch.equal(outs[0], outs[1])
+    (o, _), (alone, _) = _heads_of_one_batch(heads, tokens, False)
+    assert torch.equal(o, alone)
+
+
+@pytest.mark.parametrize("dh", [40, 56, 64, 72])
+@pytest.mark.parametrize("heads", [384, 385, 512, 513])
+def test_causal_workgroups_that_a_cu_holds_three_and_four_of(heads, dh):
+    """768 workgroups of 128 queries are three a CU, 1024 four, which another instance of the kernel takes at widths above 48: the first head alone has the
+    same bits."""
+    import torch
+    (o, lse), (alone, lse_alone) = _heads_of_one_batch(heads, 256, True, dh)
+    assert torch.equal(o, alone) and torch.equal(lse, lse_alone)
 
 
 @pytest.mark.parametrize("B,H,Nq,Nk,dh", [(1, 1, 1, 1, 1), (2, 4, 64, 64, 16), (1, 3, 65, 63, 7), (1, 2, 256, 256, 24), (1, 2, 257, 256, 24), (1, 1, 5, 512, 33), (1, 1, 5, 513, 33), (2, 1, 130, 9, 200)])
