@@ -164,7 +164,7 @@ MFMA_KINDS = {"gemm_nt", "gemm_nn", "gemm_tn", "attn_fwd", "attn_bwd_dq", "attn_
 KERNEL_NAMES = {"gemm_nt": "dp::gemm_pp_kernel, dp::gemm_wave_kernel, dp::gemm_bf16_dtl_kernel by size (y = x W^T; dx = dy W on transposed weight copies)",
                 "gemm_nn": "dp::cond_grad_kernel (gradient of the conditioning vectors), dp::gemm_wave_kernel (dx = dy W on few rows), dp::gemm_bf16_kernel",
                 "gemm_tn": "dp::gemm_dw_group_kernel (dW = dy^T x, all of a block)",
-                "attn_fwd": "dp::attn_fwd_bf16_kernel, dp::attn_fwd_short_bf16_kernel (up to 128 keys)", "attn_bwd_dq": "dp::attn_bwd_dq_bf16_kernel",
+                "attn_fwd": "dp::attn_fwd_bf16_kernel, dp::attn_fwd_short_bf16_kernel (few keys)", "attn_bwd_dq": "dp::attn_bwd_dq_bf16_kernel",
                 "attn_bwd_dkv": "dp::attn_bwd_dkv_bf16_kernel, dp::attn_bwd_short_bf16_kernel (all gradients, up to 256 keys)", "ln_fwd": "dp::ln_fwd_kernel", "ln_bwd": "dp::ln_bwd_kernel",
                 "geglu_fwd": "dp::geglu_fwd_kernel", "geglu_bwd": "dp::geglu_bwd_kernel",
                 "reduce": "dp::gemm_dw_reduce_kernel, dp::ln_bwd_reduce_kernel, dp::attn_dkv_reduce_kernel, dp::reduce_epilogue_kernel, dp::reduce_residual_ln_kernel",

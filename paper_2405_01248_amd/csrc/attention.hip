@@ -5,7 +5,7 @@
 // (dK/dV) and keeps them in registers as the MFMA B operand; the other side streams
 // through LDS in 64-row tiles.  Scores are produced transposed (S^T = K Q^T) so that a
 // lane holds one query column: the softmax statistics are lane-local (online over the tiles; over
-// all keys at once in the forward of up to 128 keys, which has them all in LDS), and the
+// all keys at once in the forward of few keys, which has them all in LDS), and the
 // probability block, once rounded to bf16, already has the register layout of the B
 // operand of the second product (O^T = V^T P^T).  The operand that needs its
 // contraction index moved (V, and K/Q/dO in the backward) is read from its row-major
@@ -1150,6 +1150,16 @@ template <class F> static void attn_dispatch(int d_head, F f) {
   else f(integral_constant<int, 96>(), integral_constant<int, 6>());
 }
 
+// Whether the forward has all keys in LDS at once.  Beyond 120 keys a fourth block of 32 is full or nearly so, and its workgroups begin when all of it
+// is there, where the loop fetches the second tile beside its work on the first: many heads of one tile of queries, which are bound by memory, are faster in the loop (128 keys
+// and queries, 512 / 768 / 1024 heads, loop and all at once, us: width 40 9.4 / 13.2 / 17.1 and 9.8 / 14.3 / 18.0, 72 12.9 / 17.8 / 22.6 and 13.8 / 19.0 / 23.7, 96 14.1 / 19.3 /
+// 24.6 and 15.1 / 20.8 / 25.9; 384 heads 8.1 / 10.7 / 11.7 and 8.1 / 10.4 / 11.1; width 64 7.7 / 12.4 / 16.0 and 7.6 / 12.9 / 16.2, 2048 heads 28.1 and 27.0; 113 keys, 768 heads of
+// width 72 16.6 and 17.3, 1536 29.8 and 29.0; causal 512 of 96 1.04x, 1024 0.99x).
+static bool attn_all_keys(const AttnArgs& a, long blocks) {
+  if (a.Nk <= 120) return true;
+  return a.Nk <= 128 && (a.causal || a.Nq > 128 || blocks < 512 || (a.d_head > 48 && a.d_head <= 64));
+}
+
 int launch_attn_fwd(const AttnArgs& a, hipStream_t s) {
   if (int e = check_attn(a, false)) return e;
   AttnK k = make_k(a);
@@ -1160,7 +1170,7 @@ int launch_attn_fwd(const AttnArgs& a, hipStream_t s) {
   if (a.dtype == BF16) {
     dim3 grid(((a.Nq + 127) / 128) * a.B * a.H);
     attn_dispatch(a.d_head, [&](auto dhp, auto kc) {
-      if (a.Nk <= 128) {
+      if (attn_all_keys(a, grid.x)) {
         auto launch = [&](auto nb) {
           constexpr int W = dhp == 64 && nb < 4 ? 4 : 3;
           if (a.causal) hipLaunchKernelGGL((attn_fwd_short_bf16_kernel<dhp, kc, nb, true, W>), grid, dim3(256), 0, s, k);

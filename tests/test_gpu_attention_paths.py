@@ -138,6 +138,16 @@ def test_causal_workgroups_that_a_cu_holds_three_and_four_of(heads, dh):
     assert torch.equal(o, alone) and torch.equal(lse, lse_alone)
 
 
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("dh", [40, 64, 72, 96])
+@pytest.mark.parametrize("heads,tokens,keys", [(511, 128, 128), (512, 128, 128), (512, 97, 121), (512, 113, 120), (256, 129, 125)])
+def test_forward_of_many_heads_in_the_loop_and_with_all_keys_at_once(heads, tokens, keys, dh, causal):
+    """From 512 workgroups of one tile of queries on the loop takes 121 to 128 keys, below that and for one head alone they lie in LDS at once: the same bits."""
+    import torch
+    (o, lse), (alone, lse_alone) = _heads_of_one_batch(heads, tokens, causal, dh, keys)
+    assert torch.equal(o, alone) and torch.equal(lse, lse_alone)
+
+
 @pytest.mark.parametrize("B,H,Nq,Nk,dh", [(1, 1, 1, 1, 1), (2, 4, 64, 64, 16), (1, 3, 65, 63, 7), (1, 2, 256, 256, 24), (1, 2, 257, 256, 24), (1, 1, 5, 512, 33), (1, 1, 5, 513, 33), (2, 1, 130, 9, 200)])
 def test_f32_backward_in_one_launch_and_in_two(B, H, Nq, Nk, dh):
     # one launch up to 512 keys over batch and heads and 256 queries, two beyond; widths that are no multiple of four, rows wider than the heads
