@@ -1398,13 +1398,26 @@ static int pp_kind(const GemmArgs& a) {
 // 3397 -> 3360, 10073 -> 9940 and 1549 -> 1487 us there, on a card whose clock falls less 3236 -> 3230, 9672 -> 9585 and 1477 -> 1469.  Tiles of
 // 128 columns wait for their operands (8192 x 5120, K = 640: 75 us either way) and keep the larger instruction, as do calls that have to agree bit for bit with
 // other tiles (choice_rows, and the fused GeGLU forward, whose bits are those of the separate kernels): the smaller one adds up 32 products at a time.  While
-// CUs idle the clock is high and the larger one ahead: K = 1152 on 96 / 128 / 160 / 192 / 256 tiles of 256x256 27.0 / 26.6 / 29.0 / 31.5 / 36.4 us against 28.6 /
-// 28.2 / 29.1 / 30.8 / 34.7.
+// CUs idle the clock is high and the larger one ahead, on 256x256 tiles the more so the longer they walk (PP_IDLE_KT; us, 32x32x16 and 16x16x32, by tiles and contraction;
+// 96 and 128 tiles of K = 1152 27.0 and 28.6, 26.6 and 28.2):
+//   K =  640: 160 tiles 19.7 and 20.1, 192 21.9 and 21.5, 256 25.2 and 24.7, 288 37.5 and 37.9, 384 40.6 and 40.6, 512 51.2 and 46.8
+//   K = 1152: 160 28.6 and 29.5, 192 30.3 and 30.7, 224 33.5 and 33.2, 256 37.1 and 35.9, 288 55.8 and 56.9, 384 60.4 and 60.2, 512 72.8 and 68.5
+//   K = 2304: 160 47.6 and 49.6, 208 54.5 and 57.4, 240 59.5 and 59.2, 256 63.1 and 61.0, 264 98.3 and 100.4, 480 117.3 and 117.0
+//   K = 4608: 160 89.4 and 96.1, 192 94.9 and 102.8, 240 109.4 and 111.0, 256 115.4 and 112.6, 288 185 and 188, 448 209 and 211
+// On 256x192 tiles the smaller one is ahead from 160 on, whatever the contraction (64 to 4608) and the last round: 160 tiles of K = 320 / 1152 / 4608 12.8 -> 12.5, 23.2 -> 22.6,
+// 67.8 -> 67.7, 224 12.7 -> 12.4, 25.5 -> 24.4, 82.4 -> 76.9, 264 21.0 -> 20.4, 44.7 -> 43.4, 149 -> 144, 512 22.2 -> 21.5, 52.6 -> 50.5, 178 -> 173.
+constexpr int PP_IDLE_KT = 3;
+template <class T>
+static bool pp_on_16(long tiles, int K) {
+  if (T::BN < 192 || tiles < 160) return false;
+  const long slots = (tiles + kCUs - 1) / kCUs * kCUs;
+  return T::BN == 192 || (slots - tiles) * (K / 64) <= PP_IDLE_KT * slots;      // k-tiles that a CU idles through in a round, on average
+}
 template <class T, int KIND>
 static int launch_pp_kind(const GemmBf16Params& p, bool any_order, hipStream_t s) {
   if (p.K % T::BK) return launch_pp_kernel<T, KIND, false, true>(p, s);
   if constexpr (T::BN >= 192 && KIND != PE_GEGLU1) {
-    if (any_order && p.tiles_m * p.tiles_n >= 160) return launch_pp_kernel<typename T::On16, KIND, false, false>(p, s);
+    if (any_order && pp_on_16<T>((long)p.tiles_m * p.tiles_n, p.K)) return launch_pp_kernel<typename T::On16, KIND, false, false>(p, s);
   }
   return launch_pp_kernel<T, KIND, false, false>(p, s);
 }

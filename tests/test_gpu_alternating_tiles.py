@@ -28,10 +28,11 @@ def test_workgroups_that_walk_over_tiles(tile_cfg, width, K):
         assert e <= TOL_BF16
 
 
-@pytest.mark.parametrize("K", [64, 320])
+@pytest.mark.parametrize("K", [64, 320, 1088])
 @pytest.mark.parametrize("tile_cfg,width", [(18, 256), (20, 192)])
 def test_one_round_of_tiles_on_either_instruction(tile_cfg, width, K):
-    # from 160 tiles on the 16x16x32 instruction, transposed on its way to the epilogue; below it the 32x32x16 one; ragged on both sides
+    # from 160 tiles on the 16x16x32 instruction, transposed on its way to the epilogue, 256 columns only where few CUs idle through few k-tiles (200 tiles: not through
+    # the 17 of the longest); below it the 32x32x16 one; ragged on both sides
     for M, N in [(40 * 256 - 5, 4 * width + 16), (39 * 256 + 3, 3 * width + 8), (39 * 256, 3 * width + 200)]:
         e = _gemm_case("nt", M, N, K, tile_cfg, seed=M + K)
         print(f"\n[gemm nt cfg {tile_cfg} {M}x{N}x{K}] rel err {e:.2e}", flush=True)
