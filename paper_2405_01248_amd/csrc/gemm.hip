@@ -964,9 +964,10 @@ static int splits_128(int rows, int N, int K, bool ln, bool heavy, float* us) {
 
 
 // Tiles whose waves share the contraction (gemm_wave_kernel): fixed part of a tile, which grows a little with the number of tiles, and the time
-// of a k-tile of the workgroup, a quarter of a wave's, each of which waits for memory; two: the same where a CU holds two tiles at a time.  us,
+// of a k-tile of the workgroup, one wave's divided by the waves, each of which waits for memory; two: the same for 257 to 512 tiles, which 64x64, 64x96 and 32x32 run two a CU side by
+// side, 32x64 and 32x96, whose buffers fill a CU, one after the other.  us,
 // fitted on MI355X over 77..4928 rows, 640..10240 columns, contractions of 640..10240 (within 8 %; two_per_kt, which grows with the contraction, on the dear side);
-// 32 rows over 80..1232 rows, 512..4096 columns, contractions of 512..4096, beyond 512 tiles, where they are never the best, on the dear side too.
+// 32 rows over 80..1232 rows, 512..4096 columns, contractions of 512..4096.
 struct WaveCost { int bm, bn; float fixed, per_tile, per_kt, per_kt_tile, two_fixed, two_per_kt; };
 static const WaveCost kWave[] = {{64, 64, 3.6f, 0.005f, 0.173f, 0.f, 4.1f, 0.36f}, {64, 96, 3.7f, 0.0075f, 0.212f, 0.f, 5.6f, 0.50f},
                                  {128, 96, 6.8f, 0.005f, 0.255f, 0.0003f, 0.f, 0.f}, {128, 128, 8.0f, 0.015f, 0.325f, 0.0002f, 0.f, 0.f},
@@ -978,6 +979,7 @@ static float wave_us(const WaveCost& c, int rows, int N, int K, bool may_split, 
   const int tiles = (int)std::min<long>((long)((rows + c.bm - 1) / c.bm) * tiles_n, 1 << 24);
   auto time = [&](int z) {
     const int n = tiles * z, part = (kt + z - 1) / z;
+    if (c.bm == 32 && n > 2 * kCUs) return 1e9f;      // a third round, of which the terms know nothing; 64 rows are as good or better (8300 x 104, K = 4096: 32.2 us, 64x64 24.3, 128x128 20.2)
     const float reduce = z > 1 ? reduce_us(rows, N, z, ln) : 0.f;
     if (n > kCUs && c.two_fixed > 0.f) return std::max(1.0f, (float)n / 512.0f) * (c.two_fixed + (float)part * c.two_per_kt) + (n > 2 * kCUs ? 1.0f : 0.f) + reduce;
     const float live = (float)std::min(n, kCUs);

@@ -75,6 +75,13 @@ def test_32_rows_with_eight_waves_that_share_the_contraction(tile_cfg, width, la
         assert e <= TOL_BF16
 
 
+@pytest.mark.parametrize("M,N,K", [(4064, 112, 512), (4128, 112, 512), (8160, 104, 2048), (8200, 104, 2048)])
+def test_few_columns_on_either_side_of_512_tiles_of_32_rows(M, N, K):
+    # 508 and 516 tiles of 32x32, 510 and 514 of 32x64: beyond 512 a tile of more rows is chosen
+    e = _gemm_case("nt", M, N, K, 0, seed=M + K)
+    assert e <= TOL_BF16, e
+
+
 @pytest.mark.parametrize("K", [64, 256, 320, 512, 576, 832, 1088])
 def test_waves_with_one_and_two_k_tiles_on_their_way(K):
     # up to 256 tiles of 64x64 a wave has two k-tiles on their way to LDS, beyond one: 1, 2, 3, 4, 5 k-tiles of the first wave, fewer of the others
