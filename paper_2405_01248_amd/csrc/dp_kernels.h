@@ -212,7 +212,7 @@ struct LnBwdArgs {
 int launch_ln_bwd(const LnBwdArgs& a, hipStream_t s);
 constexpr int LN_REDUCE_MAX = 4;
 int launch_ln_bwd_reduce(const LnBwdArgs* a, int n, hipStream_t s);
-size_t ln_bwd_partial_bytes(int rows, int d, int rows_per_batch);
+size_t ln_bwd_partial_bytes(int rows, int d, int rows_per_batch, bool modulated);
 
 // g[m, j] = u[m, j] * gelu_erf(u[m, inner + j])
 int launch_geglu_fwd(int dtype, const void* u, void* g, int rows, int inner, hipStream_t s);

@@ -240,12 +240,23 @@ int launch_ln_fwd(const LnArgs& a, hipStream_t s) {
 }
 
 // ------------------------------------------------------------------ LayerNorm backward
-// Rows per workgroup (a multiple of LNB_AT_ONCE): 16, fewer where that leaves fewer than 1536 waves for the CUs.  1024 rows of 1152 on 64
-// workgroups took 16.3 us, on 256 8.8; 8192 rows of 640 on 512 workgroups of two waves 26.8 us, on 1024 20.2.  A few dozen rows: two, one pass.
+// Rows per workgroup (a multiple of LNB_AT_ONCE): 16, fewer where that leaves few workgroups for the CUs; the lines are in 512 columns of a row, a wave and a half of
+// ln_bwd_kernel and the wave of gate_bwd_kernel in bf16.  1024 rows of 1152 on 64
+// workgroups took 16.3 us, on 256 8.8; 8192 rows of 640 on 512 workgroups 26.8 us, on 1024 20.2 (with eight columns a thread).  A few dozen rows: two, one pass.
 // (The partial sums to be added afterwards grow to the same number, a few MB.)
-static int ln_bwd_rows(int rows, int d) {
-  const long waves = (d + 511) / 512;
-  return rows * waves >= 1536 * 16 ? 16 : (rows * waves >= 1536 * 8 ? 8 : (rows * waves >= 512 ? 4 : 2));
+// Rows of more than 1024 columns are five to eight waves, and few such workgroups fit a CU: where those of the least rows do not run at once and those of
+// up to 40 do, these are taken, instead of a second round that is nearly empty (us, 16 rows and as chosen: gated, 14336 x 1152 71.5 -> 55.5, 16384 83.1 -> 70.0, 24576 122 ->
+// 106, 9216 x 1536 63.9 -> 52.3, 10240 x 1920 93.3 -> 75.2, 8 rows 6144 x 1536 29.9 -> 26.4; modulated alone, 14336 x 1600 71.8 -> 61.8; affine, 14336 x 1600 88.0 -> 80.8, 14336 x
+// 1920 101 -> 95, but 24576 x 1152, where it is two rounds either way, 91 -> 101).  Narrower rows have workgroups enough to fill their last round.
+static int ln_bwd_rows(int rows, int d, int rows_per_batch, bool modulated) {
+  const long halves = (d + 511) / 512;
+  const int least = rows * halves >= 1536 * 16 ? 16 : (rows * halves >= 1536 * 8 ? 8 : (rows * halves >= 512 ? 4 : 2));
+  const int waves = (d / 4 + 63) / 64;
+  if (least < 8 || waves < (modulated ? 5 : 6)) return least;
+  const long at_once = 256 * (modulated ? (waves == 5 ? 3 : 2) : (waves == 6 ? 4 : 3));      // (modulated: of the gated kernel; as they were seen to run)
+  for (const int r : {8, 10, 12, 14, 16, 20, 22, 24, 28, 32, 40})
+    if (r >= least && (long)(rows / rows_per_batch) * ((rows_per_batch + r - 1) / r) <= at_once) return r;
+  return least;
 }
 
 // Gated branch behind a result row: see ln_bwd_kernel.
@@ -432,10 +443,8 @@ __global__ void __launch_bounds__(THREADS) ln_bwd_reduce_kernel(const LnReduceSe
   }
 }
 
-size_t ln_bwd_partial_bytes(int rows, int d, int rows_per_batch) {
-  if (rows_per_batch <= 0) rows_per_batch = rows;
-  const int nb = rows / rows_per_batch;
-  const int wg_rows = ln_bwd_rows(rows, d), nchunk = (rows_per_batch + wg_rows - 1) / wg_rows;
+size_t ln_bwd_partial_bytes(int rows, int d, int rows_per_batch, bool modulated) {
+  const int nb = rows / rows_per_batch, wg_rows = ln_bwd_rows(rows, d, rows_per_batch, modulated), nchunk = (rows_per_batch + wg_rows - 1) / wg_rows;
   return (size_t)nb * nchunk * 2 * d * sizeof(float);
 }
 
@@ -444,7 +453,7 @@ static int ln_bwd_threads(const LnBwdArgs& a) { return (a.d / (a.dtype == BF16 ?
 template <typename T>
 static int ln_bwd_t(const LnBwdArgs& a, int rpb, int nb, int nchunk, float* partial, hipStream_t s) {
   auto kern = a.gate ? ln_bwd_kernel<T, true> : ln_bwd_kernel<T, false>;
-  hipLaunchKernelGGL(kern, dim3(nchunk, nb), dim3((a.d / 4 + 63) / 64 * 64), 0, s, a.d, rpb, ln_bwd_rows(a.rows, a.d), (const T*)a.dy,
+  hipLaunchKernelGGL(kern, dim3(nchunk, nb), dim3((a.d / 4 + 63) / 64 * 64), 0, s, a.d, rpb, ln_bwd_rows(a.rows, a.d, rpb, a.scale != nullptr), (const T*)a.dy,
                      (const float*)a.x, a.mean, a.rstd, (const T*)a.gamma, (const T*)a.scale, a.mod_ld,
                      a.dres_storage ? nullptr : (const float*)a.dres, a.dres_storage ? (const T*)a.dres : nullptr, (T*)a.dx, a.dx32, partial, gate_of(a));
   return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "ln_bwd launch failed");
@@ -456,12 +465,12 @@ int launch_ln_bwd(const LnBwdArgs& a, hipStream_t s) {
   const bool modulated = a.scale != nullptr;
   const int rpb = modulated ? a.rows_per_batch : a.rows;
   if (rpb <= 0 || a.rows % rpb) return set_error(DP_EINVAL, "ln_bwd: rows must be a multiple of rows_per_batch");
-  const int nb = a.rows / rpb, wg_rows = ln_bwd_rows(a.rows, a.d), nchunk = (rpb + wg_rows - 1) / wg_rows;
+  const int nb = a.rows / rpb, wg_rows = ln_bwd_rows(a.rows, a.d, rpb, modulated), nchunk = (rpb + wg_rows - 1) / wg_rows;
   if (a.gate && (!modulated || !a.branch || !a.dbranch || !a.gate_partial || !a.partial || a.gate_ld % 8)) return set_error(DP_EINVAL, "ln_bwd: a gated branch needs modulated rows, its operands and partial buffers");
   const bool want_cols = modulated ? (a.dscale && a.dshift) : (a.dgamma && a.dbeta);
   float* partial = nullptr;
   if (want_cols) {
-    if (!a.partial || a.partial_bytes < ln_bwd_partial_bytes(a.rows, a.d, rpb)) return set_error(DP_EWORKSPACE, "ln_bwd: partial buffer too small");
+    if (!a.partial || a.partial_bytes < ln_bwd_partial_bytes(a.rows, a.d, rpb, modulated)) return set_error(DP_EWORKSPACE, "ln_bwd: partial buffer too small");
     partial = a.partial;
   }
   int e;
@@ -478,7 +487,7 @@ int launch_gate_bwd(const LnBwdArgs& a, hipStream_t s) {
   if (int e = check_ln_dim(a.dtype, a.d)) return e;
   const void* ptrs[] = {a.dres, a.branch, a.gate, a.dbranch, a.gate_partial};
   for (const void* q : ptrs) if (!q || ((uintptr_t)q % 16)) return set_error(DP_EALIGN, "gate_bwd: operands must be non-null and 16-byte aligned");
-  const int wg_rows = ln_bwd_rows(a.rows, a.d), nchunk = (a.rows_per_batch + wg_rows - 1) / wg_rows;
+  const int wg_rows = ln_bwd_rows(a.rows, a.d, a.rows_per_batch, true), nchunk = (a.rows_per_batch + wg_rows - 1) / wg_rows;
   auto kern = a.dtype == BF16 ? gate_bwd_kernel<bf16> : gate_bwd_kernel<float>;
   KScope ks(KK_OTHER, 0.0, a.rows * (double)a.d * (4.0 + 2.0 * dtype_size(a.dtype)), s, a.rows, a.d);
   hipLaunchKernelGGL(kern, dim3(nchunk, a.rows / a.rows_per_batch), dim3(ln_bwd_threads(a)), 0, s, a.d, a.rows_per_batch, wg_rows, (const float*)a.dres, gate_of(a));
@@ -501,7 +510,7 @@ int launch_ln_bwd_reduce(const LnBwdArgs* a, int n, hipStream_t s) {
     set.out0[i] = modulated ? a[i].dscale : (void*)a[i].dgamma;
     set.out1[i] = modulated ? a[i].dshift : (void*)a[i].dbeta;
   }
-  const int nb = a[0].rows / rpb, wg_rows = ln_bwd_rows(a[0].rows, d), nchunk = (rpb + wg_rows - 1) / wg_rows;
+  const int nb = a[0].rows / rpb, wg_rows = ln_bwd_rows(a[0].rows, d, rpb, modulated), nchunk = (rpb + wg_rows - 1) / wg_rows;
   KScope ks(KK_REDUCE, 0.0, (double)n * nb * nchunk * 2 * d * 4, s, nchunk, 2 * d);
   if (modulated)
     hipLaunchKernelGGL((a[0].dtype == BF16 ? ln_bwd_reduce_kernel<256, 64, bf16> : ln_bwd_reduce_kernel<256, 64, float>), dim3((2 * d + 63) / 64, nb, n), dim3(256), 0, s, set, nchunk, d, a[0].dmod_ld, 0);

@@ -197,7 +197,7 @@ static void plan_bwd_scratch(Plan& p, const dp_stage& s, BwdScratch& b) {
   if (copies) for (int i = 0; i < 3 && i + 1 < s.d.n_blocks; ++i) b.out_h[i] = p.take(T * d * es);
   b.dh = p.take(T * d * es); b.da = p.take(T * d * es);
   b.delta = (float*)p.take((size_t)s.d.batch * s.d.n_heads * s.d.tokens * sizeof(float));
-  b.ln_partial_bytes = ln_bwd_partial_bytes((int)T, (int)d, unet ? (int)T : s.d.tokens);
+  b.ln_partial_bytes = ln_bwd_partial_bytes((int)T, (int)d, unet ? (int)T : s.d.tokens, !unet);
   for (int i = 0; i < 2; ++i) {
     BwdSet& t = b.set[i];
     if (i && (s.d.n_blocks < SIDE_MIN_BLOCKS || es == 4)) {
