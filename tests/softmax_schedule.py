@@ -1,6 +1,6 @@
 """Host model of when a tiled online softmax has to move its reference point (test helper).
 
-The fused attention forward walks the keys in tiles of 64 and keeps, per query, a reference
+Beyond 128 keys the fused attention forward walks them in tiles of 64 and keeps, per query, a reference
 exponent in log2 units.  A wave of 32 consecutive queries moves its references (and rescales the
 running sums and output accumulators) at a key tile only when some query of the wave has a score in
 that tile more than 2^8 above its reference; otherwise the old reference stays.  The first tile
@@ -56,6 +56,15 @@ def rescale_stats(logits: np.ndarray) -> dict:
     p /= p.sum(axis=-1, keepdims=True)
     return {"steps_late": steps, "moves_late": moves, "max_rise_log2": max_rise,
             "mean_max_prob": float(p.max(axis=-1).mean())}
+
+
+def far_later_keys(logits: np.ndarray) -> tuple:
+    """The rule of the forward that has all keys (at most 128) at once: a query's reference lies above the largest of its first 64 keys
+    unless one of the others is more than 2^11 above them.  Returns (queries for which one is, queries that have other keys)."""
+    s = np.asarray(logits, dtype=np.float64) * LOG2E
+    assert KEYS_PER_TILE < s.shape[-1] <= 2 * KEYS_PER_TILE
+    first, later = s[..., :KEYS_PER_TILE].max(axis=-1), s[..., KEYS_PER_TILE:].max(axis=-1)
+    return int(np.sum(later > first + 11.0)), int(np.sum(np.isfinite(later)))
 
 
 def head_logits(q: np.ndarray, k: np.ndarray, n_heads: int, causal: bool = False) -> np.ndarray:

@@ -100,7 +100,8 @@ ATTN_CASES = [
     (2, 2, 200, 200, 64, True, 1.0, 0.0),       # causal over several key tiles: the diagonal mask meets full tiles
     # sharp softmax: logits spread over tens of log2 units, a per-row shift of up to +-80, row maxima
     # arriving in late key tiles -- the running reference of the online softmax has to move after the
-    # first tile (gain 16: at almost every tile; gain 4: at some tiles and not at others)
+    # first tile (gain 16: at almost every tile; gain 4: at some tiles and not at others), and the reference
+    # of 77 keys at once has to be that of the keys past the first 64 for some queries
     (2, 3, 200, 200, 64, False, 16.0, 80.0),
     (2, 3, 200, 200, 64, False, 4.0, 80.0),
     (2, 3, 200, 77, 64, False, 16.0, 80.0),
@@ -120,7 +121,7 @@ def test_attention_forward_and_backward(case):
     import torch
     from paper_2405_01248_amd import binding as B
     from paper_2405_01248_amd.harness import _np_to_dev, _dev_to_np, rel_err, rel_l2
-    from softmax_schedule import head_logits, rescale_stats
+    from softmax_schedule import far_later_keys, head_logits, rescale_stats
     Bt, H, Nq, Nk, dh, causal, gain, row_shift = case
     d = H * dh
     q, k, v, do = si.make_attention_inputs(Bt, H, Nq, Nk, dh, seed=Nq * 31 + Nk, gain=gain, row_shift=row_shift)
@@ -130,7 +131,12 @@ def test_attention_forward_and_backward(case):
         # the oracle's logits and require that it fires after the first key tile, on peaked rows
         st = rescale_stats(s)
         print(f"\n[attention stress {_attn_id(case)}] {st}", flush=True)
-        assert st["moves_late"] > 0 and st["max_rise_log2"] > 8.0 and st["mean_max_prob"] > 0.5, st
+        assert st["mean_max_prob"] > 0.5, st
+        if Nk <= 128:      # all keys at once: where a later key is far above the first 64, and where none is
+            far, of = far_later_keys(s)
+            assert 0 < far < of, (far, of)
+        else:
+            assert st["moves_late"] > 0 and st["max_rise_log2"] > 8.0, st
         if gain <= 4.0:
             assert st["moves_late"] < st["steps_late"], st          # ... and also does not fire at some tiles
     dq_, dk_, dv_, ddo = (_np_to_dev(t, "bf16") for t in (q, k, v, do))

@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 import synth_inputs as si
-from softmax_schedule import LOG2E, head_logits, rescale_stats
+from softmax_schedule import LOG2E, far_later_keys, head_logits, rescale_stats
 
 
 def _two_tiles(rise_log2):
@@ -21,6 +21,19 @@ def test_reference_moves_only_beyond_the_threshold():
     assert (st["steps_late"], st["moves_late"], st["max_rise_log2"]) == (1, 0, 0.0)
     # uniform rows: probability 1 / Nk everywhere
     assert abs(rescale_stats(np.zeros((2, 40, 77)))["mean_max_prob"] - 1.0 / 77) < 1e-12
+
+
+def test_one_of_the_later_keys_is_far_above_the_first():
+    assert far_later_keys(_two_tiles(11.5)) == (1, 32) and far_later_keys(_two_tiles(10.5)) == (0, 32)
+    s = np.where(np.arange(77)[None, :] > np.arange(77)[:, None], -np.inf, 0.0)[None]
+    assert far_later_keys(s) == (0, 13)      # causal: the queries from 64 on have others
+    from test_gpu_ops import ATTN_CASES
+    few = [c for c in ATTN_CASES if c[6] != 1.0 and c[3] <= 128]
+    assert {c[5] for c in few} == {False, True}
+    for (B, H, Nq, Nk, dh, causal, gain, shift) in few:
+        q, k, _, _ = si.make_attention_inputs(B, H, Nq, Nk, dh, seed=Nq * 31 + Nk, gain=gain, row_shift=shift)
+        far, of = far_later_keys(head_logits(q, k, H, causal))
+        assert 0 < far < of
 
 
 def test_masked_tiles_and_waves_are_counted_as_the_kernel_walks_them():
