@@ -412,7 +412,8 @@ int dp_schedule_search(const dp_layer_cost* rows, int n_rows, const dp_search_op
  *   16, 17  64x64 and 64x128 direct-to-LDS tiles: a_kmajor = b_kmajor = 0, K % 64 == 0
  *   18..21  tiles of two alternating wave groups, 256 rows x 256, 128, 192, 160 columns: a_kmajor = b_kmajor = 0, out_is_f32 = 0
  *   22..25  the weight-gradient tiles 256x256, 256x128, 128x256, 256x192: a_kmajor = b_kmajor = 1, out_is_f32 = 1
- *   26..32  tiles whose waves share the contraction, 64x64, 64x96, 128x96, 128x128, 32x32, 32x64, 32x96: as 18..21, K % 64 == 0
+ *   26..32  tiles whose waves share the contraction, 64x64, 64x96, 128x96, 128x128, 32x32, 32x64, 32x96: a_kmajor = 0, b_kmajor = 0 or 1,
+ *           out_is_f32 = 0, K % 64 == 0
  * A forced configuration that does not fit the problem returns DP_EUNSUPPORTED without launching. */
 size_t dp_op_gemm_workspace_bytes(int M, int N, int K);
 int dp_op_gemm(int dtype, const void* A, int lda, int a_kmajor, const void* B, int ldb, int b_kmajor, int M, int N, int K,

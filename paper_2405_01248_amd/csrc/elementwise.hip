@@ -1,8 +1,8 @@
 // Bandwidth-bound kernels of a stage: LayerNorm forward/backward (affine or adaLN
 // modulated), GeGLU, SiLU, gated-residual backward, column sums (bias gradients),
-// split-K partial reduction, embedding gather.  16-byte accesses, one wave per token row or
-// columns per thread; all reductions are in a fixed order (no float atomics), so results are
-// run-to-run identical.  Templated on the storage type (bf16 or fp32); math is fp32.
+// split-K partial reduction, embedding gather.  Accesses of 16 bytes (8 for bf16 rows of a LayerNorm); 16, 32
+// or 64 lanes or a workgroup per token row, or columns per thread; all reductions are in a fixed order (no
+// float atomics), so results are run-to-run identical.  Templated on the storage type (bf16 or fp32); math is fp32.
 #include "dp_device.h"
 #include "dp_kernels.h"
 #include "dp_errors.h"
@@ -405,7 +405,7 @@ __global__ void __launch_bounds__(512, 2) ln_bwd_kernel(int d, int rows_per_batc
 
 // out_k[b * ld + col] = (acc ? old : 0) + sum_chunks partial[b][chunk][k][col], k = 0 (gain grad), 1 (shift grad).
 // grid = (ceil(2d / COLS), n_batches); a thread sums four columns of every GROUPS-th chunk in ascending order, then the groups are added in ascending
-// order, in eight parts (fixed order).  blockIdx.z: one of several LayerNorms of the same shape.  32 samples of 32 chunks of 1152, three
+// order, in PARTS parts (fixed order; four for modulated LayerNorms, eight otherwise).  blockIdx.z: one of several LayerNorms of the same shape.  32 samples of 32 chunks of 1152, three
 // LayerNorms: 6912 workgroups of 1024 threads that read a value each took 18.9 us, beside the main stream of a stage 140, now 12 and 27; 1024 chunks of 320 12 -> 6.
 struct LnReduceSet { const float* partial[LN_REDUCE_MAX]; void* out0[LN_REDUCE_MAX]; void* out1[LN_REDUCE_MAX]; };
 template <int THREADS, int COLS, typename Out>

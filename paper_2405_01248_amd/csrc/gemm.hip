@@ -662,8 +662,9 @@ struct WaveTile {
   static_assert(BM % RP == 0 && BYTES <= 160 * 1024, "tile shape");
 };
 // B_MC: dx = dy W with the weights as they are stored, [contraction][columns]; their tile is read with the transposing LDS load.  Against
-// a transposed copy (us): 64x64 and 128x128 tiles the same, 64x96, whose rows of 192 bytes begin inside cache lines, 4 to 9 % more (1024 x 1152, K = 4608 19.5 and
-// 20.8; 1026 x 1280, K = 3840 18.2 and 20.3), less than the copy costs (4 N K bytes at 6.3 TB/s: 3.4 and 3.1): a U-Net block 2 x 513 x 1280, two micro-batches of
+// a transposed copy (us): on average over 64 to 8192 rows none more on 128x128 tiles, 2 % on 64x64, 4 % on 128x96, 32x32 and 32x64, 8 to 10 % on 64x96 and 32x96, whose rows of 192 bytes begin inside cache lines (1024 x 1152, K = 4608 19.5
+// and 20.8; 1026 x 1280, K = 3840 18.1 and 19.9), which is less than the copy costs (4 N K bytes at 6.3 TB/s: 3.4 and 3.1) but for a few (1026 x 1024, K = 8192 31.0 and 39.3
+// beside 5.3; 2560 x 512, K = 4096 17.6 and 20.3 beside 1.3): a U-Net block 2 x 513 x 1280, two micro-batches of
 // three passes 1279 -> 1256, seven DiT blocks 4 x 256 x 1152 2163 -> 2150.
 template <class T, int KIND, bool B_MC = false>
 __global__ void __launch_bounds__(T::NW * 64, T::TM * T::TN == 1 ? 4 : (T::TM * T::TN <= 6 ? 2 : 1)) gemm_wave_kernel(const GemmBf16Params p) {

@@ -855,9 +855,9 @@ static size_t encoder_splitk(const dp_encoder& e, int rows, int choice_rows) {
   auto need = [&](int N, int K) { return gemm_epi_splitk_ws_bytes_for(rows, N, K, choice_rows); };
   return std::max(std::max(need(3 * d, d), need(d, d)), std::max(need(ff, d), need(d, ff)));
 }
-// More rows are split into fewer parts, down to none, and a workspace has to serve every smaller call: the running maximum over the rows.  Between two
-// multiples of 64 all tile counts are the same and the reduction of the partial sums costs least on the fewest rows, so the parts chosen there
-// are the most.
+// More rows are split into fewer parts, down to none, and a workspace has to serve every smaller call: the running maximum over the rows.  On more rows
+// no kind of tile has fewer tiles (those of 32 rows one more half way to a multiple of 64), which bound the parts and make them dearer, and the
+// reduction of the partial sums costs more, so the parts chosen for the first row of a step of 64 are the most in it.
 constexpr size_t SPLITK_STEP = 64;
 static void plan_encoder_splitk(dp_encoder& e) {
   if (e.es != 2) return;
