@@ -42,6 +42,8 @@ template <int V> __device__ __forceinline__ void store_f32(float* p, const float
 // L lanes share a row (256 / L rows per workgroup at a time); lane l has columns 4 (c L + l) .. + 3 for c = 0 .. NC - 1, so every access of a group
 // is L x 16 bytes in a row (fp32) and only the last chunk can be partly empty.  A wave of several rows asks for more bytes at a time and
 // adds up fewer lanes; a row's lanes are all in one wave, so nothing waits at a barrier.
+// Either side of the lines, 16 / 32 / 64 lanes, us: 32768 rows of 160 columns 5.9 / 7.1 / 8.3, 256 8.6 / 9.1 / 9.7, 384 11.9 / 11.8 / 12.2, 400 13.2 / 12.5 / 12.4, 768 27.9 / 20.9 /
+// 20.6, 800 - / 22.2 / 21.5, 1152 - / 34.5 / 29.9; 8192 of 320 3.8 / 4.0 / 4.6, of 400 4.5 / 4.7 / 4.8; 4096 of 400 4.1 / 3.4 / 3.4, of 768 6.4 / 4.2 / 4.4; 2048 of 768 5.9 / 3.4 / 3.2.
 constexpr int LN_MAX_CHUNKS = 8;      // d <= 64 * 4 * 8
 struct LnShape { int lanes, chunks; };
 static LnShape ln_shape(int rows, int d) {
