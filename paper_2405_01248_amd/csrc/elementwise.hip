@@ -242,8 +242,8 @@ int launch_ln_fwd(const LnArgs& a, hipStream_t s) {
 }
 
 // ------------------------------------------------------------------ LayerNorm backward
-// Rows per workgroup (a multiple of LNB_AT_ONCE): 16, fewer where that leaves few workgroups for the CUs; the lines are in 512 columns of a row, a wave and a half of
-// ln_bwd_kernel and the wave of gate_bwd_kernel in bf16.  1024 rows of 1152 on 64
+// Rows per workgroup (a multiple of LNB_AT_ONCE): 16, fewer where that leaves few workgroups for the CUs; the lines are in 512 columns of a row, two waves of
+// ln_bwd_kernel and one of gate_bwd_kernel in bf16.  1024 rows of 1152 on 64
 // workgroups took 16.3 us, on 256 8.8; 8192 rows of 640 on 512 workgroups 26.8 us, on 1024 20.2 (with eight columns a thread).  A few dozen rows: two, one pass.
 // (The partial sums to be added afterwards grow to the same number, a few MB.)
 // Rows of more than 1024 columns are five to eight waves, and few such workgroups fit a CU: where those of the least rows do not run at once and those of
