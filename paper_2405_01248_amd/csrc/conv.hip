@@ -343,31 +343,33 @@ __global__ void __launch_bounds__(512, 2) conv3x3_pp_kernel(const ConvParams p, 
   for (int j = 0; j < T::LB0; ++j) vb0[j] = offset_b(0, j);
 #pragma unroll
   for (int j = 0; j < T::LB1; ++j) vb1[j] = offset_b(1, j);
-  // per row half, the k-tile whose copies come next (each half is copied tile by tile in order): its tap and first channel, and
-  // the lanes' source offsets for that tap, which are formed once per tap
-  int it_tap[2] = {0, 0}, it_c0[2] = {0, 0};
+  // per row half, the k-tile whose copies come next (each half is copied tile by tile in order): its tap and the bytes of its first channel, and
+  // the lanes' source offsets for that tap, which are formed once per tap.  No pixel has a tenth tap, so that what is copied past the last k-tile reads
+  // nothing.  (Tap and channel counted apart, with a check against the last k-tile a copy: the class took 8.30 ms on 8 samples of 512x512, now 8.03.)
+  const int tap_bytes = 2 * p.Cin;
+  int it_tap[2] = {-1, -1}, it_off[2] = {tap_bytes, tap_bytes};
   uint32_t va[2][T::LA];
+  const rsrc_t rx = make_rsrc(p.x, x_bytes);
   typename T::acc_t acc[2][T::TM][T::TN];
   float csum[2][T::TM];
-  pp_main_loop<T, false, false>(acc, smem_raw, nk, wm, wn, wave >= 4, lane,
-      [&](int h, int t, unsigned char* dst) {
-        const rsrc_t r = make_rsrc(p.x, t < nk ? x_bytes : 0u);
-        if (it_c0[h] == 0) {
-          const int tap = it_tap[h], u = (tap * 11) >> 5, v = tap - 3 * u;          // tap / 3, tap % 3
+  pp_main_loop<T, false, false, false, T::BM == 256>(acc, smem_raw, nk, wm, wn, wave >= 4, lane,
+      [&](auto hc, int, unsigned char* dst) {
+        constexpr int h = decltype(hc)::value;
+        if (it_off[h] == tap_bytes) {
+          it_off[h] = 0;
+          const int tap = ++it_tap[h], u = (tap * 11) >> 5, v = tap - 3 * u;          // tap / 3, tap % 3
           const int off = 2 * ((u - 1) * p.W + (v - 1)) * p.Cin;
 #pragma unroll
           for (int j = 0; j < T::LA; ++j) va[h][j] = (a_taps[h][j / 2] >> (tap + 16 * (j % 2))) & 1u ? (uint32_t)(a_base[h][j] + off) : OUTSIDE;
         }
-        const uint32_t off = 2u * (uint32_t)it_c0[h];
-        it_c0[h] += T::BK;
-        if (it_c0[h] == p.Cin) { it_c0[h] = 0; ++it_tap[h]; }
 #pragma unroll
-        for (int j = 0; j < T::LA; ++j) async_copy_16B_buf(r, va[h][j], off, dst + (wave * T::LA + j) * 1024);
+        for (int j = 0; j < T::LA; ++j) async_copy_16B_buf(rx, va[h][j], (uint32_t)it_off[h], dst + (wave * T::LA + j) * 1024);
+        it_off[h] += 2 * T::BK;
       },
       [&](auto hc, int t, unsigned char* dst) {
         constexpr int h = decltype(hc)::value;
         const rsrc_t r = make_rsrc(p.w, t < nk ? w_bytes : 0u);
-        const uint32_t off = t < nk ? (uint32_t)t * (2u * T::BK) : 0u;
+        const uint32_t off = (uint32_t)t * (2u * T::BK);
 #pragma unroll
         for (int j = 0; j < (h ? T::LB1 : T::LB0); ++j) async_copy_16B_buf(r, h ? vb1[h ? j : 0] : vb0[h ? 0 : j], off, dst + piece_b(h, j) * 1024);
       }, false, csum);

@@ -73,11 +73,12 @@ __device__ __forceinline__ uint32_t pp_mc_offset(int col0, int lane) {
 // MC: both operands have the contraction strided.  colsum (MC only): a wave-uniform flag; csum[half][i] then receives
 // the sum over the contraction of row i of the wave's part of A (this lane's k-slots; lanes l and l + 32 hold the two halves).
 // AHEAD: the copies of k-tile 0 (pp_first_k_tile) are on their way already.
-template <class T, class CopyA, class CopyB>
-__device__ __forceinline__ void pp_first_k_tile(unsigned char* smem, CopyA copy_a, CopyB copy_b) {
-  copy_b(std::integral_constant<int, 0>(), 0, smem + T::OB0); copy_a(0, 0, smem); copy_b(std::integral_constant<int, 1>(), 0, smem + T::OB1); copy_a(1, 0, smem + T::A_HALF);
-}
-template <class T, bool FP8, bool MC, bool AHEAD = false, class CopyA, class CopyB>
+// PAIRS: two k-tiles a round of the loop, so that the stages' addresses are constants.  What a fetch slot issues beside its reads and copies counts: a
+// wave issues an instruction every four cycles or so, and with 44 to 64 scalar and 15 to 23 vector ones a k-tile the slots of a 256x128 tile took longer
+// than the 128 cycles of matrix work beside them; 26 to 35 and 0 to 6 are left.  bf16 products of one tile a CU: 8192 x 640, K = 640 / 5120 12.3 -> 11.3 / 57.3
+// -> 54.3 us, 8192 x 1152, K = 1152 / 4608 24.4 -> 23.1 / 78.3 -> 73.2.  Not where workgroups walk over tiles (32768 x 1280, K = 320 40.7 -> 43.0 us, 8192^3 739 -> 721) nor
+// for FP8 (8192 x 4608, K = 1152 48.7 -> 52.2), whose scalar registers run out, and not where the second set of addresses spills (512x128 convolution).
+template <class T, bool FP8, bool MC, bool AHEAD = false, bool PAIRS = true, class CopyA, class CopyB>
 __device__ __forceinline__ void pp_main_loop(typename T::acc_t (&acc)[2][T::TM][T::TN], unsigned char* smem, int nk, int wm, int wn, bool trailing,
                                              int lane, CopyA copy_a, CopyB copy_b, bool colsum, float (&csum)[2][T::TM]) {
   constexpr int TM = T::TM, TN0 = T::TN0, LA = T::LA, LB0 = T::LB0, LB1 = T::LB1, FR = T::FR;
@@ -87,14 +88,18 @@ __device__ __forceinline__ void pp_main_loop(typename T::acc_t (&acc)[2][T::TM][
   bf16x8 fa[FP8 ? 1 : TM][KS], fb[2][FP8 ? 1 : T::TNM][KS];
   i32x8 qa[FP8 ? TM : 1][2], qb[2][FP8 ? T::TNM : 1][2];
   u32x2 ra[MC ? TM : 1][4][2], rb[2][MC ? T::TNM : 1][4][2];         // transposed fragments, 8 bytes each, as they arrive
-  uint32_t oa[TM], ob0[T::TN0], ob1[T::TN1];
+  uint32_t oa[2][TM], ob0[2][T::TN0], ob1[2][T::TN1];      // by stage: the second one is out of reach of an instruction's offset
   if constexpr (MC) {
 #pragma unroll
-    for (int i = 0; i < TM; ++i) oa[i] = lds_address(smem) + pp_mc_offset<T::BM / 2>(wm * T::SM + i * 32, lane);
+    for (int st = 0; st < 2; ++st) {
+      const uint32_t base = lds_address(smem) + (uint32_t)(st * T::STAGE);
 #pragma unroll
-    for (int j = 0; j < TN0; ++j) ob0[j] = lds_address(smem) + T::OB0 + pp_mc_offset<T::BN0>(wn * T::SN0 + j * 32, lane);
+      for (int i = 0; i < TM; ++i) oa[st][i] = base + pp_mc_offset<T::BM / 2>(wm * T::SM + i * 32, lane);
 #pragma unroll
-    for (int j = 0; j < T::TN1; ++j) ob1[j] = lds_address(smem) + T::OB1 + pp_mc_offset<T::BN1>(wn * T::SN1 + j * 32, lane);
+      for (int j = 0; j < TN0; ++j) ob0[st][j] = base + T::OB0 + pp_mc_offset<T::BN0>(wn * T::SN0 + j * 32, lane);
+#pragma unroll
+      for (int j = 0; j < T::TN1; ++j) ob1[st][j] = base + T::OB1 + pp_mc_offset<T::BN1>(wn * T::SN1 + j * 32, lane);
+    }
   }
 #pragma unroll
   for (int a = 0; a < 2; ++a)
@@ -114,15 +119,14 @@ __device__ __forceinline__ void pp_main_loop(typename T::acc_t (&acc)[2][T::TM][
     const u32x4 lo = chunk16(p, r, 4 * ks + 2 * q), hi = chunk16(p, r, 4 * ks + 2 * q + 1);
     return __builtin_bit_cast(i32x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
   };
-  auto fetch_a = [&](int stage, int h) {
+  auto fetch_a = [&](auto stage, auto hc) {
+    constexpr int h = decltype(hc)::value;
     const unsigned char* p = smem + stage * T::STAGE + h * T::A_HALF;
     if constexpr (MC) {
-      constexpr int ROW = T::BM / 2 * 2;
+      constexpr int ROW = T::BM / 2 * 2, HALF = h * T::A_HALF;
 #pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        const uint32_t at = oa[i] + (uint32_t)(stage * T::STAGE + h * T::A_HALF);
-        static_for<4>([&](auto ks) { lds_read_tr_raw<ks * 16 * ROW>(ra[i][ks][0], at); lds_read_tr_raw<(ks * 16 + 4) * ROW>(ra[i][ks][1], at); });
-      }
+      for (int i = 0; i < TM; ++i)
+        static_for<4>([&](auto ks) { lds_read_tr_raw<HALF + ks * 16 * ROW>(ra[i][ks][0], oa[stage][i]); lds_read_tr_raw<HALF + (ks * 16 + 4) * ROW>(ra[i][ks][1], oa[stage][i]); });
       return;
     }
 #pragma unroll
@@ -134,14 +138,14 @@ __device__ __forceinline__ void pp_main_loop(typename T::acc_t (&acc)[2][T::TM][
         else fa[i][ks] = __builtin_bit_cast(bf16x8, chunk16(p, r, (64 / FR) * ks + q));
       }
   };
-  auto fetch_b = [&](int stage, auto hc) {
+  auto fetch_b = [&](auto stage, auto hc) {
     constexpr int h = decltype(hc)::value;
     const unsigned char* p = smem + stage * T::STAGE + (h ? T::OB1 : T::OB0);
     if constexpr (MC) {
       constexpr int ROW = (h ? T::BN1 : T::BN0) * 2;
 #pragma unroll
       for (int j = 0; j < (h ? T::TN1 : TN0); ++j) {
-        const uint32_t at = (h ? ob1[h ? j : 0] : ob0[h ? 0 : j]) + (uint32_t)(stage * T::STAGE);
+        const uint32_t at = h ? ob1[stage][h ? j : 0] : ob0[stage][h ? 0 : j];
         static_for<4>([&](auto ks) { lds_read_tr_raw<ks * 16 * ROW>(rb[h][j][ks][0], at); lds_read_tr_raw<(ks * 16 + 4) * ROW>(rb[h][j][ks][1], at); });
       }
       return;
@@ -222,15 +226,37 @@ __device__ __forceinline__ void pp_main_loop(typename T::acc_t (&acc)[2][T::TM][
     barrier_nofence();
     __builtin_amdgcn_sched_barrier(0);
   };
-  auto stage_of = [&](int t) { return smem + (t & 1) * T::STAGE; };
   constexpr std::integral_constant<int, 0> H0{};
   constexpr std::integral_constant<int, 1> H1{};
+  auto k_tile = [&](auto stage, auto other, int t) {
+    unsigned char* here = smem + stage * T::STAGE;
+    fetch_a(stage, H0);
+    copy_a(H1, t + 1, smem + other * T::STAGE + T::A_HALF);
+    wait_vmcnt<3 * LA + LB0 + LB1>();
+    slot_end();
+    multiply(0, H0, true, true);
+    fetch_b(stage, H1);
+    copy_b(H0, t + 2, here + T::OB0);
+    wait_vmcnt<2 * LA + 2 * LB0 + LB1>();
+    slot_end();
+    multiply(0, H1, false, true);
+    fetch_a(stage, H1);
+    copy_a(H0, t + 2, here);
+    wait_vmcnt<3 * LA + LB0 + LB1>();
+    slot_end();
+    multiply(1, H0, true, false);
+    fetch_b(other, H0);                 // past the last k-tile: zeros, not used
+    copy_b(H1, t + 2, here + T::OB1);
+    wait_vmcnt<2 * LA + LB0 + 2 * LB1>();
+    slot_end();
+    multiply(1, H1, false, false);
+  };
 
   if constexpr (!AHEAD) pp_first_k_tile<T>(smem, copy_a, copy_b);
-  copy_b(H0, 1, stage_of(1) + T::OB0); copy_a(0, 1, stage_of(1)); copy_b(H1, 1, stage_of(1) + T::OB1);
+  copy_b(H0, 1, smem + T::STAGE + T::OB0); copy_a(H0, 1, smem + T::STAGE); copy_b(H1, 1, smem + T::STAGE + T::OB1);
   wait_vmcnt<2 * LA + LB0 + 2 * LB1>();        // the first B0 and A0 are there
   barrier_nofence();
-  fetch_b(0, H0);
+  fetch_b(H0, H0);
   if constexpr (MC) {
     // the transposing loads are not in the compiler's books: a register it copies on the way into the loop has to hold its value by then
     wait_lgkmcnt0();
@@ -240,28 +266,15 @@ __device__ __forceinline__ void pp_main_loop(typename T::acc_t (&acc)[2][T::TM][
       for (int ks = 0; ks < 4; ++ks) { lds_arrived(rb[0][j][ks][0]); lds_arrived(rb[0][j][ks][1]); }
   }
   if (trailing) barrier_nofence();
-  for (int t = 0; t < nk; ++t) {
-    const int st = t & 1;
-    fetch_a(st, 0);
-    copy_a(1, t + 1, stage_of(t + 1) + T::A_HALF);
-    wait_vmcnt<3 * LA + LB0 + LB1>();
-    slot_end();
-    multiply(0, H0, true, true);
-    fetch_b(st, H1);
-    copy_b(H0, t + 2, stage_of(t) + T::OB0);
-    wait_vmcnt<2 * LA + 2 * LB0 + LB1>();
-    slot_end();
-    multiply(0, H1, false, true);
-    fetch_a(st, 1);
-    copy_a(0, t + 2, stage_of(t));
-    wait_vmcnt<3 * LA + LB0 + LB1>();
-    slot_end();
-    multiply(1, H0, true, false);
-    fetch_b(st ^ 1, H0);                // past the last k-tile: zeros, not used
-    copy_b(H1, t + 2, stage_of(t) + T::OB1);
-    wait_vmcnt<2 * LA + LB0 + 2 * LB1>();
-    slot_end();
-    multiply(1, H1, false, false);
+  if constexpr (PAIRS) {
+    for (int t = 0;; t += 2) {
+      k_tile(H0, H1, t);
+      if (t + 1 >= nk) break;
+      k_tile(H1, H0, t + 1);
+      if (t + 2 >= nk) break;
+    }
+  } else {
+    for (int t = 0; t < nk; ++t) k_tile(t & 1, ~t & 1, t);
   }
   if (!trailing) barrier_nofence();
   wait_vmcnt<0>();                      // the epilogue reuses the stages

@@ -581,16 +581,19 @@ __device__ __forceinline__ void gemm_pp_body(const GemmBf16Params& p) {
     const int r = pp_piece_row(piece, lane);
     return pp_piece_chunk(r, lane) * 8 < k_last ? v : OUTSIDE;
   };
-  auto copy_a = [&](int h, int t, unsigned char* dst) {
+  // (of a buffer of no size nothing is read, whatever the offset)
+  auto k_offset = [&](int t) { return WALK && t >= n_kt ? 0u : (uint32_t)t * (2u * T::BK); };
+  auto copy_a = [&](auto hc, int t, unsigned char* dst) {
+    constexpr int h = decltype(hc)::value;
     const rsrc_t r = make_rsrc(p.A, t < n_kt ? p.a_bytes : 0u);
-    const uint32_t off = t < n_kt ? (uint32_t)t * (2u * T::BK) : 0u;
+    const uint32_t off = k_offset(t);
 #pragma unroll
     for (int j = 0; j < T::LA; ++j) async_copy_16B_buf(r, tail(va[h][j], wave * T::LA + j, t), off, dst + (wave * T::LA + j) * 1024);
   };
   auto copy_b = [&](auto hc, int t, unsigned char* dst) {
     constexpr int h = decltype(hc)::value;
     const rsrc_t r = make_rsrc(p.B, t < n_kt ? p.b_bytes : 0u);
-    const uint32_t off = t < n_kt ? (uint32_t)t * (2u * T::BK) : 0u;
+    const uint32_t off = k_offset(t);
 #pragma unroll
     for (int j = 0; j < (h ? T::LB1 : T::LB0); ++j)
       async_copy_16B_buf(r, tail(h ? vb1[h ? j : 0] : vb0[h ? 0 : j], piece_b(h, j), t), off, dst + piece_b(h, j) * 1024);
@@ -599,13 +602,13 @@ __device__ __forceinline__ void gemm_pp_body(const GemmBf16Params& p) {
   float csum[2][T::TM];
   set_tile(blockIdx.x);
   if constexpr (!WALK) {
-    pp_main_loop<T, FP8, false>(acc, smem_raw, nk, wm, wn, wave >= 4, lane, copy_a, copy_b, false, csum);
+    pp_main_loop<T, FP8, false, false, !FP8>(acc, smem_raw, nk, wm, wn, wave >= 4, lane, copy_a, copy_b, false, csum);
     pp_epilogue<T, KIND, 32>(acc, smem_raw, p.epi, m0, n0, wave, wm, wn, lane, []() {});
   } else {
     const int n_tiles = p.tiles_m * p.tiles_n;
     pp_first_k_tile<T>(smem_raw, copy_a, copy_b);
     for (int id = blockIdx.x;;) {
-      pp_main_loop<T, FP8, false, true>(acc, smem_raw, nk, wm, wn, wave >= 4, lane, copy_a, copy_b, false, csum);
+      pp_main_loop<T, FP8, false, true, false>(acc, smem_raw, nk, wm, wn, wave >= 4, lane, copy_a, copy_b, false, csum);
       id += gridDim.x;
       int le = lane;
       asm volatile("" : "+v"(le));

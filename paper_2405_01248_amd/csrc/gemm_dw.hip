@@ -49,14 +49,14 @@ __global__ void __launch_bounds__(512, 2) gemm_dw_group_kernel(const DwGroup grp
   const int tiles = p.tiles_m * p.tiles_n, id = xcd_contiguous_id(blockIdx.x - p.first, tiles * p.splits), split = id / tiles;
   int tile_m, tile_n;
   tile_of_id(id % tiles, p.tiles_m, p.tiles_n, p.group_m, tile_m, tile_n);
-  const int m0 = tile_m * T::BM, n0 = tile_n * T::BN, M = p.M, N = p.N, K = p.K, lda = p.lda, ldb = p.ldb;
-  const int kt0 = split * p.kt_per_split, kt_all = (K + 63) / 64, nk = min(kt_all, kt0 + p.kt_per_split) - kt0;
-  const int k_end = K - kt0 * 64;                       // contraction rows from this split's first one on
-  constexpr uint32_t OUTSIDE = 0xFFFFFFF0u;
-  const bf16* A = p.A; const bf16* B = p.B;
-  const uint32_t a_bytes = p.a_bytes, b_bytes = p.b_bytes;
-  // columns past the edge are fetched from the last valid chunk (they only feed outputs that are never stored), rows past the
-  // end of the contraction from outside the buffers (zeros)
+  const int m0 = tile_m * T::BM, n0 = tile_n * T::BN, M = p.M, N = p.N, lda = p.lda, ldb = p.ldb;
+  const int kt0 = split * p.kt_per_split, kt_all = (p.K + 63) / 64, nk = min(kt_all, kt0 + p.kt_per_split) - kt0;
+  const uint32_t k_end = (uint32_t)(kt0 + nk) * 128u;      // twice the contraction row behind this split's last one
+  const rsrc_t ra = make_rsrc(p.A, min(p.a_bytes, k_end * (uint32_t)lda)), rb = make_rsrc(p.B, min(p.b_bytes, k_end * (uint32_t)ldb));
+  const uint32_t step_a = 128u * (uint32_t)lda, step_b = 128u * (uint32_t)ldb;
+  // Columns past the edge are fetched from the last valid chunk (they only feed outputs that are never stored); rows past the end of the contraction
+  // lie outside the buffers and arrive as zeros.  Only the lanes' own offsets are checked against a buffer's size, so they take the steps along the
+  // contraction: one addition a copy, where a copy with the step in a scalar and the last k-tile's rows picked out took four vector instructions.
   uint32_t va[2][T::LA], vb0[T::LB0], vb1[T::LB1];
 #pragma unroll
   for (int h = 0; h < 2; ++h)
@@ -75,27 +75,19 @@ __global__ void __launch_bounds__(512, 2) gemm_dw_group_kernel(const DwGroup grp
     const int k = pp_mc_piece_k<T::BN1>(wave * T::LB1 + j, lane), c = pp_mc_piece_chunk<T::BN1>(k, lane);
     vb1[j] = 2u * ((uint32_t)(kt0 * 64 + k) * ldb + min(n0 + T::BN0 + c * 8, N - 8));
   }
-  const bool ragged = k_end < nk * 64;
-  // (without a branch: the transposing loads of the other operand are outstanding)
-  auto tail = [&](uint32_t v, int k, int t) { return ((int)ragged & (int)(t == nk - 1) & (int)(t * 64 + k >= k_end)) ? OUTSIDE : v; };
   const bool do_colsum = p.colsum != nullptr && tile_n == 0 && wn == 0;
   typename T::acc_t acc[2][T::TM][T::TN];
   float csum[2][T::TM];
   pp_main_loop<T, false, true>(acc, smem_raw, nk, wm, wn, wave >= 4, lane,
-      [&](int h, int t, unsigned char* dst) {
-        const rsrc_t r = make_rsrc(A, t < nk ? a_bytes : 0u);
-        const uint32_t off = t < nk ? (uint32_t)t * 128u * (uint32_t)lda : 0u;
+      [&](auto hc, int t, unsigned char* dst) {
+        constexpr int h = decltype(hc)::value;
 #pragma unroll
-        for (int j = 0; j < T::LA; ++j)
-          async_copy_16B_buf(r, tail(va[h][j], pp_mc_piece_k<T::BM / 2>(wave * T::LA + j, lane), t), off, dst + (wave * T::LA + j) * 1024);
+        for (int j = 0; j < T::LA; ++j) async_copy_16B_buf(ra, va[h][j] + (uint32_t)t * step_a, 0, dst + (wave * T::LA + j) * 1024);
       },
       [&](auto hc, int t, unsigned char* dst) {
-        constexpr int h = decltype(hc)::value, L = h ? T::LB1 : T::LB0, COLS = h ? T::BN1 : T::BN0;
-        const rsrc_t r = make_rsrc(B, t < nk ? b_bytes : 0u);
-        const uint32_t off = t < nk ? (uint32_t)t * 128u * (uint32_t)ldb : 0u;
+        constexpr int h = decltype(hc)::value, L = h ? T::LB1 : T::LB0;
 #pragma unroll
-        for (int j = 0; j < L; ++j)
-          async_copy_16B_buf(r, tail(h ? vb1[h ? j : 0] : vb0[h ? 0 : j], pp_mc_piece_k<COLS>(wave * L + j, lane), t), off, dst + (wave * L + j) * 1024);
+        for (int j = 0; j < L; ++j) async_copy_16B_buf(rb, (h ? vb1[h ? j : 0] : vb0[h ? 0 : j]) + (uint32_t)t * step_b, 0, dst + (wave * L + j) * 1024);
       }, do_colsum, csum);
   const DwProblem& e0 = grp.p[q];
   if (do_colsum) {
