@@ -78,6 +78,11 @@ __device__ __forceinline__ uint32_t pp_mc_offset(int col0, int lane) {
 // than the 128 cycles of matrix work beside them; 26 to 35 and 0 to 6 are left.  bf16 products of one tile a CU: 8192 x 640, K = 640 / 5120 12.3 -> 11.3 / 57.3
 // -> 54.3 us, 8192 x 1152, K = 1152 / 4608 24.4 -> 23.1 / 78.3 -> 73.2.  Not where workgroups walk over tiles (32768 x 1280, K = 320 40.7 -> 43.0 us, 8192^3 739 -> 721) nor
 // for FP8 (8192 x 4608, K = 1152 48.7 -> 52.2), whose scalar registers run out, and not where the second set of addresses spills (512x128 convolution).
+template <class T, class CopyA, class CopyB>
+__device__ __forceinline__ void pp_first_k_tile(unsigned char* smem, CopyA copy_a, CopyB copy_b) {
+  copy_b(std::integral_constant<int, 0>(), 0, smem + T::OB0); copy_a(std::integral_constant<int, 0>(), 0, smem);
+  copy_b(std::integral_constant<int, 1>(), 0, smem + T::OB1); copy_a(std::integral_constant<int, 1>(), 0, smem + T::A_HALF);
+}
 template <class T, bool FP8, bool MC, bool AHEAD = false, bool PAIRS = true, class CopyA, class CopyB>
 __device__ __forceinline__ void pp_main_loop(typename T::acc_t (&acc)[2][T::TM][T::TN], unsigned char* smem, int nk, int wm, int wn, bool trailing,
                                              int lane, CopyA copy_a, CopyB copy_b, bool colsum, float (&csum)[2][T::TM]) {
