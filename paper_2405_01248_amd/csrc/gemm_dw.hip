@@ -25,28 +25,35 @@ struct DwProblem {
   uint32_t a_bytes, b_bytes;
   int tiles_m, tiles_n, group_m;
   int first;                         // first workgroup of the problem
+  int run_first, run;                // the run of problems of equally long workgroups that it is part of: first workgroup and number of them
   int splits, kt_per_split;
   int accumulate;
 };
 struct DwGroup { DwProblem p[DW_GROUP_MAX]; int n, total; };
 
-// What bounds it: fetching operands.  A CU takes 152 B per ns from the L2, 85 past it and 51 from memory, however many k-tiles are on their way and whatever
-// the rows' stride, and a k-tile of 256x128 is 48 KB beside 0.53 us of matrix work; the transposing LDS reads (208 B per clock and CU, the plain ones 250)
-// come to half of that.  Hence the tile with the least operand bytes per FLOP wherever the outputs are large enough.  A launch reads 972 MB past the L2s
-// for 302 MB of operands (a DiT block 32 x 256 x 1152, 263 us, 4.1 TB/s with what it writes) or 862 for 254 (a U-Net block 8 x 1024 x 640, 156 us, 5.7 TB/s).
-// Tiles dealt to the XCDs nearer to square, or their k-tiles taken in turned order inside windows of 2, 4 or 8, gave within 0.5 % either way.
+// What bounds it: instruction issue and LDS beside the matrix work, and the latency of the operands.  Without its copies the launch of a U-Net block
+// 8 x 1024 x 640 takes 118 us of what was 143, without its matrix work 139, with every copy an L2 hit 130.  Two things bring the latter about, 143 -> 130 us
+// (a block of 8 x 4096 x 320 181 -> 170; a DiT block of 32 x 256 x 1152 is not faster, its 4 x 256 one 1 %):
+// - an XCD's workgroups are tiles of one region of one problem, or of two, whatever the problems' number: 418 MB past the L2s for 254 MB of operands
+//   where a share of every problem to every XCD read 862;
+// - tiles that share operands run in step, so that each k-tile would come from memory for all of them at once.  Every other tile takes its k-tiles in
+//   pairs turned round: while half of the tiles have the first of a pair fetched, the other half has the second, and both find the other one in the L2.
+//   Windows of four and eight k-tiles gave 131 and 130 us.
 template <class T>
 __global__ void __launch_bounds__(512, 2) gemm_dw_group_kernel(const DwGroup grp) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave / T::WGN, wn = wave % T::WGN;
-  // The hardware deals workgroups round-robin to the 8 XCDs.  Inside each problem every XCD takes a contiguous range of
-  // (split, tile) -- neighbours share operand panels in its L2 -- and every XCD gets its share of each problem, so that the
-  // XCDs' queues are equally long whatever the problems' contractions are.
-  int q = 0;
-  while (q + 1 < grp.n && (int)blockIdx.x >= grp.p[q + 1].first) ++q;
+  // The hardware deals workgroups round-robin to the 8 XCDs.  Over a run of problems of equally long workgroups every XCD takes a contiguous
+  // range of (problem, split, tile), so that its tiles share operand panels in its L2 and the XCDs' queues are equally long.
+  auto problem_of = [&](int id) {
+    int q = 0;
+    while (q + 1 < grp.n && id >= grp.p[q + 1].first) ++q;
+    return q;
+  };
+  const int q0 = problem_of(blockIdx.x), place = grp.p[q0].run_first + xcd_contiguous_id(blockIdx.x - grp.p[q0].run_first, grp.p[q0].run), q = problem_of(place);
   const DwProblem& p = grp.p[q];
-  const int tiles = p.tiles_m * p.tiles_n, id = xcd_contiguous_id(blockIdx.x - p.first, tiles * p.splits), split = id / tiles;
+  const int tiles = p.tiles_m * p.tiles_n, id = place - p.first, split = id / tiles;
   int tile_m, tile_n;
   tile_of_id(id % tiles, p.tiles_m, p.tiles_n, p.group_m, tile_m, tile_n);
   const int m0 = tile_m * T::BM, n0 = tile_n * T::BN, M = p.M, N = p.N, lda = p.lda, ldb = p.ldb;
@@ -78,16 +85,18 @@ __global__ void __launch_bounds__(512, 2) gemm_dw_group_kernel(const DwGroup grp
   const bool do_colsum = p.colsum != nullptr && tile_n == 0 && wn == 0;
   typename T::acc_t acc[2][T::TM][T::TN];
   float csum[2][T::TM];
+  const uint32_t turn = (uint32_t)(tile_m + tile_n) & 1u, pairs = (uint32_t)nk & ~1u;      // (an odd last k-tile stays)
+  auto k_of = [&](int t) { return (uint32_t)t < pairs ? (uint32_t)t ^ turn : (uint32_t)t; };
   pp_main_loop<T, false, true>(acc, smem_raw, nk, wm, wn, wave >= 4, lane,
       [&](auto hc, int t, unsigned char* dst) {
         constexpr int h = decltype(hc)::value;
 #pragma unroll
-        for (int j = 0; j < T::LA; ++j) async_copy_16B_buf(ra, va[h][j] + (uint32_t)t * step_a, 0, dst + (wave * T::LA + j) * 1024);
+        for (int j = 0; j < T::LA; ++j) async_copy_16B_buf(ra, va[h][j] + k_of(t) * step_a, 0, dst + (wave * T::LA + j) * 1024);
       },
       [&](auto hc, int t, unsigned char* dst) {
         constexpr int h = decltype(hc)::value, L = h ? T::LB1 : T::LB0;
 #pragma unroll
-        for (int j = 0; j < L; ++j) async_copy_16B_buf(rb, (h ? vb1[h ? j : 0] : vb0[h ? 0 : j]) + (uint32_t)t * step_b, 0, dst + (wave * L + j) * 1024);
+        for (int j = 0; j < L; ++j) async_copy_16B_buf(rb, (h ? vb1[h ? j : 0] : vb0[h ? 0 : j]) + k_of(t) * step_b, 0, dst + (wave * L + j) * 1024);
       }, do_colsum, csum);
   const DwProblem& e0 = grp.p[q];
   if (do_colsum) {
@@ -158,6 +167,12 @@ static int dw_parts(const GemmArgs* a, int n, const DwGroupPlan& plan, DwPart* o
   for (int i = 0; i < n; ++i)
     if ((a[i].K + 63) / 64 * 2 < kt_max) add(i, 0, a[i].M, 1);
   return cnt;
+}
+// Rows of tiles that the order of a problem's tiles walks down before it goes to the next column: as many as make the 32 tiles in a row that an XCD
+// works on together nearly square, in groups of equal height.
+static int dw_group_rows(int tiles_m) {
+  const int groups = std::max(1, (tiles_m + 2) / 5);
+  return (tiles_m + groups - 1) / groups;
 }
 static size_t dw_part_ws_bytes(const GemmArgs& a, const DwPart& d) {
   return d.splits > 1 ? ((size_t)d.splits * ((size_t)d.rows * a.N + d.rows) * sizeof(float) + 255) / 256 * 256 : 0;
@@ -265,7 +280,7 @@ int launch_gemm_dw_group(const GemmArgs* a, int n, const DwGroupPlan& plan, hipS
     p.a_bytes = (uint32_t)operand_extent_bytes(b.K, p.M, b.lda);
     p.b_bytes = (uint32_t)operand_extent_bytes(b.K, b.N, b.ldb);
     p.tiles_m = (p.M + t.bm - 1) / t.bm; p.tiles_n = (p.N + t.bn - 1) / t.bn;
-    p.group_m = std::min(p.tiles_m, 8);
+    p.group_m = dw_group_rows(p.tiles_m);
     p.splits = parts[i].splits; p.kt_per_split = parts[i].kt_per_split;
     p.first = g.total;
     g.total += p.tiles_m * p.tiles_n * p.splits;
@@ -282,6 +297,11 @@ int launch_gemm_dw_group(const GemmArgs* a, int n, const DwGroupPlan& plan, hipS
       if (p.colsum) add(p.colsum, p.partial + (size_t)p.splits * mn, p.M);
       red += 4.0 * (p.splits + 1.0) * mn;
     }
+    // a run: neighbours in launch order that differ in the length of their workgroups by less than one k-tile in eight
+    const bool same = i && 8 * std::abs(p.kt_per_split - g.p[i - 1].kt_per_split) < p.kt_per_split;
+    p.run_first = same ? g.p[i - 1].run_first : p.first;
+    for (int j = 0; j <= i; ++j)
+      if (g.p[j].run_first == p.run_first) g.p[j].run = g.total - p.run_first;
     flops += 2.0 * mn * p.K; bytes += 2.0 * p.K * ((double)p.M + p.N) + 4.0 * mn * (p.accumulate ? 2.0 : 1.0);
   }
   {

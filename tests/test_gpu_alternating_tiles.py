@@ -100,6 +100,15 @@ def test_weight_gradient_tiles(tile_cfg, accumulate):
         assert e <= TOL_F32OUT
 
 
+@pytest.mark.parametrize("tile_cfg", [22, 23, 24, 25])
+@pytest.mark.parametrize("K", [64, 66, 128, 130, 192, 255, 320, 1025])
+def test_weight_gradient_with_k_tiles_turned_round(tile_cfg, K):
+    # 3 x 3 tiles or more, every other one with its k-tiles in pairs turned round: one to five k-tiles, whole and ragged at either end of a pair, and parts
+    for M, N in [(520, 776), (776, 520)]:
+        e = _gemm_case("tn", M, N, K, tile_cfg, seed=M + K, bias=False, accumulate=False)
+        assert e <= TOL_F32OUT, (M, N, K, e)
+
+
 @pytest.mark.parametrize("M,N,K", [(4090, 4088, 256), (4100, 4616, 128), (2060, 1544, 384)])
 def test_fp8_tiles(M, N, K):
     # 256, 192 and 128 columns wide, ragged on both sides
