@@ -14,6 +14,7 @@
 #include "dp_errors.h"
 #include "dp_ktime.h"
 #include "dp_gemm_pp.h"
+#include "dp_gemm_ring.h"
 
 #include <algorithm>
 #include <atomic>
@@ -400,10 +401,10 @@ __global__ void __launch_bounds__(512, 2) conv3x3_pp_kernel(const ConvParams p, 
 
 // ------------------------------------------------------------------ small tiles
 // 64x64 and 128x128 tiles for layers with few output pixels (a partial batch of one sample in the deep layers: 32 tiles of 256x128 for 256
-// CUs, each walking all 72 k-tiles of a 4608-deep contraction, 61 us).  A plain ring of direct-to-LDS stages, one barrier
-// per k-tile; several workgroups per CU hide each other's latencies.  The order of the additions is that of the large tiles, so
+// CUs, each walking all 72 k-tiles of a 4608-deep contraction, 61 us).  The ring of dp_gemm_ring.h.  The order of the additions is that of the large tiles, so
 // the tile shape, which depends on the number of samples, changes no bit: same k order, same 32-row statistics bands.
 // Measured (512 -> 512 channels): 48 x 41 pixels 61 -> 20 us (64x64; 24 with the fragments read right before their use), 96 x 82 65 -> 43 us (128x128); 512 -> 8 head at 48 x 41 71 -> 20 us.
+// With ring_main_loop's constant stages and the tap looked at when it changes 21.5 -> 17.9 and 36.9 -> 32.3 us.  (A fourth buffer of 128x128 changes nothing.)
 template <int BM_, int BN_, int WGM_, int WGN_, int STAGES_>
 struct ConvSmallTile {
   static constexpr int BM = BM_, BN = BN_, WGM = WGM_, WGN = WGN_, STAGES = STAGES_, NW = WGM * WGN, WM = BM / WGM, WN = BN / WGN, TN = WN / 32;
@@ -434,67 +435,29 @@ __global__ void __launch_bounds__(T::NW * 64) conv3x3_small_kernel(const ConvPar
     const int r = pp_piece_row(wave * LB + j, lane), c = pp_piece_chunk(r, lane);
     vb[j] = 2u * ((uint32_t)min(n0 + r, p.N - 1) * (uint32_t)p.K + (uint32_t)c * 8u);
   }
-  int it_tap = 0, it_c0 = 0;
-  auto issue = [&](int t) {
-    unsigned char* st = smem_raw + t % T::STAGES * T::STAGE;
-    const rsrc_t rx = make_rsrc(p.x, t < nk ? x_bytes : 0u), rw = make_rsrc(p.w, t < nk ? w_bytes : 0u);
-    if (it_c0 == 0) {
-      const int u = (it_tap * 11) >> 5, v = it_tap - 3 * u, off = 2 * ((u - 1) * p.W + (v - 1)) * p.Cin;
-#pragma unroll
-      for (int j = 0; j < LA; ++j) va[j] = (a_taps[j] >> it_tap) & 1u ? (uint32_t)(a_base[j] + off) : OUTSIDE;
-    }
-    const uint32_t oa = 2u * (uint32_t)it_c0, ob = t < nk ? (uint32_t)t * 128u : 0u;
-    it_c0 += 64;
-    if (it_c0 == p.Cin) { it_c0 = 0; ++it_tap; }
-#pragma unroll
-    for (int j = 0; j < LA; ++j) async_copy_16B_buf(rx, va[j], oa, st + (wave * LA + j) * 1024);
-#pragma unroll
-    for (int j = 0; j < LB; ++j) async_copy_16B_buf(rw, vb[j], ob, st + T::A_BYTES + (wave * LB + j) * 1024);
-  };
+  const int tap_bytes = 2 * p.Cin;
+  int it_tap = -1, it_off = tap_bytes;      // (no pixel has a tenth tap: past the last k-tile nothing is read)
+  const rsrc_t rx = make_rsrc(p.x, x_bytes);
   f32x16 acc[T::TN];
 #pragma unroll
   for (int j = 0; j < T::TN; ++j)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
+  ring_main_loop<T::STAGES, T::STAGE, T::A_BYTES, LA + LB>(acc, smem_raw, nk, wm * 32, wn * T::WN, lane,
+      [&](int t, unsigned char* st) {
+        if (it_off == tap_bytes) {
+          it_off = 0; ++it_tap;
+          const int u = (it_tap * 11) >> 5, v = it_tap - 3 * u, off = 2 * ((u - 1) * p.W + (v - 1)) * p.Cin;
 #pragma unroll
-  for (int t = 0; t < T::STAGES - 1; ++t) issue(t);
-  // The fragments of k-tile t are read while the products of k-tile t - 1 run.
-  const int ra = wm * 32 + l32;
-  bf16x8 fa[2][4], fb[2][4][T::TN];
-  auto read = [&](int t, int set) {
-    const unsigned char* st = smem_raw + t % T::STAGES * T::STAGE;
+          for (int j = 0; j < LA; ++j) va[j] = (a_taps[j] >> it_tap) & 1u ? (uint32_t)(a_base[j] + off) : OUTSIDE;
+        }
+        const rsrc_t rw = make_rsrc(p.w, t < nk ? w_bytes : 0u);
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      fa[set][ks] = *reinterpret_cast<const bf16x8*>(st + ra * 128 + ((2 * ks + g) ^ pp_key(ra)) * 16);
+        for (int j = 0; j < LA; ++j) async_copy_16B_buf(rx, va[j], (uint32_t)it_off, st + (wave * LA + j) * 1024);
 #pragma unroll
-      for (int j = 0; j < T::TN; ++j) {
-        const int r = wn * T::WN + j * 32 + l32;
-        fb[set][ks][j] = *reinterpret_cast<const bf16x8*>(st + T::A_BYTES + r * 128 + ((2 * ks + g) ^ pp_key(r)) * 16);
-      }
-    }
-  };
-  auto multiply = [&](int set) {
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-      for (int j = 0; j < T::TN; ++j) acc[j] = mfma32(fa[set][ks], fb[set][ks][j], acc[j]);
-  };
-  auto step = [&](int t, int set) {
-    wait_vmcnt<(T::STAGES - 2) * (LA + LB)>();
-    wait_lgkmcnt0();               // this wave's reads of k-tile t - 1 are done
-    barrier_nofence();             // k-tile t is there for everybody, and nobody reads k-tile t - 1 any more
-    issue(t + T::STAGES - 1);
-    read(t, set);
-    if (t > 0) multiply(set ^ 1);
-  };
-#pragma unroll 1
-  for (int t = 0; t < nk; t += 2) {
-    step(t, 0);
-    if (t + 1 < nk) step(t + 1, 1);
-  }
-  if (nk & 1) multiply(0);
-  else multiply(1);
-  wait_vmcnt<0>();
+        for (int j = 0; j < LB; ++j) async_copy_16B_buf(rw, vb[j], (uint32_t)t * 128u, st + T::A_BYTES + (wave * LB + j) * 1024);
+        it_off += 128;
+      }, []() {});
   __syncthreads();
   float* Cw = reinterpret_cast<float*>(smem_raw) + wave * 32 * T::C_LD;
   float* stat = reinterpret_cast<float*>(smem_raw + T::EPI_BYTES);      // [band][sum | sum of squares][BN], past the slabs
@@ -739,15 +702,15 @@ int launch_conv3x3(const ConvArgs& a, hipStream_t s) {
     if (a.gn_partial && (Ho * Wo) % p.gn_block == 0 && ((uintptr_t)a.gn_partial % 16) == 0) { p.gn_partial = a.gn_partial; *a.gn_applied = 1; }
     // The tile with the least estimated time, rounds over the 256 CUs x (fixed part + k-tiles x time of one).  This choice may
     // depend on the number of samples: the shapes produce the same bits, statistics included.  The times of a k-tile are measured ones
-    // (us at 72 k-tiles: 256x256 130, 256x128 87, 128x128 48 with one workgroup per CU each; 64x64 20 with one, 32 with two).
+    // (us at 72 k-tiles: 256x256 125, 256x128 77, 128x128 41 with one workgroup per CU each; 64x64 17 with one, 29 with two).
     const bool small = p.gn_block == 64 || !p.gn_partial;
-    const struct { int bm, bn, at_once; float fixed, per_kt; } tiles[] = {{256, 256, 256, 6.0f, 1.75f}, {256, 128, 256, 5.0f, 1.14f}, {512, 64, 256, 6.0f, 1.90f},
-                                                                          {512, 128, 256, 6.0f, 2.10f}, {64, 64, 512, 5.0f, 0.38f}, {128, 128, 256, 5.0f, 0.58f}};
+    const struct { int bm, bn, at_once; float fixed, per_kt; } tiles[] = {{256, 256, 256, 6.0f, 1.66f}, {256, 128, 256, 5.0f, 1.00f}, {512, 64, 256, 6.0f, 1.90f},
+                                                                          {512, 128, 256, 6.0f, 2.10f}, {64, 64, 512, 5.0f, 0.33f}, {128, 128, 256, 5.0f, 0.50f}};
     int best = 0;
     float best_us = 0.f;
     for (int i = 0; i < (small ? 6 : 4); ++i) {
       const long n = ((M + tiles[i].bm - 1) / tiles[i].bm) * ((a.Cout + tiles[i].bn - 1) / tiles[i].bn);
-      const float per_kt = i == 4 && n <= 256 ? 0.21f : tiles[i].per_kt;        // two of the smallest tiles on a CU slow each other down
+      const float per_kt = i == 4 && n <= 256 ? 0.17f : tiles[i].per_kt;        // two of the smallest tiles on a CU slow each other down
       const float us = (float)((n + tiles[i].at_once - 1) / tiles[i].at_once) * (tiles[i].fixed + (float)(p.K / 64) * per_kt);
       if (i == 0 || us < best_us) { best = i; best_us = us; }
     }

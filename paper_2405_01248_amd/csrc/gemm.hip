@@ -15,6 +15,7 @@
 #include "dp_ktime.h"
 #include "dp_gemm_epilogue.h"
 #include "dp_gemm_pp.h"
+#include "dp_gemm_ring.h"
 #include "dp_host.h"
 
 #include <algorithm>
@@ -281,10 +282,12 @@ gemm_bf16_dtl_kernel(const GemmBf16Params p) {
   constexpr int A_LOADS = S::A_BYTES / 1024 / NW, B_LOADS = S::B_BYTES / 1024 / NW, LOADS = A_LOADS + B_LOADS;
   static_assert(S::A_BYTES % (1024 * NW) == 0 && S::B_BYTES % (1024 * NW) == 0, "tile/waves mismatch");
   static_assert(KS % 2 == 0 && STAGES >= 2, "pipeline shape");
-  constexpr bool INTERLEAVE = BK == 64 && !FP8 && !A_MC && !B_MC;
+  // 64x64 tiles with four buffers on ring_main_loop (us, K = 768 / 3072 / 4608, 180 tiles: 7.1 -> 5.9 / 17.1 -> 12.4 / 23.8 -> 15.8; as dear with three, where two and more workgroups share
+  // a CU, 26.2 -> 28.2 with 612 tiles of K = 3072, and with 128x128 tiles, 8.6 -> 8.8 / 21.3 -> 21.2 / 29.9 -> 29.8 with 72)
+  constexpr bool INTERLEAVE = BK == 64 && !FP8 && !A_MC && !B_MC, RING = INTERLEAVE && BM == 64 && BN == 64 && STAGES == 4;
 
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 5, l32 = lane & 31;
   const int wm0 = (wave / WGN) * WM, wn0 = (wave % WGN) * WN;
   int tile_m, tile_n;
@@ -361,6 +364,46 @@ gemm_bf16_dtl_kernel(const GemmBf16Params p) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
+  // (from -0 on, the first segment's sums stay as they are, zeros of either sign included)
+  f32x16 total[SEG ? TM : 1][SEG ? TN : 1];
+#pragma unroll
+  for (int i = 0; i < (SEG ? TM : 0); ++i)
+#pragma unroll
+    for (int j = 0; j < (SEG ? TN : 0); ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) total[i][j][r] = -0.0f;
+  int seg_left = p.k_tiles_per_split;
+  // In place, by instructions that name the same register twice: as ordinary additions, both sets of sums are copied on the way round the loop in every
+  // k-tile, closed or not (32 instructions, 924 x 768, K = 3072 in eight segments 18.2 -> 12.6 us).  The compiler does not count wait states for
+  // inline assembly: 19 after the last product, and the ones behind for the next to take the zeros.
+  auto close_segment = [&]() {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < (SEG ? TM : 0); ++i)
+#pragma unroll
+      for (int j = 0; j < (SEG ? TN : 0); ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          float t = total[i][j][r], a = acc[i][j][r];
+          asm volatile("v_add_f32 %0, %0, %1\n\tv_mov_b32 %1, 0" : "+v"(t), "+v"(a));
+          total[i][j][r] = t; acc[i][j][r] = a;
+        }
+    asm volatile("s_nop 7" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    seg_left = p.k_tiles_per_split;
+  };
+  if constexpr (RING) {
+    ring_main_loop<STAGES, S::STAGE, S::A_BYTES, LOADS>(acc[0], smem_raw, nk, wm0, wn0, lane,
+        [&](int t, unsigned char* st) {
+          const rsrc_t a = make_rsrc(p.A, t < nk ? p.a_bytes : 0u), b = make_rsrc(p.B, t < nk ? p.b_bytes : 0u);
+#pragma unroll
+          for (int j = 0; j < A_LOADS; ++j) async_copy_16B_buf(a, va[j], (uint32_t)t * a_step, st + (wave * A_LOADS + j) * 1024);
+#pragma unroll
+          for (int j = 0; j < B_LOADS; ++j) async_copy_16B_buf(b, vb[j], (uint32_t)t * b_step, st + S::A_BYTES + (wave * B_LOADS + j) * 1024);
+        },
+        [&]() { if (SEG && --seg_left == 0) close_segment(); });
+  } else {
   // Fragment fetch of k-step ks_ of the k-tile in stage st_ into register set set_.
   bf16x8 fa[2][TM], fb[2][TN];
   i32x8 qa[2][FP8 ? TM : 1], qb[2][FP8 ? TN : 1];     // fp8: 32 bytes per lane and fragment
@@ -427,20 +470,6 @@ gemm_bf16_dtl_kernel(const GemmBf16Params p) {
   // all k-tiles but the last: no branch between the fragment reads and the MFMAs, so the waits for
   // LDS data stay exact (a merge of paths with different numbers of reads in flight would make the
   // compiler wait for all of them)
-  f32x16 total[SEG ? TM : 1][SEG ? TN : 1];
-  int seg_left = p.k_tiles_per_split, segments = 0;
-  auto close_segment = [&]() {
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          total[SEG ? i : 0][SEG ? j : 0][r] = segments ? total[SEG ? i : 0][SEG ? j : 0][r] + acc[i][j][r] : acc[i][j][r];
-          acc[i][j][r] = 0.f;
-        }
-    ++segments; seg_left = p.k_tiles_per_split;
-  };
   // buffers of k-tile t and its neighbours; the remainder by 3 is counted, which is 1 to 5 % faster, that by 4 is not, which is 1 to 7 % faster
   constexpr bool POW2 = (STAGES & (STAGES - 1)) == 0;
   int st = 0;
@@ -490,11 +519,12 @@ gemm_bf16_dtl_kernel(const GemmBf16Params p) {
       __builtin_amdgcn_sched_barrier(0);
     }
   }
+  }
 #undef DP_DTL_FRAGS
 #undef DP_DTL_MFMAS
 #undef DP_DTL_ISSUE_PART
   if (SEG) {
-    close_segment();
+    if (!RING || seg_left != p.k_tiles_per_split) close_segment();
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -935,11 +965,12 @@ static int choose_splits_epi(long tiles, int kt) {
   return s;
 }
 
-// 64x64 tiles: a k-tile costs 0.31 us while they have CUs to themselves, 0.39 us beside another, 0.5 us per 512 tiles where there are more
-// (32768 of them with two k-tiles each: 165 us; 256x256 tiles 90).
+// 64x64 tiles, up to 512 on the ring of four buffers: within 6 % over 12 to 340 tiles and contractions of 512 to 4608 (us, K = 768 / 4608: 48 tiles 5.3 / 14.5,
+// 256 5.9 / 16.1, 288 7.6 / 26.3).  More of them: 0.5 us a k-tile per 512 (32768 of them with two k-tiles each: 165 us; 256x256 tiles 90).
 static float tile64_us(long tiles, int kt, int z) {
   tiles *= z; kt = (kt + z - 1) / z;
-  const float some = 4.0f + (float)kt * (tiles <= 128 ? 0.31f : 0.39f);
+  if (tiles <= 256) return 3.4f + 0.002f * (float)tiles + (float)kt * (0.150f + 0.00008f * (float)tiles);
+  const float some = 3.9f + (float)kt * (0.26f + 0.0002f * (float)tiles);
   return tiles <= 512 ? some : std::max(some, 0.2f + (float)tiles / 512.0f * (1.57f + 0.5f * (float)kt));
 }
 // 128x128 tiles, eight waves.  heavy: an epilogue with an activation, which nothing overlaps.
@@ -1040,7 +1071,7 @@ int gemm_epi_split_rows(int N, int K) {
 //    (gemm_takes_stored_weight); else 256x256 direct-to-LDS tiles when they fill the CUs, or the register-staged kernel;
 //  - dW = dy^T x (both operands read through the transposing LDS load): register-staged 128x128 tiles,
 //    two workgroups per CU; 256x256 direct-to-LDS tiles for large M and N.
-static int choose_cfg(int M, int N, int K, bool a_mc, bool b_mc, bool dtl_ok, bool pp_ok, bool allow16 = true, bool may_split = false, bool ln = false, bool wave_ok = false, bool heavy = false, bool geglu_fwd = false, bool onto_f32 = false) {
+static int choose_cfg(int M, int N, int K, bool a_mc, bool b_mc, bool dtl_ok, bool pp_ok, bool allow16 = true, bool may_split = false, bool ln = false, bool wave_ok = false, bool heavy = false, bool geglu_fwd = false, bool onto_f32 = false, bool stored = false) {
   const long t256x256 = (long)((M + 255) / 256) * ((N + 255) / 256);
   const long t256x128 = (long)((M + 255) / 256) * ((N + 127) / 128);
   const bool dtl32 = dtl_ok && K % 32 == 0, dtl64 = dtl_ok && K % 64 == 0;
@@ -1085,7 +1116,7 @@ static int choose_cfg(int M, int N, int K, bool a_mc, bool b_mc, bool dtl_ok, bo
       }
       consider(c.idx, cost);
     }
-    if (dtl64 && !geglu_fwd) {
+    if (dtl64 && !geglu_fwd && !stored) {      // (not on weights as they are stored, for which those that share the contraction do as well)
       const long tiles = (long)((M + 63) / 64) * ((N + 63) / 64);
       const int z = may_split ? choose_splits_epi(tiles, K / 64) : 1;
       consider(15, tile64_us(tiles, K / 64, z) + (z > 1 ? reduce_us(M, N, z, ln) : outputs));
@@ -1575,16 +1606,16 @@ bool gemm_geglu_fwd_supported(const GemmArgs& a) {
 
 // The tile choice for a problem of `rows` rows.  Its estimates cost the host about a microsecond, so each thread remembers the last choices, by
 // everything they depend on.
-static int chosen_cfg(const GemmArgs& a, int rows, bool may_split) {
+static int chosen_cfg(const GemmArgs& a, int rows, bool may_split, bool stored = false) {
   struct Entry { int rows, n, k, flags, cfg; };
   constexpr int ENTRIES = 64;
   static thread_local Entry table[ENTRIES] = {};        // n = 0: empty
   const bool pp = !a.out_f32 && pp_kind(a) >= 0, any_order = a.choice_rows == 0, wave = any_order && pp && a.geglu != 1, dtl = dtl_addressable(a), heavy = heavy_epilogue(a), geglu_fwd = a.geglu == 1;
   const bool onto_f32 = any_order && a.residual && a.residual_f32;
-  const int flags = onto_f32 << 10 | geglu_fwd << 9 | heavy << 8 | (a.a_mc != 0) | (a.b_mc != 0) << 1 | dtl << 2 | pp << 3 | any_order << 4 | may_split << 5 | (a.ln_out != nullptr) << 6 | wave << 7;
+  const int flags = stored << 11 | onto_f32 << 10 | geglu_fwd << 9 | heavy << 8 | (a.a_mc != 0) | (a.b_mc != 0) << 1 | dtl << 2 | pp << 3 | any_order << 4 | may_split << 5 | (a.ln_out != nullptr) << 6 | wave << 7;
   Entry& e = table[((unsigned)rows * 0x9E3779B1u ^ (unsigned)a.N * 0x85EBCA77u ^ (unsigned)a.K * 0xC2B2AE3Du ^ (unsigned)flags * 0x27D4EB2Fu) >> 26];
   if (e.n == a.N && e.rows == rows && e.k == a.K && e.flags == flags) return e.cfg;
-  e = Entry{rows, a.N, a.K, flags, choose_cfg(rows, a.N, a.K, a.a_mc != 0, a.b_mc != 0, dtl, pp, any_order, may_split, a.ln_out != nullptr, wave, heavy, geglu_fwd, onto_f32)};
+  e = Entry{rows, a.N, a.K, flags, choose_cfg(rows, a.N, a.K, a.a_mc != 0, a.b_mc != 0, dtl, pp, any_order, may_split, a.ln_out != nullptr, wave, heavy, geglu_fwd, onto_f32, stored)};
   return e.cfg;
 }
 
@@ -1631,7 +1662,7 @@ bool gemm_takes_stored_weight(const GemmArgs& a) {
   g.b_mc = 1; g.ldb = a.N;
   if (!dtl_addressable(g)) return false;
   g.b_mc = 0; g.ldb = a.K;
-  const int cfg = chosen_cfg(g, a.M, a.splitk_ws != nullptr);
+  const int cfg = chosen_cfg(g, a.M, a.splitk_ws != nullptr, true);
   return cfg >= 25 && cfg <= 31;
 }
 
@@ -1673,7 +1704,7 @@ int launch_gemm(const GemmArgs& a, hipStream_t s) {
     if (!forced && a.b_mc && a.ldb == a.N && gemm_takes_stored_weight(a)) {
       GemmArgs g = a;
       g.b_mc = 0; g.ldb = a.K;
-      cfg = chosen_cfg(g, a.M, may_split);
+      cfg = chosen_cfg(g, a.M, may_split, true);
     }
     if (a.geglu == 1 && (cfg < 6 || cfg == 11 || cfg == 15 || cfg == 16 || cfg > 18)) return set_error(DP_EUNSUPPORTED, "gemm: the forced configuration does not have the fused GeGLU forward");
     // (11 and 12 name tiles that are there under 20 and 7 as well: callers may force them)

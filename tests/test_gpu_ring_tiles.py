@@ -12,3 +12,26 @@ def test_ring_of_buffers(tile_cfg, M, N):
     for K in (64, 128, 192, 256, 320, 384, 448, 576):
         e = _gemm_case("nt", M, N, K, tile_cfg, seed=M + K)
         assert e <= TOL_BF16, (K, e)
+
+
+@pytest.mark.parametrize("heads", [8, 12, 16])
+def test_segments_in_a_workgroup_and_parts_of_a_launch_agree(heads):
+    """Batch-invariant mode 1 on 1 sample (parts of their own), 5, 13 and 25 (the parts one after the other in a workgroup, 64x64 tiles and larger ones): the same bits."""
+    import numpy as np
+    import torch
+    import synth_inputs as si
+    from paper_2405_01248_amd.harness import DeviceEncoder
+    cfg = si.EncoderConfig(f"segments_{heads}", "bf16", 2, 64 * heads, heads, 64, 77, 512, 256 * heads, 25)
+    de = DeviceEncoder(cfg, si.make_encoder_inputs(cfg, seed=heads))
+    de.enc.set_batch_invariant(1)
+    de.ws = torch.empty(de.enc.workspace_bytes(de.gb), dtype=torch.uint8, device=de.device)
+    outs = []
+    for sizes in ((25,), (13, 12), (5,) * 5, (1,) * 25):
+        de.hidden.zero_()
+        off = 0
+        for n in sizes:
+            de.enc.fwd_partial(de.params, de.ids, de.hidden, de.gb, 0, cfg.n_layers + 2, off, n, de.ws)
+            off += n
+        torch.cuda.synchronize()
+        outs.append(de.output())
+    assert all(np.array_equal(o, outs[0]) for o in outs[1:])
