@@ -60,8 +60,12 @@ struct GemmArgs {
   // ln_out [M, N] holds LN(out; ln_gamma, ln_beta, ln_eps) in the storage dtype; otherwise it is set to 0 and
   // the caller runs the LayerNorm itself.
   const void* ln_gamma; const void* ln_beta; void* ln_out; float ln_eps; int* ln_applied;
+  // A = LN(norm_x; norm_gamma, norm_beta, norm_eps) in the storage dtype, formed from fp32 rows [M, K] inside the product instead of being read.  Only
+  // where gemm_norm_supported() says so; A names norm_x then.
+  const float* norm_x; const void* norm_gamma; const void* norm_beta; float norm_eps;
 };
 int launch_gemm(const GemmArgs& a, hipStream_t s);
+bool gemm_norm_supported(const GemmArgs& a);
 // `count` products y = x W^T (+ bias; storage-dtype or fp32 output, choice_rows < 0), operands and outputs at these distances in elements
 int launch_gemm_strided(const GemmArgs& a, int count, long stride_a, long stride_b, long stride_out, hipStream_t s);
 int launch_gemm_f32(const GemmArgs& a, hipStream_t s);      // the fp32 part of launch_gemm
@@ -244,7 +248,8 @@ int launch_cast_to_f32(int dtype, const void* in, float* out, size_t n, hipStrea
 int launch_cast_from_f32(int dtype, const float* in, void* out, size_t n, hipStream_t s);
 
 // x[row, :] = tok[ids[row], :] + pos[row % seq, :]
-int launch_embed(int dtype, const int32_t* ids, const void* tok, const void* pos, void* x, int rows, int seq,
+// x32: the rows go there in fp32, rounded to the storage dtype all the same, and not to x
+int launch_embed(int dtype, const int32_t* ids, const void* tok, const void* pos, void* x, float* x32, int rows, int seq,
                  int d, int vocab, hipStream_t s);
 
 // dst[c, r] = src[r, c] for up to kTransposeMax dense row-major 16-bit matrices in one launch.

@@ -769,7 +769,7 @@ int launch_quantize_fp8(const void* x, int ldx, void* q, int ldq, int rows, int 
 // and cannot be validated on the host); the sum is rounded once to the storage type.
 template <typename T>
 __global__ void __launch_bounds__(256) embed_kernel(const int32_t* __restrict__ ids, const T* __restrict__ tok, const T* __restrict__ pos,
-                                                    T* __restrict__ x, int rows, int seq, int d, int vocab) {
+                                                    T* __restrict__ x, float* __restrict__ x32, int rows, int seq, int d, int vocab) {
   constexpr int V = Vec<T>::N;
   const int lane = threadIdx.x & 63, row = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= rows) return;
@@ -782,16 +782,17 @@ __global__ void __launch_bounds__(256) embed_kernel(const int32_t* __restrict__ 
     load_vec<T>(t + col, a);
     load_vec<T>(p + col, b);
 #pragma unroll
-    for (int i = 0; i < V; ++i) a[i] += b[i];
-    store_vec<T>(x + (size_t)row * d + col, a);
+    for (int i = 0; i < V; ++i) a[i] = to_f<T>(from_f<T>(a[i] + b[i]));
+    if (x32) store_f32<V>(x32 + (size_t)row * d + col, a);
+    else store_vec<T>(x + (size_t)row * d + col, a);
   }
 }
-int launch_embed(int dtype, const int32_t* ids, const void* tok, const void* pos, void* x, int rows, int seq, int d, int vocab,
+int launch_embed(int dtype, const int32_t* ids, const void* tok, const void* pos, void* x, float* x32, int rows, int seq, int d, int vocab,
                  hipStream_t s) {
   if (int e = check_vec(dtype, d, "embed")) return e;
   if (rows <= 0 || seq <= 0 || vocab <= 0) return set_error(DP_EINVAL, "embed: bad sizes");
-  if (dtype == BF16) hipLaunchKernelGGL(embed_kernel<bf16>, dim3((rows + 3) / 4), dim3(256), 0, s, ids, (const bf16*)tok, (const bf16*)pos, (bf16*)x, rows, seq, d, vocab);
-  else hipLaunchKernelGGL(embed_kernel<float>, dim3((rows + 3) / 4), dim3(256), 0, s, ids, (const float*)tok, (const float*)pos, (float*)x, rows, seq, d, vocab);
+  if (dtype == BF16) hipLaunchKernelGGL(embed_kernel<bf16>, dim3((rows + 3) / 4), dim3(256), 0, s, ids, (const bf16*)tok, (const bf16*)pos, (bf16*)x, x32, rows, seq, d, vocab);
+  else hipLaunchKernelGGL(embed_kernel<float>, dim3((rows + 3) / 4), dim3(256), 0, s, ids, (const float*)tok, (const float*)pos, (float*)x, x32, rows, seq, d, vocab);
   return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "embed launch failed");
 }
 

@@ -38,6 +38,8 @@ struct GemmBf16Params {
   float* colsum; int colsum_stride; int colsum_acc;
   uint32_t a_bytes, b_bytes;   // extent of each operand in bytes (direct-to-LDS kernels address it with 32-bit offsets)
   EpiParams<bf16> epi;
+  // gemm_wave_kernel with NORM: the rows operand is LN(norm_x)
+  const float* norm_x; const bf16* norm_gamma; const bf16* norm_beta; float norm_eps;
 };
 
 // The direct-to-LDS kernels need both operands below 4 GiB.
@@ -699,9 +701,13 @@ struct WaveTile {
 // and 20.8; 1026 x 1280, K = 3840 18.1 and 19.9), which is less than the copy costs (4 N K bytes at 6.3 TB/s: 3.4 and 3.1) but for a few (1026 x 1024, K = 8192 31.0 and 39.3
 // beside 5.3; 2560 x 512, K = 4096 17.6 and 20.3 beside 1.3): a U-Net block 2 x 513 x 1280, two micro-batches of
 // three passes 1279 -> 1256, seven DiT blocks 4 x 256 x 1152 2163 -> 2150.
-template <class T, int KIND, bool B_MC = false>
+// NORM (32 rows, contractions up to 1024): the rows operand is the LayerNorm of fp32 rows, formed here instead of by a launch of its own, which on few rows is a
+// chain of two memory round trips and the gap between two launches.  Every wave normalises four rows while its first k-tile of weights is on its way; the rows lie
+// in LDS k-tile by k-tile, the waves' stages hold weights alone.  Every workgroup of a row of tiles does so again: 98 KB of rows from the L2 for 24 to 72 of them.
+template <class T, int KIND, bool B_MC = false, bool NORM = false>
 __global__ void __launch_bounds__(T::NW * 64, T::TM * T::TN == 1 ? 4 : (T::TM * T::TN <= 6 ? 2 : 1)) gemm_wave_kernel(const GemmBf16Params p) {
-  constexpr int NW = T::NW, TM = T::TM, TN = T::TN, LD = T::LD, ST = T::ST, COPIES = 4 * (TM + TN);
+  constexpr int NW = T::NW, TM = T::TM, TN = T::TN, LD = T::LD, ST = T::ST, COPIES = 4 * ((NORM ? 0 : TM) + TN), REGION = NORM ? T::BN * 128 : T::REGION, OFF_B = NORM ? 0 : T::A_BYTES;
+  static_assert(!NORM || (TM == 1 && !B_MC && ST == 1 && NW == 8), "normalised rows");
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 5, l32 = lane & 31;
   int tile_m, tile_n;
@@ -728,17 +734,17 @@ __global__ void __launch_bounds__(T::NW * 64, T::TM * T::TN == 1 ? 4 : (T::TM * 
   uint32_t ob[TN];
 #pragma unroll
   for (int j = 0; j < TN; ++j) ob[j] = B_MC ? pp_mc_offset<T::BN>(32 * j, lane) : 0;
-  unsigned char* own = smem_raw + wave * (ST * T::REGION);
+  unsigned char* own = smem_raw + (NORM ? p.K * (2 * T::BM) : 0) + wave * (ST * REGION);
   // copies of k-tile t (past the last one: issued all the same, since the waits count them, from outside the buffers)
   auto issue = [&](int t, int stage) {
     const bool in = t < kt_end;
     const rsrc_t ra = make_rsrc(p.A, in ? p.a_bytes : 0u), rb = make_rsrc(p.B, in ? p.b_bytes : 0u);
     const uint32_t off = in ? (uint32_t)t * 128u : 0u, off_b = B_MC ? off * (uint32_t)p.ldb : off;
-    unsigned char* dst = own + stage * T::REGION;
+    unsigned char* dst = own + stage * REGION;
 #pragma unroll
-    for (int j = 0; j < 4 * TM; ++j) async_copy_16B_buf(ra, va[j], off, dst + j * 1024);
+    for (int j = 0; j < (NORM ? 0 : 4 * TM); ++j) async_copy_16B_buf(ra, va[j], off, dst + j * 1024);
 #pragma unroll
-    for (int j = 0; j < 4 * TN; ++j) async_copy_16B_buf(rb, vb[j], off_b, dst + T::A_BYTES + j * 1024);
+    for (int j = 0; j < 4 * TN; ++j) async_copy_16B_buf(rb, vb[j], off_b, dst + OFF_B + j * 1024);
   };
   f32x16 acc[TM][TN];
 #pragma unroll
@@ -751,12 +757,13 @@ __global__ void __launch_bounds__(T::NW * 64, T::TM * T::TN == 1 ? 4 : (T::TM * 
     bf16x8 fa[4][TM], fb[4][TN];
     u32x2 raw[4][TN][2];
     wait_vmcnt<(ST - 1) * COPIES>();
-    const unsigned char* src = own + stage * T::REGION;
+    const unsigned char* src = own + stage * REGION;
+    const unsigned char* rows = NORM ? smem_raw + t * (T::BM * 128) : src;
     if constexpr (B_MC) {
       static_for<4>([&](auto ks) {
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
-          const uint32_t at = lds_address(src) + T::A_BYTES + ob[j];
+          const uint32_t at = lds_address(src) + OFF_B + ob[j];
           lds_read_tr_raw<ks * 32 * T::BN>(raw[ks][j][0], at);
           lds_read_tr_raw<(ks * 16 + 4) * 2 * T::BN>(raw[ks][j][1], at);
         }
@@ -767,12 +774,12 @@ __global__ void __launch_bounds__(T::NW * 64, T::TM * T::TN == 1 ? 4 : (T::TM * 
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
         const int r = 32 * i + l32;
-        fa[ks][i] = *reinterpret_cast<const bf16x8*>(src + r * 128 + ((2 * ks + g) ^ kc_key<64>(r)) * 16);
+        fa[ks][i] = *reinterpret_cast<const bf16x8*>(rows + r * 128 + ((2 * ks + g) ^ kc_key<64>(r)) * 16);
       }
 #pragma unroll
       for (int j = 0; j < (B_MC ? 0 : TN); ++j) {
         const int r = 32 * j + l32;
-        fb[ks][j] = *reinterpret_cast<const bf16x8*>(src + T::A_BYTES + r * 128 + ((2 * ks + g) ^ kc_key<64>(r)) * 16);
+        fb[ks][j] = *reinterpret_cast<const bf16x8*>(src + OFF_B + r * 128 + ((2 * ks + g) ^ kc_key<64>(r)) * 16);
       }
     }
     wait_lgkmcnt0();
@@ -795,8 +802,73 @@ __global__ void __launch_bounds__(T::NW * 64, T::TM * T::TN == 1 ? 4 : (T::TM * 
         for (int j = 0; j < TN; ++j) acc[i][j] = mfma32(fb[ks][j], fa[ks][i], acc[i][j]);      // transposed: a lane gets four neighbouring columns of a row
   };
   int t = kt_begin + wave;
+  if constexpr (NORM) {
+    constexpr int ROWS = T::BM / NW;
+    auto normalise = [&](auto ncc) {
+      constexpr int NC = decltype(ncc)::value;      // chunks of four columns a lane: K = 256 NC
+      f32x4 x[ROWS][NC];
+      bf16x4 ga[NC], be[NC];
 #pragma unroll
-  for (int i = 0; i < ST; ++i) issue(t + i * NW, i);
+      for (int i = 0; i < ROWS; ++i) {
+        const float* row = p.norm_x + (size_t)min(m0 + wave * ROWS + i, p.M - 1) * (256 * NC) + 4 * lane;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) x[i][c] = *reinterpret_cast<const f32x4*>(row + 256 * c);
+      }
+#pragma unroll
+      for (int c = 0; c < NC; ++c) { ga[c] = *reinterpret_cast<const bf16x4*>(p.norm_gamma + 256 * c + 4 * lane); be[c] = *reinterpret_cast<const bf16x4*>(p.norm_beta + 256 * c + 4 * lane); }
+      __builtin_amdgcn_sched_barrier(0);      // (the rows first: what is issued behind them need not be waited for with them)
+      issue(t, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      // as in ln_fwd_kernel
+      float mu[ROWS], rs[ROWS];
+#pragma unroll
+      for (int i = 0; i < ROWS; ++i) {
+        mu[i] = 0.f;
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+          for (int u = 0; u < 4; ++u) mu[i] += x[i][c][u];
+      }
+#pragma unroll
+      for (int i = 0; i < ROWS; ++i) mu[i] = wave_sum(mu[i]) * (1.0f / (256 * NC));
+#pragma unroll
+      for (int i = 0; i < ROWS; ++i) {
+        rs[i] = 0.f;
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            x[i][c][u] -= mu[i];
+            rs[i] = fmaf(x[i][c][u], x[i][c][u], rs[i]);
+          }
+      }
+#pragma unroll
+      for (int i = 0; i < ROWS; ++i) rs[i] = rsqrtf(fmaf(wave_sum(rs[i]), 1.0f / (256 * NC), p.norm_eps));
+      const int k_tile = lane / 16, chunk = lane % 16 / 2;      // of the first chunk; the next one lies four k-tiles on
+#pragma unroll
+      for (int i = 0; i < ROWS; ++i) {
+        const int r = wave * ROWS + i;
+        unsigned char* dst = smem_raw + k_tile * (T::BM * 128) + r * 128 + (chunk ^ kc_key<64>(r)) * 16 + lane % 2 * 8;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+          bf16x4 o;
+#pragma unroll
+          for (int u = 0; u < 4; ++u) o[u] = (bf16)fmaf(x[i][c][u] * rs[i], (float)ga[c][u], (float)be[c][u]);
+          *reinterpret_cast<bf16x4*>(dst + c * (4 * T::BM * 128)) = o;
+        }
+      }
+    };
+    switch (p.K / 256) {
+      case 1: normalise(std::integral_constant<int, 1>()); break;
+      case 2: normalise(std::integral_constant<int, 2>()); break;
+      case 3: normalise(std::integral_constant<int, 3>()); break;
+      default: normalise(std::integral_constant<int, 4>());
+    }
+    lds_barrier();
+  } else {
+#pragma unroll
+    for (int i = 0; i < ST; ++i) issue(t + i * NW, i);
+  }
 #pragma unroll 1
   for (; t < kt_end; t += ST * NW) {
 #pragma unroll
@@ -1536,6 +1608,24 @@ static int launch_wave_kind(const GemmArgs& a, GemmBf16Params& p, int splits, hi
   static std::atomic<bool> attr_set{false};
   return launch_split(a, p, gemm_wave_kernel<T, KIND, B_MC>, T::NW * 64, T::BYTES, attr_set, a.K / 64, splits, s);
 }
+// The rows operand normalised on the way in: 32-row tiles, unsplit.
+template <class T, int KIND>
+static int launch_wave_norm_kind(const GemmArgs& a, hipStream_t s) {
+  GemmBf16Params p = pp_params<T>(a);
+  p.norm_x = a.norm_x; p.norm_gamma = (const bf16*)a.norm_gamma; p.norm_beta = (const bf16*)a.norm_beta; p.norm_eps = a.norm_eps;
+  const size_t bytes = std::max((size_t)a.K * 2 * T::BM + (size_t)T::NW * T::BN * 128, (size_t)T::SLAB);
+  static std::atomic<bool> attr_set{false};
+  auto kern = gemm_wave_kernel<T, KIND, false, true>;
+  DP_TRY(set_lds_limit((const void*)kern, 160 * 1024, attr_set));
+  p.k_tiles_per_split = a.K / 64;
+  KScope ks(KK_GEMM_NT, 2.0 * a.M * a.N * a.K, gemm_tensor_bytes(a) + 2.0 * a.M * a.K, s, a.M, a.N, a.K);
+  hipLaunchKernelGGL(kern, dim3(p.tiles_m * p.tiles_n), dim3(T::NW * 64), bytes, s, p);
+  return hipGetLastError() == hipSuccess ? DP_OK : set_error(DP_EHIP, "gemm launch failed");
+}
+template <class T>
+static int launch_wave_norm(const GemmArgs& a, hipStream_t s) {
+  return a.act ? launch_wave_norm_kind<T, PE_ACT3>(a, s) : launch_wave_norm_kind<T, PE_PLAIN>(a, s);
+}
 // The kinds of a backward pass, which the tiles above have for weights as they are stored.
 static bool wave_stored_kind(int kind) { return kind == PE_PLAIN || kind == PE_DACT1 || kind == PE_DACT2 || kind == PE_GEGLU2; }
 template <class T>
@@ -1666,6 +1756,17 @@ bool gemm_takes_stored_weight(const GemmArgs& a) {
   return cfg >= 25 && cfg <= 31;
 }
 
+// Where the product runs on 32-row tiles, one a CU at most, whose launch and LayerNorm's are both mostly their beginning and end, and the rows fit LDS beside the
+// weights.  The rows cost a workgroup 2 us (vector instructions and their way through LDS), a LayerNorm launch 4 with the gap before the next: text encoder of 12 layers, one sample
+// of width 768 / 1024 / 512 340 -> 331 / 429 -> 414 / 330 -> 286 us; with two tiles a CU, 4 samples of width 1024, 558 -> 576.
+bool gemm_norm_supported(const GemmArgs& a) {
+  if (a.dtype != BF16 || a.a_mc || a.b_mc || a.out_f32 || a.choice_rows || a.force_cfg || a.K % 256 || a.K > 1024 || a.lda != a.K || a.N % 8 || !dtl_addressable(a)) return false;
+  const int kind = pp_kind(a);
+  if (kind != PE_PLAIN && kind != PE_ACT3) return false;
+  const int cfg = chosen_cfg(a, a.M, false), bn = 32 * (cfg - 28);
+  return cfg >= 29 && cfg <= 31 && (long)((a.M + 31) / 32) * ((a.N + bn - 1) / bn) <= kCUs;
+}
+
 int launch_gemm(const GemmArgs& a, hipStream_t s) {
   if (a.ln_applied) *a.ln_applied = 0;
   if (a.M <= 0 || a.N <= 0 || a.K <= 0) return set_error(DP_EINVAL, "gemm: non-positive size");
@@ -1695,6 +1796,15 @@ int launch_gemm(const GemmArgs& a, hipStream_t s) {
         if (a.N != a.geglu_inner || a.geglu_inner % 8 || !a.geglu_u || a.ld_geglu % 8 || a.ld_geglu < 2 * a.geglu_inner ||
             a.ldo < 2 * a.geglu_inner || a.pre_out || ((uintptr_t)a.geglu_u % 16))
           return set_error(DP_EINVAL, "gemm: bad fused GeGLU backward arguments");
+      }
+    }
+    if (a.norm_x) {
+      if (!gemm_norm_supported(a)) return set_error(DP_EUNSUPPORTED, "gemm: the rows of this problem cannot be normalised inside it");
+      if ((uintptr_t)a.norm_x % 16 || (uintptr_t)a.norm_gamma % 8 || (uintptr_t)a.norm_beta % 8) return set_error(DP_EALIGN, "gemm: misaligned LayerNorm operands");
+      switch (chosen_cfg(a, a.M, false)) {
+        case 29: return launch_wave_norm<WaveTile<8, 1, 1>>(a, s);
+        case 30: return launch_wave_norm<WaveTile<8, 1, 2>>(a, s);
+        default: return launch_wave_norm<WaveTile<8, 1, 3>>(a, s);
       }
     }
     const bool may_split = !a.out_f32 && a.splitk_ws && a.geglu != 1 && a.choice_rows >= 0;

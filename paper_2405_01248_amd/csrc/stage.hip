@@ -890,12 +890,21 @@ static int encoder_block(const dp_encoder& e, const void* const* P, float* x, in
   const bool fuse_ln = dt == DP_BF16;
   LnArgs ln; memset(&ln, 0, sizeof(ln));
   ln.dtype = dt; ln.rows = R; ln.d = d; ln.eps = e.d.ln_eps; ln.x_f32 = 1; ln.row_invariant = 1;
-  ln.x = x; ln.y = w.h; ln.gamma = P[E_LN1_G]; ln.beta = P[E_LN1_B];
-  if (!h_ready) DP_TRY(launch_ln_fwd(ln, st));
   const int choice_rows = e.batch_invariant == 1 ? seq : (e.batch_invariant == 2 ? -1 : 0);
-  GemmArgs g = gemm_fwd(dt, w.h, R, d, P[E_WQKV], 3 * d, P[E_BQKV], w.qkv);
-  g.splitk_ws = w.splitk; g.splitk_ws_bytes = w.splitk_bytes; g.choice_rows = choice_rows;
-  DP_TRY(launch_gemm(g, st));
+  // y = LN(x) W^T: the LayerNorm inside the product where that has it, else a launch of its own unless w.h is there
+  auto norm_proj = [&](GemmArgs g, const void* gamma, const void* beta, bool ready) -> int {
+    g.splitk_ws = w.splitk; g.splitk_ws_bytes = w.splitk_bytes; g.choice_rows = choice_rows;
+    if (!ready && gemm_norm_supported(g)) {
+      g.A = x; g.norm_x = x; g.norm_gamma = gamma; g.norm_beta = beta; g.norm_eps = e.d.ln_eps;
+    } else if (!ready) {
+      ln.x = x; ln.y = w.h; ln.gamma = gamma; ln.beta = beta;
+      DP_TRY(launch_ln_fwd(ln, st));
+    }
+    return launch_gemm(g, st);
+  };
+  DP_TRY(norm_proj(gemm_fwd(dt, w.h, R, d, P[E_WQKV], 3 * d, P[E_BQKV], w.qkv), P[E_LN1_G], P[E_LN1_B], h_ready));
+  GemmArgs fc1 = gemm_fwd(dt, w.h, R, d, P[E_FC1_W], ff, P[E_FC1_B], w.f), g;
+  fc1.act = 3; fc1.choice_rows = choice_rows;
   AttnArgs a; memset(&a, 0, sizeof(a));
   a.dtype = dt; a.B = n; a.H = e.d.n_heads; a.Nq = seq; a.Nk = seq; a.d_head = e.d.d_head; a.causal = e.d.causal;
   a.scale = 1.0f / sqrtf((float)e.d.d_head);
@@ -905,16 +914,9 @@ static int encoder_block(const dp_encoder& e, const void* const* P, float* x, in
   g = gemm_fwd(dt, w.a, R, d, P[E_WO], d, P[E_BO], x);
   g.splitk_ws = w.splitk; g.splitk_ws_bytes = w.splitk_bytes; g.choice_rows = choice_rows;
   g.residual = x; g.ld_res = d; g.residual_f32 = 1; g.out_fused_f32 = 1;
-  if (fuse_ln) { g.ln_gamma = P[E_LN2_G]; g.ln_beta = P[E_LN2_B]; g.ln_out = w.h; g.ln_eps = e.d.ln_eps; g.ln_applied = &ln_applied; }
+  if (fuse_ln && !gemm_norm_supported(fc1)) { g.ln_gamma = P[E_LN2_G]; g.ln_beta = P[E_LN2_B]; g.ln_out = w.h; g.ln_eps = e.d.ln_eps; g.ln_applied = &ln_applied; }
   DP_TRY(launch_gemm(g, st));
-  if (!ln_applied) {
-    ln.x = x; ln.y = w.h; ln.gamma = P[E_LN2_G]; ln.beta = P[E_LN2_B];
-    DP_TRY(launch_ln_fwd(ln, st));
-  }
-  g = gemm_fwd(dt, w.h, R, d, P[E_FC1_W], ff, P[E_FC1_B], w.f);
-  g.splitk_ws = w.splitk; g.splitk_ws_bytes = w.splitk_bytes; g.choice_rows = choice_rows;
-  g.act = 3;
-  DP_TRY(launch_gemm(g, st));
+  DP_TRY(norm_proj(fc1, P[E_LN2_G], P[E_LN2_B], ln_applied != 0));
   ln_applied = 0;
   g = gemm_fwd(dt, w.f, R, ff, P[E_FC2_W], d, P[E_FC2_B], x);
   g.splitk_ws = w.splitk; g.splitk_ws_bytes = w.splitk_bytes; g.choice_rows = choice_rows;
@@ -937,18 +939,18 @@ static int encoder_run(const dp_encoder& e, const void* const* params, const int
     return DP_OK;
   };
   int l = lb;
-  if (l == 0) {
+  const int tl_end = std::min(le, nl + 1);
+  const bool embed = l == 0, blocks = std::max(l, 1) < tl_end;
+  if (embed) {      // in fp32 at once where layers follow
     DP_TRY(mark(0));
-    DP_TRY(launch_embed(dt, ids + (size_t)off * seq, params[0], params[1], x, R, seq, d, e.d.vocab, st));
+    DP_TRY(launch_embed(dt, ids + (size_t)off * seq, params[0], params[1], x, blocks ? w.res : nullptr, R, seq, d, e.d.vocab, st));
     ++l;
   }
-  const int tl_end = std::min(le, nl + 1);
-  const bool blocks = l < tl_end;
   const bool final_ln = le == nl + 2;
   bool final_done = false;
   if (blocks) {
     DP_TRY(mark(l));
-    DP_TRY(launch_cast_to_f32(dt, x, w.res, (size_t)R * d, st));
+    if (!embed) DP_TRY(launch_cast_to_f32(dt, x, w.res, (size_t)R * d, st));
     // A layer's last reduction pass may also compute the LayerNorm that follows it (the next layer's first, or
     // the final one straight into `hidden`), also while layers are being timed one by one: the cost profile
     // then describes the launch sequence of an ordinary call, with a folded LayerNorm charged to the layer
