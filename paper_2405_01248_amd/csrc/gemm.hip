@@ -1037,11 +1037,12 @@ static int choose_splits_epi(long tiles, int kt) {
   return s;
 }
 
-// 64x64 tiles, up to 512 on the ring of four buffers: within 6 % over 12 to 340 tiles and contractions of 512 to 4608 (us, K = 768 / 4608: 48 tiles 5.3 / 14.5,
-// 256 5.9 / 16.1, 288 7.6 / 26.3).  More of them: 0.5 us a k-tile per 512 (32768 of them with two k-tiles each: 165 us; 256x256 tiles 90).
+// 64x64 tiles, up to 512 on the ring of four buffers (us, K = 768 / 4608: 48 tiles 5.3 / 14.5, 256 5.9 / 16.1, 288 7.6 / 26.3).  One a CU has 64 KB on its way, half of what
+// the waves that share a contraction have, and takes 0.185 us a k-tile and not 0.15 where the weights come from memory, as a frozen layer's do (two parts of 308 x 1024, K = 4096
+// 11.6 us in the text encoder, 8.9 by themselves).  More of them: 0.5 us a k-tile per 512 (32768 of them with two k-tiles each: 165 us; 256x256 tiles 90).
 static float tile64_us(long tiles, int kt, int z) {
   tiles *= z; kt = (kt + z - 1) / z;
-  if (tiles <= 256) return 3.4f + 0.002f * (float)tiles + (float)kt * (0.150f + 0.00008f * (float)tiles);
+  if (tiles <= 256) return 3.4f + 0.002f * (float)tiles + (float)kt * (0.185f + 0.00008f * (float)tiles);
   const float some = 3.9f + (float)kt * (0.26f + 0.0002f * (float)tiles);
   return tiles <= 512 ? some : std::max(some, 0.2f + (float)tiles / 512.0f * (1.57f + 0.5f * (float)kt));
 }
