@@ -61,11 +61,14 @@ struct GemmArgs {
   // the caller runs the LayerNorm itself.
   const void* ln_gamma; const void* ln_beta; void* ln_out; float ln_eps; int* ln_applied;
   // A = LN(norm_x; norm_gamma, norm_beta, norm_eps) in the storage dtype, formed from fp32 rows [M, K] inside the product instead of being read.  Only
-  // where gemm_norm_supported() says so; A names norm_x then.
+  // where gemm_norm_supported() (bf16) or gemm_f32_norm_supported() says so; A names norm_x then.  fp32: the normalised rows, their means and reciprocal deviations
+  // also go to norm_out, norm_mean and norm_rstd, and the rows themselves to norm_copy unless it is nullptr.
   const float* norm_x; const void* norm_gamma; const void* norm_beta; float norm_eps;
+  float* norm_out; float* norm_mean; float* norm_rstd; float* norm_copy;
 };
 int launch_gemm(const GemmArgs& a, hipStream_t s);
 bool gemm_norm_supported(const GemmArgs& a);
+bool gemm_f32_norm_supported(const GemmArgs& a);
 // `count` products y = x W^T (+ bias; storage-dtype or fp32 output, choice_rows < 0), operands and outputs at these distances in elements
 int launch_gemm_strided(const GemmArgs& a, int count, long stride_a, long stride_b, long stride_out, hipStream_t s);
 int launch_gemm_f32(const GemmArgs& a, hipStream_t s);      // the fp32 part of launch_gemm

@@ -445,9 +445,18 @@ static int unet_block_fwd(const dp_stage& s, const void* const* P, const float* 
   // self-attention
   ln.x = x; ln.y = u.h1; ln.gamma = P[U_LN1_G]; ln.beta = P[U_LN1_B]; ln.mean = u.mean1; ln.rstd = u.rstd1;
   if (x_storage) { ln.x = x_storage; ln.x_f32 = dt == F32; ln.x32_out = const_cast<float*>(x); }
-  DP_TRY(launch_ln_fwd(ln, st));
+  // the LayerNorm in front of a product: inside it, or as a launch of its own
+  auto normalise = [&](GemmArgs& g) -> int {
+    GemmArgs n = g;
+    n.A = ln.x; n.norm_x = (const float*)ln.x; n.norm_gamma = ln.gamma; n.norm_beta = ln.beta; n.norm_eps = ln.eps;
+    n.norm_out = (float*)ln.y; n.norm_mean = ln.mean; n.norm_rstd = ln.rstd; n.norm_copy = ln.x32_out;
+    if (!gemm_f32_norm_supported(n)) return launch_ln_fwd(ln, st);
+    g = n;
+    return DP_OK;
+  };
+  GemmArgs first[] = {gemm_fwd(dt, u.h1, T, d, P[U_WQKV], 3 * d, nullptr, u.qkv), gemm_fwd(dt, ctx, Tc, dc, P[U_WKV2], 2 * d, nullptr, u.kv2)};
+  DP_TRY(normalise(first[0]));
   ln.x_f32 = 1; ln.x32_out = nullptr;
-  const GemmArgs first[] = {gemm_fwd(dt, u.h1, T, d, P[U_WQKV], 3 * d, nullptr, u.qkv), gemm_fwd(dt, ctx, Tc, dc, P[U_WKV2], 2 * d, nullptr, u.kv2)};
   const bool both = dt == F32 && !kv_side;      // the context's projection depends on nothing before it
   if (both) DP_TRY(launch_gemm_f32_group(first, 2, st));
   else DP_TRY(proj(first[0]));
@@ -460,8 +469,9 @@ static int unet_block_fwd(const dp_stage& s, const void* const* P, const float* 
   DP_TRY(proj(g));
   // cross-attention
   ln.x = u.x1; ln.y = u.h2; ln.gamma = P[U_LN2_G]; ln.beta = P[U_LN2_B]; ln.mean = u.mean2; ln.rstd = u.rstd2;
-  DP_TRY(launch_ln_fwd(ln, st));
-  DP_TRY(proj(gemm_fwd(dt, u.h2, T, d, P[U_WQ2], d, nullptr, u.q2)));
+  g = gemm_fwd(dt, u.h2, T, d, P[U_WQ2], d, nullptr, u.q2);
+  DP_TRY(normalise(g));
+  DP_TRY(proj(g));
   if (kv_side) kv_side->wait(kv_batch);
   else if (!both) DP_TRY(proj(first[1]));
   a = attn_base(s);
@@ -473,15 +483,16 @@ static int unet_block_fwd(const dp_stage& s, const void* const* P, const float* 
   DP_TRY(proj(g));
   // GeGLU feed-forward
   ln.x = u.x2; ln.y = u.h3; ln.gamma = P[U_LN3_G]; ln.beta = P[U_LN3_B]; ln.mean = u.mean3; ln.rstd = u.rstd3;
-  DP_TRY(launch_ln_fwd(ln, st));
   {
     // u = h3 W1^T + b1 and g = value * gelu(gate) in one kernel where the GEMM supports it
     GemmArgs f = gemm_fwd(dt, u.h3, T, d, P[U_W1], 2 * inner, P[U_B1], u.g);
     f.ldo = inner; f.pre_out = u.u; f.ld_pre = 2 * inner; f.geglu = 1; f.geglu_inner = inner;
     const bool can_fuse = gemm_geglu_fwd_supported(f);
     if ((s.fuse & 1) && (can_fuse || gemm_f32_geglu_supported(f))) {
+      DP_TRY(normalise(f));
       DP_TRY(proj(f));
     } else {
+      DP_TRY(launch_ln_fwd(ln, st));
       GemmArgs v = gemm_fwd(dt, u.h3, T, d, P[U_W1], 2 * inner, P[U_B1], u.u);
       if (can_fuse) v.choice_rows = -1;      // the fused kernel's order of additions: switching the fusion off changes no bit
       DP_TRY(proj(v));
