@@ -376,7 +376,7 @@ gemm_bf16_dtl_kernel(const GemmBf16Params p) {
       for (int r = 0; r < 16; ++r) total[i][j][r] = -0.0f;
   int seg_left = p.k_tiles_per_split;
   // In place, by instructions that name the same register twice: as ordinary additions, both sets of sums are copied on the way round the loop in every
-  // k-tile, closed or not (32 instructions, 924 x 768, K = 3072 in eight segments 18.2 -> 12.6 us).  The compiler does not count wait states for
+  // k-tile, closed or not (32 instructions, 924 x 768, K = 3072 in eight segments 18.2 -> 14.5 us).  The compiler does not count wait states for
   // inline assembly: 19 after the last product, and the ones behind for the next to take the zeros.
   auto close_segment = [&]() {
     __builtin_amdgcn_sched_barrier(0);

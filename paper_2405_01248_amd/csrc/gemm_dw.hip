@@ -138,7 +138,10 @@ __global__ void __launch_bounds__(256) gemm_dw_reduce_kernel(const DwReduce r) {
 }
 
 // ------------------------------------------------------------------ host side
-struct DwTile { int bm, bn; float us; };        // us: time of a k-tile with the chip full
+// us: time of a k-tile with the chip full, as the plans weigh tiles against the reduction and partly filled rounds.  Since the copies lost their overhead and an XCD's tiles lie
+// together a k-tile takes 1.53, 0.86, 0.86 and 1.21; with these in their place the U-Net plans stay as they are and those of 7 x 32 x 256 x 1152 take smaller tiles
+// whose reduction costs what the tiles gain (26 -> 31 us a block).
+struct DwTile { int bm, bn; float us; };
 static const DwTile kDwTiles[] = {{256, 256, 1.63f}, {256, 128, 1.06f}, {128, 256, 1.06f}, {256, 192, 1.33f}};
 constexpr int kDwTileCount = 4;
 
