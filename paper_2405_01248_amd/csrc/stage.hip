@@ -492,9 +492,10 @@ static int unet_block_fwd(const dp_stage& s, const void* const* P, const float* 
       DP_TRY(normalise(f));
       DP_TRY(proj(f));
     } else {
-      DP_TRY(launch_ln_fwd(ln, st));
+      // switching the fusion off changes no bit: the LayerNorm goes where the fused kernel has it, which adds up a row in another order than a launch of its own
       GemmArgs v = gemm_fwd(dt, u.h3, T, d, P[U_W1], 2 * inner, P[U_B1], u.u);
-      if (can_fuse) v.choice_rows = -1;      // the fused kernel's order of additions: switching the fusion off changes no bit
+      if (can_fuse) v.choice_rows = -1;      // the fused kernel's order of additions
+      DP_TRY(normalise(v));
       DP_TRY(proj(v));
       DP_TRY(launch_geglu_fwd(dt, u.u, u.g, T, inner, st));
     }

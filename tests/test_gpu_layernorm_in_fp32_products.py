@@ -17,3 +17,20 @@ def test_layer_norm_inside_the_fp32_projections(heads, d_head, batch, tokens):
     cfg = si.StageConfig(f"norm_f32_{d}_{batch}x{tokens}", si.UNET, "f32", 2, batch, tokens, d, heads, d_head, 5, 24, 4 * d)
     ds, inp = _run(cfg, seed=d + tokens)
     _compare(cfg, ds.results(), _oracle_stage(cfg, inp))
+
+
+@pytest.mark.parametrize("heads,d_head", [(4, 32), (9, 16), (8, 32), (17, 16)])
+def test_switching_the_geglu_fusion_off_changes_no_bit(heads, d_head):
+    # the third LayerNorm stands before the fused product and before the plain one: both add up its rows in the same order, with four waves and with eight
+    import numpy as np
+    import torch
+    d = heads * d_head
+    cfg = si.StageConfig(f"norm_f32_unfused_{d}", si.UNET, "f32", 2, 1, 45, d, heads, d_head, 5, 24, 4 * d)
+    ds, _ = _run(cfg, seed=d)
+    fused = ds.results()
+    ds.stage.set_fusion(0)
+    ds.step()
+    torch.cuda.synchronize()
+    plain = ds.results()
+    assert np.array_equal(fused["y"], plain["y"]) and np.array_equal(fused["dx"], plain["dx"])
+    assert all(np.array_equal(fused["grads"][k], plain["grads"][k]) for k in plain["grads"])
