@@ -1040,11 +1040,21 @@ static int choose_splits_epi(long tiles, int kt) {
 // 64x64 tiles, up to 512 on the ring of four buffers (us, K = 768 / 4608: 48 tiles 5.3 / 14.5, 256 5.9 / 16.1, 288 7.6 / 26.3).  One a CU has 64 KB on its way, half of what
 // the waves that share a contraction have, and takes 0.185 us a k-tile and not 0.15 where the weights come from memory, as a frozen layer's do (two parts of 308 x 1024, K = 4096
 // 11.6 us in the text encoder, 8.9 by themselves).  More of them: 0.5 us a k-tile per 512 (32768 of them with two k-tiles each: 165 us; 256x256 tiles 90).
+static float tile64_many_us(long tiles, int kt) { return 0.2f + (float)tiles / 512.0f * (1.57f + 0.5f * (float)kt); }
 static float tile64_us(long tiles, int kt, int z) {
   tiles *= z; kt = (kt + z - 1) / z;
   if (tiles <= 256) return 3.4f + 0.002f * (float)tiles + (float)kt * (0.185f + 0.00008f * (float)tiles);
   const float some = 3.9f + (float)kt * (0.26f + 0.0002f * (float)tiles);
-  return tiles <= 512 ? some : std::max(some, 0.2f + (float)tiles / 512.0f * (1.57f + 0.5f * (float)kt));
+  return tiles <= 512 ? some : std::max(some, tile64_many_us(tiles, kt));
+}
+// The same where the tile decides in which order an output's products are added: the times of the loop before the ring.  With the ring's own times some products go
+// from waves that share the contraction to 64x64 tiles (616 x 1280, 616 x 2304, 308 x 3072, K = 768; 1232 x 1280, K = 1024), which moves everything behind them by
+// bf16 rounding and gains nothing (us, these times and the ring's: U-Net blocks 8 x 1024 x 640 1612 / 1610, 8 x 256 x 1280 1280 / 1279; text encoder of width 768 on 4 / 6 / 8 samples 466 /
+// 571 / 574 and 462 / 575 / 588, of width 512 on 6 / 8 384 / 439 and 377 / 424, of width 1024 on 4 / 6 / 8 564 / 644 / 772 and 561 / 640 / 774).
+static float tile64_choice_us(long tiles, int kt, int z) {
+  tiles *= z; kt = (kt + z - 1) / z;
+  const float some = 4.0f + (float)kt * (tiles <= 128 ? 0.31f : 0.39f);
+  return tiles <= 512 ? some : std::max(some, tile64_many_us(tiles, kt));
 }
 // 128x128 tiles, eight waves.  heavy: an epilogue with an activation, which nothing overlaps.
 static float tile128_us(long tiles, int kt, bool heavy) {
@@ -1144,7 +1154,7 @@ int gemm_epi_split_rows(int N, int K) {
 //    (gemm_takes_stored_weight); else 256x256 direct-to-LDS tiles when they fill the CUs, or the register-staged kernel;
 //  - dW = dy^T x (both operands read through the transposing LDS load): register-staged 128x128 tiles,
 //    two workgroups per CU; 256x256 direct-to-LDS tiles for large M and N.
-static int choose_cfg(int M, int N, int K, bool a_mc, bool b_mc, bool dtl_ok, bool pp_ok, bool allow16 = true, bool may_split = false, bool ln = false, bool wave_ok = false, bool heavy = false, bool geglu_fwd = false, bool onto_f32 = false, bool stored = false) {
+static int choose_cfg(int M, int N, int K, bool a_mc, bool b_mc, bool dtl_ok, bool pp_ok, bool allow16 = true, bool may_split = false, bool ln = false, bool wave_ok = false, bool heavy = false, bool geglu_fwd = false, bool onto_f32 = false) {
   const long t256x256 = (long)((M + 255) / 256) * ((N + 255) / 256);
   const long t256x128 = (long)((M + 255) / 256) * ((N + 127) / 128);
   const bool dtl32 = dtl_ok && K % 32 == 0, dtl64 = dtl_ok && K % 64 == 0;
@@ -1189,10 +1199,10 @@ static int choose_cfg(int M, int N, int K, bool a_mc, bool b_mc, bool dtl_ok, bo
       }
       consider(c.idx, cost);
     }
-    if (dtl64 && !geglu_fwd && !stored) {      // (not on weights as they are stored, for which those that share the contraction do as well)
+    if (dtl64 && !geglu_fwd) {
       const long tiles = (long)((M + 63) / 64) * ((N + 63) / 64);
       const int z = may_split ? choose_splits_epi(tiles, K / 64) : 1;
-      consider(15, tile64_us(tiles, K / 64, z) + (z > 1 ? reduce_us(M, N, z, ln) : outputs));
+      consider(15, tile64_choice_us(tiles, K / 64, z) + (z > 1 ? reduce_us(M, N, z, ln) : outputs));
     }
     if (dtl64 && wave_ok)
       for (int i = 0; i < (int)(sizeof(kWave) / sizeof(kWave[0])); ++i) {
@@ -1697,16 +1707,16 @@ bool gemm_geglu_fwd_supported(const GemmArgs& a) {
 
 // The tile choice for a problem of `rows` rows.  Its estimates cost the host about a microsecond, so each thread remembers the last choices, by
 // everything they depend on.
-static int chosen_cfg(const GemmArgs& a, int rows, bool may_split, bool stored = false) {
+static int chosen_cfg(const GemmArgs& a, int rows, bool may_split) {
   struct Entry { int rows, n, k, flags, cfg; };
   constexpr int ENTRIES = 64;
   static thread_local Entry table[ENTRIES] = {};        // n = 0: empty
   const bool pp = !a.out_f32 && pp_kind(a) >= 0, any_order = a.choice_rows == 0, wave = any_order && pp && a.geglu != 1, dtl = dtl_addressable(a), heavy = heavy_epilogue(a), geglu_fwd = a.geglu == 1;
   const bool onto_f32 = any_order && a.residual && a.residual_f32;
-  const int flags = stored << 11 | onto_f32 << 10 | geglu_fwd << 9 | heavy << 8 | (a.a_mc != 0) | (a.b_mc != 0) << 1 | dtl << 2 | pp << 3 | any_order << 4 | may_split << 5 | (a.ln_out != nullptr) << 6 | wave << 7;
+  const int flags = onto_f32 << 10 | geglu_fwd << 9 | heavy << 8 | (a.a_mc != 0) | (a.b_mc != 0) << 1 | dtl << 2 | pp << 3 | any_order << 4 | may_split << 5 | (a.ln_out != nullptr) << 6 | wave << 7;
   Entry& e = table[((unsigned)rows * 0x9E3779B1u ^ (unsigned)a.N * 0x85EBCA77u ^ (unsigned)a.K * 0xC2B2AE3Du ^ (unsigned)flags * 0x27D4EB2Fu) >> 26];
   if (e.n == a.N && e.rows == rows && e.k == a.K && e.flags == flags) return e.cfg;
-  e = Entry{rows, a.N, a.K, flags, choose_cfg(rows, a.N, a.K, a.a_mc != 0, a.b_mc != 0, dtl, pp, any_order, may_split, a.ln_out != nullptr, wave, heavy, geglu_fwd, onto_f32, stored)};
+  e = Entry{rows, a.N, a.K, flags, choose_cfg(rows, a.N, a.K, a.a_mc != 0, a.b_mc != 0, dtl, pp, any_order, may_split, a.ln_out != nullptr, wave, heavy, geglu_fwd, onto_f32)};
   return e.cfg;
 }
 
@@ -1753,7 +1763,7 @@ bool gemm_takes_stored_weight(const GemmArgs& a) {
   g.b_mc = 1; g.ldb = a.N;
   if (!dtl_addressable(g)) return false;
   g.b_mc = 0; g.ldb = a.K;
-  const int cfg = chosen_cfg(g, a.M, a.splitk_ws != nullptr, true);
+  const int cfg = chosen_cfg(g, a.M, a.splitk_ws != nullptr);
   return cfg >= 25 && cfg <= 31;
 }
 
@@ -1815,7 +1825,7 @@ int launch_gemm(const GemmArgs& a, hipStream_t s) {
     if (!forced && a.b_mc && a.ldb == a.N && gemm_takes_stored_weight(a)) {
       GemmArgs g = a;
       g.b_mc = 0; g.ldb = a.K;
-      cfg = chosen_cfg(g, a.M, may_split, true);
+      cfg = chosen_cfg(g, a.M, may_split);
     }
     if (a.geglu == 1 && (cfg < 6 || cfg == 11 || cfg == 15 || cfg == 16 || cfg > 18)) return set_error(DP_EUNSUPPORTED, "gemm: the forced configuration does not have the fused GeGLU forward");
     // (11 and 12 name tiles that are there under 20 and 7 as well: callers may force them)

@@ -35,3 +35,21 @@ def test_segments_in_a_workgroup_and_parts_of_a_launch_agree(heads):
         torch.cuda.synchronize()
         outs.append(de.output())
     assert all(np.array_equal(o, outs[0]) for o in outs[1:])
+
+
+@pytest.mark.parametrize("M,N,K", [(616, 1280, 768), (616, 2304, 768), (308, 3072, 768), (616, 3072, 768), (1232, 1280, 1024)])
+def test_products_of_a_few_hundred_rows_keep_their_order_of_additions(M, N, K):
+    """The context projection of a U-Net block and a text encoder's projections on 4 to 16 samples: partial sums of four waves, whatever the 64x64 ring takes for
+    them.  (The ring adds the k-tiles up in one sum.)"""
+    import torch
+    from paper_2405_01248_amd import binding as B
+    gen = torch.Generator(device="cuda").manual_seed(M + N)
+    a = torch.randn((M, K), generator=gen, device="cuda").bfloat16()
+    w = (torch.randn((N, K), generator=gen, device="cuda") * 0.05).bfloat16()
+    out = []
+    for tile_cfg in (0, 26, 16):
+        c = torch.zeros((M, N), dtype=torch.bfloat16, device="cuda")
+        B.op_gemm(B.DP_BF16, a, K, 0, w, K, 0, M, N, K, None, c, N, False, False, None, tile_cfg)
+        out.append(c)
+    torch.cuda.synchronize()
+    assert torch.equal(out[0], out[1]) and not torch.equal(out[0], out[2])
