@@ -819,7 +819,7 @@ __global__ void __launch_bounds__(T::NW * 64, T::TM * T::TN == 1 ? 4 : (T::TM * 
       __builtin_amdgcn_sched_barrier(0);      // (the rows first: what is issued behind them need not be waited for with them)
       issue(t, 0);
       __builtin_amdgcn_sched_barrier(0);
-      // as in ln_fwd_kernel
+      // the arithmetic of ln_fwd_kernel, which has 64 lanes a row for these widths in the encoder: the same bits
       float mu[ROWS], rs[ROWS];
 #pragma unroll
       for (int i = 0; i < ROWS; ++i) {
@@ -830,7 +830,7 @@ __global__ void __launch_bounds__(T::NW * 64, T::TM * T::TN == 1 ? 4 : (T::TM * 
           for (int u = 0; u < 4; ++u) mu[i] += x[i][c][u];
       }
 #pragma unroll
-      for (int i = 0; i < ROWS; ++i) mu[i] = wave_sum(mu[i]) * (1.0f / (256 * NC));
+      for (int i = 0; i < ROWS; ++i) mu[i] = wave_sum(mu[i]) / (256 * NC);
 #pragma unroll
       for (int i = 0; i < ROWS; ++i) {
         rs[i] = 0.f;
@@ -843,7 +843,7 @@ __global__ void __launch_bounds__(T::NW * 64, T::TM * T::TN == 1 ? 4 : (T::TM * 
           }
       }
 #pragma unroll
-      for (int i = 0; i < ROWS; ++i) rs[i] = rsqrtf(fmaf(wave_sum(rs[i]), 1.0f / (256 * NC), p.norm_eps));
+      for (int i = 0; i < ROWS; ++i) rs[i] = rsqrtf(wave_sum(rs[i]) / (256 * NC) + p.norm_eps);
       const int k_tile = lane / 16, chunk = lane % 16 / 2;      // of the first chunk; the next one lies four k-tiles on
 #pragma unroll
       for (int i = 0; i < ROWS; ++i) {
