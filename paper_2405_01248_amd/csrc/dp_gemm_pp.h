@@ -77,7 +77,9 @@ __device__ __forceinline__ uint32_t pp_mc_offset(int col0, int lane) {
 // wave issues an instruction every four cycles or so, and with 44 to 64 scalar and 15 to 23 vector ones a k-tile the slots of a 256x128 tile took longer
 // than the 128 cycles of matrix work beside them; 26 to 35 and 0 to 6 are left.  bf16 products of one tile a CU: 8192 x 640, K = 640 / 5120 12.3 -> 11.3 / 57.3
 // -> 54.3 us, 8192 x 1152, K = 1152 / 4608 24.4 -> 23.1 / 78.3 -> 73.2.  Not where workgroups walk over tiles (32768 x 1280, K = 320 40.7 -> 43.0 us, 8192^3 739 -> 721) nor
-// for FP8 (8192 x 4608, K = 1152 48.7 -> 52.2), whose scalar registers run out, and not where the second set of addresses spills (512x128 convolution).
+// for FP8 (8192 x 4608, K = 1152 48.7 -> 52.2), whose scalar registers run out, and not where the second set of addresses spills: the 512x128 convolution, and 256x256 tiles
+// of a contraction that is no multiple of 64, whose last k-tile is masked lane by lane (4096 x 4096, K = 72 / 432 / 1080 / 4104, us: 12.7 / 21.2 / 37.4 / 111.2, with
+// two k-tiles a round and 8 to 16 bytes of scratch a lane 13.0 / 21.6 / 37.7 / 110.4; fewer tiles than CUs, K = 1080: 25.7 and 24.5, where 256x128 tiles take 16.9).
 template <class T, class CopyA, class CopyB>
 __device__ __forceinline__ void pp_first_k_tile(unsigned char* smem, CopyA copy_a, CopyB copy_b) {
   copy_b(std::integral_constant<int, 0>(), 0, smem + T::OB0); copy_a(std::integral_constant<int, 0>(), 0, smem);
@@ -250,7 +252,7 @@ __device__ __forceinline__ void pp_main_loop(typename T::acc_t (&acc)[2][T::TM][
     wait_vmcnt<3 * LA + LB0 + LB1>();
     slot_end();
     multiply(1, H0, true, false);
-    fetch_b(other, H0);                 // past the last k-tile: zeros, not used
+    fetch_b(other, H0);                 // past the last k-tile: not used
     copy_b(H1, t + 2, here + T::OB1);
     wait_vmcnt<2 * LA + LB0 + 2 * LB1>();
     slot_end();

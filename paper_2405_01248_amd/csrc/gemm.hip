@@ -634,7 +634,7 @@ __device__ __forceinline__ void gemm_pp_body(const GemmBf16Params& p) {
   float csum[2][T::TM];
   set_tile(blockIdx.x);
   if constexpr (!WALK) {
-    pp_main_loop<T, FP8, false, false, !FP8>(acc, smem_raw, nk, wm, wn, wave >= 4, lane, copy_a, copy_b, false, csum);
+    pp_main_loop<T, FP8, false, false, !FP8 && !(KTAIL && T::BM == 256 && T::BN == 256)>(acc, smem_raw, nk, wm, wn, wave >= 4, lane, copy_a, copy_b, false, csum);
     pp_epilogue<T, KIND, 32>(acc, smem_raw, p.epi, m0, n0, wave, wm, wn, lane, []() {});
   } else {
     const int n_tiles = p.tiles_m * p.tiles_n;
