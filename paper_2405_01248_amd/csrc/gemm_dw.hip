@@ -138,11 +138,12 @@ __global__ void __launch_bounds__(256) gemm_dw_reduce_kernel(const DwReduce r) {
 }
 
 // ------------------------------------------------------------------ host side
-// us: time of a k-tile with the chip full, as the plans weigh tiles against the reduction and partly filled rounds.  Since the copies lost their overhead and an XCD's tiles lie
-// together a k-tile takes 1.53, 0.86, 0.86 and 1.21; with these in their place the U-Net plans stay as they are and those of 7 x 32 x 256 x 1152 take smaller tiles
-// whose reduction costs what the tiles gain (26 -> 31 us a block).
+// us: time of a k-tile with the chip full.  Over 33 blocks (U-Net of 256 to 1280 columns and 1026 to 32768 rows, DiT of 384 to 1152 and 300 to 12288), each plan within a quarter of
+// the least estimate timed, the one that is chosen takes 0.9 % more than the fastest on average and 7 % at most; with 1.63, 1.06, 1.06 and 1.33, the times before the copies lost
+// their overhead, 2.2 and 19 % (us: DiT 8192 x 768 126 -> 120, 12288 x 384 64.5 -> 60.6, 3000 x 432 37.9 -> 34.9; U-Net 8192 x 400 82.7 -> 76.8, 4096 x 256 32.5 -> 27.4; the
+// one that loses, DiT 10000 x 648, 135.6 -> 137.0).  The reduction at 5 TB/s and 6 us and the 5 us of a tile (dw_plan_us) are within 0.1 % of the best values there.
 struct DwTile { int bm, bn; float us; };
-static const DwTile kDwTiles[] = {{256, 256, 1.63f}, {256, 128, 1.06f}, {128, 256, 1.06f}, {256, 192, 1.33f}};
+static const DwTile kDwTiles[] = {{256, 256, 1.53f}, {256, 128, 0.86f}, {128, 256, 0.86f}, {256, 192, 1.21f}};
 constexpr int kDwTileCount = 4;
 
 // A problem, or a range of output rows of one, as it is launched.

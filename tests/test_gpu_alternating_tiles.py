@@ -269,3 +269,22 @@ def test_layer_norm_backward_with_an_infinite_gradient(dtype, tokens):
     torch.cuda.synchronize()
     g = ds.results()["grads"]["block0.ln3_b"]
     assert g[0] == np.inf and np.isfinite(g[1:]).all(), g[:4]
+
+
+@pytest.mark.parametrize("batch,heads,d_head,cut", [(32, 12, 64, False), (48, 6, 64, True)])
+def test_weight_gradients_are_cut_where_that_is_faster(batch, heads, d_head, cut):
+    # 8192 rows of 768: tiles of 256x128 in whole rounds 120 us, 256x256 ones in two parts 126; 12288 rows of 384 fill the chip only in parts
+    import torch
+    import synth_inputs as si
+    from paper_2405_01248_amd import binding as B
+    from paper_2405_01248_amd.harness import DeviceStage
+    d = heads * d_head
+    cfg = si.StageConfig(f"dw_plan_{d}", si.DIT, "bf16", 1, batch, 256, d, heads, d_head, 0, 0, 4 * d, 1e-6, 1)
+    ds = DeviceStage(cfg, si.make_stage_inputs(cfg, seed=0))
+    ds.step()
+    B.ktime_begin(256)
+    ds.step()
+    launches = [(r["kind"], r["m"], r["n"]) for r in B.ktime_end(256)]
+    torch.cuda.synchronize()
+    assert sum(k == "gemm_tn" for k, _, _ in launches) == 1
+    assert (("reduce", d, 4 * d) in launches) == cut, launches
