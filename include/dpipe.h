@@ -129,10 +129,10 @@ int dp_encoder_param_shape(const dp_encoder* enc, int idx, int64_t shape[2], con
  * sizes, outputs concatenated) needs if the concatenation has to equal the full-batch result bit for bit.
  *   mode 1: the parts every projection's contraction is cut into are chosen for one sample's rows instead of the
  *           slice's; the tile, and whether the parts run side by side or one after the other in a workgroup, follow the
- *           slice, since neither changes a bit.  Against mode 0 (12 layers of width 768) 14 % slower on 1 sample, 9 %
- *           on 4, 5 % on 16, 10 % on 64; larger workspace.
+ *           slice, since neither changes a bit.  Against mode 0 (12 layers of width 768) 15 % slower on 1 sample, 5 %
+ *           on 4, 4 % on 16, 10 % on 64; larger workspace.
  *   mode 2: no split-K, and only tiles built on the 32x32x16 matrix instruction (their shape does not change the
- *           order in which an output element's products are added).  39 % slower on 1 sample, 20 % on 4, no slower on 16, 3 % on 64.
+ *           order in which an output element's products are added).  52 % slower on 1 sample, 27 % on 4, 1 % on 16, 6 % on 64.
  * Set the mode before asking for the workspace size; any other value is DP_EINVAL. */
 int dp_encoder_set_batch_invariant(dp_encoder* enc, int mode);
 /* Workspace bytes for a call on at most max_samples samples (in the encoder's current mode); never less for more samples. */

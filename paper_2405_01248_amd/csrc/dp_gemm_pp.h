@@ -67,9 +67,15 @@ __device__ __forceinline__ uint32_t pp_mc_offset(int col0, int lane) {
   const int b = lane >> 4, j = lane & 15, k = 8 * (b >> 1) + (j >> 2), c = col0 / 8 + 2 * (b & 1) + ((j & 3) >> 1);
   return (uint32_t)(k * COLS + pp_mc_swz<COLS>(c, k) * 8 + 4 * (j & 1)) * 2u;
 }
+// The copies of k-tile 0, which may be issued before the loop's own (AHEAD).
+template <class T, class CopyA, class CopyB>
+__device__ __forceinline__ void pp_first_k_tile(unsigned char* smem, CopyA copy_a, CopyB copy_b) {
+  copy_b(std::integral_constant<int, 0>(), 0, smem + T::OB0); copy_a(std::integral_constant<int, 0>(), 0, smem);
+  copy_b(std::integral_constant<int, 1>(), 0, smem + T::OB1); copy_a(std::integral_constant<int, 1>(), 0, smem + T::A_HALF);
+}
 // copy_a(half, t, dst) / copy_b(half, t, dst): issue this wave's LA / LB0, LB1 copies of a half of k-tile t to dst (the
-// half's first byte in LDS).  t may be >= nk: then the copies have to be issued all the same (the waits count them), from
-// outside the buffers, so that they move nothing.
+// half's first byte in LDS).  t may be nk or nk + 1: then the copies have to be issued all the same (the waits count them), from
+// outside the buffers, so that they move nothing (or from anywhere inside them: what they bring is not multiplied).
 // MC: both operands have the contraction strided.  colsum (MC only): a wave-uniform flag; csum[half][i] then receives
 // the sum over the contraction of row i of the wave's part of A (this lane's k-slots; lanes l and l + 32 hold the two halves).
 // AHEAD: the copies of k-tile 0 (pp_first_k_tile) are on their way already.
@@ -80,11 +86,6 @@ __device__ __forceinline__ uint32_t pp_mc_offset(int col0, int lane) {
 // for FP8 (8192 x 4608, K = 1152 48.7 -> 52.2), whose scalar registers run out, and not where the second set of addresses spills: the 512x128 convolution, and 256x256 tiles
 // of a contraction that is no multiple of 64, whose last k-tile is masked lane by lane (4096 x 4096, K = 72 / 432 / 1080 / 4104, us: 12.7 / 21.2 / 37.4 / 111.2, with
 // two k-tiles a round and 8 to 16 bytes of scratch a lane 13.0 / 21.6 / 37.7 / 110.4; fewer tiles than CUs, K = 1080: 25.7 and 24.5, where 256x128 tiles take 16.9).
-template <class T, class CopyA, class CopyB>
-__device__ __forceinline__ void pp_first_k_tile(unsigned char* smem, CopyA copy_a, CopyB copy_b) {
-  copy_b(std::integral_constant<int, 0>(), 0, smem + T::OB0); copy_a(std::integral_constant<int, 0>(), 0, smem);
-  copy_b(std::integral_constant<int, 1>(), 0, smem + T::OB1); copy_a(std::integral_constant<int, 1>(), 0, smem + T::A_HALF);
-}
 template <class T, bool FP8, bool MC, bool AHEAD = false, bool PAIRS = true, class CopyA, class CopyB>
 __device__ __forceinline__ void pp_main_loop(typename T::acc_t (&acc)[2][T::TM][T::TN], unsigned char* smem, int nk, int wm, int wn, bool trailing,
                                              int lane, CopyA copy_a, CopyB copy_b, bool colsum, float (&csum)[2][T::TM]) {

@@ -672,8 +672,8 @@ __global__ void __launch_bounds__(512, 2) gemm_pp_strided_kernel(GemmBf16Params 
 
 // y = x W^T on 64x64 tiles whose NW waves share the contraction instead of the tile: wave w computes the whole tile over the k-tiles
 // w, w + NW, ... of the workgroup's range, from a stage of LDS of its own, and the NW partial tiles are added at the end, in wave order.
-// Why: a 64x64 tile split 2x2 among four waves is bound by LDS (each wave reads 2 fragments per MFMA: 32 KB read and 16 KB written per k-tile,
-// 0.23 us) and by its barriers; here a k-tile is read once (16 KB, 4 fragments for 4 MFMAs) and no wave ever waits for another before the
+// Why: of a 64x64 tile split 2x2 among four waves, each reads 2 fragments per MFMA (32 KB read and 16 KB written per k-tile) and waits at a barrier
+// a k-tile (0.15 to 0.185 us on the ring, tile64_us); here a k-tile is read once (16 KB, 4 fragments for 4 MFMAs) and no wave ever waits for another before the
 // end.  A wave holds one k-tile in registers and one on its way to LDS, two where a CU has a single workgroup of 64x64 (the stages then leave no
 // room for another); the other waves of the CU hide the latency.  What a launch of few tiles spends beside that is its beginning and
 // end: 77 x 3072, K = 768 took 6.6 us, 1.0 until the copies were issued, 2.1 for three k-tiles, 2.5 to add up 32 rows at a time with every
@@ -1171,6 +1171,7 @@ static int choose_cfg(int M, int N, int K, bool a_mc, bool b_mc, bool dtl_ok, bo
     // one), both in us, fitted on MI355X over projections of 1024..32768 rows, 320..5120 columns, contractions of
     // 320..5120.  The alternating-group tiles hold one workgroup per CU; which of their widths wins is mostly a matter of how
     // full the last round is (8192 x 4608: 576 tiles of 256x256 are 2.25 rounds, 768 of 256x192 exactly 3 shorter ones).
+    // (The times are those of one k-tile a round of the loop; with two, up to 256 tiles of 256x128 take 0.61 us a k-tile.  The choice has not been fitted to that.)
     // The fused GeGLU forward is chosen among the tiles that have it (100 x 9216 on 128x128 tiles of eight waves instead of four 19.4 -> 15.7 us,
     // 2052 x 7680 on 256x128 ones instead of 256x256 62.0 -> 59.5, 4050 x 6144 the same way 58.6 -> 60).
     struct Cand { int idx, bm, bn; float fixed, per_kt; bool pp, need64; };
@@ -1844,8 +1845,8 @@ int launch_gemm(const GemmArgs& a, hipStream_t s) {
       case 14: return launch_dtl_layout<128, 128, 32, 4, 4, 2>(a, s);
       // small tiles: many workgroups for problems of a few hundred rows (contraction-contiguous operands only: the chunk
       // permutation of a contraction-strided tile needs at least 128 columns)
-      // Four buffers beside three of 64x64 are a k-tile more on its way, but two workgroups a CU instead of three (us, contraction 768 / 3072, 72 to 348
-      // tiles: 7.0 -> 6.2 / 20.1 -> 16.2, 22.9 -> 20.4; 540 tiles 9.3 -> 11.8).
+      // Four buffers of 64x64 take the ring's loop, three leave a CU room for a third workgroup (us, contraction 3072 / 4608, four and three: 192 tiles 11.2 / 15.8 and
+      // 15.2 / 28.8, 480 20.7 / 29.0 and 22.4 / 31.5, 540 28.7 / 40.9 and 27.4 / 38.5, 768 30.6 / 44.5 and 30.4 / 42.6, two full rounds of 512 41.4 / 59.8 and 46.2 / 66.7).
       case 15:
       case 16:
         if (a.a_mc || a.b_mc || a.K % 64) return set_error(DP_EUNSUPPORTED, "gemm: the forced 64-row configurations need contraction-contiguous operands and K % 64 == 0");

@@ -32,9 +32,9 @@ struct DwProblem {
 struct DwGroup { DwProblem p[DW_GROUP_MAX]; int n, total; };
 
 // What bounds it: instruction issue and LDS beside the matrix work, and the latency of the operands.  Without its copies the launch of a U-Net block
-// 8 x 1024 x 640 takes 118 us of what was 143, without its matrix work 139, with every copy an L2 hit 130.  Two things bring the latter about, 143 -> 130 us
-// (a block of 8 x 4096 x 320 181 -> 170; a DiT block of 32 x 256 x 1152 is not faster, its 4 x 256 one 1 %):
-// - an XCD's workgroups are tiles of one region of one problem, or of two, whatever the problems' number: 418 MB past the L2s for 254 MB of operands
+// 8 x 1024 x 640 takes 118 us of what was 143, without its matrix work 139, with every copy an L2 hit 130.  Two things bring the latter about, 143 -> 130 us by itself, 134
+// inside a step (a block of 8 x 4096 x 320 181 -> 170; a DiT block of 32 x 256 x 1152 is not faster, its 4 x 256 one 1 %):
+// - an XCD's workgroups are tiles of one region of one problem, or of two, whatever the problems' number: 434 MB read past the L2s for 254 MB of operands
 //   where a share of every problem to every XCD read 862;
 // - tiles that share operands run in step, so that each k-tile would come from memory for all of them at once.  Every other tile takes its k-tiles in
 //   pairs turned round: while half of the tiles have the first of a pair fetched, the other half has the second, and both find the other one in the L2.
@@ -61,9 +61,10 @@ __global__ void __launch_bounds__(512, 2) gemm_dw_group_kernel(const DwGroup grp
   const uint32_t k_end = (uint32_t)(kt0 + nk) * 128u;      // twice the contraction row behind this split's last one
   const rsrc_t ra = make_rsrc(p.A, min(p.a_bytes, k_end * (uint32_t)lda)), rb = make_rsrc(p.B, min(p.b_bytes, k_end * (uint32_t)ldb));
   const uint32_t step_a = 128u * (uint32_t)lda, step_b = 128u * (uint32_t)ldb;
-  // Columns past the edge are fetched from the last valid chunk (they only feed outputs that are never stored); rows past the end of the contraction
-  // lie outside the buffers and arrive as zeros.  Only the lanes' own offsets are checked against a buffer's size, so they take the steps along the
-  // contraction: one addition a copy, where a copy with the step in a scalar and the last k-tile's rows picked out took four vector instructions.
+  // Columns past the edge are fetched from the last valid chunk (they only feed outputs that are never stored); rows past the end of the contraction, in its last k-tile,
+  // lie outside the buffers and arrive as zeros.  The lanes' offsets take the steps along the contraction: one addition a copy, where a copy with the step in a scalar and
+  // the last k-tile's rows picked out took four vector instructions.  The loop also copies the two k-tiles behind the last one, rows up to K + 190: their offsets
+  // may go past 4 GiB and come round to rows that are there (the buffer's size keeps every read inside it), and nothing multiplies what they bring.
   uint32_t va[2][T::LA], vb0[T::LB0], vb1[T::LB1];
 #pragma unroll
   for (int h = 0; h < 2; ++h)
@@ -242,7 +243,7 @@ bool gemm_dw_group_supported(const GemmArgs& a) {
   if (a.dtype != BF16 || !a.a_mc || !a.b_mc || !a.out_f32 || a.ldo32 != a.N) return false;
   if (a.M % 8 || a.N % 8 || a.lda % 8 || a.ldb % 8 || a.M < 8 || a.N < 8 || a.K < 1 || a.lda < a.M || a.ldb < a.N) return false;
   if ((uintptr_t)a.A % 16 || (uintptr_t)a.B % 16 || (uintptr_t)a.out_f32 % 16 || (uintptr_t)a.colsum_out % 16) return false;
-  // 32-bit offsets, also of the k-tile past the last one
+  // 32-bit offsets of the rows that reach registers: the last k-tile's and, unused, the one's behind it
   return operand_extent_bytes(a.K + 128, a.M, a.lda) < 0xFFFFFFF0ull && operand_extent_bytes(a.K + 128, a.N, a.ldb) < 0xFFFFFFF0ull;
 }
 
