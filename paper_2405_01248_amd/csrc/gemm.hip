@@ -1049,8 +1049,9 @@ static float tile64_us(long tiles, int kt, int z) {
 }
 // The same where the tile decides in which order an output's products are added: the times of the loop before the ring.  With the ring's own times some products go
 // from waves that share the contraction to 64x64 tiles (616 x 1280, 616 x 2304, 308 x 3072, K = 768; 1232 x 1280, K = 1024), which moves everything behind them by
-// bf16 rounding and gains nothing (us, these times and the ring's: U-Net blocks 8 x 1024 x 640 1612 / 1610, 8 x 256 x 1280 1280 / 1279; text encoder of width 768 on 4 / 6 / 8 samples 466 /
-// 571 / 574 and 462 / 575 / 588, of width 512 on 6 / 8 384 / 439 and 377 / 424, of width 1024 on 4 / 6 / 8 564 / 644 / 772 and 561 / 640 / 774).
+// bf16 rounding.  What that order costs, us, these times and the ring's: U-Net blocks 8 x 1024 x 640 1612 / 1610, 8 x 256 x 1280 1280 / 1279; text encoder, weights from memory, of
+// width 768 on 4 / 6 / 8 samples 466 / 571 / 574 and 462 / 575 / 588, of width 512 on 6 / 8 384 / 439 and 377 / 424, of width 1024 on 4 / 6 / 8 564 / 644 / 772 and 561 / 640 / 774;
+// slice after slice of a batch, of width 768 on 4 / 8 414 / 510 and 397 / 508, of width 512 on 8 / 16 431 / 511 and 412 / 507, of width 1024 on 4 / 8 553 / 754 and 552 / 757.
 static float tile64_choice_us(long tiles, int kt, int z) {
   tiles *= z; kt = (kt + z - 1) / z;
   const float some = 4.0f + (float)kt * (tiles <= 128 ? 0.31f : 0.39f);
